@@ -1,16 +1,20 @@
-"""Thin ctypes binding of libwinograd_mi355x.so: argument marshalling only.
+"""Thin binding of libwinograd_mi355x.so: argument marshalling only.
 
 Every step of the convolution runs in the library's HIP kernels.  PyTorch is
-used for device memory (tensors' ``data_ptr()``) and for the current HIP
-stream, nothing else.  There is no CPU or PyTorch fallback: if the shared
-library is missing or a call fails, an exception is raised.
+used for device memory and for the current HIP stream, nothing else.  The calls
+of the inference path go through a small CPython extension (csrc/torch_binding.cpp:
+tensor checks, output allocation and launch in native code, about 4 us per call);
+what runs once per layer, the queries and the test hooks go through ctypes.
+There is no CPU or PyTorch fallback: if a shared library is missing or a call
+fails, an exception is raised.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch
 
-from .build import LIB_PATH
+from .build import EXT_PATH, LIB_PATH
 
 NCHW, NHWC = 0, 1
 LOSSLESS, SCALED = 0, 1
@@ -19,6 +23,7 @@ _MODES = {"lossless": LOSSLESS, "scaled": SCALED, LOSSLESS: LOSSLESS, SCALED: SC
 _LAYOUTS = {"nchw": NCHW, "nhwc": NHWC, NCHW: NCHW, NHWC: NHWC}
 
 _lib = None
+_ext = None
 
 
 class WinogradError(RuntimeError):
@@ -82,6 +87,27 @@ def load_library():
     return lib
 
 
+def _native():
+    """The CPython extension; raises if it has not been built."""
+    global _ext
+    if _ext is None:
+        if not os.path.exists(EXT_PATH):
+            raise ImportError("extension %s not found: run `python -c 'import __graft_entry__ as g; g.build()'`" % EXT_PATH)
+        load_library()
+        spec = importlib.util.spec_from_file_location("_winograd_torch", EXT_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _ext = module
+    return _ext
+
+
+def _done(result, where):
+    """What a native call returned: the output tensor, or a status to raise."""
+    if type(result) is int:
+        raise WinogradError(result, where)
+    return result
+
+
 EXPORTED_SYMBOLS = (
     "winograd_status_string", "winograd_num_activation_planes", "winograd_num_filter_planes",
     "winograd_debug_force_path", "winograd_debug_stream_workgroups", "winograd_debug_lossless_variant", "winograd_debug_scaled_variant", "winograd_debug_stream_variant", "winograd_conv2d_path", "winograd_debug_tile_decode",
@@ -139,11 +165,15 @@ def _out(out, shape, dtype, device, what="out"):
     return out
 
 
+def _wrong_kind(packed, cls, what):
+    raise TypeError("%s needs a %s, got %s" % (what, cls.__name__, type(packed).__name__))
+
+
 def _match(packed, cls, C, what):
     """The blob must be of the right algorithm and made for the activation's channel count: the kernels only
     find a mismatch on the device, where all they can do is leave the output untouched."""
     if type(packed) is not cls:
-        raise TypeError("%s needs a %s, got %s" % (what, cls.__name__, type(packed).__name__))
+        _wrong_kind(packed, cls, what)
     if packed.C != C:
         raise ValueError("%s: the filters were packed for C = %d, the activations have C = %d" % (what, packed.C, C))
 
@@ -245,15 +275,10 @@ def winograd_filter_transform_u8(w, zero_point, layout=NCHW, mode=LOSSLESS):
 
 def winograd_conv2d_u8(x, zero_point, packed, layout=NCHW, out=None):
     """x: uint8 activations in `layout`, the values being x - zero_point; packed: PackedFilterU8.  int32 output."""
-    layout = _LAYOUTS[layout]
-    _need(x, torch.uint8, "x")
-    N, C, H, W = _dims(x, layout)
-    _match(packed, PackedFilterU8, C, "winograd_conv2d_u8")
-    K = packed.K
-    out = _out(out, (N, K, H, W) if layout == NCHW else (N, H, W, K), torch.int32, x.device)
-    _check(load_library().winograd_conv2d_u8(_ptr(x), int(zero_point), _ptr(packed.blob), _ptr(out), N, C, H, W, K, layout,
-                                             packed.mode, _stream()), "winograd_conv2d_u8")
-    return out
+    if type(packed) is not PackedFilterU8:
+        _wrong_kind(packed, PackedFilterU8, "winograd_conv2d_u8")
+    return _done(_native().conv2d_bytes(x, int(zero_point), packed.blob, packed.K, packed.C, packed.mode, _LAYOUTS[layout], out, 0),
+                 "winograd_conv2d_u8")
 
 
 def winograd_conv2d_int8_act_scaled(x, packed, layout=NCHW, out=None, want_table=False):
@@ -261,17 +286,15 @@ def winograd_conv2d_int8_act_scaled(x, packed, layout=NCHW, out=None, want_table
     blob of signed int8 filters.  want_table: also return the int32 [T, 26, 4] = (n, p, r, q) table the kernel
     derived per tile and free entry."""
     layout = _LAYOUTS[layout]
-    _need(x, torch.int8, "x")
-    N, C, H, W = _dims(x, layout)
-    _match(packed, PackedFilter, C, "winograd_conv2d_int8_act_scaled")
-    K = packed.K
-    out = _out(out, (N, K, H, W) if layout == NCHW else (N, H, W, K), torch.int32, x.device)
+    if type(packed) is not PackedFilter:
+        _wrong_kind(packed, PackedFilter, "winograd_conv2d_int8_act_scaled")
     table = None
     if want_table:
+        _need(x, torch.int8, "x")
+        N, _, H, W = _dims(x, layout)
         table = torch.empty((N * ((H + 3) // 4) * ((W + 3) // 4), 26, 4), dtype=torch.int32, device=x.device)
-    _check(load_library().winograd_conv2d_int8_act_scaled(
-        _ptr(x), _ptr(packed.blob), _ptr(out), N, C, H, W, K, layout,
-        _ptr(table) if table is not None else ctypes.c_void_p(0), _stream()), "winograd_conv2d_int8_act_scaled")
+    out = _done(_native().conv2d_act_scaled(x, packed.blob, packed.K, packed.C, layout, out, table, 0),
+                "winograd_conv2d_int8_act_scaled")
     return (out, table) if want_table else out
 
 
@@ -281,19 +304,10 @@ def make_workspace(N, C, H, W, K, mode, device="cuda"):
 
 def winograd_conv2d_int8(x, packed, layout=NCHW, out=None, workspace=None):
     """x: int8 activations in `layout`; packed: PackedFilter.  Returns int32 output in `layout`."""
-    layout = _LAYOUTS[layout]
-    _need(x, torch.int8, "x")
-    N, C, H, W = _dims(x, layout)
-    _match(packed, PackedFilter, C, "winograd_conv2d_int8")
-    K = packed.K
-    if workspace is None:
-        workspace = make_workspace(N, C, H, W, K, packed.mode, x.device)
-    _need(workspace, torch.uint8, "workspace")
-    out = _out(out, (N, K, H, W) if layout == NCHW else (N, H, W, K), torch.int32, x.device)
-    _check(load_library().winograd_conv2d_int8(_ptr(x), _ptr(packed.blob), _ptr(out), N, C, H, W, K, layout,
-                                               packed.mode, _ptr(workspace), workspace.numel(), _stream()),
-           "winograd_conv2d_int8")
-    return out
+    if type(packed) is not PackedFilter:
+        _wrong_kind(packed, PackedFilter, "winograd_conv2d_int8")
+    return _done(_native().conv2d_int8(x, packed.blob, packed.K, packed.C, packed.mode, _LAYOUTS[layout], out, workspace),
+                 "winograd_conv2d_int8")
 
 
 def static_workspace_limit():
@@ -318,17 +332,10 @@ def winograd_conv2d_int8_static_workspace(x, packed, layout=NCHW, out=None):
 def winograd_conv2d_int8_requant(x, packed, shift, relu=True, pool=False, layout=NCHW, out=None):
     """Convolution with requantisation, ReLU and optional 2x2 max-pool applied before the store: int8 output in
     `layout` (H/2 x W/2 when pool), equal to winograd_conv2d_int8 followed by requant_relu_pool_int8."""
-    layout = _LAYOUTS[layout]
-    _need(x, torch.int8, "x")
-    N, C, H, W = _dims(x, layout)
-    _match(packed, PackedFilter, C, "winograd_conv2d_int8_requant")
-    K = packed.K
-    Ho, Wo = (H // 2, W // 2) if pool else (H, W)
-    out = _out(out, (N, K, Ho, Wo) if layout == NCHW else (N, Ho, Wo, K), torch.int8, x.device)
-    _check(load_library().winograd_conv2d_int8_requant(_ptr(x), _ptr(packed.blob), _ptr(out), N, C, H, W, K, layout,
-                                                       packed.mode, int(shift), int(relu), int(pool), _stream()),
-           "winograd_conv2d_int8_requant")
-    return out
+    if type(packed) is not PackedFilter:
+        _wrong_kind(packed, PackedFilter, "winograd_conv2d_int8_requant")
+    return _done(_native().conv2d_int8_requant(x, packed.blob, packed.K, packed.C, packed.mode, _LAYOUTS[layout], out, int(shift),
+                                               bool(relu), bool(pool), 0), "winograd_conv2d_int8_requant")
 
 
 STAGE_NAMES = ("input_transform", "contraction", "output_transform", "fused_conv")
@@ -353,28 +360,11 @@ def enqueue_stage(x, packed, stage, iters, layout=NCHW, out=None, workspace=None
 
 
 def direct_conv2d_int8(x, w, layout=NCHW, out=None):
-    layout = _LAYOUTS[layout]
-    _need(x, torch.int8, "x")
-    _need(w, torch.int8, "w")
-    N, C, H, W = _dims(x, layout)
-    K = w.shape[0]
-    if tuple(w.shape) != ((K, C, 3, 3) if layout == NCHW else (K, 3, 3, C)):
-        raise ValueError("w has shape %s, which does not fit activations with C = %d" % (tuple(w.shape), C))
-    out = _out(out, (N, K, H, W) if layout == NCHW else (N, H, W, K), torch.int32, x.device)
-    _check(load_library().direct_conv2d_int8(_ptr(x), _ptr(w), _ptr(out), N, C, H, W, K, layout, _stream()),
-           "direct_conv2d_int8")
-    return out
+    return _done(_native().direct_conv2d(x, w, _LAYOUTS[layout], out), "direct_conv2d_int8")
 
 
 def requant_relu_pool_int8(y, shift, relu=True, pool=False, layout=NCHW, out=None):
-    layout = _LAYOUTS[layout]
-    _need(y, torch.int32, "y")
-    N, K, H, W = _dims(y, layout)
-    Ho, Wo = (H // 2, W // 2) if pool else (H, W)
-    out = _out(out, (N, K, Ho, Wo) if layout == NCHW else (N, Ho, Wo, K), torch.int8, y.device)
-    _check(load_library().requant_relu_pool_int8(_ptr(y), _ptr(out), N, K, H, W, layout, int(shift), int(relu),
-                                                 int(pool), _stream()), "requant_relu_pool_int8")
-    return out
+    return _done(_native().requant_relu_pool(y, _LAYOUTS[layout], out, int(shift), bool(relu), bool(pool)), "requant_relu_pool_int8")
 
 
 def debug_input_operands(x, layout=NCHW, mode=LOSSLESS):
@@ -447,51 +437,34 @@ def f2x2_filter_transform(w, layout=NCHW, mode=LOSSLESS, zero_point=None):
 
 def f2x2_conv2d_int8(x, packed, layout=NCHW, out=None, zero_point=None):
     """x: int8 activations, or uint8 activations with their zero point (values x - zero_point)."""
-    layout = _LAYOUTS[layout]
-    _need(x, torch.int8 if zero_point is None else torch.uint8, "x")
-    N, C, H, W = _dims(x, layout)
-    _match(packed, F2x2PackedFilter, C, "f2x2_conv2d_int8")
-    K = packed.K
-    out = _out(out, (N, K, H, W) if layout == NCHW else (N, H, W, K), torch.int32, x.device)
-    if zero_point is None:
-        _check(load_library().winograd_f2x2_conv2d_int8(_ptr(x), _ptr(packed.blob), _ptr(out), N, C, H, W, K, layout,
-                                                        packed.mode, _stream()), "winograd_f2x2_conv2d_int8")
-    else:
-        _check(load_library().winograd_f2x2_conv2d_u8(_ptr(x), int(zero_point), _ptr(packed.blob), _ptr(out), N, C, H, W, K,
-                                                      layout, packed.mode, _stream()), "winograd_f2x2_conv2d_u8")
-    return out
+    if type(packed) is not F2x2PackedFilter:
+        _wrong_kind(packed, F2x2PackedFilter, "f2x2_conv2d_int8")
+    return _done(_native().conv2d_bytes(x, zero_point if zero_point is None else int(zero_point), packed.blob, packed.K, packed.C,
+                                        packed.mode, _LAYOUTS[layout], out, 1),
+                 "winograd_f2x2_conv2d_int8" if zero_point is None else "winograd_f2x2_conv2d_u8")
 
 
 def f2x2_conv2d_int8_requant(x, packed, shift, relu=True, pool=False, layout=NCHW, out=None):
     """F(2x2,3x3) convolution with requantisation, ReLU and optional 2x2 max-pool before the store: int8 output."""
-    layout = _LAYOUTS[layout]
-    _need(x, torch.int8, "x")
-    N, C, H, W = _dims(x, layout)
-    _match(packed, F2x2PackedFilter, C, "f2x2_conv2d_int8_requant")
-    K = packed.K
-    Ho, Wo = (H // 2, W // 2) if pool else (H, W)
-    out = _out(out, (N, K, Ho, Wo) if layout == NCHW else (N, Ho, Wo, K), torch.int8, x.device)
-    _check(load_library().winograd_f2x2_conv2d_int8_requant(_ptr(x), _ptr(packed.blob), _ptr(out), N, C, H, W, K, layout,
-                                                            packed.mode, int(shift), int(bool(relu)), int(bool(pool)),
-                                                            _stream()), "winograd_f2x2_conv2d_int8_requant")
-    return out
+    if type(packed) is not F2x2PackedFilter:
+        _wrong_kind(packed, F2x2PackedFilter, "f2x2_conv2d_int8_requant")
+    return _done(_native().conv2d_int8_requant(x, packed.blob, packed.K, packed.C, packed.mode, _LAYOUTS[layout], out, int(shift),
+                                               bool(relu), bool(pool), 1), "winograd_f2x2_conv2d_int8_requant")
 
 
 def f2x2_conv2d_int8_act_scaled(x, packed, layout=NCHW, out=None, want_table=False):
     """F(2x2,3x3) with the activations of every tile scaled into +-127 as well; packed: a SCALED blob of signed int8
     filters.  want_table: also return the int32 [T, 16, 4] = (n, p, r, q) table the kernel derived per tile."""
     layout = _LAYOUTS[layout]
-    _need(x, torch.int8, "x")
-    N, C, H, W = _dims(x, layout)
-    _match(packed, F2x2PackedFilter, C, "f2x2_conv2d_int8_act_scaled")
-    K = packed.K
-    out = _out(out, (N, K, H, W) if layout == NCHW else (N, H, W, K), torch.int32, x.device)
+    if type(packed) is not F2x2PackedFilter:
+        _wrong_kind(packed, F2x2PackedFilter, "f2x2_conv2d_int8_act_scaled")
     table = None
     if want_table:
+        _need(x, torch.int8, "x")
+        N, _, H, W = _dims(x, layout)
         table = torch.empty((N * ((H + 1) // 2) * ((W + 1) // 2), 16, 4), dtype=torch.int32, device=x.device)
-    _check(load_library().winograd_f2x2_conv2d_int8_act_scaled(
-        _ptr(x), _ptr(packed.blob), _ptr(out), N, C, H, W, K, layout,
-        _ptr(table) if table is not None else ctypes.c_void_p(0), _stream()), "winograd_f2x2_conv2d_int8_act_scaled")
+    out = _done(_native().conv2d_act_scaled(x, packed.blob, packed.K, packed.C, layout, out, table, 1),
+                "winograd_f2x2_conv2d_int8_act_scaled")
     return (out, table) if want_table else out
 
 

@@ -3,6 +3,7 @@
 #include <atomic>
 
 #include "api_checks.h"
+#include "host_api.h"
 
 using namespace wg;
 
@@ -349,3 +350,16 @@ int winograd_debug_contraction(const int8_t* x_dev, const void* packed_dev, int3
 }
 
 }  // extern "C"
+
+namespace wg {
+
+int conv2d_int8_single_kernel(const int8_t* x, const void* packed, int32_t* y, int N, int C, int H, int W, int K, int layout,
+                              int mode, void* stream) {
+    if (!x || !packed || !y || !valid_layout(layout) || !valid_mode(mode)) return WG_EINVAL;
+    if (int st = check_shape(N, C, H, W, K)) return st;
+    if (!aligned(x, 4) || !aligned(y, 4) || !aligned(packed, 256)) return WG_EINVAL;
+    return status_of(launch_fused_conv(x, packed, y, make_problem(N, C, H, W, K), layout, mode, no_int8_epilogue(),
+                                       static_cast<hipStream_t>(stream)));
+}
+
+}  // namespace wg
