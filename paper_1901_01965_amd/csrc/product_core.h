@@ -1,0 +1,824 @@
+// Pieces shared by the single-kernel convolution variants: the per-entry matrix-core programs of the Winograd-domain
+// products, the waves' share of them, the output staging and the stores.
+#pragma once
+#include <atomic>
+
+#include "kernel_common.h"
+
+namespace wg {
+namespace {
+
+constexpr int kFusedTiles = kTileBlock;   // tiles per workgroup (rows of the 16x16x64 matrix-core product)
+constexpr int kFusedFilters = 32;   // filters per workgroup: two 16-wide column blocks
+constexpr int kFusedPlanes = 72;    // two-limb activation planes (kSplitTwoLimb)
+constexpr int kLdsBytes = kFusedPlanes * kPlaneBytes;
+constexpr int kParkBytes = 4 * 16 * 64 * 16;         // four waves x 16 outputs x 64 lanes x 4 registers
+// How the activation patch reaches the transform threads (chosen on the host):
+//   kLoadBytes:  one byte per load, any layout and channel count;
+//   kLoadDwords: channels-last, C a multiple of 4: one 4-byte load per pixel and thread;
+//   kLoadDirect: channels-last, C a multiple of 16, 16-byte aligned input: 16-byte pieces travel
+//                from global memory straight into LDS (nine instructions per wave instead of
+//                thirty-six), and the threads pick their four channels from there.
+constexpr int kLoadBytes = 0, kLoadDwords = 1, kLoadDirect = 2;
+constexpr int kRawWaveBytes = 4 * 36 * kCBlock;      // raw patches of a wave's four tiles: 36 pixels x 64 channels
+constexpr int kRawBytes = 4 * kRawWaveBytes;
+static_assert(kParkBytes <= kLdsBytes, "output staging reuses the operand planes' LDS");
+
+// ---- per-entry programs ----------------------------------------------------------------
+// An entry's product uses a few activation fragments (from LDS) and filter fragments (from
+// the packed blob) and a short list of matrix-core instructions into a few accumulators.
+//   lossless, real:    A = (h, l)  B = (h, l)          acc = (hh, hl+lh, ll)
+//   lossless, complex: A = (Re h, Re l, Im h, Im l)  B = (Wr h, Wr l, Wi h, Wi l)
+//                      acc 0-2: Dr*Wr, 3-5: Di*Wi, 6-8: Dr*Wi + Di*Wr, each as (hh, mid, ll)
+//   scaled, real:      A = (h, l)  B = (W)             acc = (h, l)
+//   scaled, complex:   B = (Wr, Wi, -Wi)               acc = (Re h, Re l, Im h, Im l)
+//   scaled, complex, without the -Wi plane (kScaledTwoPlanes as MODE of the helpers below: a
+//   third less filter traffic per complex entry for two subtractions per register):
+//                      B = (Wr, Wi)                    acc = (Dr*Wr h, l, Im h, Im l, Di*Wi h, l)
+constexpr int kScaledTwoPlanes = 2;
+static_assert(kScaledTwoPlanes != WG_LOSSLESS && kScaledTwoPlanes != WG_SCALED, "a value of its own");
+struct Op {
+    int a, b, acc;
+    bool init;   // first instruction into this accumulator (starts from zero)
+};
+constexpr bool is_real(int entry) { return entry < kRealEntries; }
+template <int MODE> constexpr int num_a(int entry) { return is_real(entry) ? 2 : 4; }
+template <int MODE> constexpr int num_b(int entry) {
+    return MODE == WG_LOSSLESS ? (is_real(entry) ? 2 : 4) : (is_real(entry) ? 1 : (MODE == kScaledTwoPlanes ? 2 : 3));
+}
+template <int MODE> constexpr int num_ops(int entry) {
+    return MODE == WG_LOSSLESS ? (is_real(entry) ? 4 : 16) : (is_real(entry) ? 2 : 8);
+}
+template <int MODE> constexpr int a_plane(int entry, int i) {
+    return is_real(entry) ? 2 * entry + i : 32 + 4 * (entry - kRealEntries) + i;
+}
+template <int MODE> constexpr int b_plane(int entry, int i) {
+    if (MODE == WG_LOSSLESS) {   // blob planes 3*value + {0: high limb, 1: low limb}
+        if (is_real(entry)) return 3 * entry + i;
+        const int value = 16 + 3 * (entry - kRealEntries) + (i >> 1);   // Re, then Im
+        return 3 * value + (i & 1);
+    }
+    return is_real(entry) ? entry : 16 + 3 * (entry - kRealEntries) + i;
+}
+template <int MODE> constexpr Op entry_op(int entry, int i) {
+    constexpr Op lossless_real[4] = {{0, 0, 0, true}, {0, 1, 1, true}, {1, 1, 2, true}, {1, 0, 1, false}};
+    // dependent instructions into one accumulator are kept at least three apart
+    constexpr Op lossless_complex[16] = {
+        {0, 0, 0, true}, {0, 1, 1, true}, {1, 1, 2, true},    // Dr*Wr: hh, mid, ll
+        {2, 2, 3, true}, {2, 3, 4, true}, {3, 3, 5, true},    // Di*Wi
+        {0, 2, 6, true}, {0, 3, 7, true}, {1, 3, 8, true},    // Dr*Wi
+        {1, 2, 7, false}, {1, 0, 1, false}, {3, 2, 4, false},
+        {2, 1, 7, false}, {2, 0, 6, false}, {3, 1, 8, false}, {3, 0, 7, false}};
+    constexpr Op scaled_real[2] = {{0, 0, 0, true}, {1, 0, 1, true}};
+    constexpr Op scaled_complex[8] = {{0, 0, 0, true}, {1, 0, 1, true}, {0, 1, 2, true}, {1, 1, 3, true},
+                                      {2, 2, 0, false}, {3, 2, 1, false}, {2, 0, 2, false}, {3, 0, 3, false}};
+    constexpr Op two_planes_complex[8] = {{0, 0, 0, true}, {1, 0, 1, true}, {0, 1, 2, true}, {1, 1, 3, true},
+                                          {2, 1, 4, true}, {3, 1, 5, true}, {2, 0, 2, false}, {3, 0, 3, false}};
+    if (MODE == WG_LOSSLESS) return is_real(entry) ? lossless_real[i] : lossless_complex[i];
+    if (MODE == kScaledTwoPlanes) return is_real(entry) ? scaled_real[i] : two_planes_complex[i];
+    return is_real(entry) ? scaled_real[i] : scaled_complex[i];
+}
+
+// ---- which entries a wave owns, in order ---------------------------------------------------
+// Half 0 owns rows 0,1,2 of M, half 1 rows 5 and 3; "half" 2 is all five rows, for a wave that
+// owns every entry.  A real row RI (rows 0,1,2,5) holds entries 4RI..4RI+3 and the complex
+// entry 16+RI; the complex row holds entries 20..25.
+constexpr int kAllRows = 2;
+constexpr int row_entries(int row) { return row < 4 ? 5 : 6; }
+constexpr int row_entry(int row, int pos) {
+    return row < 4 ? (pos < 4 ? 4 * row + pos : kRealEntries + row) : kRealEntries + 4 + pos;
+}
+constexpr int half_rows(int half) { return half == 0 ? 3 : (half == 1 ? 2 : 5); }
+constexpr int half_row(int half, int i) { return half == 1 ? (i == 0 ? 3 : 4) : i; }
+constexpr int half_entries(int half) { return half == 0 ? 15 : (half == 1 ? 11 : 26); }
+struct Slot {
+    int entry, row, pos;
+    bool last_in_row;
+};
+constexpr Slot half_slot(int half, int i) {
+    int n = 0;
+    for (int r = 0; r < half_rows(half); ++r) {
+        const int row = half_row(half, r);
+        if (i < n + row_entries(row))
+            return Slot{row_entry(row, i - n), row, i - n, i - n == row_entries(row) - 1};
+        n += row_entries(row);
+    }
+    return Slot{0, 0, 0, false};
+}
+// index of the first filter fragment of slot i in the wave's fragment stream
+template <int MODE> constexpr int b_start(int half, int i) {
+    int n = 0;
+    for (int s = 0; s < i; ++s) n += num_b<MODE>(half_slot(half, s).entry);
+    return n;
+}
+// the slot that filter fragment f of the stream belongs to
+template <int MODE> constexpr int b_slot_of(int half, int f) {
+    int s = 0;
+    while (b_start<MODE>(half, s + 1) <= f) ++s;
+    return s;
+}
+
+// Direct global -> LDS transfer of the raw 6x6 patches of a wave's four tiles (one 64-channel
+// block).  Instruction i (0..8) moves pixels 4i..4i+3 of the patch (pixel = 6 a + b): lane l
+// carries 16 channels (piece l % 4) of tile (l % 16) / 4 at pixel 4i + l / 16, and the hardware
+// puts lane l's piece at (wave-uniform destination) + 16 l.  The raw area of a wave is therefore
+// [pixel][tile][64 channels], and transform thread (tile, channel quad) = lane reads its pixel
+// p at p * 256 + 4 * lane: a wave reads 256 contiguous bytes.
+struct DirectPatch {
+    uint32_t pixel_off[9];   // byte offset of this lane's pixel (channel 0) for each instruction
+    // (n, ty, tx): the tile this lane moves pieces of.  With j = lane / 16, instruction i covers
+    // pixel 4i + j = 6a + b of the patch: a = {0,0,1,2,2,3,4,4,5}[i] + (i % 3 == 1 and j >= 2),
+    // and b takes only three values per lane: j (i % 3 == 0), (j + 4) % 6 (i % 3 == 1) and j + 2
+    // (i % 3 == 2).  Row terms follow each other by one clamped row step, so the whole table
+    // costs four multiplications.
+    __device__ inline void init(const Problem& p, int n, int ty, int tx, int lane) {
+        const int h0 = 4 * ty - 1, w0 = 4 * tx - 1, j = lane >> 4;
+        const uint32_t row_step = (uint32_t)(p.W * p.C);
+        uint32_t row_term[6];
+        row_term[0] = (uint32_t)(n * p.H + max(h0, 0)) * row_step;
+#pragma unroll
+        for (int a = 1; a < 6; ++a)   // rows clamp to [0, H-1]: the step is taken only inside the image
+            row_term[a] = row_term[a - 1] + ((unsigned)(h0 + a - 1) < (unsigned)(p.H - 1) ? row_step : 0u);
+        const int b1 = j < 2 ? j + 4 : j - 2;
+        const uint32_t col_term[3] = {(uint32_t)(min(max(w0 + j, 0), p.W - 1) * p.C),
+                                      (uint32_t)(min(max(w0 + b1, 0), p.W - 1) * p.C),
+                                      (uint32_t)(min(max(w0 + j + 2, 0), p.W - 1) * p.C)};
+        constexpr int a_base[9] = {0, 0, 1, 2, 2, 3, 4, 4, 5};
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            uint32_t row = row_term[a_base[i]];
+            if (i % 3 == 1) row = j >= 2 ? row_term[a_base[i] + 1] : row;
+            pixel_off[i] = row + col_term[i % 3];
+        }
+    }
+    // Pieces beyond C (the last channel block of a C that is not a multiple of 64) re-read
+    // channel 0; bias_patch() discards them.
+    __device__ inline void issue(const int8_t* __restrict__ x, const Problem& p, int cb, int lane,
+                                 int8_t* raw_wave) const {
+        const int c = cb * kCBlock + (lane & 3) * 16;
+        const int8_t* src = x + (c < p.C ? c : 0);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) __builtin_amdgcn_global_load_lds(src + pixel_off[i], raw_wave + i * 1024, 16, 0, 0);
+    }
+    __device__ inline static void read(const int8_t* raw_wave, int lane, uint32_t u[6][6]) {
+#pragma unroll
+        for (int a = 0; a < 6; ++a)
+#pragma unroll
+            for (int b = 0; b < 6; ++b)
+                u[a][b] = *reinterpret_cast<const uint32_t*>(raw_wave + (6 * a + b) * 256 + 4 * lane);
+    }
+};
+
+struct LaneContext {
+    const int8_t* a_lds;        // this lane's 16-byte slot in plane 0
+    const int8_t* b_glob;       // this lane's 16 bytes of filter plane 0, current channel block
+    const ScaleEntry* table_k;  // scaling table row of this lane's filter (scaled mode)
+    const uint32_t* parked;     // role-specialised kernels, scaled mode: see park_scales
+};
+
+constexpr int kFilterPrefetch = 16;   // filter fragments in flight per wave (covers L2 latency)
+
+// value = 4096 hh + 64 mid + ll, modulo 2^32, as two shift-and-add instructions per register.
+// The empty statement only pins the intermediate value, so that the compiler does not rewrite
+// the expression as two shifts and a three-operand add.
+__device__ inline v4i join_limbs(v4i hh, v4i mid, v4i ll) {
+    v4i out;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        int t = (hh[q] << 6) + mid[q];
+        asm("" : "+v"(t));
+        out[q] = (t << 6) + ll[q];
+    }
+    return out;
+}
+
+template <int MODE, int HALF>
+struct ProductPhase {
+    static constexpr int NE = half_entries(HALF);
+    static constexpr int NB = b_start<MODE>(HALF, NE);
+    static constexpr int NPRE = NB < kFilterPrefetch ? NB : kFilterPrefetch;
+    v4i bring[kFilterPrefetch];
+
+    // F-th filter fragment of this wave's stream.  A workgroup that covers more than 32 filters
+    // goes through its entries once per 32 (pass F / NB); the wave's 16-filter fragment of the
+    // next pass lies two fragments (2 * planes KB) further on in the blob.
+    template <int F>
+    __device__ inline static v4i load_b(const LaneContext& cx) {
+        constexpr int pass = F / NB, f = F % NB;
+        constexpr int slot = b_slot_of<MODE>(HALF, f);
+        constexpr int plane = b_plane<MODE>(half_slot(HALF, slot).entry, f - b_start<MODE>(HALF, slot));
+        constexpr int planes = MODE == WG_LOSSLESS ? 138 : 46;
+        return *reinterpret_cast<const v4i*>(cx.b_glob + (pass * 2 * planes + plane) * kFilterFragBytes);
+    }
+    template <int SLOT, int I>
+    __device__ inline static v4i load_a(const LaneContext& cx) {
+        constexpr int plane = a_plane<MODE>(half_slot(HALF, SLOT).entry, I);
+        return *reinterpret_cast<const v4i*>(cx.a_lds + plane * kPlaneBytes);
+    }
+
+    // Filter fragments do not depend on the transform phase: start them before it.
+    __device__ inline void prefetch(const LaneContext& cx) {
+        static_for<NPRE>([&](auto I) { bring[I] = load_b<I>(cx); });
+    }
+    static_assert(NB >= kFilterPrefetch || MODE != WG_LOSSLESS, "the ring is full from the first pass on");
+
+    // One 64-channel block of this wave's rows.  Software pipeline over entries: while entry i's
+    // matrix-core instructions run, entry i+1's activation fragments come from LDS, the filter
+    // ring is refilled sixteen fragments ahead, and entry i-1's accumulators are joined,
+    // (un)scaled and reduced into the outputs.
+    // PASS of NPASS: which 32 of the workgroup's filters (see load_b).
+    template <int PASS = 0, int NPASS = 1>
+    __device__ inline void run(const LaneContext& cx, v4i (&Y)[16]) {
+        constexpr int F0 = PASS * NB, FEND = NPASS * NB;   // this pass's place in the fragment stream
+        v4i afr[2][4], acc[2][9], er[6], ei[6];
+        static_for<num_a<MODE>(half_slot(HALF, 0).entry)>([&](auto I) { afr[0][I] = load_a<0, I>(cx); });
+        static_for<NE + 1>([&](auto S) {
+            constexpr int s = S;
+            if constexpr (s < NE) {
+                constexpr int entry = half_slot(HALF, s).entry;
+                constexpr int b0 = b_start<MODE>(HALF, s);
+                if constexpr (s + 1 < NE)
+                    static_for<num_a<MODE>(half_slot(HALF, s + 1).entry)>(
+                        [&](auto I) { afr[(s + 1) & 1][I] = load_a<s + 1, I>(cx); });
+                static_for<num_ops<MODE>(entry)>([&](auto I) {
+                    constexpr Op op = entry_op<MODE>(entry, I);
+                    constexpr v4i zero = {0, 0, 0, 0};
+                    acc[s & 1][op.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                        afr[s & 1][op.a], bring[(F0 + b0 + op.b) % kFilterPrefetch],
+                        op.init ? zero : acc[s & 1][op.acc], 0, 0, 0);
+                });
+                static_for<num_b<MODE>(entry)>([&](auto I) {
+                    if constexpr (F0 + b0 + I + kFilterPrefetch < FEND)
+                        bring[(F0 + b0 + I) % kFilterPrefetch] = load_b<F0 + b0 + I + kFilterPrefetch>(cx);
+                });
+            }
+            if constexpr (s > 0) {
+                constexpr Slot sl = half_slot(HALF, s - 1);
+                const v4i(&a)[9] = acc[(s - 1) & 1];
+                v4i re, im = {0, 0, 0, 0};
+                if constexpr (MODE == WG_LOSSLESS) {
+                    if constexpr (is_real(sl.entry)) {
+                        re = join_limbs(a[0], a[1], a[2]);
+                    } else {   // Re = Dr Wr - Di Wi,  Im = Dr Wi + Di Wr
+                        re = join_limbs(a[0] - a[3], a[1] - a[4], a[2] - a[5]);
+                        im = join_limbs(a[6], a[7], a[8]);
+                    }
+                } else {
+                    re = (a[0] << kByteLimbShift) + a[1];
+                    if constexpr (!is_real(sl.entry)) im = (a[2] << kByteLimbShift) + a[3];
+                    const ReverseScale unscale(cx.table_k[PASS * kFusedFilters * kEntries + sl.entry]);   // Section 4.2
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        re[q] = unscale(re[q]);
+                        if constexpr (!is_real(sl.entry)) im[q] = unscale(im[q]);
+                    }
+                }
+                er[sl.pos] = re;
+                ei[sl.pos] = im;
+                if constexpr (sl.last_in_row) finish_row<sl.row>(er, ei, Y);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+};
+
+// Role-specialised kernels, scaled mode: the reverse-scaling factors (r, q) of the entries a
+// product wave owns, read once at the start of the kernel (while the wave would only wait for
+// the first operand planes) and parked in LDS as q << 8 | r, [slot][filter of the wave], so that
+// the reverse scaling after the last channel block does not begin with a trip to L2.  Lane
+// group g = lane / 16 reads slots g, 4 + g, 8 + g, 12 + g of filter lane % 16: ask() issues the
+// four loads, park() writes what they brought, and a caller puts its first filter prefetch
+// between the two so that one wait covers both.  Each wave writes and later reads its own 1 KB
+// (16 slots x 16 filters; 2 KB for a wave that owns all 26 entries), in program order: no barrier.
+constexpr int kParkedScaleBytes = 16 * 16 * 4;
+template <int HALF>
+struct ParkedScales {
+    static constexpr int NE = ProductPhase<WG_SCALED, HALF>::NE;
+    static constexpr int kRounds = (NE + 3) / 4;   // a wave that owns every entry: seven loads per lane, 2 KB
+    static constexpr int kBytes = kRounds * 4 * 16 * 4;
+    int2 rq[kRounds];
+    __device__ inline void ask(const LaneContext& cx, int lane) {
+        const int g = lane >> 4;
+        static_for<kRounds>([&](auto J) {
+            int entry = half_slot(HALF, 4 * J).entry;   // slot 4 J + g, clamped to the last slot
+            static_for<3>([&](auto G) {
+                constexpr int slot = 4 * J + G + 1 < NE ? 4 * J + G + 1 : NE - 1;
+                if (g > G) entry = half_slot(HALF, slot).entry;
+            });
+            rq[J] = *reinterpret_cast<const int2*>(&cx.table_k[entry].r);
+        });
+    }
+    __device__ inline void park(LaneContext& cx, int8_t* area, int lane) {
+        uint32_t* const base = reinterpret_cast<uint32_t*>(area) + (lane & 15);
+        const int g = lane >> 4;
+        static_for<kRounds>([&](auto J) {
+            if (4 * J + g < NE) base[(4 * J + g) * 16] = ((uint32_t)rq[J].y << 8) | (uint32_t)rq[J].x;   // r <= 255, q <= 7
+        });
+        cx.parked = base;
+    }
+};
+template <int SLOT>
+__device__ inline ReverseScale parked_scale(const LaneContext& cx) {
+    const uint32_t v = cx.parked[SLOT * 16];
+    return ReverseScale((int)(v & 0xffu), (int)(v >> 8));
+}
+
+// Scaled mode over several channel blocks: the products of every entry a wave owns accumulate
+// in registers across the blocks (run, once per block), and the reverse scaling and the output
+// transform are applied to the finished channel sums (finish, once).
+template <int HALF>
+struct ScaledSums {
+    static constexpr int MODE = WG_SCALED;
+    using Phase = ProductPhase<MODE, HALF>;
+    static constexpr int NE = Phase::NE, NB = Phase::NB;
+    static constexpr int sum_start(int slot) {   // first sum of a slot: one per real entry, Re and Im per complex
+        int n = 0;
+        for (int s = 0; s < slot; ++s) n += is_real(half_slot(HALF, s).entry) ? 1 : 2;
+        return n;
+    }
+    static constexpr int kSums = sum_start(NE);
+
+    // One channel block: each entry's limb products are formed from zero, and its value
+    // 256 * high + low (byte limbs) joins the entry's running sum one entry later.
+    template <int PASS = 0, int NPASS = 1>
+    __device__ inline static void run(const LaneContext& cx, v4i (&bring)[kFilterPrefetch], v4i (&sums)[kSums]) {
+        constexpr int F0 = PASS * NB, FEND = NPASS * NB;   // this pass's place in the fragment stream
+        v4i afr[2][4], acc[2][4];
+        static_for<num_a<MODE>(half_slot(HALF, 0).entry)>([&](auto I) { afr[0][I] = Phase::template load_a<0, I>(cx); });
+        static_for<NE + 1>([&](auto S) {
+            constexpr int s = S;
+            if constexpr (s < NE) {
+                constexpr int entry = half_slot(HALF, s).entry;
+                constexpr int b0 = b_start<MODE>(HALF, s);
+                if constexpr (s + 1 < NE)
+                    static_for<num_a<MODE>(half_slot(HALF, s + 1).entry)>(
+                        [&](auto I) { afr[(s + 1) & 1][I] = Phase::template load_a<s + 1, I>(cx); });
+                static_for<num_ops<MODE>(entry)>([&](auto I) {
+                    constexpr Op op = entry_op<MODE>(entry, I);
+                    constexpr v4i zero = {0, 0, 0, 0};
+                    acc[s & 1][op.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                        afr[s & 1][op.a], bring[(F0 + b0 + op.b) % kFilterPrefetch],
+                        op.init ? zero : acc[s & 1][op.acc], 0, 0, 0);
+                });
+                static_for<num_b<MODE>(entry)>([&](auto I) {
+                    if constexpr (F0 + b0 + I + kFilterPrefetch < FEND)
+                        bring[(F0 + b0 + I) % kFilterPrefetch] = Phase::template load_b<F0 + b0 + I + kFilterPrefetch>(cx);
+                });
+            }
+            if constexpr (s > 0) {
+                constexpr int v = sum_start(s - 1);
+                const v4i(&a)[4] = acc[(s - 1) & 1];
+                sums[v] += (a[0] << kByteLimbShift) + a[1];
+                if constexpr (!is_real(half_slot(HALF, s - 1).entry)) sums[v + 1] += (a[2] << kByteLimbShift) + a[3];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+
+    // After the last channel block: reverse scaling of the finished sums and the output transform.
+    template <int PASS = 0, bool PARKED = false>
+    __device__ inline static void finish(const LaneContext& cx, const v4i (&sums)[kSums], v4i (&Y)[16]) {
+        v4i er[6], ei[6];
+        static_for<NE>([&](auto S) {
+            constexpr Slot sl = half_slot(HALF, S);
+            constexpr int v = sum_start(S);
+            v4i re = sums[v], im = {0, 0, 0, 0};
+            if constexpr (!is_real(sl.entry)) im = sums[v + 1];
+            const ReverseScale unscale = PARKED ? parked_scale<S>(cx)   // Section 4.2
+                                                : ReverseScale(cx.table_k[PASS * kFusedFilters * kEntries + sl.entry]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                re[q] = unscale(re[q]);
+                if constexpr (!is_real(sl.entry)) im[q] = unscale(im[q]);
+            }
+            er[sl.pos] = re;
+            ei[sl.pos] = im;
+            if constexpr (sl.last_in_row) {
+                finish_row<sl.row>(er, ei, Y);
+                // all rows in one wave: row by row, so that a row's sums are dead before the next row's work begins
+                if constexpr (HALF == kAllRows) __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+    }
+};
+constexpr int kChannelSums = 18;
+static_assert(ScaledSums<0>::kSums == kChannelSums && ScaledSums<1>::kSums == kChannelSums, "both halves keep 18 sums");
+
+// Who a thread is when the four product waves store their outputs, and where its tile lies.
+struct StoreContext {
+    int8_t* lds;
+    int tid, lane, wave, half, kblock;          // within the four waves that hold the outputs
+    int my_n, my_row, my_col, my_origin;        // of tile (lane & 15): image, first output row and column, offset in y (-1: none)
+    int rnd;                                    // rounding added before the final >> 4
+    int32_t* y;
+};
+
+// Adds the two row halves and stores the 16 tiles x 32 filters (from kbase) whose partial outputs
+// the four waves hold in Yp.  All four waves call it together (it contains one barrier).
+// PART 1 / PART 2 (channels-last with K % 4 = 0 only): just the staging of Yp into LDS / just
+// the adding and storing of what was staged, for callers that put their own barrier between
+// the two and may run them on different waves.  PART 3: PART 2 for a caller whose waves own every
+// entry and staged one finished copy (in the place of half 0): nothing is added.
+template <int LAYOUT, bool Q8, int PART = 0>
+__device__ __forceinline__ void store_block(const StoreContext& sc, const Problem& p, const Int8Epilogue& q8,
+                                            const v4i (&Yp)[16], int kbase) {
+    int8_t* const lds = sc.lds;
+    const int tid = sc.tid, lane = sc.lane, wave = sc.wave, half = sc.half, kblock = sc.kblock;
+    const int my_n = sc.my_n, my_row = sc.my_row, my_col = sc.my_col, my_origin = sc.my_origin, rnd = sc.rnd;
+    int32_t* const y = sc.y;
+    int* parki = reinterpret_cast<int*>(lds);
+    (void)wave; (void)my_n;
+    if (LAYOUT == WG_NHWC && (p.K & 3) == 0) {
+        // Channels-last with K a multiple of four: outputs are staged filter-fastest,
+        // stage[half][output 4i+j][tile][36] (32 filters, rows padded to 36 dwords so that the
+        // four 16-lane groups of a wave land in different banks), then every thread adds the
+        // halves for four consecutive filters and stores 16 bytes; eight lanes cover the 128
+        // contiguous bytes this block owns of a pixel.
+        constexpr int kRow = 36, kHalf = 16 * 16 * kRow;
+        static_assert(2 * kHalf * 4 <= kLdsBytes, "staging fits the operand planes' LDS");
+        // the second half's staged copy of four consecutive filters (none with PART 3)
+        auto other_half = [&](int at) {
+            if constexpr (PART == 3) return (v4i){0, 0, 0, 0};
+            else return *reinterpret_cast<const v4i*>(parki + kHalf + at);
+        };
+        if constexpr (PART < 2) {
+            int* dst = parki + half * kHalf + (4 * (lane >> 4)) * kRow + kblock * 16 + (lane & 15);
+#pragma unroll
+            for (int o = 0; o < 16; ++o)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) dst[(o * 16 + q) * kRow] = Yp[o][q];
+        }
+        if constexpr (PART == 1) return;
+        if constexpr (PART == 0) __syncthreads();
+        // thread: filters 4*k4..4*k4+3; pass ps: output row i = ps/2, tile = 8*(ps%2) + px/4, column j = px%4
+        const int k4 = tid & 7, px = tid >> 3, j = px & 3;
+        const int kk = kbase + 4 * k4;
+        if constexpr (Q8) {
+            // finished int32 outputs of filters 4*g .. 4*g+3 of the block
+            auto staged = [&](int o, int tile, int g) {
+                const int at = (o * 16 + tile) * kRow + 4 * g;
+                return (*reinterpret_cast<const v4i*>(parki + at) + other_half(at) + rnd) >> 4;
+            };
+            if (q8.pool) {
+                // 16 tiles x 2x2 pooled pixels = 64 pixels; thread: four filters of pixels px and px + 32
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int pp = px + 32 * e, tile = pp >> 2, pi = (pp >> 1) & 1, pj = pp & 1;
+                    v4i best = requantise(staged(4 * (2 * pi) + 2 * pj, tile, k4), q8);
+                    best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi) + 2 * pj + 1, tile, k4), q8));
+                    best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj, tile, k4), q8));
+                    best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj + 1, tile, k4), q8));
+                    const int n = __shfl(my_n, tile), row = __shfl(my_row, tile), col = __shfl(my_col, tile);
+                    const bool ok = __shfl(my_origin, tile) >= 0 && row + 2 * pi < p.H && col + 2 * pj < p.W && kk < p.K;
+                    const size_t at = (((size_t)n * (p.H >> 1) + (row >> 1) + pi) * (p.W >> 1) + (col >> 1) + pj) * p.K + kk;
+                    if (ok) *reinterpret_cast<uint32_t*>(q8.out + at) = pack_bytes(best);
+                }
+                return;
+            }
+            // thread: 16 filters (half h16 of the block) of its own tile (lane & 15) at outputs
+            // tid/32 and tid/32 + 8: sixteen lanes read sixteen tiles' rows, which fall in
+            // different banks, and a thread stores 16 bytes where the alignment allows
+            const int h16 = (tid >> 4) & 1, kq = kbase + 16 * h16;
+            const bool vector_store = ((p.K & 15) | (reinterpret_cast<uintptr_t>(q8.out) & 15)) == 0;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int o = (tid >> 5) + 8 * e, i = o >> 2, jj = o & 3;
+                uint32_t bytes[4];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) bytes[g] = pack_bytes(requantise(staged(o, lane & 15, 4 * h16 + g), q8));
+                const bool ok = my_origin >= 0 && my_row + i < p.H && my_col + jj < p.W;
+                int8_t* dst = q8.out + (size_t)my_origin + (size_t)(i * p.W + jj) * p.K + kq;
+                if (ok && vector_store && kq < p.K) {
+                    *reinterpret_cast<uint4*>(dst) = make_uint4(bytes[0], bytes[1], bytes[2], bytes[3]);
+                } else if (ok) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        if (kq + 4 * g < p.K) reinterpret_cast<uint32_t*>(dst)[g] = bytes[g];
+                }
+            }
+            return;
+        }
+        int32_t* first[2];   // output row 0 of the thread's two tiles (e = 0, 1); null where nothing is stored
+        int rows[2];         // output rows of that tile inside the image
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int origin = __shfl(my_origin, 8 * e + (px >> 2));
+            const bool ok = origin >= 0 && __shfl(my_col, 8 * e + (px >> 2)) + j < p.W && kk < p.K;
+            first[e] = ok ? y + (size_t)origin + j * p.K + kk : nullptr;
+            rows[e] = p.H - __shfl(my_row, 8 * e + (px >> 2));
+        }
+        const size_t row_pitch = (size_t)p.W * p.K;
+        v4i v[8];
+#pragma unroll
+        for (int ps = 0; ps < 8; ++ps) {
+            const int i = ps >> 1, tile = 8 * (ps & 1) + (px >> 2);
+            const int at = ((4 * i + j) * 16 + tile) * kRow + 4 * k4;
+            v[ps] = (*reinterpret_cast<const v4i*>(parki + at) + other_half(at) + rnd) >> 4;
+        }
+#pragma unroll
+        for (int ps = 0; ps < 8; ++ps) {
+            const int i = ps >> 1, e = ps & 1;
+            if (first[e] != nullptr && i < rows[e]) *reinterpret_cast<v4i*>(first[e] + i * row_pitch) = v[ps];
+        }
+        return;
+    }
+    // General path: park[wave][output 0..15][lane] (four registers = four tiles each); the value
+    // of (tile, output 4i+j, filter kl) sits in waves kl/16 and 2 + kl/16 at output 4i+j, lane
+    // (tile/4)*16 + kl%16, register tile%4.  16 x 16 x 32 = 8192 results, 32 per thread.
+    v4i* park = reinterpret_cast<v4i*>(lds);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) park[(wave * 16 + i) * 64 + lane] = Yp[i];
+    __syncthreads();
+    if constexpr (Q8) {
+        // One byte per (tile, output pixel, filter), in the order of the output layout; lg = log2
+        // of the output pixels per tile side (4, or 2 after pooling).
+        const int lg = q8.pool ? 1 : 2, side = 1 << lg, span = q8.pool ? 2 : 1;
+        const int Ho = q8.pool ? p.H >> 1 : p.H, Wo = q8.pool ? p.W >> 1 : p.W;
+        const int items = (16 * 32) << (2 * lg);
+        for (int e = tid; e < items; e += 256) {
+            int kl, tile, pi, pj;
+            if constexpr (LAYOUT == WG_NHWC) {
+                kl = e & 31; pj = (e >> 5) & (side - 1); pi = (e >> (5 + lg)) & (side - 1); tile = e >> (5 + 2 * lg);
+            } else {
+                pj = e & (side - 1); tile = (e >> lg) & 15; pi = (e >> (lg + 4)) & (side - 1); kl = e >> (2 * lg + 4);
+            }
+            int best = -129;
+            for (int a = 0; a < span; ++a)
+                for (int b = 0; b < span; ++b) {
+                    const int o = 4 * (span * pi + a) + span * pj + b;
+                    const int at = ((((kl >> 4) * 16 + o) * 64) + (tile >> 2) * 16 + (kl & 15)) * 4 + (tile & 3);
+                    best = max(best, requantise((parki[at] + parki[at + 2 * 16 * 64 * 4] + rnd) >> 4, q8));
+                }
+            const int n = __shfl(my_n, tile), row = __shfl(my_row, tile), col = __shfl(my_col, tile);
+            const bool ok = __shfl(my_origin, tile) >= 0 && row + span * pi < p.H && col + span * pj < p.W && kbase + kl < p.K;
+            const int oh = (q8.pool ? row >> 1 : row) + pi, ow = (q8.pool ? col >> 1 : col) + pj;
+            const size_t at = LAYOUT == WG_NHWC ? (((size_t)n * Ho + oh) * Wo + ow) * p.K + kbase + kl
+                                                : (((size_t)n * p.K + kbase + kl) * Ho + oh) * Wo + ow;
+            if (ok) q8.out[at] = (int8_t)best;
+        }
+        return;
+    }
+    int v[32];
+    if constexpr (LAYOUT == WG_NHWC) {
+        // thread: filter kl and output column j fixed; iteration it: tile it/2, output row 2(it%2) + tid/128
+        const int kl = tid & 31, j = (tid >> 5) & 3, ih = tid >> 7;
+        const int kk = kbase + kl;
+        const int at0 = (((kl >> 4) * 16 + j) * 64 + (kl & 15)) * 4;
+#pragma unroll
+        for (int it = 0; it < 32; ++it) {
+            const int tile = it >> 1, i = 2 * (it & 1) + ih;
+            const int at = at0 + (4 * i * 64 + (tile >> 2) * 16) * 4 + (tile & 3);
+            v[it] = (parki[at] + parki[at + 2 * 16 * 64 * 4] + rnd) >> 4;
+        }
+#pragma unroll
+        for (int it = 0; it < 32; ++it) {
+            const int tile = it >> 1, i = 2 * (it & 1) + ih;
+            const int origin = __builtin_amdgcn_readlane(my_origin, tile);
+            const int h = __builtin_amdgcn_readlane(my_row, tile) + i, w = __builtin_amdgcn_readlane(my_col, tile) + j;
+            if (origin >= 0 && h < p.H && w < p.W && kk < p.K) y[(size_t)origin + (i * p.W + j) * p.K + kk] = v[it];
+        }
+    } else {
+        // thread: tile, output row i and column j fixed; iteration it: filter it.  A wave writes one
+        // output row of 16 consecutive tiles = 256 contiguous bytes.
+        const int j = tid & 3, tile = (tid >> 2) & 15, i = tid >> 6;
+        const int origin = __shfl(my_origin, tile), h = __shfl(my_row, tile) + i, w = __shfl(my_col, tile) + j;
+        const bool ok = origin >= 0 && h < p.H && w < p.W;
+        const int at0 = ((4 * i + j) * 64 + (tile >> 2) * 16) * 4 + (tile & 3);
+#pragma unroll
+        for (int it = 0; it < 32; ++it) {
+            const int at = at0 + ((it >> 4) * 16 * 64 + (it & 15)) * 4;
+            v[it] = (parki[at] + parki[at + 2 * 16 * 64 * 4] + rnd) >> 4;
+        }
+#pragma unroll
+        for (int it = 0; it < 32; ++it)
+            if (ok && kbase + it < p.K) y[(size_t)origin + ((size_t)(kbase + it) * p.H + i) * p.W + j] = v[it];
+    }
+
+}
+
+// Product phase of the role-specialised kernel: the same arithmetic as ProductPhase / ScaledSums
+// without their software pipelining (one set of fragments and accumulators, an eight-deep filter
+// ring), because a product wave there has 256 registers and its waits are covered by the
+// transform wave on the same SIMD.
+// AHEAD: the activation fragments of the next entry are asked for before the current entry's
+// matrix-core instructions (a second set of fragment registers), for callers whose product waves
+// are the longer chain of the two roles.
+// PIPE: an entry's vector work runs beside the next entry's matrix-core instructions (a second set of accumulators).
+template <int MODE, int HALF, bool SUMS, int RING = 8, bool AHEAD = false, bool PIPE = false>
+struct LeanProducts {
+    // scaled mode with joined channel sums, or in a wave that owns every entry: complex entries without the -Wi plane
+    static constexpr int PM = MODE == WG_SCALED && (SUMS || HALF == kAllRows) ? kScaledTwoPlanes : MODE;
+    using Phase = ProductPhase<PM, HALF>;
+    static constexpr int NE = Phase::NE, NB = Phase::NB;
+    static constexpr int kRing = RING;
+    static constexpr int kSums = SUMS ? ScaledSums<HALF>::kSums : 1;   // 18 per half, 36 for a wave that owns every entry
+    v4i ring[kRing];
+
+    __device__ inline void prefetch(const LaneContext& cx) {
+        static_for<(NB < kRing ? NB : kRing)>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
+    }
+
+    // sums: the 18 channel sums of ScaledSums (SUMS), else unused; Y: the outputs (not SUMS)
+    __device__ inline void run(const LaneContext& cx, v4i (&sums)[kSums], v4i (&Y)[16]) {
+        v4i er[6], ei[6];
+        v4i afr2[AHEAD ? 2 : 1][4];
+        if constexpr (AHEAD)
+            static_for<num_a<PM>(half_slot(HALF, 0).entry)>([&](auto I) { afr2[0][I] = Phase::template load_a<0, I>(cx); });
+        // the matrix-core part of slot S: activation fragments, products into acc, refill of the filter ring
+        auto multiply = [&](auto S, v4i (&acc)[9]) {
+            constexpr int s = S;
+            constexpr int entry = half_slot(HALF, s).entry;
+            constexpr int b0 = b_start<PM>(HALF, s);
+            v4i (&afr)[4] = afr2[AHEAD ? (s & 1) : 0];
+            if constexpr (!AHEAD) {
+                static_for<num_a<PM>(entry)>([&](auto I) { afr[I] = Phase::template load_a<s, I>(cx); });
+            } else if constexpr (s + 1 < NE) {
+                static_for<num_a<PM>(half_slot(HALF, s + 1).entry)>(
+                    [&](auto I) { afr2[(s + 1) & 1][I] = Phase::template load_a<s + 1, I>(cx); });
+            }
+            static_for<num_ops<PM>(entry)>([&](auto I) {
+                constexpr Op op = entry_op<PM>(entry, I);
+                constexpr v4i zero = {0, 0, 0, 0};
+                acc[op.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(afr[op.a], ring[(b0 + op.b) % kRing],
+                                                                    op.init ? zero : acc[op.acc], 0, 0, 0);
+            });
+            static_for<num_b<PM>(entry)>([&](auto I) {
+                if constexpr (b0 + I + kRing < NB) ring[(b0 + I) % kRing] = Phase::template load_b<b0 + I + kRing>(cx);
+            });
+        };
+        // the vector part of slot S: limbs joined; then into the channel sums, or reverse scaling and output transform
+        auto reduce = [&](auto S, const v4i (&acc)[9]) {
+            constexpr int s = S;
+            constexpr Slot sl = half_slot(HALF, s);
+            constexpr int entry = sl.entry;
+            if constexpr (SUMS) {
+                // joined values only; scaling (scaled mode) and the output transform wait for finish()
+                constexpr int v = ScaledSums<HALF>::sum_start(s);
+                if constexpr (MODE == WG_SCALED) {   // Re = Dr Wr - Di Wi,  Im = Dr Wi + Di Wr
+                    if constexpr (is_real(entry)) {
+                        sums[v] += (acc[0] << kByteLimbShift) + acc[1];
+                    } else {
+                        sums[v] += ((acc[0] - acc[4]) << kByteLimbShift) + (acc[1] - acc[5]);
+                        sums[v + 1] += (acc[2] << kByteLimbShift) + acc[3];
+                    }
+                } else if constexpr (is_real(entry)) {
+                    sums[v] += join_limbs(acc[0], acc[1], acc[2]);
+                } else {
+                    sums[v] += join_limbs(acc[0] - acc[3], acc[1] - acc[4], acc[2] - acc[5]);
+                    sums[v + 1] += join_limbs(acc[6], acc[7], acc[8]);
+                }
+            } else {
+                v4i re, im = {0, 0, 0, 0};
+                if constexpr (MODE == WG_LOSSLESS) {
+                    if constexpr (is_real(entry)) {
+                        re = join_limbs(acc[0], acc[1], acc[2]);
+                    } else {   // Re = Dr Wr - Di Wi,  Im = Dr Wi + Di Wr
+                        re = join_limbs(acc[0] - acc[3], acc[1] - acc[4], acc[2] - acc[5]);
+                        im = join_limbs(acc[6], acc[7], acc[8]);
+                    }
+                } else {
+                    if constexpr (is_real(entry)) re = (acc[0] << kByteLimbShift) + acc[1];
+                    else if constexpr (PM == kScaledTwoPlanes) re = ((acc[0] - acc[4]) << kByteLimbShift) + (acc[1] - acc[5]);
+                    else re = (acc[0] << kByteLimbShift) + acc[1];
+                    if constexpr (!is_real(entry)) im = (acc[2] << kByteLimbShift) + acc[3];
+                    // Section 4.2 (a wave that owns every entry exists only where the factors were parked)
+                    const ReverseScale unscale = HALF == kAllRows ? parked_scale<s>(cx) : ReverseScale(cx.table_k[entry]);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        re[q] = unscale(re[q]);
+                        if constexpr (!is_real(entry)) im[q] = unscale(im[q]);
+                    }
+                }
+                er[sl.pos] = re;
+                ei[sl.pos] = im;
+                if constexpr (sl.last_in_row) finish_row<sl.row>(er, ei, Y);
+                if constexpr (HALF == kAllRows) {
+                    // Pins the entry's value, and a finished row's outputs, to this place.  Left alone, the compiler moves
+                    // the vector work of all 26 entries behind the last matrix-core instruction (into the block that
+                    // stages the outputs) and keeps every accumulator alive until then.
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        asm volatile("" ::"v"(re[q]));
+                        if constexpr (!is_real(entry)) asm volatile("" ::"v"(im[q]));
+                    }
+                    if constexpr (sl.last_in_row) {
+#pragma unroll
+                        for (int i = 0; i < 16; ++i)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) asm volatile("" ::"v"(Y[i][q]));
+                    }
+                }
+            }
+        };
+        if constexpr (PIPE) {
+            // slot s + 1's matrix-core instructions are issued before slot s's vector work, which then runs beside them
+            v4i acc2[2][9];
+            static_for<NE + 1>([&](auto S) {
+                if constexpr (S < NE) multiply(S, acc2[S & 1]);
+                if constexpr (S > 0) reduce(std::integral_constant<int, S - 1>{}, acc2[(S - 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        } else {
+            static_for<NE>([&](auto S) {
+                v4i acc[9];
+                multiply(S, acc);
+                reduce(S, acc);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+    }
+
+    // SUMS, lossless mode, after the last channel block: the output transform of the channel sums
+    // (it is linear, so it may as well run once on the sums as once per block).
+    __device__ inline static void finish_lossless(const v4i (&sums)[kSums], v4i (&Y)[16]) {
+        v4i er[6], ei[6];
+        static_for<NE>([&](auto S) {
+            constexpr Slot sl = half_slot(HALF, S);
+            constexpr int v = ScaledSums<HALF>::sum_start(S);
+            er[sl.pos] = sums[v];
+            if constexpr (!is_real(sl.entry)) ei[sl.pos] = sums[v + 1];
+            else                              ei[sl.pos] = (v4i){0, 0, 0, 0};
+            if constexpr (sl.last_in_row) {
+                finish_row<sl.row>(er, ei, Y);
+                if constexpr (HALF == kAllRows) __builtin_amdgcn_sched_barrier(0);   // row by row (see ScaledSums::finish)
+            }
+        });
+    }
+};
+
+// Scaled mode in the role-specialised kernel: every limb product of every entry a wave owns has
+// its own matrix-core accumulator for the whole kernel (two per real entry: high and low
+// activation limb; four per complex entry: Re and Im, each high and low; 36 per wave), so a
+// channel block costs a product wave nothing but fragment loads and matrix-core instructions
+// and the vector ALU is left to the transform wave.  The limbs are joined, the reverse scaling
+// applied and the output transform run once, on the finished channel sums.
+template <int HALF>
+struct ResidentScaled {
+    static constexpr int MODE = WG_SCALED;
+    using Phase = ProductPhase<MODE, HALF>;
+    static constexpr int NE = Phase::NE, NB = Phase::NB;
+    static constexpr int kRing = 8;
+    static constexpr int acc_start(int slot) {
+        int n = 0;
+        for (int s = 0; s < slot; ++s) n += is_real(half_slot(HALF, s).entry) ? 2 : 4;
+        return n;
+    }
+    static constexpr int kAcc = acc_start(NE);
+    v4i ring[kRing];
+
+    __device__ inline void prefetch(const LaneContext& cx) {
+        static_for<(NB < kRing ? NB : kRing)>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
+    }
+    __device__ inline void run(const LaneContext& cx, v4i (&acc)[kAcc]) {
+        static_for<NE>([&](auto S) {
+            constexpr int s = S;
+            constexpr int entry = half_slot(HALF, s).entry;
+            constexpr int b0 = b_start<MODE>(HALF, s);
+            constexpr int v = acc_start(s);
+            v4i afr[4];
+            static_for<num_a<MODE>(entry)>([&](auto I) { afr[I] = Phase::template load_a<s, I>(cx); });
+            static_for<num_ops<MODE>(entry)>([&](auto I) {
+                constexpr Op op = entry_op<MODE>(entry, I);
+                acc[v + op.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(afr[op.a], ring[(b0 + op.b) % kRing], acc[v + op.acc], 0, 0, 0);
+            });
+            static_for<num_b<MODE>(entry)>([&](auto I) {
+                if constexpr (b0 + I + kRing < NB) ring[(b0 + I) % kRing] = Phase::template load_b<b0 + I + kRing>(cx);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+    __device__ inline static void finish(const LaneContext& cx, const v4i (&acc)[kAcc], v4i (&Y)[16]) {
+        v4i er[6], ei[6];
+        static_for<NE>([&](auto S) {
+            constexpr Slot sl = half_slot(HALF, S);
+            constexpr int v = acc_start(S);
+            v4i re = (acc[v] << kByteLimbShift) + acc[v + 1], im = {0, 0, 0, 0};
+            if constexpr (!is_real(sl.entry)) im = (acc[v + 2] << kByteLimbShift) + acc[v + 3];
+            const ReverseScale unscale = parked_scale<S>(cx);   // Section 4.2
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                re[q] = unscale(re[q]);
+                if constexpr (!is_real(sl.entry)) im[q] = unscale(im[q]);
+            }
+            er[sl.pos] = re;
+            ei[sl.pos] = im;
+            if constexpr (sl.last_in_row) finish_row<sl.row>(er, ei, Y);
+        });
+    }
+};
+static_assert(ResidentScaled<0>::kAcc == 36 && ResidentScaled<1>::kAcc == 36, "both halves keep 36 accumulators");
+
+// Compute units of the current device (256 on MI355X), asked once.
+int compute_units() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+            return n;
+        return 256;
+    }();
+    return cus;
+}
+
+}  // namespace
+}  // namespace wg
