@@ -69,13 +69,7 @@ int winograd_filter_transform_u8(const uint8_t* w_dev, int zero_point, int K, in
 
 int winograd_conv2d_u8(const uint8_t* x_dev, int zero_point, const void* packed_dev, int32_t* y_dev, int N, int C, int H,
                        int W, int K, int layout, int mode, void* hip_stream) {
-    if (!x_dev || !packed_dev || !y_dev || !valid_layout(layout) || !valid_mode(mode)) return WG_EINVAL;
-    if (zero_point < 0 || zero_point > 255) return WG_EINVAL;
-    if (int st = check_shape(N, C, H, W, K)) return st;
-    if (C > kMaxChannelsInt9) return WG_EUNSUPPORTED;
-    if (!aligned(x_dev, 4) || !aligned(y_dev, 4) || !aligned(packed_dev, 256)) return WG_EINVAL;
-    return status_of(launch_fused_conv_u8(x_dev, zero_point, packed_dev, y_dev, make_problem(N, C, H, W, K), layout, mode,
-                                          static_cast<hipStream_t>(hip_stream)));
+    return conv2d_u8_with_scratch(x_dev, zero_point, packed_dev, y_dev, N, C, H, W, K, layout, mode, nullptr, 0, hip_stream);
 }
 
 int winograd_conv2d_int8_act_scaled(const int8_t* x_dev, const void* packed_dev, int32_t* y_dev, int N, int C, int H, int W,
@@ -117,7 +111,8 @@ int winograd_conv2d_int8(const int8_t* x_dev, const void* packed_dev, int32_t* y
     const Problem p = make_problem(N, C, H, W, K);
     const WorkspaceLayout wl = workspace_layout(p, mode);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    if (use_fused()) return status_of(launch_fused_conv(x_dev, packed_dev, y_dev, p, layout, mode, no_int8_epilogue(), s));
+    if (use_fused())
+        return status_of(launch_fused_conv(x_dev, packed_dev, y_dev, p, layout, mode, no_int8_epilogue(), Scratch{workspace_dev, workspace_bytes}, s));
     int8_t* V = static_cast<int8_t*>(workspace_dev) + wl.v_off;
     int32_t* M = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(workspace_dev) + wl.m_off);
     if (int st = status_of(launch_input_transform(x_dev, p, layout, mode, V, s))) return st;
@@ -128,15 +123,8 @@ int winograd_conv2d_int8(const int8_t* x_dev, const void* packed_dev, int32_t* y
 int winograd_conv2d_int8_requant(const int8_t* x_dev, const void* packed_dev, int8_t* out_dev, int N, int C, int H,
                                  int W, int K, int layout, int mode, int shift, int relu, int pool,
                                  void* hip_stream) {
-    if (!x_dev || !packed_dev || !out_dev || !valid_layout(layout) || !valid_mode(mode)) return WG_EINVAL;
-    if (shift < 0 || shift > 31) return WG_EINVAL;
-    if (int st = check_shape(N, C, H, W, K)) return st;
-    if (!aligned(x_dev, 4) || !aligned(out_dev, 4) || !aligned(packed_dev, 256)) return WG_EINVAL;
-    if (pool && ((H | W) & 1)) return WG_EUNSUPPORTED;
-    const Problem p = make_problem(N, C, H, W, K);
-    return status_of(launch_fused_conv(x_dev, packed_dev, nullptr, p, layout, mode,
-                                       make_int8_epilogue(out_dev, shift, relu != 0, pool != 0),
-                                       static_cast<hipStream_t>(hip_stream)));
+    return conv2d_int8_requant_with_scratch(x_dev, packed_dev, out_dev, N, C, H, W, K, layout, mode, shift, relu, pool, nullptr, 0,
+                                            hip_stream);
 }
 
 size_t winograd_f2x2_packed_filter_bytes(int K, int C, int mode) {
@@ -285,7 +273,7 @@ int winograd_conv2d_int8_enqueue_stage(const int8_t* x_dev, const void* packed_d
         if (stage == 0)      e = launch_input_transform(x_dev, p, layout, mode, V, s);
         else if (stage == 1) e = launch_contraction(V, packed_dev, M, p, mode, s);
         else if (stage == 2) e = launch_output_transform(M, packed_dev, y_dev, p, layout, mode, s);
-        else                 e = launch_fused_conv(x_dev, packed_dev, y_dev, p, layout, mode, no_int8_epilogue(), s);
+        else                 e = launch_fused_conv(x_dev, packed_dev, y_dev, p, layout, mode, no_int8_epilogue(), Scratch{workspace_dev, workspace_bytes}, s);
     }
     return status_of(e);
 }
@@ -353,13 +341,41 @@ int winograd_debug_contraction(const int8_t* x_dev, const void* packed_dev, int3
 
 namespace wg {
 
-int conv2d_int8_single_kernel(const int8_t* x, const void* packed, int32_t* y, int N, int C, int H, int W, int K, int layout,
-                              int mode, void* stream) {
+size_t conv2d_scratch_bytes(int N, int C, int H, int W, int K, int layout, int mode, int is_unsigned) {
+    if (check_shape(N, C, H, W, K) != WG_OK || !valid_layout(layout) || !valid_mode(mode)) return 0;
+    return fused_conv_scratch_wanted(make_problem(N, C, H, W, K), layout, mode, is_unsigned != 0);
+}
+
+int conv2d_int8_with_scratch(const int8_t* x, const void* packed, int32_t* y, int N, int C, int H, int W, int K, int layout,
+                             int mode, void* scratch, size_t scratch_bytes, void* stream) {
     if (!x || !packed || !y || !valid_layout(layout) || !valid_mode(mode)) return WG_EINVAL;
     if (int st = check_shape(N, C, H, W, K)) return st;
-    if (!aligned(x, 4) || !aligned(y, 4) || !aligned(packed, 256)) return WG_EINVAL;
+    if (!aligned(x, 4) || !aligned(y, 4) || !aligned(packed, 256) || !aligned(scratch, 256)) return WG_EINVAL;
     return status_of(launch_fused_conv(x, packed, y, make_problem(N, C, H, W, K), layout, mode, no_int8_epilogue(),
+                                       Scratch{scratch, scratch_bytes}, static_cast<hipStream_t>(stream)));
+}
+
+int conv2d_int8_requant_with_scratch(const int8_t* x, const void* packed, int8_t* out, int N, int C, int H, int W, int K, int layout,
+                                     int mode, int shift, int relu, int pool, void* scratch, size_t scratch_bytes, void* stream) {
+    if (!x || !packed || !out || !valid_layout(layout) || !valid_mode(mode)) return WG_EINVAL;
+    if (shift < 0 || shift > 31) return WG_EINVAL;
+    if (int st = check_shape(N, C, H, W, K)) return st;
+    if (!aligned(x, 4) || !aligned(out, 4) || !aligned(packed, 256) || !aligned(scratch, 256)) return WG_EINVAL;
+    if (pool && ((H | W) & 1)) return WG_EUNSUPPORTED;
+    return status_of(launch_fused_conv(x, packed, nullptr, make_problem(N, C, H, W, K), layout, mode,
+                                       make_int8_epilogue(out, shift, relu != 0, pool != 0), Scratch{scratch, scratch_bytes},
                                        static_cast<hipStream_t>(stream)));
+}
+
+int conv2d_u8_with_scratch(const uint8_t* x, int zero_point, const void* packed, int32_t* y, int N, int C, int H, int W, int K,
+                           int layout, int mode, void* scratch, size_t scratch_bytes, void* stream) {
+    if (!x || !packed || !y || !valid_layout(layout) || !valid_mode(mode)) return WG_EINVAL;
+    if (zero_point < 0 || zero_point > 255) return WG_EINVAL;
+    if (int st = check_shape(N, C, H, W, K)) return st;
+    if (C > kMaxChannelsInt9) return WG_EUNSUPPORTED;
+    if (!aligned(x, 4) || !aligned(y, 4) || !aligned(packed, 256) || !aligned(scratch, 256)) return WG_EINVAL;
+    return status_of(launch_fused_conv_u8(x, zero_point, packed, y, make_problem(N, C, H, W, K), layout, mode,
+                                          Scratch{scratch, scratch_bytes}, static_cast<hipStream_t>(stream)));
 }
 
 }  // namespace wg

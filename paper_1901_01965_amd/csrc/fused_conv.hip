@@ -20,7 +20,10 @@
 // two filter planes per value) and a complex product as its four real products,
 // instead of the three-multiplication forms of Section 3.1 that the staged
 // contraction kernel uses; those would need half again as many operand planes.
+#include <algorithm>
+
 #include "product_core.h"
+#include "roles_conv.h"
 
 namespace wg {
 namespace {
@@ -111,7 +114,7 @@ __device__ __forceinline__ void fused_conv_body(const int8_t* __restrict__ x, co
     if constexpr (LOAD != kLoadDirect) {
         if (a_t < p.T) load_patch<LAYOUT, VEC4>(x, p, a_n, a_ty, a_tx, 4 * a_cq, patch, enc);
     }
-    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.C, MODE, ENC::kMagic)) return;
+    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.Cf, MODE, ENC::kMagic)) return;
 
     ProductPhase<MODE, 0> phase0;
     ProductPhase<MODE, 1> phase1;
@@ -181,19 +184,15 @@ __device__ __forceinline__ void fused_conv_body(const int8_t* __restrict__ x, co
     }
 
     // ---- add the two halves and store ------------------------------------------------------
-    // Where tile (lane & 15) of this block starts in y (offsets fit 32 bits, checked on the
-    // host; -1 marks tiles beyond T), and its first output row and column.
-    const int my_row = 4 * my_ty, my_col = 4 * my_tx;
-    int my_origin = -1;
-    if (tile0 + (lane & 15) < p.T)
-        my_origin = LAYOUT == WG_NHWC ? ((my_n * p.H + my_row) * p.W + my_col) * p.K
-                                      : (my_n * p.K * p.H + my_row) * p.W + my_col;
-    const int rnd = MODE == WG_SCALED ? 8 : 0;
-    const StoreContext sc = {lds, tid, lane, wave, half, kblock, my_n, my_row, my_col, my_origin, rnd, y};
+    StoreContext sc;
+    sc.lds = lds; sc.tid = tid; sc.lane = lane; sc.rnd = MODE == WG_SCALED ? 8 : 0; sc.y = y;
+    locate_tile<LAYOUT>(sc, p, tile0);
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
         __syncthreads();   // the operand planes (or the previous pass's staged outputs) are dead
-        store_block<LAYOUT, Q8>(sc, p, q8, Yall[pass], k0 + pass * kFusedFilters);
+        stage_outputs(lds, lane, half, kblock, Yall[pass]);
+        __syncthreads();
+        store_staged<LAYOUT, Q8, true>(sc, p, q8, k0 + pass * kFusedFilters);
     }
 }
 
@@ -415,7 +414,7 @@ __global__ __launch_bounds__(256) void fused_conv_act_scaled_kernel(const int8_t
     const int kblock = wave & 1, half = wave >> 1;
     const int tile0 = blockIdx.x * kFusedTiles, k0 = blockIdx.y * kFusedFilters;
     const int k = k0 + kblock * 16 + (lane & 15);
-    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.C, WG_SCALED)) return;
+    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.Cf, WG_SCALED)) return;
 
     int my_n = 0, my_ty = 0, my_tx = 0;
     if (tile0 + (lane & 15) < p.T) decode_tile(p, tile0 + (lane & 15), my_n, my_ty, my_tx);
@@ -508,13 +507,13 @@ __global__ __launch_bounds__(256) void fused_conv_act_scaled_kernel(const int8_t
     for (int i = 0; i < 16; ++i) Y[i] = (v4i){0, 0, 0, 0};
     if (half == 0) BothScaledSums<0>::finish(cx, rq_tab, lane, sums, Y); else BothScaledSums<1>::finish(cx, rq_tab, lane, sums, Y);
 
-    const int my_row = 4 * my_ty, my_col = 4 * my_tx;
-    int my_origin = -1;
-    if (tile0 + (lane & 15) < p.T)
-        my_origin = LAYOUT == WG_NHWC ? ((my_n * p.H + my_row) * p.W + my_col) * p.K : (my_n * p.K * p.H + my_row) * p.W + my_col;
-    const StoreContext sc = {lds, tid, lane, wave, half, kblock, my_n, my_row, my_col, my_origin, 8, y};
+    StoreContext sc;
+    sc.lds = lds; sc.tid = tid; sc.lane = lane; sc.rnd = 8; sc.y = y;
+    locate_tile<LAYOUT>(sc, p, tile0);
     __syncthreads();   // the operand planes are dead (the tables lie behind them)
-    store_block<LAYOUT, false>(sc, p, Int8Epilogue{}, Y, k0);
+    stage_outputs(lds, lane, half, kblock, Y);
+    __syncthreads();
+    store_staged<LAYOUT, false, true>(sc, p, Int8Epilogue{}, k0);
 }
 
 template <int LAYOUT, int LOAD, int MODE, bool SUMS>
@@ -535,25 +534,195 @@ hipError_t launch_u8_mode(const int8_t* x, ZeroPointU8 zero, const uint8_t* blob
     return launch_u8<LAYOUT, LOAD, WG_SCALED, true>(x, zero, blob, bl, y, p, s);
 }
 
+// Test hooks (see winograd_c.h).
+std::atomic<int> g_stream_workgroups{0}, g_stream_variant{0}, g_scaled_variant{0};
+
+// How a convolution is run where the fast loads apply (channels-last, C % 4 = 0, as given or as a copy).
+struct Plan {
+    bool copies;         // through a channels-last copy in scratch memory
+    int splits, blocks;  // > 1: the channel blocks are dealt to `splits` workgroups each, `blocks` per workgroup
+};
+
+// Deep layers with few tiles leave most of the chip idle while a workgroup walks through its channel blocks one after the
+// other.  Dealing the blocks to several workgroups takes a second kernel that adds the splits and finishes.  Measured on
+// single images of 128 .. 512 channels, CB channel blocks, b of them per workgroup (us):
+//   lossless: 4.3 + 2.9 CB in one kernel, 6.5 + 4.5 b split (512 channels at 14x14: 27 -> 11)
+//   scaled:   5.1 + 1.95 CB in one kernel, 10 + 5 b split (36 sums per tile and filter to move instead of 16 outputs)
+bool split_pays(int mode, int CB, int b) {
+    return mode == WG_LOSSLESS ? 4.3 + 2.9 * CB > 6.5 + 4.5 * b : 5.1 + 1.95 * CB > 10.0 + 5.0 * b;
+}
+
+Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t scratch_bytes) {
+    Plan plan = {false, 1, p.CB};
+    size_t left = scratch_bytes;
+    if (layout != WG_NHWC || p.C % 4 != 0) {
+        plan.copies = left >= channels_last_bytes(p);
+        if (!plan.copies) return plan;
+        left -= channels_last_bytes(p);
+    }
+    const bool hooked = g_stream_workgroups.load(std::memory_order_relaxed) > 0 || g_stream_variant.load(std::memory_order_relaxed) != 0 ||
+                        g_scaled_variant.load(std::memory_order_relaxed) != 0;
+    const int workgroups = ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters);
+    if (p.CB >= 2 && 2 * workgroups <= compute_units() && !is_unsigned && !hooked) {
+        const int blocks = ceil_div(p.CB, std::min(p.CB, compute_units() / workgroups)), splits = ceil_div(p.CB, blocks);
+        if (split_pays(mode, p.CB, blocks) && split_partial_bytes(p, mode, splits) <= left) {
+            plan.splits = splits;
+            plan.blocks = blocks;
+        }
+    }
+    return plan;
+}
+
 }  // namespace
 
-// uint8 activations with a zero point: the four-wave kernel with the load paths that select padding pixels explicitly
-// (they must read as the zero point, not as zero bytes), for every channel count the int9 path accepts.
+void set_scaled_variant(int v) { g_scaled_variant.store(v, std::memory_order_relaxed); }
+void set_stream_variant(int v) { g_stream_variant.store(v, std::memory_order_relaxed); }
+void set_stream_workgroups(int n) { g_stream_workgroups.store(n > 0 ? n : 0, std::memory_order_relaxed); }
+
+int stream_workgroups(int tile_blocks, int filter_blocks) {
+    const int forced = g_stream_workgroups.load(std::memory_order_relaxed);
+    if (forced > 0) return std::max(1, std::min(tile_blocks, forced));
+    // as many as the compute units allow, then as few as still finish in the same number of rounds
+    const int wanted = std::max(1, compute_units() / filter_blocks);
+    const int rounds = ceil_div(tile_blocks, wanted);
+    return std::max(1, ceil_div(tile_blocks, rounds));
+}
+
+size_t fused_conv_scratch_wanted(const Problem& p, int layout, int mode, bool is_unsigned) {
+    if (!is_unsigned && layout == WG_NHWC && p.C <= kNarrowChannels) return 0;
+    const Plan plan = plan_conv(p, layout, mode, is_unsigned, ~(size_t)0 >> 1);
+    return (plan.copies ? channels_last_bytes(p) : 0) + (plan.splits > 1 ? split_partial_bytes(p, mode, plan.splits) : 0);
+}
+
+namespace {
+
+// Runs c through one of the role-specialised forms, which read channels-last activations with C % 4 = 0.  False: another
+// kernel is the better one (it is left to the caller).
+bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial, hipStream_t s, hipError_t& status) {
+    const Problem& p = c.p;
+    if (plan.splits > 1) {
+        status = mode == WG_LOSSLESS ? launch_lossless_pair_sums(c.x, c.blob, partial, p, plan.blocks, plan.splits, s)
+                                     : launch_scaled_sums(c.x, c.blob, partial, p, plan.blocks, plan.splits, s);
+        if (status == hipSuccess)
+            status = mode == WG_LOSSLESS ? launch_sums_finish(c, partial, plan.splits, s) : launch_split_finish(c, partial, plan.splits, s);
+        return true;
+    }
+    // The streaming form when every workgroup gets at least six tile blocks to stream over (measured: +10-17 % on the
+    // large layers; with fewer, the fill and drain of its pipeline cost more than the overlap saves), or when a test asks
+    // for it.
+    const int tile_blocks = ceil_div(p.T, kFusedTiles), filter_blocks = p.Kp / kFusedFilters;
+    // The 64-filter form of that kernel (see below for when it applies) is also the fastest form for a layer with one
+    // channel block as soon as the 32-filter grid exceeds one round of the compute units, whatever the number of tile
+    // blocks per workgroup (56x56x64 at N = 12 .. 48: 8-30 % ahead of the limb-pair and 64-filter four-wave kernels).
+    const int stream_variant = g_stream_variant.load(std::memory_order_relaxed);
+    const bool whole64 = (p.K & 63) == 0 || (p.K & 63) > 32;   // padding to 64 filters adds no 32-filter block of nothing
+    const bool wide_one_block = p.CB == 1 && whole64 && stream_variant == 0 && (long long)tile_blocks * filter_blocks > compute_units();
+    // One channel block, a 32-filter grid of at most one round: the streaming kernel's 32-filter form with one tile block
+    // per workgroup (its eight waves: four transform, four multiply) is 10-14 % ahead of the four-wave kernel in scaled
+    // mode (56x56x64 at N = 8: 9.3 -> 8.5 us).  Lossless mode has the limb-pair kernel for signed channels-last layers of
+    // this kind; the others come here, too.
+    const bool forced_stream = g_stream_workgroups.load(std::memory_order_relaxed) > 0;
+    const bool pair_layer = mode == WG_LOSSLESS && c.zero == nullptr && c.layout == WG_NHWC;
+    const bool narrow_one_round = !pair_layer && p.CB == 1 && stream_variant == 0 && !forced_stream &&
+                                  (long long)tile_blocks * filter_blocks <= compute_units();
+    const bool streams = forced_stream || wide_one_block || narrow_one_round ||
+                         tile_blocks >= 6 * stream_workgroups(tile_blocks, filter_blocks);
+    // Lossless mode, channels-last, one channel block, too few tile blocks to stream over: the limb-pair form (eight waves
+    // per 16 tiles x 32 filters, lossless_conv.hip) against the four-wave forms of this file, by rounds of the compute
+    // units: measured on 56x56x64 layers, a round of the former takes 6.5 us, a round of the latter 7.4 us with 32 filters
+    // per workgroup (a grid of at most one round) and 11.7 us with 64 filters.
+    if (pair_layer && !streams) {
+        const int form = lossless_pair_conv_choice(c.x, p, c.layout);   // 0: not applicable or switched off, 1: the library decides, 2: forced
+        const long long w32 = (long long)tile_blocks * filter_blocks, cus = compute_units();
+        const double pair_cost = 6.5 * (double)((w32 + cus - 1) / cus);
+        const double here_cost = w32 <= cus ? 7.4 : 11.7 * (double)((w32 / 2 + cus - 1) / cus);
+        if (form == 2 || (form == 1 && p.CB == 1 && pair_cost < here_cost)) {
+            status = launch_lossless_pair_conv(c.x, c.blob, c.y, p, c.q8, s);
+            return true;
+        }
+    }
+    // Several channel blocks: the role-specialised kernel with eight product waves and 64 filters per workgroup, as soon as
+    // the 32-filter grid would need more than one round of the compute units (with a 64-filter grid of at most half the
+    // compute units the 32-filter form, which then fills the chip in one round, stays ahead).
+    // Measured on the layers of the VGG-16-shaped stack at N = 16 and on the 128-, 256- and 512-channel configurations.
+    // Scaled mode: 15-30 % faster than the streaming, 64-filter four-wave and 32-filter role-specialised forms wherever
+    // there are two or more channel blocks.  Lossless mode (twice the matrix-core work and filter bytes per product):
+    // +10-25 % with two or more channel blocks where the layer is too small to stream; where it streams, the streaming
+    // kernel's 64-filter form is level (two blocks) or 4 % ahead (four blocks) and takes the layer.
+    const int variant = g_scaled_variant.load(std::memory_order_relaxed);
+    const long long wide_grid = (long long)tile_blocks * (p.Kp / (2 * kFusedFilters));
+    // scaled mode also with one channel block, where the 64-filter grid is a single round and the 32-filter grid is not
+    // (56x56x64 at N = 16: 11.4 -> 10.9 us against the streaming kernel's 64-filter form)
+    const bool deep_enough = (p.CB >= 2 && (mode == WG_SCALED || !streams)) || (mode == WG_SCALED && wide_grid <= compute_units());
+    if (variant == 1 || (variant == 0 && deep_enough && 2 * wide_grid > compute_units())) {
+        status = launch_roles(c, mode, true, s);
+        return true;
+    }
+    if (streams) {
+        // the 64-filter form: lossless mode, or one channel block (see the kernel), unless the padding to 64 filters
+        // would add a 32-filter block of nothing
+        const bool wide = !narrow_one_round && (mode == WG_LOSSLESS || p.CB == 1) &&
+                          (stream_variant == 1 || (stream_variant == 0 && whole64));
+        status = launch_stream(c, mode, wide, s);
+        return true;
+    }
+    // Transform and products on separate waves: with several channel blocks and no more 32-filter workgroups than compute
+    // units (where the 64-filter variant would leave units idle), and in scaled mode from four channel blocks on
+    // when the grid is at least three rounds of the compute units (there the product waves do no
+    // vector work per block; measured on 256- and 512-channel layers: 10 % faster than the
+    // 64-filter variant, while in lossless mode, with two channel blocks, or with a grid of one
+    // or two rounds the 64-filter variant stays ahead).  Outputs and encodings that the four-wave kernel reaches only
+    // through its slow loads take it with any grid.
+    const long long workgroups = (long long)tile_blocks * filter_blocks;
+    const bool others = c.zero != nullptr || c.layout != WG_NHWC;
+    if ((p.CB >= 2 && (workgroups <= compute_units() || (mode == WG_SCALED && p.CB >= 4 && workgroups >= 3 * compute_units()))) || others) {
+        status = launch_roles(c, mode, false, s);
+        return true;
+    }
+    return false;
+}
+
+// The call with its activations channels-last, C % 4 = 0: as given, or copied into scratch memory, where the channel
+// sums of a split follow.  False where the layout would need a copy and there is no memory for it.
+bool make_fast_call(RolesCall& c, const Plan& plan, int layout, const Scratch& scratch, int32_t*& partial, hipStream_t s, hipError_t& status) {
+    partial = static_cast<int32_t*>(scratch.p);
+    status = hipSuccess;
+    if (layout == WG_NHWC && c.p.C % 4 == 0) return true;
+    if (!plan.copies) return false;
+    int8_t* const copy = static_cast<int8_t*>(scratch.p);
+    const int padded = padded_channels(c.p.C);
+    status = launch_channels_last(c.x, copy, c.p, layout, padded, c.zero ? (uint8_t)c.zero->zero_bytes : 0, s);
+    partial = reinterpret_cast<int32_t*>(copy + channels_last_bytes(c.p));
+    c.x = copy;
+    c.p.C = padded;
+    return true;
+}
+
+}  // namespace
+
+// uint8 activations with a zero point: the role-specialised forms; without the scratch memory for a channels-last copy
+// the four-wave kernel's byte loads.
 hipError_t launch_fused_conv_u8(const uint8_t* x_u8, int zero_point, const void* blob, int32_t* y, const Problem& p, int layout,
-                                int mode, hipStream_t s) {
-    const BlobLayout bl = blob_layout(p.Kp, p.C, mode);
+                                int mode, const Scratch& scratch, hipStream_t s) {
+    const BlobLayout bl = blob_layout(p.Kp, p.Cf, mode);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
     const int8_t* x = reinterpret_cast<const int8_t*>(x_u8);
     const ZeroPointU8 zero = make_zero_point(zero_point);
-    if (layout == WG_NHWC && p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0)
-        return launch_u8_mode<WG_NHWC, kLoadDwords>(x, zero, b, bl, y, p, mode, s);
+    const Plan plan = plan_conv(p, layout, mode, true, scratch.bytes);
+    RolesCall c = {x, &zero, b, bl, y, p, layout, no_int8_epilogue()};
+    int32_t* partial;
+    hipError_t status;
+    if (make_fast_call(c, plan, layout, scratch, partial, s, status)) {
+        if (status == hipSuccess) run_roles(c, mode, plan, partial, s, status);
+        return status;
+    }
     if (layout == WG_NHWC) return launch_u8_mode<WG_NHWC, kLoadBytes>(x, zero, b, bl, y, p, mode, s);
     return launch_u8_mode<WG_NCHW, kLoadBytes>(x, zero, b, bl, y, p, mode, s);
 }
 
 hipError_t launch_fused_conv_act_scaled(const int8_t* x, const void* blob, int32_t* y, int32_t* act_table, const Problem& p,
                                         int layout, hipStream_t s) {
-    const BlobLayout bl = blob_layout(p.Kp, p.C, WG_SCALED);
+    const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
     dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / kFusedFilters);
     auto go = [&](auto kernel) -> hipError_t {
@@ -569,86 +738,18 @@ hipError_t launch_fused_conv_act_scaled(const int8_t* x, const void* blob, int32
 }
 
 hipError_t launch_fused_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p, int layout, int mode,
-                             const Int8Epilogue& q8, hipStream_t s) {
+                             const Int8Epilogue& q8, const Scratch& scratch, hipStream_t s) {
     if (layout == WG_NHWC && p.C <= kNarrowChannels) return launch_narrow_conv(x, blob, y, p, mode, q8, s);
-    const BlobLayout bl = blob_layout(p.Kp, p.C, mode);
+    const BlobLayout bl = blob_layout(p.Kp, p.Cf, mode);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
-    // The streaming variant of the role-specialised kernel when every workgroup gets at least six
-    // tile blocks to stream over (measured: +10-17 % on the large layers; with fewer, the fill
-    // and drain of its pipeline cost more than the overlap saves), or when a test asks for it.
-    const bool can_stream = layout == WG_NHWC && p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0 && (p.K & 3) == 0;
-    const int tile_blocks = ceil_div(p.T, kFusedTiles), filter_blocks = p.Kp / kFusedFilters;
-    // The 64-filter form of that kernel (see below for when it applies) is also the fastest form for a layer with one
-    // channel block as soon as the 32-filter grid exceeds one round of the compute units, whatever the number of tile
-    // blocks per workgroup (56x56x64 at N = 12 .. 48: 8-30 % ahead of the limb-pair and 64-filter four-wave kernels).
-    const int stream_variant = g_stream_variant.load(std::memory_order_relaxed);
-    const bool whole64 = (p.K & 63) == 0 || (p.K & 63) > 32;   // padding to 64 filters adds no 32-filter block of nothing
-    const bool wide_one_block = can_stream && p.CB == 1 && whole64 && stream_variant == 0 &&
-                                (long long)tile_blocks * filter_blocks > compute_units();
-    // Scaled mode, one channel block, a 32-filter grid of at most one round: the streaming kernel's 32-filter form with
-    // one tile block per workgroup (its eight waves: four transform, four multiply) is 10-14 % ahead of the four-wave
-    // kernel (56x56x64 at N = 8: 9.3 -> 8.5 us); lossless mode has the limb-pair kernel for these layers.
-    const bool forced_stream = g_stream_workgroups.load(std::memory_order_relaxed) > 0;
-    const bool narrow_one_round = can_stream && mode == WG_SCALED && p.CB == 1 && stream_variant == 0 && !forced_stream &&
-                                  (long long)tile_blocks * filter_blocks <= compute_units();
-    const bool streams = can_stream && (forced_stream || wide_one_block || narrow_one_round ||
-                                        tile_blocks >= 6 * stream_workgroups(tile_blocks, filter_blocks));
-    // Lossless mode, channels-last, one channel block, too few tile blocks to stream over: the limb-pair form (eight waves
-    // per 16 tiles x 32 filters, lossless_conv.hip) against this file's four-wave forms, by rounds of the compute units:
-    // measured on 56x56x64 layers, a round of the former takes 6.5 us, a round of the latter 7.4 us with 32 filters per
-    // workgroup (a grid of at most one round) and 11.7 us with 64 filters.
-    if (mode == WG_LOSSLESS && !streams) {
-        const int form = lossless_pair_conv_choice(x, p, layout);   // 0: not applicable or switched off, 1: the library decides, 2: forced
-        const long long w32 = (long long)tile_blocks * filter_blocks, cus = compute_units();
-        const double pair_cost = 6.5 * (double)((w32 + cus - 1) / cus);
-        const double here_cost = w32 <= cus ? 7.4 : 11.7 * (double)((w32 / 2 + cus - 1) / cus);
-        if (form == 2 || (form == 1 && p.CB == 1 && pair_cost < here_cost)) return launch_lossless_pair_conv(x, blob, y, p, q8, s);
-    }
-    // Channels-last, K % 4 = 0, several channel blocks: the role-specialised kernel with eight product waves and 64 filters
-    // per workgroup, as soon as the 32-filter grid would need more than one round of the compute units (with a 64-filter
-    // grid of at most half the compute units the 32-filter form, which then fills the chip in one round, stays ahead).
-    // Measured on the layers of the VGG-16-shaped stack at N = 16 and on the 128-, 256- and 512-channel configurations.
-    // Scaled mode: 15-30 % faster than the streaming, 64-filter four-wave and 32-filter role-specialised forms wherever
-    // there are two or more channel blocks.  Lossless mode (twice the matrix-core work and filter bytes per product):
-    // +10-25 % with two or more channel blocks where the layer is too small to stream; where it streams, the streaming
-    // kernel's 64-filter form is level (two blocks) or 4 % ahead (four blocks) and takes the layer.
-    if (layout == WG_NHWC && p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0 && (p.K & 3) == 0) {
-        const int variant = g_scaled_variant.load(std::memory_order_relaxed);
-        const long long wide_grid = (long long)tile_blocks * (p.Kp / (2 * kFusedFilters));
-        // scaled mode also with one channel block, where the 64-filter grid is a single round and the 32-filter grid is not
-        // (56x56x64 at N = 16: 11.4 -> 10.9 us against the streaming kernel's 64-filter form)
-        const bool deep_enough = (p.CB >= 2 && (mode == WG_SCALED || !streams)) ||
-                                 (mode == WG_SCALED && wide_grid <= compute_units());
-        if (variant == 1 || (variant == 0 && deep_enough && 2 * wide_grid > compute_units()))
-            return q8.out != nullptr ? launch_roles_mode<true>(x, b, bl, y, p, mode, q8, s, true)
-                                     : launch_roles_mode<false>(x, b, bl, y, p, mode, q8, s, true);
-    }
-    if (streams) {
-        // the 64-filter form: lossless mode, or one channel block (see the kernel), unless the padding to 64 filters
-        // would add a 32-filter block of nothing
-        const bool wide = !narrow_one_round && (mode == WG_LOSSLESS || p.CB == 1) &&
-                          (stream_variant == 1 || (stream_variant == 0 && whole64));
-        if (mode == WG_LOSSLESS) {
-            if (wide) return q8.out ? launch_stream<WG_LOSSLESS, true, true>(x, b, bl, y, p, q8, s) : launch_stream<WG_LOSSLESS, false, true>(x, b, bl, y, p, q8, s);
-            return q8.out ? launch_stream<WG_LOSSLESS, true>(x, b, bl, y, p, q8, s) : launch_stream<WG_LOSSLESS, false>(x, b, bl, y, p, q8, s);
-        }
-        if (wide) return q8.out ? launch_stream<WG_SCALED, true, true>(x, b, bl, y, p, q8, s) : launch_stream<WG_SCALED, false, true>(x, b, bl, y, p, q8, s);
-        return q8.out ? launch_stream<WG_SCALED, true>(x, b, bl, y, p, q8, s) : launch_stream<WG_SCALED, false>(x, b, bl, y, p, q8, s);
-    }
-    // Transform and products on separate waves (channels-last with 4-byte pixel loads): with
-    // several channel blocks and no more 32-filter workgroups than compute units (where the
-    // 64-filter variant would leave units idle), and in scaled mode from four channel blocks on
-    // when the grid is at least three rounds of the compute units (there the product waves do no
-    // vector work per block; measured on 256- and 512-channel layers: 10 % faster than the
-    // 64-filter variant, while in lossless mode, with two channel blocks, or with a grid of one
-    // or two rounds the 64-filter variant stays ahead).
-    const long long workgroups = (long long)ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters);
-    if (layout == WG_NHWC && p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0 && p.CB >= 2 &&
-        (workgroups <= compute_units() || (mode == WG_SCALED && p.CB >= 4 && workgroups >= 3 * compute_units())))
-        return q8.out != nullptr ? launch_roles_mode<true>(x, b, bl, y, p, mode, q8, s)
-                                 : launch_roles_mode<false>(x, b, bl, y, p, mode, q8, s);
-    return q8.out != nullptr ? launch_layout<true>(x, b, bl, y, p, layout, mode, q8, s)
-                             : launch_layout<false>(x, b, bl, y, p, layout, mode, q8, s);
+    const Plan plan = plan_conv(p, layout, mode, false, scratch.bytes);
+    RolesCall c = {x, nullptr, b, bl, y, p, layout, q8};
+    int32_t* partial;
+    hipError_t status;
+    if (make_fast_call(c, plan, layout, scratch, partial, s, status) && (status != hipSuccess || run_roles(c, mode, plan, partial, s, status)))
+        return status;
+    return q8.out != nullptr ? launch_layout<true>(c.x, b, bl, y, c.p, layout, mode, q8, s)
+                             : launch_layout<false>(c.x, b, bl, y, c.p, layout, mode, q8, s);
 }
 
 }  // namespace wg

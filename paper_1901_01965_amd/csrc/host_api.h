@@ -5,8 +5,15 @@
 
 namespace wg {
 
-// winograd_conv2d_int8 where winograd_conv2d_path() is the single kernel, which needs no workspace.
-int conv2d_int8_single_kernel(const int8_t* x, const void* packed, int32_t* y, int N, int C, int H, int W, int K, int layout,
-                              int mode, void* stream);
+// Scratch memory with which the single-kernel path runs this convolution best (0: it has no use for any), and its entry
+// points with that memory: 256-byte aligned, for this call alone while it runs; null / fewer bytes are accepted and only
+// cost time.
+size_t conv2d_scratch_bytes(int N, int C, int H, int W, int K, int layout, int mode, int is_unsigned);
+int conv2d_int8_with_scratch(const int8_t* x, const void* packed, int32_t* y, int N, int C, int H, int W, int K, int layout,
+                             int mode, void* scratch, size_t scratch_bytes, void* stream);
+int conv2d_int8_requant_with_scratch(const int8_t* x, const void* packed, int8_t* out, int N, int C, int H, int W, int K, int layout,
+                                     int mode, int shift, int relu, int pool, void* scratch, size_t scratch_bytes, void* stream);
+int conv2d_u8_with_scratch(const uint8_t* x, int zero_point, const void* packed, int32_t* y, int N, int C, int H, int W, int K,
+                           int layout, int mode, void* scratch, size_t scratch_bytes, void* stream);
 
 }  // namespace wg

@@ -92,11 +92,45 @@ __device__ inline void request_patch(__amdgpu_buffer_rsrc_t xbuf, const Problem&
             patch[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, pixel[i], cb * kCBlock, 0);
     }
 }
-// u = x + 128 on every byte; what does not exist arrived as zeros, i.e. x = 0.
-__device__ inline void bias_buffer_patch(uint32_t patch[6][6]) {
+// What remains to be done to a patch loaded that way: u = x + bias on every byte.  Pixels outside the image arrived as
+// zero bytes: for signed int8 that is x = 0 like any other byte; for uint8 they have to become the zero point, which
+// one three-input OR per pixel does (row and column terms that are zero inside the image), as many
+// instructions as the XOR of the signed form.  (Channels beyond C meet zero filters, whatever they hold.)
+template <class ENC>
+struct PatchBias;
+template <>
+struct PatchBias<SignedInt8> {
+    __device__ inline void enter(const Problem&, int, int, const SignedInt8) {}
+    __device__ inline void apply(uint32_t patch[6][6]) const {
 #pragma unroll
-    for (int i = 0; i < 36; ++i) patch[i / 6][i % 6] ^= kBiasBytes;
-}
+        for (int i = 0; i < 36; ++i) patch[i / 6][i % 6] ^= kBiasBytes;
+    }
+};
+template <>
+struct PatchBias<ZeroPointU8> {
+    uint32_t outside;      // bit a: patch row a lies outside the image, bit 6 + b: column b (one register while it waits)
+    uint32_t zero_bytes;
+    __device__ inline void enter(const Problem& p, int ty, int tx, const ZeroPointU8 enc) {
+        outside = 0;
+        zero_bytes = enc.zero_bytes;
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            outside |= (unsigned)(4 * ty - 1 + a) < (unsigned)p.H ? 0u : 1u << a;
+            outside |= (unsigned)(4 * tx - 1 + a) < (unsigned)p.W ? 0u : 64u << a;
+        }
+    }
+    __device__ inline void apply(uint32_t patch[6][6]) const {
+        uint32_t row[6], col[6], o = outside;
+        asm volatile("" : "+v"(o));   // the terms are formed here, not ahead of the channel-block loop (36 registers)
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            row[a] = (uint32_t)((int)(o << (31 - a)) >> 31) & zero_bytes;
+            col[a] = (uint32_t)((int)(o << (25 - a)) >> 31) & zero_bytes;
+        }
+#pragma unroll
+        for (int i = 0; i < 36; ++i) patch[i / 6][i % 6] |= row[i / 6] | col[i % 6];
+    }
+};
 
 // Row rule of A^T on (m0, m1, m2, m3, conj(m3), m5) with m0,m1,m2,m5 real:
 //   z0 = m0+m1+m2+2Re m3, z1 = m1-m2-2Im m3, z2 = m1+m2-2Re m3, z3 = m1-m2+2Im m3+m5

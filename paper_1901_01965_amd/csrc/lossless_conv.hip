@@ -304,12 +304,82 @@ __device__ inline void buffer_to_lds_16(__amdgpu_buffer_rsrc_t buffer, int8_t* l
     __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (__attribute__((address_space(3))) int8_t*)lds_dst, 16, voffset, soffset, 0, 0);
 }
 
-// grid (ceil(T/16), Kp/32), 512 threads.
-template <int LOAD, bool Q8>
+// How the eight waves of a workgroup bring the raw patches of their 16 tiles: wave = quad + 4 half, four tiles per quad.
+// Direct transfers (LOAD kLoadDirect): transfer i (0..8) moves pixels 4i .. 4i+3 of the four tiles: lane = 16 (pixel % 4) +
+// 4 (tile % 4) + piece of 16 channels, and the hardware puts lane l's 16 bytes at (uniform destination) + 16 l, so the raw
+// area is [pixel][tile % 4][64 channels].  Waves 0-3 issue transfers 0..4, waves 4-7 transfers 5..8.
+// Otherwise every thread loads the 36 pixels of its tile and four channels itself.
+template <int LOAD>
+struct RawPatch {
+    int8_t* area;                                    // of the quad
+    uint32_t raw_off[LOAD == kLoadDirect ? 5 : 1];   // this lane's piece in each of the wave's transfers
+    uint32_t pixel[LOAD == kLoadDwords ? 36 : 1];    // or this thread's 36 pixels
+    int first_transfer, transfers, channel;          // channel: first one of this lane's pieces
+    __device__ inline void init(const Problem& p, int8_t* lds, int tile0, int quad, int half, int lane) {
+        area = lds + kPlanesBytes + quad * kRawQuad;
+        first_transfer = half == 0 ? 0 : 5;
+        transfers = half == 0 ? 5 : 4;
+        const int t = tile0 + 4 * quad + (LOAD == kLoadDirect ? (lane >> 2) & 3 : lane >> 4);
+        int n = 0, ty = 0, tx = 0;
+        if (t < p.T) decode_tile(p, t, n, ty, tx);
+        if constexpr (LOAD == kLoadDirect) {
+            channel = 16 * (lane & 3);
+#pragma unroll
+            for (int j = 0; j < 5; ++j)
+                raw_off[j] = pixel_offset(p, t < p.T, n, ty, tx, 4 * (first_transfer + j) + (lane >> 4), channel);
+        } else {
+            channel = 4 * (lane & 15);
+            patch_offsets(p, n, ty, tx, channel, pixel);
+            if (t >= p.T) {
+#pragma unroll
+                for (int i = 0; i < 36; ++i) pixel[i] = kOutsideOffset;
+            }
+        }
+    }
+    // Channel block cb.  In the last block of a C that is not a multiple of 64 (a uniform branch) lanes whose
+    // channels lie beyond C ask for the outside offset and get zeros.
+    __device__ inline void request(__amdgpu_buffer_rsrc_t xbuf, const Problem& p, int cb, uint32_t (&u)[6][6]) const {
+        const bool tail = (cb + 1) * kCBlock > p.C;
+        const bool have = !tail || cb * kCBlock + channel < p.C;
+        if constexpr (LOAD == kLoadDirect) {
+#pragma unroll
+            for (int j = 0; j < 5; ++j)
+                if (j < transfers)
+                    buffer_to_lds_16(xbuf, area + (first_transfer + j) * 1024, have ? raw_off[j] : kOutsideOffset, cb * kCBlock);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 36; ++i)
+                u[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, have ? pixel[i] : kOutsideOffset, cb * kCBlock, 0);
+        }
+    }
+    // Waits for what was requested; afterwards (`again`: this is not the first block) everyone is done reading the
+    // previous block's planes as well.
+    __device__ inline void take(bool again, int lane, uint32_t (&u)[6][6]) const {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (LOAD == kLoadDirect || again) {
+            // the raw pieces of a wave's tiles were moved by two waves
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+        }
+        if constexpr (LOAD == kLoadDirect) {
+#pragma unroll
+            for (int i = 0; i < 36; ++i) u[i / 6][i % 6] = *reinterpret_cast<const uint32_t*>(area + i * kRawPixel + 4 * lane);
+        }
+    }
+};
+
+// grid (ceil(T/16), Kp/32, splits), 512 threads.
+// OUT kOutSums: the workgroup takes `blocks` channel blocks from blockIdx.z * blocks on and leaves the sum of its outputs,
+// before the rescale by 2^-4, at y as int32 [blockIdx.z][16 gridDim.x tiles][output 4i+j][Kp] (the output transform is
+// linear, so these add up to the whole; sums_finish_kernel adds, rescales and stores).
+constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2;
+template <int LOAD, int OUT>
 __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                             size_t pairs_off, int32_t* __restrict__ y, Problem p,
-                                                            Int8Epilogue q8) {
+                                                            Int8Epilogue q8, int blocks) {
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
+    constexpr bool Q8 = OUT == kOutInt8;
+    const int cb_first = OUT == kOutSums ? (int)blockIdx.z * blocks : 0, cb_end = OUT == kOutSums ? min(cb_first + blocks, p.CB) : p.CB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tile0 = blockIdx.x * kTileBlock;
     const int k0 = blockIdx.y * kBlockFilters;
@@ -320,49 +390,10 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     // Transform thread: tile 4 (wave % 4) + lane / 16, channels 4 (lane % 16) .. + 3, rows by wave / 4.
     const int quad = wave & 3, half = wave >> 2;   // the same split serves the product phase: filters 8 quad .. + 7, half of the entries
     const int a_tile = 4 * quad + (lane >> 4), a_cq = lane & 15;
-    int8_t* const raw_quad = lds + kPlanesBytes + quad * kRawQuad;
-    uint32_t raw_off[LOAD == kLoadDirect ? 5 : 1];   // this lane's piece in each of the wave's transfers
-    uint32_t pixel[LOAD == kLoadDwords ? 36 : 1];    // or this thread's 36 pixels
+    RawPatch<LOAD> raw;
+    raw.init(p, lds, tile0, quad, half, lane);
     uint32_t u[6][6];
-    // Direct transfers: transfer i (0..8) moves pixels 4i .. 4i+3 of the four tiles: lane = 16 (pixel % 4) + 4 (tile % 4)
-    // + piece of 16 channels, and the hardware puts lane l's 16 bytes at (uniform destination) + 16 l, so the raw area
-    // is [pixel][tile % 4][64 channels].  Waves 0-3 issue transfers 0..4, waves 4-7 transfers 5..8.
-    const int first_transfer = half == 0 ? 0 : 5, transfers = half == 0 ? 5 : 4;
-    if constexpr (LOAD == kLoadDirect) {
-        const int dt = tile0 + 4 * quad + ((lane >> 2) & 3);
-        int dn = 0, dty = 0, dtx = 0;
-        if (dt < p.T) decode_tile(p, dt, dn, dty, dtx);
-#pragma unroll
-        for (int j = 0; j < 5; ++j)
-            raw_off[j] = pixel_offset(p, dt < p.T, dn, dty, dtx, 4 * (first_transfer + j) + (lane >> 4), 16 * (lane & 3));
-    } else {
-        const int at = tile0 + a_tile;
-        int an = 0, aty = 0, atx = 0;
-        if (at < p.T) decode_tile(p, at, an, aty, atx);
-        patch_offsets(p, an, aty, atx, 4 * a_cq, pixel);
-        if (at >= p.T) {
-#pragma unroll
-            for (int i = 0; i < 36; ++i) pixel[i] = kOutsideOffset;
-        }
-    }
-    // Channel block cb.  In the last block of a C that is not a multiple of 64 (a uniform branch) lanes whose
-    // channels lie beyond C ask for the outside offset and get zeros.
-    auto request = [&](int cb) {
-        const bool tail = (cb + 1) * kCBlock > p.C;
-        if constexpr (LOAD == kLoadDirect) {
-            const bool have = !tail || cb * kCBlock + 16 * (lane & 3) < p.C;
-#pragma unroll
-            for (int j = 0; j < 5; ++j)
-                if (j < transfers)
-                    buffer_to_lds_16(xbuf, raw_quad + (first_transfer + j) * 1024, have ? raw_off[j] : kOutsideOffset, cb * kCBlock);
-        } else {
-            const bool have = !tail || cb * kCBlock + 4 * a_cq < p.C;
-#pragma unroll
-            for (int i = 0; i < 36; ++i)
-                u[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, have ? pixel[i] : kOutsideOffset, cb * kCBlock, 0);
-        }
-    };
-    request(0);
+    raw.request(xbuf, p, cb_first, u);
     // the blob header: requested now, looked at after the transform, so its latency hides behind the patch's
     __builtin_amdgcn_sched_barrier(0);
     const BlobHeaderWords header = read_blob_header(blob);
@@ -376,7 +407,7 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     const int8_t* const flt0 = reinterpret_cast<const int8_t*>(blob + pairs_off) +
                                filter_pair_offset(0, 0, k0 + kPairFilters * quad, 0, 0, p.Kp) + (lane & 15) * kCBlock + (lane >> 4) * 16;
     const size_t flt_block = (size_t)(p.Kp >> 3) * kPairValues * kFilterFragBytes;
-    cx.flt = flt0;
+    cx.flt = flt0 + cb_first * flt_block;
 
     v2i Y[16];
 #pragma unroll
@@ -385,36 +416,24 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     Products<0> products0;
     Products<1> products1;
     WG_STAMP(1);
-    for (int cb = 0; cb < p.CB; ++cb) {
+    for (int cb = cb_first; cb < cb_end; ++cb) {
         // This wave's share of the raw patch (or its 36 pixels) has arrived.  The filter fragments are only requested
         // now, so that at the start of the kernel, when every workgroup of the grid asks at once, the patches do not
         // share the memory system with them; the transform gives the fragments time enough to arrive.
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if constexpr (LOAD == kLoadDirect) {
-            // the raw pieces of a wave's tiles were moved by two waves; from the second block on the barrier also
-            // says that everyone is done reading the previous block's planes
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            WG_STAMP(2);
-#pragma unroll
-            for (int i = 0; i < 36; ++i)
-                u[i / 6][i % 6] = *reinterpret_cast<const uint32_t*>(raw_quad + i * kRawPixel + 4 * lane);
-        } else if (cb > 0) {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-        }
+        raw.take(cb > cb_first, lane, u);
+        WG_STAMP(2);
         // the first kRing filter fragments are requested at ten places spread over the transform
         static_assert(kRing == 10, "transform_rows calls its tick ten times");
         if (half == 0) transform_rows<0>(u, out, [&](auto I) { products0.template prefetch_one<I>(cx); });
         else           transform_rows<1>(u, out, [&](auto I) { products1.template prefetch_one<I>(cx); });
-        if (cb == 0 && !blob_matches(header, p.K, p.C, WG_LOSSLESS)) return;   // uniform: nobody reaches the next barrier
+        if (cb == cb_first && !blob_matches(header, p.K, p.Cf, WG_LOSSLESS)) return;   // uniform: nobody reaches the next barrier
         // the operand planes are complete once every wave's LDS writes have landed (and every wave has read its
         // raw patch); global requests stay in flight across the barrier
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         WG_STAMP(3);
         __builtin_amdgcn_s_barrier();
         WG_STAMP(4);
-        if (cb + 1 < p.CB) request(cb + 1);   // travels while this block's products run
+        if (cb + 1 < cb_end) raw.request(xbuf, p, cb + 1, u);   // travels while this block's products run
         if (half == 0) products0.run(cx, Y); else products1.run(cx, Y);
         cx.flt += flt_block;
         WG_STAMP(5);
@@ -439,10 +458,17 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     if (t < p.T) decode_tile(p, t, n, ty, tx);
     const int row = 4 * ty, col = 4 * tx + j;
     const bool live = t < p.T && col < p.W && kk < p.K;
-    auto staged = [&](int o) {   // finished outputs of the thread's four filters at output o of its tile
+    auto sixteen = [&](int o) {   // 16 x the finished outputs of the thread's four filters at output o of its tile
         const int at = o * kStageOut + tile * kStageRow + 4 * k4;
-        return (*reinterpret_cast<const v4i*>(stage + at) + *reinterpret_cast<const v4i*>(stage + kStageHalf + at)) >> 4;
+        return *reinterpret_cast<const v4i*>(stage + at) + *reinterpret_cast<const v4i*>(stage + kStageHalf + at);
     };
+    auto staged = [&](int o) { return sixteen(o) >> 4; };
+    if constexpr (OUT == kOutSums) {
+        v4i* const to = reinterpret_cast<v4i*>(y) + ((((size_t)blockIdx.z * gridDim.x * kTileBlock + t) * 16 + j) * p.Kp + kk) / 4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) to[(size_t)r * p.Kp] = sixteen(4 * r + j);
+        return;
+    }
     if constexpr (!Q8) {
         int32_t* const first = y + ((size_t)(n * p.H + row) * p.W + col) * p.K + kk;
         const bool vector_store = (p.K & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
@@ -497,13 +523,154 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     WG_STAMP(7);
 }
 
-template <int LOAD, bool Q8>
+// ---- scaled mode, split channels ---------------------------------------------------------------------
+// The same eight-wave structure for layers with few tiles in scaled mode (Section 4.2), whose channel blocks are dealt to
+// several workgroups: the filters are single int8 values, so a fragment is 16 filters, and the channel sums have to be
+// complete before they are scaled back, so the workgroup leaves them as they are.  Wave = filter group of 16 (wave & 1) and a
+// quarter of the entries (wave >> 1), 28 matrix-core instructions per channel block each:
+//   quarters 0, 1: six real entries and two complex ones, quarters 2, 3: two and three.
+// A complex entry multiplies with Wr and Wi only (Di Wi in accumulators of its own); every limb product keeps its
+// accumulator across the channel blocks, so a block costs no vector work but the transform.  All eight to ten fragments of
+// a wave and block are in flight before its transform ends.
+constexpr int quarter_slots(int q) { return q < 2 ? 8 : 5; }
+constexpr int quarter_entry(int q, int s) {
+    if (q < 2) return s < 6 ? 6 * q + s : kRealEntries + 2 * q + s - 6;
+    return s < 2 ? 12 + 2 * (q - 2) + s : kRealEntries + 4 + 3 * (q - 2) + s - 2;
+}
+constexpr int quarter_frag(int q, int s) {   // fragments before slot s
+    int n = 0;
+    for (int i = 0; i < s; ++i) n += entry_fragments(quarter_entry(q, i));
+    return n;
+}
+constexpr int quarter_acc(int q, int s) {    // accumulators before slot s: (h, l), or Dr Wr, Im, Di Wi as (h, l) each
+    int n = 0;
+    for (int i = 0; i < s; ++i) n += real_entry(quarter_entry(q, i)) ? 2 : 6;
+    return n;
+}
+template <int Q>
+struct QuarterProducts {
+    static constexpr int NS = quarter_slots(Q), NF = quarter_frag(Q, NS), NA = quarter_acc(Q, NS);
+    static_assert(NF <= 10, "a wave's fragments are requested at the ten ticks of the transform");
+    v4i w[NF], acc[NA];
+    __device__ inline void clear() {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) acc[i] = (v4i){0, 0, 0, 0};
+    }
+    template <int I>
+    __device__ inline void prefetch_one(const int8_t* flt) {
+        if constexpr (I < NF) {
+            __builtin_amdgcn_sched_barrier(0);
+            constexpr auto plane = [] {   // blob plane of fragment I: real entry p: p; complex entry j: 16 + 3j (Wr), + 1 (Wi)
+                int s = 0;
+                while (quarter_frag(Q, s + 1) <= I) ++s;
+                const int e = quarter_entry(Q, s);
+                return real_entry(e) ? e : kRealEntries + 3 * (e - kRealEntries) + (I - quarter_frag(Q, s));
+            }();
+            w[I] = *reinterpret_cast<const v4i*>(flt + plane * kFilterFragBytes);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __device__ inline void run(const int8_t* act) {
+        v4i d[2][4];
+        auto load = [&](auto S) {
+            constexpr int e = quarter_entry(Q, S);
+            static_for<2 * entry_fragments(e)>(
+                [&](auto I) { d[S & 1][I] = *reinterpret_cast<const v4i*>(act + (entry_plane(e) + I) * kPlaneBytes); });
+        };
+        load(std::integral_constant<int, 0>{});
+        static_for<NS>([&](auto S) {
+            constexpr int e = quarter_entry(Q, S), f = quarter_frag(Q, S), a = quarter_acc(Q, S);
+            if constexpr (S + 1 < NS) load(std::integral_constant<int, S + 1>{});
+            auto mac = [&](int to, int filter, int from) {
+                acc[a + to] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[f + filter], d[S & 1][from], acc[a + to], 0, 0, 0);
+            };
+            mac(0, 0, 0);
+            mac(1, 0, 1);
+            if constexpr (!real_entry(e)) {   // d = (Dr h, Dr l, Di h, Di l)
+                mac(2, 0, 2);
+                mac(3, 0, 3);
+                mac(4, 1, 2);
+                mac(5, 1, 3);
+                mac(2, 1, 0);
+                mac(3, 1, 1);
+            }
+        });
+    }
+    // lane = tile (lane & 15) x four filters: one 16-byte store per sum
+    __device__ inline void store(v4i* to, size_t plane) const {
+        static_for<NS>([&](auto S) {
+            constexpr int e = quarter_entry(Q, S), a = quarter_acc(Q, S);
+            if constexpr (real_entry(e)) {
+                to[e * plane] = (acc[a] << kByteLimbShift) + acc[a + 1];
+            } else {
+                constexpr int at = kRealEntries + 2 * (e - kRealEntries);
+                to[at * plane] = ((acc[a] - acc[a + 4]) << kByteLimbShift) + (acc[a + 1] - acc[a + 5]);
+                to[(at + 1) * plane] = (acc[a + 2] << kByteLimbShift) + acc[a + 3];
+            }
+        });
+    }
+};
+
+// grid (ceil(T/16), Kp/32, splits), 512 threads; sums: int32 [split][36][16 gridDim.x tiles][Kp].
+template <int LOAD>
+__global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t planes_off,
+                                                          int32_t* __restrict__ sums, Problem p, int blocks) {
+    extern __shared__ __attribute__((aligned(16))) int8_t lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tile0 = blockIdx.x * kTileBlock, k0 = blockIdx.y * kBlockFilters;
+    const int cb_first = (int)blockIdx.z * blocks, cb_end = min(cb_first + blocks, p.CB);
+    const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
+    const int quad = wave & 3, half = wave >> 2;   // of the transform
+    const int a_tile = 4 * quad + (lane >> 4), a_cq = lane & 15;
+    RawPatch<LOAD> raw;
+    raw.init(p, lds, tile0, quad, half, lane);
+    uint32_t u[6][6];
+    raw.request(xbuf, p, cb_first, u);
+    __builtin_amdgcn_sched_barrier(0);
+    const BlobHeaderWords header = read_blob_header(blob);
+    __builtin_amdgcn_sched_barrier(0);
+    OperandSplitter<kSplitByteLimbs, LdsPlaneSink> out;
+    out.sink.base = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
+    const int8_t* const act = lds + lds_slot(lane >> 4, lane & 15) * 16;
+    constexpr int NP = 46;
+    const int kgroup = k0 + 16 * (wave & 1);
+    const size_t flt_block = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
+    const int8_t* flt = reinterpret_cast<const int8_t*>(blob + planes_off) + filter_plane_offset(0, 0, kgroup + (lane & 15), (lane >> 4) * 16, p.Kp, NP) +
+                        cb_first * flt_block;
+    // one loop per quarter (the same barriers in all four), so that each is allocated registers on its own
+    auto blocks_of = [&](auto Q) {
+        QuarterProducts<Q> products;
+        products.clear();
+        for (int cb = cb_first; cb < cb_end; ++cb) {
+            raw.take(cb > cb_first, lane, u);
+            auto tick = [&](auto I) { products.template prefetch_one<I>(flt); };
+            if (half == 0) transform_rows<0>(u, out, tick); else transform_rows<1>(u, out, tick);
+            if (cb == cb_first && !blob_matches(header, p.K, p.Cf, WG_SCALED)) return;   // uniform: nobody reaches the next barrier
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            if (cb + 1 < cb_end) raw.request(xbuf, p, cb + 1, u);
+            products.run(act);
+            flt += flt_block;
+        }
+        const size_t tiles = (size_t)gridDim.x * kTileBlock, plane = tiles * p.Kp / 4;   // in units of four sums
+        products.store(reinterpret_cast<v4i*>(sums) + (size_t)blockIdx.z * kAccPlanes * plane +
+                           ((size_t)(tile0 + (lane & 15)) * p.Kp + kgroup + 4 * (lane >> 4)) / 4, plane);
+    };
+    switch (wave >> 1) {
+        case 0: blocks_of(std::integral_constant<int, 0>{}); break;
+        case 1: blocks_of(std::integral_constant<int, 1>{}); break;
+        case 2: blocks_of(std::integral_constant<int, 2>{}); break;
+        default: blocks_of(std::integral_constant<int, 3>{}); break;
+    }
+}
+
+template <int LOAD, int OUT>
 hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p,
-                  const Int8Epilogue& q8, hipStream_t s) {
+                  const Int8Epilogue& q8, hipStream_t s, int blocks = 0, int splits = 1) {
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LOAD, Q8>), kLdsBytes)) return e;
-    dim3 grid(ceil_div(p.T, kTileBlock), p.Kp / kBlockFilters);
-    lossless_pair_kernel<LOAD, Q8><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, blob, bl.pairs_off, y, p, q8);
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LOAD, OUT>), kLdsBytes)) return e;
+    dim3 grid(ceil_div(p.T, kTileBlock), p.Kp / kBlockFilters, splits);
+    lossless_pair_kernel<LOAD, OUT><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, blob, bl.pairs_off, y, p, q8, blocks);
     return hipGetLastError();
 }
 
@@ -528,12 +695,36 @@ int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout) {
 
 hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p,
                                      const Int8Epilogue& q8, hipStream_t s) {
-    const BlobLayout bl = blob_layout(p.Kp, p.C, WG_LOSSLESS);
+    const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
     const bool direct = p.C % 16 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
     if (q8.out != nullptr)
-        return direct ? launch<kLoadDirect, true>(x, b, bl, y, p, q8, s) : launch<kLoadDwords, true>(x, b, bl, y, p, q8, s);
-    return direct ? launch<kLoadDirect, false>(x, b, bl, y, p, q8, s) : launch<kLoadDwords, false>(x, b, bl, y, p, q8, s);
+        return direct ? launch<kLoadDirect, kOutInt8>(x, b, bl, y, p, q8, s) : launch<kLoadDwords, kOutInt8>(x, b, bl, y, p, q8, s);
+    return direct ? launch<kLoadDirect, kOutInt32>(x, b, bl, y, p, q8, s) : launch<kLoadDwords, kOutInt32>(x, b, bl, y, p, q8, s);
+}
+
+hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s) {
+    const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
+    const uint8_t* b = static_cast<const uint8_t*>(blob);
+    if (p.C % 16 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0)
+        return launch<kLoadDirect, kOutSums>(x, b, bl, sums, p, no_int8_epilogue(), s, blocks, splits);
+    return launch<kLoadDwords, kOutSums>(x, b, bl, sums, p, no_int8_epilogue(), s, blocks, splits);
+}
+
+hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s) {
+    const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
+    const dim3 grid(ceil_div(p.T, kTileBlock), p.Kp / kBlockFilters, splits);
+    auto go = [&](auto kernel, auto&) -> hipError_t {
+        static LdsLimitOnce lds_limit;   // per kernel: the lambda's body is instantiated once per argument type
+        constexpr int lds_bytes = kPlanesBytes + 4 * kRawQuad;
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(kernel), lds_bytes)) return e;
+        kernel<<<grid, 64 * kWaves, lds_bytes, s>>>(x, static_cast<const uint8_t*>(blob), bl.planes_off, sums, p, blocks);
+        return hipGetLastError();
+    };
+    std::integral_constant<int, kLoadDirect> direct;
+    std::integral_constant<int, kLoadDwords> dwords;
+    if (p.C % 16 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) return go(&scaled_sums_kernel<kLoadDirect>, direct);
+    return go(&scaled_sums_kernel<kLoadDwords>, dwords);
 }
 
 }  // namespace wg

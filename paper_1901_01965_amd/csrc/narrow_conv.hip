@@ -202,7 +202,7 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
     // SIMD evenly: two waves on each of the 1,024 SIMDs (two cover each other's LDS and memory
     // waits; a third would only add transform phases with mostly idle lanes).
     const long long work = (long long)p.T * (p.Kp / 64);
-    const int tiles = (int)std::min<long long>(kNarrowTiles, std::max<long long>(8, (work + 2047) / 2048));
+    const int tiles = (int)std::min<long long>(kNarrowTiles, std::max<long long>(2, (work + 2047) / 2048));
     dim3 grid(ceil_div(p.T, tiles), p.Kp / 64);
     narrow_conv_kernel<MODE, Q8><<<grid, 64, 0, s>>>(x, blob, bl.table_off, bl.narrow_off, y, p, q8, tiles);
     return hipGetLastError();

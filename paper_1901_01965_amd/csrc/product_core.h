@@ -12,7 +12,6 @@ constexpr int kFusedTiles = kTileBlock;   // tiles per workgroup (rows of the 16
 constexpr int kFusedFilters = 32;   // filters per workgroup: two 16-wide column blocks
 constexpr int kFusedPlanes = 72;    // two-limb activation planes (kSplitTwoLimb)
 constexpr int kLdsBytes = kFusedPlanes * kPlaneBytes;
-constexpr int kParkBytes = 4 * 16 * 64 * 16;         // four waves x 16 outputs x 64 lanes x 4 registers
 // How the activation patch reaches the transform threads (chosen on the host):
 //   kLoadBytes:  one byte per load, any layout and channel count;
 //   kLoadDwords: channels-last, C a multiple of 4: one 4-byte load per pixel and thread;
@@ -22,7 +21,15 @@ constexpr int kParkBytes = 4 * 16 * 64 * 16;         // four waves x 16 outputs 
 constexpr int kLoadBytes = 0, kLoadDwords = 1, kLoadDirect = 2;
 constexpr int kRawWaveBytes = 4 * 36 * kCBlock;      // raw patches of a wave's four tiles: 36 pixels x 64 channels
 constexpr int kRawBytes = 4 * kRawWaveBytes;
-static_assert(kParkBytes <= kLdsBytes, "output staging reuses the operand planes' LDS");
+
+// Development aid (never compiled into the library): time spent in each part of a kernel's loop.
+#ifdef WG_TIMESTAMPS
+__device__ unsigned long long* g_roles_stamps = nullptr;
+#define WG_CLOCK() __builtin_amdgcn_s_memtime()
+#define WG_SPENT(i, since) do { const unsigned long long now_ = WG_CLOCK(); spent[i] += now_ - (since); (since) = now_; } while (0)
+#else
+#define WG_SPENT(i, since) do { } while (0)
+#endif
 
 // ---- per-entry programs ----------------------------------------------------------------
 // An entry's product uses a few activation fragments (from LDS) and filter fragments (from
@@ -404,196 +411,197 @@ struct ScaledSums {
 constexpr int kChannelSums = 18;
 static_assert(ScaledSums<0>::kSums == kChannelSums && ScaledSums<1>::kSums == kChannelSums, "both halves keep 18 sums");
 
-// Who a thread is when the four product waves store their outputs, and where its tile lies.
+// Who a thread is when 256 threads store the staged outputs of 16 tiles x 32 filters, and where its tile lies.
 struct StoreContext {
-    int8_t* lds;
-    int tid, lane, wave, half, kblock;          // within the four waves that hold the outputs
+    int8_t* lds;                                // the staged outputs
+    int tid, lane;                              // within the four waves that store together
     int my_n, my_row, my_col, my_origin;        // of tile (lane & 15): image, first output row and column, offset in y (-1: none)
     int rnd;                                    // rounding added before the final >> 4
     int32_t* y;
 };
 
-// Adds the two row halves and stores the 16 tiles x 32 filters (from kbase) whose partial outputs
-// the four waves hold in Yp.  All four waves call it together (it contains one barrier).
-// PART 1 / PART 2 (channels-last with K % 4 = 0 only): just the staging of Yp into LDS / just
-// the adding and storing of what was staged, for callers that put their own barrier between
-// the two and may run them on different waves.  PART 3: PART 2 for a caller whose waves own every
-// entry and staged one finished copy (in the place of half 0): nothing is added.
-template <int LAYOUT, bool Q8, int PART = 0>
-__device__ __forceinline__ void store_block(const StoreContext& sc, const Problem& p, const Int8Epilogue& q8,
-                                            const v4i (&Yp)[16], int kbase) {
-    int8_t* const lds = sc.lds;
-    const int tid = sc.tid, lane = sc.lane, wave = sc.wave, half = sc.half, kblock = sc.kblock;
-    const int my_n = sc.my_n, my_row = sc.my_row, my_col = sc.my_col, my_origin = sc.my_origin, rnd = sc.rnd;
-    int32_t* const y = sc.y;
-    int* parki = reinterpret_cast<int*>(lds);
-    (void)wave; (void)my_n;
-    if (LAYOUT == WG_NHWC && (p.K & 3) == 0) {
-        // Channels-last with K a multiple of four: outputs are staged filter-fastest,
-        // stage[half][output 4i+j][tile][36] (32 filters, rows padded to 36 dwords so that the
-        // four 16-lane groups of a wave land in different banks), then every thread adds the
-        // halves for four consecutive filters and stores 16 bytes; eight lanes cover the 128
-        // contiguous bytes this block owns of a pixel.
-        constexpr int kRow = 36, kHalf = 16 * 16 * kRow;
-        static_assert(2 * kHalf * 4 <= kLdsBytes, "staging fits the operand planes' LDS");
-        // the second half's staged copy of four consecutive filters (none with PART 3)
-        auto other_half = [&](int at) {
-            if constexpr (PART == 3) return (v4i){0, 0, 0, 0};
-            else return *reinterpret_cast<const v4i*>(parki + kHalf + at);
-        };
-        if constexpr (PART < 2) {
-            int* dst = parki + half * kHalf + (4 * (lane >> 4)) * kRow + kblock * 16 + (lane & 15);
+// Outputs are staged filter-fastest, stage[half][output 4i+j][tile][36] (32 filters, rows padded to 36 dwords so that the
+// four 16-lane groups of a wave land in different banks): wave (half, kblock) holds outputs of filters 16 kblock .. + 15.
+constexpr int kStageRow = 36, kStageHalf = 16 * 16 * kStageRow;   // dwords
+static_assert(2 * kStageHalf * 4 <= kLdsBytes, "staging fits the operand planes' LDS");
+__device__ __forceinline__ void stage_outputs(int8_t* lds, int lane, int half, int kblock, const v4i (&Yp)[16]) {
+    int* dst = reinterpret_cast<int*>(lds) + half * kStageHalf + (4 * (lane >> 4)) * kStageRow + kblock * 16 + (lane & 15);
 #pragma unroll
-            for (int o = 0; o < 16; ++o)
+    for (int o = 0; o < 16; ++o)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) dst[(o * 16 + q) * kRow] = Yp[o][q];
-        }
-        if constexpr (PART == 1) return;
-        if constexpr (PART == 0) __syncthreads();
-        // thread: filters 4*k4..4*k4+3; pass ps: output row i = ps/2, tile = 8*(ps%2) + px/4, column j = px%4
-        const int k4 = tid & 7, px = tid >> 3, j = px & 3;
-        const int kk = kbase + 4 * k4;
-        if constexpr (Q8) {
-            // finished int32 outputs of filters 4*g .. 4*g+3 of the block
-            auto staged = [&](int o, int tile, int g) {
-                const int at = (o * 16 + tile) * kRow + 4 * g;
-                return (*reinterpret_cast<const v4i*>(parki + at) + other_half(at) + rnd) >> 4;
-            };
-            if (q8.pool) {
-                // 16 tiles x 2x2 pooled pixels = 64 pixels; thread: four filters of pixels px and px + 32
+        for (int q = 0; q < 4; ++q) dst[(o * 16 + q) * kStageRow] = Yp[o][q];
+}
+
+// Where tile (lane & 15) of tile block `tile0` starts in an output tensor of pixels (offsets fit 32 bits, checked on the
+// host), into sc.
+template <int LAYOUT>
+__device__ __forceinline__ void locate_tile(StoreContext& sc, const Problem& p, int tile0) {
+    const int t = tile0 + (sc.lane & 15);
+    int n = 0, ty = 0, tx = 0;
+    if (t < p.T) decode_tile(p, t, n, ty, tx);
+    sc.my_n = n;
+    sc.my_row = 4 * ty;
+    sc.my_col = 4 * tx;
+    sc.my_origin = t >= p.T ? -1 : LAYOUT == WG_NHWC ? ((n * p.H + 4 * ty) * p.W + 4 * tx) * p.K : (n * p.K * p.H + 4 * ty) * p.W + 4 * tx;
+}
+
+// Stores the 16 tiles x 32 filters (from kbase) that were staged (a barrier lies between): int32 to y, or requantised
+// (and pooled) to int8 at q8.out.  ADD: two halves were staged and are added; otherwise one finished copy (half 0).
+// Any K and either layout; 16-byte (int8: 4- or 16-byte) stores where K and the alignment allow.
+template <int LAYOUT, bool Q8, bool ADD>
+__device__ __forceinline__ void store_staged(const StoreContext& sc, const Problem& p, const Int8Epilogue& q8, int kbase) {
+    const int tid = sc.tid, lane = sc.lane;
+    const int* const parki = reinterpret_cast<const int*>(sc.lds);
+    // finished outputs of filters 4*g .. 4*g+3 of the block
+    auto staged = [&](int o, int tile, int g) {
+        const int at = (o * 16 + tile) * kStageRow + 4 * g;
+        v4i v = *reinterpret_cast<const v4i*>(parki + at);
+        if constexpr (ADD) v += *reinterpret_cast<const v4i*>(parki + kStageHalf + at);
+        return (v + sc.rnd) >> 4;
+    };
+    auto best_of_window = [&](int tile, int pi, int pj, int g) {   // 2x2 maximum of requantised outputs
+        v4i best = requantise(staged(4 * (2 * pi) + 2 * pj, tile, g), q8);
+        best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi) + 2 * pj + 1, tile, g), q8));
+        best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj, tile, g), q8));
+        return __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj + 1, tile, g), q8));
+    };
+    if constexpr (LAYOUT == WG_NCHW) {
+        // A filter's outputs lie together: sixteen consecutive tiles of an image row are 64 consecutive pixels.
+        if constexpr (!Q8) {
+            // thread: output row i, column j of a tile; iteration: four filters, 256 contiguous bytes per wave and filter
+            const int j = tid & 3, tile = (tid >> 2) & 15, i = tid >> 6;
+            const int origin = __shfl(sc.my_origin, tile), h = __shfl(sc.my_row, tile) + i, w = __shfl(sc.my_col, tile) + j;
+            const bool ok = origin >= 0 && h < p.H && w < p.W;
+            int32_t* const first = sc.y + (size_t)(ok ? origin : 0) + i * p.W + j;
+            const size_t plane = (size_t)p.H * p.W;
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int pp = px + 32 * e, tile = pp >> 2, pi = (pp >> 1) & 1, pj = pp & 1;
-                    v4i best = requantise(staged(4 * (2 * pi) + 2 * pj, tile, k4), q8);
-                    best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi) + 2 * pj + 1, tile, k4), q8));
-                    best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj, tile, k4), q8));
-                    best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj + 1, tile, k4), q8));
-                    const int n = __shfl(my_n, tile), row = __shfl(my_row, tile), col = __shfl(my_col, tile);
-                    const bool ok = __shfl(my_origin, tile) >= 0 && row + 2 * pi < p.H && col + 2 * pj < p.W && kk < p.K;
-                    const size_t at = (((size_t)n * (p.H >> 1) + (row >> 1) + pi) * (p.W >> 1) + (col >> 1) + pj) * p.K + kk;
-                    if (ok) *reinterpret_cast<uint32_t*>(q8.out + at) = pack_bytes(best);
-                }
-                return;
+            for (int g = 0; g < 8; ++g) {
+                const v4i v = staged(4 * i + j, tile, g);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (ok && kbase + 4 * g + c < p.K) first[(size_t)(kbase + 4 * g + c) * plane] = v[c];
             }
-            // thread: 16 filters (half h16 of the block) of its own tile (lane & 15) at outputs
-            // tid/32 and tid/32 + 8: sixteen lanes read sixteen tiles' rows, which fall in
-            // different banks, and a thread stores 16 bytes where the alignment allows
-            const int h16 = (tid >> 4) & 1, kq = kbase + 16 * h16;
-            const bool vector_store = ((p.K & 15) | (reinterpret_cast<uintptr_t>(q8.out) & 15)) == 0;
+        } else if (q8.pool) {
+            // thread: one pooled pixel of a tile; the four waves take two groups of four filters each
+            const int pj = tid & 1, pi = (tid >> 1) & 1, tile = (tid >> 2) & 15, Ho = p.H >> 1, Wo = p.W >> 1;
+            const int n = __shfl(sc.my_n, tile), row = __shfl(sc.my_row, tile), col = __shfl(sc.my_col, tile);
+            const bool ok = __shfl(sc.my_origin, tile) >= 0 && row + 2 * pi < p.H && col + 2 * pj < p.W;
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                const int o = (tid >> 5) + 8 * e, i = o >> 2, jj = o & 3;
-                uint32_t bytes[4];
+                const int g = 2 * (tid >> 6) + e;
+                const v4i best = best_of_window(tile, pi, pj, g);
 #pragma unroll
-                for (int g = 0; g < 4; ++g) bytes[g] = pack_bytes(requantise(staged(o, lane & 15, 4 * h16 + g), q8));
-                const bool ok = my_origin >= 0 && my_row + i < p.H && my_col + jj < p.W;
-                int8_t* dst = q8.out + (size_t)my_origin + (size_t)(i * p.W + jj) * p.K + kq;
-                if (ok && vector_store && kq < p.K) {
-                    *reinterpret_cast<uint4*>(dst) = make_uint4(bytes[0], bytes[1], bytes[2], bytes[3]);
-                } else if (ok) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        if (kq + 4 * g < p.K) reinterpret_cast<uint32_t*>(dst)[g] = bytes[g];
+                for (int c = 0; c < 4; ++c) {
+                    const int kk = kbase + 4 * g + c;
+                    if (ok && kk < p.K) q8.out[(((size_t)n * p.K + kk) * Ho + (row >> 1) + pi) * Wo + (col >> 1) + pj] = (int8_t)best[c];
                 }
+            }
+        } else {
+            // thread: output row i of a tile (four pixels: one dword where rows stay aligned), two groups of four filters
+            const int i = tid & 3, tile = (tid >> 2) & 15;
+            const int origin = __shfl(sc.my_origin, tile), row = __shfl(sc.my_row, tile) + i, col = __shfl(sc.my_col, tile);
+            const bool ok = origin >= 0 && row < p.H;
+            const bool word_store = ((p.W & 3) | (int)(reinterpret_cast<uintptr_t>(q8.out) & 3)) == 0;
+            int8_t* const first = q8.out + (size_t)(ok ? origin : 0) + i * p.W;
+            const size_t plane = (size_t)p.H * p.W;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int g = 2 * (tid >> 6) + e;
+                v4i px[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) px[j] = requantise(staged(4 * i + j, tile, g), q8);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (!ok || kbase + 4 * g + c >= p.K) continue;
+                    int8_t* at = first + (size_t)(kbase + 4 * g + c) * plane;
+                    if (word_store) {
+                        *reinterpret_cast<uint32_t*>(at) = pack_bytes((v4i){px[0][c], px[1][c], px[2][c], px[3][c]});
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (col + j < p.W) at[j] = (int8_t)px[j][c];
+                    }
+                }
+            }
+        }
+        return;
+    }
+    // Channels-last.  Thread: filters 4*k4..4*k4+3, eight lanes cover the 128 contiguous bytes this block owns of a pixel;
+    // pass ps: output row i = ps/2, tile = 8*(ps%2) + px/4, column j = px%4
+    const int k4 = tid & 7, px = tid >> 3, j = px & 3;
+    const int kk = kbase + 4 * k4;
+    const bool quads = (p.K & 3) == 0;
+    auto put4 = [&](int8_t* at, v4i v, int k_first) {   // four bytes of filters k_first ..
+        if (quads) {
+            if (k_first < p.K) *reinterpret_cast<uint32_t*>(at) = pack_bytes(v);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (k_first + c < p.K) at[c] = (int8_t)v[c];
+        }
+    };
+    if constexpr (Q8) {
+        if (q8.pool) {
+            // 16 tiles x 2x2 pooled pixels = 64 pixels; thread: four filters of pixels px and px + 32
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int pp = px + 32 * e, tile = pp >> 2, pi = (pp >> 1) & 1, pj = pp & 1;
+                const v4i best = best_of_window(tile, pi, pj, k4);
+                const int n = __shfl(sc.my_n, tile), row = __shfl(sc.my_row, tile), col = __shfl(sc.my_col, tile);
+                const bool ok = __shfl(sc.my_origin, tile) >= 0 && row + 2 * pi < p.H && col + 2 * pj < p.W;
+                const size_t at = (((size_t)n * (p.H >> 1) + (row >> 1) + pi) * (p.W >> 1) + (col >> 1) + pj) * p.K + kk;
+                if (ok) put4(q8.out + at, best, kk);
             }
             return;
         }
-        int32_t* first[2];   // output row 0 of the thread's two tiles (e = 0, 1); null where nothing is stored
-        int rows[2];         // output rows of that tile inside the image
+        // thread: 16 filters (half h16 of the block) of its own tile (lane & 15) at outputs
+        // tid/32 and tid/32 + 8: sixteen lanes read sixteen tiles' rows, which fall in
+        // different banks, and a thread stores 16 bytes where the alignment allows
+        const int h16 = (tid >> 4) & 1, kq = kbase + 16 * h16;
+        const bool vector_store = ((p.K & 15) | (reinterpret_cast<uintptr_t>(q8.out) & 15)) == 0;
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            const int origin = __shfl(my_origin, 8 * e + (px >> 2));
-            const bool ok = origin >= 0 && __shfl(my_col, 8 * e + (px >> 2)) + j < p.W && kk < p.K;
-            first[e] = ok ? y + (size_t)origin + j * p.K + kk : nullptr;
-            rows[e] = p.H - __shfl(my_row, 8 * e + (px >> 2));
-        }
-        const size_t row_pitch = (size_t)p.W * p.K;
-        v4i v[8];
+            const int o = (tid >> 5) + 8 * e, i = o >> 2, jj = o & 3;
+            v4i v[4];
 #pragma unroll
-        for (int ps = 0; ps < 8; ++ps) {
-            const int i = ps >> 1, tile = 8 * (ps & 1) + (px >> 2);
-            const int at = ((4 * i + j) * 16 + tile) * kRow + 4 * k4;
-            v[ps] = (*reinterpret_cast<const v4i*>(parki + at) + other_half(at) + rnd) >> 4;
-        }
+            for (int g = 0; g < 4; ++g) v[g] = requantise(staged(o, lane & 15, 4 * h16 + g), q8);
+            const bool ok = sc.my_origin >= 0 && sc.my_row + i < p.H && sc.my_col + jj < p.W;
+            int8_t* dst = q8.out + (size_t)sc.my_origin + (size_t)(i * p.W + jj) * p.K + kq;
+            if (ok && vector_store && kq < p.K) {
+                *reinterpret_cast<uint4*>(dst) = make_uint4(pack_bytes(v[0]), pack_bytes(v[1]), pack_bytes(v[2]), pack_bytes(v[3]));
+            } else if (ok) {
 #pragma unroll
-        for (int ps = 0; ps < 8; ++ps) {
-            const int i = ps >> 1, e = ps & 1;
-            if (first[e] != nullptr && i < rows[e]) *reinterpret_cast<v4i*>(first[e] + i * row_pitch) = v[ps];
-        }
-        return;
-    }
-    // General path: park[wave][output 0..15][lane] (four registers = four tiles each); the value
-    // of (tile, output 4i+j, filter kl) sits in waves kl/16 and 2 + kl/16 at output 4i+j, lane
-    // (tile/4)*16 + kl%16, register tile%4.  16 x 16 x 32 = 8192 results, 32 per thread.
-    v4i* park = reinterpret_cast<v4i*>(lds);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) park[(wave * 16 + i) * 64 + lane] = Yp[i];
-    __syncthreads();
-    if constexpr (Q8) {
-        // One byte per (tile, output pixel, filter), in the order of the output layout; lg = log2
-        // of the output pixels per tile side (4, or 2 after pooling).
-        const int lg = q8.pool ? 1 : 2, side = 1 << lg, span = q8.pool ? 2 : 1;
-        const int Ho = q8.pool ? p.H >> 1 : p.H, Wo = q8.pool ? p.W >> 1 : p.W;
-        const int items = (16 * 32) << (2 * lg);
-        for (int e = tid; e < items; e += 256) {
-            int kl, tile, pi, pj;
-            if constexpr (LAYOUT == WG_NHWC) {
-                kl = e & 31; pj = (e >> 5) & (side - 1); pi = (e >> (5 + lg)) & (side - 1); tile = e >> (5 + 2 * lg);
-            } else {
-                pj = e & (side - 1); tile = (e >> lg) & 15; pi = (e >> (lg + 4)) & (side - 1); kl = e >> (2 * lg + 4);
+                for (int g = 0; g < 4; ++g) put4(dst + 4 * g, v[g], kq + 4 * g);
             }
-            int best = -129;
-            for (int a = 0; a < span; ++a)
-                for (int b = 0; b < span; ++b) {
-                    const int o = 4 * (span * pi + a) + span * pj + b;
-                    const int at = ((((kl >> 4) * 16 + o) * 64) + (tile >> 2) * 16 + (kl & 15)) * 4 + (tile & 3);
-                    best = max(best, requantise((parki[at] + parki[at + 2 * 16 * 64 * 4] + rnd) >> 4, q8));
-                }
-            const int n = __shfl(my_n, tile), row = __shfl(my_row, tile), col = __shfl(my_col, tile);
-            const bool ok = __shfl(my_origin, tile) >= 0 && row + span * pi < p.H && col + span * pj < p.W && kbase + kl < p.K;
-            const int oh = (q8.pool ? row >> 1 : row) + pi, ow = (q8.pool ? col >> 1 : col) + pj;
-            const size_t at = LAYOUT == WG_NHWC ? (((size_t)n * Ho + oh) * Wo + ow) * p.K + kbase + kl
-                                                : (((size_t)n * p.K + kbase + kl) * Ho + oh) * Wo + ow;
-            if (ok) q8.out[at] = (int8_t)best;
         }
         return;
     }
-    int v[32];
-    if constexpr (LAYOUT == WG_NHWC) {
-        // thread: filter kl and output column j fixed; iteration it: tile it/2, output row 2(it%2) + tid/128
-        const int kl = tid & 31, j = (tid >> 5) & 3, ih = tid >> 7;
-        const int kk = kbase + kl;
-        const int at0 = (((kl >> 4) * 16 + j) * 64 + (kl & 15)) * 4;
+    int32_t* first[2];   // output row 0 of the thread's two tiles (e = 0, 1); null where nothing is stored
+    int rows[2];         // output rows of that tile inside the image
 #pragma unroll
-        for (int it = 0; it < 32; ++it) {
-            const int tile = it >> 1, i = 2 * (it & 1) + ih;
-            const int at = at0 + (4 * i * 64 + (tile >> 2) * 16) * 4 + (tile & 3);
-            v[it] = (parki[at] + parki[at + 2 * 16 * 64 * 4] + rnd) >> 4;
-        }
-#pragma unroll
-        for (int it = 0; it < 32; ++it) {
-            const int tile = it >> 1, i = 2 * (it & 1) + ih;
-            const int origin = __builtin_amdgcn_readlane(my_origin, tile);
-            const int h = __builtin_amdgcn_readlane(my_row, tile) + i, w = __builtin_amdgcn_readlane(my_col, tile) + j;
-            if (origin >= 0 && h < p.H && w < p.W && kk < p.K) y[(size_t)origin + (i * p.W + j) * p.K + kk] = v[it];
-        }
-    } else {
-        // thread: tile, output row i and column j fixed; iteration it: filter it.  A wave writes one
-        // output row of 16 consecutive tiles = 256 contiguous bytes.
-        const int j = tid & 3, tile = (tid >> 2) & 15, i = tid >> 6;
-        const int origin = __shfl(my_origin, tile), h = __shfl(my_row, tile) + i, w = __shfl(my_col, tile) + j;
-        const bool ok = origin >= 0 && h < p.H && w < p.W;
-        const int at0 = ((4 * i + j) * 64 + (tile >> 2) * 16) * 4 + (tile & 3);
-#pragma unroll
-        for (int it = 0; it < 32; ++it) {
-            const int at = at0 + ((it >> 4) * 16 * 64 + (it & 15)) * 4;
-            v[it] = (parki[at] + parki[at + 2 * 16 * 64 * 4] + rnd) >> 4;
-        }
-#pragma unroll
-        for (int it = 0; it < 32; ++it)
-            if (ok && kbase + it < p.K) y[(size_t)origin + ((size_t)(kbase + it) * p.H + i) * p.W + j] = v[it];
+    for (int e = 0; e < 2; ++e) {
+        const int origin = __shfl(sc.my_origin, 8 * e + (px >> 2));
+        const bool ok = origin >= 0 && __shfl(sc.my_col, 8 * e + (px >> 2)) + j < p.W && kk < p.K;
+        first[e] = ok ? sc.y + (size_t)origin + j * p.K + kk : nullptr;
+        rows[e] = p.H - __shfl(sc.my_row, 8 * e + (px >> 2));
     }
-
+    const size_t row_pitch = (size_t)p.W * p.K;
+    v4i v[8];
+#pragma unroll
+    for (int ps = 0; ps < 8; ++ps) v[ps] = staged(4 * (ps >> 1) + j, 8 * (ps & 1) + (px >> 2), k4);
+#pragma unroll
+    for (int ps = 0; ps < 8; ++ps) {
+        const int i = ps >> 1, e = ps & 1;
+        if (first[e] == nullptr || i >= rows[e]) continue;
+        int32_t* at = first[e] + i * row_pitch;
+        if (quads) {
+            *reinterpret_cast<v4i*>(at) = v[ps];
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (kk + c < p.K) at[c] = v[ps][c];
+        }
+    }
 }
 
 // Product phase of the role-specialised kernel: the same arithmetic as ProductPhase / ScaledSums
@@ -807,18 +815,6 @@ struct ResidentScaled {
     }
 };
 static_assert(ResidentScaled<0>::kAcc == 36 && ResidentScaled<1>::kAcc == 36, "both halves keep 36 accumulators");
-
-// Compute units of the current device (256 on MI355X), asked once.
-int compute_units() {
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-            return n;
-        return 256;
-    }();
-    return cus;
-}
 
 }  // namespace
 }  // namespace wg

@@ -1,0 +1,279 @@
+// fused_conv_roles_kernel: the single-kernel convolution with transform and products on different waves, one tile block
+// per workgroup.  See fused_conv.hip for the method and the dispatch.
+#pragma once
+#include "product_core.h"
+#include "roles_conv.h"
+
+namespace wg {
+namespace {
+
+// The same computation for layers with several channel blocks, with the two kinds of work on
+// different waves.  Eight waves: waves 0-3 only transform (vector ALU), waves 4-7 only multiply
+// (matrix cores, joins, output transform); each SIMD hosts one of each, so the transform of
+// channel block cb + 1 runs under the products of block cb instead of before them, and a
+// product wave's waits are filled with the transform wave's work.  The operand planes are
+// double-buffered in LDS (2 x 72 KB); patches come through 4-byte or byte loads into the
+// transform threads' registers, one channel block ahead.  One barrier per channel block:
+// barrier j (j = 1..CB) publishes the planes of block j - 1 and frees the buffer that the
+// products of block j - 2 were reading.  32 filters per workgroup (a second pass would not fit
+// the 256 registers a wave has when two share a SIMD).
+// PW = 8 (channels-last, 4-byte buffer loads, K % 4 = 0): eight product waves, twelve waves in all, 64 filters per workgroup.
+// On deep layers the workgroup's pace is set by the transform waves and by what the compute unit's vector-memory path
+// takes in, while the product waves of the eight-wave form idle half of the time: with two product waves per SIMD one
+// transform (and one set of patch loads) serves twice the filters.  Product wave pw owns filter block pw % 4 and half
+// pw / 4 of the entries.  Three waves per SIMD leave a wave 168 registers, so in both modes the product waves keep 18
+// joined channel sums (scaled mode: instead of the 36 resident limb accumulators), with a loop per half so that each
+// half is allocated registers on its own, and the transform waves form their patch offsets per load.  The two 32-filter
+// halves stage their outputs in one operand buffer each and store at the same time.
+
+template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
+__global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
+                                                                         size_t table_off, size_t planes_off, int32_t* __restrict__ y,
+                                                                         Problem p, Int8Epilogue q8, ENC enc) {
+    static_assert(PW == 4 || PW == 8, "one or two product waves per SIMD");
+    extern __shared__ __attribute__((aligned(16))) int8_t lds[];
+    const int lane = threadIdx.x & 63, wave8 = threadIdx.x >> 6;
+    const bool transforms = wave8 < 4;
+    const int tid = threadIdx.x & 255, wave = wave8 & 3;   // within the role (PW = 8: within the four waves that store together)
+    int bx = blockIdx.x, by = blockIdx.y;
+    {
+        const int total = gridDim.x * gridDim.y;
+        if (gridDim.y >= 2 && (total & 7) == 0) {   // XCD-major order, as in fused_conv_body
+            const int launch = blockIdx.y * gridDim.x + blockIdx.x;
+            const int w = (launch & 7) * (total >> 3) + (launch >> 3);
+            by = w / (int)gridDim.x;
+            bx = w - by * (int)gridDim.x;
+        }
+    }
+    const int tile0 = bx * kFusedTiles, k0 = by * (kFusedFilters * (PW / 4));
+    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.Cf, MODE, ENC::kMagic)) return;
+    int my_n = 0, my_ty = 0, my_tx = 0;
+    if (tile0 + (lane & 15) < p.T) decode_tile(p, tile0 + (lane & 15), my_n, my_ty, my_tx);
+#ifdef WG_TIMESTAMPS
+    unsigned long long spent[4] = {0, 0, 0, 0}, mark = WG_CLOCK();
+    const unsigned long long entered = mark;
+    auto report = [&]() {
+        if (g_roles_stamps != nullptr && lane == 0) {
+            unsigned long long* o = g_roles_stamps + ((size_t)(blockIdx.y * gridDim.x + blockIdx.x) * 12 + wave8) * 8;
+            o[0] = spent[0]; o[1] = spent[1]; o[2] = spent[2]; o[3] = spent[3]; o[4] = WG_CLOCK() - entered; o[6] = entered;
+        }
+    };
+#endif
+
+    if (transforms) {
+        const int a_tile = tid >> 4, a_cq = tid & 15;
+        const int a_t = tile0 + a_tile;
+        const int a_tx = __shfl(my_tx, a_tile), a_ty = __shfl(my_ty, a_tile), a_n = __shfl(my_n, a_tile);
+        OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
+        int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
+        uint32_t patch[6][6];
+        // 4-byte pixel loads through the buffer descriptor.  PW = 4: the 36 offsets of the patch are formed once and a
+        // channel block is a uniform offset on top of these; PW = 8: they are formed per load from 6 + 6 terms
+        // (registers are scarce).
+        uint32_t pixel[PW == 4 ? 36 : 1];
+        uint32_t row_off[PW == 8 ? 6 : 1], col_off[PW == 8 ? 6 : 1];
+        const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
+        PatchBias<ENC> bias;
+        bias.enter(p, a_ty, a_tx, enc);
+        auto request = [&](int cb) {
+            if constexpr (PW == 8) {
+                // channel groups beyond C (last block of a C that is not a multiple of 64: a uniform branch) get zeros
+                const bool have = (cb + 1) * kCBlock <= p.C || cb * kCBlock + 4 * a_cq < p.C;
+#pragma unroll
+                for (int i = 0; i < 36; ++i) {
+                    const uint32_t at = __builtin_elementwise_add_sat(row_off[i / 6], col_off[i % 6]);
+                    patch[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, have ? at : kOutsideOffset, cb * kCBlock, 0);
+                }
+            } else {
+                request_patch(xbuf, p, pixel, cb, 4 * a_cq, patch);
+            }
+        };
+        if constexpr (PW == 8) {
+            const int h0 = 4 * a_ty - 1, w0 = 4 * a_tx - 1;
+            const uint32_t image = (uint32_t)a_n * (uint32_t)p.H * (uint32_t)p.W * (uint32_t)p.C + (uint32_t)(4 * a_cq);
+#pragma unroll
+            for (int a = 0; a < 6; ++a) {
+                row_off[a] = (unsigned)(h0 + a) < (unsigned)p.H ? image + (uint32_t)(h0 + a) * (uint32_t)p.W * (uint32_t)p.C : kOutsideOffset;
+                col_off[a] = (unsigned)(w0 + a) < (unsigned)p.W ? (uint32_t)(w0 + a) * (uint32_t)p.C : kOutsideOffset;
+            }
+        } else {
+            patch_offsets(p, a_n, a_ty, a_tx, 4 * a_cq, pixel);
+        }
+        if (a_t < p.T) request(0);
+        WG_SPENT(3, mark);
+        for (int cb = 0; cb < p.CB; ++cb) {
+            if (cb > 0) {   // barrier cb
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+            }
+            WG_SPENT(0, mark);   // LDS writes landed + barrier
+            out.sink.base = slot + (cb & 1) * kLdsBytes;
+            if (a_t < p.T) {
+#ifdef WG_TIMESTAMPS
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                WG_SPENT(1, mark);   // wait for the patch
+#endif
+                bias.apply(patch);
+                transform_patch(patch, out, enc);
+                WG_SPENT(2, mark);   // transform
+                if (cb + 1 < p.CB) request(cb + 1);
+                WG_SPENT(3, mark);   // requests
+            }
+        }
+#ifdef WG_TIMESTAMPS
+        report();
+#endif
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // barrier CB: the last block's planes are published
+        __syncthreads();                // the two barriers of the product waves' store
+        __syncthreads();
+        return;
+    }
+
+    // PW = 4: wave = 2 half + kblock.  PW = 8: product wave pw = wave8 - 4 owns filter block pw % 4 and half pw / 4; the
+    // waves of filter blocks 2 group, 2 group + 1 store together (`wave` counts within that group, as store_staged expects)
+    const int pw = wave8 - 4;
+    const int kblock4 = PW == 8 ? (pw & 3) : (wave & 1), half = PW == 8 ? (pw >> 2) : (wave >> 1);
+    const int kblock = kblock4 & 1, group = kblock4 >> 1;
+    const int k = k0 + kblock4 * 16 + (lane & 15);
+    LaneContext cx;
+    cx.table_k = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
+    cx.parked = nullptr;
+    constexpr bool PARKED = MODE == WG_SCALED;
+    int8_t* const scale_area = lds + 2 * kLdsBytes + pw * kParkedScaleBytes;   // behind the two plane buffers: 1 KB per product wave
+    constexpr int NP = MODE == WG_LOSSLESS ? 138 : 46;
+    const int8_t* b_lane = reinterpret_cast<const int8_t*>(blob + planes_off) +
+                           filter_plane_offset(0, 0, k, (lane >> 4) * 16, p.Kp, NP);
+    const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
+    v4i Y[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) Y[i] = (v4i){0, 0, 0, 0};
+    // The product waves do no output transform per block.  Scaled: all 36 limb-product
+    // accumulators stay resident (PW = 4), or 18 joined channel sums (PW = 8: 168 registers per wave); lossless: 18
+    // joined channel sums (54 accumulators would not fit).
+    constexpr bool RESIDENT = MODE == WG_SCALED && PW == 4;
+    constexpr int kLeanRing = PW == 8 ? (MODE == WG_SCALED ? 10 : 6) : 8;
+    std::conditional_t<RESIDENT, ResidentScaled<0>, LeanProducts<MODE, 0, true, kLeanRing>> phase0;
+    std::conditional_t<RESIDENT, ResidentScaled<1>, LeanProducts<MODE, 1, true, kLeanRing>> phase1;
+    constexpr int kSumRegs = RESIDENT ? 36 : kChannelSums;
+    v4i sums[kSumRegs];
+#pragma unroll
+    for (int i = 0; i < kSumRegs; ++i) sums[i] = (v4i){0, 0, 0, 0};
+    if constexpr (PW == 8) {
+        // one loop per half (the same barriers in both), so that each is allocated registers on its own
+        auto blocks = [&](auto& phase, auto H) {
+            // the first block's filter prefetch goes out between the request for the reverse-scaling factors and their parking
+            ParkedScales<H> scales;
+            if constexpr (PARKED) scales.ask(cx, lane);
+            cx.b_glob = b_lane;
+            phase.prefetch(cx);
+            if constexpr (PARKED) scales.park(cx, scale_area, lane);
+            for (int cb = 0; cb < p.CB; ++cb) {
+                if (cb > 0) {
+                    cx.b_glob = b_lane + cb * b_block_stride;
+                    phase.prefetch(cx);
+                }
+                WG_SPENT(3, mark);   // ring prefetch issue
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();   // barrier cb + 1
+                WG_SPENT(0, mark);   // barrier
+                cx.a_lds = lds + (cb & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
+                phase.run(cx, sums, Y);
+                WG_SPENT(2, mark);   // products
+            }
+        };
+        if (half == 0) blocks(phase0, std::integral_constant<int, 0>{}); else blocks(phase1, std::integral_constant<int, 1>{});
+    } else {
+        cx.b_glob = b_lane;
+        if (half == 0) {
+            ParkedScales<0> scales;
+            if constexpr (PARKED) scales.ask(cx, lane);
+            phase0.prefetch(cx);
+            if constexpr (PARKED) scales.park(cx, scale_area, lane);
+        } else {
+            ParkedScales<1> scales;
+            if constexpr (PARKED) scales.ask(cx, lane);
+            phase1.prefetch(cx);
+            if constexpr (PARKED) scales.park(cx, scale_area, lane);
+        }
+        for (int cb = 0; cb < p.CB; ++cb) {
+            if (cb > 0) {
+                cx.b_glob = b_lane + cb * b_block_stride;
+                if (half == 0) phase0.prefetch(cx); else phase1.prefetch(cx);
+            }
+            WG_SPENT(3, mark);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();   // barrier cb + 1
+            WG_SPENT(0, mark);
+            cx.a_lds = lds + (cb & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
+            if constexpr (RESIDENT) {
+                if (half == 0) phase0.run(cx, sums); else phase1.run(cx, sums);
+            } else {
+                if (half == 0) phase0.run(cx, sums, Y); else phase1.run(cx, sums, Y);
+            }
+            WG_SPENT(2, mark);
+        }
+    }
+#ifdef WG_TIMESTAMPS
+    report();
+#endif
+    if constexpr (RESIDENT) {
+        if (half == 0) ResidentScaled<0>::finish(cx, sums, Y);
+        else           ResidentScaled<1>::finish(cx, sums, Y);
+    } else if constexpr (MODE == WG_SCALED) {
+        if (half == 0) ScaledSums<0>::template finish<0, true>(cx, sums, Y);
+        else           ScaledSums<1>::template finish<0, true>(cx, sums, Y);
+    } else {
+        if (half == 0) LeanProducts<MODE, 0, true>::finish_lossless(sums, Y);
+        else           LeanProducts<MODE, 1, true>::finish_lossless(sums, Y);
+    }
+    // PW = 8: the two 32-filter halves of the workgroup stage in one operand buffer each and store side by side
+    StoreContext sc;
+    sc.lds = lds + group * kLdsBytes;
+    sc.tid = PW == 8 ? (2 * half + kblock) * 64 + lane : tid;
+    sc.lane = lane; sc.rnd = MODE == WG_SCALED ? 8 : 0; sc.y = y;
+    locate_tile<LAYOUT>(sc, p, tile0);
+    __syncthreads();   // the operand planes are dead
+    stage_outputs(sc.lds, lane, half, kblock, Y);
+    __syncthreads();
+    store_staged<LAYOUT, Q8, true>(sc, p, q8, k0 + group * kFusedFilters);
+#ifdef WG_TIMESTAMPS
+    if (g_roles_stamps != nullptr && lane == 0)
+        g_roles_stamps[((size_t)(blockIdx.y * gridDim.x + blockIdx.x) * 12 + wave8) * 8 + 5] = WG_CLOCK() - entered;
+#endif
+}
+
+template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
+hipError_t launch_roles(const int8_t* x, const ENC& enc, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p,
+                        const Int8Epilogue& q8, hipStream_t s) {
+    constexpr int lds_bytes = 2 * kLdsBytes + PW * kParkedScaleBytes;   // two plane buffers, the parked reverse-scaling factors
+    static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
+    static LdsLimitOnce lds_limit;   // per template instance
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC>), lds_bytes)) return e;
+    dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / (kFusedFilters * (PW / 4)));   // Kp is a multiple of 64
+    fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC><<<grid, 64 * (4 + PW), lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, q8,
+                                                                                             enc);
+    return hipGetLastError();
+}
+
+// One mode's launches (each mode is compiled in a file of its own).
+template <int MODE>
+hipError_t launch_roles_mode(const RolesCall& c, bool wide, hipStream_t s) {
+    auto go = [&](auto L, auto Q8, auto PW, const auto& enc) {
+        return launch_roles<L, MODE, Q8, PW>(c.x, enc, c.blob, c.bl, c.y, c.p, c.q8, s);
+    };
+    using std::integral_constant;
+    auto form = [&](auto L, auto Q8, const auto& enc) {
+        return wide ? go(L, Q8, integral_constant<int, 8>{}, enc) : go(L, Q8, integral_constant<int, 4>{}, enc);
+    };
+    constexpr integral_constant<int, WG_NHWC> nhwc{};
+    constexpr integral_constant<int, WG_NCHW> nchw{};
+    if (c.zero != nullptr)   // uint8 tensors: int32 outputs only
+        return c.layout == WG_NHWC ? form(nhwc, std::false_type{}, *c.zero) : form(nchw, std::false_type{}, *c.zero);
+    if (c.q8.out != nullptr)
+        return c.layout == WG_NHWC ? form(nhwc, std::true_type{}, SignedInt8{}) : form(nchw, std::true_type{}, SignedInt8{});
+    return c.layout == WG_NHWC ? form(nhwc, std::false_type{}, SignedInt8{}) : form(nchw, std::false_type{}, SignedInt8{});
+}
+
+}  // namespace
+}  // namespace wg

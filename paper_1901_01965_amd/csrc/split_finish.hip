@@ -1,0 +1,185 @@
+// Second half of a convolution whose channel blocks were dealt to several workgroups (lossless_conv.hip): adds the splits
+// and finishes.  Scaled mode: Winograd-domain channel sums, scaled back (Section 4.2) and transformed (Section 3.3) here;
+// lossless mode: 16 x outputs.  Only layers with few tiles come here (without the split they would fill less than half the
+// chip), so the kernels are bound by the latency of their reads, not by their amount: all of a thread's reads of a split are
+// in flight together.
+// One image, lossless, int8 out, both kernels together: 512 -> 512 at 14x14 28 -> 12 us (16 workgroups of eight channel
+// blocks before, 128 of one now), at 28x28 27 -> 19 us.
+#include "kernel_common.h"
+#include "output_transform_core.h"
+#include "roles_conv.h"
+
+namespace wg {
+namespace {
+
+constexpr int kItems = 64;   // filters of one tile per workgroup
+
+// grid: (padded tiles, Kp / 64), 256 threads: lane = filter.
+template <int LAYOUT, bool Q8>
+__global__ __launch_bounds__(256) void split_finish_kernel(const int32_t* __restrict__ partial, const uint8_t* __restrict__ blob,
+                                                           size_t table_off, int32_t* __restrict__ y, Problem p, Int8Epilogue q8,
+                                                           int splits) {
+    __shared__ int sums[3][kAccPlanes][kItems];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = blockIdx.y * kItems + lane, t = blockIdx.x;
+    if (t >= p.T) return;
+    const size_t plane = (size_t)gridDim.x * p.Kp;
+    const int32_t* const mine = partial + (size_t)t * p.Kp + k;
+    const BlobHeaderWords header = read_blob_header(blob);
+    // the first wave finishes: it asks for its filter's factors (r, q) along with its sums
+    int2 rq[kEntries];
+    if (wave == 0) {
+        const ScaleEntry* tk = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
+#pragma unroll
+        for (int e = 0; e < kEntries; ++e) rq[e] = *reinterpret_cast<const int2*>(&tk[e].r);
+    }
+    int m[kAccPlanes];
+#pragma unroll
+    for (int e = 0; e < kAccPlanes; ++e) m[e] = 0;
+    for (int s = wave; s < splits; s += 8) {   // two splits at a time
+        int v[2][kAccPlanes];
+        const bool second = s + 4 < splits;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int e = 0; e < kAccPlanes; ++e) v[i][e] = mine[((size_t)(second ? s + 4 * i : s) * kAccPlanes + e) * plane];
+#pragma unroll
+        for (int e = 0; e < kAccPlanes; ++e) m[e] += v[0][e] + (second ? v[1][e] : 0);
+    }
+    if (wave > 0) {
+#pragma unroll
+        for (int e = 0; e < kAccPlanes; ++e) sums[wave - 1][e][lane] = m[e];
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    const int others = min(splits, 4) - 1;
+    for (int w = 0; w < others; ++w)
+#pragma unroll
+        for (int e = 0; e < kAccPlanes; ++e) m[e] += sums[w][e][lane];
+    if (k >= p.K || !blob_matches(header, p.K, p.Cf, WG_SCALED)) return;
+
+    int re[16], cr[10], ci[10];
+    auto unscale = [&](int e, int v) { return ReverseScale(rq[e].x, rq[e].y)(v); };   // Section 4.2
+#pragma unroll
+    for (int e = 0; e < 16; ++e) re[e] = unscale(e, m[e]);
+#pragma unroll
+    for (int j = 0; j < 10; ++j) {
+        cr[j] = unscale(16 + j, m[16 + 2 * j]);
+        ci[j] = unscale(16 + j, m[17 + 2 * j]);
+    }
+    int out[4][4];   // out[j][i]: output row i, column j
+    output_tile(re, cr, ci, out);
+
+    int n, ty, tx;
+    decode_tile(p, t, n, ty, tx);
+    constexpr int rnd = 8;
+    auto at = [&](int h, int w, int H, int W) {
+        return LAYOUT == WG_NHWC ? (((size_t)n * H + h) * W + w) * p.K + k : (((size_t)n * p.K + k) * H + h) * W + w;
+    };
+    if (Q8 && q8.pool) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int h = 2 * ty + i, w = 2 * tx + j;
+                if (h >= p.H >> 1 || w >= p.W >> 1) continue;
+                int best = -129;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) best = max(best, requantise((out[2 * j + (a & 1)][2 * i + (a >> 1)] + rnd) >> 4, q8));
+                q8.out[at(h, w, p.H >> 1, p.W >> 1)] = (int8_t)best;
+            }
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int h = 4 * ty + i, w = 4 * tx + j;
+            if (h >= p.H || w >= p.W) continue;
+            const int v = (out[j][i] + rnd) >> 4;
+            if constexpr (Q8) q8.out[at(h, w, p.H, p.W)] = (int8_t)requantise(v, q8);
+            else              y[at(h, w, p.H, p.W)] = v;
+        }
+}
+
+// The same for launch_lossless_pair_sums, whose workgroups leave 16 x outputs: adds the splits, rescales and stores.
+// Thread: four filters of one output (one 2x2 window) of a tile, all splits' reads in flight together.
+// grid: (padded tiles, ceil(items / 256)): items = 16 (4) x Kp / 4 per tile.
+template <int LAYOUT, bool Q8>
+__global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restrict__ sums, const uint8_t* __restrict__ blob,
+                                                          int32_t* __restrict__ y, Problem p, Int8Epilogue q8, int splits) {
+    const int t = blockIdx.x, item = blockIdx.y * 256 + threadIdx.x, k4s = p.Kp >> 2;
+    const int pool = Q8 ? q8.pool : 0;
+    if (t >= p.T || item >= (pool ? 4 : 16) * k4s) return;
+    const BlobHeaderWords header = read_blob_header(blob);
+    const int o = item / k4s, kk = 4 * (item - o * k4s);
+    const size_t split = (size_t)gridDim.x * 4 * p.Kp;   // v4i per split
+    auto total = [&](int out) {   // finished outputs of filters kk .. kk + 3 at output `out`
+        const v4i* from = reinterpret_cast<const v4i*>(sums) + (((size_t)t * 16 + out) * p.Kp + kk) / 4;
+        v4i v = {0, 0, 0, 0};
+        for (int s = 0; s < splits; s += 4) {
+            v4i part[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[i] = from[(size_t)min(s + i, splits - 1) * split];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v += s + i < splits ? part[i] : (v4i){0, 0, 0, 0};
+        }
+        return v >> 4;
+    };
+    int n, ty, tx;
+    decode_tile(p, t, n, ty, tx);
+    int h = 4 * ty + (o >> 2), w = 4 * tx + (o & 3), H = p.H, W = p.W;
+    v4i v;
+    if (pool) {
+        const int pi = o >> 1, pj = o & 1;
+        v = requantise(total(8 * pi + 2 * pj), q8);
+        v = __builtin_elementwise_max(v, requantise(total(8 * pi + 2 * pj + 1), q8));
+        v = __builtin_elementwise_max(v, requantise(total(8 * pi + 4 + 2 * pj), q8));
+        v = __builtin_elementwise_max(v, requantise(total(8 * pi + 4 + 2 * pj + 1), q8));
+        h = 2 * ty + pi; w = 2 * tx + pj; H >>= 1; W >>= 1;
+    } else {
+        v = total(o);
+        if constexpr (Q8) v = requantise(v, q8);
+    }
+    if (!blob_matches(header, p.K, p.Cf, WG_LOSSLESS) || h >= H || w >= W) return;
+    const size_t pixel = ((size_t)n * H + h) * W + w, plane = (size_t)H * W;
+    if (LAYOUT == WG_NHWC && (p.K & 3) == 0) {
+        if (kk >= p.K) return;
+        if constexpr (Q8) *reinterpret_cast<uint32_t*>(q8.out + pixel * p.K + kk) = pack_bytes(v);
+        else              *reinterpret_cast<v4i*>(y + pixel * p.K + kk) = v;
+        return;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        if (kk + c >= p.K) break;
+        const size_t at = LAYOUT == WG_NHWC ? pixel * p.K + kk + c : ((size_t)n * p.K + kk + c) * plane + (pixel - (size_t)n * plane);
+        if constexpr (Q8) q8.out[at] = (int8_t)v[c];
+        else              y[at] = v[c];
+    }
+}
+
+}  // namespace
+
+hipError_t launch_sums_finish(const RolesCall& c, const int32_t* sums, int splits, hipStream_t s) {
+    const int items = (c.q8.out != nullptr && c.q8.pool ? 4 : 16) * (c.p.Kp / 4);
+    // tiles beyond T have sums, but nothing to store; `gridDim.x` is the padded count because it strides the splits
+    const dim3 grid(16 * ceil_div(c.p.T, 16), ceil_div(items, 256));
+    auto go = [&](auto kernel) {
+        kernel<<<grid, 256, 0, s>>>(sums, c.blob, c.y, c.p, c.q8, splits);
+        return hipGetLastError();
+    };
+    if (c.layout == WG_NHWC) return c.q8.out ? go(&sums_finish_kernel<WG_NHWC, true>) : go(&sums_finish_kernel<WG_NHWC, false>);
+    return c.q8.out ? go(&sums_finish_kernel<WG_NCHW, true>) : go(&sums_finish_kernel<WG_NCHW, false>);
+}
+
+hipError_t launch_split_finish(const RolesCall& c, const int32_t* partial, int splits, hipStream_t s) {
+    const dim3 grid(16 * ceil_div(c.p.T, 16), c.p.Kp / kItems);
+    auto go = [&](auto kernel) {
+        kernel<<<grid, 256, 0, s>>>(partial, c.blob, c.bl.table_off, c.y, c.p, c.q8, splits);
+        return hipGetLastError();
+    };
+    if (c.layout == WG_NHWC) return c.q8.out ? go(&split_finish_kernel<WG_NHWC, true>) : go(&split_finish_kernel<WG_NHWC, false>);
+    return c.q8.out ? go(&split_finish_kernel<WG_NCHW, true>) : go(&split_finish_kernel<WG_NCHW, false>);
+}
+
+}  // namespace wg

@@ -69,6 +69,18 @@ at::Tensor output(PyObject* out, int N, int K, int H, int W, int layout, at::Sca
     return t;
 }
 
+// Scratch memory of one call, from torch's caching allocator (which hands it out again only to work queued behind it).
+struct ScratchTensor {
+    at::Tensor t;
+    void* p = nullptr;
+    size_t bytes = 0;
+    ScratchTensor(size_t wanted, const at::Tensor& like) : bytes(wanted) {
+        if (wanted == 0) return;
+        t = at::Tensor(at::detail::empty_cuda({(int64_t)wanted}, at::kByte, like.device(), std::nullopt));
+        p = t.data_ptr();
+    }
+};
+
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 
 void need_channels(int packed_for, int C, const char* what) {
@@ -114,17 +126,22 @@ PyObject* conv2d_int8(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const Dims d = dims(x, layout);
         need_channels(packed_c, d.C, "winograd_conv2d_int8");
         const at::Tensor& blob = tensor(a[1], at::kByte, "blob");
-        at::Tensor ws;
-        if (a[7] != Py_None) ws = tensor(a[7], at::kByte, "workspace");
-        else if (winograd_conv2d_path(d.N, d.C, d.H, d.W, K, mode) == 1)   // the staged pipeline works through memory
-            ws = at::Tensor(at::detail::empty_cuda({(int64_t)winograd_workspace_bytes(d.N, d.C, d.H, d.W, K, mode)}, at::kByte, x.device(), std::nullopt));
         const at::Tensor y = output(a[6], d.N, K, d.H, d.W, layout, at::kInt, x);
         void* const s = stream();
+        // the staged pipeline, or a caller's workspace: the C ABI's entry point
+        const bool staged = a[7] == Py_None && winograd_conv2d_path(d.N, d.C, d.H, d.W, K, mode) == 1;
+        if (staged || a[7] != Py_None) {
+            const ScratchTensor own(staged ? winograd_workspace_bytes(d.N, d.C, d.H, d.W, K, mode) : 0, x);
+            const at::Tensor& ws = staged ? own.t : tensor(a[7], at::kByte, "workspace");
+            return finish(y, [&] {
+                return winograd_conv2d_int8(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode,
+                                            ws.data_ptr(), (size_t)ws.numel(), s);
+            });
+        }
+        const ScratchTensor scratch(wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 0), x);
         return finish(y, [&] {
-            if (!ws.defined())
-                return wg::conv2d_int8_single_kernel(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode, s);
-            return winograd_conv2d_int8(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode,
-                                        ws.data_ptr(), (size_t)ws.numel(), s);
+            return wg::conv2d_int8_with_scratch(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode,
+                                                scratch.p, scratch.bytes, s);
         });
     });
 }
@@ -140,9 +157,13 @@ PyObject* conv2d_int8_requant(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& blob = tensor(a[1], at::kByte, "blob");
         const at::Tensor y = output(a[6], d.N, K, pool ? d.H / 2 : d.H, pool ? d.W / 2 : d.W, layout, at::kChar, x);
         void* const s = stream();
+        const ScratchTensor scratch(f2x2 ? 0 : wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 0), x);
         return finish(y, [&] {
-            return (f2x2 ? winograd_f2x2_conv2d_int8_requant : winograd_conv2d_int8_requant)(
-                data<int8_t>(x), blob.data_ptr(), data<int8_t>(y), d.N, d.C, d.H, d.W, K, layout, mode, shift, relu, pool, s);
+            if (f2x2)
+                return winograd_f2x2_conv2d_int8_requant(data<int8_t>(x), blob.data_ptr(), data<int8_t>(y), d.N, d.C, d.H, d.W, K, layout,
+                                                         mode, shift, relu, pool, s);
+            return wg::conv2d_int8_requant_with_scratch(data<int8_t>(x), blob.data_ptr(), data<int8_t>(y), d.N, d.C, d.H, d.W, K, layout,
+                                                        mode, shift, relu, pool, scratch.p, scratch.bytes, s);
         });
     });
 }
@@ -159,11 +180,14 @@ PyObject* conv2d_bytes(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& blob = tensor(a[2], at::kByte, "blob");
         const at::Tensor y = output(a[7], d.N, K, d.H, d.W, layout, at::kInt, x);
         void* const s = stream();
+        const ScratchTensor scratch(f2x2 ? 0 : wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 1), x);
         return finish(y, [&] {
+            if (!f2x2)
+                return wg::conv2d_u8_with_scratch(data<uint8_t>(x), zero, blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout,
+                                                  mode, scratch.p, scratch.bytes, s);
             if (!is_unsigned)
                 return winograd_f2x2_conv2d_int8(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode, s);
-            return (f2x2 ? winograd_f2x2_conv2d_u8 : winograd_conv2d_u8)(data<uint8_t>(x), zero, blob.data_ptr(), data<int32_t>(y), d.N,
-                                                                         d.C, d.H, d.W, K, layout, mode, s);
+            return winograd_f2x2_conv2d_u8(data<uint8_t>(x), zero, blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode, s);
         });
     });
 }

@@ -47,6 +47,8 @@ __host__ __device__ inline uint32_t fast_div(uint32_t n, FastDiv f) {
 
 struct Problem {
     int N, C, H, W, K;
+    int Cf;          // channels the filters were packed for; C, the pixel stride of channels-last activations, is larger only
+                     // where the activations are a padded channels-last copy
     int TH, TW, T;   // tiles per column / row, total tiles
     int Tp;          // T padded to kTilePad
     int CB;          // ceil(C / 64)
@@ -67,7 +69,7 @@ inline size_t round_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
 
 inline Problem make_problem(int N, int C, int H, int W, int K) {
     Problem p;
-    p.N = N; p.C = C; p.H = H; p.W = W; p.K = K;
+    p.N = N; p.C = p.Cf = C; p.H = H; p.W = W; p.K = K;
     p.TH = ceil_div(H, 4); p.TW = ceil_div(W, 4);
     p.T = N * p.TH * p.TW;
     p.Tp = ceil_div(p.T, kTilePad) * kTilePad;
@@ -235,9 +237,21 @@ inline Int8Epilogue no_int8_epilogue() { return Int8Epilogue{nullptr, 0, 0, 0, 0
 inline Int8Epilogue make_int8_epilogue(int8_t* out, int shift, bool relu, bool pool) {
     return Int8Epilogue{out, shift, shift > 0 ? 1 << (shift - 1) : 0, relu ? 0 : -128, pool ? 1 : 0};
 }
-// Single-kernel path (no workspace traffic).
+// Device memory a convolution may use while it runs (bytes = 0: none); what it would like to have is scratch_wanted().
+struct Scratch {
+    void* p;
+    size_t bytes;
+};
+inline Scratch no_scratch() { return Scratch{nullptr, 0}; }
+size_t fused_conv_scratch_wanted(const Problem& p, int layout, int mode, bool is_unsigned);
+// Single-kernel path.  With scratch: inputs that the fast loads cannot read go through a channels-last copy, and small
+// deep layers deal their channel blocks to several workgroups; without it these run as they can.
 hipError_t launch_fused_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p, int layout,
-                             int mode, const Int8Epilogue& q8, hipStream_t s);
+                             int mode, const Int8Epilogue& q8, const Scratch& scratch, hipStream_t s);
+// Channels-last copy of x with `padded` channels per pixel (4, or a multiple of 16; channels beyond C hold fill_byte).
+hipError_t launch_channels_last(const int8_t* x, int8_t* out, const Problem& p, int layout, int padded, uint8_t fill_byte, hipStream_t s);
+inline int padded_channels(int C) { return C <= 4 ? 4 : ceil_div(C, 16) * 16; }
+inline size_t channels_last_bytes(const Problem& p) { return round_up((size_t)p.N * p.H * p.W * padded_channels(p.C), 256); }
 // Test hook: n > 0 makes the single-kernel path use its streaming variant wherever the layout
 // allows, with n workgroups per filter block; 0 restores the library's own choice.
 void set_stream_workgroups(int n);
@@ -249,18 +263,23 @@ hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t*
 // 0: this form does not apply (layout) or is switched off, 1: applies, the dispatcher decides, 2: forced by the test hook
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout);
 void set_lossless_variant(int v);
+// The same form with the channel blocks dealt to `splits` workgroups each: leaves 16 x outputs as int32
+// [splits][16 ceil(T/16)][16][Kp], which launch_sums_finish adds and stores.
+hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s);
 // Test hook (both modes): 0 the library's choice, 1 the role-specialised kernel with eight product waves (64 filters
 // per workgroup) wherever the layout allows (channels-last, C % 4 = 0, K % 4 = 0), 2 never that form.
 void set_scaled_variant(int v);
 // The same for the streaming kernel's form with eight product waves (0, 1: wherever the layer streams, 2: never).
 void set_stream_variant(int v);
+// Scaled mode, likewise: leaves the Winograd-domain channel sums as int32 [splits][36][16 ceil(T/16)][Kp] for launch_split_finish.
+hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s);
 // Single-kernel path with the activations scaled per tile as well (WG_SCALED blob of signed int8 filters).
 // act_table: null, or int32 [T][26][4] that receives every tile's (n, p, r, q).
 hipError_t launch_fused_conv_act_scaled(const int8_t* x, const void* blob, int32_t* y, int32_t* act_table, const Problem& p,
                                         int layout, hipStream_t s);
 // Single-kernel path for uint8 activations with a zero point and a kBlobMagicInt9 blob (C <= kMaxChannelsInt9).
 hipError_t launch_fused_conv_u8(const uint8_t* x, int zero_point, const void* blob, int32_t* y, const Problem& p, int layout,
-                                int mode, hipStream_t s);
+                                int mode, const Scratch& scratch, hipStream_t s);
 // Single-kernel path for channels-last inputs with C <= kNarrowChannels.
 hipError_t launch_narrow_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p, int mode,
                               const Int8Epilogue& q8, hipStream_t s);
@@ -274,6 +293,18 @@ hipError_t launch_unpack_filter_planes(const void* blob, int8_t* dense, int32_t*
                                        int mode, hipStream_t s);
 hipError_t launch_unpack_accumulators(const int32_t* M, int32_t* dense, const Problem& p, int mode,
                                       hipStream_t s);
+
+// Compute units of the current device (256 on MI355X), asked once.
+inline int compute_units() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+            return n;
+        return 256;
+    }();
+    return cus;
+}
 
 // Raises a kernel's dynamic LDS limit the first time its launcher runs; safe when several host
 // threads make that first call together.  Every call returns the status of the one attempt.
@@ -308,9 +339,9 @@ __device__ inline BlobHeaderWords read_blob_header(const void* blob) {
     for (int i = 0; i < 8; ++i) out.w[i] = h[i];
     return out;
 }
-__device__ inline bool blob_matches(const BlobHeaderWords& h, int K, int C, int mode) {
+__device__ inline bool blob_matches(const BlobHeaderWords& h, int K, int C, int mode, uint32_t magic = kBlobMagic) {
     static_assert(offsetof(BlobHeader, mode) == 16, "magic, version, K, C, mode are the first five dwords");
-    return (h.w[0] == kBlobMagic) & (h.w[1] == kBlobVersion) & ((int)h.w[2] == K) & ((int)h.w[3] == C) & ((int)h.w[4] == mode);
+    return (h.w[0] == magic) & (h.w[1] == kBlobVersion) & ((int)h.w[2] == K) & ((int)h.w[3] == C) & ((int)h.w[4] == mode);
 }
 
 }  // namespace wg

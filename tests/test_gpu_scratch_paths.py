@@ -1,0 +1,83 @@
+"""Paths that use scratch memory: channels-last copies of channel-major and odd-channel inputs, channel blocks dealt to
+several workgroups, and the stores of any K in either layout, against the oracle; and the same calls through the C ABI,
+which gives the int8 entry point no scratch."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1901_01965_amd as wg
+from paper_1901_01965_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+# N, C, K, H, W: split channels with one and several blocks per workgroup, a last split that is shorter, a last block that
+# is not full; ragged tiles; K at and around multiples of 4, 16, 32 and 64; images of one to four pixels
+SPLIT = [(1, 512, 40, 14, 14), (1, 320, 96, 8, 10), (1, 896, 31, 6, 6), (2, 500, 65, 4, 14), (1, 448, 512, 14, 9)]
+COPY = [(2, 5, 7, 9, 11), (1, 130, 33, 3, 5), (3, 67, 66, 1, 1), (2, 64, 100, 1, 3), (1, 3, 64, 10, 6), (2, 31, 130, 21, 20)]
+
+
+def _inputs(shape, layout):
+    N, C, K, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, act="uniform", wgt="uniform", seed=5)
+    nhwc = layout == wg.NHWC
+    return x, g, torch.from_numpy(wl.to_nhwc(x) if nhwc else x).cuda(), torch.from_numpy(wl.to_krsc(g) if nhwc else g).cuda()
+
+
+def _nchw(t, layout):
+    a = t.cpu().numpy()
+    return wl.from_nhwc(a) if layout == wg.NHWC else a
+
+
+@pytest.mark.parametrize("mode", [wg.LOSSLESS, wg.SCALED])
+@pytest.mark.parametrize("layout", [wg.NCHW, wg.NHWC])
+@pytest.mark.parametrize("shape", SPLIT + COPY)
+def test_int32_and_int8_outputs(shape, layout, mode):
+    x, g, xd, gd = _inputs(shape, layout)
+    want = oracle.direct_conv2d(x, g) if mode == wg.LOSSLESS else oracle.winograd_conv2d(x, g, oracle.SCALED, 127)[0]
+    packed = wg.winograd_filter_transform(gd, layout, mode)
+    assert np.array_equal(_nchw(wg.winograd_conv2d_int8(xd, packed, layout), layout), want)
+    N, C, K, H, W = shape
+    for relu, pool in ((True, False), (False, True)):
+        if pool and (H | W) & 1:
+            continue
+        got = wg.winograd_conv2d_int8_requant(xd, packed, 9, relu, pool, layout)
+        expect = oracle.requant_relu_pool(want, 9, relu, pool)
+        assert np.array_equal(_nchw(got, layout), expect)
+        # the C ABI's entry point has no scratch memory to offer
+        bare = torch.full_like(got, 77)
+        p = lambda t: ctypes.c_void_p(t.data_ptr())
+        stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        assert wg.load_library().winograd_conv2d_int8_requant(p(xd), p(packed.blob), p(bare), N, C, H, W, K, layout, mode, 9,
+                                                              int(relu), int(pool), stream) == 0
+        assert np.array_equal(_nchw(bare, layout), expect)
+
+
+@pytest.mark.parametrize("mode", [wg.LOSSLESS, wg.SCALED])
+@pytest.mark.parametrize("layout", [wg.NCHW, wg.NHWC])
+@pytest.mark.parametrize("shape", [(2, 64, 64, 9, 10), (2, 6, 70, 5, 5), (1, 200, 33, 14, 7), (40, 32, 128, 14, 14), (9, 128, 72, 28, 28)])
+def test_uint8_inputs(shape, layout, mode):
+    """Padding pixels read as the zero point on every form that takes uint8 tensors."""
+    N, C, K, H, W = shape
+    rng = np.random.default_rng(11)
+    x, g = rng.integers(0, 256, (N, C, H, W), dtype=np.uint8), rng.integers(0, 256, (K, C, 3, 3), dtype=np.uint8)
+    zx, zw = 201, 117
+    xi, gi = x.astype(np.int16) - zx, g.astype(np.int16) - zw
+    want = oracle.direct_conv2d_i16(xi, gi) if mode == wg.LOSSLESS else oracle.winograd_conv2d_i16(xi, gi, oracle.SCALED, 127)[0]
+    nhwc = layout == wg.NHWC
+    xd = torch.from_numpy(wl.to_nhwc(x) if nhwc else x).cuda()
+    packed = wg.winograd_filter_transform_u8(torch.from_numpy(wl.to_krsc(g) if nhwc else g).cuda(), zw, layout, mode)
+    assert np.array_equal(_nchw(wg.winograd_conv2d_u8(xd, zx, packed, layout), layout), want)
+
+
+def test_mismatched_filters_leave_the_output_untouched_with_split_channels():
+    """The kernels find a blob of another layer on the device and write nothing, in both halves of a split convolution."""
+    x, g, xd, gd = _inputs((1, 512, 64, 8, 8), wg.NHWC)
+    for mode in (wg.LOSSLESS, wg.SCALED):
+        packed = wg.winograd_filter_transform(gd, wg.NHWC, mode)
+        packed.blob[8] += 1            # K in the header
+        out = torch.full((1, 8, 8, 64), 123, dtype=torch.int32, device="cuda")
+        wg.winograd_conv2d_int8(xd, packed, wg.NHWC, out=out)
+        assert bool((out == 123).all())
