@@ -280,11 +280,7 @@ int winograd_conv2d_int8_enqueue_stage(const int8_t* x_dev, const void* packed_d
 
 int direct_conv2d_int8(const int8_t* x_dev, const int8_t* w_dev, int32_t* y_dev, int N, int C, int H, int W,
                        int K, int layout, void* hip_stream) {
-    if (!x_dev || !w_dev || !y_dev || !valid_layout(layout)) return WG_EINVAL;
-    if (int st = check_shape(N, C, H, W, K)) return st;
-    if (!aligned(x_dev, 4) || !aligned(w_dev, 4) || !aligned(y_dev, 4)) return WG_EINVAL;
-    return status_of(launch_direct_conv(x_dev, w_dev, y_dev, make_problem(N, C, H, W, K), layout,
-                                        static_cast<hipStream_t>(hip_stream)));
+    return direct_conv2d_with_scratch(x_dev, w_dev, y_dev, N, C, H, W, K, layout, nullptr, 0, hip_stream);
 }
 
 int requant_relu_pool_int8(const int32_t* y_dev, int8_t* out_dev, int N, int K, int H, int W, int layout,
@@ -376,6 +372,20 @@ int conv2d_u8_with_scratch(const uint8_t* x, int zero_point, const void* packed,
     if (!aligned(x, 4) || !aligned(y, 4) || !aligned(packed, 256) || !aligned(scratch, 256)) return WG_EINVAL;
     return status_of(launch_fused_conv_u8(x, zero_point, packed, y, make_problem(N, C, H, W, K), layout, mode,
                                           Scratch{scratch, scratch_bytes}, static_cast<hipStream_t>(stream)));
+}
+
+size_t direct_conv2d_scratch_bytes(int N, int C, int H, int W, int K, int layout) {
+    if (check_shape(N, C, H, W, K) != WG_OK || !valid_layout(layout)) return 0;
+    return direct_conv_scratch_wanted(make_problem(N, C, H, W, K), layout);
+}
+
+int direct_conv2d_with_scratch(const int8_t* x, const int8_t* w, int32_t* y, int N, int C, int H, int W, int K, int layout, void* scratch,
+                               size_t scratch_bytes, void* stream) {
+    if (!x || !w || !y || !valid_layout(layout)) return WG_EINVAL;
+    if (int st = check_shape(N, C, H, W, K)) return st;
+    if (!aligned(x, 4) || !aligned(w, 4) || !aligned(y, 4) || !aligned(scratch, 256)) return WG_EINVAL;
+    return status_of(launch_direct_conv(x, w, y, make_problem(N, C, H, W, K), layout, Scratch{scratch, scratch_bytes},
+                                        static_cast<hipStream_t>(stream)));
 }
 
 }  // namespace wg

@@ -1,10 +1,11 @@
 // Direct evaluation of the 3x3 stride-1 pad-1 convolution, the method with 144
 // multiplications per 4x4 output tile and channel pair that Section 3.4 compares
 // against:  y[n,k,h,w] = sum_{c,a,b} x[n,c,h+a-1,w+b-1] g[k,c,a,b].
-// Serves as the on-device cross-check and the direct baseline.  Channels-last tensors with
-// K % 4 == 0 and a 16-byte aligned output run on the matrix cores (operands are staged with
-// 16-byte loads when C % 16 == 0 and the pointers allow it, else byte by byte); everything else
-// takes the plain kernel.
+// Serves as the on-device cross-check and the direct baseline.  Where scratch memory (or the layout) allows, the
+// matrix product over linear pixels in direct_gemm.hip runs; this file has what is left for calls without scratch memory and
+// for rows too long for that kernel's LDS: channels-last tensors with K % 4 == 0 and a 16-byte aligned output on the matrix
+// cores by patches (operands are staged with 16-byte loads when C % 16 == 0 and the pointers allow it, else byte by byte),
+// everything else in the plain kernel; and the requantisation kernels.
 #include "wg_internal.h"
 
 namespace wg {
@@ -161,7 +162,60 @@ __global__ __launch_bounds__(256) void direct_conv_mfma_kernel(const int8_t* __r
         }
 }
 
-// v = (y + 2^(shift-1)) >> shift, clamp, optional 2x2 max-pool; one thread per output element.
+// v = (y + 2^(shift-1)) >> shift without the sum (y is any int32): the arithmetic shift plus the last bit shifted out.
+__device__ inline v4i requant_any(v4i y, int shift, int lo) {
+    if (shift > 0) y = (y >> shift) + ((y >> (shift - 1)) & 1);
+    const v4i low = {lo, lo, lo, lo}, high = {127, 127, 127, 127};
+    return __builtin_elementwise_min(__builtin_elementwise_max(y, low), high);
+}
+__device__ inline uint32_t bytes_of(v4i v) {
+    return (uint32_t)(v[0] & 0xff) | ((uint32_t)(v[1] & 0xff) << 8) | ((uint32_t)(v[2] & 0xff) << 16) | ((uint32_t)v[3] << 24);
+}
+// Without pooling every output is a function of the input at the same place, whatever the layout: four (a thread's 16-byte
+// load and 4-byte store) at a time.  Bound by memory: 5 bytes per element.
+__global__ __launch_bounds__(256) void requant_kernel(const int32_t* __restrict__ y, int8_t* __restrict__ out, size_t total, int shift, int lo) {
+    const size_t i = 4 * ((size_t)blockIdx.x * 256 + threadIdx.x);
+    if (i + 4 <= total) {
+        *reinterpret_cast<uint32_t*>(out + i) = bytes_of(requant_any(*reinterpret_cast<const v4i*>(y + i), shift, lo));
+    } else {
+        for (size_t j = i; j < total; ++j) out[j] = (int8_t)requant_any((v4i){y[j], 0, 0, 0}, shift, lo)[0];
+    }
+}
+// 2x2 stride-2 maximum, four outputs per thread: four channels of a pixel (channels-last, K % 4 = 0: `run` = K, four 16-byte
+// loads) or four pixels of a row (channel-major, (W / 2) % 4 = 0: two rows of eight values).  256 -> 256 outputs at 56x56,
+// N = 16: 17 us with one thread and four 4-byte loads per output, 11 us so.
+template <int LAYOUT>
+__global__ __launch_bounds__(256) void requant_pool4_kernel(const int32_t* __restrict__ y, int8_t* __restrict__ out, uint32_t quads, int run,
+                                                            int W, FastDiv div_run4, FastDiv div_wo, int shift, int lo) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;   // output quad
+    if (i >= quads) return;
+    v4i best;
+    if constexpr (LAYOUT == WG_NHWC) {
+        // output pixel q of the batch: row q / Wo (two input rows each), column q % Wo
+        const uint32_t q = fast_div(i, div_run4), k4 = i - q * ((uint32_t)run >> 2), row = fast_div(q, div_wo), col = q - row * ((uint32_t)W >> 1);
+        const int32_t* at = y + ((size_t)(2 * row) * W + 2 * col) * run + 4 * k4;
+        v4i v[4];
+        v[0] = *reinterpret_cast<const v4i*>(at);
+        v[1] = *reinterpret_cast<const v4i*>(at + run);
+        v[2] = *reinterpret_cast<const v4i*>(at + (size_t)W * run);
+        v[3] = *reinterpret_cast<const v4i*>(at + (size_t)W * run + run);
+        best = __builtin_elementwise_max(__builtin_elementwise_max(v[0], v[1]), __builtin_elementwise_max(v[2], v[3]));
+    } else {
+        const uint32_t row = fast_div(i, div_wo), c4 = i - row * ((uint32_t)W >> 3);   // div_wo: quads per output row
+        const int32_t* at = y + (size_t)(2 * row) * W + 8 * c4;
+        v4i v[4];
+        v[0] = *reinterpret_cast<const v4i*>(at);
+        v[1] = *reinterpret_cast<const v4i*>(at + 4);
+        v[2] = *reinterpret_cast<const v4i*>(at + W);
+        v[3] = *reinterpret_cast<const v4i*>(at + W + 4);
+        const v4i a = __builtin_elementwise_max(v[0], v[2]), b = __builtin_elementwise_max(v[1], v[3]);
+        best = (v4i){max(a[0], a[1]), max(a[2], a[3]), max(b[0], b[1]), max(b[2], b[3])};
+    }
+    // rounding and clamp do not change the order, so the maximum comes first
+    *reinterpret_cast<uint32_t*>(out + 4 * (size_t)i) = bytes_of(requant_any(best, shift, lo));
+}
+
+// ... and one output element per thread, for the shapes the kernel above does not take.
 template <int LAYOUT>
 __global__ __launch_bounds__(256) void requant_relu_pool_kernel(const int32_t* __restrict__ y,
                                                                 int8_t* __restrict__ out, int N, int K,
@@ -195,9 +249,48 @@ __global__ __launch_bounds__(256) void requant_relu_pool_kernel(const int32_t* _
 
 }  // namespace
 
+namespace {
+
+bool aligned16(const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; }
+
+// What the linear-pixel kernel (direct_gemm.hip) needs: channels-last operands with 16-byte pieces, as given or as padded
+// copies.  It takes every layer whose image rows fit its LDS and whose (padded) operands fit 32-bit offsets.
+struct DirectPlan {
+    bool applies, copy_x, copy_w;
+    Problem padded;
+    size_t x_bytes, bytes;   // scratch: the copies of x and w
+};
+DirectPlan plan_direct(const Problem& p, int layout, bool operands_aligned) {
+    DirectPlan d;
+    d.copy_x = d.copy_w = layout != WG_NHWC || p.C % 16 != 0 || !operands_aligned;
+    d.padded = p;
+    if (d.copy_x) d.padded.C = ceil_div(p.C, 16) * 16;
+    const long long limit = 0x7fffffffll, C = d.padded.C;
+    d.applies = (long long)p.N * p.H * p.W * C <= limit && (long long)p.K * 9 * C <= limit && direct_gemm_applies(d.padded);
+    d.x_bytes = d.applies && d.copy_x ? round_up((size_t)p.N * p.H * p.W * C, 256) : 0;
+    d.bytes = d.x_bytes + (d.applies && d.copy_w ? round_up((size_t)p.K * 9 * C, 256) : 0);
+    return d;
+}
+
+}  // namespace
+
+size_t direct_conv_scratch_wanted(const Problem& p, int layout) { return plan_direct(p, layout, true).bytes; }
+
 hipError_t launch_direct_conv(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, int layout,
-                              hipStream_t s) {
-    auto aligned16 = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
+                              const Scratch& scratch, hipStream_t s) {
+    const DirectPlan d = plan_direct(p, layout, aligned16(x) && aligned16(w));
+    if (d.applies && d.bytes <= scratch.bytes) {
+        if (d.copy_x) {
+            int8_t* const xs = static_cast<int8_t*>(scratch.p);
+            int8_t* const ws = xs + d.x_bytes;
+            if (hipError_t e = launch_channels_last(x, xs, p, layout, d.padded.C, 0, s)) return e;
+            // [K][C][3][3] (or [K][3][3][C]) as a batch of K images of nine pixels
+            if (hipError_t e = launch_channels_last(w, ws, make_problem(p.K, p.C, 3, 3, 1), layout, d.padded.C, 0, s)) return e;
+            x = xs;
+            w = ws;
+        }
+        return launch_direct_gemm(x, w, y, d.padded, layout, s);
+    }
     if (layout == WG_NHWC && p.K % 4 == 0 && aligned16(y)) {
         const int patches_h = ceil_div(p.H, kPatchRows), patches_w = ceil_div(p.W, kPatchCols);
         dim3 grid((unsigned)(p.N * patches_h * patches_w), ceil_div(p.K, kDirectFilters));
@@ -217,8 +310,22 @@ hipError_t launch_direct_conv(const int8_t* x, const int8_t* w, int32_t* y, cons
 hipError_t launch_requant_relu_pool(const int32_t* y, int8_t* out, int N, int K, int H, int W, int layout,
                                     int shift, int relu, int pool, hipStream_t s) {
     const size_t total = (size_t)N * K * (pool ? H / 2 : H) * (pool ? W / 2 : W);
-    const unsigned blocks = (unsigned)((total + 255) / 256);
     const int lo = relu ? 0 : -128;
+    const bool vectors = aligned16(y) && reinterpret_cast<uintptr_t>(out) % 4 == 0;
+    if (!pool && vectors) {
+        requant_kernel<<<(unsigned)((total + 1023) / 1024), 256, 0, s>>>(y, out, total, shift, lo);
+        return hipGetLastError();
+    }
+    const unsigned quads = (unsigned)(total / 4), quad_blocks = (quads + 255) / 256;
+    if (pool && vectors && layout == WG_NHWC && K % 4 == 0) {
+        requant_pool4_kernel<WG_NHWC><<<quad_blocks, 256, 0, s>>>(y, out, quads, K, W, make_fast_div(K / 4), make_fast_div(W / 2), shift, lo);
+        return hipGetLastError();
+    }
+    if (pool && vectors && layout == WG_NCHW && W % 8 == 0) {
+        requant_pool4_kernel<WG_NCHW><<<quad_blocks, 256, 0, s>>>(y, out, quads, 0, W, make_fast_div(1), make_fast_div(W / 8), shift, lo);
+        return hipGetLastError();
+    }
+    const unsigned blocks = (unsigned)((total + 255) / 256);
     if (layout == WG_NHWC) requant_relu_pool_kernel<WG_NHWC><<<blocks, 256, 0, s>>>(y, out, N, K, H, W, shift, lo, pool);
     else                   requant_relu_pool_kernel<WG_NCHW><<<blocks, 256, 0, s>>>(y, out, N, K, H, W, shift, lo, pool);
     return hipGetLastError();

@@ -556,7 +556,8 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
     Plan plan = {false, 1, p.CB};
     size_t left = scratch_bytes;
     if (layout != WG_NHWC || p.C % 4 != 0) {
-        plan.copies = left >= channels_last_bytes(p);
+        // (the copy is addressed with 32-bit offsets)
+        plan.copies = left >= channels_last_bytes(p) && (long long)p.N * p.H * p.W * padded_channels(p.C) <= 0x7fffffffll;
         if (!plan.copies) return plan;
         left -= channels_last_bytes(p);
     }

@@ -225,8 +225,10 @@ PyObject* direct_conv2d(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int K = (int)w.size(0);
         const at::Tensor y = output(a[3], d.N, K, d.H, d.W, layout, at::kInt, x);
         void* const s = stream();
+        const ScratchTensor scratch(wg::direct_conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout), x);
         return finish(y, [&] {
-            return direct_conv2d_int8(data<int8_t>(x), data<int8_t>(w), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, s);
+            return wg::direct_conv2d_with_scratch(data<int8_t>(x), data<int8_t>(w), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout,
+                                                  scratch.p, scratch.bytes, s);
         });
     });
 }

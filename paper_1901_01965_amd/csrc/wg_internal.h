@@ -283,8 +283,13 @@ hipError_t launch_fused_conv_u8(const uint8_t* x, int zero_point, const void* bl
 // Single-kernel path for channels-last inputs with C <= kNarrowChannels.
 hipError_t launch_narrow_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p, int mode,
                               const Int8Epilogue& q8, hipStream_t s);
+// Direct convolution; with scratch memory for channels-last copies of both operands any layout and channel count runs as a
+// matrix product over linear pixels (direct_gemm.hip: channels-last, p.C % 16 = 0, filters [K][9][C]).
+size_t direct_conv_scratch_wanted(const Problem& p, int layout);
 hipError_t launch_direct_conv(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p,
-                              int layout, hipStream_t s);
+                              int layout, const Scratch& scratch, hipStream_t s);
+bool direct_gemm_applies(const Problem& p);
+hipError_t launch_direct_gemm(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, int layout, hipStream_t s);
 hipError_t launch_requant_relu_pool(const int32_t* y, int8_t* out, int N, int K, int H, int W,
                                     int layout, int shift, int relu, int pool, hipStream_t s);
 hipError_t launch_unpack_activation_planes(const int8_t* V, int8_t* dense, const Problem& p, int mode,
