@@ -1,0 +1,281 @@
+// The complex F(4x4,3x3) path with the activations of every tile scaled as well (act_scale.h), in two kernels: the factors
+// of all tiles first, then a role-specialised convolution with them.  One kernel that does both (fused_conv.hip) transforms
+// every tile twice per filter block, 2 K / 32 times in all, and the transform is what the kernels of this path are bound by:
+// 256 -> 256 channels at 14x14, N = 64: 54 us.  Here a tile is transformed once for its factors and K / 64 times for its
+// products, and the products run beside the next channel block's transform.
+#include "act_scale.h"
+#include "roles_conv.h"
+
+namespace wg {
+namespace {
+
+// ---- factors ---------------------------------------------------------------------------------------------
+// grid: ceil(T / 4), 64 CB threads: wave = 64-channel block, lane = (tile, four channels).  Bound by the latency of one patch
+// load and one transform.
+__global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
+                                                           uint32_t* __restrict__ factors, int32_t* __restrict__ act_table, Problem p) {
+    __shared__ int maxima[4 * kEntries];
+    const int tid = threadIdx.x, lane = tid & 63, cb = tid >> 6;
+    const BlobHeaderWords header = read_blob_header(blob);
+    const int t = blockIdx.x * 4 + (lane >> 4), cq = lane & 15;
+    int n = 0, ty = 0, tx = 0;
+    if (t < p.T) decode_tile(p, t, n, ty, tx);
+    uint32_t pixel[36], patch[6][6];
+    patch_offsets(p, n, ty, tx, 4 * cq, pixel);
+    request_patch(activation_buffer(x, p), p, pixel, cb, 4 * cq, patch);
+    for (int i = tid; i < 4 * kEntries; i += blockDim.x) maxima[i] = 0;
+    __syncthreads();
+    s16x2 mx[kEntries];
+#pragma unroll
+    for (int e = 0; e < kEntries; ++e) mx[e] = (s16x2){0, 0};
+    PatchBias<SignedInt8>().apply(patch);
+    transform_patch(patch, MaxKeeper{mx});
+    // over the sixteen threads of a tile, two entries per register; then one LDS maximum per tile, entry and wave
+#pragma unroll
+    for (int j = 0; j < kEntries / 2; ++j) {
+        s16x2 m = {max(mx[2 * j].x, mx[2 * j].y), max(mx[2 * j + 1].x, mx[2 * j + 1].y)};
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1)
+            m = __builtin_elementwise_max(m, as_s16x2((uint32_t)__shfl_xor((int)as_u32(m), off)));
+        if (cq == j) {
+            atomicMax(&maxima[(lane >> 4) * kEntries + 2 * j], (int)m.x);
+            atomicMax(&maxima[(lane >> 4) * kEntries + 2 * j + 1], (int)m.y);
+        }
+    }
+    __syncthreads();
+    if (!blob_matches(header, p.K, p.Cf, WG_SCALED)) return;
+    for (int i = tid; i < 4 * kEntries; i += blockDim.x) {
+        const size_t at = (size_t)blockIdx.x * 4 * kEntries + i;   // [tile][entry]
+        if (at >= (size_t)p.T * kEntries) break;
+        const uint32_t entry = kActScale.v[min(maxima[i], kActMax)];
+        factors[at] = entry;
+        if (act_table != nullptr) *reinterpret_cast<v4i*>(act_table + 4 * at) = act_table_row(entry);
+    }
+}
+
+// ---- products ---------------------------------------------------------------------------------------------
+// A wave's half of the entries; every sum is a matrix-core accumulator for the whole kernel.  A complex entry multiplies with
+// Wr and Wi only: Re = Dr Wr - Di Wi needs an accumulator of its own for Di Wi.
+template <int HALF, int RING>
+struct ActProducts {
+    using Phase = ProductPhase<kScaledTwoPlanes, HALF>;
+    static constexpr int NE = Phase::NE, NB = Phase::NB;
+    static constexpr int acc_start(int slot) {   // real: D W; complex: Dr Wr, Im, Di Wi
+        int n = 0;
+        for (int s = 0; s < slot; ++s) n += is_real(half_slot(HALF, s).entry) ? 1 : 3;
+        return n;
+    }
+    static constexpr int kAcc = acc_start(NE);
+    v4i ring[RING], acc[kAcc];
+    __device__ inline void clear() {
+#pragma unroll
+        for (int i = 0; i < kAcc; ++i) acc[i] = (v4i){0, 0, 0, 0};
+    }
+    __device__ inline void prefetch(const LaneContext& cx) {
+        static_for<(NB < RING ? NB : RING)>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
+    }
+    __device__ inline void run(const LaneContext& cx) {
+        static_for<NE>([&](auto S) {
+            constexpr int entry = half_slot(HALF, S).entry, b = b_start<kScaledTwoPlanes>(HALF, S), v = acc_start(S);
+            constexpr int plane = is_real(entry) ? entry : kRealEntries + 2 * (entry - kRealEntries);
+            const v4i re = *reinterpret_cast<const v4i*>(cx.a_lds + plane * kPlaneBytes);
+            auto mac = [&](int to, v4i d, int filter) {
+                acc[v + to] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d, ring[(b + filter) % RING], acc[v + to], 0, 0, 0);
+            };
+            mac(0, re, 0);
+            if constexpr (!is_real(entry)) {
+                const v4i im = *reinterpret_cast<const v4i*>(cx.a_lds + (plane + 1) * kPlaneBytes);
+                mac(1, re, 1);
+                mac(2, im, 1);
+                mac(1, im, 0);
+            }
+            static_for<num_b<kScaledTwoPlanes>(entry)>([&](auto I) {
+                if constexpr (b + I + RING < NB) ring[(b + I) % RING] = Phase::template load_b<b + I + RING>(cx);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+    // The filter's reverse scaling, then the tile's (register q of a lane belongs to tile 4 (lane / 16) + q), and the output
+    // transform.
+    __device__ inline void finish(const LaneContext& cx, const uint32_t* rq_tab, int lane, v4i (&Y)[16]) const {
+        v4i er[6], ei[6];
+        static_for<NE>([&](auto S) {
+            constexpr Slot sl = half_slot(HALF, S);
+            constexpr int v = acc_start(S);
+            v4i re = acc[v], im = {0, 0, 0, 0};
+            if constexpr (!is_real(sl.entry)) {
+                re -= acc[v + 2];
+                im = acc[v + 1];
+            }
+            const ReverseScale filter_side = parked_scale<S>(cx);
+            const v4i rq = *reinterpret_cast<const v4i*>(rq_tab + sl.entry * 16 + 4 * (lane >> 4));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const ReverseScale tile_side((int)(((uint32_t)rq[q] >> 16) & 255u), (int)((uint32_t)rq[q] >> 24));
+                re[q] = tile_side(filter_side(re[q]));
+                if constexpr (!is_real(sl.entry)) im[q] = tile_side(filter_side(im[q]));
+            }
+            er[sl.pos] = re;
+            ei[sl.pos] = im;
+            if constexpr (sl.last_in_row) finish_row<sl.row>(er, ei, Y);
+        });
+    }
+};
+
+constexpr int kActPlaneBuffer = kActPlanes * kPlaneBytes;   // 36 KB per channel block, double-buffered
+// The transform's factors lie behind the planes, where (PW = 8) the second half of the outputs is staged later; what the
+// finishing lanes read lies behind what is staged.
+constexpr int kActFactorsOff = kLdsBytes;
+template <int PW> constexpr int act_rq_off() { return PW == 8 ? 2 * kLdsBytes : kLdsBytes + kActNpBytes; }
+template <int PW> constexpr int act_lds_bytes() { return act_rq_off<PW>() + kActRqBytes + PW * kParkedScaleBytes; }
+static_assert(2 * kActPlaneBuffer <= kLdsBytes && act_lds_bytes<8>() <= 160 * 1024, "LDS of one compute unit");
+
+// grid (ceil(T/16), Kp/(8 PW)), 64 (4 + PW) threads: the roles of fused_conv_roles_kernel (roles_kernel.h): waves 0-3 transform one
+// channel block ahead, the others multiply; product wave pw owns filter block pw % (PW / 2) and half pw / (PW / 2) of the entries.
+template <int LAYOUT, int PW>
+__global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
+                                                                         size_t table_off, size_t planes_off, int32_t* __restrict__ y,
+                                                                         const uint32_t* __restrict__ factors, Problem p) {
+    extern __shared__ __attribute__((aligned(16))) int8_t lds[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int bx = blockIdx.x, by = blockIdx.y;
+    {
+        const int total = gridDim.x * gridDim.y;
+        if (gridDim.y >= 2 && (total & 7) == 0) {   // XCD-major order, as in fused_conv_body
+            const int launch = blockIdx.y * gridDim.x + blockIdx.x;
+            const int w = (launch & 7) * (total >> 3) + (launch >> 3);
+            by = w / (int)gridDim.x;
+            bx = w - by * (int)gridDim.x;
+        }
+    }
+    const int tile0 = bx * kFusedTiles, k0 = by * 8 * PW;
+    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.Cf, WG_SCALED)) return;
+    v4i* const np_tab = reinterpret_cast<v4i*>(lds + kActFactorsOff);
+    uint32_t* const rq_tab = reinterpret_cast<uint32_t*>(lds + act_rq_off<PW>());
+    // the tiles' factors; tiles beyond the last one keep n = 1
+    auto expand_factors = [&] {
+        for (int i = threadIdx.x; i < 16 * kEntries; i += 64 * (4 + PW)) {
+            const int tile = i / kEntries, e = i - tile * kEntries;
+            const uint32_t entry = tile0 + tile < p.T ? factors[(size_t)tile0 * kEntries + i] : 0x00010000u;
+            np_tab[i] = act_factors(entry);
+            rq_tab[e * 16 + tile] = entry;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+    };
+
+    if (wave < 4) {
+        const int tid = threadIdx.x, a_tile = tid >> 4, a_cq = tid & 15, a_t = tile0 + a_tile;
+        int n = 0, ty = 0, tx = 0;
+        if (a_t < p.T) decode_tile(p, a_t, n, ty, tx);
+        uint32_t patch[6][6], row_off[6], col_off[6];
+        const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
+        const uint32_t image = (uint32_t)n * (uint32_t)p.H * (uint32_t)p.W * (uint32_t)p.C + (uint32_t)(4 * a_cq);
+#pragma unroll
+        for (int a = 0; a < 6; ++a) {
+            const int h = 4 * ty - 1 + a, w = 4 * tx - 1 + a;
+            row_off[a] = (unsigned)h < (unsigned)p.H ? image + (uint32_t)h * (uint32_t)p.W * (uint32_t)p.C : kOutsideOffset;
+            col_off[a] = (unsigned)w < (unsigned)p.W ? (uint32_t)w * (uint32_t)p.C : kOutsideOffset;
+        }
+        auto request = [&](int cb) {
+            const bool have = (cb + 1) * kCBlock <= p.C || cb * kCBlock + 4 * a_cq < p.C;
+#pragma unroll
+            for (int i = 0; i < 36; ++i) {
+                const uint32_t at = __builtin_elementwise_add_sat(row_off[i / 6], col_off[i % 6]);
+                patch[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, have ? at : kOutsideOffset, cb * kCBlock, 0);
+            }
+        };
+        request(0);
+        ScaledPlanes out;
+        int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
+        out.np = np_tab + a_tile * kEntries;
+        expand_factors();
+        for (int cb = 0; cb < p.CB; ++cb) {
+            if (cb > 0) {   // barrier cb
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+            }
+            out.sink.base = slot + (cb & 1) * kActPlaneBuffer;
+            PatchBias<SignedInt8>().apply(patch);
+            transform_patch(patch, out);
+            if (cb + 1 < p.CB) request(cb + 1);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // barrier CB: the last block's planes are published
+        __syncthreads();                // the two barriers of the product waves' store
+        __syncthreads();
+        return;
+    }
+
+    const int pw = wave - 4, kblock_all = pw % (PW / 2), half = pw / (PW / 2);
+    const int kblock = kblock_all & 1, group = kblock_all >> 1;
+    const int k = k0 + kblock_all * 16 + (lane & 15);
+    LaneContext cx;
+    cx.table_k = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
+    int8_t* const scale_area = lds + act_rq_off<PW>() + kActRqBytes + pw * kParkedScaleBytes;
+    constexpr int NP = 46;
+    const int8_t* b_lane = reinterpret_cast<const int8_t*>(blob + planes_off) + filter_plane_offset(0, 0, k, (lane >> 4) * 16, p.Kp, NP);
+    const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
+    v4i Y[16];
+    // one loop per half (the same barriers in both), so that each is allocated registers on its own
+    auto blocks = [&](auto H) {
+        ActProducts<H, 8> products;
+        ParkedScales<H> scales;
+        scales.ask(cx, lane);
+        cx.b_glob = b_lane;
+        products.prefetch(cx);
+        scales.park(cx, scale_area, lane);
+        products.clear();
+        expand_factors();
+        for (int cb = 0; cb < p.CB; ++cb) {
+            if (cb > 0) {
+                cx.b_glob = b_lane + cb * b_block_stride;
+                products.prefetch(cx);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();   // barrier cb + 1
+            cx.a_lds = lds + (cb & 1) * kActPlaneBuffer + lds_slot(lane >> 4, lane & 15) * 16;
+            products.run(cx);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) Y[i] = (v4i){0, 0, 0, 0};
+        products.finish(cx, rq_tab, lane, Y);
+    };
+    if (half == 0) blocks(std::integral_constant<int, 0>{}); else blocks(std::integral_constant<int, 1>{});
+    StoreContext sc;
+    sc.lds = lds + group * kLdsBytes;   // the 32-filter halves of the workgroup stage and store side by side
+    sc.tid = (2 * half + kblock) * 64 + lane;
+    sc.lane = lane; sc.rnd = 8; sc.y = y;
+    locate_tile<LAYOUT>(sc, p, tile0);
+    __syncthreads();   // the operand planes are dead
+    stage_outputs(sc.lds, lane, half, kblock, Y);
+    __syncthreads();
+    store_staged<LAYOUT, false, true>(sc, p, Int8Epilogue{}, k0 + group * kFusedFilters);
+}
+
+}  // namespace
+
+hipError_t launch_act_factors(const RolesCall& c, uint32_t* factors, int32_t* act_table, hipStream_t s) {
+    act_factors_kernel<<<ceil_div(c.p.T, 4), 64 * c.p.CB, 0, s>>>(c.x, c.blob, factors, act_table, c.p);
+    return hipGetLastError();
+}
+
+hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, hipStream_t s) {
+    // 64 filters per workgroup unless a 64-filter grid leaves more than half of the compute units idle (see fused_conv.hip)
+    auto go = [&](auto L, auto W) -> hipError_t {
+        constexpr int PW = W;
+        static LdsLimitOnce lds_limit;   // per instance
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW>), act_lds_bytes<PW>())) return e;
+        const dim3 grid(ceil_div(c.p.T, kFusedTiles), c.p.Kp / (8 * PW));
+        act_scaled_roles_kernel<L, PW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y,
+                                                                                      factors, c.p);
+        return hipGetLastError();
+    };
+    using std::integral_constant;
+    const bool wide = 2LL * ceil_div(c.p.T, kFusedTiles) * (c.p.Kp / 64) > compute_units();
+    if (c.layout == WG_NHWC)
+        return wide ? go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 4>{});
+    return wide ? go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 4>{});
+}
+
+}  // namespace wg

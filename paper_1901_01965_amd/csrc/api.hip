@@ -74,12 +74,7 @@ int winograd_conv2d_u8(const uint8_t* x_dev, int zero_point, const void* packed_
 
 int winograd_conv2d_int8_act_scaled(const int8_t* x_dev, const void* packed_dev, int32_t* y_dev, int N, int C, int H, int W,
                                     int K, int layout, int32_t* act_table_dev, void* hip_stream) {
-    if (!x_dev || !packed_dev || !y_dev || !valid_layout(layout)) return WG_EINVAL;
-    if (int st = check_shape(N, C, H, W, K)) return st;
-    if (!aligned(x_dev, 4) || !aligned(y_dev, 4) || !aligned(packed_dev, 256)) return WG_EINVAL;
-    if (act_table_dev && !aligned(act_table_dev, 16)) return WG_EINVAL;
-    return status_of(launch_fused_conv_act_scaled(x_dev, packed_dev, y_dev, act_table_dev, make_problem(N, C, H, W, K), layout,
-                                                  static_cast<hipStream_t>(hip_stream)));
+    return conv2d_int8_act_scaled_with_scratch(x_dev, packed_dev, y_dev, N, C, H, W, K, layout, act_table_dev, nullptr, 0, hip_stream);
 }
 
 int winograd_packed_filter_check(const void* packed_dev, int K, int C, int mode, void* hip_stream) {
@@ -386,6 +381,21 @@ int direct_conv2d_with_scratch(const int8_t* x, const int8_t* w, int32_t* y, int
     if (!aligned(x, 4) || !aligned(w, 4) || !aligned(y, 4) || !aligned(scratch, 256)) return WG_EINVAL;
     return status_of(launch_direct_conv(x, w, y, make_problem(N, C, H, W, K), layout, Scratch{scratch, scratch_bytes},
                                         static_cast<hipStream_t>(stream)));
+}
+
+size_t act_scaled_scratch_bytes(int N, int C, int H, int W, int K, int layout) {
+    if (check_shape(N, C, H, W, K) != WG_OK || !valid_layout(layout)) return 0;
+    return act_scaled_scratch_wanted(make_problem(N, C, H, W, K), layout);
+}
+
+int conv2d_int8_act_scaled_with_scratch(const int8_t* x, const void* packed, int32_t* y, int N, int C, int H, int W, int K, int layout,
+                                        int32_t* act_table, void* scratch, size_t scratch_bytes, void* stream) {
+    if (!x || !packed || !y || !valid_layout(layout)) return WG_EINVAL;
+    if (int st = check_shape(N, C, H, W, K)) return st;
+    if (!aligned(x, 4) || !aligned(y, 4) || !aligned(packed, 256) || !aligned(scratch, 256)) return WG_EINVAL;
+    if (act_table && !aligned(act_table, 16)) return WG_EINVAL;
+    return status_of(launch_fused_conv_act_scaled(x, packed, y, act_table, make_problem(N, C, H, W, K), layout,
+                                                  Scratch{scratch, scratch_bytes}, static_cast<hipStream_t>(stream)));
 }
 
 }  // namespace wg

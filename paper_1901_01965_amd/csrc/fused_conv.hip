@@ -22,6 +22,7 @@
 // contraction kernel uses; those would need half again as many operand planes.
 #include <algorithm>
 
+#include "act_scale.h"
 #include "product_core.h"
 #include "roles_conv.h"
 
@@ -263,73 +264,10 @@ hipError_t launch_layout(const int8_t* x, const uint8_t* b, const BlobLayout& bl
     return launch_mode<WG_NCHW, kLoadBytes, Q8>(x, b, bl, y, p, mode, q8, s);
 }
 
-// ---- activations scaled as well (the remark that closes Section 4.1) --------------------------------------------
-// Section 4.1 ends by noting that the analysis of Section 4.2 applies to B^T d B too (12 bits here for int8 data).
-// The rule used is that section's with a tile in the place of an output feature map: at each of a tile's 26 free
-// entries the largest max(|Re|, |Im|) over the input channels decides one factor n/2^p, Re and Im of every channel's
-// value there are multiplied by it (round half up), and the channel sums are multiplied back by its reciprocal r/2^q
-// after the filter's.  Both operands are then single int8 values: one matrix-core instruction per real product, 36
-// operand planes instead of 72, channel sums accumulated by the matrix cores themselves.
-//
-// (n, p, r, q) for every possible maximum of int8 data, one byte each (n = 0: within the range, nothing applied).
-constexpr int kActMax = 16 * 128;
-struct ActScaleTable {
-    uint32_t v[kActMax + 1];
-};
-constexpr ActScaleTable make_act_scale_table() {
-    ActScaleTable t = {};
-    for (int mx = 0; mx <= kActMax; ++mx) {
-        uint32_t n = 0, p = 0, r = 1, q = 0;
-        if (mx > kWeightRange) {
-            const int num = kWeightRange * 128;
-            int y = 0;
-            while ((mx << (y + 1)) <= num) ++y;
-            n = (uint32_t)((num * 8) / (mx << y));
-            p = (uint32_t)(10 - y);
-            for (int qq = 7; qq >= 0; --qq) {
-                const uint32_t rr = ((2u << (p + qq)) + n) / (2 * n);
-                if (rr <= 255) { r = rr; q = (uint32_t)qq; break; }
-            }
-        }
-        t.v[mx] = n | (p << 8) | (r << 16) | (q << 24);
-    }
-    return t;
-}
-__device__ const ActScaleTable kActScale = make_act_scale_table();
-
-constexpr int kActPlanes = 36;                       // 16 real entries, then (Re, Im) of each complex entry
-static_assert(kActPlanes * kPlaneBytes <= kLdsBytes, "the single-limb planes lie where the two-limb planes do");
-constexpr int kActNpOff = kLdsBytes;                 // v4i [tile][26]: (n, n), (half, half), (p, p) in 16-bit pairs
-constexpr int kActRqOff = kActNpOff + 16 * kEntries * 16;   // uint32 [26][tile]: the table entry (r, q in its upper bytes)
-constexpr int kActLdsBytes = kActRqOff + kEntries * 16 * 4;
-
-__device__ inline s16x2 abs_max(Quad v) {
-    const s16x2 zero = {0, 0};
-    return __builtin_elementwise_max(__builtin_elementwise_max(v.a, zero - v.a), __builtin_elementwise_max(v.b, zero - v.b));
-}
-// transform_patch's receiver in the first pass: running maxima per free entry, two channels per register
-struct MaxKeeper {
-    s16x2* mx;
-    __device__ inline void real_entry(int p, Quad v) const { mx[p] = __builtin_elementwise_max(mx[p], abs_max(v)); }
-    __device__ inline void complex_entry(int j, Quad re, Quad im) const {
-        mx[kRealEntries + j] = __builtin_elementwise_max(mx[kRealEntries + j], __builtin_elementwise_max(abs_max(re), abs_max(im)));
-    }
-};
-// ... and in the second: every value times its tile's factor, rounded half up, as one int8 operand plane
-struct ScaledPlanes {
-    LdsPlaneSink sink;
-    const v4i* np;   // this tile's 26 factors
-    __device__ inline uint32_t scaled(int entry, Quad v) const {
-        const v4i t = np[entry];
-        const s16x2 mul = as_s16x2((uint32_t)t[0]), half = as_s16x2((uint32_t)t[1]), sh = as_s16x2((uint32_t)t[2]);
-        return pack_low_bytes(Quad{(v.a * mul + half) >> sh, (v.b * mul + half) >> sh});
-    }
-    __device__ inline void real_entry(int p, Quad v) const { sink.put(p, scaled(p, v)); }
-    __device__ inline void complex_entry(int j, Quad re, Quad im) const {
-        sink.put(kRealEntries + 2 * j, scaled(kRealEntries + j, re));
-        sink.put(kRealEntries + 2 * j + 1, scaled(kRealEntries + j, im));
-    }
-};
+// ---- activations scaled as well (act_scale.h) in one kernel, for calls without scratch memory -------------------
+constexpr int kActNpOff = kLdsBytes;
+constexpr int kActRqOff = kActNpOff + kActNpBytes;
+constexpr int kActLdsBytes = kActRqOff + kActRqBytes;
 
 // Product phase: the channel sums of a wave's entries (18 of four registers) are the matrix cores' accumulators.
 //   real:    sum += D W;    complex: Re += Dr Wr + Di (-Wi),  Im += Dr Wi + Di Wr
@@ -461,12 +399,10 @@ __global__ __launch_bounds__(256) void fused_conv_act_scaled_kernel(const int8_t
             const int e = 16 * part + a_cq;
             if (e >= kEntries) break;
             const uint32_t entry = kActScale.v[min(mine[part], kActMax)];
-            const uint32_t n = max(entry & 255u, 1u), sh = (entry >> 8) & 255u, hf = (1u << sh) >> 1;
-            np_tab[a_tile * kEntries + e] = (v4i){(int)(n * 0x00010001u), (int)(hf * 0x00010001u), (int)(sh * 0x00010001u), 0};
+            np_tab[a_tile * kEntries + e] = act_factors(entry);
             rq_tab[e * 16 + a_tile] = entry;
             if (act_table != nullptr && blockIdx.y == 0 && a_t < p.T)
-                *reinterpret_cast<v4i*>(act_table + ((size_t)a_t * kEntries + e) * 4) =
-                    (v4i){(int)(entry & 255u), (int)((entry >> 8) & 255u), (int)((entry >> 16) & 255u), (int)(entry >> 24)};
+                *reinterpret_cast<v4i*>(act_table + ((size_t)a_t * kEntries + e) * 4) = act_table_row(entry);
         }
     }
     __syncthreads();
@@ -721,10 +657,33 @@ hipError_t launch_fused_conv_u8(const uint8_t* x_u8, int zero_point, const void*
     return launch_u8_mode<WG_NCHW, kLoadBytes>(x, zero, b, bl, y, p, mode, s);
 }
 
+// With scratch memory: factors first, then a role-specialised kernel (act_scaled_conv.hip), through a channels-last copy where
+// the layout asks for one.  Without: both passes in the four-wave kernel.
+static Plan plan_act_scaled(const Problem& p, int layout, size_t scratch_bytes) {
+    Plan plan = {false, 1, p.CB};
+    if (layout != WG_NHWC || p.C % 4 != 0)
+        plan.copies = scratch_bytes >= channels_last_bytes(p) && (long long)p.N * p.H * p.W * padded_channels(p.C) <= 0x7fffffffll;
+    return plan;
+}
+
+size_t act_scaled_scratch_wanted(const Problem& p, int layout) {
+    return (plan_act_scaled(p, layout, ~(size_t)0 >> 1).copies ? channels_last_bytes(p) : 0) + act_factor_bytes(p);
+}
+
 hipError_t launch_fused_conv_act_scaled(const int8_t* x, const void* blob, int32_t* y, int32_t* act_table, const Problem& p,
-                                        int layout, hipStream_t s) {
+                                        int layout, const Scratch& scratch, hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
+    if (scratch.bytes >= act_scaled_scratch_wanted(p, layout)) {
+        RolesCall c = {x, nullptr, b, bl, y, p, layout, no_int8_epilogue()};
+        int32_t* rest;
+        hipError_t status;
+        if (make_fast_call(c, plan_act_scaled(p, layout, scratch.bytes), layout, scratch, rest, s, status)) {
+            if (status == hipSuccess) status = launch_act_factors(c, reinterpret_cast<uint32_t*>(rest), act_table, s);
+            if (status == hipSuccess) status = launch_act_scaled_roles(c, reinterpret_cast<const uint32_t*>(rest), s);
+            return status;
+        }
+    }
     dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / kFusedFilters);
     auto go = [&](auto kernel) -> hipError_t {
         static LdsLimitOnce lds_limit;   // per kernel: the lambda's body is instantiated once per argument type

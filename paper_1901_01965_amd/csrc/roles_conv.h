@@ -36,6 +36,11 @@ hipError_t launch_stream_scaled(const RolesCall& c, bool wide, hipStream_t s);
 inline hipError_t launch_stream(const RolesCall& c, int mode, bool wide, hipStream_t s) {
     return mode == WG_LOSSLESS ? launch_stream_lossless(c, wide, s) : launch_stream_scaled(c, wide, s);
 }
+// Activations scaled per tile as well (WG_SCALED blob, signed int8): the factors of every tile into factors (uint32 [T][26],
+// act_factor_bytes; act_table: null or the exported int32 [T][26][4]), then the convolution with them.
+inline size_t act_factor_bytes(const Problem& p) { return round_up((size_t)p.T * kEntries * sizeof(uint32_t), 256); }
+hipError_t launch_act_factors(const RolesCall& c, uint32_t* factors, int32_t* act_table, hipStream_t s);
+hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, hipStream_t s);
 // Workgroups per filter block of the streaming kernel: about one workgroup per compute unit in total (a test hook can set
 // a smaller number, so that small problems stream, too).
 int stream_workgroups(int tile_blocks, int filter_blocks);

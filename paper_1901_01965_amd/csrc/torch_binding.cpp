@@ -203,9 +203,13 @@ PyObject* conv2d_act_scaled(PyObject*, PyObject* const* a, Py_ssize_t n) {
         int32_t* const table = a[6] == Py_None ? nullptr : data<int32_t>(tensor(a[6], at::kInt, "table"));
         const at::Tensor y = output(a[5], d.N, K, d.H, d.W, layout, at::kInt, x);
         void* const s = stream();
+        const ScratchTensor scratch(f2x2 ? 0 : wg::act_scaled_scratch_bytes(d.N, d.C, d.H, d.W, K, layout), x);
         return finish(y, [&] {
-            return (f2x2 ? winograd_f2x2_conv2d_int8_act_scaled : winograd_conv2d_int8_act_scaled)(
-                data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, table, s);
+            if (f2x2)
+                return winograd_f2x2_conv2d_int8_act_scaled(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K,
+                                                            layout, table, s);
+            return wg::conv2d_int8_act_scaled_with_scratch(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K,
+                                                           layout, table, scratch.p, scratch.bytes, s);
         });
     });
 }

@@ -214,6 +214,13 @@ inline WorkspaceLayout workspace_layout(const Problem& p, int mode) {
     return w;
 }
 
+// Device memory a convolution may use while it runs (bytes = 0: none); what it would like to have is scratch_wanted().
+struct Scratch {
+    void* p;
+    size_t bytes;
+};
+inline Scratch no_scratch() { return Scratch{nullptr, 0}; }
+
 // ---- stage launchers (each enqueues on `s` and returns the launch status) --------
 // is_unsigned: the bytes are uint8 with the given zero point (values = byte - zero_point, the int9
 // of Section 4.1) and the blob gets kBlobMagicInt9; otherwise signed int8 and zero_point is ignored.
@@ -237,12 +244,6 @@ inline Int8Epilogue no_int8_epilogue() { return Int8Epilogue{nullptr, 0, 0, 0, 0
 inline Int8Epilogue make_int8_epilogue(int8_t* out, int shift, bool relu, bool pool) {
     return Int8Epilogue{out, shift, shift > 0 ? 1 << (shift - 1) : 0, relu ? 0 : -128, pool ? 1 : 0};
 }
-// Device memory a convolution may use while it runs (bytes = 0: none); what it would like to have is scratch_wanted().
-struct Scratch {
-    void* p;
-    size_t bytes;
-};
-inline Scratch no_scratch() { return Scratch{nullptr, 0}; }
 size_t fused_conv_scratch_wanted(const Problem& p, int layout, int mode, bool is_unsigned);
 // Single-kernel path.  With scratch: inputs that the fast loads cannot read go through a channels-last copy, and small
 // deep layers deal their channel blocks to several workgroups; without it these run as they can.
@@ -275,8 +276,9 @@ void set_stream_variant(int v);
 hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s);
 // Single-kernel path with the activations scaled per tile as well (WG_SCALED blob of signed int8 filters).
 // act_table: null, or int32 [T][26][4] that receives every tile's (n, p, r, q).
+size_t act_scaled_scratch_wanted(const Problem& p, int layout);
 hipError_t launch_fused_conv_act_scaled(const int8_t* x, const void* blob, int32_t* y, int32_t* act_table, const Problem& p,
-                                        int layout, hipStream_t s);
+                                        int layout, const Scratch& scratch, hipStream_t s);
 // Single-kernel path for uint8 activations with a zero point and a kBlobMagicInt9 blob (C <= kMaxChannelsInt9).
 hipError_t launch_fused_conv_u8(const uint8_t* x, int zero_point, const void* blob, int32_t* y, const Problem& p, int layout,
                                 int mode, const Scratch& scratch, hipStream_t s);

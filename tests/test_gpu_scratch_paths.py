@@ -81,3 +81,21 @@ def test_mismatched_filters_leave_the_output_untouched_with_split_channels():
         out = torch.full((1, 8, 8, 64), 123, dtype=torch.int32, device="cuda")
         wg.winograd_conv2d_int8(xd, packed, wg.NHWC, out=out)
         assert bool((out == 123).all())
+
+
+@pytest.mark.parametrize("layout", [wg.NCHW, wg.NHWC])
+@pytest.mark.parametrize("shape", [(1, 5, 33, 7, 6), (2, 130, 65, 10, 9), (40, 64, 160, 14, 14), (1, 896, 20, 4, 5)])
+def test_both_sides_scaled_with_and_without_scratch(shape, layout):
+    """32 and 64 filters per workgroup, one to fourteen channel blocks, against the oracle; the C ABI's entry point has no
+    scratch memory and runs both passes in one kernel."""
+    N, C, K, H, W = shape
+    x, g, xd, gd = _inputs(shape, layout)
+    want = oracle.winograd_conv2d(x, g, 2, 127)[0]
+    packed = wg.winograd_filter_transform(gd, layout, wg.SCALED)
+    got, table = wg.winograd_conv2d_int8_act_scaled(xd, packed, layout, want_table=True)
+    assert np.array_equal(_nchw(got, layout), want)
+    bare, bare_table = torch.full_like(got, 77), torch.zeros_like(table)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert wg.load_library().winograd_conv2d_int8_act_scaled(p(xd), p(packed.blob), p(bare), N, C, H, W, K, layout, p(bare_table), stream) == 0
+    assert torch.equal(bare, got) and torch.equal(bare_table, table)
