@@ -139,7 +139,7 @@ static int f2_filter_transform(const void* w_dev, int is_unsigned, int zero_poin
 }
 
 static int f2_conv2d(const void* x_dev, int is_unsigned, int zero_point, const void* packed_dev, int32_t* y_dev, int N,
-                     int C, int H, int W, int K, int layout, int mode, void* hip_stream) {
+                     int C, int H, int W, int K, int layout, int mode, const Scratch& scratch, void* hip_stream) {
     if (!x_dev || !packed_dev || !y_dev || !valid_layout(layout) || !valid_mode(mode)) return WG_EINVAL;
     if (is_unsigned && (zero_point < 0 || zero_point > 255)) return WG_EINVAL;
     if (int st = check_shape(N, C, H, W, K)) return st;
@@ -147,23 +147,15 @@ static int f2_conv2d(const void* x_dev, int is_unsigned, int zero_point, const v
     if (tiles + kTilePad > kIndexLimit / 64) return WG_EUNSUPPORTED;
     if (!aligned(x_dev, 4) || !aligned(y_dev, 4) || !aligned(packed_dev, 256)) return WG_EINVAL;
     return status_of(launch_f2_conv(static_cast<const int8_t*>(x_dev), is_unsigned, zero_point, packed_dev, y_dev,
-                                    make_problem_f2(N, C, H, W, K), layout, mode, no_int8_epilogue(),
+                                    make_problem_f2(N, C, H, W, K), layout, mode, no_int8_epilogue(), scratch,
                                     static_cast<hipStream_t>(hip_stream)));
 }
 
 int winograd_f2x2_conv2d_int8_requant(const int8_t* x_dev, const void* packed_dev, int8_t* out_dev, int N, int C, int H,
                                       int W, int K, int layout, int mode, int shift, int relu, int pool,
                                       void* hip_stream) {
-    if (!x_dev || !packed_dev || !out_dev || !valid_layout(layout) || !valid_mode(mode)) return WG_EINVAL;
-    if (shift < 0 || shift > 31) return WG_EINVAL;
-    if (int st = check_shape(N, C, H, W, K)) return st;
-    const long long tiles = (long long)N * ((H + 1) / 2) * ((W + 1) / 2);
-    if (tiles + kTilePad > kIndexLimit / 64) return WG_EUNSUPPORTED;
-    if (!aligned(x_dev, 4) || !aligned(out_dev, 4) || !aligned(packed_dev, 256)) return WG_EINVAL;
-    if (pool && ((H | W) & 1)) return WG_EUNSUPPORTED;
-    return status_of(launch_f2_conv(x_dev, 0, 0, packed_dev, nullptr, make_problem_f2(N, C, H, W, K), layout, mode,
-                                    make_int8_epilogue(out_dev, shift, relu != 0, pool != 0),
-                                    static_cast<hipStream_t>(hip_stream)));
+    return f2x2_conv2d_int8_requant_with_scratch(x_dev, packed_dev, out_dev, N, C, H, W, K, layout, mode, shift, relu, pool, nullptr, 0,
+                                                 hip_stream);
 }
 
 int winograd_f2x2_filter_transform(const int8_t* w_dev, int K, int C, int layout, int mode, void* packed_dev,
@@ -178,12 +170,12 @@ int winograd_f2x2_filter_transform_u8(const uint8_t* w_dev, int zero_point, int 
 
 int winograd_f2x2_conv2d_int8(const int8_t* x_dev, const void* packed_dev, int32_t* y_dev, int N, int C, int H,
                               int W, int K, int layout, int mode, void* hip_stream) {
-    return f2_conv2d(x_dev, 0, 0, packed_dev, y_dev, N, C, H, W, K, layout, mode, hip_stream);
+    return f2_conv2d(x_dev, 0, 0, packed_dev, y_dev, N, C, H, W, K, layout, mode, no_scratch(), hip_stream);
 }
 
 int winograd_f2x2_conv2d_u8(const uint8_t* x_dev, int zero_point, const void* packed_dev, int32_t* y_dev, int N, int C,
                             int H, int W, int K, int layout, int mode, void* hip_stream) {
-    return f2_conv2d(x_dev, 1, zero_point, packed_dev, y_dev, N, C, H, W, K, layout, mode, hip_stream);
+    return f2_conv2d(x_dev, 1, zero_point, packed_dev, y_dev, N, C, H, W, K, layout, mode, no_scratch(), hip_stream);
 }
 
 int winograd_f2x2_conv2d_int8_act_scaled(const int8_t* x_dev, const void* packed_dev, int32_t* y_dev, int N, int C,
@@ -396,6 +388,32 @@ int conv2d_int8_act_scaled_with_scratch(const int8_t* x, const void* packed, int
     if (act_table && !aligned(act_table, 16)) return WG_EINVAL;
     return status_of(launch_fused_conv_act_scaled(x, packed, y, act_table, make_problem(N, C, H, W, K), layout,
                                                   Scratch{scratch, scratch_bytes}, static_cast<hipStream_t>(stream)));
+}
+
+size_t f2x2_conv2d_scratch_bytes(int N, int C, int H, int W, int K, int layout) {
+    if (check_shape(N, C, H, W, K) != WG_OK || !valid_layout(layout)) return 0;
+    return f2_conv_scratch_wanted(make_problem_f2(N, C, H, W, K), layout);
+}
+
+int f2x2_conv2d_with_scratch(const void* x, int is_unsigned, int zero_point, const void* packed, int32_t* y, int N, int C, int H, int W,
+                             int K, int layout, int mode, void* scratch, size_t scratch_bytes, void* stream) {
+    if (!aligned(scratch, 256)) return WG_EINVAL;
+    return f2_conv2d(x, is_unsigned, zero_point, packed, y, N, C, H, W, K, layout, mode, Scratch{scratch, scratch_bytes}, stream);
+}
+
+int f2x2_conv2d_int8_requant_with_scratch(const int8_t* x, const void* packed, int8_t* out, int N, int C, int H, int W, int K,
+                                          int layout, int mode, int shift, int relu, int pool, void* scratch, size_t scratch_bytes,
+                                          void* stream) {
+    if (!x || !packed || !out || !valid_layout(layout) || !valid_mode(mode)) return WG_EINVAL;
+    if (shift < 0 || shift > 31) return WG_EINVAL;
+    if (int st = check_shape(N, C, H, W, K)) return st;
+    const long long tiles = (long long)N * ((H + 1) / 2) * ((W + 1) / 2);
+    if (tiles + kTilePad > kIndexLimit / 64) return WG_EUNSUPPORTED;
+    if (!aligned(x, 4) || !aligned(out, 4) || !aligned(packed, 256) || !aligned(scratch, 256)) return WG_EINVAL;
+    if (pool && ((H | W) & 1)) return WG_EUNSUPPORTED;
+    return status_of(launch_f2_conv(x, 0, 0, packed, nullptr, make_problem_f2(N, C, H, W, K), layout, mode,
+                                    make_int8_epilogue(out, shift, relu != 0, pool != 0), Scratch{scratch, scratch_bytes},
+                                    static_cast<hipStream_t>(stream)));
 }
 
 }  // namespace wg

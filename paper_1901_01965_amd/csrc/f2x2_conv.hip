@@ -733,14 +733,27 @@ hipError_t launch_f2_unpack_filter_planes(const void* blob_v, int8_t* dense, int
     return hipGetLastError();
 }
 
+static bool f2_needs_copy(const Problem& p, int layout) { return layout != WG_NHWC || p.C % 4 != 0; }
+static bool f2_copy_fits(const Problem& p) { return (long long)p.N * p.H * p.W * padded_channels(p.C) <= 0x7fffffffll; }
+
+size_t f2_conv_scratch_wanted(const Problem& p, int layout) {
+    return f2_needs_copy(p, layout) && f2_copy_fits(p) ? channels_last_bytes(p) : 0;
+}
+
 hipError_t launch_f2_conv(const int8_t* x, int is_unsigned, int zero_point, const void* blob, int32_t* y, const Problem& p,
-                          int layout, int mode, const Int8Epilogue& q8, hipStream_t s) {
+                          int layout, int mode, const Int8Epilogue& q8, const Scratch& scratch, hipStream_t s) {
+    if (!f2_needs_copy(p, layout)) return launch_f2_fast(x, is_unsigned, zero_point, blob, y, p, layout, mode, q8, s);
+    if (f2_copy_fits(p) && scratch.bytes >= channels_last_bytes(p)) {
+        int8_t* const copy = static_cast<int8_t*>(scratch.p);
+        Problem padded = p;
+        padded.C = padded_channels(p.C);
+        if (hipError_t e = launch_channels_last(x, copy, p, layout, padded.C, is_unsigned ? (uint8_t)zero_point : 0, s)) return e;
+        return launch_f2_fast(copy, is_unsigned, zero_point, blob, y, padded, layout, mode, q8, s);
+    }
     const uint32_t bias = is_unsigned ? (uint32_t)zero_point : 128u;
     const ActivationBias ab = {is_unsigned ? 0u : 0x80808080u, bias * 0x01010101u, (int)(4 * bias)};
     const F2BlobLayout bl = f2_blob_layout(p.Kp, p.C, mode);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
-    if (layout == WG_NHWC && p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0)
-        return launch_mode<WG_NHWC, true>(x, b, bl, y, p, mode, ab, q8, s);
     if (layout == WG_NHWC) return launch_mode<WG_NHWC, false>(x, b, bl, y, p, mode, ab, q8, s);
     return launch_mode<WG_NCHW, false>(x, b, bl, y, p, mode, ab, q8, s);
 }

@@ -157,11 +157,12 @@ PyObject* conv2d_int8_requant(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& blob = tensor(a[1], at::kByte, "blob");
         const at::Tensor y = output(a[6], d.N, K, pool ? d.H / 2 : d.H, pool ? d.W / 2 : d.W, layout, at::kChar, x);
         void* const s = stream();
-        const ScratchTensor scratch(f2x2 ? 0 : wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 0), x);
+        const ScratchTensor scratch(f2x2 ? wg::f2x2_conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout)
+                                         : wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 0), x);
         return finish(y, [&] {
             if (f2x2)
-                return winograd_f2x2_conv2d_int8_requant(data<int8_t>(x), blob.data_ptr(), data<int8_t>(y), d.N, d.C, d.H, d.W, K, layout,
-                                                         mode, shift, relu, pool, s);
+                return wg::f2x2_conv2d_int8_requant_with_scratch(data<int8_t>(x), blob.data_ptr(), data<int8_t>(y), d.N, d.C, d.H, d.W, K,
+                                                                 layout, mode, shift, relu, pool, scratch.p, scratch.bytes, s);
             return wg::conv2d_int8_requant_with_scratch(data<int8_t>(x), blob.data_ptr(), data<int8_t>(y), d.N, d.C, d.H, d.W, K, layout,
                                                         mode, shift, relu, pool, scratch.p, scratch.bytes, s);
         });
@@ -180,14 +181,14 @@ PyObject* conv2d_bytes(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& blob = tensor(a[2], at::kByte, "blob");
         const at::Tensor y = output(a[7], d.N, K, d.H, d.W, layout, at::kInt, x);
         void* const s = stream();
-        const ScratchTensor scratch(f2x2 ? 0 : wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 1), x);
+        const ScratchTensor scratch(f2x2 ? wg::f2x2_conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout)
+                                         : wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 1), x);
         return finish(y, [&] {
-            if (!f2x2)
-                return wg::conv2d_u8_with_scratch(data<uint8_t>(x), zero, blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout,
-                                                  mode, scratch.p, scratch.bytes, s);
-            if (!is_unsigned)
-                return winograd_f2x2_conv2d_int8(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode, s);
-            return winograd_f2x2_conv2d_u8(data<uint8_t>(x), zero, blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode, s);
+            if (f2x2)
+                return wg::f2x2_conv2d_with_scratch(x.data_ptr(), is_unsigned, zero, blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K,
+                                                    layout, mode, scratch.p, scratch.bytes, s);
+            return wg::conv2d_u8_with_scratch(data<uint8_t>(x), zero, blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode,
+                                              scratch.p, scratch.bytes, s);
         });
     });
 }

@@ -161,6 +161,13 @@ inline BlobLayout blob_layout(int Kp, int C, int mode) {
     return b;
 }
 
+// Device memory a convolution may use while it runs (bytes = 0: none); what it would like to have is scratch_wanted().
+struct Scratch {
+    void* p;
+    size_t bytes;
+};
+inline Scratch no_scratch() { return Scratch{nullptr, 0}; }
+
 // ---- rational F(2x2,3x3) (Sections 4.1-4.2) ----------------------------------------
 // Its packed filter blob: [BlobHeader][maxmag: uint32 [Kp][16]][table: ScaleEntry [Kp][16]]
 // [operand planes: int8 [CB][Kp/16][planes][16][64]] with planes = 32 (lossless: entry e as limbs
@@ -199,7 +206,11 @@ struct Int8Epilogue;   // defined with the single-kernel path's launchers below
 hipError_t launch_f2_conv_act_scaled(const int8_t* x, const void* blob, int32_t* y, int32_t* act_table, const Problem& p,
                                      int layout, hipStream_t s);
 hipError_t launch_f2_conv(const int8_t* x, int is_unsigned, int zero_point, const void* blob, int32_t* y, const Problem& p,
-                          int layout, int mode, const Int8Epilogue& q8, hipStream_t s);
+                          int layout, int mode, const Int8Epilogue& q8, const Scratch& scratch, hipStream_t s);
+size_t f2_conv_scratch_wanted(const Problem& p, int layout);   // for a channels-last copy
+// Channels-last activations with p.C % 4 = 0 (see f2x2_fast.hip).
+hipError_t launch_f2_fast(const int8_t* x, int is_unsigned, int zero_point, const void* blob, int32_t* y, const Problem& p, int layout,
+                          int mode, const Int8Epilogue& q8, hipStream_t s);
 
 // ---- workspace ------------------------------------------------------------------
 // [V: int8 [planes][CB][Tp][64]][M: int32 [46 lossless | 36 scaled][Tp][Kp]]
@@ -213,13 +224,6 @@ inline WorkspaceLayout workspace_layout(const Problem& p, int mode) {
     w.total = w.m_off + (size_t)(mode == WG_LOSSLESS ? kMaxWorkspacePlanes : kAccPlanes) * p.Tp * p.Kp * sizeof(int32_t);
     return w;
 }
-
-// Device memory a convolution may use while it runs (bytes = 0: none); what it would like to have is scratch_wanted().
-struct Scratch {
-    void* p;
-    size_t bytes;
-};
-inline Scratch no_scratch() { return Scratch{nullptr, 0}; }
 
 // ---- stage launchers (each enqueues on `s` and returns the launch status) --------
 // is_unsigned: the bytes are uint8 with the given zero point (values = byte - zero_point, the int9
