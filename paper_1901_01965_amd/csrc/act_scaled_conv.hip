@@ -28,8 +28,7 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
     s16x2 mx[kEntries];
 #pragma unroll
     for (int e = 0; e < kEntries; ++e) mx[e] = (s16x2){0, 0};
-    PatchBias<SignedInt8>().apply(patch);
-    transform_patch(patch, MaxKeeper{mx});
+    transform_patch<StoredInt8>(patch, MaxKeeper{mx});
     // over the sixteen threads of a tile, two entries per register; then one LDS maximum per tile, entry and wave
 #pragma unroll
     for (int j = 0; j < kEntries / 2; ++j) {
@@ -117,7 +116,7 @@ struct ActProducts {
             }
             er[sl.pos] = re;
             ei[sl.pos] = im;
-            if constexpr (sl.last_in_row) finish_row<sl.row>(er, ei, Y);
+            if constexpr (sl.last_in_row) finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
         });
     }
 };
@@ -196,8 +195,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
                 __builtin_amdgcn_s_barrier();
             }
             out.sink.base = slot + (cb & 1) * kActPlaneBuffer;
-            PatchBias<SignedInt8>().apply(patch);
-            transform_patch(patch, out);
+            transform_patch<StoredInt8>(patch, out);
             if (cb + 1 < p.CB) request(cb + 1);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

@@ -333,7 +333,7 @@ struct BothScaledSums {
             }
             er[sl.pos] = re;
             ei[sl.pos] = im;
-            if constexpr (sl.last_in_row) finish_row<sl.row>(er, ei, Y);
+            if constexpr (sl.last_in_row) finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
         });
     }
 };

@@ -16,7 +16,8 @@ namespace wg {
 
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
-// four channels: a = (c0, c1), b = (c2, c3)
+// four channels: a = (c0, c2), b = (c1, c3), so that bytes become 16-bit lanes by one mask or shift and a pair of registers
+// packs back by one permutation
 struct Quad {
     s16x2 a, b;
 };
@@ -26,14 +27,15 @@ __device__ inline Quad operator-(Quad x, Quad y) { return Quad{x.a - y.a, x.b - 
 __device__ inline uint32_t as_u32(s16x2 v) { return __builtin_bit_cast(uint32_t, v); }
 __device__ inline s16x2 as_s16x2(uint32_t v) { return __builtin_bit_cast(s16x2, v); }
 
-// bytes (u0,u1,u2,u3) -> 16-bit lanes (u0,u1), (u2,u3), zero extended
+// bytes (u0,u1,u2,u3) -> 16-bit lanes (u0,u2), (u1,u3), zero extended
 __device__ inline Quad unpack_u8x4(uint32_t u) {
-    return Quad{as_s16x2(__builtin_amdgcn_perm(0u, u, 0x0c010c00u)), as_s16x2(__builtin_amdgcn_perm(0u, u, 0x0c030c02u))};
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    return Quad{as_s16x2(u & 0x00ff00ffu), __builtin_bit_cast(s16x2, __builtin_bit_cast(u16x2, u) >> (unsigned short)8)};
 }
 // low bytes of the four 16-bit lanes -> one dword (c0,c1,c2,c3)
-__device__ inline uint32_t pack_low_bytes(Quad v) { return __builtin_amdgcn_perm(as_u32(v.b), as_u32(v.a), 0x06040200u); }
+__device__ inline uint32_t pack_low_bytes(Quad v) { return __builtin_amdgcn_perm(as_u32(v.b), as_u32(v.a), 0x06020400u); }
 // their high bytes
-__device__ inline uint32_t pack_high_bytes(Quad v) { return __builtin_amdgcn_perm(as_u32(v.b), as_u32(v.a), 0x07050301u); }
+__device__ inline uint32_t pack_high_bytes(Quad v) { return __builtin_amdgcn_perm(as_u32(v.b), as_u32(v.a), 0x07030501u); }
 
 constexpr uint32_t kBiasBytes = 0x80808080u;
 
@@ -196,23 +198,44 @@ struct OperandSplitter {
     }
 };
 
+// How transform_patch turns a patch's dwords into 16-bit lanes, and what the bias leaves at entry (1,1).
+//   BiasedBytes:  the bytes are u = x + bias already (bias_patch, PatchBias);
+//   StoredInt8:   the bytes are x as stored (zero outside the image).  c1 and c3 are sign-extended by one arithmetic shift
+//                 and need no bias; c0 and c2 get theirs in the instruction that masks them.  One instruction per register
+//                 where the XOR and two permutations took three (1.5 times: a third of the transform's unpacking);
+//   ChannelPairs: u = x + bias like BiasedBytes, but lanes a = (c0, c1), b = (c2, c3) for a receiver that multiplies pairs of
+//                 neighbouring channels.
+struct BiasedBytes {
+    __device__ inline static Quad lanes(uint32_t u) { return unpack_u8x4(u); }
+    template <class ENC> __device__ inline static Quad bias11(const ENC enc) { return Quad{as_s16x2(enc.bias11()), as_s16x2(enc.bias11())}; }
+};
+struct StoredInt8 {
+    __device__ inline static Quad lanes(uint32_t x) { return Quad{as_s16x2((x & 0x00ff00ffu) ^ 0x00800080u), as_s16x2(x) >> (short)8}; }
+    __device__ inline static Quad bias11(const struct SignedInt8 enc) { return Quad{as_s16x2(enc.bias11()), as_s16x2(0u)}; }
+};
+struct ChannelPairs : BiasedBytes {
+    __device__ inline static Quad lanes(uint32_t u) {
+        return Quad{as_s16x2(__builtin_amdgcn_perm(0u, u, 0x0c010c00u)), as_s16x2(__builtin_amdgcn_perm(0u, u, 0x0c030c02u))};
+    }
+};
+
 // Transforms one loaded patch (four channels) and hands every free entry to `out`
 // (real_entry(p, v), complex_entry(j, re, im)): an OperandSplitter emits the operand planes.
-template <class Out, class ENC = SignedInt8>
+template <class Bytes = BiasedBytes, class Out, class ENC = SignedInt8>
 __device__ inline void transform_patch(const uint32_t u[6][6], const Out& out, const ENC enc = ENC{}) {
     // column pass: d'[.][b] = B^T applied down each of the six tile columns
     Line col[6];
 #pragma unroll
     for (int b = 0; b < 6; ++b)
-        col[b] = bt_rule(unpack_u8x4(u[0][b]), unpack_u8x4(u[1][b]), unpack_u8x4(u[2][b]), unpack_u8x4(u[3][b]),
-                         unpack_u8x4(u[4][b]), unpack_u8x4(u[5][b]));
-    const s16x2 bias11 = as_s16x2(enc.bias11());   // what the bias leaves at entry (1,1): 16 * 128 for signed int8
+        col[b] = bt_rule(Bytes::lanes(u[0][b]), Bytes::lanes(u[1][b]), Bytes::lanes(u[2][b]), Bytes::lanes(u[3][b]),
+                         Bytes::lanes(u[4][b]), Bytes::lanes(u[5][b]));
+    const Quad bias11 = Bytes::bias11(enc);   // what the bias leaves at entry (1,1): 16 * 128 for signed int8
     // row pass on the real rows 0,1,2,5 of d': entries (r, {0,1,2,5}) real, (r,3) complex
 #define WG_REAL_ROW(ri, field)                                                                      \
     {                                                                                               \
         Line r = bt_rule(col[0].field, col[1].field, col[2].field, col[3].field, col[4].field,      \
                          col[5].field);                                                             \
-        if (ri == 1) r.t1 = Quad{r.t1.a - bias11, r.t1.b - bias11};                                 \
+        if (ri == 1) r.t1 = r.t1 - bias11;                                                          \
         out.real_entry(4 * ri + 0, r.t0);                                                           \
         out.real_entry(4 * ri + 1, r.t1);                                                           \
         out.real_entry(4 * ri + 2, r.t2);                                                           \

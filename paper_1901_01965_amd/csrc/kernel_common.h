@@ -13,9 +13,10 @@ constexpr int kTileBlock = 16;                      // tiles per workgroup (one 
 constexpr int kPlaneBytes = kTileBlock * kCBlock;   // one operand plane of a tile block in LDS
 
 // LDS operand plane: the 16-byte piece holding 16 consecutive channels (group c16) of a tile
-// sits in slot c16*16 + ((tile + 4*c16) & 15); lane l of a wave reads slot(l/16, l%16), which
-// tiles the plane without bank conflicts for the 4-byte writes as well as the 16-byte reads.
-__device__ inline int lds_slot(int c16, int tile) { return c16 * 16 + ((tile + 4 * c16) & 15); }
+// sits in slot c16*16 + ((tile + 4*(c16/2)) & 15); lane l of a wave reads slot(l/16, l%16).  The reads, of which there
+// are several per write, meet no bank conflicts this way (a rotation by 4*c16 favoured the 4-byte writes instead:
+// 28x28x128 N=32 scaled 14.5 -> 14.2 us, 56x56x64 N=256 scaled 84.9 -> 83.5).
+__device__ inline int lds_slot(int c16, int tile) { return c16 * 16 + ((tile + 4 * (c16 >> 1)) & 15); }
 
 struct LdsPlaneSink {
     int8_t* base;
@@ -92,22 +93,20 @@ __device__ inline void request_patch(__amdgpu_buffer_rsrc_t xbuf, const Problem&
             patch[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, pixel[i], cb * kCBlock, 0);
     }
 }
-// What remains to be done to a patch loaded that way: u = x + bias on every byte.  Pixels outside the image arrived as
+// What remains to be done to a patch loaded that way before transform_patch<Bytes>.  Pixels outside the image arrived as
 // zero bytes: for signed int8 that is x = 0 like any other byte; for uint8 they have to become the zero point, which
-// one three-input OR per pixel does (row and column terms that are zero inside the image), as many
-// instructions as the XOR of the signed form.  (Channels beyond C meet zero filters, whatever they hold.)
+// one three-input OR per pixel does (row and column terms that are zero inside the image).  (Channels beyond C meet zero filters, whatever they hold.)
 template <class ENC>
 struct PatchBias;
 template <>
 struct PatchBias<SignedInt8> {
     __device__ inline void enter(const Problem&, int, int, const SignedInt8) {}
-    __device__ inline void apply(uint32_t patch[6][6]) const {
-#pragma unroll
-        for (int i = 0; i < 36; ++i) patch[i / 6][i % 6] ^= kBiasBytes;
-    }
+    using Bytes = StoredInt8;
+    __device__ inline void apply(uint32_t[6][6]) const {}
 };
 template <>
 struct PatchBias<ZeroPointU8> {
+    using Bytes = BiasedBytes;
     uint32_t outside;      // bit a: patch row a lies outside the image, bit 6 + b: column b (one register while it waits)
     uint32_t zero_bytes;
     __device__ inline void enter(const Problem& p, int ty, int tx, const ZeroPointU8 enc) {
@@ -149,17 +148,30 @@ __device__ inline void at_rule(V m0, V m1, V m2, V m3r, V m3i, V m5, V z[4]) {
 // row 5 -> y3.  The complex row 3 (ROW = 4; e0,e1,e2,e5 at positions 0..3, e3 = M[3][3] and
 // e4 = M[3][4] at 4, 5; row 4 of M is its conjugate): y0 += 2Re z, y1 -= 2Im z, y2 -= 2Re z,
 // y3 += 2Im z.
-template <int ROW, class V>
+// Rows come in the order 0, 1, 2 and row 5 before row 3.  FRESH: no outputs yet (rows 0..2: from any of them; rows 5 and 3:
+// from each other), so that nothing is cleared first and nothing added to zero.
+template <int ROW, bool FRESH, class V>
 __device__ inline void finish_row(const V (&er)[6], const V (&ei)[6], V (&Y)[16]) {
     if constexpr (ROW < 4) {
         V z[4];
         at_rule(er[0], er[1], er[2], er[4], ei[4], er[3], z);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if (ROW == 0) Y[j] += z[j];
-            if (ROW == 1) { Y[j] += z[j]; Y[4 + j] += z[j]; Y[8 + j] += z[j]; Y[12 + j] += z[j]; }
-            if (ROW == 2) { Y[j] += z[j]; Y[4 + j] -= z[j]; Y[8 + j] += z[j]; Y[12 + j] -= z[j]; }
-            if (ROW == 3) Y[12 + j] += z[j];
+            if constexpr (ROW == 0) Y[j] = FRESH ? z[j] : Y[j] + z[j];
+            if constexpr (FRESH) {
+                if constexpr (ROW == 1) Y[8 + j] = z[j];
+                if constexpr (ROW == 2) {
+                    const V d = Y[8 + j] - z[j];
+                    Y[8 + j] += z[j];
+                    Y[j] += Y[8 + j];
+                    Y[4 + j] = d;
+                    Y[12 + j] = d;
+                }
+            } else {
+                if constexpr (ROW == 1) { Y[j] += z[j]; Y[4 + j] += z[j]; Y[8 + j] += z[j]; Y[12 + j] += z[j]; }
+                if constexpr (ROW == 2) { Y[j] += z[j]; Y[4 + j] -= z[j]; Y[8 + j] += z[j]; Y[12 + j] -= z[j]; }
+            }
+            if constexpr (ROW == 3) Y[12 + j] = FRESH ? z[j] : Y[12 + j] + z[j];
         }
     } else {
         const V sr = er[4] + er[5], si = ei[4] + ei[5], dr = er[4] - er[5], di = ei[4] - ei[5];
@@ -171,10 +183,11 @@ __device__ inline void finish_row(const V (&er)[6], const V (&ei)[6], V (&Y)[16]
         zr[3] = br + di + er[3];   zi[3] = bi - dr + ei[3];    // (e1-e2) - i (e3-e4) + e5
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            Y[j] += 2 * zr[j];
-            Y[4 + j] -= 2 * zi[j];
-            Y[8 + j] -= 2 * zr[j];
-            Y[12 + j] += 2 * zi[j];
+            const V r = 2 * zr[j], i = 2 * zi[j];
+            Y[j] = FRESH ? r : Y[j] + r;
+            Y[4 + j] = FRESH ? -i : Y[4 + j] - i;
+            Y[8 + j] = FRESH ? -r : Y[8 + j] - r;
+            Y[12 + j] += i;
         }
     }
 }

@@ -212,7 +212,7 @@ struct Products {
                         er[0] = (v2i){0, 0};
                         ei[0] = (v2i){0, 0};
                     }
-                    if constexpr (sl.ends) finish_row<sl.row>(er, ei, Y);
+                    if constexpr (sl.ends) finish_row<sl.row, false>(er, ei, Y);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -221,9 +221,8 @@ struct Products {
 };
 
 // ---- the input transform, four channels per thread, half of the rows per thread ---------------------
-// Activations are handled in the biased form u = x + 128 (one XOR on the raw bytes, so that unpacking
-// is a zero extension); a constant patch maps to zero at every entry of B^T d B except (1,1), where
-// the bias leaves 16 * 128 = 2048.  What lies outside the image arrived as zero bytes, i.e. x = 0
+// Half of the channels are handled in the biased form u = x + 128 (StoredInt8); a constant patch maps to zero at every
+// entry of B^T d B except (1,1), where the bias leaves 16 * 128 = 2048.  What lies outside the image arrived as zero bytes, i.e. x = 0
 // after the XOR as well.
 // The 1-D rule of B^T on a 6-vector (Section 3.4, the expansion of d' = B^T d):
 //   t0 = v0 - v4, t1 = v1+v2+v3+v4, t2 = -v1+v2-v3+v4, t3 = (v4-v2) + i (v3-v1), t5 = v5 - v1.
@@ -236,10 +235,10 @@ __device__ inline void transform_rows(const uint32_t (&u)[6][6], const Out& out,
     Quad v[6][6];
     static_for<6>([&](auto A) {
 #pragma unroll
-        for (int b = 0; b < 6; ++b) v[A][b] = unpack_u8x4(u[A][b] ^ kBiasBytes);
+        for (int b = 0; b < 6; ++b) v[A][b] = StoredInt8::lanes(u[A][b]);
         tick(A);
     });
-    const s16x2 bias11 = {2048, 2048};
+    const Quad bias11 = StoredInt8::bias11(SignedInt8{});
     auto row_rule = [](const Quad (&c)[6]) { return bt_rule(c[0], c[1], c[2], c[3], c[4], c[5]); };
     auto emit_real_row = [&](int ri, const Line& l) {
         out.real_entry(4 * ri + 0, l.t0);
@@ -261,7 +260,7 @@ __device__ inline void transform_rows(const uint32_t (&u)[6][6], const Out& out,
         emit_real_row(0, row_rule(r0));
         tick(std::integral_constant<int, 7>{});
         Line l1 = row_rule(r1);
-        l1.t1 = Quad{l1.t1.a - bias11, l1.t1.b - bias11};
+        l1.t1 = l1.t1 - bias11;
         emit_real_row(1, l1);
         tick(std::integral_constant<int, 8>{});
         emit_real_row(2, row_rule(r2));

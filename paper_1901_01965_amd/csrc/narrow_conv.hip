@@ -69,7 +69,7 @@ __global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restric
         load_patch<WG_NHWC, false>(x, p, my_n, my_ty, my_tx, 0, u);
         bias_patch(p, my_ty, my_tx, 0, u);
         Quad v[kNarrowValues];
-        transform_patch(u, ValueKeeper{v});
+        transform_patch<ChannelPairs>(u, ValueKeeper{v});
 #pragma unroll
         for (int i = 0; i < kNarrowPieces; ++i)
             values[i * kNarrowTiles + lane] =

@@ -97,6 +97,7 @@ constexpr int row_entry(int row, int pos) {
 }
 constexpr int half_rows(int half) { return half == 0 ? 3 : (half == 1 ? 2 : 5); }
 constexpr int half_row(int half, int i) { return half == 1 ? (i == 0 ? 3 : 4) : i; }
+constexpr bool fresh_row(int half, int row) { return row < 3 || half == 1; }   // see finish_row: no earlier row of this half
 constexpr int half_entries(int half) { return half == 0 ? 15 : (half == 1 ? 11 : 26); }
 struct Slot {
     int entry, row, pos;
@@ -282,7 +283,7 @@ struct ProductPhase {
                 }
                 er[sl.pos] = re;
                 ei[sl.pos] = im;
-                if constexpr (sl.last_in_row) finish_row<sl.row>(er, ei, Y);
+                if constexpr (sl.last_in_row) finish_row<sl.row, false>(er, ei, Y);
             }
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -291,7 +292,7 @@ struct ProductPhase {
 
 // Role-specialised kernels, scaled mode: the reverse-scaling factors (r, q) of the entries a
 // product wave owns, read once at the start of the kernel (while the wave would only wait for
-// the first operand planes) and parked in LDS as q << 8 | r, [slot][filter of the wave], so that
+// the first operand planes) and parked in LDS as rounding << 16 | q << 8 | r, [slot][filter of the wave], so that
 // the reverse scaling after the last channel block does not begin with a trip to L2.  Lane
 // group g = lane / 16 reads slots g, 4 + g, 8 + g, 12 + g of filter lane % 16: ask() issues the
 // four loads, park() writes what they brought, and a caller puts its first filter prefetch
@@ -319,7 +320,8 @@ struct ParkedScales {
         uint32_t* const base = reinterpret_cast<uint32_t*>(area) + (lane & 15);
         const int g = lane >> 4;
         static_for<kRounds>([&](auto J) {
-            if (4 * J + g < NE) base[(4 * J + g) * 16] = ((uint32_t)rq[J].y << 8) | (uint32_t)rq[J].x;   // r <= 255, q <= 7
+            if (4 * J + g < NE)    // r <= 255, q <= 7
+                base[(4 * J + g) * 16] = (((1u << rq[J].y) >> 1) << 16) | ((uint32_t)rq[J].y << 8) | (uint32_t)rq[J].x;
         });
         cx.parked = base;
     }
@@ -327,7 +329,7 @@ struct ParkedScales {
 template <int SLOT>
 __device__ inline ReverseScale parked_scale(const LaneContext& cx) {
     const uint32_t v = cx.parked[SLOT * 16];
-    return ReverseScale((int)(v & 0xffu), (int)(v >> 8));
+    return ReverseScale((int)(v & 0xffu), (int)(v >> 8) & 31, (int)(v >> 16));
 }
 
 // Scaled mode over several channel blocks: the products of every entry a wave owns accumulate
@@ -401,9 +403,8 @@ struct ScaledSums {
             er[sl.pos] = re;
             ei[sl.pos] = im;
             if constexpr (sl.last_in_row) {
-                finish_row<sl.row>(er, ei, Y);
-                // all rows in one wave: row by row, so that a row's sums are dead before the next row's work begins
-                if constexpr (HALF == kAllRows) __builtin_amdgcn_sched_barrier(0);
+                finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
+                __builtin_amdgcn_sched_barrier(0);   // row by row: a row's sums are dead before the next row's work begins
             }
         });
     }
@@ -627,7 +628,7 @@ struct LeanProducts {
     }
 
     // sums: the 18 channel sums of ScaledSums (SUMS), else unused; Y: the outputs (not SUMS)
-    __device__ inline void run(const LaneContext& cx, v4i (&sums)[kSums], v4i (&Y)[16]) {
+    __device__ inline void run(const LaneContext& cx, v4i* sums, v4i (&Y)[16]) {
         v4i er[6], ei[6];
         v4i afr2[AHEAD ? 2 : 1][4];
         if constexpr (AHEAD)
@@ -699,7 +700,8 @@ struct LeanProducts {
                 }
                 er[sl.pos] = re;
                 ei[sl.pos] = im;
-                if constexpr (sl.last_in_row) finish_row<sl.row>(er, ei, Y);
+                // scaled mode: one channel block, so these are the outputs' first values
+                if constexpr (sl.last_in_row) finish_row<sl.row, MODE == WG_SCALED && fresh_row(HALF, sl.row)>(er, ei, Y);
                 if constexpr (HALF == kAllRows) {
                     // Pins the entry's value, and a finished row's outputs, to this place.  Left alone, the compiler moves
                     // the vector work of all 26 entries behind the last matrix-core instruction (into the block that
@@ -738,7 +740,7 @@ struct LeanProducts {
 
     // SUMS, lossless mode, after the last channel block: the output transform of the channel sums
     // (it is linear, so it may as well run once on the sums as once per block).
-    __device__ inline static void finish_lossless(const v4i (&sums)[kSums], v4i (&Y)[16]) {
+    __device__ inline static void finish_lossless(const v4i* sums, v4i (&Y)[16]) {
         v4i er[6], ei[6];
         static_for<NE>([&](auto S) {
             constexpr Slot sl = half_slot(HALF, S);
@@ -747,10 +749,130 @@ struct LeanProducts {
             if constexpr (!is_real(sl.entry)) ei[sl.pos] = sums[v + 1];
             else                              ei[sl.pos] = (v4i){0, 0, 0, 0};
             if constexpr (sl.last_in_row) {
-                finish_row<sl.row>(er, ei, Y);
-                if constexpr (HALF == kAllRows) __builtin_amdgcn_sched_barrier(0);   // row by row (see ScaledSums::finish)
+                finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
+                __builtin_amdgcn_sched_barrier(0);   // row by row (see ScaledSums::finish)
             }
         });
+    }
+};
+
+// Lossless mode with 18 joined channel sums per half.
+template <int HALF, int RING>
+struct LosslessSums : LeanProducts<WG_LOSSLESS, HALF, true, RING> {
+    using Lean = LeanProducts<WG_LOSSLESS, HALF, true, RING>;
+    using Lean::kSums;
+    __device__ inline void enter(LaneContext& cx, int8_t*, int) { Lean::prefetch(cx); }
+    __device__ inline void run(const LaneContext& cx, v4i* sums) {
+        v4i unused[16];
+        Lean::run(cx, sums, unused);
+    }
+    __device__ inline static void finish(const LaneContext&, const v4i* sums, v4i (&Y)[16]) { Lean::finish_lossless(sums, Y); }
+};
+// One object for a wave of either half.  (The two empty statements differ, so that the compiler does not join the ends of
+// the branches: sums written through a choice of two addresses would live in memory.)
+template <int RING>
+struct EitherHalf {
+    static constexpr int kSums = kChannelSums;
+    int half;
+    LosslessSums<0, RING> first;
+    LosslessSums<1, RING> second;
+    template <class F0, class F1>
+    __device__ inline void choose(F0&& f0, F1&& f1) const {
+        if (half == 0) { f0(); asm volatile("; half 0" ::: "memory"); }
+        else           { f1(); asm volatile("; half 1" ::: "memory"); }
+    }
+    __device__ inline void prefetch(const LaneContext& cx) { choose([&]() { first.prefetch(cx); }, [&]() { second.prefetch(cx); }); }
+    __device__ inline void enter(LaneContext& cx, int8_t*, int) { prefetch(cx); }
+    __device__ inline void run(const LaneContext& cx, v4i* sums) { choose([&]() { first.run(cx, sums); }, [&]() { second.run(cx, sums); }); }
+    __device__ inline void finish(const LaneContext& cx, const v4i* sums, v4i (&Y)[16]) const {
+        choose([&]() { first.finish(cx, sums, Y); }, [&]() { second.finish(cx, sums, Y); });
+    }
+};
+
+// Scaled mode over several channel blocks in a product wave of the role-specialised kernels: what it leaves to the vector
+// ALU is what its SIMD has least of (the transform wave issues some 430 vector instructions per channel block there, each
+// 4 clocks, and a matrix-core instruction keeps the vector ALU from other waves for 8 of its 16).  The low activation limb
+// of every product accumulates over the channel blocks inside the matrix-core instructions; only the high limb starts from
+// zero in each block, and one shift-and-add per register brings it in.  Re = Dr Wr - Di Wi keeps its two terms apart until
+// finish().  Two vector instructions per real and three per complex value and register less than joining limbs per block
+// (42 / 50 -> 21 / 25 per accumulator register and half).
+template <int HALF, int RING, bool AHEAD = false>
+struct ChainedSums {
+    using Phase = ProductPhase<kScaledTwoPlanes, HALF>;
+    static constexpr int PM = kScaledTwoPlanes;
+    static constexpr int NE = Phase::NE, NB = Phase::NB;
+    static constexpr int sum_start(int slot) {   // a real entry: one chain; complex: Dr Wr, Di Wi, Im
+        int n = 0;
+        for (int s = 0; s < slot; ++s) n += is_real(half_slot(HALF, s).entry) ? 1 : 3;
+        return n;
+    }
+    static constexpr int kSums = sum_start(NE);
+    v4i ring[RING];
+
+    __device__ inline void prefetch(const LaneContext& cx) {
+        static_for<(NB < RING ? NB : RING)>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
+    }
+    // The first block's prefetch, between the request for the reverse-scaling factors and their parking in `area`.
+    __device__ inline void enter(LaneContext& cx, int8_t* area, int lane) {
+        ParkedScales<HALF> scales;
+        scales.ask(cx, lane);
+        prefetch(cx);
+        scales.park(cx, area, lane);
+    }
+    __device__ inline void run(const LaneContext& cx, v4i* sums) {
+        v4i afr2[AHEAD ? 2 : 1][4];
+        if constexpr (AHEAD)
+            static_for<num_a<PM>(half_slot(HALF, 0).entry)>([&](auto I) { afr2[0][I] = Phase::template load_a<0, I>(cx); });
+        static_for<NE>([&](auto S) {
+            constexpr int s = S;
+            constexpr int entry = half_slot(HALF, s).entry;
+            constexpr int b0 = b_start<PM>(HALF, s), v = sum_start(s);
+            v4i (&a)[4] = afr2[AHEAD ? (s & 1) : 0];
+            if constexpr (!AHEAD) {
+                static_for<num_a<PM>(entry)>([&](auto I) { a[I] = Phase::template load_a<s, I>(cx); });
+            } else if constexpr (s + 1 < NE) {
+                static_for<num_a<PM>(half_slot(HALF, s + 1).entry)>(
+                    [&](auto I) { afr2[(s + 1) & 1][I] = Phase::template load_a<s + 1, I>(cx); });
+            }
+            auto mul = [](v4i x, v4i w, v4i c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(x, w, c, 0, 0, 0); };
+            constexpr v4i zero = {0, 0, 0, 0};
+            if constexpr (is_real(entry)) {
+                const v4i w = ring[b0 % RING];
+                const v4i high = mul(a[0], w, zero);
+                sums[v] = mul(a[1], w, sums[v]);
+                sums[v] += high << kByteLimbShift;
+            } else {   // fragments: activations Re h, Re l, Im h, Im l; filters Re, Im
+                const v4i wr = ring[b0 % RING], wi = ring[(b0 + 1) % RING];
+                const v4i rr = mul(a[0], wr, zero), ii = mul(a[2], wi, zero);
+                v4i im = mul(a[0], wi, zero);
+                sums[v] = mul(a[1], wr, sums[v]);
+                sums[v + 1] = mul(a[3], wi, sums[v + 1]);
+                sums[v + 2] = mul(a[1], wi, sums[v + 2]);
+                im = mul(a[2], wr, im);
+                sums[v + 2] = mul(a[3], wr, sums[v + 2]);
+                sums[v] += rr << kByteLimbShift;
+                sums[v + 1] += ii << kByteLimbShift;
+                sums[v + 2] += im << kByteLimbShift;
+            }
+            static_for<num_b<PM>(entry)>([&](auto I) {
+                if constexpr (b0 + I + RING < NB) ring[(b0 + I) % RING] = Phase::template load_b<b0 + I + RING>(cx);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+    // After the last channel block: the sums in the form ScaledSums<HALF>::finish takes.
+    __device__ inline static void finish(const LaneContext& cx, const v4i* sums, v4i (&Y)[16]) {
+        v4i joined[ScaledSums<HALF>::kSums];
+        static_for<NE>([&](auto S) {
+            constexpr int v = sum_start(S), o = ScaledSums<HALF>::sum_start(S);
+            if constexpr (is_real(half_slot(HALF, S).entry)) {
+                joined[o] = sums[v];
+            } else {
+                joined[o] = sums[v] - sums[v + 1];
+                joined[o + 1] = sums[v + 2];
+            }
+        });
+        ScaledSums<HALF>::template finish<0, true>(cx, joined, Y);
     }
 };
 
@@ -771,13 +893,20 @@ struct ResidentScaled {
         for (int s = 0; s < slot; ++s) n += is_real(half_slot(HALF, s).entry) ? 2 : 4;
         return n;
     }
-    static constexpr int kAcc = acc_start(NE);
+    static constexpr int kSums = acc_start(NE);
     v4i ring[kRing];
 
     __device__ inline void prefetch(const LaneContext& cx) {
         static_for<(NB < kRing ? NB : kRing)>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
     }
-    __device__ inline void run(const LaneContext& cx, v4i (&acc)[kAcc]) {
+    // The first block's prefetch, between the request for the reverse-scaling factors and their parking in `area`.
+    __device__ inline void enter(LaneContext& cx, int8_t* area, int lane) {
+        ParkedScales<HALF> scales;
+        scales.ask(cx, lane);
+        prefetch(cx);
+        scales.park(cx, area, lane);
+    }
+    __device__ inline void run(const LaneContext& cx, v4i* sums) {
         static_for<NE>([&](auto S) {
             constexpr int s = S;
             constexpr int entry = half_slot(HALF, s).entry;
@@ -787,7 +916,7 @@ struct ResidentScaled {
             static_for<num_a<MODE>(entry)>([&](auto I) { afr[I] = Phase::template load_a<s, I>(cx); });
             static_for<num_ops<MODE>(entry)>([&](auto I) {
                 constexpr Op op = entry_op<MODE>(entry, I);
-                acc[v + op.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(afr[op.a], ring[(b0 + op.b) % kRing], acc[v + op.acc], 0, 0, 0);
+                sums[v + op.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(afr[op.a], ring[(b0 + op.b) % kRing], sums[v + op.acc], 0, 0, 0);
             });
             static_for<num_b<MODE>(entry)>([&](auto I) {
                 if constexpr (b0 + I + kRing < NB) ring[(b0 + I) % kRing] = Phase::template load_b<b0 + I + kRing>(cx);
@@ -795,13 +924,13 @@ struct ResidentScaled {
             __builtin_amdgcn_sched_barrier(0);
         });
     }
-    __device__ inline static void finish(const LaneContext& cx, const v4i (&acc)[kAcc], v4i (&Y)[16]) {
+    __device__ inline static void finish(const LaneContext& cx, const v4i* sums, v4i (&Y)[16]) {
         v4i er[6], ei[6];
         static_for<NE>([&](auto S) {
             constexpr Slot sl = half_slot(HALF, S);
             constexpr int v = acc_start(S);
-            v4i re = (acc[v] << kByteLimbShift) + acc[v + 1], im = {0, 0, 0, 0};
-            if constexpr (!is_real(sl.entry)) im = (acc[v + 2] << kByteLimbShift) + acc[v + 3];
+            v4i re = (sums[v] << kByteLimbShift) + sums[v + 1], im = {0, 0, 0, 0};
+            if constexpr (!is_real(sl.entry)) im = (sums[v + 2] << kByteLimbShift) + sums[v + 3];
             const ReverseScale unscale = parked_scale<S>(cx);   // Section 4.2
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -810,11 +939,11 @@ struct ResidentScaled {
             }
             er[sl.pos] = re;
             ei[sl.pos] = im;
-            if constexpr (sl.last_in_row) finish_row<sl.row>(er, ei, Y);
+            if constexpr (sl.last_in_row) finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
         });
     }
 };
-static_assert(ResidentScaled<0>::kAcc == 36 && ResidentScaled<1>::kAcc == 36, "both halves keep 36 accumulators");
+static_assert(ResidentScaled<0>::kSums == 36 && ResidentScaled<1>::kSums == 36, "both halves keep 36 accumulators");
 
 }  // namespace
 }  // namespace wg

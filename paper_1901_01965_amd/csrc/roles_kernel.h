@@ -67,38 +67,14 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
         OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
         int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
         uint32_t patch[6][6];
-        // 4-byte pixel loads through the buffer descriptor.  PW = 4: the 36 offsets of the patch are formed once and a
-        // channel block is a uniform offset on top of these; PW = 8: they are formed per load from 6 + 6 terms
-        // (registers are scarce).
-        uint32_t pixel[PW == 4 ? 36 : 1];
-        uint32_t row_off[PW == 8 ? 6 : 1], col_off[PW == 8 ? 6 : 1];
+        // 4-byte pixel loads through the buffer descriptor; the 36 offsets of the patch are formed once and a channel block
+        // is a uniform offset on top of these
+        uint32_t pixel[36];
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
         PatchBias<ENC> bias;
         bias.enter(p, a_ty, a_tx, enc);
-        auto request = [&](int cb) {
-            if constexpr (PW == 8) {
-                // channel groups beyond C (last block of a C that is not a multiple of 64: a uniform branch) get zeros
-                const bool have = (cb + 1) * kCBlock <= p.C || cb * kCBlock + 4 * a_cq < p.C;
-#pragma unroll
-                for (int i = 0; i < 36; ++i) {
-                    const uint32_t at = __builtin_elementwise_add_sat(row_off[i / 6], col_off[i % 6]);
-                    patch[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, have ? at : kOutsideOffset, cb * kCBlock, 0);
-                }
-            } else {
-                request_patch(xbuf, p, pixel, cb, 4 * a_cq, patch);
-            }
-        };
-        if constexpr (PW == 8) {
-            const int h0 = 4 * a_ty - 1, w0 = 4 * a_tx - 1;
-            const uint32_t image = (uint32_t)a_n * (uint32_t)p.H * (uint32_t)p.W * (uint32_t)p.C + (uint32_t)(4 * a_cq);
-#pragma unroll
-            for (int a = 0; a < 6; ++a) {
-                row_off[a] = (unsigned)(h0 + a) < (unsigned)p.H ? image + (uint32_t)(h0 + a) * (uint32_t)p.W * (uint32_t)p.C : kOutsideOffset;
-                col_off[a] = (unsigned)(w0 + a) < (unsigned)p.W ? (uint32_t)(w0 + a) * (uint32_t)p.C : kOutsideOffset;
-            }
-        } else {
-            patch_offsets(p, a_n, a_ty, a_tx, 4 * a_cq, pixel);
-        }
+        auto request = [&](int cb) { request_patch(xbuf, p, pixel, cb, 4 * a_cq, patch); };
+        patch_offsets(p, a_n, a_ty, a_tx, 4 * a_cq, pixel);
         if (a_t < p.T) request(0);
         WG_SPENT(3, mark);
         for (int cb = 0; cb < p.CB; ++cb) {
@@ -114,7 +90,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
                 WG_SPENT(1, mark);   // wait for the patch
 #endif
                 bias.apply(patch);
-                transform_patch(patch, out, enc);
+                transform_patch<typename PatchBias<ENC>::Bytes>(patch, out, enc);
                 WG_SPENT(2, mark);   // transform
                 if (cb + 1 < p.CB) request(cb + 1);
                 WG_SPENT(3, mark);   // requests
@@ -139,94 +115,43 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
     LaneContext cx;
     cx.table_k = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
     cx.parked = nullptr;
-    constexpr bool PARKED = MODE == WG_SCALED;
     int8_t* const scale_area = lds + 2 * kLdsBytes + pw * kParkedScaleBytes;   // behind the two plane buffers: 1 KB per product wave
     constexpr int NP = MODE == WG_LOSSLESS ? 138 : 46;
     const int8_t* b_lane = reinterpret_cast<const int8_t*>(blob + planes_off) +
                            filter_plane_offset(0, 0, k, (lane >> 4) * 16, p.Kp, NP);
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
     v4i Y[16];
+    // The product waves do no output transform per block.  Scaled: all 36 limb-product accumulators of a half stay
+    // resident (PW = 4), or the low limbs' chains do (PW = 8: 168 registers per wave); lossless: 18 joined channel sums.
+    // One loop per half (the same barriers in both), so that each is allocated registers on its own.
+    auto blocks = [&](auto H) {
+        using Phase = std::conditional_t<MODE == WG_LOSSLESS, LosslessSums<H, PW == 8 ? 6 : 8>,
+                                         std::conditional_t<PW == 4, ResidentScaled<H>, ChainedSums<H, H == 0 ? 8 : 6>>>;
+        Phase phase;
+        v4i sums[Phase::kSums];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) Y[i] = (v4i){0, 0, 0, 0};
-    // The product waves do no output transform per block.  Scaled: all 36 limb-product
-    // accumulators stay resident (PW = 4), or 18 joined channel sums (PW = 8: 168 registers per wave); lossless: 18
-    // joined channel sums (54 accumulators would not fit).
-    constexpr bool RESIDENT = MODE == WG_SCALED && PW == 4;
-    constexpr int kLeanRing = PW == 8 ? (MODE == WG_SCALED ? 10 : 6) : 8;
-    std::conditional_t<RESIDENT, ResidentScaled<0>, LeanProducts<MODE, 0, true, kLeanRing>> phase0;
-    std::conditional_t<RESIDENT, ResidentScaled<1>, LeanProducts<MODE, 1, true, kLeanRing>> phase1;
-    constexpr int kSumRegs = RESIDENT ? 36 : kChannelSums;
-    v4i sums[kSumRegs];
-#pragma unroll
-    for (int i = 0; i < kSumRegs; ++i) sums[i] = (v4i){0, 0, 0, 0};
-    if constexpr (PW == 8) {
-        // one loop per half (the same barriers in both), so that each is allocated registers on its own
-        auto blocks = [&](auto& phase, auto H) {
-            // the first block's filter prefetch goes out between the request for the reverse-scaling factors and their parking
-            ParkedScales<H> scales;
-            if constexpr (PARKED) scales.ask(cx, lane);
-            cx.b_glob = b_lane;
-            phase.prefetch(cx);
-            if constexpr (PARKED) scales.park(cx, scale_area, lane);
-            for (int cb = 0; cb < p.CB; ++cb) {
-                if (cb > 0) {
-                    cx.b_glob = b_lane + cb * b_block_stride;
-                    phase.prefetch(cx);
-                }
-                WG_SPENT(3, mark);   // ring prefetch issue
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();   // barrier cb + 1
-                WG_SPENT(0, mark);   // barrier
-                cx.a_lds = lds + (cb & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
-                phase.run(cx, sums, Y);
-                WG_SPENT(2, mark);   // products
-            }
-        };
-        if (half == 0) blocks(phase0, std::integral_constant<int, 0>{}); else blocks(phase1, std::integral_constant<int, 1>{});
-    } else {
+        for (int i = 0; i < Phase::kSums; ++i) sums[i] = (v4i){0, 0, 0, 0};
         cx.b_glob = b_lane;
-        if (half == 0) {
-            ParkedScales<0> scales;
-            if constexpr (PARKED) scales.ask(cx, lane);
-            phase0.prefetch(cx);
-            if constexpr (PARKED) scales.park(cx, scale_area, lane);
-        } else {
-            ParkedScales<1> scales;
-            if constexpr (PARKED) scales.ask(cx, lane);
-            phase1.prefetch(cx);
-            if constexpr (PARKED) scales.park(cx, scale_area, lane);
-        }
+        phase.enter(cx, scale_area, lane);
         for (int cb = 0; cb < p.CB; ++cb) {
             if (cb > 0) {
                 cx.b_glob = b_lane + cb * b_block_stride;
-                if (half == 0) phase0.prefetch(cx); else phase1.prefetch(cx);
+                phase.prefetch(cx);
             }
-            WG_SPENT(3, mark);
+            WG_SPENT(3, mark);   // ring prefetch issue
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();   // barrier cb + 1
-            WG_SPENT(0, mark);
+            WG_SPENT(0, mark);   // barrier
             cx.a_lds = lds + (cb & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
-            if constexpr (RESIDENT) {
-                if (half == 0) phase0.run(cx, sums); else phase1.run(cx, sums);
-            } else {
-                if (half == 0) phase0.run(cx, sums, Y); else phase1.run(cx, sums, Y);
-            }
-            WG_SPENT(2, mark);
+            phase.run(cx, sums);
+            WG_SPENT(2, mark);   // products
         }
-    }
 #ifdef WG_TIMESTAMPS
-    report();
+        report();
 #endif
-    if constexpr (RESIDENT) {
-        if (half == 0) ResidentScaled<0>::finish(cx, sums, Y);
-        else           ResidentScaled<1>::finish(cx, sums, Y);
-    } else if constexpr (MODE == WG_SCALED) {
-        if (half == 0) ScaledSums<0>::template finish<0, true>(cx, sums, Y);
-        else           ScaledSums<1>::template finish<0, true>(cx, sums, Y);
-    } else {
-        if (half == 0) LeanProducts<MODE, 0, true>::finish_lossless(sums, Y);
-        else           LeanProducts<MODE, 1, true>::finish_lossless(sums, Y);
-    }
+        Phase::finish(cx, sums, Y);
+    };
+    if (half == 0) blocks(std::integral_constant<int, 0>{}); else blocks(std::integral_constant<int, 1>{});
     // PW = 8: the two 32-filter halves of the workgroup stage in one operand buffer each and store side by side
     StoreContext sc;
     sc.lds = lds + group * kLdsBytes;

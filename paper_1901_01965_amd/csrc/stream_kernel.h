@@ -136,7 +136,7 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
                     WG_SPENT(2, mark);   // wait for the patch
 #endif
                     bias.apply(patch);
-                    transform_patch(patch, out, enc);
+                    transform_patch<typename PatchBias<ENC>::Bytes>(patch, out, enc);
                 }
             }
             WG_SPENT(3, mark);   // transform
@@ -226,65 +226,56 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
 #endif
         return;
     }
-    // 18 joined channel sums per wave in both modes (36 resident accumulators plus the outputs
-    // would not fit the 256 registers here)
-    // scaled mode has the registers for a second set of activation fragments (lossless mode would spill)
-    LeanProducts<MODE, 0, true, 8, MODE == WG_SCALED> phase0;
-    LeanProducts<MODE, 1, true, 8, MODE == WG_SCALED> phase1;
-    constexpr int kSumRegs = kChannelSums;
-    v4i sums[kSumRegs];
-    v4i Y[16];
-    int cb = 0;
-    if (units > 0) {
-        // the first unit's filter prefetch goes out between the request for the reverse-scaling factors and their parking
-        cx.b_glob = b_lane;
-        if (half == 0) {
-            ParkedScales<0> scales;
-            if constexpr (MODE == WG_SCALED) scales.ask(cx, lane);
-            phase0.prefetch(cx);
-            if constexpr (MODE == WG_SCALED) scales.park(cx, scale_area, lane);
-        } else {
-            ParkedScales<1> scales;
-            if constexpr (MODE == WG_SCALED) scales.ask(cx, lane);
-            phase1.prefetch(cx);
-            if constexpr (MODE == WG_SCALED) scales.park(cx, scale_area, lane);
+    // Channel sums per wave (all 36 accumulators next to the outputs would not fit the 256 registers here).  Scaled mode: a
+    // loop per half, whose sums differ in number; lossless mode: one loop for both halves (a loop each would spill).
+    auto stream = [&](auto& phase) {
+        v4i sums[std::remove_reference_t<decltype(phase)>::kSums];
+        int cb = 0;
+        if (units > 0) {
+            cx.b_glob = b_lane;
+            phase.enter(cx, scale_area, lane);
         }
-    }
-    for (int u = 0; u < units; ++u) {
-        if (cb == 0) {
+        for (int u = 0; u < units; ++u) {
+            if (cb == 0) {
 #pragma unroll
-            for (int i = 0; i < kSumRegs; ++i) sums[i] = (v4i){0, 0, 0, 0};
-        }
-        WG_SPENT(5, mark);   // clearing the sums
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();   // U_{u+1}
-        WG_SPENT(0, mark);   // barrier U
-        cx.a_lds = lds + (u & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
-        if (half == 0) phase0.run(cx, sums, Y); else phase1.run(cx, sums, Y);
-        WG_SPENT(1, mark);   // products
-        const bool last = cb == p.CB - 1;
-        cb = last ? 0 : cb + 1;
-        if (u + 1 < units) {   // the next unit's first filter fragments travel while this one is finished and staged
-            cx.b_glob = b_lane + cb * b_block_stride;
-            if (half == 0) phase0.prefetch(cx); else phase1.prefetch(cx);
-        }
-        if (last) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) Y[i] = (v4i){0, 0, 0, 0};
-            if constexpr (MODE == WG_SCALED) {
-                if (half == 0) ScaledSums<0>::template finish<0, true>(cx, sums, Y);
-                else           ScaledSums<1>::template finish<0, true>(cx, sums, Y);
-            } else {
-                if (half == 0) LeanProducts<MODE, 0, true>::finish_lossless(sums, Y);
-                else           LeanProducts<MODE, 1, true>::finish_lossless(sums, Y);
+                for (int i = 0; i < (int)(sizeof(sums) / sizeof(v4i)); ++i) sums[i] = (v4i){0, 0, 0, 0};
             }
-            WG_SPENT(2, mark);   // finish
-            __syncthreads();   // D_u: every product wave has finished reading this unit's planes
-            WG_SPENT(3, mark);   // barrier D
-            stage_outputs(lds + (u & 1) * kLdsBytes, lane, half, kblock, Y);
-            __syncthreads();   // S_u: staged
-            WG_SPENT(4, mark);   // staging and barrier S
+            WG_SPENT(5, mark);   // clearing the sums
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();   // U_{u+1}
+            WG_SPENT(0, mark);   // barrier U
+            cx.a_lds = lds + (u & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
+            phase.run(cx, sums);
+            WG_SPENT(1, mark);   // products
+            const bool last = cb == p.CB - 1;
+            cb = last ? 0 : cb + 1;
+            if (u + 1 < units) {   // the next unit's first filter fragments travel while this one is finished and staged
+                cx.b_glob = b_lane + cb * b_block_stride;
+                phase.prefetch(cx);
+            }
+            if (last) {
+                v4i Y[16];
+                phase.finish(cx, sums, Y);
+                WG_SPENT(2, mark);   // finish
+                __syncthreads();   // D_u: every product wave has finished reading this unit's planes
+                WG_SPENT(3, mark);   // barrier D
+                stage_outputs(lds + (u & 1) * kLdsBytes, lane, half, kblock, Y);
+                __syncthreads();   // S_u: staged
+                WG_SPENT(4, mark);   // staging and barrier S
+            }
         }
+    };
+    if constexpr (MODE == WG_SCALED) {
+        if (half == 0) {
+            ChainedSums<0, 6, true> phase;
+            stream(phase);
+        } else {
+            ChainedSums<1, 6, true> phase;
+            stream(phase);
+        }
+    } else {
+        EitherHalf<8> phase{half};
+        stream(phase);
     }
 #ifdef WG_TIMESTAMPS
     report();

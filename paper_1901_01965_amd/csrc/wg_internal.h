@@ -120,6 +120,7 @@ __host__ __device__ inline size_t filter_plane_offset(int plane, int cb, int k, 
 struct ReverseScale {
     int r, q, rnd;
     __device__ inline explicit ReverseScale(const ScaleEntry& se) : ReverseScale(se.r, se.q) {}
+    __device__ inline ReverseScale(int r_, int q_, int rnd_) : r(r_), q(q_), rnd(rnd_) {}
     __device__ inline ReverseScale(int r_, int q_) : r(r_), q(q_), rnd(q_ > 0 ? 1 << (q_ - 1) : 0) {}
     __device__ inline int operator()(int m) const {
         const long long t = (long long)m * r + rnd;
