@@ -22,7 +22,8 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
     if (t < p.T) decode_tile(p, t, n, ty, tx);
     uint32_t pixel[36], patch[6][6];
     patch_offsets(p, n, ty, tx, 4 * cq, pixel);
-    request_patch(activation_buffer(x, p), p, pixel, cb, 4 * cq, patch);
+    drop_absent_channels(p, cb, 4 * cq, pixel);
+    request_patch(activation_buffer(x, p), pixel, cb, patch);
     for (int i = tid; i < 4 * kEntries; i += blockDim.x) maxima[i] = 0;
     __syncthreads();
     s16x2 mx[kEntries];
@@ -167,24 +168,11 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
         const int tid = threadIdx.x, a_tile = tid >> 4, a_cq = tid & 15, a_t = tile0 + a_tile;
         int n = 0, ty = 0, tx = 0;
         if (a_t < p.T) decode_tile(p, a_t, n, ty, tx);
-        uint32_t patch[6][6], row_off[6], col_off[6];
+        uint32_t patch[6][6], pixel[36];
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
-        const uint32_t image = (uint32_t)n * (uint32_t)p.H * (uint32_t)p.W * (uint32_t)p.C + (uint32_t)(4 * a_cq);
-#pragma unroll
-        for (int a = 0; a < 6; ++a) {
-            const int h = 4 * ty - 1 + a, w = 4 * tx - 1 + a;
-            row_off[a] = (unsigned)h < (unsigned)p.H ? image + (uint32_t)h * (uint32_t)p.W * (uint32_t)p.C : kOutsideOffset;
-            col_off[a] = (unsigned)w < (unsigned)p.W ? (uint32_t)w * (uint32_t)p.C : kOutsideOffset;
-        }
-        auto request = [&](int cb) {
-            const bool have = (cb + 1) * kCBlock <= p.C || cb * kCBlock + 4 * a_cq < p.C;
-#pragma unroll
-            for (int i = 0; i < 36; ++i) {
-                const uint32_t at = __builtin_elementwise_add_sat(row_off[i / 6], col_off[i % 6]);
-                patch[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, have ? at : kOutsideOffset, cb * kCBlock, 0);
-            }
-        };
-        request(0);
+        patch_offsets(p, n, ty, tx, 4 * a_cq, pixel);
+        drop_absent_channels(p, 0, 4 * a_cq, pixel);
+        request_patch(xbuf, pixel, 0, patch);
         ScaledPlanes out;
         int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
         out.np = np_tab + a_tile * kEntries;
@@ -195,8 +183,12 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
                 __builtin_amdgcn_s_barrier();
             }
             out.sink.base = slot + (cb & 1) * kActPlaneBuffer;
-            transform_patch<StoredInt8>(patch, out);
-            if (cb + 1 < p.CB) request(cb + 1);
+            if (cb + 1 < p.CB) {
+                drop_absent_channels(p, cb + 1, 4 * a_cq, pixel);
+                transform_patch<StoredInt8>(patch, out, SignedInt8{}, NextColumns{xbuf, pixel, cb + 1, patch});
+            } else {
+                transform_patch<StoredInt8>(patch, out);
+            }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();   // barrier CB: the last block's planes are published

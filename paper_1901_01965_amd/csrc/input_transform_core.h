@@ -221,14 +221,21 @@ struct ChannelPairs : BiasedBytes {
 
 // Transforms one loaded patch (four channels) and hands every free entry to `out`
 // (real_entry(p, v), complex_entry(j, re, im)): an OperandSplitter emits the operand planes.
-template <class Bytes = BiasedBytes, class Out, class ENC = SignedInt8>
-__device__ inline void transform_patch(const uint32_t u[6][6], const Out& out, const ENC enc = ENC{}) {
+// done_with(b) is called when column b of the patch has been read: a caller whose next patch goes into the same registers
+// asks for that column there.
+struct NothingToDo {
+    __device__ inline void operator()(int) const {}
+};
+template <class Bytes = BiasedBytes, class Out, class ENC = SignedInt8, class Done = NothingToDo>
+__device__ inline void transform_patch(const uint32_t u[6][6], const Out& out, const ENC enc = ENC{}, const Done& done_with = Done{}) {
     // column pass: d'[.][b] = B^T applied down each of the six tile columns
     Line col[6];
 #pragma unroll
-    for (int b = 0; b < 6; ++b)
+    for (int b = 0; b < 6; ++b) {
         col[b] = bt_rule(Bytes::lanes(u[0][b]), Bytes::lanes(u[1][b]), Bytes::lanes(u[2][b]), Bytes::lanes(u[3][b]),
                          Bytes::lanes(u[4][b]), Bytes::lanes(u[5][b]));
+        done_with(b);
+    }
     const Quad bias11 = Bytes::bias11(enc);   // what the bias leaves at entry (1,1): 16 * 128 for signed int8
     // row pass on the real rows 0,1,2,5 of d': entries (r, {0,1,2,5}) real, (r,3) complex
 #define WG_REAL_ROW(ri, field)                                                                      \

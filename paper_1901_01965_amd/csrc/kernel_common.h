@@ -75,22 +75,40 @@ __device__ inline void patch_offsets(const Problem& p, int n, int ty, int tx, in
 #pragma unroll
         for (int b = 0; b < 6; ++b) pixel[6 * a + b] = __builtin_elementwise_add_sat(row_off[a], col_off[b]);
 }
-// One channel block of the patch: 36 loads, nothing waits for them here.  pixel[] holds the
+// Column b of one channel block of the patch: six loads, nothing waits for them here.  pixel[] holds the
 // offsets of the lane's channel group in channel block 0; the block is a uniform offset on top.
-// Only the last channel block of a C that is not a multiple of 64 has channel groups beyond C:
-// there (a uniform branch) such a lane asks for the outside offset, so that it gets zeros and
-// never touches memory next to the tensor.
-__device__ inline void request_patch(__amdgpu_buffer_rsrc_t xbuf, const Problem& p, const uint32_t pixel[36], int cb,
-                                     int c_lane, uint32_t patch[6][6]) {
+__device__ inline void request_column(__amdgpu_buffer_rsrc_t xbuf, const uint32_t pixel[36], int cb, int b, uint32_t patch[6][6]) {
+#pragma unroll
+    for (int a = 0; a < 6; ++a)
+        patch[a][b] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, pixel[6 * a + b], cb * kCBlock, 0);
+}
+__device__ inline void request_patch(__amdgpu_buffer_rsrc_t xbuf, const uint32_t pixel[36], int cb, uint32_t patch[6][6]) {
+#pragma unroll
+    for (int b = 0; b < 6; ++b) request_column(xbuf, pixel, cb, b, patch);
+}
+// transform_patch's done_with: column b of the block after the one being transformed is asked for as its registers become
+// free.  A compute unit's memory path is full of filter fragments (a load instruction waits some 100 clocks to enter it), so
+// 36 loads in a row held the transform waves up longer than their arithmetic takes; spread over the column pass they enter
+// beside it.  The barriers keep the compiler from collecting them in one place again.
+struct NextColumns {
+    __amdgpu_buffer_rsrc_t xbuf;
+    const uint32_t* pixel;
+    int cb;
+    uint32_t (*patch)[6];
+    __device__ inline void operator()(int b) const {
+        __builtin_amdgcn_sched_barrier(0);
+        request_column(xbuf, pixel, cb, b, patch);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+};
+// To be called before block cb is asked for.  Only the last channel block of a C that is not a multiple of 64 has channel
+// groups beyond C (a uniform branch): there such a lane asks for the outside offset, so that it gets zeros and never touches
+// memory next to the tensor.  No block follows that one, so the table itself can change.
+__device__ inline void drop_absent_channels(const Problem& p, int cb, int c_lane, uint32_t pixel[36]) {
     if ((cb + 1) * kCBlock > p.C) {
         const bool have = cb * kCBlock + c_lane < p.C;
 #pragma unroll
-        for (int i = 0; i < 36; ++i)
-            patch[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, have ? pixel[i] : kOutsideOffset, cb * kCBlock, 0);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 36; ++i)
-            patch[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, pixel[i], cb * kCBlock, 0);
+        for (int i = 0; i < 36; ++i) pixel[i] = have ? pixel[i] : kOutsideOffset;
     }
 }
 // What remains to be done to a patch loaded that way before transform_patch<Bytes>.  Pixels outside the image arrived as

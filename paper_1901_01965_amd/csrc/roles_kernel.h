@@ -62,7 +62,6 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
 
     if (transforms) {
         const int a_tile = tid >> 4, a_cq = tid & 15;
-        const int a_t = tile0 + a_tile;
         const int a_tx = __shfl(my_tx, a_tile), a_ty = __shfl(my_ty, a_tile), a_n = __shfl(my_n, a_tile);
         OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
         int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
@@ -73,9 +72,9 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
         PatchBias<ENC> bias;
         bias.enter(p, a_ty, a_tx, enc);
-        auto request = [&](int cb) { request_patch(xbuf, p, pixel, cb, 4 * a_cq, patch); };
         patch_offsets(p, a_n, a_ty, a_tx, 4 * a_cq, pixel);
-        if (a_t < p.T) request(0);
+        drop_absent_channels(p, 0, 4 * a_cq, pixel);
+        request_patch(xbuf, pixel, 0, patch);
         WG_SPENT(3, mark);
         for (int cb = 0; cb < p.CB; ++cb) {
             if (cb > 0) {   // barrier cb
@@ -84,17 +83,18 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
             }
             WG_SPENT(0, mark);   // LDS writes landed + barrier
             out.sink.base = slot + (cb & 1) * kLdsBytes;
-            if (a_t < p.T) {
 #ifdef WG_TIMESTAMPS
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                WG_SPENT(1, mark);   // wait for the patch
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            WG_SPENT(1, mark);   // wait for the patch
 #endif
-                bias.apply(patch);
+            bias.apply(patch);
+            if (cb + 1 < p.CB) {
+                drop_absent_channels(p, cb + 1, 4 * a_cq, pixel);
+                transform_patch<typename PatchBias<ENC>::Bytes>(patch, out, enc, NextColumns{xbuf, pixel, cb + 1, patch});
+            } else {
                 transform_patch<typename PatchBias<ENC>::Bytes>(patch, out, enc);
-                WG_SPENT(2, mark);   // transform
-                if (cb + 1 < p.CB) request(cb + 1);
-                WG_SPENT(3, mark);   // requests
             }
+            WG_SPENT(2, mark);   // transform and requests
         }
 #ifdef WG_TIMESTAMPS
         report();

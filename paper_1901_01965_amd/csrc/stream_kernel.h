@@ -78,19 +78,16 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
         OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
         int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
         uint32_t patch[6][6], pixel[36];
-        int a_t = 0, a_ty = 0, a_tx = 0;
-        PatchBias<ENC> bias;
-        // identity of the thread's tile in tile block tb, and the 36 pixel offsets of its patch
+        PatchBias<ENC> bias, next_bias;   // of the patch being transformed, of the one in flight
+        // the 36 pixel offsets of the patch of the thread's tile in tile block tb (none: of some tile, whose outputs nobody stores)
         auto enter_tile_block = [&](int tb) {
-            a_t = tb * kFusedTiles + a_tile;
-            int a_n = 0;
-            a_ty = 0; a_tx = 0;
-            if (a_t < p.T) decode_tile(p, a_t, a_n, a_ty, a_tx);
-            patch_offsets(p, a_n, a_ty, a_tx, 4 * a_cq, pixel);
-            bias.enter(p, a_ty, a_tx, enc);
+            const int t = tb * kFusedTiles + a_tile;
+            int n = 0, ty = 0, tx = 0;
+            if (t < p.T) decode_tile(p, t, n, ty, tx);
+            patch_offsets(p, n, ty, tx, 4 * a_cq, pixel);
+            next_bias.enter(p, ty, tx, enc);
         };
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
-        auto request = [&](int cb) { request_patch(xbuf, p, pixel, cb, 4 * a_cq, patch); };
         // adds the two halves staged in `buffer` for tile block tb and writes them out
         auto flush = [&](int tb, int buffer) {
             StoreContext sc;
@@ -109,7 +106,8 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
         int cb = 0, jb = 0;   // unit u = (tile block number jb of this workgroup, channel block cb)
         if (units > 0) {
             enter_tile_block(blockIdx.x);
-            request(0);
+            drop_absent_channels(p, 0, 4 * a_cq, pixel);
+            request_patch(xbuf, pixel, 0, patch);
         }
         // was unit v the last channel block of its tile block?  v % CB == CB - 1, tracked without division:
         // last1 = for unit u - 1, last2 = for unit u - 2; tb1 / tb2 = their tile blocks
@@ -128,27 +126,27 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
             }
             WG_SPENT(1, mark);   // flush
             const int tb = (int)blockIdx.x + jb * (int)gridDim.x;
+            const bool last0 = u < units && cb == p.CB - 1;
             if (u < units) {
                 out.sink.base = slot + (u & 1) * kLdsBytes;
-                if (a_t < p.T) {
 #ifdef WG_TIMESTAMPS
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                    WG_SPENT(2, mark);   // wait for the patch
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                WG_SPENT(2, mark);   // wait for the patch
 #endif
-                    bias.apply(patch);
-                    transform_patch<typename PatchBias<ENC>::Bytes>(patch, out, enc);
+                // the next unit's patch is asked for as the registers of this one become free
+                const bool more = u + 1 < units;
+                if (++cb == p.CB) { cb = 0; ++jb; }
+                bias = next_bias;
+                if (more) {
+                    if (cb == 0) enter_tile_block((int)blockIdx.x + jb * (int)gridDim.x);
+                    drop_absent_channels(p, cb, 4 * a_cq, pixel);
                 }
+                bias.apply(patch);
+                WG_SPENT(5, mark);   // offsets
+                if (more) transform_patch<typename PatchBias<ENC>::Bytes>(patch, out, enc, NextColumns{xbuf, pixel, cb, patch});
+                else      transform_patch<typename PatchBias<ENC>::Bytes>(patch, out, enc);
             }
             WG_SPENT(3, mark);   // transform
-            const bool last0 = u < units && cb == p.CB - 1;
-            if (u < units) {   // next unit's patch, asked for before the waits below so that they cover its latency
-                if (++cb == p.CB) { cb = 0; ++jb; }
-                if (u + 1 < units) {
-                    if (cb == 0) enter_tile_block((int)blockIdx.x + jb * (int)gridDim.x);
-                    if (a_t < p.T) request(cb);
-                }
-            }
-            WG_SPENT(5, mark);   // requests
             if (last1) {   // D_{u-1}, S_{u-1}
                 __syncthreads();
                 __syncthreads();
