@@ -12,34 +12,37 @@ namespace {
 // ---- factors ---------------------------------------------------------------------------------------------
 // grid: ceil(T / 4), 64 CB threads: wave = 64-channel block, lane = (tile, four channels).  Bound by the latency of one patch
 // load and one transform.
+template <bool PIECES>
 __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                            uint32_t* __restrict__ factors, int32_t* __restrict__ act_table, Problem p) {
     __shared__ int maxima[4 * kEntries];
     const int tid = threadIdx.x, lane = tid & 63, cb = tid >> 6;
     const BlobHeaderWords header = read_blob_header(blob);
-    const int t = blockIdx.x * 4 + (lane >> 4), cq = lane & 15;
+    using Loader = PatchLoader<PIECES>;
+    const int tile = Loader::tile_of(0, lane), t = blockIdx.x * 4 + tile, cq = Loader::quad_of(lane);
     int n = 0, ty = 0, tx = 0;
     if (t < p.T) decode_tile(p, t, n, ty, tx);
-    uint32_t pixel[36], patch[6][6];
-    patch_offsets(p, n, ty, tx, 4 * cq, pixel);
-    drop_absent_channels(p, cb, 4 * cq, pixel);
-    request_patch(activation_buffer(x, p), pixel, cb, patch);
+    Loader loader;
+    loader.enter(p, n, ty, tx, lane);
+    loader.drop_absent_channels(p, cb, lane);
+    loader.request(activation_buffer(x, p), cb);
     for (int i = tid; i < 4 * kEntries; i += blockDim.x) maxima[i] = 0;
     __syncthreads();
     s16x2 mx[kEntries];
 #pragma unroll
     for (int e = 0; e < kEntries; ++e) mx[e] = (s16x2){0, 0};
-    transform_patch<StoredInt8>(patch, MaxKeeper{mx});
+    loader.take();
+    transform_patch<StoredInt8>(loader, MaxKeeper{mx});
     // over the sixteen threads of a tile, two entries per register; then one LDS maximum per tile, entry and wave
 #pragma unroll
     for (int j = 0; j < kEntries / 2; ++j) {
         s16x2 m = {max(mx[2 * j].x, mx[2 * j].y), max(mx[2 * j + 1].x, mx[2 * j + 1].y)};
 #pragma unroll
-        for (int off = 1; off < 16; off <<= 1)
+        for (int off : {1, 2, 16, 32})   // the lanes of a tile (PatchLoader)
             m = __builtin_elementwise_max(m, as_s16x2((uint32_t)__shfl_xor((int)as_u32(m), off)));
         if (cq == j) {
-            atomicMax(&maxima[(lane >> 4) * kEntries + 2 * j], (int)m.x);
-            atomicMax(&maxima[(lane >> 4) * kEntries + 2 * j + 1], (int)m.y);
+            atomicMax(&maxima[tile * kEntries + 2 * j], (int)m.x);
+            atomicMax(&maxima[tile * kEntries + 2 * j + 1], (int)m.y);
         }
     }
     __syncthreads();
@@ -132,7 +135,7 @@ static_assert(2 * kActPlaneBuffer <= kLdsBytes && act_lds_bytes<8>() <= 160 * 10
 
 // grid (ceil(T/16), Kp/(8 PW)), 64 (4 + PW) threads: the roles of fused_conv_roles_kernel (roles_kernel.h): waves 0-3 transform one
 // channel block ahead, the others multiply; product wave pw owns filter block pw % (PW / 2) and half pw / (PW / 2) of the entries.
-template <int LAYOUT, int PW>
+template <int LAYOUT, int PW, bool PIECES>
 __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                                          size_t table_off, size_t planes_off, int32_t* __restrict__ y,
                                                                          const uint32_t* __restrict__ factors, Problem p) {
@@ -165,14 +168,15 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
     };
 
     if (wave < 4) {
-        const int tid = threadIdx.x, a_tile = tid >> 4, a_cq = tid & 15, a_t = tile0 + a_tile;
+        using Loader = PatchLoader<PIECES>;
+        const int a_tile = Loader::tile_of(wave, lane), a_cq = Loader::quad_of(lane), a_t = tile0 + a_tile;
         int n = 0, ty = 0, tx = 0;
         if (a_t < p.T) decode_tile(p, a_t, n, ty, tx);
-        uint32_t patch[6][6], pixel[36];
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
-        patch_offsets(p, n, ty, tx, 4 * a_cq, pixel);
-        drop_absent_channels(p, 0, 4 * a_cq, pixel);
-        request_patch(xbuf, pixel, 0, patch);
+        Loader loader;
+        loader.enter(p, n, ty, tx, lane);
+        loader.drop_absent_channels(p, 0, lane);
+        loader.request(xbuf, 0);
         ScaledPlanes out;
         int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
         out.np = np_tab + a_tile * kEntries;
@@ -183,11 +187,12 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
                 __builtin_amdgcn_s_barrier();
             }
             out.sink.base = slot + (cb & 1) * kActPlaneBuffer;
+            loader.take();
             if (cb + 1 < p.CB) {
-                drop_absent_channels(p, cb + 1, 4 * a_cq, pixel);
-                transform_patch<StoredInt8>(patch, out, SignedInt8{}, NextColumns{xbuf, pixel, cb + 1, patch});
+                loader.drop_absent_channels(p, cb + 1, lane);
+                transform_patch<StoredInt8>(loader, out, SignedInt8{}, NextColumns<Loader>{loader, xbuf, cb + 1});
             } else {
-                transform_patch<StoredInt8>(patch, out);
+                transform_patch<StoredInt8>(loader, out);
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -204,7 +209,8 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
     cx.table_k = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
     int8_t* const scale_area = lds + act_rq_off<PW>() + kActRqBytes + pw * kParkedScaleBytes;
     constexpr int NP = 46;
-    const int8_t* b_lane = reinterpret_cast<const int8_t*>(blob + planes_off) + filter_plane_offset(0, 0, k, (lane >> 4) * 16, p.Kp, NP);
+    const int8_t* const b_wave = filter_fragments(blob + planes_off, k - (lane & 15), p.Kp, NP);
+    cx.b_lane = fragment_lane(lane);
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
     v4i Y[16];
     // one loop per half (the same barriers in both), so that each is allocated registers on its own
@@ -212,14 +218,14 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
         ActProducts<H, 8> products;
         ParkedScales<H> scales;
         scales.ask(cx, lane);
-        cx.b_glob = b_lane;
+        cx.b_glob = b_wave;
         products.prefetch(cx);
         scales.park(cx, scale_area, lane);
         products.clear();
         expand_factors();
         for (int cb = 0; cb < p.CB; ++cb) {
             if (cb > 0) {
-                cx.b_glob = b_lane + cb * b_block_stride;
+                cx.b_glob = b_wave + cb * b_block_stride;
                 products.prefetch(cx);
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -246,26 +252,29 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
 }  // namespace
 
 hipError_t launch_act_factors(const RolesCall& c, uint32_t* factors, int32_t* act_table, hipStream_t s) {
-    act_factors_kernel<<<ceil_div(c.p.T, 4), 64 * c.p.CB, 0, s>>>(c.x, c.blob, factors, act_table, c.p);
+    const auto kernel = comes_in_pieces(c.x, c.p) ? act_factors_kernel<true> : act_factors_kernel<false>;
+    kernel<<<ceil_div(c.p.T, 4), 64 * c.p.CB, 0, s>>>(c.x, c.blob, factors, act_table, c.p);
     return hipGetLastError();
 }
 
 hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, hipStream_t s) {
     // 64 filters per workgroup unless a 64-filter grid leaves more than half of the compute units idle (see fused_conv.hip)
-    auto go = [&](auto L, auto W) -> hipError_t {
+    auto go = [&](auto L, auto W, auto P) -> hipError_t {
         constexpr int PW = W;
         static LdsLimitOnce lds_limit;   // per instance
-        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW>), act_lds_bytes<PW>())) return e;
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW, P>), act_lds_bytes<PW>())) return e;
         const dim3 grid(ceil_div(c.p.T, kFusedTiles), c.p.Kp / (8 * PW));
-        act_scaled_roles_kernel<L, PW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y,
-                                                                                      factors, c.p);
+        act_scaled_roles_kernel<L, PW, P><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y,
+                                                                                         factors, c.p);
         return hipGetLastError();
     };
     using std::integral_constant;
     const bool wide = 2LL * ceil_div(c.p.T, kFusedTiles) * (c.p.Kp / 64) > compute_units();
-    if (c.layout == WG_NHWC)
-        return wide ? go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 4>{});
-    return wide ? go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 4>{});
+    auto form = [&](auto L, auto P) { return wide ? go(L, integral_constant<int, 8>{}, P) : go(L, integral_constant<int, 4>{}, P); };
+    auto layout = [&](auto P) {
+        return c.layout == WG_NHWC ? form(integral_constant<int, WG_NHWC>{}, P) : form(integral_constant<int, WG_NCHW>{}, P);
+    };
+    return comes_in_pieces(c.x, c.p) ? layout(std::true_type{}) : layout(std::false_type{});
 }
 
 }  // namespace wg

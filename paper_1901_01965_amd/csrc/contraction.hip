@@ -27,7 +27,8 @@ constexpr int kStageBytes = 2 * kOperandBytes;      // activations + filters
 constexpr int kStages = 6;
 constexpr int kContractionLds = kStages * kStageBytes;   // 96 KB
 
-// A staged row keeps its 64 bytes but stores 16-byte chunk c at position c ^ swizzle(row), which
+// A staged filter fragment keeps the order it has in the blob, [16-byte piece][row]: its reads meet no conflicts.
+// A staged activation row keeps its 64 bytes but stores 16-byte chunk c at position c ^ swizzle(row), which
 // spreads the fragment reads of 16 consecutive rows over all banks.  The permutation is applied
 // on the global side: the LDS side of a direct load is fixed (lane l lands at base + 16 l).
 __device__ inline int swizzle(int row) { return (row ^ (row >> 2)) & 3; }
@@ -53,9 +54,9 @@ struct BlockLoader {
             const int row = wave * 32 + i * 16 + (lane >> 2);
             const int chunk = (lane & 3) ^ swizzle(row);
             // rows beyond the padded extent are clamped: their products are never stored
-            const int t = min(t0 + row, p.Tp - 1), k = min(k0 + row, p.Kp - 1);
+            const int t = min(t0 + row, p.Tp - 1), k = min(k0 + wave * 32 + i * 16 + (lane & 15), p.Kp - 1);
             a_off[i] = t * kCBlock + chunk * 16;
-            b_off[i] = (int)filter_plane_offset(0, 0, k, chunk * 16, p.Kp, NP);
+            b_off[i] = (int)filter_plane_offset(0, 0, k, (lane >> 4) * 16, p.Kp, NP);   // a whole fragment, kept in its own order
             lds_off[i] = (wave * 32 + i * 16) * kCBlock;
         }
     }
@@ -72,15 +73,15 @@ struct BlockLoader {
 
 // Fragments of one staged block for one multiplying wave: for each of the two 32-channel steps,
 // two activation and two filter fragments.  a_row/b_row: byte offset of this lane's row
-// (lane % 32) in each operand block; sw = swizzle of that row (the same for the row 32 further
+// (lane % 32) in each operand block; sw_a = swizzle of that row (the same for the row 32 further
 // on); half = lane / 32 selects the 16-byte half of a step.
 struct Frags {
     v4i a[2][2], b[2][2];   // [step][fragment]
 };
-__device__ inline void read_frags(Frags& f, const int8_t* stage, int a_row, int b_row, int sw_a, int sw_b, int half) {
+__device__ inline void read_frags(Frags& f, const int8_t* stage, int a_row, int b_row, int sw_a, int half) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-        const int ca = ((2 * ks + half) ^ sw_a) * 16, cb = ((2 * ks + half) ^ sw_b) * 16;
+        const int ca = ((2 * ks + half) ^ sw_a) * 16, cb = (2 * ks + half) * 256;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             f.a[ks][i] = *reinterpret_cast<const v4i*>(stage + a_row + i * 32 * kCBlock + ca);
@@ -188,8 +189,8 @@ __global__ __launch_bounds__(512) void contraction_kernel(const int8_t* __restri
     }
 
     const int wm = wave & 1, wn = wave >> 1;
-    const int a_row = (wm * 64 + (lane & 31)) * kCBlock, b_row = (wn * 64 + (lane & 31)) * kCBlock;
-    const int sw_a = swizzle(wm * 64 + (lane & 31)), sw_b = swizzle(wn * 64 + (lane & 31)), half = lane >> 5;
+    const int a_row = (wm * 64 + (lane & 31)) * kCBlock, b_row = wn * 64 * kCBlock + ((lane >> 4) & 1) * kFilterFragBytes + (lane & 15) * 16;
+    const int sw_a = swizzle(wm * 64 + (lane & 31)), half = lane >> 5;
 
     v16i out[2][2], acc[2][2];
 #pragma unroll
@@ -226,19 +227,19 @@ __global__ __launch_bounds__(512) void contraction_kernel(const int8_t* __restri
     // matrix-core instructions of stage f are issued, so LDS latency hides behind them.
     Frags fa, fb;
     __builtin_amdgcn_s_barrier();   // barrier 0
-    read_frags(fa, lds, a_row, b_row, sw_a, sw_b, half);
+    read_frags(fa, lds, a_row, b_row, sw_a, half);
     for (int f = 0; f < total; f += 2) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // fa (stage f) is in registers
         if (f + 1 < total) {
             __builtin_amdgcn_s_barrier();
-            read_frags(fb, lds + ((f + 1) % kStages) * kStageBytes, a_row, b_row, sw_a, sw_b, half);
+            read_frags(fb, lds + ((f + 1) % kStages) * kStageBytes, a_row, b_row, sw_a, half);
         }
         multiply_stage(fa);
         if (f + 1 >= total) break;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // fb (stage f+1) is in registers
         if (f + 2 < total) {
             __builtin_amdgcn_s_barrier();
-            read_frags(fa, lds + ((f + 2) % kStages) * kStageBytes, a_row, b_row, sw_a, sw_b, half);
+            read_frags(fa, lds + ((f + 2) % kStages) * kStageBytes, a_row, b_row, sw_a, half);
         }
         multiply_stage(fb);
     }

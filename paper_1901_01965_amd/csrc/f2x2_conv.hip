@@ -112,8 +112,9 @@ __global__ void f2_table_kernel(const uint32_t* maxmag, ScaleEntry* table, int c
 // One thread per (filter row k < Kp, channel c < 64*CB); padding rows and channels are zeros.
 __global__ __launch_bounds__(256) void f2_pack_kernel(const int8_t* w, Quantisation qn, int K, int C, int layout, int mode,
                                                       int Kp, const ScaleEntry* table, int8_t* planes) {
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int k = blockIdx.y * 4 + (threadIdx.x >> 6);
+    // a wave has 16 channels of four filters: 64 bytes in a row of every plane
+    const int c = blockIdx.x * 64 + (threadIdx.x >> 6) * 16 + (threadIdx.x & 15);
+    const int k = blockIdx.y * 4 + ((threadIdx.x >> 4) & 3);
     if (k >= Kp) return;
     int g[9], v[16];
     f2_load_filter(w, qn, k, c, K, C, layout, g);

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     // a wave-uniform base and a lane offset: the fragments' addresses take no vector registers
     const int8_t* const b_wave = reinterpret_cast<const int8_t*>(blob + planes_off) +
                                  filter_plane_offset(0, 0, kbase + __builtin_amdgcn_readfirstlane(wave) * 16, 0, p.Kp, NP);
-    const uint32_t b_lane = (uint32_t)((lane & 15) * kCBlock + (lane >> 4) * 16);
+    const uint32_t b_lane = (uint32_t)lane * 16u;
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
     uint32_t* const scales = reinterpret_cast<uint32_t*>(lds + kPlanesBytes);
     if constexpr (MODE == WG_SCALED) {   // this wave's factors, for itself: entry lane / 4 of filters lane % 4 + 4 i

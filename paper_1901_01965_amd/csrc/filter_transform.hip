@@ -115,8 +115,9 @@ __global__ __launch_bounds__(256) void filter_pack_kernel(const int8_t* w, Filte
                                                           int mode, int Kp, int CB,
                                                           const ScaleEntry* table, int8_t* planes,
                                                           int16_t* narrow, int8_t* pairs) {
-    int c = blockIdx.x * 64 + (threadIdx.x & 63);
-    int k = blockIdx.y * 4 + (threadIdx.x >> 6);
+    // a wave has 16 channels of four filters: 64 bytes in a row of every plane
+    int c = blockIdx.x * 64 + (threadIdx.x >> 6) * 16 + (threadIdx.x & 15);
+    int k = blockIdx.y * 4 + ((threadIdx.x >> 4) & 3);
     if (k >= Kp) return;
     int g[9], re[16], cr[10], ci[10];
     load_filter(w, fb, k, c, K, C, layout, g);
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(256) void filter_pack_kernel(const int8_t* w, Filte
         auto put_pair = [&](int value_index, int v) {
             int8_t* at = pairs + filter_pair_offset(value_index, c >> 6, k, 0, c & 63, Kp);
             at[0] = (int8_t)((v + 128) >> 8);
-            at[kCBlock] = (int8_t)(v & 0xff);
+            at[16] = (int8_t)(v & 0xff);
         };
         for (int e = 0; e < 16; ++e) put_pair(e, re[e]);
         for (int j = 0; j < 10; ++j) {

@@ -98,8 +98,8 @@ __device__ __forceinline__ void fused_conv_body(const int8_t* __restrict__ x, co
     cx.a_lds = lds + lds_slot(lane >> 4, lane & 15) * 16;
     cx.table_k = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
     constexpr int NP = MODE == WG_LOSSLESS ? 138 : 46;
-    const int8_t* b_lane = reinterpret_cast<const int8_t*>(blob + planes_off) +
-                           filter_plane_offset(0, 0, k, (lane >> 4) * 16, p.Kp, NP);
+    const int8_t* const b_wave = filter_fragments(blob + planes_off, k - (lane & 15), p.Kp, NP);
+    cx.b_lane = fragment_lane(lane);
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
 
     v4i Yall[NPASS][16];
@@ -130,7 +130,7 @@ __device__ __forceinline__ void fused_conv_body(const int8_t* __restrict__ x, co
     static_assert(ProductPhase<MODE, 0>::NPRE == kFilterPrefetch && ProductPhase<MODE, 1>::NPRE == kFilterPrefetch,
                   "the wait for the direct patch transfer counts the filter fragments requested after it");
     for (int cb = 0; cb < p.CB; ++cb) {
-        cx.b_glob = b_lane + cb * b_block_stride;
+        cx.b_glob = b_wave + cb * b_block_stride;
         if (half == 0) phase0.prefetch(cx); else phase1.prefetch(cx);
         if (cb > 0) {   // everyone is done reading the previous block's planes
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -415,7 +415,8 @@ __global__ __launch_bounds__(256) void fused_conv_act_scaled_kernel(const int8_t
     cx.a_lds = lds + lds_slot(lane >> 4, lane & 15) * 16;
     cx.table_k = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
     constexpr int NP = 46;
-    const int8_t* b_lane = reinterpret_cast<const int8_t*>(blob + planes_off) + filter_plane_offset(0, 0, k, (lane >> 4) * 16, p.Kp, NP);
+    const int8_t* const b_wave = filter_fragments(blob + planes_off, k - (lane & 15), p.Kp, NP);
+    cx.b_lane = fragment_lane(lane);
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
     ProductPhase<WG_SCALED, 0> phase0;
     ProductPhase<WG_SCALED, 1> phase1;
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(256) void fused_conv_act_scaled_kernel(const int8_t
 #pragma unroll
     for (int i = 0; i < kChannelSums; ++i) sums[i] = (v4i){0, 0, 0, 0};
     for (int cb = 0; cb < p.CB; ++cb) {
-        cx.b_glob = b_lane + cb * b_block_stride;
+        cx.b_glob = b_wave + cb * b_block_stride;
         if (half == 0) phase0.prefetch(cx); else phase1.prefetch(cx);
         if (cb > 0) {   // everyone is done reading the previous block's planes
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

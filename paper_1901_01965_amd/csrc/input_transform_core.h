@@ -219,21 +219,21 @@ struct ChannelPairs : BiasedBytes {
     }
 };
 
-// Transforms one loaded patch (four channels) and hands every free entry to `out`
+// Transforms one loaded patch (four channels, pixel (a, b) at 6 b + a) and hands every free entry to `out`
 // (real_entry(p, v), complex_entry(j, re, im)): an OperandSplitter emits the operand planes.
 // done_with(b) is called when column b of the patch has been read: a caller whose next patch goes into the same registers
 // asks for that column there.
 struct NothingToDo {
     __device__ inline void operator()(int) const {}
 };
-template <class Bytes = BiasedBytes, class Out, class ENC = SignedInt8, class Done = NothingToDo>
-__device__ inline void transform_patch(const uint32_t u[6][6], const Out& out, const ENC enc = ENC{}, const Done& done_with = Done{}) {
+template <class Bytes = BiasedBytes, class Patch, class Out, class ENC = SignedInt8, class Done = NothingToDo>
+__device__ inline void transform_patch(const Patch& u, const Out& out, const ENC enc = ENC{}, const Done& done_with = Done{}) {
     // column pass: d'[.][b] = B^T applied down each of the six tile columns
     Line col[6];
 #pragma unroll
     for (int b = 0; b < 6; ++b) {
-        col[b] = bt_rule(Bytes::lanes(u[0][b]), Bytes::lanes(u[1][b]), Bytes::lanes(u[2][b]), Bytes::lanes(u[3][b]),
-                         Bytes::lanes(u[4][b]), Bytes::lanes(u[5][b]));
+        col[b] = bt_rule(Bytes::lanes(u[6 * b]), Bytes::lanes(u[6 * b + 1]), Bytes::lanes(u[6 * b + 2]), Bytes::lanes(u[6 * b + 3]),
+                         Bytes::lanes(u[6 * b + 4]), Bytes::lanes(u[6 * b + 5]));
         done_with(b);
     }
     const Quad bias11 = Bytes::bias11(enc);   // what the bias leaves at entry (1,1): 16 * 128 for signed int8
@@ -264,6 +264,15 @@ __device__ inline void transform_patch(const uint32_t u[6][6], const Out& out, c
     out.complex_entry(7, ra.t5, rb.t5);
     out.complex_entry(8, ra.t3r - rb.t3i, rb.t3r + ra.t3i);
     out.complex_entry(9, ra.t3r + rb.t3i, rb.t3r - ra.t3i);
+}
+
+// The same for a patch held as u[a][b].
+template <class Bytes = BiasedBytes, class Out, class ENC = SignedInt8>
+__device__ inline void transform_patch(const uint32_t (&u)[6][6], const Out& out, const ENC enc = ENC{}) {
+    uint32_t columns[36];
+#pragma unroll
+    for (int i = 0; i < 36; ++i) columns[i] = u[i % 6][i / 6];
+    transform_patch<Bytes>(columns, out, enc);
 }
 
 }  // namespace wg

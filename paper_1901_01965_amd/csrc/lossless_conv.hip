@@ -328,11 +328,16 @@ struct RawPatch {
                 raw_off[j] = pixel_offset(p, t < p.T, n, ty, tx, 4 * (first_transfer + j) + (lane >> 4), channel);
         } else {
             channel = 4 * (lane & 15);
-            patch_offsets(p, n, ty, tx, channel, pixel);
-            if (t >= p.T) {
+            const uint32_t row = (uint32_t)p.W * (uint32_t)p.C, image = (uint32_t)n * (uint32_t)p.H * row + (uint32_t)channel;
+            uint32_t row_off[6], col_off[6];
 #pragma unroll
-                for (int i = 0; i < 36; ++i) pixel[i] = kOutsideOffset;
+            for (int a = 0; a < 6; ++a) {
+                const int h = 4 * ty - 1 + a, w = 4 * tx - 1 + a;
+                row_off[a] = t < p.T && (unsigned)h < (unsigned)p.H ? image + (uint32_t)h * row : kOutsideOffset;
+                col_off[a] = (unsigned)w < (unsigned)p.W ? (uint32_t)w * (uint32_t)p.C : kOutsideOffset;
             }
+#pragma unroll
+            for (int i = 0; i < 36; ++i) pixel[i] = __builtin_elementwise_add_sat(row_off[i / 6], col_off[i % 6]);
         }
     }
     // Channel block cb.  In the last block of a C that is not a multiple of 64 (a uniform branch) lanes whose
@@ -404,7 +409,7 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     WaveContext cx;
     cx.act = lds + lds_slot(lane >> 4, lane & 15) * 16;
     const int8_t* const flt0 = reinterpret_cast<const int8_t*>(blob + pairs_off) +
-                               filter_pair_offset(0, 0, k0 + kPairFilters * quad, 0, 0, p.Kp) + (lane & 15) * kCBlock + (lane >> 4) * 16;
+                               filter_pair_offset(0, 0, k0 + kPairFilters * quad, 0, 0, p.Kp) + lane * 16;
     const size_t flt_block = (size_t)(p.Kp >> 3) * kPairValues * kFilterFragBytes;
     cx.flt = flt0 + cb_first * flt_block;
 

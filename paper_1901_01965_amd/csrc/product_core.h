@@ -179,10 +179,17 @@ struct DirectPatch {
 
 struct LaneContext {
     const int8_t* a_lds;        // this lane's 16-byte slot in plane 0
-    const int8_t* b_glob;       // this lane's 16 bytes of filter plane 0, current channel block
+    const int8_t* b_glob;       // filter plane 0 of the wave's 16 filters, current channel block; the same for the whole wave
+    uint32_t b_lane;            // this lane's 16 bytes in a fragment: a scalar base and a 32-bit offset cost no address arithmetic
     const ScaleEntry* table_k;  // scaling table row of this lane's filter (scaled mode)
     const uint32_t* parked;     // role-specialised kernels, scaled mode: see park_scales
 };
+
+// The first fragment of the 16 filters from k (wave-uniform) on, channel block 0, and a lane's place in a fragment.
+__device__ inline const int8_t* filter_fragments(const uint8_t* planes, int k, int Kp, int nplanes) {
+    return reinterpret_cast<const int8_t*>(planes) + filter_plane_offset(0, 0, __builtin_amdgcn_readfirstlane(k), 0, Kp, nplanes);
+}
+__device__ inline uint32_t fragment_lane(int lane) { return (uint32_t)lane * 16u; }
 
 constexpr int kFilterPrefetch = 16;   // filter fragments in flight per wave (covers L2 latency)
 
@@ -216,7 +223,7 @@ struct ProductPhase {
         constexpr int slot = b_slot_of<MODE>(HALF, f);
         constexpr int plane = b_plane<MODE>(half_slot(HALF, slot).entry, f - b_start<MODE>(HALF, slot));
         constexpr int planes = MODE == WG_LOSSLESS ? 138 : 46;
-        return *reinterpret_cast<const v4i*>(cx.b_glob + (pass * 2 * planes + plane) * kFilterFragBytes);
+        return *reinterpret_cast<const v4i*>(cx.b_glob + (pass * 2 * planes + plane) * kFilterFragBytes + cx.b_lane);
     }
     template <int SLOT, int I>
     __device__ inline static v4i load_a(const LaneContext& cx) {
@@ -796,7 +803,8 @@ struct EitherHalf {
 // zero in each block, and one shift-and-add per register brings it in.  Re = Dr Wr - Di Wi keeps its two terms apart until
 // finish().  Two vector instructions per real and three per complex value and register less than joining limbs per block
 // (42 / 50 -> 21 / 25 per accumulator register and half).
-template <int HALF, int RING, bool AHEAD = false>
+// RING filter fragments and ARING activation fragments are in flight.
+template <int HALF, int RING, int ARING>
 struct ChainedSums {
     using Phase = ProductPhase<kScaledTwoPlanes, HALF>;
     static constexpr int PM = kScaledTwoPlanes;
@@ -806,11 +814,22 @@ struct ChainedSums {
         for (int s = 0; s < slot; ++s) n += is_real(half_slot(HALF, s).entry) ? 1 : 3;
         return n;
     }
-    static constexpr int kSums = sum_start(NE);
-    v4i ring[RING];
+    static constexpr int a_start(int slot) {     // first activation fragment of a slot
+        int n = 0;
+        for (int s = 0; s < slot; ++s) n += num_a<PM>(half_slot(HALF, s).entry);
+        return n;
+    }
+    static constexpr int kSums = sum_start(NE), NA = a_start(NE);
+    static_assert(ARING >= 4 && NB >= RING, "an entry's fragments are there together");
+    v4i ring[RING], aring[ARING];
 
+    template <int F>
+    __device__ inline static v4i load_a(const LaneContext& cx) {
+        constexpr int slot = [] { int s = 0; while (a_start(s + 1) <= F) ++s; return s; }();
+        return Phase::template load_a<slot, F - a_start(slot)>(cx);
+    }
     __device__ inline void prefetch(const LaneContext& cx) {
-        static_for<(NB < RING ? NB : RING)>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
+        static_for<RING>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
     }
     // The first block's prefetch, between the request for the reverse-scaling factors and their parking in `area`.
     __device__ inline void enter(LaneContext& cx, int8_t* area, int lane) {
@@ -820,43 +839,38 @@ struct ChainedSums {
         scales.park(cx, area, lane);
     }
     __device__ inline void run(const LaneContext& cx, v4i* sums) {
-        v4i afr2[AHEAD ? 2 : 1][4];
-        if constexpr (AHEAD)
-            static_for<num_a<PM>(half_slot(HALF, 0).entry)>([&](auto I) { afr2[0][I] = Phase::template load_a<0, I>(cx); });
+        static_for<ARING>([&](auto I) { aring[I] = load_a<I>(cx); });
         static_for<NE>([&](auto S) {
             constexpr int s = S;
             constexpr int entry = half_slot(HALF, s).entry;
-            constexpr int b0 = b_start<PM>(HALF, s), v = sum_start(s);
-            v4i (&a)[4] = afr2[AHEAD ? (s & 1) : 0];
-            if constexpr (!AHEAD) {
-                static_for<num_a<PM>(entry)>([&](auto I) { a[I] = Phase::template load_a<s, I>(cx); });
-            } else if constexpr (s + 1 < NE) {
-                static_for<num_a<PM>(half_slot(HALF, s + 1).entry)>(
-                    [&](auto I) { afr2[(s + 1) & 1][I] = Phase::template load_a<s + 1, I>(cx); });
-            }
+            constexpr int b0 = b_start<PM>(HALF, s), a0 = a_start(s), v = sum_start(s);
             auto mul = [](v4i x, v4i w, v4i c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(x, w, c, 0, 0, 0); };
             constexpr v4i zero = {0, 0, 0, 0};
+            v4i high[3];
             if constexpr (is_real(entry)) {
                 const v4i w = ring[b0 % RING];
-                const v4i high = mul(a[0], w, zero);
-                sums[v] = mul(a[1], w, sums[v]);
-                sums[v] += high << kByteLimbShift;
+                high[0] = mul(aring[a0 % ARING], w, zero);
+                sums[v] = mul(aring[(a0 + 1) % ARING], w, sums[v]);
             } else {   // fragments: activations Re h, Re l, Im h, Im l; filters Re, Im
                 const v4i wr = ring[b0 % RING], wi = ring[(b0 + 1) % RING];
-                const v4i rr = mul(a[0], wr, zero), ii = mul(a[2], wi, zero);
-                v4i im = mul(a[0], wi, zero);
-                sums[v] = mul(a[1], wr, sums[v]);
-                sums[v + 1] = mul(a[3], wi, sums[v + 1]);
-                sums[v + 2] = mul(a[1], wi, sums[v + 2]);
-                im = mul(a[2], wr, im);
-                sums[v + 2] = mul(a[3], wr, sums[v + 2]);
-                sums[v] += rr << kByteLimbShift;
-                sums[v + 1] += ii << kByteLimbShift;
-                sums[v + 2] += im << kByteLimbShift;
+                const v4i rh = aring[a0 % ARING], rl = aring[(a0 + 1) % ARING], ih = aring[(a0 + 2) % ARING], il = aring[(a0 + 3) % ARING];
+                high[2] = mul(rh, wi, zero);
+                high[0] = mul(rh, wr, zero);
+                sums[v + 2] = mul(rl, wi, sums[v + 2]);
+                sums[v] = mul(rl, wr, sums[v]);
+                high[2] = mul(ih, wr, high[2]);
+                high[1] = mul(ih, wi, zero);
+                sums[v + 2] = mul(il, wr, sums[v + 2]);
+                sums[v + 1] = mul(il, wi, sums[v + 1]);
             }
+            static_for<num_a<PM>(entry)>([&](auto I) {
+                if constexpr (a0 + I + ARING < NA) aring[(a0 + I) % ARING] = load_a<a0 + I + ARING>(cx);
+            });
             static_for<num_b<PM>(entry)>([&](auto I) {
                 if constexpr (b0 + I + RING < NB) ring[(b0 + I) % RING] = Phase::template load_b<b0 + I + RING>(cx);
             });
+#pragma unroll
+            for (int i = 0; i < (is_real(entry) ? 1 : 3); ++i) sums[v + i] += high[i] << kByteLimbShift;
             __builtin_amdgcn_sched_barrier(0);
         });
     }

@@ -45,7 +45,7 @@ struct TransformWavesBarrier {
 // channel sums: see the product side), so one transform serves twice the filters, no halves are added, and
 // the workgroup stages one finished copy of its outputs (32 filters in the place of each half), which the
 // transform waves write out.
-template <int LAYOUT, int MODE, bool Q8, bool WIDE, class ENC>
+template <int LAYOUT, int MODE, bool Q8, bool WIDE, bool PIECES, class ENC>
 __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                                 size_t table_off, size_t planes_off, int32_t* __restrict__ y,
                                                                 Problem p, Int8Epilogue q8, int tile_blocks, ENC enc) {
@@ -74,17 +74,17 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
 #endif
 
     if (transforms) {
-        const int a_tile = tid >> 4, a_cq = tid & 15;
+        using Loader = PatchLoader<PIECES>;
+        const int a_tile = Loader::tile_of(wave, lane), a_cq = Loader::quad_of(lane);
         OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
         int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
-        uint32_t patch[6][6], pixel[36];
         PatchBias<ENC> bias, next_bias;   // of the patch being transformed, of the one in flight
-        // the 36 pixel offsets of the patch of the thread's tile in tile block tb (none: of some tile, whose outputs nobody stores)
+        Loader loader;
         auto enter_tile_block = [&](int tb) {
             const int t = tb * kFusedTiles + a_tile;
             int n = 0, ty = 0, tx = 0;
             if (t < p.T) decode_tile(p, t, n, ty, tx);
-            patch_offsets(p, n, ty, tx, 4 * a_cq, pixel);
+            loader.enter(p, n, ty, tx, lane);
             next_bias.enter(p, ty, tx, enc);
         };
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
@@ -106,8 +106,8 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
         int cb = 0, jb = 0;   // unit u = (tile block number jb of this workgroup, channel block cb)
         if (units > 0) {
             enter_tile_block(blockIdx.x);
-            drop_absent_channels(p, 0, 4 * a_cq, pixel);
-            request_patch(xbuf, pixel, 0, patch);
+            loader.drop_absent_channels(p, 0, lane);
+            loader.request(xbuf, 0);
         }
         // was unit v the last channel block of its tile block?  v % CB == CB - 1, tracked without division:
         // last1 = for unit u - 1, last2 = for unit u - 2; tb1 / tb2 = their tile blocks
@@ -139,12 +139,13 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
                 bias = next_bias;
                 if (more) {
                     if (cb == 0) enter_tile_block((int)blockIdx.x + jb * (int)gridDim.x);
-                    drop_absent_channels(p, cb, 4 * a_cq, pixel);
+                    loader.drop_absent_channels(p, cb, lane);
                 }
-                bias.apply(patch);
+                loader.take();
+                bias.apply(loader);
                 WG_SPENT(5, mark);   // offsets
-                if (more) transform_patch<typename PatchBias<ENC>::Bytes>(patch, out, enc, NextColumns{xbuf, pixel, cb, patch});
-                else      transform_patch<typename PatchBias<ENC>::Bytes>(patch, out, enc);
+                if (more) transform_patch<typename PatchBias<ENC>::Bytes>(loader, out, enc, NextColumns<Loader>{loader, xbuf, cb});
+                else      transform_patch<typename PatchBias<ENC>::Bytes>(loader, out, enc);
             }
             WG_SPENT(3, mark);   // transform
             if (last1) {   // D_{u-1}, S_{u-1}
@@ -172,8 +173,8 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
     // behind the plane buffers and the barrier counter
     int8_t* const scale_area = lds + 2 * kLdsBytes + 64 + wave * (WIDE ? ParkedScales<kAllRows>::kBytes : kParkedScaleBytes);
     constexpr int NP = MODE == WG_LOSSLESS ? 138 : 46;
-    const int8_t* b_lane = reinterpret_cast<const int8_t*>(blob + planes_off) +
-                           filter_plane_offset(0, 0, k, (lane >> 4) * 16, p.Kp, NP);
+    const int8_t* const b_wave = filter_fragments(blob + planes_off, k - (lane & 15), p.Kp, NP);
+    cx.b_lane = fragment_lane(lane);
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
     if constexpr (WIDE) {
         // Every entry of 16 filters in one wave.  36 joined channel sums next to the fragments would not fit the registers,
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
         v4i Y[16];
         int cb = 0;
         if (units > 0) {
-            cx.b_glob = b_lane;
+            cx.b_glob = b_wave;
             ParkedScales<kAllRows> scales;
             if constexpr (MODE == WG_SCALED) scales.ask(cx, lane);
             all.prefetch(cx);
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
             const bool last = cb == p.CB - 1;
             cb = last ? 0 : cb + 1;
             if (u + 1 < units) {   // the next unit's first filter fragments travel while this one is staged
-                cx.b_glob = b_lane + cb * b_block_stride;
+                cx.b_glob = b_wave + cb * b_block_stride;
                 all.prefetch(cx);
             }
             if (last) {
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
         v4i sums[std::remove_reference_t<decltype(phase)>::kSums];
         int cb = 0;
         if (units > 0) {
-            cx.b_glob = b_lane;
+            cx.b_glob = b_wave;
             phase.enter(cx, scale_area, lane);
         }
         for (int u = 0; u < units; ++u) {
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
             const bool last = cb == p.CB - 1;
             cb = last ? 0 : cb + 1;
             if (u + 1 < units) {   // the next unit's first filter fragments travel while this one is finished and staged
-                cx.b_glob = b_lane + cb * b_block_stride;
+                cx.b_glob = b_wave + cb * b_block_stride;
                 phase.prefetch(cx);
             }
             if (last) {
@@ -265,10 +266,10 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
     };
     if constexpr (MODE == WG_SCALED) {
         if (half == 0) {
-            ChainedSums<0, 6, true> phase;
+            ChainedSums<0, 6, 8> phase;
             stream(phase);
         } else {
-            ChainedSums<1, 6, true> phase;
+            ChainedSums<1, 6, 6> phase;
             stream(phase);
         }
     } else {
@@ -280,16 +281,16 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
 #endif
 }
 
-template <int LAYOUT, int MODE, bool Q8, bool WIDE, class ENC>
+template <int LAYOUT, int MODE, bool Q8, bool WIDE, bool PIECES, class ENC>
 hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
     // two plane buffers, the transform waves' barrier counter, the parked reverse-scaling factors
     constexpr int lds_bytes = 2 * kLdsBytes + 64 + 4 * (WIDE ? ParkedScales<kAllRows>::kBytes : kParkedScaleBytes);
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, ENC>), lds_bytes)) return e;
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, PIECES, ENC>), lds_bytes)) return e;
     const int tile_blocks = ceil_div(c.p.T, kFusedTiles), filter_blocks = c.p.Kp / (kFusedFilters * (WIDE ? 2 : 1));   // Kp is a multiple of 64
     const int gx = stream_workgroups(tile_blocks, filter_blocks);
-    fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, ENC><<<dim3(gx, filter_blocks), 512, lds_bytes, s>>>(
+    fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, PIECES, ENC><<<dim3(gx, filter_blocks), 512, lds_bytes, s>>>(
         c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y, c.p, c.q8, tile_blocks, enc);
     return hipGetLastError();
 }
@@ -298,7 +299,9 @@ hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
 template <int MODE>
 hipError_t launch_stream_mode(const RolesCall& c, bool wide, hipStream_t s) {
     auto form = [&](auto L, auto Q8, const auto& enc) {
-        return wide ? launch_stream<L, MODE, Q8, true>(c, enc, s) : launch_stream<L, MODE, Q8, false>(c, enc, s);
+        const bool pieces = comes_in_pieces(c.x, c.p);
+        if (wide) return pieces ? launch_stream<L, MODE, Q8, true, true>(c, enc, s) : launch_stream<L, MODE, Q8, true, false>(c, enc, s);
+        return pieces ? launch_stream<L, MODE, Q8, false, true>(c, enc, s) : launch_stream<L, MODE, Q8, false, false>(c, enc, s);
     };
     constexpr std::integral_constant<int, WG_NHWC> nhwc{};
     constexpr std::integral_constant<int, WG_NCHW> nchw{};

@@ -85,17 +85,21 @@ __host__ __device__ inline int num_filter_planes(int mode) { return mode == WG_L
 
 // ---- packed filter blob -------------------------------------------------------
 // [BlobHeader, 256 B][maxmag: uint32 [Kp][26]][table: ScaleEntry [Kp][26]]
-// [operand planes: int8 [CB][Kp/16][planes][16][64]][narrow table, only when C <= 4:
-// int16 [Kp][36][4]][limb-pair planes, lossless only: int8 [CB][Kp/8][36][8 filters x 2 limbs][64]],
+// [operand planes: int8 [CB][Kp/16][planes][4][16][16]][narrow table, only when C <= 4:
+// int16 [Kp][36][4]][limb-pair planes, lossless only: int8 [CB][Kp/8][36][4][8 filters x 2 limbs][16]],
 // each section 256-byte aligned.
 // The operand planes are fragment-major: the 1 KB piece (16 filters x 64 channels) that one
 // matrix-core instruction consumes is contiguous, and all planes of a (channel block, filter
-// block) follow each other, so a kernel steps from plane to plane with constant offsets.
+// block) follow each other, so a kernel steps from plane to plane with constant offsets.  Inside a
+// fragment the 16-byte pieces lie in lane order, [channels / 16][filter][16 channels]: a wave's load is
+// 1 KB in a row, which a compute unit takes in at 58 bytes per clock (eight waves streaming fragments, every compute
+// unit busy); with the pieces of a filter side by side, [filter][64 channels], it was 32, and that was what the
+// convolution kernels ran at.
 constexpr uint32_t kBlobMagic = 0x33344757u;       // "WG43": signed int8 filters, Winograd-domain values of 12 bits
 constexpr uint32_t kBlobMagicInt9 = 0x39344757u;   // "WG49": uint8 filters minus a zero point (int9), values of 13 bits
 // Channel limit of the int9 path: 16 y is formed in int32 and |y| <= 9 C 255^2, so 16 * 9 * C * 255^2 < 2^31.
 constexpr int kMaxChannelsInt9 = 229;
-constexpr uint32_t kBlobVersion = 4;
+constexpr uint32_t kBlobVersion = 5;
 
 struct BlobHeader {
     uint32_t magic, version;
@@ -110,7 +114,7 @@ struct ScaleEntry {  // per (filter k, free entry): down-scale n/2^p, inverse r/
 
 constexpr int kFilterFragBytes = 16 * kCBlock;
 __host__ __device__ inline size_t filter_plane_offset(int plane, int cb, int k, int c64, int Kp, int nplanes) {
-    return ((((size_t)cb * (Kp >> 4) + (k >> 4)) * nplanes + plane) * 16 + (k & 15)) * kCBlock + c64;
+    return (((size_t)cb * (Kp >> 4) + (k >> 4)) * nplanes + plane) * kFilterFragBytes + (c64 >> 4) * 256 + (k & 15) * 16 + (c64 & 15);
 }
 
 // Reverse scaling of Section 4.2 for a 32-bit channel sum m: (m * r + 2^(q-1)) >> q with an
@@ -144,7 +148,7 @@ constexpr int kNarrowFilterBytes = kNarrowValues * kNarrowChannels * 2;   // 288
 constexpr int kPairValues = 36;
 constexpr int kPairFilters = 8;   // filters per fragment
 __host__ __device__ inline size_t filter_pair_offset(int value, int cb, int k, int limb, int c64, int Kp) {
-    return (((((size_t)cb * (Kp >> 3) + (k >> 3)) * kPairValues + value) * 16 + 2 * (k & 7) + limb) * kCBlock) + c64;
+    return (((size_t)cb * (Kp >> 3) + (k >> 3)) * kPairValues + value) * kFilterFragBytes + (c64 >> 4) * 256 + (2 * (k & 7) + limb) * 16 + (c64 & 15);
 }
 
 struct BlobLayout {
@@ -171,7 +175,7 @@ inline Scratch no_scratch() { return Scratch{nullptr, 0}; }
 
 // ---- rational F(2x2,3x3) (Sections 4.1-4.2) ----------------------------------------
 // Its packed filter blob: [BlobHeader][maxmag: uint32 [Kp][16]][table: ScaleEntry [Kp][16]]
-// [operand planes: int8 [CB][Kp/16][planes][16][64]] with planes = 32 (lossless: entry e as limbs
+// [operand planes: int8 [CB][Kp/16][planes][4][16][16]] with planes = 32 (lossless: entry e as limbs
 // 2e, 2e+1) or 16 (scaled).  Tiles are 2x2 outputs: a Problem made by make_problem_f2 counts them.
 constexpr int kF2Entries = 16;
 constexpr uint32_t kF2BlobMagic = 0x32324757u;  // "WG22"
