@@ -12,17 +12,15 @@ namespace {
 // ---- factors ---------------------------------------------------------------------------------------------
 // grid: ceil(T / 4), 64 CB threads: wave = 64-channel block, lane = (tile, four channels).  Bound by the latency of one patch
 // load and one transform.
-template <bool PIECES>
 __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                            uint32_t* __restrict__ factors, int32_t* __restrict__ act_table, Problem p) {
     __shared__ int maxima[4 * kEntries];
     const int tid = threadIdx.x, lane = tid & 63, cb = tid >> 6;
     const BlobHeaderWords header = read_blob_header(blob);
-    using Loader = PatchLoader<PIECES>;
-    const int tile = Loader::tile_of(0, lane), t = blockIdx.x * 4 + tile, cq = Loader::quad_of(lane);
+    const int tile = PatchLoader::tile_of(0, lane), t = blockIdx.x * 4 + tile, cq = PatchLoader::quad_of(lane);
     int n = 0, ty = 0, tx = 0;
     if (t < p.T) decode_tile(p, t, n, ty, tx);
-    Loader loader;
+    PatchLoader loader;
     loader.enter(p, n, ty, tx, lane);
     loader.drop_absent_channels(p, cb, lane);
     loader.request(activation_buffer(x, p), cb);
@@ -31,14 +29,13 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
     s16x2 mx[kEntries];
 #pragma unroll
     for (int e = 0; e < kEntries; ++e) mx[e] = (s16x2){0, 0};
-    loader.take();
-    transform_patch<StoredInt8>(loader, MaxKeeper{mx});
+    transform_patch<StoredInt8>(loader.patch, MaxKeeper{mx});
     // over the sixteen threads of a tile, two entries per register; then one LDS maximum per tile, entry and wave
 #pragma unroll
     for (int j = 0; j < kEntries / 2; ++j) {
         s16x2 m = {max(mx[2 * j].x, mx[2 * j].y), max(mx[2 * j + 1].x, mx[2 * j + 1].y)};
 #pragma unroll
-        for (int off : {1, 2, 16, 32})   // the lanes of a tile (PatchLoader)
+        for (int off = 1; off < 16; off <<= 1)
             m = __builtin_elementwise_max(m, as_s16x2((uint32_t)__shfl_xor((int)as_u32(m), off)));
         if (cq == j) {
             atomicMax(&maxima[tile * kEntries + 2 * j], (int)m.x);
@@ -135,7 +132,7 @@ static_assert(2 * kActPlaneBuffer <= kLdsBytes && act_lds_bytes<8>() <= 160 * 10
 
 // grid (ceil(T/16), Kp/(8 PW)), 64 (4 + PW) threads: the roles of fused_conv_roles_kernel (roles_kernel.h): waves 0-3 transform one
 // channel block ahead, the others multiply; product wave pw owns filter block pw % (PW / 2) and half pw / (PW / 2) of the entries.
-template <int LAYOUT, int PW, bool PIECES>
+template <int LAYOUT, int PW>
 __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                                          size_t table_off, size_t planes_off, int32_t* __restrict__ y,
                                                                          const uint32_t* __restrict__ factors, Problem p) {
@@ -168,12 +165,11 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
     };
 
     if (wave < 4) {
-        using Loader = PatchLoader<PIECES>;
-        const int a_tile = Loader::tile_of(wave, lane), a_cq = Loader::quad_of(lane), a_t = tile0 + a_tile;
+        const int a_tile = PatchLoader::tile_of(wave, lane), a_cq = PatchLoader::quad_of(lane), a_t = tile0 + a_tile;
         int n = 0, ty = 0, tx = 0;
         if (a_t < p.T) decode_tile(p, a_t, n, ty, tx);
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
-        Loader loader;
+        PatchLoader loader;
         loader.enter(p, n, ty, tx, lane);
         loader.drop_absent_channels(p, 0, lane);
         loader.request(xbuf, 0);
@@ -187,12 +183,11 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
                 __builtin_amdgcn_s_barrier();
             }
             out.sink.base = slot + (cb & 1) * kActPlaneBuffer;
-            loader.take();
             if (cb + 1 < p.CB) {
                 loader.drop_absent_channels(p, cb + 1, lane);
-                transform_patch<StoredInt8>(loader, out, SignedInt8{}, NextColumns<Loader>{loader, xbuf, cb + 1});
+                transform_patch<StoredInt8>(loader.patch, out, SignedInt8{}, NextColumns{loader, xbuf, cb + 1});
             } else {
-                transform_patch<StoredInt8>(loader, out);
+                transform_patch<StoredInt8>(loader.patch, out);
             }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -252,29 +247,26 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
 }  // namespace
 
 hipError_t launch_act_factors(const RolesCall& c, uint32_t* factors, int32_t* act_table, hipStream_t s) {
-    const auto kernel = comes_in_pieces(c.x, c.p) ? act_factors_kernel<true> : act_factors_kernel<false>;
-    kernel<<<ceil_div(c.p.T, 4), 64 * c.p.CB, 0, s>>>(c.x, c.blob, factors, act_table, c.p);
+    act_factors_kernel<<<ceil_div(c.p.T, 4), 64 * c.p.CB, 0, s>>>(c.x, c.blob, factors, act_table, c.p);
     return hipGetLastError();
 }
 
 hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, hipStream_t s) {
     // 64 filters per workgroup unless a 64-filter grid leaves more than half of the compute units idle (see fused_conv.hip)
-    auto go = [&](auto L, auto W, auto P) -> hipError_t {
+    auto go = [&](auto L, auto W) -> hipError_t {
         constexpr int PW = W;
         static LdsLimitOnce lds_limit;   // per instance
-        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW, P>), act_lds_bytes<PW>())) return e;
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW>), act_lds_bytes<PW>())) return e;
         const dim3 grid(ceil_div(c.p.T, kFusedTiles), c.p.Kp / (8 * PW));
-        act_scaled_roles_kernel<L, PW, P><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y,
-                                                                                         factors, c.p);
+        act_scaled_roles_kernel<L, PW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y,
+                                                                                      factors, c.p);
         return hipGetLastError();
     };
     using std::integral_constant;
     const bool wide = 2LL * ceil_div(c.p.T, kFusedTiles) * (c.p.Kp / 64) > compute_units();
-    auto form = [&](auto L, auto P) { return wide ? go(L, integral_constant<int, 8>{}, P) : go(L, integral_constant<int, 4>{}, P); };
-    auto layout = [&](auto P) {
-        return c.layout == WG_NHWC ? form(integral_constant<int, WG_NHWC>{}, P) : form(integral_constant<int, WG_NCHW>{}, P);
-    };
-    return comes_in_pieces(c.x, c.p) ? layout(std::true_type{}) : layout(std::false_type{});
+    if (c.layout == WG_NHWC)
+        return wide ? go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 4>{});
+    return wide ? go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 4>{});
 }
 
 }  // namespace wg

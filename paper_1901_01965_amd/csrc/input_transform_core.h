@@ -226,8 +226,8 @@ struct ChannelPairs : BiasedBytes {
 struct NothingToDo {
     __device__ inline void operator()(int) const {}
 };
-template <class Bytes = BiasedBytes, class Patch, class Out, class ENC = SignedInt8, class Done = NothingToDo>
-__device__ inline void transform_patch(const Patch& u, const Out& out, const ENC enc = ENC{}, const Done& done_with = Done{}) {
+template <class Bytes = BiasedBytes, class Out, class ENC = SignedInt8, class Done = NothingToDo>
+__device__ inline void transform_patch(const uint32_t (&u)[36], const Out& out, const ENC enc = ENC{}, const Done& done_with = Done{}) {
     // column pass: d'[.][b] = B^T applied down each of the six tile columns
     Line col[6];
 #pragma unroll

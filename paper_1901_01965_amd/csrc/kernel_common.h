@@ -61,27 +61,21 @@ __device__ inline __amdgpu_buffer_rsrc_t activation_buffer(const int8_t* x, cons
 }
 
 // How the four transform waves of the role-specialised kernels bring the 6x6 patches of their 16 tiles, one channel block at
-// a time: wave w has tiles 4w .. 4w + 3; lane = 16 j + m holds four channels, quad(lane) = 4 (m % 4) + j, of tile 4w + m / 4.
-// The compute unit's vector-memory path takes a load instruction per 16 clocks whatever its width, and the product waves
-// fill it with filter fragments (144 per channel block and 64 filters), so 144 four-byte loads of patches were as many again.
-// PIECES (C % 16 = 0 and an aligned tensor): a lane loads 16 channels of every fourth pixel: nine instructions per wave, after
-// which the four lanes of equal m exchange dwords, one lane-swap instruction per register.  (Through LDS the same exchange
-// cost more than it saved.)  Otherwise every lane loads its four channels of every pixel.
+// a time: wave w has tiles 4w .. 4w + 3, lane = (tile, four channels).  Every lane loads its four channels of every pixel,
+// sixteen neighbouring lanes 64 bytes in a row.  (Sixteen channels of every fourth pixel per lane, nine instructions instead of
+// 36, and an exchange of dwords between lanes by lane swaps or through LDS were 1-2 % and 5-15 % slower: the exchange lengthens
+// the transform waves' chain, and these loads are not what fills the memory path.)
 // Pixels are numbered down the columns, i = 6 b + a.
-template <bool PIECES>
 struct PatchLoader {
-    static constexpr int kOffsets = PIECES ? 9 : 36;
-    v4i piece[PIECES ? 9 : 1];        // in flight
-    uint32_t dword[PIECES ? 1 : 36];
-    uint32_t at[kOffsets];   // channel block 0: pixel 4 i + j, 16 channels (PIECES); else pixel i, four channels
-    __device__ inline static int tile_of(int wave, int lane) { return 4 * wave + ((lane & 15) >> 2); }
-    __device__ inline static int quad_of(int lane) { return 4 * (lane & 3) + (lane >> 4); }   // of four channels
-    __device__ inline static int first_channel(int lane) { return PIECES ? 16 * (lane & 3) : 4 * quad_of(lane); }   // of a load
+    uint32_t patch[36];   // the patch, or what is in flight of it
+    uint32_t at[36];      // each pixel's offset, channel block 0; a channel block is a uniform offset on top
+    __device__ inline static int tile_of(int wave, int lane) { return 4 * wave + (lane >> 4); }
+    __device__ inline static int quad_of(int lane) { return lane & 15; }   // of four channels
 
     // tile (n, ty, tx) of this lane; one that does not exist may be any: nobody stores its outputs
     __device__ inline void enter(const Problem& p, int n, int ty, int tx, int lane) {
-        const int h0 = 4 * ty - 1, w0 = 4 * tx - 1, j = lane >> 4;
-        const uint32_t row = (uint32_t)p.W * (uint32_t)p.C, image = (uint32_t)n * (uint32_t)p.H * row + (uint32_t)first_channel(lane);
+        const int h0 = 4 * ty - 1, w0 = 4 * tx - 1;
+        const uint32_t row = (uint32_t)p.W * (uint32_t)p.C, image = (uint32_t)n * (uint32_t)p.H * row + (uint32_t)(4 * quad_of(lane));
         uint32_t row_off[6], col_off[6];
 #pragma unroll
         for (int a = 0; a < 6; ++a) {
@@ -89,75 +83,33 @@ struct PatchLoader {
             col_off[a] = (unsigned)(w0 + a) < (unsigned)p.W ? (uint32_t)(w0 + a) * (uint32_t)p.C : kOutsideOffset;
         }
 #pragma unroll
-        for (int i = 0; i < kOffsets; ++i) {
-            const int first = PIECES ? 4 * i : i;
-            uint32_t r = row_off[first % 6], c = col_off[first / 6];
-            if constexpr (PIECES) {
-#pragma unroll
-                for (int k = 1; k < 4; ++k) {
-                    r = j == k ? row_off[(first + k) % 6] : r;
-                    if ((first + k) / 6 != first / 6) c = j == k ? col_off[(first + k) / 6] : c;
-                }
-            }
-            at[i] = __builtin_elementwise_add_sat(r, c);
-        }
+        for (int i = 0; i < 36; ++i) at[i] = __builtin_elementwise_add_sat(row_off[i % 6], col_off[i / 6]);
     }
     // To be called before block cb is asked for.  Only the last channel block of a C that is not a multiple of 64 has channels
     // beyond C (a uniform branch): there such a lane asks for the outside offset, so that it gets zeros and never touches
     // memory next to the tensor.  The table changes: enter() comes before another tile's or block's request.
     __device__ inline void drop_absent_channels(const Problem& p, int cb, int lane) {
         if ((cb + 1) * kCBlock > p.C) {
-            const bool have = cb * kCBlock + first_channel(lane) < p.C;
+            const bool have = cb * kCBlock + 4 * quad_of(lane) < p.C;
 #pragma unroll
-            for (int i = 0; i < kOffsets; ++i) at[i] = have ? at[i] : kOutsideOffset;
+            for (int i = 0; i < 36; ++i) at[i] = have ? at[i] : kOutsideOffset;
         }
     }
-    // What column b of the patch needs and no earlier column does.
     __device__ inline void request_column(__amdgpu_buffer_rsrc_t xbuf, int cb, int b) {
-        if constexpr (PIECES) {
 #pragma unroll
-            for (int i = 0; i < 9; ++i)
-                if ((4 * i + 3) / 6 == b) piece[i] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(xbuf, at[i], cb * kCBlock, 0));
-        } else {
-#pragma unroll
-            for (int a = 0; a < 6; ++a) dword[6 * b + a] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, at[6 * b + a], cb * kCBlock, 0);
-        }
+        for (int i = 6 * b; i < 6 * b + 6; ++i) patch[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, at[i], cb * kCBlock, 0);
     }
     __device__ inline void request(__amdgpu_buffer_rsrc_t xbuf, int cb) {
 #pragma unroll
         for (int b = 0; b < 6; ++b) request_column(xbuf, cb, b);
     }
-    // From here (*this)[i] is pixel i, this lane's four channels.  PIECES: dword k of pixel 4 i + j, which lane row j has, becomes
-    // dword j of pixel 4 i + k: a transposition in two steps, halves of the wave and then rows of 16 lanes.
-    __device__ inline void take() {
-        if constexpr (PIECES) {
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                const auto s02 = __builtin_amdgcn_permlane32_swap((uint32_t)piece[i][0], (uint32_t)piece[i][2], false, false);
-                const auto s13 = __builtin_amdgcn_permlane32_swap((uint32_t)piece[i][1], (uint32_t)piece[i][3], false, false);
-                const auto t01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
-                const auto t23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
-                piece[i] = (v4i){(int)t01[0], (int)t01[1], (int)t23[0], (int)t23[1]};
-            }
-        }
-    }
-    __device__ inline uint32_t operator[](int i) const {
-        if constexpr (PIECES) return (uint32_t)piece[i >> 2][i & 3];
-        else                  return dword[i];
-    }
-    __device__ inline void set(int i, uint32_t v) {
-        if constexpr (PIECES) piece[i >> 2][i & 3] = (int)v;
-        else                  dword[i] = v;
-    }
 };
-inline bool comes_in_pieces(const int8_t* x, const Problem& p) { return ((p.C & 15) | (int)(reinterpret_cast<uintptr_t>(x) & 15)) == 0; }
 // transform_patch's done_with: column b of the block after the one being transformed is asked for as its registers become
 // free.  A compute unit's memory path is full of filter fragments (a load instruction waits some 100 clocks to enter it), so
 // a patch's loads in a row held the transform waves up longer than their arithmetic takes; spread over the column pass they
 // enter beside it.  The barriers keep the compiler from collecting them in one place again.
-template <class Loader>
 struct NextColumns {
-    Loader& loader;
+    PatchLoader& loader;
     __amdgpu_buffer_rsrc_t xbuf;
     int cb;
     __device__ inline void operator()(int b) const {
@@ -167,7 +119,7 @@ struct NextColumns {
     }
 };
 
-// What remains to be done to a patch that was taken, before transform_patch<Bytes>.  Pixels outside the image arrived as
+// What remains to be done to a loaded patch before transform_patch<Bytes>.  Pixels outside the image arrived as
 // zero bytes: for signed int8 that is x = 0 like any other byte; for uint8 they have to become the zero point, which
 // one three-input OR per pixel does (row and column terms that are zero inside the image).  (Channels beyond C meet zero filters, whatever they hold.)
 template <class ENC>
@@ -176,7 +128,7 @@ template <>
 struct PatchBias<SignedInt8> {
     __device__ inline void enter(const Problem&, int, int, const SignedInt8) {}
     using Bytes = StoredInt8;
-    template <class Patch> __device__ inline void apply(Patch&) const {}
+    __device__ inline void apply(uint32_t (&)[36]) const {}
 };
 template <>
 struct PatchBias<ZeroPointU8> {
@@ -192,8 +144,7 @@ struct PatchBias<ZeroPointU8> {
             outside |= (unsigned)(4 * tx - 1 + a) < (unsigned)p.W ? 0u : 64u << a;
         }
     }
-    template <class Patch>
-    __device__ inline void apply(Patch& patch) const {
+    __device__ inline void apply(uint32_t (&patch)[36]) const {
         uint32_t row[6], col[6], o = outside;
         asm volatile("" : "+v"(o));   // the terms are formed here, not ahead of the channel-block loop (36 registers)
 #pragma unroll
@@ -202,7 +153,7 @@ struct PatchBias<ZeroPointU8> {
             col[a] = (uint32_t)((int)(o << (25 - a)) >> 31) & zero_bytes;
         }
 #pragma unroll
-        for (int i = 0; i < 36; ++i) patch.set(i, patch[i] | row[i % 6] | col[i / 6]);
+        for (int i = 0; i < 36; ++i) patch[i] |= row[i % 6] | col[i / 6];
     }
 };
 

@@ -26,7 +26,7 @@ namespace {
 // half is allocated registers on its own, and the transform waves form their patch offsets per load.  The two 32-filter
 // halves stage their outputs in one operand buffer each and store at the same time.
 
-template <int LAYOUT, int MODE, bool Q8, int PW, bool PIECES, class ENC>
+template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
 __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                                          size_t table_off, size_t planes_off, int32_t* __restrict__ y,
                                                                          Problem p, Int8Epilogue q8, ENC enc) {
@@ -61,15 +61,14 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
 #endif
 
     if (transforms) {
-        using Loader = PatchLoader<PIECES>;
-        const int a_tile = Loader::tile_of(wave, lane), a_cq = Loader::quad_of(lane);
+        const int a_tile = PatchLoader::tile_of(wave, lane), a_cq = PatchLoader::quad_of(lane);
         const int a_tx = __shfl(my_tx, a_tile), a_ty = __shfl(my_ty, a_tile), a_n = __shfl(my_n, a_tile);
         OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
         int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
         PatchBias<ENC> bias;
         bias.enter(p, a_ty, a_tx, enc);
-        Loader loader;
+        PatchLoader loader;
         loader.enter(p, a_n, a_ty, a_tx, lane);
         loader.drop_absent_channels(p, 0, lane);
         loader.request(xbuf, 0);
@@ -85,13 +84,12 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             WG_SPENT(1, mark);   // wait for the patch
 #endif
-            loader.take();
-            bias.apply(loader);
+            bias.apply(loader.patch);
             if (cb + 1 < p.CB) {
                 loader.drop_absent_channels(p, cb + 1, lane);
-                transform_patch<typename PatchBias<ENC>::Bytes>(loader, out, enc, NextColumns<Loader>{loader, xbuf, cb + 1});
+                transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc, NextColumns{loader, xbuf, cb + 1});
             } else {
-                transform_patch<typename PatchBias<ENC>::Bytes>(loader, out, enc);
+                transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc);
             }
             WG_SPENT(2, mark);   // transform and requests
         }
@@ -125,7 +123,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
     // One loop per half (the same barriers in both), so that each is allocated registers on its own.
     auto blocks = [&](auto H) {
         using Phase = std::conditional_t<MODE == WG_LOSSLESS, LosslessSums<H, PW == 8 ? 6 : 8>,
-                                         std::conditional_t<PW == 4, ResidentScaled<H>, ChainedSums<H, H == 0 ? 8 : 6, H == 0 ? 6 : 4>>>;
+                                         std::conditional_t<PW == 4, ResidentScaled<H>, ChainedSums<H, H == 0 ? 8 : 6, 4>>>;
         Phase phase;
         v4i sums[Phase::kSums];
 #pragma unroll
@@ -167,15 +165,15 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
 #endif
 }
 
-template <int LAYOUT, int MODE, bool Q8, int PW, bool PIECES, class ENC>
+template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
 hipError_t launch_roles(const int8_t* x, const ENC& enc, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p,
                         const Int8Epilogue& q8, hipStream_t s) {
     constexpr int lds_bytes = 2 * kLdsBytes + PW * kParkedScaleBytes;   // two plane buffers, the parked reverse-scaling factors
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, PIECES, ENC>), lds_bytes)) return e;
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC>), lds_bytes)) return e;
     dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / (kFusedFilters * (PW / 4)));   // Kp is a multiple of 64
-    fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, PIECES, ENC><<<grid, 64 * (4 + PW), lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, q8,
+    fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC><<<grid, 64 * (4 + PW), lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, q8,
                                                                                              enc);
     return hipGetLastError();
 }
@@ -184,8 +182,7 @@ hipError_t launch_roles(const int8_t* x, const ENC& enc, const uint8_t* blob, co
 template <int MODE>
 hipError_t launch_roles_mode(const RolesCall& c, bool wide, hipStream_t s) {
     auto go = [&](auto L, auto Q8, auto PW, const auto& enc) {
-        return comes_in_pieces(c.x, c.p) ? launch_roles<L, MODE, Q8, PW, true>(c.x, enc, c.blob, c.bl, c.y, c.p, c.q8, s)
-                                         : launch_roles<L, MODE, Q8, PW, false>(c.x, enc, c.blob, c.bl, c.y, c.p, c.q8, s);
+        return launch_roles<L, MODE, Q8, PW>(c.x, enc, c.blob, c.bl, c.y, c.p, c.q8, s);
     };
     using std::integral_constant;
     auto form = [&](auto L, auto Q8, const auto& enc) {

@@ -45,7 +45,7 @@ struct TransformWavesBarrier {
 // channel sums: see the product side), so one transform serves twice the filters, no halves are added, and
 // the workgroup stages one finished copy of its outputs (32 filters in the place of each half), which the
 // transform waves write out.
-template <int LAYOUT, int MODE, bool Q8, bool WIDE, bool PIECES, class ENC>
+template <int LAYOUT, int MODE, bool Q8, bool WIDE, class ENC>
 __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                                 size_t table_off, size_t planes_off, int32_t* __restrict__ y,
                                                                 Problem p, Int8Epilogue q8, int tile_blocks, ENC enc) {
@@ -74,12 +74,11 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
 #endif
 
     if (transforms) {
-        using Loader = PatchLoader<PIECES>;
-        const int a_tile = Loader::tile_of(wave, lane), a_cq = Loader::quad_of(lane);
+        const int a_tile = PatchLoader::tile_of(wave, lane), a_cq = PatchLoader::quad_of(lane);
         OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
         int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
         PatchBias<ENC> bias, next_bias;   // of the patch being transformed, of the one in flight
-        Loader loader;
+        PatchLoader loader;
         auto enter_tile_block = [&](int tb) {
             const int t = tb * kFusedTiles + a_tile;
             int n = 0, ty = 0, tx = 0;
@@ -141,11 +140,10 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
                     if (cb == 0) enter_tile_block((int)blockIdx.x + jb * (int)gridDim.x);
                     loader.drop_absent_channels(p, cb, lane);
                 }
-                loader.take();
-                bias.apply(loader);
+                bias.apply(loader.patch);
                 WG_SPENT(5, mark);   // offsets
-                if (more) transform_patch<typename PatchBias<ENC>::Bytes>(loader, out, enc, NextColumns<Loader>{loader, xbuf, cb});
-                else      transform_patch<typename PatchBias<ENC>::Bytes>(loader, out, enc);
+                if (more) transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc, NextColumns{loader, xbuf, cb});
+                else      transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc);
             }
             WG_SPENT(3, mark);   // transform
             if (last1) {   // D_{u-1}, S_{u-1}
@@ -281,16 +279,16 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
 #endif
 }
 
-template <int LAYOUT, int MODE, bool Q8, bool WIDE, bool PIECES, class ENC>
+template <int LAYOUT, int MODE, bool Q8, bool WIDE, class ENC>
 hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
     // two plane buffers, the transform waves' barrier counter, the parked reverse-scaling factors
     constexpr int lds_bytes = 2 * kLdsBytes + 64 + 4 * (WIDE ? ParkedScales<kAllRows>::kBytes : kParkedScaleBytes);
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, PIECES, ENC>), lds_bytes)) return e;
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, ENC>), lds_bytes)) return e;
     const int tile_blocks = ceil_div(c.p.T, kFusedTiles), filter_blocks = c.p.Kp / (kFusedFilters * (WIDE ? 2 : 1));   // Kp is a multiple of 64
     const int gx = stream_workgroups(tile_blocks, filter_blocks);
-    fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, PIECES, ENC><<<dim3(gx, filter_blocks), 512, lds_bytes, s>>>(
+    fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, ENC><<<dim3(gx, filter_blocks), 512, lds_bytes, s>>>(
         c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y, c.p, c.q8, tile_blocks, enc);
     return hipGetLastError();
 }
@@ -299,9 +297,7 @@ hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
 template <int MODE>
 hipError_t launch_stream_mode(const RolesCall& c, bool wide, hipStream_t s) {
     auto form = [&](auto L, auto Q8, const auto& enc) {
-        const bool pieces = comes_in_pieces(c.x, c.p);
-        if (wide) return pieces ? launch_stream<L, MODE, Q8, true, true>(c, enc, s) : launch_stream<L, MODE, Q8, true, false>(c, enc, s);
-        return pieces ? launch_stream<L, MODE, Q8, false, true>(c, enc, s) : launch_stream<L, MODE, Q8, false, false>(c, enc, s);
+        return wide ? launch_stream<L, MODE, Q8, true>(c, enc, s) : launch_stream<L, MODE, Q8, false>(c, enc, s);
     };
     constexpr std::integral_constant<int, WG_NHWC> nhwc{};
     constexpr std::integral_constant<int, WG_NCHW> nchw{};
