@@ -115,9 +115,7 @@ struct ActProducts {
                 re[q] = tile_side(filter_side(re[q]));
                 if constexpr (!is_real(sl.entry)) im[q] = tile_side(filter_side(im[q]));
             }
-            er[sl.pos] = re;
-            ei[sl.pos] = im;
-            if constexpr (sl.last_in_row) finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
+            place_entry<HALF, S>(re, im, er, ei, Y);
         });
     }
 };

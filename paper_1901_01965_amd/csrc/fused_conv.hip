@@ -331,9 +331,7 @@ struct BothScaledSums {
                 re[q] = tile_side(filter_side(re[q]));
                 if constexpr (!is_real(sl.entry)) im[q] = tile_side(filter_side(im[q]));
             }
-            er[sl.pos] = re;
-            ei[sl.pos] = im;
-            if constexpr (sl.last_in_row) finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
+            place_entry<HALF, S>(re, im, er, ei, Y);
         });
     }
 };
@@ -592,6 +590,15 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
     // scaled mode also with one channel block, where the 64-filter grid is a single round and the 32-filter grid is not
     // (56x56x64 at N = 16: 11.4 -> 10.9 us against the streaming kernel's 64-filter form)
     const bool deep_enough = (p.CB >= 2 && (mode == WG_SCALED || !streams)) || (mode == WG_SCALED && wide_grid <= compute_units());
+    // Several channel blocks and several tile blocks for every workgroup (scaled mode: three): the streaming kernel with eight
+    // product waves.  Scaled: 112x112x128 N = 16 69.4 -> 65.2 us, 56x56x256 61.7 -> 59.4; with two tile blocks per workgroup it
+    // is 2-5 % behind the form below (28x28x128 N = 64 23.0 -> 24.2).  Lossless: 56x56x256 N = 16 84.2 -> 75.9, 112x112x128
+    // 78.7 -> 74.5, 28x28x128 N = 64 27.1 -> 26.2.
+    const bool long_streams = p.CB >= 2 && wide_grid > (mode == WG_SCALED ? 2LL : 1LL) * compute_units();
+    if (stream_variant == 3 || (stream_variant == 0 && variant == 0 && !forced_stream && long_streams)) {
+        status = launch_stream(c, mode, kStreamEight, s);
+        return true;
+    }
     if (variant == 1 || (variant == 0 && deep_enough && 2 * wide_grid > compute_units())) {
         status = launch_roles(c, mode, true, s);
         return true;
@@ -601,7 +608,7 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
         // would add a 32-filter block of nothing
         const bool wide = !narrow_one_round && (mode == WG_LOSSLESS || p.CB == 1) &&
                           (stream_variant == 1 || (stream_variant == 0 && whole64));
-        status = launch_stream(c, mode, wide, s);
+        status = launch_stream(c, mode, wide ? kStreamWhole : kStreamHalves, s);
         return true;
     }
     // Transform and products on separate waves: with several channel blocks and no more 32-filter workgroups than compute

@@ -87,7 +87,8 @@ template <int MODE> constexpr Op entry_op(int entry, int i) {
 }
 
 // ---- which entries a wave owns, in order ---------------------------------------------------
-// Half 0 owns rows 0,1,2 of M, half 1 rows 5 and 3; "half" 2 is all five rows, for a wave that
+// Half 0 owns rows 0,1,2 of M and M[3][0], half 1 row 5 and the rest of row 3, so that both have the same number of
+// matrix-core instructions (scaled mode 56 and 56; by whole rows 48 and 64); "half" 2 is all five rows, for a wave that
 // owns every entry.  A real row RI (rows 0,1,2,5) holds entries 4RI..4RI+3 and the complex
 // entry 16+RI; the complex row holds entries 20..25.
 constexpr int kAllRows = 2;
@@ -95,23 +96,38 @@ constexpr int row_entries(int row) { return row < 4 ? 5 : 6; }
 constexpr int row_entry(int row, int pos) {
     return row < 4 ? (pos < 4 ? 4 * row + pos : kRealEntries + row) : kRealEntries + 4 + pos;
 }
-constexpr int half_rows(int half) { return half == 0 ? 3 : (half == 1 ? 2 : 5); }
-constexpr int half_row(int half, int i) { return half == 1 ? (i == 0 ? 3 : 4) : i; }
+constexpr int half_entries(int half) { return half == 0 ? 16 : (half == 1 ? 10 : 26); }
 constexpr bool fresh_row(int half, int row) { return row < 3 || half == 1; }   // see finish_row: no earlier row of this half
-constexpr int half_entries(int half) { return half == 0 ? 15 : (half == 1 ? 11 : 26); }
 struct Slot {
     int entry, row, pos;
-    bool last_in_row;
+    bool last_in_row;   // of those this half has
 };
 constexpr Slot half_slot(int half, int i) {
+    if (half == 0 && i == 15) return Slot{row_entry(4, 0), 4, 0, true};
     int n = 0;
-    for (int r = 0; r < half_rows(half); ++r) {
-        const int row = half_row(half, r);
-        if (i < n + row_entries(row))
-            return Slot{row_entry(row, i - n), row, i - n, i - n == row_entries(row) - 1};
-        n += row_entries(row);
+    for (int r = half == 1 ? 3 : 0; r < 5; ++r) {   // half 1: row 5, then row 3 from its second entry on
+        const int skip = half == 1 && r == 4 ? 1 : 0, entries = row_entries(r) - skip;
+        if (i < n + entries) return Slot{row_entry(r, i - n + skip), r, i - n + skip, i - n == entries - 1};
+        n += entries;
     }
     return Slot{0, 0, 0, false};
+}
+// The value of slot S of a half takes its place in the row being collected; the last of a row enters the outputs.
+// ACCUMULATE: onto outputs that exist already.
+template <int HALF, int S, bool ACCUMULATE = false>
+__device__ inline void place_entry(const v4i re, const v4i im, v4i (&er)[6], v4i (&ei)[6], v4i (&Y)[16]) {
+    constexpr Slot sl = half_slot(HALF, S);
+    if constexpr (HALF == 0 && sl.row == 4) {   // M[3][0] alone: it only enters z0 = e0 + .. of finish_row
+        Y[0] += 2 * re;
+        Y[4] -= 2 * im;
+        Y[8] -= 2 * re;
+        Y[12] += 2 * im;
+    } else {
+        er[sl.pos] = re;
+        ei[sl.pos] = im;
+        if constexpr (HALF == 1 && sl.row == 4 && sl.pos == 1) er[0] = ei[0] = (v4i){0, 0, 0, 0};
+        if constexpr (sl.last_in_row) finish_row<sl.row, !ACCUMULATE && fresh_row(HALF, sl.row)>(er, ei, Y);
+    }
 }
 // index of the first filter fragment of slot i in the wave's fragment stream
 template <int MODE> constexpr int b_start(int half, int i) {
@@ -288,9 +304,7 @@ struct ProductPhase {
                         if constexpr (!is_real(sl.entry)) im[q] = unscale(im[q]);
                     }
                 }
-                er[sl.pos] = re;
-                ei[sl.pos] = im;
-                if constexpr (sl.last_in_row) finish_row<sl.row, false>(er, ei, Y);
+                place_entry<HALF, s - 1, true>(re, im, er, ei, Y);
             }
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -357,7 +371,7 @@ struct ScaledSums {
     // One channel block: each entry's limb products are formed from zero, and its value
     // 256 * high + low (byte limbs) joins the entry's running sum one entry later.
     template <int PASS = 0, int NPASS = 1>
-    __device__ inline static void run(const LaneContext& cx, v4i (&bring)[kFilterPrefetch], v4i (&sums)[kSums]) {
+    __device__ inline static void run(const LaneContext& cx, v4i (&bring)[kFilterPrefetch], v4i* sums) {
         constexpr int F0 = PASS * NB, FEND = NPASS * NB;   // this pass's place in the fragment stream
         v4i afr[2][4], acc[2][4];
         static_for<num_a<MODE>(half_slot(HALF, 0).entry)>([&](auto I) { afr[0][I] = Phase::template load_a<0, I>(cx); });
@@ -393,7 +407,7 @@ struct ScaledSums {
 
     // After the last channel block: reverse scaling of the finished sums and the output transform.
     template <int PASS = 0, bool PARKED = false>
-    __device__ inline static void finish(const LaneContext& cx, const v4i (&sums)[kSums], v4i (&Y)[16]) {
+    __device__ inline static void finish(const LaneContext& cx, const v4i* sums, v4i (&Y)[16]) {
         v4i er[6], ei[6];
         static_for<NE>([&](auto S) {
             constexpr Slot sl = half_slot(HALF, S);
@@ -407,17 +421,13 @@ struct ScaledSums {
                 re[q] = unscale(re[q]);
                 if constexpr (!is_real(sl.entry)) im[q] = unscale(im[q]);
             }
-            er[sl.pos] = re;
-            ei[sl.pos] = im;
-            if constexpr (sl.last_in_row) {
-                finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
-                __builtin_amdgcn_sched_barrier(0);   // row by row: a row's sums are dead before the next row's work begins
-            }
+            place_entry<HALF, S>(re, im, er, ei, Y);
+            if constexpr (sl.last_in_row) __builtin_amdgcn_sched_barrier(0);   // row by row: a row's sums are dead before the next row's work begins
         });
     }
 };
-constexpr int kChannelSums = 18;
-static_assert(ScaledSums<0>::kSums == kChannelSums && ScaledSums<1>::kSums == kChannelSums, "both halves keep 18 sums");
+constexpr int kChannelSums = 20;
+static_assert(ScaledSums<0>::kSums == kChannelSums && ScaledSums<1>::kSums <= kChannelSums, "room for either half's sums");
 
 // Who a thread is when 256 threads store the staged outputs of 16 tiles x 32 filters, and where its tile lies.
 struct StoreContext {
@@ -438,6 +448,15 @@ __device__ __forceinline__ void stage_outputs(int8_t* lds, int lane, int half, i
     for (int o = 0; o < 16; ++o)
 #pragma unroll
         for (int q = 0; q < 4; ++q) dst[(o * 16 + q) * kStageRow] = Yp[o][q];
+}
+
+// The same outputs of another wave's entries, added to what is staged.
+__device__ __forceinline__ void add_staged_outputs(int8_t* lds, int lane, int half, int kblock, const v4i (&Yp)[16]) {
+    int* dst = reinterpret_cast<int*>(lds) + half * kStageHalf + (4 * (lane >> 4)) * kStageRow + kblock * 16 + (lane & 15);
+#pragma unroll
+    for (int o = 0; o < 16; ++o)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) __hip_atomic_fetch_add(&dst[(o * 16 + q) * kStageRow], Yp[o][q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Where tile (lane & 15) of tile block `tile0` starts in an output tensor of pixels (offsets fit 32 bits, checked on the
@@ -683,6 +702,8 @@ struct LeanProducts {
                     sums[v] += join_limbs(acc[0] - acc[3], acc[1] - acc[4], acc[2] - acc[5]);
                     sums[v + 1] += join_limbs(acc[6], acc[7], acc[8]);
                 }
+                asm volatile("" : "+v"(sums[v]));   // here, not in front of the next use of the sums with the limbs alive until then
+                if constexpr (!is_real(entry)) asm volatile("" : "+v"(sums[v + 1]));
             } else {
                 v4i re, im = {0, 0, 0, 0};
                 if constexpr (MODE == WG_LOSSLESS) {
@@ -705,10 +726,7 @@ struct LeanProducts {
                         if constexpr (!is_real(entry)) im[q] = unscale(im[q]);
                     }
                 }
-                er[sl.pos] = re;
-                ei[sl.pos] = im;
-                // scaled mode: one channel block, so these are the outputs' first values
-                if constexpr (sl.last_in_row) finish_row<sl.row, MODE == WG_SCALED && fresh_row(HALF, sl.row)>(er, ei, Y);
+                place_entry<HALF, s, MODE != WG_SCALED>(re, im, er, ei, Y);   // scaled mode: one channel block, these are the outputs' first values
                 if constexpr (HALF == kAllRows) {
                     // Pins the entry's value, and a finished row's outputs, to this place.  Left alone, the compiler moves
                     // the vector work of all 26 entries behind the last matrix-core instruction (into the block that
@@ -752,13 +770,10 @@ struct LeanProducts {
         static_for<NE>([&](auto S) {
             constexpr Slot sl = half_slot(HALF, S);
             constexpr int v = ScaledSums<HALF>::sum_start(S);
-            er[sl.pos] = sums[v];
-            if constexpr (!is_real(sl.entry)) ei[sl.pos] = sums[v + 1];
-            else                              ei[sl.pos] = (v4i){0, 0, 0, 0};
-            if constexpr (sl.last_in_row) {
-                finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
-                __builtin_amdgcn_sched_barrier(0);   // row by row (see ScaledSums::finish)
-            }
+            v4i im = {0, 0, 0, 0};
+            if constexpr (!is_real(sl.entry)) im = sums[v + 1];
+            place_entry<HALF, S>(sums[v], im, er, ei, Y);
+            if constexpr (sl.last_in_row) __builtin_amdgcn_sched_barrier(0);   // row by row (see ScaledSums::finish)
         });
     }
 };
@@ -870,7 +885,10 @@ struct ChainedSums {
                 if constexpr (b0 + I + RING < NB) ring[(b0 + I) % RING] = Phase::template load_b<b0 + I + RING>(cx);
             });
 #pragma unroll
-            for (int i = 0; i < (is_real(entry) ? 1 : 3); ++i) sums[v + i] += high[i] << kByteLimbShift;
+            for (int i = 0; i < (is_real(entry) ? 1 : 3); ++i) {
+                sums[v + i] += high[i] << kByteLimbShift;
+                asm volatile("" : "+v"(sums[v + i]));   // here, not in front of the next use of the sums with every high limb alive until then
+            }
             __builtin_amdgcn_sched_barrier(0);
         });
     }
@@ -951,13 +969,9 @@ struct ResidentScaled {
                 re[q] = unscale(re[q]);
                 if constexpr (!is_real(sl.entry)) im[q] = unscale(im[q]);
             }
-            er[sl.pos] = re;
-            ei[sl.pos] = im;
-            if constexpr (sl.last_in_row) finish_row<sl.row, fresh_row(HALF, sl.row)>(er, ei, Y);
+            place_entry<HALF, S>(re, im, er, ei, Y);
         });
     }
 };
-static_assert(ResidentScaled<0>::kSums == 36 && ResidentScaled<1>::kSums == 36, "both halves keep 36 accumulators");
-
 }  // namespace
 }  // namespace wg

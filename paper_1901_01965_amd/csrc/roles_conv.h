@@ -29,12 +29,13 @@ hipError_t launch_sums_finish(const RolesCall& c, const int32_t* sums, int split
 inline size_t split_partial_bytes(const Problem& p, int mode, int splits) {
     return (size_t)splits * (mode == WG_LOSSLESS ? 16 : kAccPlanes) * 16 * ceil_div(p.T, 16) * p.Kp * sizeof(int32_t);
 }
-// A workgroup walks over many tile blocks of one filter block.  wide: 64 filters per workgroup (lossless mode, or one
-// channel block), else 32.
-hipError_t launch_stream_lossless(const RolesCall& c, bool wide, hipStream_t s);
-hipError_t launch_stream_scaled(const RolesCall& c, bool wide, hipStream_t s);
-inline hipError_t launch_stream(const RolesCall& c, int mode, bool wide, hipStream_t s) {
-    return mode == WG_LOSSLESS ? launch_stream_lossless(c, wide, s) : launch_stream_scaled(c, wide, s);
+// A workgroup walks over many tile blocks of one filter block (see stream_kernel.h for the forms): 32 filters or, kStreamWhole
+// (lossless mode, or one channel block) and kStreamEight, 64.
+enum StreamForm { kStreamHalves, kStreamWhole, kStreamEight };
+hipError_t launch_stream_lossless(const RolesCall& c, StreamForm form, hipStream_t s);
+hipError_t launch_stream_scaled(const RolesCall& c, StreamForm form, hipStream_t s);
+inline hipError_t launch_stream(const RolesCall& c, int mode, StreamForm form, hipStream_t s) {
+    return mode == WG_LOSSLESS ? launch_stream_lossless(c, form, s) : launch_stream_scaled(c, form, s);
 }
 // Activations scaled per tile as well (WG_SCALED blob, signed int8): the factors of every tile into factors (uint32 [T][26],
 // act_factor_bytes; act_table: null or the exported int32 [T][26][4]), then the convolution with them.

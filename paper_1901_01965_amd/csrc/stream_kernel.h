@@ -7,16 +7,15 @@
 namespace wg {
 namespace {
 
-// Barrier among the four transform waves of the streaming kernel (s_barrier would stop the product
-// waves as well): a counter in LDS that only grows, four arrivals per use.  A wave arrives once its
-// own LDS reads have returned and leaves when all four have arrived, so no wave writes the shared
-// buffer while another still reads it.  Every transform wave runs the same (workgroup-uniform)
-// sequence of uses, and all four are resident together, so the wait ends.
-struct TransformWavesBarrier {
+// Barrier among the waves of one role (s_barrier would stop the other role as well): a counter in LDS that only grows,
+// one arrival per wave and use.  A wave arrives once its own LDS accesses have completed and leaves when all have arrived.
+// Every wave of the role runs the same (workgroup-uniform) sequence of uses, and all are resident together, so the wait ends.
+template <int WAVES>
+struct RoleBarrier {
     uint32_t* counter;
     uint32_t arrivals;   // what the counter reads once everyone has arrived at the current use
     __device__ inline void sync(int lane) {
-        arrivals += 4;
+        arrivals += WAVES;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (lane == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         while ((int)(__hip_atomic_load(counter, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) - arrivals) < 0)
@@ -33,30 +32,51 @@ struct TransformWavesBarrier {
 // tile block the product waves only stage their outputs in LDS (in the buffer whose planes
 // they have just consumed), and the transform waves add the halves and write them out while
 // the product waves already multiply the next unit.
-// Barriers, in the same order on both roles: U_u (u = 1..U) publishes the planes of unit u - 1 and
-// frees the buffer of unit u - 2; after the last channel block of a tile block, D_u (every product
-// wave has finished reading the planes) and S_u (the outputs are staged).
-// The staged outputs of unit u - 2 and the planes of unit u share a buffer, and the four transform
-// waves both read the former (each thread reads rows that other waves' plane writes cover) and
-// write the latter: between the two they meet at a barrier of their own (TransformWavesBarrier;
-// the product waves, which are multiplying unit u - 1 in the other buffer, do not take part).
-// Channels-last, C % 4 = 0 (4-byte pixel loads), K % 4 = 0 (16-byte stores).
-// WIDE: 64 filters per workgroup.  Each product wave owns every entry of its 16 filters (and keeps no
-// channel sums: see the product side), so one transform serves twice the filters, no halves are added, and
-// the workgroup stages one finished copy of its outputs (32 filters in the place of each half), which the
-// transform waves write out.
-template <int LAYOUT, int MODE, bool Q8, bool WIDE, class ENC>
-__global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
-                                                                size_t table_off, size_t planes_off, int32_t* __restrict__ y,
-                                                                Problem p, Int8Epilogue q8, int tile_blocks, ENC enc) {
+// Barriers of both roles, in the same order: U_u (u = 1 .. U) publishes the planes of unit u - 1 and frees the buffer of unit
+// u - 2; after the last channel block of a tile block, D_u (every product wave has finished reading the planes) and S_u (the
+// outputs are staged).  kStreamEight: the product waves meet at a barrier of their own instead of D_u and again between the two
+// stagings, and U_{u+2} (there is a U_{U+1}) stands for S_u, so that the transform waves wait for neither; with four product
+// waves, whose chain is the longer one, that barrier's polling cost more than it gave (2-3 %).
+// The staged outputs of unit u - 2 and the planes of unit u share a buffer, and the four transform waves both read the former
+// (each thread reads rows that other waves' plane writes cover) and write the latter: between the two they meet at a barrier
+// of their own.
+// Activations channels-last, C % 4 = 0 (4-byte pixel loads).
+// Forms, by who owns what:
+//   kStreamHalves:  32 filters per workgroup; four product waves, each half of the entries of 16 filters.
+//   kStreamWhole:   64 filters; four product waves, each every entry of its 16 filters, so that one transform serves twice the
+//                   filters and no halves are added.  36 joined channel sums next to the fragments would not fit the
+//                   registers: each channel block's products go through the output transform at once and the outputs
+//                   accumulate, exact in lossless mode (the transform is linear); in scaled mode the reverse scaling applies
+//                   to the channel sum (Section 4.2), so there the host uses this form for one-block layers only.
+//   kStreamEight:   64 filters; eight product waves, each half of the entries of 16 filters: the tile blocks' fill and finish of
+//                   fused_conv_roles_kernel<PW = 8>, a third of its time at two channel blocks, run beside other tile blocks'
+//                   work.  The two halves would need twice the staging: the first writes, the second adds to it in LDS, a
+//                   longer chain per tile block, which one channel block does not pay for (56x56x64 N = 256 scaled: 77 us
+//                   with whole entries, 80 here).
+template <int FORM> constexpr int stream_filters() { return FORM == kStreamHalves ? 32 : 64; }
+template <int FORM> constexpr int stream_product_waves() { return FORM == kStreamEight ? 8 : 4; }
+
+template <int LAYOUT, int MODE, bool Q8, int FORM, class ENC>
+__global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused_conv_stream_kernel(
+    const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t table_off, size_t planes_off, int32_t* __restrict__ y, Problem p,
+    Int8Epilogue q8, int tile_blocks, ENC enc) {
+    constexpr int PW = stream_product_waves<FORM>();
+    constexpr bool OWN_BARRIER = FORM == kStreamEight;
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int lane = threadIdx.x & 63, wave8 = threadIdx.x >> 6;
     const bool transforms = wave8 < 4;
     const int tid = threadIdx.x & 255, wave = wave8 & 3;   // within the role
-    const int k0 = blockIdx.y * kFusedFilters * (WIDE ? 2 : 1);
+    int bx = blockIdx.x, by = blockIdx.y;
+    if (const int total = gridDim.x * gridDim.y; gridDim.y >= 2 && (total & 7) == 0) {   // XCD-major order, as in fused_conv_body
+        const int launch = blockIdx.y * gridDim.x + blockIdx.x;
+        const int w = (launch & 7) * (total >> 3) + (launch >> 3);
+        by = w / (int)gridDim.x;
+        bx = w - by * (int)gridDim.x;
+    }
+    const int k0 = by * stream_filters<FORM>();
     if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.Cf, MODE, ENC::kMagic)) return;
-    // this workgroup's tile blocks: blockIdx.x, blockIdx.x + gridDim.x, ...
-    const int my_blocks = (tile_blocks - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+    // this workgroup's tile blocks: bx, bx + gridDim.x, ...
+    const int my_blocks = (tile_blocks - bx + (int)gridDim.x - 1) / (int)gridDim.x;
     const int units = my_blocks * p.CB;
     const int rnd = MODE == WG_SCALED ? 8 : 0;
 #ifdef WG_TIMESTAMPS
@@ -87,12 +107,14 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
             next_bias.enter(p, ty, tx, enc);
         };
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
-        // adds the two halves staged in `buffer` for tile block tb and writes them out
+        // writes out what is staged in `buffer` for tile block tb
         auto flush = [&](int tb, int buffer) {
             StoreContext sc;
             sc.lds = lds + buffer * kLdsBytes; sc.tid = tid; sc.lane = lane; sc.rnd = rnd; sc.y = y;
+            // (opaque: what follows from these is formed here, not ahead of the loop: registers are scarce)
+            if constexpr (FORM == kStreamEight || LAYOUT == WG_NCHW) asm volatile("" : "+v"(sc.tid), "+v"(sc.lane));
             locate_tile<LAYOUT>(sc, p, tb * kFusedTiles);
-            if constexpr (WIDE) {   // one finished copy per 32 filters
+            if constexpr (FORM != kStreamHalves) {   // one finished copy per 32 filters
                 store_staged<LAYOUT, Q8, false>(sc, p, q8, k0);
                 sc.lds += kStageHalf * 4;
                 store_staged<LAYOUT, Q8, false>(sc, p, q8, k0 + kFusedFilters);
@@ -100,11 +122,11 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
                 store_staged<LAYOUT, Q8, true>(sc, p, q8, k0);
             }
         };
-        TransformWavesBarrier among_us = {reinterpret_cast<uint32_t*>(lds + 2 * kLdsBytes), 0u};
-        if (tid == 0) *among_us.counter = 0u;   // lands before the first s_barrier, long before the first use
+        RoleBarrier<4> among_us = {reinterpret_cast<uint32_t*>(lds + 2 * kLdsBytes), 0u};
+        if (tid < 2) among_us.counter[tid] = 0u;   // this role's counter and the other's: land before the first s_barrier, long before the first use
         int cb = 0, jb = 0;   // unit u = (tile block number jb of this workgroup, channel block cb)
         if (units > 0) {
-            enter_tile_block(blockIdx.x);
+            enter_tile_block(bx);
             loader.drop_absent_channels(p, 0, lane);
             loader.request(xbuf, 0);
         }
@@ -124,7 +146,7 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
                 among_us.sync(lane);   // every transform wave has read its share before any of them writes planes
             }
             WG_SPENT(1, mark);   // flush
-            const int tb = (int)blockIdx.x + jb * (int)gridDim.x;
+            const int tb = bx + jb * (int)gridDim.x;
             const bool last0 = u < units && cb == p.CB - 1;
             if (u < units) {
                 out.sink.base = slot + (u & 1) * kLdsBytes;
@@ -137,7 +159,7 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
                 if (++cb == p.CB) { cb = 0; ++jb; }
                 bias = next_bias;
                 if (more) {
-                    if (cb == 0) enter_tile_block((int)blockIdx.x + jb * (int)gridDim.x);
+                    if (cb == 0) enter_tile_block(bx + jb * (int)gridDim.x);
                     loader.drop_absent_channels(p, cb, lane);
                 }
                 bias.apply(loader.patch);
@@ -146,7 +168,7 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
                 else      transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc);
             }
             WG_SPENT(3, mark);   // transform
-            if (last1) {   // D_{u-1}, S_{u-1}
+            if (!OWN_BARRIER && last1) {   // D_{u-1}, S_{u-1}
                 __syncthreads();
                 __syncthreads();
             }
@@ -154,38 +176,59 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
             last2 = last1; tb2 = tb1;
             last1 = last0; tb1 = tb;
         }
-        if (last2) flush(tb2, (units + 1) & 1);   // the last tile block, staged in the buffer of unit U - 1
+        if (units > 0) {   // the last unit ends a tile block, staged in its buffer
+            if (OWN_BARRIER) {   // U_{U+1}
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+            }
+            flush(tb2, (units + 1) & 1);
+        }
 #ifdef WG_TIMESTAMPS
         report();
 #endif
         return;
     }
 
-    // WIDE: wave w owns filters 16 w .. 16 w + 15 of the 64 and every entry; in the staging it stands where wave
-    // (half = w / 2, kblock = w % 2) of a 32-filter workgroup stands, so that copy w / 2 holds filters 32 (w / 2) ..
-    const int kblock = wave & 1, half = wave >> 1;
-    const int k = k0 + (WIDE ? wave : kblock) * 16 + (lane & 15);
+    // 64 filters: those of the workgroup's second 32 are staged as a copy of their own
+    const int pw = wave8 - 4;
+    const int kblock4 = FORM == kStreamHalves ? (pw & 1) : (pw & 3), half = FORM == kStreamHalves ? (pw >> 1) : (FORM == kStreamWhole ? 0 : pw >> 2);
+    const int kblock = kblock4 & 1, copy = FORM == kStreamHalves ? half : kblock4 >> 1;
+    const int k = k0 + kblock4 * 16 + (lane & 15);
+    RoleBarrier<PW> among_us = {reinterpret_cast<uint32_t*>(lds + 2 * kLdsBytes) + 1, 0u};
     LaneContext cx;
     cx.table_k = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
     cx.parked = nullptr;
-    // behind the plane buffers and the barrier counter
-    int8_t* const scale_area = lds + 2 * kLdsBytes + 64 + wave * (WIDE ? ParkedScales<kAllRows>::kBytes : kParkedScaleBytes);
+    // behind the plane buffers and the barrier counters
+    int8_t* const scale_area = lds + 2 * kLdsBytes + 64 + pw * (FORM == kStreamWhole ? ParkedScales<kAllRows>::kBytes : kParkedScaleBytes);
     constexpr int NP = MODE == WG_LOSSLESS ? 138 : 46;
     const int8_t* const b_wave = filter_fragments(blob + planes_off, k - (lane & 15), p.Kp, NP);
     cx.b_lane = fragment_lane(lane);
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
-    if constexpr (WIDE) {
-        // Every entry of 16 filters in one wave.  36 joined channel sums next to the fragments would not fit the registers,
-        // so each channel block's products go through the reverse scaling and the output transform at once and the
-        // outputs accumulate: exact in lossless mode (the transform is linear); in scaled mode the reverse scaling applies
-        // to the channel sum (Section 4.2), so there the host uses this form for one-block layers only.
+    // stages a tile block's outputs once every product wave is done with the planes of unit u
+    auto stage = [&](int u, const v4i (&Y)[16]) {
+        int8_t* const at = lds + (u & 1) * kLdsBytes;
+        if constexpr (OWN_BARRIER) among_us.sync(lane); else __syncthreads();
+        WG_SPENT(3, mark);   // everyone is done with the planes
+        if (FORM != kStreamEight || half == 0) stage_outputs(at, lane, copy, kblock, Y);
+        if constexpr (FORM == kStreamEight) {
+            among_us.sync(lane);
+            if (half == 1) add_staged_outputs(at, lane, copy, kblock, Y);
+        } else {
+            __syncthreads();
+        }
+        WG_SPENT(4, mark);   // staging
+    };
+    auto published = [&]() {   // U_{u+1}
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+    };
+    if constexpr (FORM == kStreamWhole) {
         // filter ring: lossless mode has twice the fragments per entry and the registers for twelve in flight
         LeanProducts<MODE, kAllRows, false, MODE == WG_SCALED ? 8 : 12, true, true> all;
-        v4i unused[1];
         v4i Y[16];
         int cb = 0;
+        cx.b_glob = b_wave;
         if (units > 0) {
-            cx.b_glob = b_wave;
             ParkedScales<kAllRows> scales;
             if constexpr (MODE == WG_SCALED) scales.ask(cx, lane);
             all.prefetch(cx);
@@ -197,10 +240,10 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
                 for (int i = 0; i < 16; ++i) Y[i] = (v4i){0, 0, 0, 0};
             }
             WG_SPENT(5, mark);   // clearing the outputs
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();   // U_{u+1}
+            published();
             WG_SPENT(0, mark);   // barrier U
             cx.a_lds = lds + (u & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
+            v4i unused[1];
             all.run(cx, unused, Y);
             WG_SPENT(1, mark);   // products
             const bool last = cb == p.CB - 1;
@@ -209,95 +252,99 @@ __global__ __launch_bounds__(512) void fused_conv_stream_kernel(const int8_t* __
                 cx.b_glob = b_wave + cb * b_block_stride;
                 all.prefetch(cx);
             }
-            if (last) {
-                WG_SPENT(2, mark);   // prefetch issue
-                __syncthreads();   // D_u: every product wave has finished reading this unit's planes
-                WG_SPENT(3, mark);   // barrier D
-                stage_outputs(lds + (u & 1) * kLdsBytes, lane, half, kblock, Y);
-                __syncthreads();   // S_u: staged
-                WG_SPENT(4, mark);   // staging and barrier S
-            }
-        }
-#ifdef WG_TIMESTAMPS
-        report();
-#endif
-        return;
-    }
-    // Channel sums per wave (all 36 accumulators next to the outputs would not fit the 256 registers here).  Scaled mode: a
-    // loop per half, whose sums differ in number; lossless mode: one loop for both halves (a loop each would spill).
-    auto stream = [&](auto& phase) {
-        v4i sums[std::remove_reference_t<decltype(phase)>::kSums];
-        int cb = 0;
-        if (units > 0) {
-            cx.b_glob = b_wave;
-            phase.enter(cx, scale_area, lane);
-        }
-        for (int u = 0; u < units; ++u) {
-            if (cb == 0) {
-#pragma unroll
-                for (int i = 0; i < (int)(sizeof(sums) / sizeof(v4i)); ++i) sums[i] = (v4i){0, 0, 0, 0};
-            }
-            WG_SPENT(5, mark);   // clearing the sums
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();   // U_{u+1}
-            WG_SPENT(0, mark);   // barrier U
-            cx.a_lds = lds + (u & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
-            phase.run(cx, sums);
-            WG_SPENT(1, mark);   // products
-            const bool last = cb == p.CB - 1;
-            cb = last ? 0 : cb + 1;
-            if (u + 1 < units) {   // the next unit's first filter fragments travel while this one is finished and staged
-                cx.b_glob = b_wave + cb * b_block_stride;
-                phase.prefetch(cx);
-            }
-            if (last) {
-                v4i Y[16];
-                phase.finish(cx, sums, Y);
-                WG_SPENT(2, mark);   // finish
-                __syncthreads();   // D_u: every product wave has finished reading this unit's planes
-                WG_SPENT(3, mark);   // barrier D
-                stage_outputs(lds + (u & 1) * kLdsBytes, lane, half, kblock, Y);
-                __syncthreads();   // S_u: staged
-                WG_SPENT(4, mark);   // staging and barrier S
-            }
-        }
-    };
-    if constexpr (MODE == WG_SCALED) {
-        if (half == 0) {
-            ChainedSums<0, 6, 8> phase;
-            stream(phase);
-        } else {
-            ChainedSums<1, 6, 6> phase;
-            stream(phase);
+            WG_SPENT(2, mark);   // prefetch issue
+            if (last) stage(u, Y);
         }
     } else {
-        EitherHalf<8> phase{half};
-        stream(phase);
+        // Channel sums per wave.  A loop per half, whose sums differ in number; lossless mode with four product waves: one loop
+        // for both halves (a loop each would spill).
+        auto stream = [&](auto& phase) {
+            v4i sums[std::remove_reference_t<decltype(phase)>::kSums];
+            auto clear = [&]() {
+#pragma unroll
+                for (int i = 0; i < (int)(sizeof(sums) / sizeof(v4i)); ++i) sums[i] = (v4i){0, 0, 0, 0};
+            };
+            int cb = 0;
+            cx.b_glob = b_wave;
+            if (units > 0) phase.enter(cx, scale_area, lane);
+            clear();
+            for (int u = 0; u < units; ++u) {
+                WG_SPENT(5, mark);
+                published();
+                WG_SPENT(0, mark);   // barrier U
+                cx.a_lds = lds + (u & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
+                phase.run(cx, sums);
+                WG_SPENT(1, mark);   // products
+                const bool last = cb == p.CB - 1;
+                cb = last ? 0 : cb + 1;
+                // the next unit's first filter fragments travel while this one is finished and staged (eight product waves: while
+                // it is staged, for want of registers)
+                cx.b_glob = b_wave + cb * b_block_stride;
+                if (u + 1 < units && (PW == 4 || !last)) phase.prefetch(cx);
+                if (last) {
+                    v4i Y[16];
+                    phase.finish(cx, sums, Y);
+                    // (pinned: left alone, the compiler moves the outputs' arithmetic behind the waits of the staging)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(Y[i]));
+                    WG_SPENT(2, mark);   // finish
+                    if constexpr (PW == 8) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (u + 1 < units) phase.prefetch(cx);
+                    }
+                    stage(u, Y);
+                    clear();   // (here, so that their registers are free while the outputs are formed)
+                }
+            }
+        };
+        if constexpr (MODE == WG_SCALED) {
+            if (half == 0) {
+                ChainedSums<0, 6, PW == 8 ? 4 : 8> phase;
+                stream(phase);
+            } else {
+                ChainedSums<1, 6, PW == 8 ? 4 : 6> phase;
+                stream(phase);
+            }
+        } else if constexpr (PW == 8) {
+            if (half == 0) {
+                LosslessSums<0, 6> phase;
+                stream(phase);
+            } else {
+                LosslessSums<1, 6> phase;
+                stream(phase);
+            }
+        } else {
+            EitherHalf<8> phase{half};
+            stream(phase);
+        }
     }
+    if (OWN_BARRIER && units > 0) published();   // U_{U+1}
 #ifdef WG_TIMESTAMPS
     report();
 #endif
 }
 
-template <int LAYOUT, int MODE, bool Q8, bool WIDE, class ENC>
+template <int LAYOUT, int MODE, bool Q8, int FORM, class ENC>
 hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
-    // two plane buffers, the transform waves' barrier counter, the parked reverse-scaling factors
-    constexpr int lds_bytes = 2 * kLdsBytes + 64 + 4 * (WIDE ? ParkedScales<kAllRows>::kBytes : kParkedScaleBytes);
+    // two plane buffers, the roles' barrier counters, the parked reverse-scaling factors
+    constexpr int lds_bytes = 2 * kLdsBytes + 64 + (FORM == kStreamWhole ? 4 * ParkedScales<kAllRows>::kBytes : stream_product_waves<FORM>() * kParkedScaleBytes);
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, ENC>), lds_bytes)) return e;
-    const int tile_blocks = ceil_div(c.p.T, kFusedTiles), filter_blocks = c.p.Kp / (kFusedFilters * (WIDE ? 2 : 1));   // Kp is a multiple of 64
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC>), lds_bytes)) return e;
+    const int tile_blocks = ceil_div(c.p.T, kFusedTiles), filter_blocks = c.p.Kp / stream_filters<FORM>();   // Kp is a multiple of 64
     const int gx = stream_workgroups(tile_blocks, filter_blocks);
-    fused_conv_stream_kernel<LAYOUT, MODE, Q8, WIDE, ENC><<<dim3(gx, filter_blocks), 512, lds_bytes, s>>>(
+    fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC><<<dim3(gx, filter_blocks), 64 * (4 + stream_product_waves<FORM>()), lds_bytes, s>>>(
         c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y, c.p, c.q8, tile_blocks, enc);
     return hipGetLastError();
 }
 
 // One mode's launches (each mode is compiled in a file of its own).
 template <int MODE>
-hipError_t launch_stream_mode(const RolesCall& c, bool wide, hipStream_t s) {
+hipError_t launch_stream_mode(const RolesCall& c, StreamForm which, hipStream_t s) {
     auto form = [&](auto L, auto Q8, const auto& enc) {
-        return wide ? launch_stream<L, MODE, Q8, true>(c, enc, s) : launch_stream<L, MODE, Q8, false>(c, enc, s);
+        if (which == kStreamEight) return launch_stream<L, MODE, Q8, kStreamEight>(c, enc, s);
+        if (which == kStreamWhole) return launch_stream<L, MODE, Q8, kStreamWhole>(c, enc, s);
+        return launch_stream<L, MODE, Q8, kStreamHalves>(c, enc, s);
     };
     constexpr std::integral_constant<int, WG_NHWC> nhwc{};
     constexpr std::integral_constant<int, WG_NCHW> nchw{};

@@ -3,6 +3,6 @@
 
 namespace wg {
 
-hipError_t launch_stream_lossless(const RolesCall& c, bool wide, hipStream_t s) { return launch_stream_mode<WG_LOSSLESS>(c, wide, s); }
+hipError_t launch_stream_lossless(const RolesCall& c, StreamForm form, hipStream_t s) { return launch_stream_mode<WG_LOSSLESS>(c, form, s); }
 
 }  // namespace wg

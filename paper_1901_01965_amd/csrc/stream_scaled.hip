@@ -3,6 +3,6 @@
 
 namespace wg {
 
-hipError_t launch_stream_scaled(const RolesCall& c, bool wide, hipStream_t s) { return launch_stream_mode<WG_SCALED>(c, wide, s); }
+hipError_t launch_stream_scaled(const RolesCall& c, StreamForm form, hipStream_t s) { return launch_stream_mode<WG_SCALED>(c, form, s); }
 
 }  // namespace wg
