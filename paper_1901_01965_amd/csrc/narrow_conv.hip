@@ -44,11 +44,49 @@ __device__ inline int dot4(uint32_t a01, uint32_t a23, uint32_t b01, uint32_t b2
                                   false);
 }
 
+// The 6x6 patch of tile (n, ty, tx), a pixel's C <= 4 channels in the low bytes of u[a][b], zeros above them: one unaligned
+// dword per pixel.  It also brings what follows the pixel, which is masked off; where that lies beyond the tensor (a branch
+// of the whole wave, near the tensor's end) the load begins earlier and is shifted.  A pixel's bytes one by one were four
+// times the loads, 16 clocks each in the compute unit's memory path (one 224x224x3 image, 64 filters, lossless: 16.1 us instead of 8.9).
+// Pixels outside the image are clamped into it (bias_patch replaces them).
+__device__ inline void load_narrow_patch(const int8_t* __restrict__ x, const Problem& p, int n, int ty, int tx, uint32_t (&u)[6][6]) {
+    const uint32_t total = (uint32_t)p.N * (uint32_t)p.H * (uint32_t)p.W * (uint32_t)p.C;
+    if (total < 4) {
+        load_patch<WG_NHWC, false>(x, p, n, ty, tx, 0, u);
+        return;
+    }
+    uint32_t row_off[6], col_off[6];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        row_off[a] = ((uint32_t)n * (uint32_t)p.H + (uint32_t)min(max(4 * ty - 1 + a, 0), p.H - 1)) * (uint32_t)p.W * (uint32_t)p.C;
+        col_off[a] = (uint32_t)min(max(4 * tx - 1 + a, 0), p.W - 1) * (uint32_t)p.C;
+    }
+    const uint32_t channels = 0xffffffffu >> (32 - 8 * p.C);
+    auto dword = [&](uint32_t at) {
+        uint32_t v;
+        __builtin_memcpy(&v, x + at, 4);
+        return v;
+    };
+    if (__ballot(row_off[5] + col_off[5] > total - 4) == 0) {
+#pragma unroll
+        for (int i = 0; i < 36; ++i) u[i / 6][i % 6] = dword(row_off[i / 6] + col_off[i % 6]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 36; ++i) {
+            const uint32_t at = row_off[i / 6] + col_off[i % 6], from = min(at, total - 4);
+            u[i / 6][i % 6] = dword(from) >> (8 * (at - from));
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 36; ++i) u[i / 6][i % 6] &= channels;
+}
+
 // The int8 epilogue on the output transform's 16 Y (before its rescale by 2^-4): the two nested
 // floor divisions ((Y + rnd) >> 4, then (. + round) >> shift) are one, floor((Y + rnd + 16 round) /
 // 2^(4 + shift)); then the clamp to [lo, 127].
-__device__ inline int requantise_y16(int y16, int add, int shift, int lo) {
-    return min(max((y16 + add) >> shift, lo), 127);   // the compiler picks v_med3_i32
+// `add` = rnd + 16 round is in y16 already.
+__device__ inline int requantise_y16(int y16, int shift, int lo) {
+    return min(max(y16 >> shift, lo), 127);   // the compiler picks v_med3_i32
 }
 
 // grid: (ceil(T/tiles_per_wave), Kp/64), 64 threads.
@@ -66,7 +104,7 @@ __global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restric
     if (tile0 + lane < p.T) decode_tile(p, tile0 + lane, my_n, my_ty, my_tx);   // else tile (0,0,0): loaded, never used
     if (lane < tiles_per_wave) {
         uint32_t u[6][6];
-        load_patch<WG_NHWC, false>(x, p, my_n, my_ty, my_tx, 0, u);
+        load_narrow_patch(x, p, my_n, my_ty, my_tx, u);
         bias_patch(p, my_ty, my_tx, 0, u);
         Quad v[kNarrowValues];
         transform_patch<ChannelPairs>(u, ValueKeeper{v});
@@ -84,7 +122,8 @@ __global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restric
 #pragma unroll
         for (int i = 0; i < kNarrowPieces; ++i) w[i] = mine[i];
     }
-    // reverse scaling factors r | q << 8 of this filter's 26 entries
+    // reverse scaling factors r | q << 8 of this filter's 26 entries (64 lines per load, which the compute unit's waves share in
+    // its first-level cache: reading the table in order and handing it over through LDS was 14 % slower)
     uint32_t rq[MODE == WG_SCALED ? kEntries : 1];
     if constexpr (MODE == WG_SCALED) {
         const ScaleEntry* tk = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
@@ -110,7 +149,11 @@ __global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restric
     const bool vector_store = Q8 && ((p.K & 15) | (reinterpret_cast<uintptr_t>(q8.out) & 15)) == 0;
 
     const int count = min(tiles_per_wave, p.T - tile0);
-    const int rnd = MODE == WG_SCALED ? 8 : 0;
+    // With at most four input channels |y| < 2^21, so every shift from 22 on gives 0; capping it
+    // at 24 changes no result and keeps 16 * round and 4 + shift within 32 bits for shifts up to 31.
+    const int sh = Q8 ? min(q8.shift, 24) : 0, shift = 4 + sh;
+    // what is added to every output before its final shift: M[1][1] enters each of the sixteen once, with weight one
+    const int add = (MODE == WG_SCALED ? 8 : 0) + (sh > 0 ? 16 << (sh - 1) : 0);
     for (int t = 0; t < count; ++t) {
         // all of the tile's numbers are requested before the first one is used, so the wave waits
         // for LDS once per tile
@@ -130,6 +173,7 @@ __global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restric
             cr[j] = unscale(16 + j, dot4(a.x, a.y, b.x, b.y) - dot4(a.z, a.w, b.z, b.w));
             ci[j] = unscale(16 + j, dot4(a.z, a.w, b.x, b.y, dot4(a.x, a.y, b.z, b.w)));
         }
+        re[5] += add;
         int out[4][4];   // out[j][i]: output row i, column j
         output_tile(re, cr, ci, out);
 
@@ -141,17 +185,13 @@ __global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restric
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (k < p.K && row + i < p.H && col + j < p.W) dst[(size_t)(i * p.W + j) * p.K] = (out[j][i] + rnd) >> 4;
+                    if (k < p.K && row + i < p.H && col + j < p.W) dst[(size_t)(i * p.W + j) * p.K] = out[j][i] >> 4;
         } else {
             // side x side output pixels per tile (2 x 2 after pooling), one byte per lane and pixel
             const int side = q8.pool ? 2 : 4, lg = q8.pool ? 1 : 2;
             const int Ho = p.H >> (q8.pool ? 1 : 0), Wo = p.W >> (q8.pool ? 1 : 0);
             const int orow = q8.pool ? row >> 1 : row, ocol = q8.pool ? col >> 1 : col;
             int8_t* tile_out = q8.out + (((size_t)n * Ho + orow) * Wo + ocol) * p.K;
-            // With at most four input channels |y| < 2^21, so every shift from 22 on gives 0; capping it
-            // at 24 changes no result and keeps 16 * round and 4 + shift within 32 bits for shifts up to 31.
-            const int sh = min(q8.shift, 24);
-            const int add = rnd + (sh > 0 ? 16 << (sh - 1) : 0), shift = 4 + sh;
             int8_t bytes[16];   // pixel (i, j) of the tile at 4 i + j; pooled: (pi, pj) at 2 pi + pj
             if (q8.pool) {
 #pragma unroll
@@ -163,14 +203,14 @@ __global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restric
                         for (int a = 0; a < 2; ++a)
 #pragma unroll
                             for (int b = 0; b < 2; ++b)
-                                best = max(best, requantise_y16(out[2 * pj + b][2 * pi + a], add, shift, q8.lo));
+                                best = max(best, requantise_y16(out[2 * pj + b][2 * pi + a], shift, q8.lo));
                         bytes[2 * pi + pj] = (int8_t)best;
                     }
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) bytes[4 * i + j] = (int8_t)requantise_y16(out[j][i], add, shift, q8.lo);
+                    for (int j = 0; j < 4; ++j) bytes[4 * i + j] = (int8_t)requantise_y16(out[j][i], shift, q8.lo);
             }
             if (vector_store) {
                 // through LDS, so that a lane stores 16 consecutive filters of one pixel: stage[pixel][filter]
