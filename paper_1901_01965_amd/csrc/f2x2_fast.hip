@@ -59,11 +59,8 @@ struct Patch {
         for (int i = 0; i < 16; ++i)
             u[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, base | r[i / 4] | c[i % 4], ((i / 4) * p.W + i % 4) * p.C + cb * kCBlock, 0);
     }
-    // u = x + bias: signed int8 by an XOR; uint8 as it is, pixels outside the image become the zero point
-    __device__ inline void bias(uint32_t (&u)[16], const SignedInt8) const {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) u[i] ^= kBiasBytes;
-    }
+    // signed int8: StoredInt8 takes the bytes as they are; uint8: pixels outside the image become the zero point
+    __device__ inline void bias(uint32_t (&)[16], const SignedInt8) const {}
     __device__ inline void bias(uint32_t (&u)[16], const ZeroPointU8 enc) const {
         uint32_t r[4], c[4];
         terms(r, c, enc.zero_bytes);
@@ -74,8 +71,8 @@ struct Patch {
 
 // B^T d B (rule t0 = v0 - v2, t1 = v1 + v2, t2 = v2 - v1, t3 = v1 - v3 down the columns, then along the rows) into operand
 // planes 2e (high limb), 2e + 1 (low): byte limbs in scaled mode, v = 64 h + l in lossless mode (input_transform_core.h).
-template <int MODE>
-__device__ inline void transform(const uint32_t (&u)[16], uint32_t bias11_pair, int8_t* put) {
+template <int MODE, class Bytes>
+__device__ inline void transform(const uint32_t (&u)[16], const Quad bias11, int8_t* put) {
     Quad col[4][4];
     auto rule = [](Quad v0, Quad v1, Quad v2, Quad v3, Quad (&t)[4]) {
         t[0] = v0 - v2;
@@ -84,15 +81,14 @@ __device__ inline void transform(const uint32_t (&u)[16], uint32_t bias11_pair, 
         t[3] = v1 - v3;
     };
 #pragma unroll
-    for (int b = 0; b < 4; ++b) rule(unpack_u8x4(u[b]), unpack_u8x4(u[4 + b]), unpack_u8x4(u[8 + b]), unpack_u8x4(u[12 + b]), col[b]);
-    const s16x2 bias11 = as_s16x2(bias11_pair);   // 4 * bias: what the bias leaves at entry (1,1)
+    for (int b = 0; b < 4; ++b) rule(Bytes::lanes(u[b]), Bytes::lanes(u[4 + b]), Bytes::lanes(u[8 + b]), Bytes::lanes(u[12 + b]), col[b]);
     OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
     out.sink.base = put;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         Quad t[4];
         rule(col[0][r], col[1][r], col[2][r], col[3][r], t);
-        if (r == 1) t[1] = Quad{t[1].a - bias11, t[1].b - bias11};
+        if (r == 1) t[1] = t[1] - bias11;
 #pragma unroll
         for (int c = 0; c < 4; ++c) out.limbs(2 * (4 * r + c), t[c]);
     }
@@ -113,6 +109,7 @@ template <int LAYOUT, int MODE, bool Q8, bool NARROW, class ENC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f2_fast_kernel(
     const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t table_off, size_t planes_off, int32_t* __restrict__ y,
     Problem p, ENC enc, Int8Epilogue q8) {
+    using Bytes = std::conditional_t<std::is_same_v<ENC, SignedInt8>, StoredInt8, BiasedBytes>;
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int bx = blockIdx.x, by = blockIdx.y;
@@ -176,7 +173,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
         };
         if (step > 0) __syncthreads();   // the previous block's operand planes have been consumed
         patch.bias(u, enc);
-        transform<MODE>(u, enc.bias11() >> 2, put);
+        const Quad bias16 = Bytes::bias11(enc);   // of the 6x6 transform: 16 * bias; here it leaves 4 * bias
+        transform<MODE, Bytes>(u, Quad{bias16.a >> (short)2, bias16.b >> (short)2}, put);
         __builtin_amdgcn_sched_barrier(0);   // the transform's registers are dead: 128 are to do
         static_for<kRing - 1>([&](auto E) { request_b(E); });
         cb = cb + 1 == p.CB ? 0 : cb + 1;
