@@ -375,7 +375,7 @@ __device__ __forceinline__ void f2_output_transform_store(const v4i (&m)[kF2Entr
 // Product phase: wave w owns filter block w (16 filters) of the 16 tiles for all 16 entries; the
 // filter fragments travel through a ring that is filled before the transform, the activation
 // fragments of entry e + 2 are read from LDS while entry e multiplies.
-template <int LAYOUT, bool VEC4, int MODE, bool Q8>
+template <int LAYOUT, int MODE, bool Q8>
 __global__ __launch_bounds__(256) void f2_conv_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                       size_t table_off, size_t planes_off, int32_t* __restrict__ y,
                                                       Problem p, ActivationBias ab, Int8Epilogue q8) {
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(256) void f2_conv_kernel(const int8_t* __restrict__
     // all ask the same L2 channels for the same lines at the same time.
     int cb = bx % p.CB;
     uint32_t u[4][4];
-    f2_request_patch<LAYOUT, VEC4>(x, p, ab, a_n, a_ty, a_tx, cb * kCBlock + 4 * cq, u);
+    f2_request_patch<LAYOUT, false>(x, p, ab, a_n, a_ty, a_tx, cb * kCBlock + 4 * cq, u);
     // filter fragments in flight: requested before the transform, they arrive under it
     constexpr int kRing = MODE == WG_LOSSLESS ? 4 : 6;
     for (int step = 0; step < p.CB; ++step) {
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(256) void f2_conv_kernel(const int8_t* __restrict__
         f2_transform_patch(u, ab.entry11, put);
         cb = cb + 1 == p.CB ? 0 : cb + 1;
         // the next channel block's patch travels while this one multiplies
-        if (step + 1 < p.CB) f2_request_patch<LAYOUT, VEC4>(x, p, ab, a_n, a_ty, a_tx, cb * kCBlock + 4 * cq, u);
+        if (step + 1 < p.CB) f2_request_patch<LAYOUT, false>(x, p, ab, a_n, a_ty, a_tx, cb * kCBlock + 4 * cq, u);
         __syncthreads();               // the operand planes are complete
         request_a(std::integral_constant<int, 0>{});
         request_a(std::integral_constant<int, 1>{});
@@ -670,24 +670,24 @@ __global__ __launch_bounds__(256) void f2_conv_act_scaled_kernel(const int8_t* _
 }
 
 
-template <int LAYOUT, bool VEC4, int MODE, bool Q8>
+template <int LAYOUT, int MODE, bool Q8>
 hipError_t launch(const int8_t* x, const uint8_t* blob, const F2BlobLayout& bl, int32_t* y, const Problem& p,
                   const ActivationBias& ab, const Int8Epilogue& q8, hipStream_t s) {
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&f2_conv_kernel<LAYOUT, VEC4, MODE, Q8>), kF2LdsBytes)) return e;
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&f2_conv_kernel<LAYOUT, MODE, Q8>), kF2LdsBytes)) return e;
     dim3 grid(ceil_div(p.T, kF2Tiles), p.Kp / kF2Filters);
-    f2_conv_kernel<LAYOUT, VEC4, MODE, Q8><<<grid, 256, kF2LdsBytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, ab, q8);
+    f2_conv_kernel<LAYOUT, MODE, Q8><<<grid, 256, kF2LdsBytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, ab, q8);
     return hipGetLastError();
 }
 
-template <int LAYOUT, bool VEC4>
+template <int LAYOUT>
 hipError_t launch_mode(const int8_t* x, const uint8_t* blob, const F2BlobLayout& bl, int32_t* y, const Problem& p, int mode,
                        const ActivationBias& ab, const Int8Epilogue& q8, hipStream_t s) {
     if (q8.out != nullptr)
-        return mode == WG_LOSSLESS ? launch<LAYOUT, VEC4, WG_LOSSLESS, true>(x, blob, bl, y, p, ab, q8, s)
-                                   : launch<LAYOUT, VEC4, WG_SCALED, true>(x, blob, bl, y, p, ab, q8, s);
-    return mode == WG_LOSSLESS ? launch<LAYOUT, VEC4, WG_LOSSLESS, false>(x, blob, bl, y, p, ab, q8, s)
-                               : launch<LAYOUT, VEC4, WG_SCALED, false>(x, blob, bl, y, p, ab, q8, s);
+        return mode == WG_LOSSLESS ? launch<LAYOUT, WG_LOSSLESS, true>(x, blob, bl, y, p, ab, q8, s)
+                                   : launch<LAYOUT, WG_SCALED, true>(x, blob, bl, y, p, ab, q8, s);
+    return mode == WG_LOSSLESS ? launch<LAYOUT, WG_LOSSLESS, false>(x, blob, bl, y, p, ab, q8, s)
+                               : launch<LAYOUT, WG_SCALED, false>(x, blob, bl, y, p, ab, q8, s);
 }
 
 template <int LAYOUT, bool VEC4>
@@ -755,8 +755,8 @@ hipError_t launch_f2_conv(const int8_t* x, int is_unsigned, int zero_point, cons
     const ActivationBias ab = {is_unsigned ? 0u : 0x80808080u, bias * 0x01010101u, (int)(4 * bias)};
     const F2BlobLayout bl = f2_blob_layout(p.Kp, p.C, mode);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
-    if (layout == WG_NHWC) return launch_mode<WG_NHWC, false>(x, b, bl, y, p, mode, ab, q8, s);
-    return launch_mode<WG_NCHW, false>(x, b, bl, y, p, mode, ab, q8, s);
+    if (layout == WG_NHWC) return launch_mode<WG_NHWC>(x, b, bl, y, p, mode, ab, q8, s);
+    return launch_mode<WG_NCHW>(x, b, bl, y, p, mode, ab, q8, s);
 }
 
 hipError_t launch_f2_conv_act_scaled(const int8_t* x, const void* blob, int32_t* y, int32_t* act_table, const Problem& p,
