@@ -653,7 +653,7 @@ struct LeanProducts {
         static_for<(NB < kRing ? NB : kRing)>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
     }
 
-    // sums: the 18 channel sums of ScaledSums (SUMS), else unused; Y: the outputs (not SUMS)
+    // sums: the channel sums of ScaledSums (SUMS), else unused; Y: the outputs (not SUMS)
     __device__ inline void run(const LaneContext& cx, v4i* sums, v4i (&Y)[16]) {
         v4i er[6], ei[6];
         v4i afr2[AHEAD ? 2 : 1][4];
@@ -778,7 +778,7 @@ struct LeanProducts {
     }
 };
 
-// Lossless mode with 18 joined channel sums per half.
+// Lossless mode with joined channel sums (20 and 16 per half).
 template <int HALF, int RING>
 struct LosslessSums : LeanProducts<WG_LOSSLESS, HALF, true, RING> {
     using Lean = LeanProducts<WG_LOSSLESS, HALF, true, RING>;
@@ -816,8 +816,8 @@ struct EitherHalf {
 // 4 clocks, and a matrix-core instruction keeps the vector ALU from other waves for 8 of its 16).  The low activation limb
 // of every product accumulates over the channel blocks inside the matrix-core instructions; only the high limb starts from
 // zero in each block, and one shift-and-add per register brings it in.  Re = Dr Wr - Di Wi keeps its two terms apart until
-// finish().  Two vector instructions per real and three per complex value and register less than joining limbs per block
-// (42 / 50 -> 21 / 25 per accumulator register and half).
+// finish().  24 / 22 vector instructions per accumulator register and half and channel block, where joining the limbs per
+// block took 48 / 44 (56x56x256 N = 16 with int8 outputs 72.0 -> 64.9 us, together with the cheaper unpacking of StoredInt8).
 // RING filter fragments and ARING activation fragments are in flight.
 template <int HALF, int RING, int ARING>
 struct ChainedSums {

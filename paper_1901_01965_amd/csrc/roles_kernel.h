@@ -17,14 +17,15 @@ namespace {
 // barrier j (j = 1..CB) publishes the planes of block j - 1 and frees the buffer that the
 // products of block j - 2 were reading.  32 filters per workgroup (a second pass would not fit
 // the 256 registers a wave has when two share a SIMD).
-// PW = 8 (channels-last, 4-byte buffer loads, K % 4 = 0): eight product waves, twelve waves in all, 64 filters per workgroup.
-// On deep layers the workgroup's pace is set by the transform waves and by what the compute unit's vector-memory path
-// takes in, while the product waves of the eight-wave form idle half of the time: with two product waves per SIMD one
+// PW = 8: eight product waves, twelve waves in all, 64 filters per workgroup: with two product waves per SIMD one
 // transform (and one set of patch loads) serves twice the filters.  Product wave pw owns filter block pw % 4 and half
-// pw / 4 of the entries.  Three waves per SIMD leave a wave 168 registers, so in both modes the product waves keep 18
-// joined channel sums (scaled mode: instead of the 36 resident limb accumulators), with a loop per half so that each
-// half is allocated registers on its own, and the transform waves form their patch offsets per load.  The two 32-filter
-// halves stage their outputs in one operand buffer each and store at the same time.
+// pw / 4 of the entries.  Three waves per SIMD leave a wave 168 registers, so in scaled mode the product waves keep the low
+// limbs' chains (ChainedSums) instead of the 32 to 40 resident limb accumulators.  The two 32-filter halves stage their
+// outputs in one operand buffer each and store at the same time.
+// What bounds a channel block of that form in scaled mode (some 4,900 clocks): a SIMD's vector ALU, 431 instructions of the
+// transform wave and 2 x 110 of the product waves at 4 clocks + 8 for each of 112 matrix-core instructions = 3,500; filter
+// fragments and patches through the memory path, 2,500 + up to 2,300; LDS, 288 fragment reads and 288 writes, some 4,000; and the
+// transform wave's own chain, an instruction per 5 clocks, 2,650.
 
 template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
 __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
     v4i Y[16];
     // The product waves do no output transform per block.  Scaled: all 36 limb-product accumulators of a half stay
-    // resident (PW = 4), or the low limbs' chains do (PW = 8: 168 registers per wave); lossless: 18 joined channel sums.
+    // resident (PW = 4), or the low limbs' chains do (PW = 8: 168 registers per wave); lossless: joined channel sums.
     // One loop per half (the same barriers in both), so that each is allocated registers on its own.
     auto blocks = [&](auto H) {
         using Phase = std::conditional_t<MODE == WG_LOSSLESS, LosslessSums<H, PW == 8 ? 6 : 8>,
