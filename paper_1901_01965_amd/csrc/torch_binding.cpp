@@ -36,6 +36,9 @@ const at::Tensor& tensor(PyObject* o, at::ScalarType dtype, const char* what) {
     throw PyError();
 }
 
+template <class T>
+T* data(const at::Tensor& t) { return static_cast<T*>(t.data_ptr()); }
+
 int integer(PyObject* o) {
     const long v = PyLong_AsLong(o);
     if (v == -1 && PyErr_Occurred()) throw PyError();
@@ -89,13 +92,22 @@ void need_channels(int packed_for, int C, const char* what) {
     throw PyError();
 }
 
-// The enqueueing call itself runs without the interpreter lock, like a ctypes call.
+// The interpreter lock given up for as long as one of these lives, also when an exception ends that.
+struct Unlocked {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// The enqueueing call itself runs without the interpreter lock, like a ctypes call.  It is given plain pointers: asking a
+// tensor for its data can throw (a vmap batch, a wrapper subclass: tensors without storage), and a call that is refused for
+// that is refused before anything is allocated or asked of the device.
 template <class F>
 PyObject* finish(const at::Tensor& y, F&& enqueue) {
     int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = enqueue();
-    Py_END_ALLOW_THREADS
+    {
+        const Unlocked unlocked;
+        status = enqueue();
+    }
     return status == WG_OK ? THPVariable_Wrap(y) : PyLong_FromLong(status);
 }
 
@@ -115,9 +127,6 @@ PyObject* guarded(Py_ssize_t got, Py_ssize_t want, F&& body) {
     }
 }
 
-template <class T>
-T* data(const at::Tensor& t) { return static_cast<T*>(t.data_ptr()); }
-
 // (x, blob, K, C, mode, layout, out, workspace)
 PyObject* conv2d_int8(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded(n, 8, [&]() -> PyObject* {
@@ -125,23 +134,29 @@ PyObject* conv2d_int8(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& x = tensor(a[0], at::kChar, "x");
         const Dims d = dims(x, layout);
         need_channels(packed_c, d.C, "winograd_conv2d_int8");
-        const at::Tensor& blob = tensor(a[1], at::kByte, "blob");
+        const int8_t* const xp = data<int8_t>(x);
+        const void* const blob = data<void>(tensor(a[1], at::kByte, "blob"));
+        void* given = nullptr;   // a caller's workspace
+        size_t given_bytes = 0;
+        if (a[7] != Py_None) {
+            const at::Tensor& t = tensor(a[7], at::kByte, "workspace");
+            given = data<void>(t);
+            given_bytes = (size_t)t.numel();
+        }
         const at::Tensor y = output(a[6], d.N, K, d.H, d.W, layout, at::kInt, x);
+        int32_t* const yp = data<int32_t>(y);
         void* const s = stream();
         // the staged pipeline, or a caller's workspace: the C ABI's entry point
         const bool staged = a[7] == Py_None && winograd_conv2d_path(d.N, d.C, d.H, d.W, K, mode) == 1;
         if (staged || a[7] != Py_None) {
             const ScratchTensor own(staged ? winograd_workspace_bytes(d.N, d.C, d.H, d.W, K, mode) : 0, x);
-            const at::Tensor& ws = staged ? own.t : tensor(a[7], at::kByte, "workspace");
-            return finish(y, [&] {
-                return winograd_conv2d_int8(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode,
-                                            ws.data_ptr(), (size_t)ws.numel(), s);
-            });
+            void* const ws = staged ? own.p : given;
+            const size_t ws_bytes = staged ? own.bytes : given_bytes;
+            return finish(y, [&] { return winograd_conv2d_int8(xp, blob, yp, d.N, d.C, d.H, d.W, K, layout, mode, ws, ws_bytes, s); });
         }
         const ScratchTensor scratch(wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 0), x);
         return finish(y, [&] {
-            return wg::conv2d_int8_with_scratch(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode,
-                                                scratch.p, scratch.bytes, s);
+            return wg::conv2d_int8_with_scratch(xp, blob, yp, d.N, d.C, d.H, d.W, K, layout, mode, scratch.p, scratch.bytes, s);
         });
     });
 }
@@ -154,17 +169,19 @@ PyObject* conv2d_int8_requant(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& x = tensor(a[0], at::kChar, "x");
         const Dims d = dims(x, layout);
         need_channels(packed_c, d.C, f2x2 ? "f2x2_conv2d_int8_requant" : "winograd_conv2d_int8_requant");
-        const at::Tensor& blob = tensor(a[1], at::kByte, "blob");
+        const int8_t* const xp = data<int8_t>(x);
+        const void* const blob = data<void>(tensor(a[1], at::kByte, "blob"));
         const at::Tensor y = output(a[6], d.N, K, pool ? d.H / 2 : d.H, pool ? d.W / 2 : d.W, layout, at::kChar, x);
+        int8_t* const yp = data<int8_t>(y);
         void* const s = stream();
         const ScratchTensor scratch(f2x2 ? wg::f2x2_conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout)
                                          : wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 0), x);
         return finish(y, [&] {
             if (f2x2)
-                return wg::f2x2_conv2d_int8_requant_with_scratch(data<int8_t>(x), blob.data_ptr(), data<int8_t>(y), d.N, d.C, d.H, d.W, K,
-                                                                 layout, mode, shift, relu, pool, scratch.p, scratch.bytes, s);
-            return wg::conv2d_int8_requant_with_scratch(data<int8_t>(x), blob.data_ptr(), data<int8_t>(y), d.N, d.C, d.H, d.W, K, layout,
-                                                        mode, shift, relu, pool, scratch.p, scratch.bytes, s);
+                return wg::f2x2_conv2d_int8_requant_with_scratch(xp, blob, yp, d.N, d.C, d.H, d.W, K, layout, mode, shift, relu, pool,
+                                                                 scratch.p, scratch.bytes, s);
+            return wg::conv2d_int8_requant_with_scratch(xp, blob, yp, d.N, d.C, d.H, d.W, K, layout, mode, shift, relu, pool, scratch.p,
+                                                        scratch.bytes, s);
         });
     });
 }
@@ -178,17 +195,19 @@ PyObject* conv2d_bytes(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& x = tensor(a[0], is_unsigned ? at::kByte : at::kChar, "x");
         const Dims d = dims(x, layout);
         need_channels(packed_c, d.C, f2x2 ? "f2x2_conv2d_int8" : "winograd_conv2d_u8");
-        const at::Tensor& blob = tensor(a[2], at::kByte, "blob");
+        const void* const xp = data<void>(x);
+        const void* const blob = data<void>(tensor(a[2], at::kByte, "blob"));
         const at::Tensor y = output(a[7], d.N, K, d.H, d.W, layout, at::kInt, x);
+        int32_t* const yp = data<int32_t>(y);
         void* const s = stream();
         const ScratchTensor scratch(f2x2 ? wg::f2x2_conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout)
                                          : wg::conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout, mode, 1), x);
         return finish(y, [&] {
             if (f2x2)
-                return wg::f2x2_conv2d_with_scratch(x.data_ptr(), is_unsigned, zero, blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K,
-                                                    layout, mode, scratch.p, scratch.bytes, s);
-            return wg::conv2d_u8_with_scratch(data<uint8_t>(x), zero, blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout, mode,
-                                              scratch.p, scratch.bytes, s);
+                return wg::f2x2_conv2d_with_scratch(xp, is_unsigned, zero, blob, yp, d.N, d.C, d.H, d.W, K, layout, mode, scratch.p,
+                                                    scratch.bytes, s);
+            return wg::conv2d_u8_with_scratch(static_cast<const uint8_t*>(xp), zero, blob, yp, d.N, d.C, d.H, d.W, K, layout, mode, scratch.p,
+                                              scratch.bytes, s);
         });
     });
 }
@@ -200,17 +219,17 @@ PyObject* conv2d_act_scaled(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor& x = tensor(a[0], at::kChar, "x");
         const Dims d = dims(x, layout);
         need_channels(packed_c, d.C, f2x2 ? "f2x2_conv2d_int8_act_scaled" : "winograd_conv2d_int8_act_scaled");
-        const at::Tensor& blob = tensor(a[1], at::kByte, "blob");
+        const int8_t* const xp = data<int8_t>(x);
+        const void* const blob = data<void>(tensor(a[1], at::kByte, "blob"));
         int32_t* const table = a[6] == Py_None ? nullptr : data<int32_t>(tensor(a[6], at::kInt, "table"));
         const at::Tensor y = output(a[5], d.N, K, d.H, d.W, layout, at::kInt, x);
+        int32_t* const yp = data<int32_t>(y);
         void* const s = stream();
         const ScratchTensor scratch(f2x2 ? 0 : wg::act_scaled_scratch_bytes(d.N, d.C, d.H, d.W, K, layout), x);
         return finish(y, [&] {
             if (f2x2)
-                return winograd_f2x2_conv2d_int8_act_scaled(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K,
-                                                            layout, table, s);
-            return wg::conv2d_int8_act_scaled_with_scratch(data<int8_t>(x), blob.data_ptr(), data<int32_t>(y), d.N, d.C, d.H, d.W, K,
-                                                           layout, table, scratch.p, scratch.bytes, s);
+                return winograd_f2x2_conv2d_int8_act_scaled(xp, blob, yp, d.N, d.C, d.H, d.W, K, layout, table, s);
+            return wg::conv2d_int8_act_scaled_with_scratch(xp, blob, yp, d.N, d.C, d.H, d.W, K, layout, table, scratch.p, scratch.bytes, s);
         });
     });
 }
@@ -228,12 +247,13 @@ PyObject* direct_conv2d(PyObject*, PyObject* const* a, Py_ssize_t n) {
             throw PyError();
         }
         const int K = (int)w.size(0);
+        const int8_t *const xp = data<int8_t>(x), *const wp = data<int8_t>(w);
         const at::Tensor y = output(a[3], d.N, K, d.H, d.W, layout, at::kInt, x);
+        int32_t* const yp = data<int32_t>(y);
         void* const s = stream();
         const ScratchTensor scratch(wg::direct_conv2d_scratch_bytes(d.N, d.C, d.H, d.W, K, layout), x);
         return finish(y, [&] {
-            return wg::direct_conv2d_with_scratch(data<int8_t>(x), data<int8_t>(w), data<int32_t>(y), d.N, d.C, d.H, d.W, K, layout,
-                                                  scratch.p, scratch.bytes, s);
+            return wg::direct_conv2d_with_scratch(xp, wp, yp, d.N, d.C, d.H, d.W, K, layout, scratch.p, scratch.bytes, s);
         });
     });
 }
@@ -244,10 +264,12 @@ PyObject* requant_relu_pool(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int layout = integer(a[1]), shift = integer(a[3]), relu = integer(a[4]), pool = integer(a[5]);
         const at::Tensor& y = tensor(a[0], at::kInt, "y");
         const Dims d = dims(y, layout);
+        const int32_t* const yp = data<int32_t>(y);
         const at::Tensor out = output(a[2], d.N, d.C, pool ? d.H / 2 : d.H, pool ? d.W / 2 : d.W, layout, at::kChar, y);
+        int8_t* const op = data<int8_t>(out);
         void* const s = stream();
         return finish(out, [&] {
-            return requant_relu_pool_int8(data<int32_t>(y), data<int8_t>(out), d.N, d.C, d.H, d.W, layout, shift, relu, pool, s);
+            return requant_relu_pool_int8(yp, op, d.N, d.C, d.H, d.W, layout, shift, relu, pool, s);
         });
     });
 }
