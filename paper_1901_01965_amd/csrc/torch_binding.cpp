@@ -10,6 +10,7 @@
 
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "host_api.h"
@@ -73,14 +74,21 @@ at::Tensor output(PyObject* out, int N, int K, int H, int W, int layout, at::Sca
 }
 
 // Scratch memory of one call, from torch's caching allocator (which hands it out again only to work queued behind it).
+// Where it only makes the call faster (`needed` false), a device without room for it leaves the call without.
 struct ScratchTensor {
     at::Tensor t;
     void* p = nullptr;
     size_t bytes = 0;
-    ScratchTensor(size_t wanted, const at::Tensor& like) : bytes(wanted) {
+    ScratchTensor(size_t wanted, const at::Tensor& like, bool needed = false) {
         if (wanted == 0) return;
-        t = at::Tensor(at::detail::empty_cuda({(int64_t)wanted}, at::kByte, like.device(), std::nullopt));
+        try {
+            t = at::Tensor(at::detail::empty_cuda({(int64_t)wanted}, at::kByte, like.device(), std::nullopt));
+        } catch (const c10::OutOfMemoryError&) {
+            if (needed) throw;
+            return;
+        }
         p = t.data_ptr();
+        bytes = wanted;
     }
 };
 
@@ -121,8 +129,8 @@ PyObject* guarded(Py_ssize_t got, Py_ssize_t want, F&& body) {
         return body();
     } catch (const PyError&) {
         return nullptr;
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {   // torch's own errors become the Python exceptions that torch's functions raise for them
+        torch::translate_exception_to_python(std::current_exception());
         return nullptr;
     }
 }
@@ -149,7 +157,7 @@ PyObject* conv2d_int8(PyObject*, PyObject* const* a, Py_ssize_t n) {
         // the staged pipeline, or a caller's workspace: the C ABI's entry point
         const bool staged = a[7] == Py_None && winograd_conv2d_path(d.N, d.C, d.H, d.W, K, mode) == 1;
         if (staged || a[7] != Py_None) {
-            const ScratchTensor own(staged ? winograd_workspace_bytes(d.N, d.C, d.H, d.W, K, mode) : 0, x);
+            const ScratchTensor own(staged ? winograd_workspace_bytes(d.N, d.C, d.H, d.W, K, mode) : 0, x, true);
             void* const ws = staged ? own.p : given;
             const size_t ws_bytes = staged ? own.bytes : given_bytes;
             return finish(y, [&] { return winograd_conv2d_int8(xp, blob, yp, d.N, d.C, d.H, d.W, K, layout, mode, ws, ws_bytes, s); });

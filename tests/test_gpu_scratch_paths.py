@@ -99,3 +99,40 @@ def test_both_sides_scaled_with_and_without_scratch(shape, layout):
     stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     assert wg.load_library().winograd_conv2d_int8_act_scaled(p(xd), p(packed.blob), p(bare), N, C, H, W, K, layout, p(bare_table), stream) == 0
     assert torch.equal(bare, got) and torch.equal(bare_table, table)
+
+
+def test_calls_run_without_the_memory_they_would_like_and_outputs_without_memory_raise_torchs_error():
+    """Channel-major tensors with an odd channel count: every call would like a copy of 29 MB.  With no memory left they
+    write the caller's output as they can; without a caller's output they raise torch.cuda.OutOfMemoryError."""
+    N, C, K, H, W = 8, 67, 48, 224, 224
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    bytes_like = lambda *shape: torch.randint(-128, 128, shape, dtype=torch.int8, device="cuda", generator=gen)
+    x, w = bytes_like(N, C, H, W), bytes_like(K, C, 3, 3)
+    y = lambda dtype: torch.zeros((N, K, H, W), dtype=dtype, device="cuda")
+    packed = {m: wg.winograd_filter_transform(w, wg.NCHW, m) for m in (wg.LOSSLESS, wg.SCALED)}
+    packed_u8 = wg.winograd_filter_transform_u8(w.view(torch.uint8), 100, wg.NCHW, wg.SCALED)
+    packed_f2 = wg.f2x2_filter_transform(w, wg.NCHW, wg.LOSSLESS)
+    calls = [(torch.int32, lambda out: wg.winograd_conv2d_int8(x, packed[wg.LOSSLESS], wg.NCHW, out=out)),
+             (torch.int8, lambda out: wg.winograd_conv2d_int8_requant(x, packed[wg.SCALED], 12, layout=wg.NCHW, out=out)),
+             (torch.int32, lambda out: wg.winograd_conv2d_u8(x.view(torch.uint8), 90, packed_u8, wg.NCHW, out=out)),
+             (torch.int32, lambda out: wg.winograd_conv2d_int8_act_scaled(x, packed[wg.SCALED], wg.NCHW, out=out)),
+             (torch.int32, lambda out: wg.f2x2_conv2d_int8(x, packed_f2, wg.NCHW, out=out)),
+             (torch.int8, lambda out: wg.f2x2_conv2d_int8_requant(x, packed_f2, 12, layout=wg.NCHW, out=out)),
+             (torch.int32, lambda out: wg.direct_conv2d_int8(x, w, wg.NCHW, out=out))]
+    wanted = [call(None) for _, call in calls]
+    outs = [y(dtype) for dtype, _ in calls]
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    try:
+        torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / torch.cuda.get_device_properties(0).total_memory)
+        for (_, call), out in zip(calls, outs):
+            call(out)
+        for _, call in calls:
+            with pytest.raises(torch.cuda.OutOfMemoryError):
+                call(None)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    for out, want in zip(outs, wanted):
+        assert torch.equal(out, want)
