@@ -247,6 +247,10 @@ int winograd_f2x2_filter_transform_u8(const uint8_t* w_dev, int zero_point, int 
                                       int mode, void* packed_dev, size_t packed_bytes, void* hip_stream);
 int winograd_f2x2_conv2d_u8(const uint8_t* x_dev, int zero_point, const void* packed_dev, int32_t* y_dev,
                             int N, int C, int H, int W, int K, int layout, int mode, void* hip_stream);
+/* Host-only: which kernel an F(2x2,3x3) convolution of this shape runs, with the scratch memory that the Python calls give
+   it or without any: 0 a kernel that takes every shape, 1 the faster one, whose 32-bit offsets hold all but tensors with
+   extremely long rows, 2 that one on a channels-last copy of the activations. */
+int winograd_f2x2_debug_route(int N, int C, int H, int W, int K, int layout, int with_scratch);
 int winograd_f2x2_debug_filter_operands(const void* packed_dev, int K, int C, int mode,
                                         int8_t* planes_dev, int32_t* table_dev, void* hip_stream);
 /*

@@ -66,6 +66,7 @@ def load_library():
         "winograd_f2x2_filter_transform": (i, [vp, i, i, i, i, vp, sz, vp]),
         "winograd_f2x2_conv2d_int8": (i, [vp, vp, vp, i, i, i, i, i, i, i, vp]),
         "winograd_f2x2_debug_filter_operands": (i, [vp, i, i, i, vp, vp, vp]),
+        "winograd_f2x2_debug_route": (i, [i, i, i, i, i, i, i]),
         "winograd_filter_transform_u8": (i, [vp, i, i, i, i, i, vp, sz, vp]),
         "winograd_conv2d_int8_act_scaled": (i, [vp, vp, vp, i, i, i, i, i, i, vp, vp]),
         "winograd_conv2d_u8": (i, [vp, i, vp, vp, i, i, i, i, i, i, i, vp]),
@@ -118,7 +119,7 @@ EXPORTED_SYMBOLS = (
     "direct_conv2d_int8", "requant_relu_pool_int8",
     "winograd_debug_input_operands", "winograd_debug_filter_operands", "winograd_debug_contraction",
     "winograd_f2x2_packed_filter_bytes", "winograd_f2x2_filter_transform", "winograd_f2x2_conv2d_int8",
-    "winograd_f2x2_debug_filter_operands", "winograd_f2x2_filter_transform_u8", "winograd_f2x2_conv2d_u8",
+    "winograd_f2x2_debug_filter_operands", "winograd_f2x2_debug_route", "winograd_f2x2_filter_transform_u8", "winograd_f2x2_conv2d_u8",
     "winograd_f2x2_conv2d_int8_act_scaled", "winograd_f2x2_conv2d_int8_requant",
     "winograd_filter_transform_u8", "winograd_conv2d_u8", "winograd_conv2d_int8_act_scaled",
 )

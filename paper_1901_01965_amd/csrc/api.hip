@@ -190,6 +190,14 @@ int winograd_f2x2_conv2d_int8_act_scaled(const int8_t* x_dev, const void* packed
                                                layout, static_cast<hipStream_t>(hip_stream)));
 }
 
+int winograd_f2x2_debug_route(int N, int C, int H, int W, int K, int layout, int with_scratch) {
+    if (!valid_layout(layout)) return WG_EINVAL;
+    if (int st = check_shape(N, C, H, W, K)) return st;
+    const long long tiles = (long long)N * ((H + 1) / 2) * ((W + 1) / 2);
+    if (tiles + kTilePad > kIndexLimit / 64) return WG_EUNSUPPORTED;
+    return f2_conv_route(make_problem_f2(N, C, H, W, K), layout, with_scratch ? ~(size_t)0 : 0);
+}
+
 int winograd_f2x2_debug_filter_operands(const void* packed_dev, int K, int C, int mode, int8_t* planes_dev,
                                         int32_t* table_dev, void* hip_stream) {
     if (!packed_dev || !planes_dev || !table_dev || !valid_mode(mode)) return WG_EINVAL;

@@ -734,20 +734,28 @@ hipError_t launch_f2_unpack_filter_planes(const void* blob_v, int8_t* dense, int
     return hipGetLastError();
 }
 
-static bool f2_needs_copy(const Problem& p, int layout) { return layout != WG_NHWC || p.C % 4 != 0; }
-static bool f2_copy_fits(const Problem& p) { return (long long)p.N * p.H * p.W * padded_channels(p.C) <= 0x7fffffffll; }
+static Problem f2_copy(const Problem& p) {
+    Problem padded = p;
+    padded.C = padded_channels(p.C);
+    return padded;
+}
+
+int f2_conv_route(const Problem& p, int layout, size_t scratch_bytes) {
+    if (layout == WG_NHWC && p.C % 4 == 0) return f2_fast_holds(p) ? 1 : 0;
+    return f2_fast_holds(f2_copy(p)) && scratch_bytes >= channels_last_bytes(p) ? 2 : 0;
+}
 
 size_t f2_conv_scratch_wanted(const Problem& p, int layout) {
-    return f2_needs_copy(p, layout) && f2_copy_fits(p) ? channels_last_bytes(p) : 0;
+    return f2_conv_route(p, layout, ~(size_t)0) == 2 ? channels_last_bytes(p) : 0;
 }
 
 hipError_t launch_f2_conv(const int8_t* x, int is_unsigned, int zero_point, const void* blob, int32_t* y, const Problem& p,
                           int layout, int mode, const Int8Epilogue& q8, const Scratch& scratch, hipStream_t s) {
-    if (!f2_needs_copy(p, layout)) return launch_f2_fast(x, is_unsigned, zero_point, blob, y, p, layout, mode, q8, s);
-    if (f2_copy_fits(p) && scratch.bytes >= channels_last_bytes(p)) {
+    const int route = f2_conv_route(p, layout, scratch.bytes);
+    if (route == 1) return launch_f2_fast(x, is_unsigned, zero_point, blob, y, p, layout, mode, q8, s);
+    if (route == 2) {
         int8_t* const copy = static_cast<int8_t*>(scratch.p);
-        Problem padded = p;
-        padded.C = padded_channels(p.C);
+        const Problem padded = f2_copy(p);
         if (hipError_t e = launch_channels_last(x, copy, p, layout, padded.C, is_unsigned ? (uint8_t)zero_point : 0, s)) return e;
         return launch_f2_fast(copy, is_unsigned, zero_point, blob, y, padded, layout, mode, q8, s);
     }

@@ -27,8 +27,8 @@ static_assert(4 * 16 * kRow * 4 <= kPlanesBytes, "staging fits the operand plane
 struct Patch {
     uint32_t first, outside;   // outside: bit a: patch row a lies outside the image, bit 4 + b: column b
     __device__ inline static __amdgpu_buffer_rsrc_t buffer(const int8_t* x, const Problem& p) {
-        const uint32_t before = (uint32_t)(p.W + 1) * (uint32_t)p.C;
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(x) - before, 0, (int)min((uint32_t)(p.N * p.H * p.W * p.C) + before, kOutsideOffset), kRawBufferWord3);
+        const int before = (p.W + 1) * p.C;   // these sums and products fit: f2_fast_holds
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(x) - before, 0, p.N * p.H * p.W * p.C + before, kRawBufferWord3);
     }
     __device__ inline void enter(const Problem& p, int n, int ty, int tx, int c_lane) {
         first = ((uint32_t)(n * p.H + 2 * ty) * (uint32_t)p.W + (uint32_t)(2 * tx)) * (uint32_t)p.C + (uint32_t)c_lane;
@@ -320,6 +320,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
 }
 
 }  // namespace
+
+// The whole offset of a load, from the start of its descriptor, is compared with the descriptor's 32-bit range, and the
+// distance of a pixel from the patch's first one is a signed 32-bit scalar: the tensor together with the row and the pixel
+// before it, and four rows and pixels, have to stay below 2^31.  Tensors of less than 2 GiB exceed that only where an image
+// row is long against the whole (N = H = 1, or within a row of 2 GiB); such calls take the kernel in f2x2_conv.hip, whose
+// addresses are 64-bit.
+bool f2_fast_holds(const Problem& p) {
+    const long long before = (long long)(p.W + 1ll) * p.C, limit = 0x7fffffffll;
+    return (long long)p.N * p.H * p.W * p.C + before <= limit && 4 * before <= limit;
+}
 
 hipError_t launch_f2_fast(const int8_t* x, int is_unsigned, int zero_point, const void* blob, int32_t* y, const Problem& p, int layout,
                           int mode, const Int8Epilogue& q8, hipStream_t s) {

@@ -213,7 +213,11 @@ hipError_t launch_f2_conv_act_scaled(const int8_t* x, const void* blob, int32_t*
 hipError_t launch_f2_conv(const int8_t* x, int is_unsigned, int zero_point, const void* blob, int32_t* y, const Problem& p,
                           int layout, int mode, const Int8Epilogue& q8, const Scratch& scratch, hipStream_t s);
 size_t f2_conv_scratch_wanted(const Problem& p, int layout);   // for a channels-last copy
-// Channels-last activations with p.C % 4 = 0 (see f2x2_fast.hip).
+// Which kernel such a call runs, given enough scratch memory or none: 0 the four-wave kernel of f2x2_conv.hip, 1 the one of
+// f2x2_fast.hip, 2 the same on a channels-last copy.
+int f2_conv_route(const Problem& p, int layout, size_t scratch_bytes);
+// Channels-last activations with p.C % 4 = 0 for which f2_fast_holds(p) (see f2x2_fast.hip).
+bool f2_fast_holds(const Problem& p);
 hipError_t launch_f2_fast(const int8_t* x, int is_unsigned, int zero_point, const void* blob, int32_t* y, const Problem& p, int layout,
                           int mode, const Int8Epilogue& q8, hipStream_t s);
 

@@ -200,3 +200,36 @@ def test_tile_decode_by_multiply_and_shift_matches_division(lib):
             ty, tx = divmod(rem, TW)
             assert (out[0], out[1], out[2]) == (n, ty, tx), (N, H, W, t)
     assert lib.winograd_debug_tile_decode(1, 4, 8, 8, 4, 4, out) == EINVAL      # only 4 tiles
+
+
+def _f2_fast_offsets_hold(N, C, H, W):
+    """The F(2x2,3x3) fast kernel's load offsets in exact integers: a pixel's whole offset (vector part plus scalar part) from a
+    base one row and one pixel before the tensor has to stay inside the descriptor's range, which is at most 2^31 bytes,
+    and the scalar part is a signed 32-bit number."""
+    before = (W + 1) * C
+    farthest = (3 * W + 3) * C + (C - 1) // 64 * 64        # scalar part: patch pixel (3, 3), last channel block
+    last = N * H * W * C - 4 + before                      # the last four channels of the tensor
+    return farthest < 2 ** 31 and last + 4 <= min(N * H * W * C + before, 2 ** 31)
+
+
+@pytest.mark.parametrize("N,C,H,W", [
+    (1, 512, 1, 3_000_000), (1, 512, 1, 2_097_150), (1, 512, 1, 2_097_152), (1, 512, 1, 1_048_574), (1, 512, 1, 1_048_577),
+    (2, 512, 1, 1_398_101), (1, 64, 3, 11_184_810), (1, 896, 2, 1_198_371), (1, 16, 1, 60_000_000), (37, 512, 336, 336), (38, 512, 332, 332),
+    (1, 16, 1, 1), (8, 64, 56, 56), (256, 64, 112, 112)])
+def test_f2x2_fast_kernel_only_where_its_offsets_hold(lib, N, C, H, W):
+    K = 1
+    route = lib.winograd_f2x2_debug_route
+    assert N * C * H * W < 2 ** 31
+    got = route(N, C, H, W, K, wg.NHWC, 0)
+    assert got in (0, 1)
+    if got == 1:
+        assert _f2_fast_offsets_hold(N, C, H, W)
+    else:   # what is turned away is large: nothing ordinary loses the fast kernel
+        assert N * H * W * C + 4 * (W + 1) * C > 2 ** 31
+    for layout, channels in ((wg.NCHW, C), (wg.NCHW, C - 1), (wg.NHWC, C - 1)):
+        padded = 4 if channels <= 4 else (channels + 15) // 16 * 16
+        with_memory, without = route(N, channels, H, W, K, layout, 1), route(N, channels, H, W, K, layout, 0)
+        assert without == 0 and with_memory in (0, 2)
+        if with_memory == 2:
+            assert N * H * W * padded < 2 ** 31 and _f2_fast_offsets_hold(N, padded, H, W)
+    assert route(N, C, H, W, K, 7, 0) == EINVAL and route(0, C, H, W, K, 0, 0) == EINVAL

@@ -298,3 +298,22 @@ def test_int8_epilogue_full_size_cfg3():
     assert torch.equal(q, wg.requant_relu_pool_int8(y32, shift, True, True, wg.NHWC))
     want = oracle.requant_relu_pool(oracle.direct_conv2d(x[:1], g), shift, True, True)
     assert np.array_equal(wl.from_nhwc(q[:1].cpu().numpy()), want)
+
+
+@pytest.mark.parametrize("layout,C", [(wg.NHWC, 512), (wg.NHWC, 510)])
+def test_rows_too_long_for_32_bit_offsets(layout, C):
+    """One row of 2.1 million pixels, 1.07 GB: the tensor and the row before it exceed 2^31 bytes.  A pixel of the output
+    depends on its neighbours only, so windows at both ends and across the middle equal the same call on a crop."""
+    W, K = 2_100_000, 8
+    assert wg.load_library().winograd_f2x2_debug_route(1, C, 1, W, K, layout, 1) == 0
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(72)
+    x = torch.randint(-128, 128, (1, 1, W, C), dtype=torch.int8, device="cuda", generator=gen)
+    w = torch.randint(-128, 128, (K, 3, 3, C), dtype=torch.int8, device="cuda", generator=gen)
+    for mode in (wg.LOSSLESS, wg.SCALED):
+        packed = wg.f2x2_filter_transform(w, layout, mode)
+        y = wg.f2x2_conv2d_int8(x, packed, layout)
+        for first, last in ((0, 200), (1_048_500, 1_048_700), (W - 200, W)):
+            crop = wg.f2x2_conv2d_int8(x[:, :, first:last].contiguous(), packed, layout)
+            inner = slice(0 if first == 0 else 2, 200 if last == W else 198)
+            assert torch.equal(y[:, :, first:last][:, :, inner], crop[:, :, inner])
