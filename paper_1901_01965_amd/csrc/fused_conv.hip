@@ -496,8 +496,9 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
         if (!plan.copies) return plan;
         left -= channels_last_bytes(p);
     }
+    // a test hook asks for one kernel (lossless mode: the split is the limb-pair form as well)
     const bool hooked = g_stream_workgroups.load(std::memory_order_relaxed) > 0 || g_stream_variant.load(std::memory_order_relaxed) != 0 ||
-                        g_scaled_variant.load(std::memory_order_relaxed) != 0;
+                        g_scaled_variant.load(std::memory_order_relaxed) != 0 || (mode == WG_LOSSLESS && lossless_variant() != 0);
     const int workgroups = ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters);
     if (p.CB >= 2 && 2 * workgroups <= compute_units() && !is_unsigned && !hooked) {
         const int blocks = ceil_div(p.CB, std::min(p.CB, compute_units() / workgroups)), splits = ceil_div(p.CB, blocks);

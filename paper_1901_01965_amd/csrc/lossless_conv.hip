@@ -689,9 +689,10 @@ extern "C" int winograd_debug_set_stamps(void* dev_ptr) {
 #endif
 
 void set_lossless_variant(int v) { g_lossless_variant.store(v, std::memory_order_relaxed); }
+int lossless_variant() { return g_lossless_variant.load(std::memory_order_relaxed); }
 
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout) {
-    const int v = g_lossless_variant.load(std::memory_order_relaxed);
+    const int v = lossless_variant();
     const bool applies = layout == WG_NHWC && p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0;
     if (v == 2 || !applies) return 0;
     return v == 1 ? 2 : 1;

@@ -277,6 +277,7 @@ hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t*
 // 0: this form does not apply (layout) or is switched off, 1: applies, the dispatcher decides, 2: forced by the test hook
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout);
 void set_lossless_variant(int v);
+int lossless_variant();
 // The same form with the channel blocks dealt to `splits` workgroups each: leaves 16 x outputs as int32
 // [splits][16 ceil(T/16)][16][Kp], which launch_sums_finish adds and stores.
 hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s);

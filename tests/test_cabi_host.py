@@ -233,3 +233,23 @@ def test_f2x2_fast_kernel_only_where_its_offsets_hold(lib, N, C, H, W):
         if with_memory == 2:
             assert N * H * W * padded < 2 ** 31 and _f2_fast_offsets_hold(N, padded, H, W)
     assert route(N, C, H, W, K, 7, 0) == EINVAL and route(0, C, H, W, K, 0, 0) == EINVAL
+
+
+@pytest.mark.parametrize("hook,value,modes", [
+    ("lossless_variant", 1, (wg.LOSSLESS,)), ("lossless_variant", 2, (wg.LOSSLESS,)), ("scaled_variant", 1, (0, 1)), ("scaled_variant", 2, (0, 1)),
+    ("stream_variant", 1, (0, 1)), ("stream_variant", 2, (0, 1)), ("stream_variant", 3, (0, 1)), ("stream_workgroups", 2, (0, 1))])
+def test_a_forced_form_runs_in_one_kernel(lib, hook, value, modes):
+    """The channel blocks of a deep layer with few tiles are dealt to several workgroups, which takes scratch memory; a test
+    hook that asks for a form, or for never the limb-pair form (which the lossless split is), gets one kernel without."""
+    wanted = lib._ZN2wg20conv2d_scratch_bytesEiiiiiiii    # what the extension asks before such a call
+    wanted.restype, wanted.argtypes = ctypes.c_size_t, [ctypes.c_int] * 8
+    sizes = lambda: [wanted(1, 512, 14, 14, 64, wg.NHWC, mode, 0) for mode in (wg.LOSSLESS, wg.SCALED)]
+    by_itself = sizes()
+    assert min(by_itself) > 0
+    try:
+        getattr(binding, hook)(value)
+        forced = sizes()
+    finally:
+        getattr(binding, hook)(0)
+    assert forced == [0 if mode in modes else by_itself[mode] for mode in (wg.LOSSLESS, wg.SCALED)]
+    assert sizes() == by_itself
