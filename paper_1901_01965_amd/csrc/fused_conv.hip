@@ -451,6 +451,16 @@ __global__ __launch_bounds__(256) void fused_conv_act_scaled_kernel(const int8_t
     store_staged<LAYOUT, false, true>(sc, p, Int8Epilogue{}, k0);
 }
 
+template <int LAYOUT, int LOAD>
+hipError_t launch_act_scaled(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, int32_t* y, int32_t* act_table, const Problem& p,
+                             hipStream_t s) {
+    static LdsLimitOnce lds_limit;   // per template instance
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_act_scaled_kernel<LAYOUT, LOAD>), kActLdsBytes)) return e;
+    dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / kFusedFilters);
+    fused_conv_act_scaled_kernel<LAYOUT, LOAD><<<grid, 256, kActLdsBytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, act_table, p);
+    return hipGetLastError();
+}
+
 template <int LAYOUT, int LOAD, int MODE, bool SUMS>
 hipError_t launch_u8(const int8_t* x, ZeroPointU8 zero, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p,
                      hipStream_t s) {
@@ -693,17 +703,10 @@ hipError_t launch_fused_conv_act_scaled(const int8_t* x, const void* blob, int32
             return status;
         }
     }
-    dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / kFusedFilters);
-    auto go = [&](auto kernel) -> hipError_t {
-        static LdsLimitOnce lds_limit;   // per kernel: the lambda's body is instantiated once per argument type
-        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(kernel), kActLdsBytes)) return e;
-        kernel<<<grid, 256, kActLdsBytes, s>>>(x, b, bl.table_off, bl.planes_off, y, act_table, p);
-        return hipGetLastError();
-    };
     if (layout == WG_NHWC && p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0)
-        return go(&fused_conv_act_scaled_kernel<WG_NHWC, kLoadDwords>);
-    if (layout == WG_NHWC) return go(&fused_conv_act_scaled_kernel<WG_NHWC, kLoadBytes>);
-    return go(&fused_conv_act_scaled_kernel<WG_NCHW, kLoadBytes>);
+        return launch_act_scaled<WG_NHWC, kLoadDwords>(x, b, bl, y, act_table, p, s);
+    if (layout == WG_NHWC) return launch_act_scaled<WG_NHWC, kLoadBytes>(x, b, bl, y, act_table, p, s);
+    return launch_act_scaled<WG_NCHW, kLoadBytes>(x, b, bl, y, act_table, p, s);
 }
 
 hipError_t launch_fused_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p, int layout, int mode,

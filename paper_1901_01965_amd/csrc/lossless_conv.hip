@@ -720,7 +720,7 @@ hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, 
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
     const dim3 grid(ceil_div(p.T, kTileBlock), p.Kp / kBlockFilters, splits);
     auto go = [&](auto kernel, auto&) -> hipError_t {
-        static LdsLimitOnce lds_limit;   // per kernel: the lambda's body is instantiated once per argument type
+        static LdsLimitOnce lds_limit;   // per kernel: the second argument's type tells the two apart, whose pointers are of one type
         constexpr int lds_bytes = kPlanesBytes + 4 * kRawQuad;
         if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(kernel), lds_bytes)) return e;
         kernel<<<grid, 64 * kWaves, lds_bytes, s>>>(x, static_cast<const uint8_t*>(blob), bl.planes_off, sums, p, blocks);
