@@ -631,41 +631,42 @@ __device__ __forceinline__ void store_staged(const StoreContext& sc, const Probl
     }
 }
 
-// Product phase of the role-specialised kernel: the same arithmetic as ProductPhase / ScaledSums
-// without their software pipelining (one set of fragments and accumulators, an eight-deep filter
-// ring), because a product wave there has 256 registers and its waits are covered by the
-// transform wave on the same SIMD.
-// AHEAD: the activation fragments of the next entry are asked for before the current entry's
-// matrix-core instructions (a second set of fragment registers), for callers whose product waves
-// are the longer chain of the two roles.
-// PIPE: an entry's vector work runs beside the next entry's matrix-core instructions (a second set of accumulators).
-template <int MODE, int HALF, bool SUMS, int RING = 8, bool AHEAD = false, bool PIPE = false>
+// Product phase of the role-specialised kernels: the same arithmetic as ProductPhase / ScaledSums in the registers a product
+// wave has there, with a filter ring of RING fragments.
+//   Half of the entries (lossless mode only): channel sums of the joined values; one set of fragments and accumulators, no
+//   software pipelining: such a wave's waits are covered by the other waves of its SIMD.
+//   Every entry (kAllRows, either mode; scaled: one channel block): each block's products go through to the outputs at once.
+//   These waves are the longer chain of the two roles, so the activation fragments of the next entry are asked for before
+//   the current entry's matrix-core instructions, and an entry's vector work runs beside the next entry's matrix-core
+//   instructions (a second set of fragments and of accumulators).
+template <int MODE, int HALF, int RING>
 struct LeanProducts {
-    // scaled mode with joined channel sums, or in a wave that owns every entry: complex entries without the -Wi plane
-    static constexpr int PM = MODE == WG_SCALED && (SUMS || HALF == kAllRows) ? kScaledTwoPlanes : MODE;
+    static constexpr bool WHOLE = HALF == kAllRows;
+    static_assert(WHOLE || MODE == WG_LOSSLESS, "scaled mode keeps its channel sums in ChainedSums or ResidentScaled");
+    static constexpr int PM = MODE == WG_SCALED ? kScaledTwoPlanes : MODE;   // complex entries without the -Wi plane
     using Phase = ProductPhase<PM, HALF>;
+    using Target = std::conditional_t<WHOLE, v4i (&)[16], v4i*>;   // the outputs, or the channel sums in ScaledSums' order
     static constexpr int NE = Phase::NE, NB = Phase::NB;
-    static constexpr int kRing = RING;
-    static constexpr int kSums = SUMS ? ScaledSums<HALF>::kSums : 1;   // 18 per half, 36 for a wave that owns every entry
-    v4i ring[kRing];
+    static constexpr int kSums = ScaledSums<HALF>::kSums;
+    static_assert(NB >= RING, "the ring is full from the first channel block on");
+    v4i ring[RING];
 
     __device__ inline void prefetch(const LaneContext& cx) {
-        static_for<(NB < kRing ? NB : kRing)>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
+        static_for<RING>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
     }
 
-    // sums: the channel sums of ScaledSums (SUMS), else unused; Y: the outputs (not SUMS)
-    __device__ inline void run(const LaneContext& cx, v4i* sums, v4i (&Y)[16]) {
+    __device__ inline void run(const LaneContext& cx, Target to) {
         v4i er[6], ei[6];
-        v4i afr2[AHEAD ? 2 : 1][4];
-        if constexpr (AHEAD)
+        v4i afr2[WHOLE ? 2 : 1][4];
+        if constexpr (WHOLE)
             static_for<num_a<PM>(half_slot(HALF, 0).entry)>([&](auto I) { afr2[0][I] = Phase::template load_a<0, I>(cx); });
         // the matrix-core part of slot S: activation fragments, products into acc, refill of the filter ring
         auto multiply = [&](auto S, v4i (&acc)[9]) {
             constexpr int s = S;
             constexpr int entry = half_slot(HALF, s).entry;
             constexpr int b0 = b_start<PM>(HALF, s);
-            v4i (&afr)[4] = afr2[AHEAD ? (s & 1) : 0];
-            if constexpr (!AHEAD) {
+            v4i (&afr)[4] = afr2[WHOLE ? (s & 1) : 0];
+            if constexpr (!WHOLE) {
                 static_for<num_a<PM>(entry)>([&](auto I) { afr[I] = Phase::template load_a<s, I>(cx); });
             } else if constexpr (s + 1 < NE) {
                 static_for<num_a<PM>(half_slot(HALF, s + 1).entry)>(
@@ -674,78 +675,70 @@ struct LeanProducts {
             static_for<num_ops<PM>(entry)>([&](auto I) {
                 constexpr Op op = entry_op<PM>(entry, I);
                 constexpr v4i zero = {0, 0, 0, 0};
-                acc[op.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(afr[op.a], ring[(b0 + op.b) % kRing],
+                acc[op.acc] = __builtin_amdgcn_mfma_i32_16x16x64_i8(afr[op.a], ring[(b0 + op.b) % RING],
                                                                     op.init ? zero : acc[op.acc], 0, 0, 0);
             });
             static_for<num_b<PM>(entry)>([&](auto I) {
-                if constexpr (b0 + I + kRing < NB) ring[(b0 + I) % kRing] = Phase::template load_b<b0 + I + kRing>(cx);
+                if constexpr (b0 + I + RING < NB) ring[(b0 + I) % RING] = Phase::template load_b<b0 + I + RING>(cx);
             });
         };
-        // the vector part of slot S: limbs joined; then into the channel sums, or reverse scaling and output transform
+        // the vector part of slot S: limbs joined (Re = Dr Wr - Di Wi, Im = Dr Wi + Di Wr); then into the channel sums, or
+        // reverse scaling and output transform
         auto reduce = [&](auto S, const v4i (&acc)[9]) {
             constexpr int s = S;
             constexpr Slot sl = half_slot(HALF, s);
             constexpr int entry = sl.entry;
-            if constexpr (SUMS) {
-                // joined values only; scaling (scaled mode) and the output transform wait for finish()
+            if constexpr (!WHOLE) {   // the output transform waits for finish_lossless()
                 constexpr int v = ScaledSums<HALF>::sum_start(s);
-                if constexpr (MODE == WG_SCALED) {   // Re = Dr Wr - Di Wi,  Im = Dr Wi + Di Wr
-                    if constexpr (is_real(entry)) {
-                        sums[v] += (acc[0] << kByteLimbShift) + acc[1];
-                    } else {
-                        sums[v] += ((acc[0] - acc[4]) << kByteLimbShift) + (acc[1] - acc[5]);
-                        sums[v + 1] += (acc[2] << kByteLimbShift) + acc[3];
-                    }
-                } else if constexpr (is_real(entry)) {
-                    sums[v] += join_limbs(acc[0], acc[1], acc[2]);
+                if constexpr (is_real(entry)) {
+                    to[v] += join_limbs(acc[0], acc[1], acc[2]);
                 } else {
-                    sums[v] += join_limbs(acc[0] - acc[3], acc[1] - acc[4], acc[2] - acc[5]);
-                    sums[v + 1] += join_limbs(acc[6], acc[7], acc[8]);
+                    to[v] += join_limbs(acc[0] - acc[3], acc[1] - acc[4], acc[2] - acc[5]);
+                    to[v + 1] += join_limbs(acc[6], acc[7], acc[8]);
                 }
-                asm volatile("" : "+v"(sums[v]));   // here, not in front of the next use of the sums with the limbs alive until then
-                if constexpr (!is_real(entry)) asm volatile("" : "+v"(sums[v + 1]));
+                asm volatile("" : "+v"(to[v]));   // here, not in front of the next use of the sums with the limbs alive until then
+                if constexpr (!is_real(entry)) asm volatile("" : "+v"(to[v + 1]));
             } else {
                 v4i re, im = {0, 0, 0, 0};
                 if constexpr (MODE == WG_LOSSLESS) {
                     if constexpr (is_real(entry)) {
                         re = join_limbs(acc[0], acc[1], acc[2]);
-                    } else {   // Re = Dr Wr - Di Wi,  Im = Dr Wi + Di Wr
+                    } else {
                         re = join_limbs(acc[0] - acc[3], acc[1] - acc[4], acc[2] - acc[5]);
                         im = join_limbs(acc[6], acc[7], acc[8]);
                     }
                 } else {
-                    if constexpr (is_real(entry)) re = (acc[0] << kByteLimbShift) + acc[1];
-                    else if constexpr (PM == kScaledTwoPlanes) re = ((acc[0] - acc[4]) << kByteLimbShift) + (acc[1] - acc[5]);
-                    else re = (acc[0] << kByteLimbShift) + acc[1];
-                    if constexpr (!is_real(entry)) im = (acc[2] << kByteLimbShift) + acc[3];
-                    // Section 4.2 (a wave that owns every entry exists only where the factors were parked)
-                    const ReverseScale unscale = HALF == kAllRows ? parked_scale<s>(cx) : ReverseScale(cx.table_k[entry]);
+                    if constexpr (is_real(entry)) {
+                        re = (acc[0] << kByteLimbShift) + acc[1];
+                    } else {
+                        re = ((acc[0] - acc[4]) << kByteLimbShift) + (acc[1] - acc[5]);
+                        im = (acc[2] << kByteLimbShift) + acc[3];
+                    }
+                    const ReverseScale unscale = parked_scale<s>(cx);   // Section 4.2
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         re[q] = unscale(re[q]);
                         if constexpr (!is_real(entry)) im[q] = unscale(im[q]);
                     }
                 }
-                place_entry<HALF, s, MODE != WG_SCALED>(re, im, er, ei, Y);   // scaled mode: one channel block, these are the outputs' first values
-                if constexpr (HALF == kAllRows) {
-                    // Pins the entry's value, and a finished row's outputs, to this place.  Left alone, the compiler moves
-                    // the vector work of all 26 entries behind the last matrix-core instruction (into the block that
-                    // stages the outputs) and keeps every accumulator alive until then.
+                place_entry<HALF, s, MODE != WG_SCALED>(re, im, er, ei, to);   // scaled mode: one channel block, these are the outputs' first values
+                // Pins the entry's value, and a finished row's outputs, to this place.  Left alone, the compiler moves
+                // the vector work of all 26 entries behind the last matrix-core instruction (into the block that
+                // stages the outputs) and keeps every accumulator alive until then.
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        asm volatile("" ::"v"(re[q]));
-                        if constexpr (!is_real(entry)) asm volatile("" ::"v"(im[q]));
-                    }
-                    if constexpr (sl.last_in_row) {
+                for (int q = 0; q < 4; ++q) {
+                    asm volatile("" ::"v"(re[q]));
+                    if constexpr (!is_real(entry)) asm volatile("" ::"v"(im[q]));
+                }
+                if constexpr (sl.last_in_row) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i)
+                    for (int i = 0; i < 16; ++i)
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) asm volatile("" ::"v"(Y[i][q]));
-                    }
+                        for (int q = 0; q < 4; ++q) asm volatile("" ::"v"(to[i][q]));
                 }
             }
         };
-        if constexpr (PIPE) {
+        if constexpr (WHOLE) {
             // slot s + 1's matrix-core instructions are issued before slot s's vector work, which then runs beside them
             v4i acc2[2][9];
             static_for<NE + 1>([&](auto S) {
@@ -763,7 +756,7 @@ struct LeanProducts {
         }
     }
 
-    // SUMS, lossless mode, after the last channel block: the output transform of the channel sums
+    // Half of the entries, after the last channel block: the output transform of the channel sums
     // (it is linear, so it may as well run once on the sums as once per block).
     __device__ inline static void finish_lossless(const v4i* sums, v4i (&Y)[16]) {
         v4i er[6], ei[6];
@@ -780,14 +773,10 @@ struct LeanProducts {
 
 // Lossless mode with joined channel sums (20 and 16 per half).
 template <int HALF, int RING>
-struct LosslessSums : LeanProducts<WG_LOSSLESS, HALF, true, RING> {
-    using Lean = LeanProducts<WG_LOSSLESS, HALF, true, RING>;
+struct LosslessSums : LeanProducts<WG_LOSSLESS, HALF, RING> {
+    using Lean = LeanProducts<WG_LOSSLESS, HALF, RING>;
     using Lean::kSums;
     __device__ inline void enter(LaneContext& cx, int8_t*, int) { Lean::prefetch(cx); }
-    __device__ inline void run(const LaneContext& cx, v4i* sums) {
-        v4i unused[16];
-        Lean::run(cx, sums, unused);
-    }
     __device__ inline static void finish(const LaneContext&, const v4i* sums, v4i (&Y)[16]) { Lean::finish_lossless(sums, Y); }
 };
 // One object for a wave of either half.  (The two empty statements differ, so that the compiler does not join the ends of

@@ -224,7 +224,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
     };
     if constexpr (FORM == kStreamWhole) {
         // filter ring: lossless mode has twice the fragments per entry and the registers for twelve in flight
-        LeanProducts<MODE, kAllRows, false, MODE == WG_SCALED ? 8 : 12, true, true> all;
+        LeanProducts<MODE, kAllRows, MODE == WG_SCALED ? 8 : 12> all;
         v4i Y[16];
         int cb = 0;
         cx.b_glob = b_wave;
@@ -243,8 +243,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             published();
             WG_SPENT(0, mark);   // barrier U
             cx.a_lds = lds + (u & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
-            v4i unused[1];
-            all.run(cx, unused, Y);
+            all.run(cx, Y);
             WG_SPENT(1, mark);   // products
             const bool last = cb == p.CB - 1;
             cb = last ? 0 : cb + 1;
