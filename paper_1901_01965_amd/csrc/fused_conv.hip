@@ -604,8 +604,13 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
     // Several channel blocks and several tile blocks for every workgroup (scaled mode: three): the streaming kernel with eight
     // product waves.  Scaled: 112x112x128 N = 16 69.4 -> 65.2 us, 56x56x256 61.7 -> 59.4; with two tile blocks per workgroup it
     // is 2-5 % behind the form below (28x28x128 N = 64 23.0 -> 24.2).  Lossless: 56x56x256 N = 16 84.2 -> 75.9, 112x112x128
-    // 78.7 -> 74.5, 28x28x128 N = 64 27.1 -> 26.2.
-    const bool long_streams = p.CB >= 2 && wide_grid > (mode == WG_SCALED ? 2LL : 1LL) * compute_units();
+    // 78.7 -> 74.5, 28x28x128 N = 64 27.1 -> 26.2.  Not with channel-major int32 outputs, which are written in 64-byte rows of 32
+    // planes and spill registers here (stream_kernel.h).  Scaled, the form below against this one: 56x56x256 N = 16 81.2 us
+    // against 87.7, 112x112x128 N = 16 98.9 / 105.4 (uint8 99.5 / 114.4), 56x56x128 N = 32 60.0 / 67.4 (uint8 60.5 / 73.0); lossless,
+    // whole entries: 96.9 / 102.3, 97.8 / 113.7 (99.2 / 114.4), 62.0 / 69.4 (62.8 / 69.7), and 28x28x128 N = 64 (the form below)
+    // 38.7 / 41.1.  Channel-major int8 outputs are level or ahead here (scaled 72.6 against 76.6, 87.3 / 89.6, 56.3 / 56.1).
+    const bool planes32 = c.layout == WG_NCHW && c.q8.out == nullptr;
+    const bool long_streams = p.CB >= 2 && !planes32 && wide_grid > (mode == WG_SCALED ? 2LL : 1LL) * compute_units();
     if (stream_variant == 3 || (stream_variant == 0 && variant == 0 && !forced_stream && long_streams)) {
         status = launch_stream(c, mode, kStreamEight, s);
         return true;
