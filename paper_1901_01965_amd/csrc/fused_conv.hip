@@ -682,7 +682,14 @@ hipError_t launch_fused_conv_u8(const uint8_t* x_u8, int zero_point, const void*
 }
 
 // With scratch memory: factors first, then a role-specialised kernel (act_scaled_conv.hip), through a channels-last copy where
-// the layout asks for one.  Without: both passes in the four-wave kernel.
+// the layout asks for one.  Without: both passes in the four-wave kernel.  So, too, where that reads the activations as they
+// are, its 32-filter grid is a single round of the compute units and it has at most two channel blocks: what the two
+// kernels save there is less than a launch (a grid of one round, one block 11.5 - 13 us in one kernel, 15 - 16.5 in two, two
+// blocks 16.4 / 17.8, three 21 / 20; one block and 1.2 - 1.5 rounds 23 / 19).
+static bool one_act_scaled_kernel(const Problem& p, int layout) {
+    return layout == WG_NHWC && p.C % 4 == 0 && p.CB <= 2 && (long long)ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters) <= compute_units();
+}
+
 static Plan plan_act_scaled(const Problem& p, int layout, size_t scratch_bytes) {
     Plan plan = {false, 1, p.CB};
     if (layout != WG_NHWC || p.C % 4 != 0)
@@ -691,6 +698,7 @@ static Plan plan_act_scaled(const Problem& p, int layout, size_t scratch_bytes) 
 }
 
 size_t act_scaled_scratch_wanted(const Problem& p, int layout) {
+    if (one_act_scaled_kernel(p, layout)) return 0;
     return (plan_act_scaled(p, layout, ~(size_t)0 >> 1).copies ? channels_last_bytes(p) : 0) + act_factor_bytes(p);
 }
 
@@ -698,7 +706,7 @@ hipError_t launch_fused_conv_act_scaled(const int8_t* x, const void* blob, int32
                                         int layout, const Scratch& scratch, hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
-    if (scratch.bytes >= act_scaled_scratch_wanted(p, layout)) {
+    if (!one_act_scaled_kernel(p, layout) && scratch.bytes >= act_scaled_scratch_wanted(p, layout)) {
         RolesCall c = {x, nullptr, b, bl, y, p, layout, no_int8_epilogue()};
         int32_t* rest;
         hipError_t status;

@@ -84,7 +84,10 @@ def test_mismatched_filters_leave_the_output_untouched_with_split_channels():
 
 
 @pytest.mark.parametrize("layout", [wg.NCHW, wg.NHWC])
-@pytest.mark.parametrize("shape", [(1, 5, 33, 7, 6), (2, 130, 65, 10, 9), (40, 64, 160, 14, 14), (1, 896, 20, 4, 5)])
+@pytest.mark.parametrize("shape", [(1, 5, 33, 7, 6), (2, 130, 65, 10, 9), (40, 64, 160, 14, 14), (1, 896, 20, 4, 5),
+                                   # one round of workgroups and a little more, one and two channel blocks: both sides of the
+                                   # rule that keeps the two passes in one kernel
+                                   (32, 64, 250, 16, 16), (33, 64, 250, 16, 16), (43, 100, 150, 14, 13), (32, 128, 256, 15, 14), (2, 192, 33, 9, 9)])
 def test_both_sides_scaled_with_and_without_scratch(shape, layout):
     """32 and 64 filters per workgroup, one to fourteen channel blocks, against the oracle; the C ABI's entry point has no
     scratch memory and runs both passes in one kernel."""
