@@ -129,6 +129,13 @@ def test_calls_run_without_the_memory_they_would_like_and_outputs_without_memory
     torch.cuda.empty_cache()
     try:
         torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / torch.cuda.get_device_properties(0).total_memory)
+        held = []   # what the allocator holds in reserve from earlier work, in pieces down to 2 MB
+        for mb in (1024, 256, 64, 16, 4, 2):
+            try:
+                while True:
+                    held.append(torch.empty(mb << 20, dtype=torch.uint8, device="cuda"))
+            except torch.cuda.OutOfMemoryError:
+                pass
         for (_, call), out in zip(calls, outs):
             call(out)
         for _, call in calls:
