@@ -2,10 +2,10 @@
 // multiplications per 4x4 output tile and channel pair that Section 3.4 compares
 // against:  y[n,k,h,w] = sum_{c,a,b} x[n,c,h+a-1,w+b-1] g[k,c,a,b].
 // Serves as the on-device cross-check and the direct baseline.  Where scratch memory (or the layout) allows, the
-// matrix product over linear pixels in direct_gemm.hip runs; this file has what is left for calls without scratch memory and
-// for rows too long for that kernel's LDS: channels-last tensors with K % 4 == 0 and a 16-byte aligned output on the matrix
-// cores by patches (operands are staged with 16-byte loads when C % 16 == 0 and the pointers allow it, else byte by byte),
-// everything else in the plain kernel; and the requantisation kernels.
+// matrix product over linear pixels in direct_gemm.hip runs; this file has what is left for calls without scratch memory,
+// for rows too long for that kernel's LDS and for deep layers of few pixels (see few_patches): channels-last tensors with
+// K % 4 == 0 and a 16-byte aligned output on the matrix cores by patches (operands are staged with 16-byte loads when
+// C % 16 == 0 and the pointers allow it, else byte by byte), everything else in the plain kernel; and the requantisation kernels.
 #include "wg_internal.h"
 
 namespace wg {
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void requant_kernel(const int32_t* __restrict_
 }
 // 2x2 stride-2 maximum, four outputs per thread: four channels of a pixel (channels-last, K % 4 = 0: `run` = K, four 16-byte
 // loads) or four pixels of a row (channel-major, (W / 2) % 4 = 0: two rows of eight values).  256 -> 256 outputs at 56x56,
-// N = 16: 17 us with one thread and four 4-byte loads per output, 11 us so.
+// N = 16: 17 us with one thread and four 4-byte loads per output, 8.8 us so (58 MB).
 template <int LAYOUT>
 __global__ __launch_bounds__(256) void requant_pool4_kernel(const int32_t* __restrict__ y, int8_t* __restrict__ out, uint32_t quads, int run,
                                                             int W, FastDiv div_run4, FastDiv div_wo, int shift, int lo) {
@@ -274,12 +274,24 @@ DirectPlan plan_direct(const Problem& p, int layout, bool operands_aligned) {
 
 }  // namespace
 
+// Deep layers of few pixels: a workgroup of the linear-pixel kernel takes 1.8 - 2.0 us per 64 channels (three stages, each
+// with a barrier and a wait for its taps), one of the patch kernel, which loads all nine taps of a block at once, 1.5 - 1.6, and
+// with fewer workgroups than the chip holds that is the layer's time (1x14x14, 512 -> 512: 16.4 us by patches, 19.6 by linear
+// pixels; 8x56x56, 256 -> 64: 12.3 / 12.9).  Beyond that the linear-pixel kernel's rate counts.  The lines, in patch workgroups
+// per compute unit, by patches / by linear pixels: four channel blocks or more, 1.5: 26.9 / 28.3 us and 16.5 / 17.7, 1.75: 16.9 / 16.6
+// and 26.9 / 28.0, 2: 28.5 / 26.5; two or three, 0.56: 7.8 / 8.1, 0.88: 8.7 / 8.5, 1: 8.7 / 8.3.  One block: level.
+bool few_patches(const Problem& p) {
+    const long long patches = (long long)p.N * ceil_div(p.H, kPatchRows) * ceil_div(p.W, kPatchCols) * ceil_div(p.K, kDirectFilters);
+    return p.CB >= 4 ? 8 * patches <= 13LL * compute_units() : p.CB >= 2 && 4 * patches <= 3LL * compute_units();
+}
+
 size_t direct_conv_scratch_wanted(const Problem& p, int layout) { return plan_direct(p, layout, true).bytes; }
 
 hipError_t launch_direct_conv(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, int layout,
                               const Scratch& scratch, hipStream_t s) {
+    const bool vectors = p.C % 16 == 0 && aligned16(x) && aligned16(w), by_patches = layout == WG_NHWC && p.K % 4 == 0 && aligned16(y);
     const DirectPlan d = plan_direct(p, layout, aligned16(x) && aligned16(w));
-    if (d.applies && d.bytes <= scratch.bytes) {
+    if (d.applies && d.bytes <= scratch.bytes && !(by_patches && vectors && few_patches(p))) {
         if (d.copy_x) {
             int8_t* const xs = static_cast<int8_t*>(scratch.p);
             int8_t* const ws = xs + d.x_bytes;
@@ -291,10 +303,10 @@ hipError_t launch_direct_conv(const int8_t* x, const int8_t* w, int32_t* y, cons
         }
         return launch_direct_gemm(x, w, y, d.padded, layout, s);
     }
-    if (layout == WG_NHWC && p.K % 4 == 0 && aligned16(y)) {
+    if (by_patches) {
         const int patches_h = ceil_div(p.H, kPatchRows), patches_w = ceil_div(p.W, kPatchCols);
         dim3 grid((unsigned)(p.N * patches_h * patches_w), ceil_div(p.K, kDirectFilters));
-        if (p.C % 16 == 0 && aligned16(x) && aligned16(w))
+        if (vectors)
             direct_conv_mfma_kernel<true><<<grid, 256, 0, s>>>(x, w, y, p, patches_h, patches_w);
         else
             direct_conv_mfma_kernel<false><<<grid, 256, 0, s>>>(x, w, y, p, patches_h, patches_w);

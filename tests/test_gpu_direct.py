@@ -44,3 +44,18 @@ def test_requantisation_of_any_int32(shape, layout, pool):
         if pool:
             v = v.reshape(N, K, H // 2, 2, W // 2, 2).max(axis=(3, 5))
         assert np.array_equal(wl.from_nhwc(got) if nhwc else got, v.astype(np.int8))
+
+
+# N, C, K, H, W around the lines between the patch kernel and the linear-pixel kernel (patch workgroups: 3/4 of 256 with two or
+# three channel blocks, 13/8 of 256 with more), and patches that are not full
+@pytest.mark.parametrize("shape", [(96, 128, 128, 8, 16), (97, 128, 128, 8, 16), (16, 176, 36, 19, 50), (104, 256, 256, 7, 16), (105, 256, 200, 8, 15),
+                                   (1, 496, 68, 13, 21), (5, 256, 4, 1, 1)])
+def test_few_patches_of_deep_layers(shape):
+    """Channels-last tensors, which take either kernel by their sizes, against the same layer channel-major, which always runs
+    the linear-pixel kernel, and the first image against the oracle."""
+    N, C, K, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, act="uniform", wgt="uniform", seed=4)
+    got = wg.direct_conv2d_int8(torch.from_numpy(wl.to_nhwc(x)).cuda(), torch.from_numpy(wl.to_krsc(g)).cuda(), wg.NHWC)
+    other = wg.direct_conv2d_int8(torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda(), wg.NCHW)
+    assert torch.equal(got.permute(0, 3, 1, 2), other)
+    assert np.array_equal(other[:1].cpu().numpy(), oracle.direct_conv2d(x[:1], g))
