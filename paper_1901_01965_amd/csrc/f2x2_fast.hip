@@ -163,7 +163,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     v4i sum[kF2Entries];
 #pragma unroll
     for (int e = 0; e < kF2Entries; ++e) sum[e] = (v4i){0, 0, 0, 0};
-    constexpr int kRing = MODE == WG_LOSSLESS ? 2 : 4;   // entries' filter fragments in flight
+    // Entries' filter fragments in flight (one less while an entry multiplies).  Where the fragments miss the L2 (fewer than eight
+    // filter blocks, which every XCD then reads, and few workgroups to share them) a deep layer's time is their latency: lossless,
+    // N = 1, 512 -> 256 at 28x28 32.4 us with two, 25.8 three, 23.3 four, 22.1 five, as many as three waves' registers hold
+    // (166 of 168); 28x28x128 N = 32 18.9 / 17.7 / 18.3 / 18.3.
+    constexpr int kRing = MODE == WG_LOSSLESS ? 5 : 4;
     for (int step = 0; step < p.CB; ++step) {
         const int8_t* const b_cb = b_wave + cb * b_block_stride;
         v4i bf[kRing][NBP];
