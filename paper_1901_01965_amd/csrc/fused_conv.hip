@@ -489,12 +489,18 @@ struct Plan {
 };
 
 // Deep layers with few tiles leave most of the chip idle while a workgroup walks through its channel blocks one after the
-// other.  Dealing the blocks to several workgroups takes a second kernel that adds the splits and finishes.  Measured on
-// single images of 128 .. 512 channels, CB channel blocks, b of them per workgroup (us):
-//   lossless: 4.3 + 2.9 CB in one kernel, 6.5 + 4.5 b split (512 channels at 14x14: 27 -> 11)
-//   scaled:   5.1 + 1.95 CB in one kernel, 10 + 5 b split (36 sums per tile and filter to move instead of 16 outputs)
-bool split_pays(int mode, int CB, int b) {
-    return mode == WG_LOSSLESS ? 4.3 + 2.9 * CB > 6.5 + 4.5 * b : 5.1 + 1.95 * CB > 10.0 + 5.0 * b;
+// other.  Dealing the blocks to several workgroups takes a second kernel that adds the splits and finishes.  CB channel blocks in
+// one workgroup against b in each of W, whose partial sums are written and read (36 per tile and filter in scaled mode, 16
+// otherwise).  Fitted to 330 layers of 128 .. 896 channels and K = 32 .. 512 filters that fill at most half the chip, with filters
+// that are not in the L2, as in a network (us; nine in ten are off by 8 % at most, the choice is 0.2 % from the better one on
+// average, with filters in the L2 as well):
+//   lossless: 5.7 + 2.68 CB in one kernel, 4.8 + 3.27 b + W / 50 + CB K / 2700 split (N = 1, 512 -> 512 at 14x14: 26 - 36, 11.1 - 12.8)
+//   scaled:   5.9 + 1.65 CB in one kernel, 9.1 + 1.92 b + W / 28 split (18 - 24, 16.7 - 17.6; N = 4: 18.4, 21.4)
+// and 3.9 b - 2.2 more where the split kernels cannot read 16-byte pieces (N = 2, 324 -> 512 at 28x28, lossless: 21.6, 32.8).
+bool split_pays(int mode, int CB, int K, int b, int W, bool pieces) {
+    const double one = mode == WG_LOSSLESS ? 5.7 + 2.68 * CB : 5.9 + 1.65 * CB;
+    const double split = mode == WG_LOSSLESS ? 4.8 + 3.27 * b + W / 50.0 + CB * K / 2700.0 : 9.1 + 1.92 * b + W / 28.0;
+    return one > split + (pieces ? 0.0 : 3.9 * b - 2.2);
 }
 
 Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t scratch_bytes) {
@@ -512,7 +518,8 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
     const int workgroups = ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters);
     if (p.CB >= 2 && 2 * workgroups <= compute_units() && !is_unsigned && !hooked) {
         const int blocks = ceil_div(p.CB, std::min(p.CB, compute_units() / workgroups)), splits = ceil_div(p.CB, blocks);
-        if (split_pays(mode, p.CB, blocks) && split_partial_bytes(p, mode, splits) <= left) {
+        const bool pieces = plan.copies ? padded_channels(p.C) % 16 == 0 : p.C % 16 == 0;   // (a caller's view may still start off a boundary)
+        if (split_pays(mode, p.CB, p.Kp, blocks, splits * workgroups, pieces) && split_partial_bytes(p, mode, splits) <= left) {
             plan.splits = splits;
             plan.blocks = blocks;
         }

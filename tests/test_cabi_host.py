@@ -253,3 +253,18 @@ def test_a_forced_form_runs_in_one_kernel(lib, hook, value, modes):
         getattr(binding, hook)(0)
     assert forced == [0 if mode in modes else by_itself[mode] for mode in (wg.LOSSLESS, wg.SCALED)]
     assert sizes() == by_itself
+
+
+@pytest.mark.parametrize("N,C,K,HW,splits", [
+    # channel blocks dealt to this many workgroups (lossless, scaled); 1: one kernel
+    (1, 512, 512, 14, (8, 8)), (1, 512, 512, 28, (4, 1)), (4, 512, 512, 14, (4, 1)), (1, 256, 256, 56, (2, 1)), (2, 256, 512, 28, (1, 1)),
+    (1, 256, 512, 28, (4, 1)), (4, 820, 250, 14, (7, 7)), (2, 324, 512, 28, (1, 1)), (1, 128, 64, 14, (2, 1)), (8, 512, 512, 28, (1, 1))])
+def test_which_layers_deal_their_channel_blocks_to_several_workgroups(lib, N, C, K, HW, splits):
+    """The scratch memory that the extension asks for holds the splits' partial sums: 16 outputs (lossless) or 36 channel sums
+    (scaled) per tile and filter, tiles padded to 16 and filters to 64."""
+    wanted = lib._ZN2wg20conv2d_scratch_bytesEiiiiiiii
+    wanted.restype, wanted.argtypes = ctypes.c_size_t, [ctypes.c_int] * 8
+    tiles = (N * ((HW + 3) // 4) ** 2 + 15) // 16 * 16
+    for mode, sums in ((wg.LOSSLESS, 16), (wg.SCALED, 36)):
+        per_split = sums * tiles * ((K + 63) // 64 * 64) * 4
+        assert wanted(N, C, HW, HW, K, wg.NHWC, mode, 0) == (0 if splits[mode] == 1 else splits[mode] * per_split), mode

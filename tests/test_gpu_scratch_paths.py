@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 # N, C, K, H, W: split channels with one and several blocks per workgroup, a last split that is shorter, a last block that
 # is not full; ragged tiles; K at and around multiples of 4, 16, 32 and 64; images of one to four pixels
-SPLIT = [(1, 512, 40, 14, 14), (1, 320, 96, 8, 10), (1, 896, 31, 6, 6), (2, 500, 65, 4, 14), (1, 448, 512, 14, 9)]
+SPLIT = [(1, 512, 40, 14, 14), (1, 320, 96, 8, 10), (1, 896, 31, 6, 6), (2, 500, 65, 4, 14), (1, 448, 512, 14, 9),
+         (4, 820, 250, 14, 14), (4, 448, 512, 14, 14)]   # (these two: two blocks per workgroup, one in the last)
 COPY = [(2, 5, 7, 9, 11), (1, 130, 33, 3, 5), (3, 67, 66, 1, 1), (2, 64, 100, 1, 3), (1, 3, 64, 10, 6), (2, 31, 130, 21, 20)]
 
 
