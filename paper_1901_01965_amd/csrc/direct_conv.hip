@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void requant_kernel(const int32_t* __restrict_
 }
 // 2x2 stride-2 maximum, four outputs per thread: four channels of a pixel (channels-last, K % 4 = 0: `run` = K, four 16-byte
 // loads) or four pixels of a row (channel-major, (W / 2) % 4 = 0: two rows of eight values).  256 -> 256 outputs at 56x56,
-// N = 16: 17 us with one thread and four 4-byte loads per output, 8.8 us so (58 MB).
+// N = 16: 17 us with one thread and four 4-byte loads per output, 8.8 us so (55 MB).
 template <int LAYOUT>
 __global__ __launch_bounds__(256) void requant_pool4_kernel(const int32_t* __restrict__ y, int8_t* __restrict__ out, uint32_t quads, int run,
                                                             int W, FastDiv div_run4, FastDiv div_wo, int shift, int lo) {

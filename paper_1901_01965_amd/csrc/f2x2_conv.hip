@@ -8,9 +8,12 @@
 // transformed filters 12, so both travel as two int8 limbs v = 64 h + l (l in 0..63); in scaled
 // mode the filters are back in int8 and are a single operand.  Per entry the matrix cores form
 //   lossless: hh, hl + lh, ll  (value = 4096 hh + 64 mid + ll)      scaled: h w, l w  (64 hw + lw)
-// and, unlike in the F(4x4,3x3) kernel, every accumulator of a wave (16 entries x 3) fits its
-// registers for the whole kernel: the matrix cores sum over all input channels and the limbs
-// are joined, unscaled (Section 4.2, scaled mode) and run through A^T . A once, at the end.
+//
+// f2x2_fast.hip has the convolution that runs wherever there are channels-last activations with C % 4 = 0, as given or as a
+// copy in scratch memory.  f2_conv_kernel in this file is left for calls without that memory (the C entry points have none
+// to give) and for tensors whose rows are too long for the other's 32-bit offsets: it reads byte by byte, and keeps every
+// accumulator of a wave (16 entries x 3 or 2) in registers for the whole kernel: the matrix cores sum over all input channels
+// and the limbs are joined, unscaled (Section 4.2, scaled mode) and run through A^T . A once, at the end.
 #include <type_traits>
 #include <utility>
 

@@ -3,11 +3,13 @@
 //
 // What bounds it: latency.  A workgroup of 16 tiles x 64 filters waits for its patch, transforms, waits at a barrier,
 // multiplies, and a layer of 128 channels has two such rounds; with the limb products in accumulators of their own (32 or 48
-// of four registers) two workgroups fit a compute unit and 28x28, 128 -> 128, N = 32 (784 workgroups) took 22 us for 3 us
-// worth of bytes.  Here the limbs are joined block by block: the low products accumulate in the channel sum itself, the
-// others enter it by one shift-and-add per register, which leaves 16 sums per wave: 128 registers, four workgroups per
-// compute unit, so their waits overlap and such a grid is one round.  The reverse-scaling factors are parked in LDS at the
-// start, the blob header is compared only before the store, and pixels outside the image arrive as zeros.
+// of four registers) two workgroups fit a compute unit and 28x28, 128 -> 128, N = 32 (784 workgroups) took 22 us scaled and
+// 31 lossless for 3 us worth of bytes.  Here the limbs are joined block by block: the low products accumulate in the channel
+// sum itself, the others enter it by one shift-and-add per register, which leaves 16 sums per wave: 136 registers in scaled
+// mode, 166 in lossless, so that three workgroups share a compute unit and their waits overlap: 15.5 and 18.3 us.  (128
+// registers and four workgroups were 4-12 % slower.)  The 784 workgroups are 16 more than the chip holds, which cost the last
+// 3.5 of those microseconds: N = 31 takes 12.0 and 13.  The reverse-scaling factors are parked in LDS at the start, the
+// blob header is compared only before the store, and pixels outside the image arrive as zeros.
 #include "kernel_common.h"
 
 namespace wg {
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
         patch.bias(u, enc);
         const Quad bias16 = Bytes::bias11(enc);   // of the 6x6 transform: 16 * bias; here it leaves 4 * bias
         transform<MODE, Bytes>(u, Quad{bias16.a >> (short)2, bias16.b >> (short)2}, put);
-        __builtin_amdgcn_sched_barrier(0);   // the transform's registers are dead: 128 are to do
+        __builtin_amdgcn_sched_barrier(0);   // the transform's registers are dead before the fragments take theirs
         static_for<kRing - 1>([&](auto E) { request_b(E); });
         cb = cb + 1 == p.CB ? 0 : cb + 1;
         if (step + 1 < p.CB) patch.request(xbuf, p, cb, 4 * cq, u);   // travels while this block multiplies

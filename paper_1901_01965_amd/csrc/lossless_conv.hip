@@ -127,7 +127,7 @@ constexpr int kRing = 10;   // filter fragments in flight per wave
 template <int HALF>
 struct Products {
     static constexpr int NS = half_slots(HALF), NF = half_fragments(HALF);
-    // Eight waves share what the compute unit takes in, some 58 bytes per clock, so a wave's 16 to 20 filter
+    // Eight waves share what the compute unit takes in, some 57 bytes per clock, so a wave's 16 to 20 filter
     // fragments per channel block are requested well ahead: the first kRing before the transform, the others each
     // time a ring slot has been used.
     v4i ring[kRing];

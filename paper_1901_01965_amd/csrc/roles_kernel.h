@@ -22,10 +22,11 @@ namespace {
 // pw / 4 of the entries.  Three waves per SIMD leave a wave 168 registers, so in scaled mode the product waves keep the low
 // limbs' chains (ChainedSums) instead of the 32 to 40 resident limb accumulators.  The two 32-filter halves stage their
 // outputs in one operand buffer each and store at the same time.
-// What bounds a channel block of that form in scaled mode (some 4,900 clocks): a SIMD's vector ALU, 431 instructions of the
-// transform wave and 2 x 110 of the product waves at 4 clocks + 8 for each of 112 matrix-core instructions = 3,500; filter
+// What bounds a further channel block of that form in scaled mode (14x14, K = 256, N = 64, one round: 2.66 us, 5,600 clocks; 4,900
+// in the streaming kernel's form with eight product waves): a SIMD's vector ALU, 431 instructions of the transform wave and
+// 2 x 110 of the product waves at 4.4 clocks + 8 for each of 112 matrix-core instructions = 3,800 (counted: 645 + 112); filter
 // fragments and patches through the memory path, 2,500 + up to 2,300; LDS, 288 fragment reads and 288 writes, some 4,000; and the
-// transform wave's own chain, an instruction per 5 clocks, 2,650.
+// transform wave's own chain, an instruction per 5 clocks, 2,650.  (Four product waves and 32 filters: 1.76 us, 3,700 clocks.)
 
 template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
 __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,

@@ -52,7 +52,16 @@ struct RoleBarrier {
 //                   fused_conv_roles_kernel<PW = 8>, a third of its time at two channel blocks, run beside other tile blocks'
 //                   work.  The two halves would need twice the staging: the first writes, the second adds to it in LDS, a
 //                   longer chain per tile block, which one channel block does not pay for (56x56x64 N = 256 scaled: 77 us
-//                   with whole entries, 80 here).
+//                   with whole entries, 80 here).  Twelve waves leave 168 registers each, which is not quite enough: 4 - 6 are
+//                   spilled and reloaded in the unit loop with signed channels-last tensors, 12 - 25 with uint8 or channel-major
+//                   outputs, up to 45 with both.  It is the fastest form all the same where fused_conv.hip chooses it, except for
+//                   channel-major int32 outputs, whose 32 plane offsets also spill 66 - 232 scalar registers (in every form).
+// What bounds kStreamWhole (56x56x64, N = 256, clocks per tile block of 64 filters, lossless / scaled): the product wave's chain,
+// 13,500 / 12,400 = products with their joins, reverse scaling and output transform 10,700 / 9,800 + staging 880 + clearing the
+// outputs 800 / 1,000 + barriers, waits and prefetch 1,060 / 650.  It issues some 1,200 instructions, an instruction per 5
+// clocks alone; but the transform wave on its SIMD (transform 4,300, flush of the staged tile block 4,000, waiting 4,000)
+// is the older one and goes first, and their vector instructions together occupy the SIMD for 1,764 x 4.4 + 224 x 8 = 9,600
+// (scaled 1,831 x 4.4 + 112 x 8 = 9,000) of those clocks.
 template <int FORM> constexpr int stream_filters() { return FORM == kStreamHalves ? 32 : 64; }
 template <int FORM> constexpr int stream_product_waves() { return FORM == kStreamEight ? 8 : 4; }
 

@@ -92,7 +92,7 @@ __host__ __device__ inline int num_filter_planes(int mode) { return mode == WG_L
 // matrix-core instruction consumes is contiguous, and all planes of a (channel block, filter
 // block) follow each other, so a kernel steps from plane to plane with constant offsets.  Inside a
 // fragment the 16-byte pieces lie in lane order, [channels / 16][filter][16 channels]: a wave's load is
-// 1 KB in a row, which a compute unit takes in at 58 bytes per clock (eight waves streaming fragments, every compute
+// 1 KB in a row, which a compute unit takes in at 57 bytes per clock (eight waves streaming fragments, every compute
 // unit busy); with the pieces of a filter side by side, [filter][64 channels], it was 32, and that was what the
 // convolution kernels ran at.
 constexpr uint32_t kBlobMagic = 0x33344757u;       // "WG43": signed int8 filters, Winograd-domain values of 12 bits
