@@ -147,7 +147,8 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
         }
     }
     const int tile0 = bx * kFusedTiles, k0 = by * 8 * PW;
-    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.Cf, WG_SCALED)) return;
+    const BlobHeaderWords header = read_blob_header(blob);   // compared by either role, see fused_conv_roles_kernel
+    auto matches = [&] { return blob_matches(header, p.K, p.Cf, WG_SCALED); };
     v4i* const np_tab = reinterpret_cast<v4i*>(lds + kActFactorsOff);
     uint32_t* const rq_tab = reinterpret_cast<uint32_t*>(lds + act_rq_off<PW>());
     // the tiles' factors; tiles beyond the last one keep n = 1
@@ -171,6 +172,8 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
         loader.enter(p, n, ty, tx, lane);
         loader.drop_absent_channels(p, 0, lane);
         loader.request(xbuf, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (!matches()) return;
         ScaledPlanes out;
         int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
         out.np = np_tab + a_tile * kEntries;
@@ -195,6 +198,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
         return;
     }
 
+    if (!matches()) return;
     const int pw = wave - 4, kblock_all = pw % (PW / 2), half = pw / (PW / 2);
     const int kblock = kblock_all & 1, group = kblock_all >> 1;
     const int k = k0 + kblock_all * 16 + (lane & 15);

@@ -97,14 +97,15 @@ __global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restric
     __shared__ uint4 values[kNarrowPieces * kNarrowTiles];   // [piece][tile]
     const int lane = threadIdx.x;
     const int tile0 = blockIdx.x * tiles_per_wave;
-    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.C, MODE)) return;
+    const BlobHeaderWords header = read_blob_header(blob);   // requested here, compared once the patch is on its way
 
     // ---- phase 1: lane = tile -----------------------------------------------------------------
     int my_n = 0, my_ty = 0, my_tx = 0;
     if (tile0 + lane < p.T) decode_tile(p, tile0 + lane, my_n, my_ty, my_tx);   // else tile (0,0,0): loaded, never used
+    uint32_t u[6][6];
+    if (lane < tiles_per_wave) load_narrow_patch(x, p, my_n, my_ty, my_tx, u);
+    if (!blob_matches(header, p.K, p.C, MODE)) return;
     if (lane < tiles_per_wave) {
-        uint32_t u[6][6];
-        load_narrow_patch(x, p, my_n, my_ty, my_tx, u);
         bias_patch(p, my_ty, my_tx, 0, u);
         Quad v[kNarrowValues];
         transform_patch<ChannelPairs>(u, ValueKeeper{v});

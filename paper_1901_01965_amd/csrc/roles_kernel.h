@@ -48,7 +48,11 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
         }
     }
     const int tile0 = bx * kFusedTiles, k0 = by * (kFusedFilters * (PW / 4));
-    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.Cf, MODE, ENC::kMagic)) return;
+    // requested first, compared by either role before it goes on from what does not depend on the blob (uniform: nobody reaches a
+    // barrier otherwise): compared up here, field by field, it stood before the first patch (28x28x128 N = 32 13.60 -> 13.21 us,
+    // 16 channels at 16x16 10.28 -> 9.92)
+    const BlobHeaderWords header = read_blob_header(blob);
+    auto matches = [&] { return blob_matches(header, p.K, p.Cf, MODE, ENC::kMagic); };
     int my_n = 0, my_ty = 0, my_tx = 0;
     if (tile0 + (lane & 15) < p.T) decode_tile(p, tile0 + (lane & 15), my_n, my_ty, my_tx);
 #ifdef WG_TIMESTAMPS
@@ -74,6 +78,8 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
         loader.enter(p, a_n, a_ty, a_tx, lane);
         loader.drop_absent_channels(p, 0, lane);
         loader.request(xbuf, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (!matches()) return;
         WG_SPENT(3, mark);
         for (int cb = 0; cb < p.CB; ++cb) {
             if (cb > 0) {   // barrier cb
@@ -107,6 +113,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
 
     // PW = 4: wave = 2 half + kblock.  PW = 8: product wave pw = wave8 - 4 owns filter block pw % 4 and half pw / 4; the
     // waves of filter blocks 2 group, 2 group + 1 store together (`wave` counts within that group, as store_staged expects)
+    if (!matches()) return;
     const int pw = wave8 - 4;
     const int kblock4 = PW == 8 ? (pw & 3) : (wave & 1), half = PW == 8 ? (pw >> 2) : (wave >> 1);
     const int kblock = kblock4 & 1, group = kblock4 >> 1;

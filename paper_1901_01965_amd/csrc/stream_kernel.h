@@ -83,7 +83,9 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
         bx = w - by * (int)gridDim.x;
     }
     const int k0 = by * stream_filters<FORM>();
-    if (!blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.Cf, MODE, ENC::kMagic)) return;
+    // requested first, compared by either role before it goes on from what does not depend on the blob (see fused_conv_roles_kernel)
+    const BlobHeaderWords header = read_blob_header(blob);
+    auto matches = [&] { return blob_matches(header, p.K, p.Cf, MODE, ENC::kMagic); };
     // this workgroup's tile blocks: bx, bx + gridDim.x, ...
     const int my_blocks = (tile_blocks - bx + (int)gridDim.x - 1) / (int)gridDim.x;
     const int units = my_blocks * p.CB;
@@ -139,6 +141,8 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             loader.drop_absent_channels(p, 0, lane);
             loader.request(xbuf, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if (!matches()) return;
         // was unit v the last channel block of its tile block?  v % CB == CB - 1, tracked without division:
         // last1 = for unit u - 1, last2 = for unit u - 2; tb1 / tb2 = their tile blocks
         bool last1 = false, last2 = false;
@@ -198,6 +202,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
         return;
     }
 
+    if (!matches()) return;
     // 64 filters: those of the workgroup's second 32 are staged as a copy of their own
     const int pw = wave8 - 4;
     const int kblock4 = FORM == kStreamHalves ? (pw & 1) : (pw & 3), half = FORM == kStreamHalves ? (pw >> 1) : (FORM == kStreamWhole ? 0 : pw >> 2);
