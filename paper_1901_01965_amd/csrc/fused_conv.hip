@@ -485,6 +485,7 @@ std::atomic<int> g_stream_workgroups{0}, g_stream_variant{0}, g_scaled_variant{0
 // How a convolution is run where the fast loads apply (channels-last, C % 4 = 0, as given or as a copy).
 struct Plan {
     bool copies;         // through a channels-last copy in scratch memory
+    bool planes;         // channel-major activations read as they are: split channels, or the limb-pair kernel
     int splits, blocks;  // > 1: the channel blocks are dealt to `splits` workgroups each, `blocks` per workgroup
 };
 
@@ -503,27 +504,41 @@ bool split_pays(int mode, int CB, int K, int b, int W, bool pieces) {
     return one > split + (pieces ? 0.0 : 3.9 * b - 2.2);
 }
 
+// Channel-major activations in lossless mode, not split: the limb-pair kernel with patches turned on their way into LDS, while
+// its grid is one round of the compute units, against a copy and the forms of run_roles (fifty drawn layers, us: one
+// channel block 7.9 - 8.9 against 10.1 - 12.4; two 12.3 - 13.5 / 12.8 - 15.4; three 16.9 - 18.7 / 15.4 - 23.5, seven 35 / 30 - 41; two
+// rounds, one block 15.4 - 16.7 / 14.4 - 18.5).
+bool pair_reads_planes(const Problem& p) {
+    return p.CB <= 2 && (long long)ceil_div(p.T, kFusedTiles) * ceil_div(p.K, kFusedFilters) <= compute_units();
+}
+
 Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t scratch_bytes) {
-    Plan plan = {false, 1, p.CB};
+    Plan plan = {false, false, 1, p.CB};
     size_t left = scratch_bytes;
+    // a test hook asks for one kernel (lossless mode: the split is the limb-pair form as well)
+    const bool hooked = g_stream_workgroups.load(std::memory_order_relaxed) > 0 || g_stream_variant.load(std::memory_order_relaxed) != 0 ||
+                        g_scaled_variant.load(std::memory_order_relaxed) != 0 || (mode == WG_LOSSLESS && lossless_variant() != 0);
+    const int workgroups = ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters);
+    const bool may_split = p.CB >= 2 && 2 * workgroups <= compute_units() && !is_unsigned && !hooked;
+    const int blocks = may_split ? ceil_div(p.CB, std::min(p.CB, compute_units() / workgroups)) : p.CB, splits = ceil_div(p.CB, blocks);
+    auto split = [&](bool pieces) {
+        if (!may_split || !split_pays(mode, p.CB, p.Kp, blocks, splits * workgroups, pieces) || split_partial_bytes(p, mode, splits) > left) return false;
+        plan.splits = splits;
+        plan.blocks = blocks;
+        return true;
+    };
+    if (layout == WG_NCHW && !is_unsigned && plane_patches_hold(p)) {
+        // the split kernels read channel-major patches as well, at 1.1 us more per further block, while a copy is a launch
+        plan.planes = (blocks <= 2 && split(true)) || (mode == WG_LOSSLESS && (lossless_variant() == 1 || (!hooked && pair_reads_planes(p))));
+        if (plan.planes) return plan;
+    }
     if (layout != WG_NHWC || p.C % 4 != 0) {
         // (the copy is addressed with 32-bit offsets)
         plan.copies = left >= channels_last_bytes(p) && (long long)p.N * p.H * p.W * padded_channels(p.C) <= 0x7fffffffll;
         if (!plan.copies) return plan;
         left -= channels_last_bytes(p);
     }
-    // a test hook asks for one kernel (lossless mode: the split is the limb-pair form as well)
-    const bool hooked = g_stream_workgroups.load(std::memory_order_relaxed) > 0 || g_stream_variant.load(std::memory_order_relaxed) != 0 ||
-                        g_scaled_variant.load(std::memory_order_relaxed) != 0 || (mode == WG_LOSSLESS && lossless_variant() != 0);
-    const int workgroups = ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters);
-    if (p.CB >= 2 && 2 * workgroups <= compute_units() && !is_unsigned && !hooked) {
-        const int blocks = ceil_div(p.CB, std::min(p.CB, compute_units() / workgroups)), splits = ceil_div(p.CB, blocks);
-        const bool pieces = plan.copies ? padded_channels(p.C) % 16 == 0 : p.C % 16 == 0;   // (a caller's view may still start off a boundary)
-        if (split_pays(mode, p.CB, p.Kp, blocks, splits * workgroups, pieces) && split_partial_bytes(p, mode, splits) <= left) {
-            plan.splits = splits;
-            plan.blocks = blocks;
-        }
-    }
+    split(plan.copies ? padded_channels(p.C) % 16 == 0 : p.C % 16 == 0);   // (a caller's view may still start off a boundary)
     return plan;
 }
 
@@ -555,8 +570,9 @@ namespace {
 bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial, hipStream_t s, hipError_t& status) {
     const Problem& p = c.p;
     if (plan.splits > 1) {
-        status = mode == WG_LOSSLESS ? launch_lossless_pair_sums(c.x, c.blob, partial, p, plan.blocks, plan.splits, s)
-                                     : launch_scaled_sums(c.x, c.blob, partial, p, plan.blocks, plan.splits, s);
+        const int layout = plan.planes ? WG_NCHW : WG_NHWC;   // of the activations, as given or as a copy
+        status = mode == WG_LOSSLESS ? launch_lossless_pair_sums(c.x, c.blob, partial, p, layout, plan.blocks, plan.splits, s)
+                                     : launch_scaled_sums(c.x, c.blob, partial, p, layout, plan.blocks, plan.splits, s);
         if (status == hipSuccess)
             status = mode == WG_LOSSLESS ? launch_sums_finish(c, partial, plan.splits, s) : launch_split_finish(c, partial, plan.splits, s);
         return true;
@@ -591,7 +607,7 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
         const double pair_cost = 6.5 * (double)((w32 + cus - 1) / cus);
         const double here_cost = w32 <= cus ? 7.4 : 11.7 * (double)((w32 / 2 + cus - 1) / cus);
         if (form == 2 || (form == 1 && p.CB == 1 && pair_cost < here_cost)) {
-            status = launch_lossless_pair_conv(c.x, c.blob, c.y, p, c.q8, s);
+            status = launch_lossless_pair_conv(c.x, c.blob, c.y, p, c.layout, c.q8, s);
             return true;
         }
     }
@@ -655,7 +671,7 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
 bool make_fast_call(RolesCall& c, const Plan& plan, int layout, const Scratch& scratch, int32_t*& partial, hipStream_t s, hipError_t& status) {
     partial = static_cast<int32_t*>(scratch.p);
     status = hipSuccess;
-    if (layout == WG_NHWC && c.p.C % 4 == 0) return true;
+    if (plan.planes || (layout == WG_NHWC && c.p.C % 4 == 0)) return true;
     if (!plan.copies) return false;
     int8_t* const copy = static_cast<int8_t*>(scratch.p);
     const int padded = padded_channels(c.p.C);
@@ -698,7 +714,7 @@ static bool one_act_scaled_kernel(const Problem& p, int layout) {
 }
 
 static Plan plan_act_scaled(const Problem& p, int layout, size_t scratch_bytes) {
-    Plan plan = {false, 1, p.CB};
+    Plan plan = {false, false, 1, p.CB};
     if (layout != WG_NHWC || p.C % 4 != 0)
         plan.copies = scratch_bytes >= channels_last_bytes(p) && (long long)p.N * p.H * p.W * padded_channels(p.C) <= 0x7fffffffll;
     return plan;
@@ -735,6 +751,7 @@ hipError_t launch_fused_conv(const int8_t* x, const void* blob, int32_t* y, cons
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, mode);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
     const Plan plan = plan_conv(p, layout, mode, false, scratch.bytes);
+    if (plan.planes && plan.splits == 1) return launch_lossless_pair_conv(x, b, y, p, layout, q8, s);
     RolesCall c = {x, nullptr, b, bl, y, p, layout, q8};
     int32_t* partial;
     hipError_t status;

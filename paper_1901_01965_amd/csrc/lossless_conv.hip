@@ -1,5 +1,5 @@
 // The whole hot path in one kernel, lossless mode, for channels-last activations whose channel
-// count is a multiple of four.
+// count is a multiple of four, and for channel-major ones.
 //
 // A 12-bit Winograd-domain filter value W = 256 Wh + Wl (byte limbs) enters the matrix cores as TWO
 // ROWS of the first operand: a fragment is 8 filters x (Wh, Wl) x 64 channels.  The second operand
@@ -54,7 +54,7 @@ constexpr int kBlockFilters = 4 * kPairFilters;         // 32 filters per workgr
 constexpr int kActPlanes = 72;                          // byte-limb planes: real p: 2p, 2p+1; complex j: 32+4j + {Re h, Re l, Im h, Im l}
 constexpr int kPlanesBytes = kActPlanes * kPlaneBytes;  // 72 KB
 constexpr int kRawPixel = 4 * kCBlock;                  // raw patches of four tiles (waves w and w + 4): [pixel 0..35][tile][64 channels]
-constexpr int kRawQuad = 36 * kRawPixel;                // 9 KB: nine 1 KB transfers
+constexpr int kRawQuad = 36 * kRawPixel + 16;           // 9 KB: nine 1 KB transfers; the quads' dwords of a pixel fall into different banks
 // output staging (after the products): stage[half][output o][tile][32 filters], tile rows 36 dwords apart and
 // outputs 16*36 + 32 dwords apart, so that the 16-byte reads of a 16-lane group (two outputs x eight filter
 // quads) fall into different banks
@@ -66,6 +66,7 @@ static_assert(kStageBytes >= 4 * kRawQuad, "the staged outputs start in the raw 
 constexpr int kLdsBytes = kPlanesBytes + kStageBytes;
 static_assert(kLdsBytes <= 160 * 1024, "LDS of one compute unit");
 constexpr int kLoadDwords = 1, kLoadDirect = 2;         // 4-byte loads into registers / 16-byte pieces straight into LDS
+constexpr int kLoadPlanes = 3;                          // channel-major activations: rows of a patch, turned on the way into LDS
 
 // ---- which entries a wave multiplies, in order -------------------------------------------------
 // Half 0: rows 0, 1, 2 of M (five entries each: four real, then the complex M[row][3]) and M[3][0];
@@ -303,19 +304,110 @@ __device__ inline void buffer_to_lds_16(__amdgpu_buffer_rsrc_t buffer, int8_t* l
     __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (__attribute__((address_space(3))) int8_t*)lds_dst, 16, voffset, soffset, 0, 0);
 }
 
+// The raw patches of 16 tiles from channel-major activations.  A lane takes one row of one tile's patch in four channels: six
+// bytes of each, with one 8-byte load at any address, so that the lanes of sixteen tiles side by side read 68 bytes in a row;
+// twelve v_perm turn them into six pixels of four channels, whose dwords go where the direct transfers put theirs.  A
+// workgroup's 6 x 16 rows and channel quads are three per thread.  (Without it such a layer is copied to channels-last first, a
+// launch of its own: 16 -> 16 channels at 16x16 9.9 -> 7.6 us, 100 -> 75 at 37x53, N = 4, 15.4 -> 12.6.)
+struct __attribute__((packed)) PackedPair {   // an 8-byte load at any address
+    uint64_t v;
+};
+struct PlanePatch {
+    static constexpr int kRows = 3;   // per thread
+    int8_t* to[kRows];      // this lane's place in the raw area
+    int from[kRows];        // offset of its row's first pixel in its first channel; -1 at most before the tensor
+    uint32_t low[kRows], high[kRows];   // pixels 0 .. 3 and 4, 5 of the row that lie inside the image
+    uint64_t row[kRows][4];             // the row in four channels, in flight
+    __device__ inline static int quad_of(int wave, int i, int lane) { return 4 * ((wave * kRows + i) / 6) + (lane >> 4); }   // of four channels
+    __device__ inline void enter(const Problem& p, int8_t* lds, int tile0, int wave, int lane) {
+        const int tile = lane & 15, t = tile0 + tile;
+        int n = 0, ty = 0, tx = 0;   // a tile that does not exist may be any: nobody stores its outputs
+        if (t < p.T) decode_tile(p, t, n, ty, tx);
+        const int w0 = 4 * tx - 1;
+        uint32_t inside[2] = {0, 0};
+#pragma unroll
+        for (int b = 0; b < 6; ++b) inside[b >> 2] |= (unsigned)(w0 + b) < (unsigned)p.W ? 0xffu << (8 * (b & 3)) : 0u;
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
+            const int a = (wave * kRows + i) % 6, cq = quad_of(wave, i, lane), h = 4 * ty - 1 + a;
+            const bool have = (unsigned)h < (unsigned)p.H;
+            from[i] = ((n * p.C + min(4 * cq, p.C - 1)) * p.H + min(max(h, 0), p.H - 1)) * p.W + w0;
+            low[i] = have ? inside[0] : 0u;
+            high[i] = have ? inside[1] : 0u;
+            to[i] = lds + kPlanesBytes + (tile >> 2) * kRawQuad + (6 * a) * kRawPixel + (tile & 3) * kCBlock + 4 * cq;
+        }
+    }
+    // Rows of channels beyond C repeat the last channel (they meet zero filters); the first and the last row of the tensor are
+    // read up to seven bytes later or earlier and shifted into place.
+    __device__ inline void request(const int8_t* __restrict__ x, const Problem& p, int cb, int wave, int lane) {
+        const int plane = p.H * p.W, last = p.N * p.C * plane - 8;   // >= 0: see lossless_pair_conv_choice
+        int at[kRows][4];
+        bool moved = false;
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
+            const int c0 = min(4 * quad_of(wave, i, lane), p.C - 1), c = cb * kCBlock + 4 * quad_of(wave, i, lane);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                at[i][j] = from[i] + (min(c + j, p.C - 1) - c0) * plane;
+                moved |= at[i][j] < 0 || at[i][j] > last;
+            }
+        }
+        if (__ballot(moved) == 0) {
+#pragma unroll
+            for (int i = 0; i < kRows; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) row[i][j] = reinterpret_cast<const PackedPair*>(x + at[i][j])->v;
+        } else {
+#pragma unroll
+            for (int i = 0; i < kRows; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int s = min(max(at[i][j], 0), last);
+                    const uint64_t v = reinterpret_cast<const PackedPair*>(x + s)->v;
+                    row[i][j] = at[i][j] < s ? v << 8 : v >> (8 * (at[i][j] - s));
+                }
+        }
+    }
+    __device__ inline void put() const {
+        auto perm = [](uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); };
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
+            uint32_t l[4], h[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                l[j] = (uint32_t)row[i][j] & low[i];
+                h[j] = (uint32_t)(row[i][j] >> 32) & high[i];
+            }
+            const uint32_t l01a = perm(l[1], l[0], 0x05010400u), l01b = perm(l[1], l[0], 0x07030602u);
+            const uint32_t l23a = perm(l[3], l[2], 0x05010400u), l23b = perm(l[3], l[2], 0x07030602u);
+            const uint32_t h01 = perm(h[1], h[0], 0x05010400u), h23 = perm(h[3], h[2], 0x05010400u);
+            const uint32_t px[6] = {perm(l23a, l01a, 0x05040100u), perm(l23a, l01a, 0x07060302u), perm(l23b, l01b, 0x05040100u),
+                                    perm(l23b, l01b, 0x07060302u), perm(h23, h01, 0x05040100u), perm(h23, h01, 0x07060302u)};
+#pragma unroll
+            for (int b = 0; b < 6; ++b) *reinterpret_cast<uint32_t*>(to[i] + b * kRawPixel) = px[b];
+        }
+    }
+};
+
 // How the eight waves of a workgroup bring the raw patches of their 16 tiles: wave = quad + 4 half, four tiles per quad.
 // Direct transfers (LOAD kLoadDirect): transfer i (0..8) moves pixels 4i .. 4i+3 of the four tiles: lane = 16 (pixel % 4) +
 // 4 (tile % 4) + piece of 16 channels, and the hardware puts lane l's 16 bytes at (uniform destination) + 16 l, so the raw
 // area is [pixel][tile % 4][64 channels].  Waves 0-3 issue transfers 0..4, waves 4-7 transfers 5..8.
+// Channel-major activations (kLoadPlanes, see PlanePatch): the same raw area.
 // Otherwise every thread loads the 36 pixels of its tile and four channels itself.
 template <int LOAD>
 struct RawPatch {
+    std::conditional_t<LOAD == kLoadPlanes, PlanePatch, int> planes;
     int8_t* area;                                    // of the quad
     uint32_t raw_off[LOAD == kLoadDirect ? 5 : 1];   // this lane's piece in each of the wave's transfers
     uint32_t pixel[LOAD == kLoadDwords ? 36 : 1];    // or this thread's 36 pixels
     int first_transfer, transfers, channel;          // channel: first one of this lane's pieces
     __device__ inline void init(const Problem& p, int8_t* lds, int tile0, int quad, int half, int lane) {
         area = lds + kPlanesBytes + quad * kRawQuad;
+        if constexpr (LOAD == kLoadPlanes) {
+            planes.enter(p, lds, tile0, quad + 4 * half, lane);
+            return;
+        }
         first_transfer = half == 0 ? 0 : 5;
         transfers = half == 0 ? 5 : 4;
         const int t = tile0 + 4 * quad + (LOAD == kLoadDirect ? (lane >> 2) & 3 : lane >> 4);
@@ -342,7 +434,12 @@ struct RawPatch {
     }
     // Channel block cb.  In the last block of a C that is not a multiple of 64 (a uniform branch) lanes whose
     // channels lie beyond C ask for the outside offset and get zeros.
-    __device__ inline void request(__amdgpu_buffer_rsrc_t xbuf, const Problem& p, int cb, uint32_t (&u)[6][6]) const {
+    __device__ inline void request(const int8_t* __restrict__ x, const Problem& p, int cb, int wave, int lane, uint32_t (&u)[6][6]) {
+        if constexpr (LOAD == kLoadPlanes) {
+            planes.request(x, p, cb, wave, lane);
+            return;
+        }
+        const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
         const bool tail = (cb + 1) * kCBlock > p.C;
         const bool have = !tail || cb * kCBlock + channel < p.C;
         if constexpr (LOAD == kLoadDirect) {
@@ -359,13 +456,14 @@ struct RawPatch {
     // Waits for what was requested; afterwards (`again`: this is not the first block) everyone is done reading the
     // previous block's planes as well.
     __device__ inline void take(bool again, int lane, uint32_t (&u)[6][6]) const {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (LOAD == kLoadDirect || again) {
-            // the raw pieces of a wave's tiles were moved by two waves
+        if constexpr (LOAD == kLoadPlanes) planes.put();   // nobody reads the previous block's raw patches any more: its planes were published since
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (LOAD != kLoadDwords || again) {
+            // the raw pieces of a wave's tiles were moved by other waves
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
         }
-        if constexpr (LOAD == kLoadDirect) {
+        if constexpr (LOAD != kLoadDwords) {
 #pragma unroll
             for (int i = 0; i < 36; ++i) u[i / 6][i % 6] = *reinterpret_cast<const uint32_t*>(area + i * kRawPixel + 4 * lane);
         }
@@ -377,7 +475,7 @@ struct RawPatch {
 // before the rescale by 2^-4, at y as int32 [blockIdx.z][16 gridDim.x tiles][output 4i+j][Kp] (the output transform is
 // linear, so these add up to the whole; sums_finish_kernel adds, rescales and stores).
 constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2;
-template <int LOAD, int OUT>
+template <int LAYOUT, int LOAD, int OUT>
 __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                             size_t pairs_off, int32_t* __restrict__ y, Problem p,
                                                             Int8Epilogue q8, int blocks) {
@@ -387,7 +485,6 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tile0 = blockIdx.x * kTileBlock;
     const int k0 = blockIdx.y * kBlockFilters;
-    const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
     WG_STAMP(0);
 
     // ---- the raw patch of the first channel block: the longest wait of the kernel, requested first ----
@@ -397,7 +494,7 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     RawPatch<LOAD> raw;
     raw.init(p, lds, tile0, quad, half, lane);
     uint32_t u[6][6];
-    raw.request(xbuf, p, cb_first, u);
+    raw.request(x, p, cb_first, wave, lane, u);
     // the blob header: requested now, looked at after the transform, so its latency hides behind the patch's
     __builtin_amdgcn_sched_barrier(0);
     const BlobHeaderWords header = read_blob_header(blob);
@@ -437,7 +534,7 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
         WG_STAMP(3);
         __builtin_amdgcn_s_barrier();
         WG_STAMP(4);
-        if (cb + 1 < cb_end) raw.request(xbuf, p, cb + 1, u);   // travels while this block's products run
+        if (cb + 1 < cb_end) raw.request(x, p, cb + 1, wave, lane, u);   // travels while this block's products run
         if (half == 0) products0.run(cx, Y); else products1.run(cx, Y);
         cx.flt += flt_block;
         WG_STAMP(5);
@@ -455,6 +552,70 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     }
     __syncthreads();
     WG_STAMP(6);
+    auto sixteen = [&](int o, int tile, int k4) {   // 16 x the finished outputs of filters k0 + 4 k4 .. + 3 at output o of a tile
+        const int at = o * kStageOut + tile * kStageRow + 4 * k4;
+        return *reinterpret_cast<const v4i*>(stage + at) + *reinterpret_cast<const v4i*>(stage + kStageHalf + at);
+    };
+    auto staged = [&](int o, int tile, int k4) { return sixteen(o, tile, k4) >> 4; };
+    auto best_of_window = [&](int pi, int pj, int tile, int k4) {   // 2x2 maximum of requantised outputs
+        v4i best = requantise(staged(4 * (2 * pi) + 2 * pj, tile, k4), q8);
+        best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi) + 2 * pj + 1, tile, k4), q8));
+        best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj, tile, k4), q8));
+        return __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj + 1, tile, k4), q8));
+    };
+    if constexpr (LAYOUT == WG_NCHW && OUT != kOutSums) {
+        // a filter's outputs lie together: sixteen consecutive tiles of an image row are 64 consecutive pixels
+        const int tile = (tid >> 2) & 15, t = tile0 + tile;
+        int n = 0, ty = 0, tx = 0;
+        if (t < p.T) decode_tile(p, t, n, ty, tx);
+        const int H = Q8 && q8.pool ? p.H >> 1 : p.H, W = Q8 && q8.pool ? p.W >> 1 : p.W;
+        const size_t plane = (size_t)H * W;
+        auto first = [&](auto* base, int k4, int h, int w) { return base + ((size_t)n * p.K + k0 + 4 * k4) * plane + (size_t)h * W + w; };
+        if constexpr (!Q8) {
+            // thread: row i, column j of a tile, four groups of four filters
+            const int j = tid & 3, i = (tid >> 6) & 3, h = 4 * ty + i, w = 4 * tx + j;
+            if (t >= p.T || h >= H || w >= W) return;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int k4 = 4 * (tid >> 8) + g;
+                const v4i v = staged(4 * i + j, tile, k4);
+                int32_t* const at = first(y, k4, h, w);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (k0 + 4 * k4 + c < p.K) at[c * plane] = v[c];
+            }
+        } else if (q8.pool) {
+            // thread: one pooled pixel of a tile, four filters
+            const int pj = tid & 1, pi = (tid >> 1) & 1, k4 = tid >> 6, h = 2 * ty + pi, w = 2 * tx + pj;
+            if (t >= p.T || h >= H || w >= W) return;
+            const v4i best = best_of_window(pi, pj, tile, k4);
+            int8_t* const at = first(q8.out, k4, h, w);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (k0 + 4 * k4 + c < p.K) at[c * plane] = (int8_t)best[c];
+        } else {
+            // thread: row i of a tile (four pixels: one dword where rows stay aligned), four filters
+            const int i = tid & 3, k4 = tid >> 6, h = 4 * ty + i, w = 4 * tx;
+            if (t >= p.T || h >= H) return;
+            const bool word_store = ((W & 3) | (int)(reinterpret_cast<uintptr_t>(q8.out) & 3)) == 0;
+            v4i px[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) px[j] = requantise(staged(4 * i + j, tile, k4), q8);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (k0 + 4 * k4 + c >= p.K) continue;
+                int8_t* const at = first(q8.out, k4, h, w) + c * plane;
+                if (word_store) {
+                    *reinterpret_cast<uint32_t*>(at) = pack_bytes((v4i){px[0][c], px[1][c], px[2][c], px[3][c]});
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (w + j < W) at[j] = (int8_t)px[j][c];
+                }
+            }
+        }
+        return;
+    }
     // thread: filters k0 + 4 k4 .. + 3 of output column j of tile `tile`; round r: output row r
     const int k4 = tid & 7, j = (tid >> 3) & 3, tile = tid >> 5;
     const int t = tile0 + tile, kk = k0 + 4 * k4;
@@ -462,15 +623,10 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     if (t < p.T) decode_tile(p, t, n, ty, tx);
     const int row = 4 * ty, col = 4 * tx + j;
     const bool live = t < p.T && col < p.W && kk < p.K;
-    auto sixteen = [&](int o) {   // 16 x the finished outputs of the thread's four filters at output o of its tile
-        const int at = o * kStageOut + tile * kStageRow + 4 * k4;
-        return *reinterpret_cast<const v4i*>(stage + at) + *reinterpret_cast<const v4i*>(stage + kStageHalf + at);
-    };
-    auto staged = [&](int o) { return sixteen(o) >> 4; };
     if constexpr (OUT == kOutSums) {
         v4i* const to = reinterpret_cast<v4i*>(y) + ((((size_t)blockIdx.z * gridDim.x * kTileBlock + t) * 16 + j) * p.Kp + kk) / 4;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) to[(size_t)r * p.Kp] = sixteen(4 * r + j);
+        for (int r = 0; r < 4; ++r) to[(size_t)r * p.Kp] = sixteen(4 * r + j, tile, k4);
         return;
     }
     if constexpr (!Q8) {
@@ -478,7 +634,7 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
         const bool vector_store = (p.K & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
         v4i v[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = staged(4 * r + j);
+        for (int r = 0; r < 4; ++r) v[r] = staged(4 * r + j, tile, k4);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             if (!live || row + r >= p.H) continue;
@@ -506,7 +662,7 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
         if (!q8.pool) {
             v4i v[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = requantise(staged(4 * r + j), q8);
+            for (int r = 0; r < 4; ++r) v[r] = requantise(staged(4 * r + j, tile, k4), q8);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 if (live && row + r < p.H) put(q8.out + ((size_t)(n * p.H + row + r) * p.W + col) * p.K + kk, v[r]);
@@ -515,10 +671,7 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
             const int Ho = p.H >> 1, Wo = p.W >> 1, ocol = 2 * tx + j;
 #pragma unroll
             for (int pi = 0; pi < 2; ++pi) {
-                v4i best = requantise(staged(4 * (2 * pi) + 2 * j), q8);
-                best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi) + 2 * j + 1), q8));
-                best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * j), q8));
-                best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * j + 1), q8));
+                const v4i best = best_of_window(pi, j, tile, k4);
                 if (t < p.T && kk < p.K && ocol < Wo && 2 * ty + pi < Ho)
                     put(q8.out + ((size_t)(n * Ho + 2 * ty + pi) * Wo + ocol) * p.K + kk, best);
             }
@@ -623,13 +776,12 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tile0 = blockIdx.x * kTileBlock, k0 = blockIdx.y * kBlockFilters;
     const int cb_first = (int)blockIdx.z * blocks, cb_end = min(cb_first + blocks, p.CB);
-    const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
     const int quad = wave & 3, half = wave >> 2;   // of the transform
     const int a_tile = 4 * quad + (lane >> 4), a_cq = lane & 15;
     RawPatch<LOAD> raw;
     raw.init(p, lds, tile0, quad, half, lane);
     uint32_t u[6][6];
-    raw.request(xbuf, p, cb_first, u);
+    raw.request(x, p, cb_first, wave, lane, u);
     __builtin_amdgcn_sched_barrier(0);
     const BlobHeaderWords header = read_blob_header(blob);
     __builtin_amdgcn_sched_barrier(0);
@@ -652,7 +804,7 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
             if (cb == cb_first && !blob_matches(header, p.K, p.Cf, WG_SCALED)) return;   // uniform: nobody reaches the next barrier
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
-            if (cb + 1 < cb_end) raw.request(xbuf, p, cb + 1, u);
+            if (cb + 1 < cb_end) raw.request(x, p, cb + 1, wave, lane, u);
             products.run(act);
             flt += flt_block;
         }
@@ -668,14 +820,21 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
     }
 }
 
-template <int LOAD, int OUT>
+template <int LAYOUT, int LOAD, int OUT>
 hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p,
                   const Int8Epilogue& q8, hipStream_t s, int blocks = 0, int splits = 1) {
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LOAD, OUT>), kLdsBytes)) return e;
-    dim3 grid(ceil_div(p.T, kTileBlock), p.Kp / kBlockFilters, splits);
-    lossless_pair_kernel<LOAD, OUT><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, blob, bl.pairs_off, y, p, q8, blocks);
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LAYOUT, LOAD, OUT>), kLdsBytes)) return e;
+    // sums are stored for every padded filter; otherwise a block of filters that do not exist has nothing to do
+    dim3 grid(ceil_div(p.T, kTileBlock), OUT == kOutSums ? p.Kp / kBlockFilters : ceil_div(p.K, kBlockFilters), splits);
+    lossless_pair_kernel<LAYOUT, LOAD, OUT><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, blob, bl.pairs_off, y, p, q8, blocks);
     return hipGetLastError();
+}
+
+// How the patches of a tensor are read (see kLoadDwords ..).
+int load_of(const int8_t* x, const Problem& p, int layout) {
+    if (layout != WG_NHWC) return kLoadPlanes;
+    return p.C % 16 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 ? kLoadDirect : kLoadDwords;
 }
 
 std::atomic<int> g_lossless_variant{0};
@@ -691,45 +850,60 @@ extern "C" int winograd_debug_set_stamps(void* dev_ptr) {
 void set_lossless_variant(int v) { g_lossless_variant.store(v, std::memory_order_relaxed); }
 int lossless_variant() { return g_lossless_variant.load(std::memory_order_relaxed); }
 
+bool plane_patches_hold(const Problem& p) { return (long long)p.N * p.C * p.H * p.W >= 8; }   // whole 8-byte loads exist
+
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout) {
     const int v = lossless_variant();
-    const bool applies = layout == WG_NHWC && p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0;
+    const bool applies = layout == WG_NHWC ? p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0 : plane_patches_hold(p);
     if (v == 2 || !applies) return 0;
     return v == 1 ? 2 : 1;
 }
 
-hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p,
+hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p, int layout,
                                      const Int8Epilogue& q8, hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
-    const bool direct = p.C % 16 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
-    if (q8.out != nullptr)
-        return direct ? launch<kLoadDirect, kOutInt8>(x, b, bl, y, p, q8, s) : launch<kLoadDwords, kOutInt8>(x, b, bl, y, p, q8, s);
-    return direct ? launch<kLoadDirect, kOutInt32>(x, b, bl, y, p, q8, s) : launch<kLoadDwords, kOutInt32>(x, b, bl, y, p, q8, s);
+    auto go = [&](auto LAYOUT, auto LOAD) {
+        return q8.out != nullptr ? launch<LAYOUT, LOAD, kOutInt8>(x, b, bl, y, p, q8, s) : launch<LAYOUT, LOAD, kOutInt32>(x, b, bl, y, p, q8, s);
+    };
+    using std::integral_constant;
+    constexpr integral_constant<int, WG_NHWC> nhwc{};
+    switch (load_of(x, p, layout)) {
+        case kLoadPlanes: return go(integral_constant<int, WG_NCHW>{}, integral_constant<int, kLoadPlanes>{});
+        case kLoadDirect: return go(nhwc, integral_constant<int, kLoadDirect>{});
+        default: return go(nhwc, integral_constant<int, kLoadDwords>{});
+    }
 }
 
-hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s) {
+hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits,
+                                     hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
-    if (p.C % 16 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0)
-        return launch<kLoadDirect, kOutSums>(x, b, bl, sums, p, no_int8_epilogue(), s, blocks, splits);
-    return launch<kLoadDwords, kOutSums>(x, b, bl, sums, p, no_int8_epilogue(), s, blocks, splits);
+    auto go = [&](auto LOAD) { return launch<WG_NHWC, LOAD, kOutSums>(x, b, bl, sums, p, no_int8_epilogue(), s, blocks, splits); };
+    using std::integral_constant;
+    switch (load_of(x, p, layout)) {
+        case kLoadPlanes: return go(integral_constant<int, kLoadPlanes>{});
+        case kLoadDirect: return go(integral_constant<int, kLoadDirect>{});
+        default: return go(integral_constant<int, kLoadDwords>{});
+    }
 }
 
-hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s) {
+hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits, hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
     const dim3 grid(ceil_div(p.T, kTileBlock), p.Kp / kBlockFilters, splits);
-    auto go = [&](auto kernel, auto&) -> hipError_t {
-        static LdsLimitOnce lds_limit;   // per kernel: the second argument's type tells the two apart, whose pointers are of one type
+    auto go = [&](auto LOAD) -> hipError_t {
+        static LdsLimitOnce lds_limit;   // per LOAD
         constexpr int lds_bytes = kPlanesBytes + 4 * kRawQuad;
-        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(kernel), lds_bytes)) return e;
-        kernel<<<grid, 64 * kWaves, lds_bytes, s>>>(x, static_cast<const uint8_t*>(blob), bl.planes_off, sums, p, blocks);
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&scaled_sums_kernel<LOAD>), lds_bytes)) return e;
+        scaled_sums_kernel<LOAD><<<grid, 64 * kWaves, lds_bytes, s>>>(x, static_cast<const uint8_t*>(blob), bl.planes_off, sums, p, blocks);
         return hipGetLastError();
     };
-    std::integral_constant<int, kLoadDirect> direct;
-    std::integral_constant<int, kLoadDwords> dwords;
-    if (p.C % 16 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) return go(&scaled_sums_kernel<kLoadDirect>, direct);
-    return go(&scaled_sums_kernel<kLoadDwords>, dwords);
+    using std::integral_constant;
+    switch (load_of(x, p, layout)) {
+        case kLoadPlanes: return go(integral_constant<int, kLoadPlanes>{});
+        case kLoadDirect: return go(integral_constant<int, kLoadDirect>{});
+        default: return go(integral_constant<int, kLoadDwords>{});
+    }
 }
 
 }  // namespace wg

@@ -269,25 +269,27 @@ inline size_t channels_last_bytes(const Problem& p) { return round_up((size_t)p.
 // Test hook: n > 0 makes the single-kernel path use its streaming variant wherever the layout
 // allows, with n workgroups per filter block; 0 restores the library's own choice.
 void set_stream_workgroups(int n);
-// Single-kernel path, lossless mode, channels-last with C % 4 == 0: the form whose filter operand carries
+// Single-kernel path, lossless mode, channels-last with C % 4 == 0 or channel-major: the form whose filter operand carries
 // both limbs of eight filters (see lossless_conv.hip).  set_lossless_variant: 0 the library's choice,
 // 1 this form wherever the layout allows, 2 never (test hook).
-hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p,
+hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p, int layout,
                                      const Int8Epilogue& q8, hipStream_t s);
+bool plane_patches_hold(const Problem& p);   // channel-major activations of p can be read that way
 // 0: this form does not apply (layout) or is switched off, 1: applies, the dispatcher decides, 2: forced by the test hook
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout);
 void set_lossless_variant(int v);
 int lossless_variant();
 // The same form with the channel blocks dealt to `splits` workgroups each: leaves 16 x outputs as int32
 // [splits][16 ceil(T/16)][16][Kp], which launch_sums_finish adds and stores.
-hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s);
+hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits,
+                                     hipStream_t s);
 // Test hook (both modes): 0 the library's choice, 1 the role-specialised kernel with eight product waves (64 filters
 // per workgroup) wherever the layout allows (channels-last, C % 4 = 0, K % 4 = 0), 2 never that form.
 void set_scaled_variant(int v);
 // The same for the streaming kernel's form with eight product waves (0, 1: wherever the layer streams, 2: never).
 void set_stream_variant(int v);
 // Scaled mode, likewise: leaves the Winograd-domain channel sums as int32 [splits][36][16 ceil(T/16)][Kp] for launch_split_finish.
-hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int blocks, int splits, hipStream_t s);
+hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits, hipStream_t s);
 // Single-kernel path with the activations scaled per tile as well (WG_SCALED blob of signed int8 filters).
 // act_table: null, or int32 [T][26][4] that receives every tile's (n, p, r, q).
 size_t act_scaled_scratch_wanted(const Problem& p, int layout);
