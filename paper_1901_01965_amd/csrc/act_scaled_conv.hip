@@ -133,19 +133,11 @@ static_assert(2 * kActPlaneBuffer <= kLdsBytes && act_lds_bytes<8>() <= 160 * 10
 template <int LAYOUT, int PW>
 __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                                          size_t table_off, size_t planes_off, int32_t* __restrict__ y,
-                                                                         const uint32_t* __restrict__ factors, Problem p) {
+                                                                         const uint32_t* __restrict__ factors, Problem p, GridOrder order) {
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int bx = blockIdx.x, by = blockIdx.y;
-    {
-        const int total = gridDim.x * gridDim.y;
-        if (gridDim.y >= 2 && (total & 7) == 0) {   // XCD-major order, as in fused_conv_body
-            const int launch = blockIdx.y * gridDim.x + blockIdx.x;
-            const int w = (launch & 7) * (total >> 3) + (launch >> 3);
-            by = w / (int)gridDim.x;
-            bx = w - by * (int)gridDim.x;
-        }
-    }
+    int bx, by;
+    order.place(bx, by);
     const int tile0 = bx * kFusedTiles, k0 = by * 8 * PW;
     const BlobHeaderWords header = read_blob_header(blob);   // compared by either role, see fused_conv_roles_kernel
     auto matches = [&] { return blob_matches(header, p.K, p.Cf, WG_SCALED); };
@@ -254,18 +246,21 @@ hipError_t launch_act_factors(const RolesCall& c, uint32_t* factors, int32_t* ac
 }
 
 hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, hipStream_t s) {
-    // 64 filters per workgroup unless a 64-filter grid leaves more than half of the compute units idle (see fused_conv.hip)
+    // 64 filters per workgroup unless 32 fill the compute units in one round, or in so few rounds that a half-empty 64-filter block
+    // costs more (see run_roles in fused_conv.hip)
     auto go = [&](auto L, auto W) -> hipError_t {
         constexpr int PW = W;
         static LdsLimitOnce lds_limit;   // per instance
         if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW>), act_lds_bytes<PW>())) return e;
-        const dim3 grid(ceil_div(c.p.T, kFusedTiles), c.p.Kp / (8 * PW));
+        const dim3 grid(ceil_div(c.p.T, kFusedTiles), ceil_div(c.p.K, 8 * PW));
         act_scaled_roles_kernel<L, PW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y,
-                                                                                      factors, c.p);
+                                                                                      factors, c.p, grid_order(grid));
         return hipGetLastError();
     };
     using std::integral_constant;
-    const bool wide = 2LL * ceil_div(c.p.T, kFusedTiles) * (c.p.Kp / 64) > compute_units();
+    const int tile_blocks = ceil_div(c.p.T, kFusedTiles), cus = compute_units();
+    auto rounds = [&](int filters) { return ((long long)tile_blocks * ceil_div(c.p.K, filters) + cus - 1) / cus; };
+    const bool wide = rounds(32) > 1 && 100 * rounds(32) >= 134 * rounds(64);
     if (c.layout == WG_NHWC)
         return wide ? go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 4>{});
     return wide ? go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 4>{});

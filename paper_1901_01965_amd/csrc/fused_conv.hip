@@ -45,27 +45,13 @@ namespace {
 template <int LAYOUT, int LOAD, int MODE, bool SUMS, bool WIDE, bool Q8, class ENC = SignedInt8>
 __device__ __forceinline__ void fused_conv_body(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                 size_t table_off, size_t planes_off, int32_t* __restrict__ y,
-                                                const Problem p, const Int8Epilogue q8, const ENC enc = ENC{}) {
+                                                const Problem p, const Int8Epilogue q8, const GridOrder order, const ENC enc = ENC{}) {
     static_assert(LOAD != kLoadDirect || ENC::kMagic == kBlobMagic, "direct transfers deliver zero bytes for absent pixels");
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int kblock = wave & 1, half = wave >> 1;
-    // Workgroups are handed to the eight XCDs (each with its own L2) round-robin in launch order.
-    // With several filter blocks and channel blocks, the grid is dealt out XCD-major instead, so
-    // that an XCD runs consecutive tile blocks of as few filter blocks as possible at the same
-    // time: a filter block's operand planes (46-138 KB per channel block) are then fetched into
-    // one or two L2s instead of into all eight.  (With a single channel block the planes are
-    // small and the order made no difference.)
-    int bx = blockIdx.x, by = blockIdx.y;
-    {
-        const int total = gridDim.x * gridDim.y;
-        if (gridDim.y >= 2 && p.CB >= 2 && (total & 7) == 0) {
-            const int launch = blockIdx.y * gridDim.x + blockIdx.x;
-            const int w = (launch & 7) * (total >> 3) + (launch >> 3);   // XCD-major position
-            by = w / (int)gridDim.x;
-            bx = w - by * (int)gridDim.x;
-        }
-    }
+    int bx, by;
+    order.place(bx, by);
     const int tile0 = bx * kFusedTiles;
     constexpr int NPASS = WIDE ? 2 : 1;
     const int k0 = by * (kFusedFilters * NPASS);
@@ -197,25 +183,28 @@ __device__ __forceinline__ void fused_conv_body(const int8_t* __restrict__ x, co
     }
 }
 
+// (with a single channel block the planes are small and the order made no difference)
+inline GridOrder order_of(dim3 grid, const Problem& p) { return grid_order(grid, p.CB >= 2 ? 5 : ~0u); }
+
 template <int LAYOUT, int LOAD, int MODE, bool SUMS, bool WIDE>
 __global__ __launch_bounds__(256) void fused_conv_kernel(const int8_t* __restrict__ x,
                                                          const uint8_t* __restrict__ blob, size_t table_off,
-                                                         size_t planes_off, int32_t* __restrict__ y, Problem p) {
-    fused_conv_body<LAYOUT, LOAD, MODE, SUMS, WIDE, false>(x, blob, table_off, planes_off, y, p, Int8Epilogue{});
+                                                         size_t planes_off, int32_t* __restrict__ y, Problem p, GridOrder order) {
+    fused_conv_body<LAYOUT, LOAD, MODE, SUMS, WIDE, false>(x, blob, table_off, planes_off, y, p, Int8Epilogue{}, order);
 }
 
 template <int LAYOUT, int LOAD, int MODE, bool SUMS, bool WIDE>
 __global__ __launch_bounds__(256) void fused_conv_int8_kernel(const int8_t* __restrict__ x,
                                                               const uint8_t* __restrict__ blob, size_t table_off,
-                                                              size_t planes_off, Problem p, Int8Epilogue q8) {
-    fused_conv_body<LAYOUT, LOAD, MODE, SUMS, WIDE, true>(x, blob, table_off, planes_off, nullptr, p, q8);
+                                                              size_t planes_off, Problem p, Int8Epilogue q8, GridOrder order) {
+    fused_conv_body<LAYOUT, LOAD, MODE, SUMS, WIDE, true>(x, blob, table_off, planes_off, nullptr, p, q8, order);
 }
 
 template <int LAYOUT, int LOAD, int MODE, bool SUMS>
 __global__ __launch_bounds__(256) void fused_conv_u8_kernel(const int8_t* __restrict__ x, ZeroPointU8 zero,
                                                             const uint8_t* __restrict__ blob, size_t table_off,
-                                                            size_t planes_off, int32_t* __restrict__ y, Problem p) {
-    fused_conv_body<LAYOUT, LOAD, MODE, SUMS, false, false, ZeroPointU8>(x, blob, table_off, planes_off, y, p, Int8Epilogue{}, zero);
+                                                            size_t planes_off, int32_t* __restrict__ y, Problem p, GridOrder order) {
+    fused_conv_body<LAYOUT, LOAD, MODE, SUMS, false, false, ZeroPointU8>(x, blob, table_off, planes_off, y, p, Int8Epilogue{}, order, zero);
 }
 
 template <int LAYOUT, int LOAD, int MODE, bool SUMS, bool WIDE, bool Q8>
@@ -226,11 +215,11 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
                             : reinterpret_cast<const void*>(&fused_conv_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE>);
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(kernel, lds_bytes)) return e;
-    dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / (kFusedFilters * (WIDE ? 2 : 1)));
+    dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters * (WIDE ? 2 : 1)));
     if constexpr (Q8)
-        fused_conv_int8_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE><<<grid, 256, lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, p, q8);
+        fused_conv_int8_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE><<<grid, 256, lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, p, q8, order_of(grid, p));
     else
-        fused_conv_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE><<<grid, 256, lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p);
+        fused_conv_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE><<<grid, 256, lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, order_of(grid, p));
     return hipGetLastError();
 }
 
@@ -241,7 +230,7 @@ hipError_t launch_mode(const int8_t* x, const uint8_t* blob, const BlobLayout& b
     // compute units (Kp is a multiple of 64).  Only the direct-transfer variants have the
     // registers for it (the others hold a patch in registers across the product phase).
     if constexpr (LOAD == kLoadDirect) {
-        const long long workgroups = (long long)ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters);
+        const long long workgroups = (long long)ceil_div(p.T, kFusedTiles) * ceil_div(p.K, kFusedFilters);
         if (workgroups > compute_units()) {
             if (mode == WG_LOSSLESS) return launch<LAYOUT, LOAD, WG_LOSSLESS, false, true, Q8>(x, blob, bl, y, p, q8, s);
             // scaled mode keeps channel sums here also for a single channel block: the variant that
@@ -456,7 +445,7 @@ hipError_t launch_act_scaled(const int8_t* x, const uint8_t* blob, const BlobLay
                              hipStream_t s) {
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_act_scaled_kernel<LAYOUT, LOAD>), kActLdsBytes)) return e;
-    dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / kFusedFilters);
+    dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters));
     fused_conv_act_scaled_kernel<LAYOUT, LOAD><<<grid, 256, kActLdsBytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, act_table, p);
     return hipGetLastError();
 }
@@ -466,8 +455,8 @@ hipError_t launch_u8(const int8_t* x, ZeroPointU8 zero, const uint8_t* blob, con
                      hipStream_t s) {
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_u8_kernel<LAYOUT, LOAD, MODE, SUMS>), kLdsBytes)) return e;
-    dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / kFusedFilters);
-    fused_conv_u8_kernel<LAYOUT, LOAD, MODE, SUMS><<<grid, 256, kLdsBytes, s>>>(x, zero, blob, bl.table_off, bl.planes_off, y, p);
+    dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters));
+    fused_conv_u8_kernel<LAYOUT, LOAD, MODE, SUMS><<<grid, 256, kLdsBytes, s>>>(x, zero, blob, bl.table_off, bl.planes_off, y, p, order_of(grid, p));
     return hipGetLastError();
 }
 
@@ -518,7 +507,7 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
     // a test hook asks for one kernel (lossless mode: the split is the limb-pair form as well)
     const bool hooked = g_stream_workgroups.load(std::memory_order_relaxed) > 0 || g_stream_variant.load(std::memory_order_relaxed) != 0 ||
                         g_scaled_variant.load(std::memory_order_relaxed) != 0 || (mode == WG_LOSSLESS && lossless_variant() != 0);
-    const int workgroups = ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters);
+    const int workgroups = ceil_div(p.T, kFusedTiles) * ceil_div(p.K, kFusedFilters);
     const bool may_split = p.CB >= 2 && 2 * workgroups <= compute_units() && !is_unsigned && !hooked;
     const int blocks = may_split ? ceil_div(p.CB, std::min(p.CB, compute_units() / workgroups)) : p.CB, splits = ceil_div(p.CB, blocks);
     auto split = [&](bool pieces) {
@@ -580,12 +569,15 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
     // The streaming form when every workgroup gets at least six tile blocks to stream over (measured: +10-17 % on the
     // large layers; with fewer, the fill and drain of its pipeline cost more than the overlap saves), or when a test asks
     // for it.
-    const int tile_blocks = ceil_div(p.T, kFusedTiles), filter_blocks = p.Kp / kFusedFilters;
+    const int tile_blocks = ceil_div(p.T, kFusedTiles), filter_blocks = ceil_div(p.K, kFusedFilters);
     // The 64-filter form of that kernel (see below for when it applies) is also the fastest form for a layer with one
     // channel block as soon as the 32-filter grid exceeds one round of the compute units, whatever the number of tile
     // blocks per workgroup (56x56x64 at N = 12 .. 48: 8-30 % ahead of the limb-pair and 64-filter four-wave kernels).
     const int stream_variant = g_stream_variant.load(std::memory_order_relaxed);
     const bool whole64 = (p.K & 63) == 0 || (p.K & 63) > 32;   // padding to 64 filters adds no 32-filter block of nothing
+    const int variant = g_scaled_variant.load(std::memory_order_relaxed);
+    const long long cus = compute_units(), w32 = (long long)tile_blocks * filter_blocks;
+    const long long wide_grid = (long long)tile_blocks * ceil_div(p.K, 2 * kFusedFilters);
     const bool wide_one_block = p.CB == 1 && whole64 && stream_variant == 0 && (long long)tile_blocks * filter_blocks > compute_units();
     // One channel block, a 32-filter grid of at most one round: the streaming kernel's 32-filter form with one tile block
     // per workgroup (its eight waves: four transform, four multiply) is 10-14 % ahead of the four-wave kernel in scaled
@@ -593,6 +585,31 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
     // this kind; the others come here, too.
     const bool forced_stream = g_stream_workgroups.load(std::memory_order_relaxed) > 0;
     const bool pair_layer = mode == WG_LOSSLESS && c.zero == nullptr && c.layout == WG_NHWC;
+    // K mod 64 = 1 .. 32 and more than one round of 32-filter workgroups: 64-filter workgroups multiply a 32-filter block of
+    // nothing in every tile block, 32-filter ones transform twice as often.  Which costs more is a matter of rounds: the streaming
+    // forms take, for one channel block, us (K = 32 .. 288, 14 - 2500 workgroups, off by 5 % at most)
+    //   32 filters, r rounds: 5.0 + 3.65 r scaled, 4.4 + 4.25 r lossless; 64 filters: 4.8 + 5.5 r, 4.3 + 6.15 r;
+    //   the limb-pair kernel 1.0 + 5.9 r; the form with eight product waves, scaled, a single round: 9
+    // and with several blocks 32-filter rounds take 1 / 1.34 of those with eight product waves (C = 128, scaled: 32 filters 15.6
+    // and 22.0 for two and three rounds, 64 filters 11.4, 20.4, 30.4 for one to three; lossless 18.0, 25.3 / 13.8, 23.5, 33.8).
+    // (64 -> 32 filters, 28x28, N = 162, scaled: 34 -> 15.6 us, lossless N = 490 60 -> 30; 128 -> 32, N = 162, 30.2 -> 22.0.)
+    if (!whole64 && w32 > cus && stream_variant == 0 && variant == 0 && !forced_stream && lossless_variant() != 1) {
+        const int r32 = ceil_div(tile_blocks, std::max(1, (int)cus / filter_blocks)), r64 = (int)((wide_grid + cus - 1) / cus);
+        if (p.CB > 1) {
+            if (100 * r32 < 134 * r64) {
+                status = launch_stream(c, mode, kStreamHalves, s);
+                return true;
+            }
+        } else {
+            const bool scaled = mode == WG_SCALED;
+            const double halves = scaled ? 5.0 + 3.65 * r32 : 4.4 + 4.25 * r32, whole = scaled ? 4.8 + 5.5 * r64 : 4.3 + 6.15 * r64;
+            const bool pairs = pair_layer && lossless_pair_conv_choice(c.x, p, c.layout) != 0;
+            const double other = scaled ? (r64 == 1 ? 9.0 : 1e9) : pairs ? 1.0 + 5.9 * (double)((w32 + cus - 1) / cus) : 1e9;
+            if (other < halves && other < whole) status = scaled ? launch_roles(c, mode, true, s) : launch_lossless_pair_conv(c.x, c.blob, c.y, p, c.layout, c.q8, s);
+            else                                 status = launch_stream(c, mode, halves < whole ? kStreamHalves : kStreamWhole, s);
+            return true;
+        }
+    }
     const bool narrow_one_round = !pair_layer && p.CB == 1 && stream_variant == 0 && !forced_stream &&
                                   (long long)tile_blocks * filter_blocks <= compute_units();
     const bool streams = forced_stream || wide_one_block || narrow_one_round ||
@@ -603,7 +620,6 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
     // per workgroup (a grid of at most one round) and 11.7 us with 64 filters.
     if (pair_layer && !streams) {
         const int form = lossless_pair_conv_choice(c.x, p, c.layout);   // 0: not applicable or switched off, 1: the library decides, 2: forced
-        const long long w32 = (long long)tile_blocks * filter_blocks, cus = compute_units();
         const double pair_cost = 6.5 * (double)((w32 + cus - 1) / cus);
         const double here_cost = w32 <= cus ? 7.4 : 11.7 * (double)((w32 / 2 + cus - 1) / cus);
         if (form == 2 || (form == 1 && p.CB == 1 && pair_cost < here_cost)) {
@@ -619,8 +635,6 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
     // there are two or more channel blocks.  Lossless mode (twice the matrix-core work and filter bytes per product):
     // +10-25 % with two or more channel blocks where the layer is too small to stream; where it streams, the streaming
     // kernel's 64-filter form is level (two blocks) or 4 % ahead (four blocks) and takes the layer.
-    const int variant = g_scaled_variant.load(std::memory_order_relaxed);
-    const long long wide_grid = (long long)tile_blocks * (p.Kp / (2 * kFusedFilters));
     // scaled mode also with one channel block, where the 64-filter grid is a single round and the 32-filter grid is not
     // (56x56x64 at N = 16: 11.4 -> 10.9 us against the streaming kernel's 64-filter form)
     const bool deep_enough = (p.CB >= 2 && (mode == WG_SCALED || !streams)) || (mode == WG_SCALED && wide_grid <= compute_units());
@@ -638,7 +652,7 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
         status = launch_stream(c, mode, kStreamEight, s);
         return true;
     }
-    if (variant == 1 || (variant == 0 && deep_enough && 2 * wide_grid > compute_units())) {
+    if (variant == 1 || (variant == 0 && deep_enough && w32 > cus)) {
         status = launch_roles(c, mode, true, s);
         return true;
     }
@@ -710,7 +724,7 @@ hipError_t launch_fused_conv_u8(const uint8_t* x_u8, int zero_point, const void*
 // kernels save there is less than a launch (a grid of one round, one block 11.5 - 13 us in one kernel, 15 - 16.5 in two, two
 // blocks 16.4 / 17.8, three 21 / 20; one block and 1.2 - 1.5 rounds 23 / 19).
 static bool one_act_scaled_kernel(const Problem& p, int layout) {
-    return layout == WG_NHWC && p.C % 4 == 0 && p.CB <= 2 && (long long)ceil_div(p.T, kFusedTiles) * (p.Kp / kFusedFilters) <= compute_units();
+    return layout == WG_NHWC && p.C % 4 == 0 && p.CB <= 2 && (long long)ceil_div(p.T, kFusedTiles) * ceil_div(p.K, kFusedFilters) <= compute_units();
 }
 
 static Plan plan_act_scaled(const Problem& p, int layout, size_t scratch_bytes) {

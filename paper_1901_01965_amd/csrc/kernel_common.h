@@ -25,6 +25,33 @@ struct LdsPlaneSink {
     }
 };
 
+// Workgroups are dealt to the eight XCDs (each with its own L2) in turn.  With five or more filter blocks, the order in which an
+// XCD runs consecutive tile blocks of as few filter blocks as possible, so that a filter block's operand planes enter one or two
+// L2s instead of all eight (several channel blocks: 272 -> 400 filters at 9x21, N = 32, scaled 20.5 -> 18.5 us, 336 -> 464 at
+// 20x10, N = 35, 33.5 -> 31.3; 166 -> 402 at 85x27, lossless, 19.3 -> 17.8).  With fewer, every XCD would read most of the activations
+// instead of an eighth, while all filters may lie in every L2: launch order (164 -> 67 filters at 27x27, N = 73, lossless 47.8 us in
+// the other, 42.6 in this one; 368 -> 64 at 31x31, N = 20, scaled 28.1, 25.2; 120 drawn layers of at most 256 filters 1.2 %).
+// (What it takes is worked out on the host: a division by gridDim.x, which is itself a load, stood before a workgroup's first
+// request and cost a 19 us kernel half a microsecond.)
+struct GridOrder {
+    int across;            // gridDim.x
+    uint32_t each, rest;   // workgroups per XCD, rounded down, and what is left; each = 0: launch order
+    FastDiv by_across;
+    __device__ inline void place(int& bx, int& by) const {
+        bx = blockIdx.x;
+        by = blockIdx.y;
+        if (each == 0) return;
+        const uint32_t launch = blockIdx.y * (uint32_t)across + blockIdx.x, xcd = launch & 7;
+        const uint32_t at = xcd * each + min(xcd, rest) + (launch >> 3);
+        by = (int)fast_div(at, by_across);
+        bx = (int)at - by * across;
+    }
+};
+inline GridOrder grid_order(dim3 grid, unsigned from = 5) {   // from: filter blocks
+    const uint32_t total = grid.x * grid.y;
+    return GridOrder{(int)grid.x, grid.y < from ? 0 : total >> 3, total & 7, make_fast_div(grid.x)};
+}
+
 // compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(<N-1>)
 template <class F, int... Is>
 __device__ inline void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {

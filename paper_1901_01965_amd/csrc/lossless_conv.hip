@@ -825,8 +825,8 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
                   const Int8Epilogue& q8, hipStream_t s, int blocks = 0, int splits = 1) {
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LAYOUT, LOAD, OUT>), kLdsBytes)) return e;
-    // sums are stored for every padded filter; otherwise a block of filters that do not exist has nothing to do
-    dim3 grid(ceil_div(p.T, kTileBlock), OUT == kOutSums ? p.Kp / kBlockFilters : ceil_div(p.K, kBlockFilters), splits);
+    // (of the padding to 64 filters, a block of 32 that do not exist has nothing to do: no sums of theirs are looked at)
+    dim3 grid(ceil_div(p.T, kTileBlock), ceil_div(p.K, kBlockFilters), splits);
     lossless_pair_kernel<LAYOUT, LOAD, OUT><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, blob, bl.pairs_off, y, p, q8, blocks);
     return hipGetLastError();
 }
@@ -890,7 +890,7 @@ hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t*
 
 hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits, hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
-    const dim3 grid(ceil_div(p.T, kTileBlock), p.Kp / kBlockFilters, splits);
+    const dim3 grid(ceil_div(p.T, kTileBlock), ceil_div(p.K, kBlockFilters), splits);
     auto go = [&](auto LOAD) -> hipError_t {
         static LdsLimitOnce lds_limit;   // per LOAD
         constexpr int lds_bytes = kPlanesBytes + 4 * kRawQuad;

@@ -31,22 +31,14 @@ namespace {
 template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
 __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                                          size_t table_off, size_t planes_off, int32_t* __restrict__ y,
-                                                                         Problem p, Int8Epilogue q8, ENC enc) {
+                                                                         Problem p, Int8Epilogue q8, ENC enc, GridOrder order) {
     static_assert(PW == 4 || PW == 8, "one or two product waves per SIMD");
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int lane = threadIdx.x & 63, wave8 = threadIdx.x >> 6;
     const bool transforms = wave8 < 4;
     const int tid = threadIdx.x & 255, wave = wave8 & 3;   // within the role (PW = 8: within the four waves that store together)
-    int bx = blockIdx.x, by = blockIdx.y;
-    {
-        const int total = gridDim.x * gridDim.y;
-        if (gridDim.y >= 2 && (total & 7) == 0) {   // XCD-major order, as in fused_conv_body
-            const int launch = blockIdx.y * gridDim.x + blockIdx.x;
-            const int w = (launch & 7) * (total >> 3) + (launch >> 3);
-            by = w / (int)gridDim.x;
-            bx = w - by * (int)gridDim.x;
-        }
-    }
+    int bx, by;
+    order.place(bx, by);
     const int tile0 = bx * kFusedTiles, k0 = by * (kFusedFilters * (PW / 4));
     // requested first, compared by either role before it goes on from what does not depend on the blob (uniform: nobody reaches a
     // barrier otherwise): compared up here, field by field, it stood before the first patch (28x28x128 N = 32 13.60 -> 13.21 us,
@@ -181,9 +173,9 @@ hipError_t launch_roles(const int8_t* x, const ENC& enc, const uint8_t* blob, co
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC>), lds_bytes)) return e;
-    dim3 grid(ceil_div(p.T, kFusedTiles), p.Kp / (kFusedFilters * (PW / 4)));   // Kp is a multiple of 64
+    dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters * (PW / 4)));
     fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC><<<grid, 64 * (4 + PW), lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, q8,
-                                                                                             enc);
+                                                                                             enc, grid_order(grid));
     return hipGetLastError();
 }
 

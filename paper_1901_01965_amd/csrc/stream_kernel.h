@@ -68,26 +68,21 @@ template <int FORM> constexpr int stream_product_waves() { return FORM == kStrea
 template <int LAYOUT, int MODE, bool Q8, int FORM, class ENC>
 __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused_conv_stream_kernel(
     const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t table_off, size_t planes_off, int32_t* __restrict__ y, Problem p,
-    Int8Epilogue q8, int tile_blocks, ENC enc) {
+    Int8Epilogue q8, int tile_blocks, ENC enc, GridOrder order) {
     constexpr int PW = stream_product_waves<FORM>();
     constexpr bool OWN_BARRIER = FORM == kStreamEight;
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int lane = threadIdx.x & 63, wave8 = threadIdx.x >> 6;
     const bool transforms = wave8 < 4;
     const int tid = threadIdx.x & 255, wave = wave8 & 3;   // within the role
-    int bx = blockIdx.x, by = blockIdx.y;
-    if (const int total = gridDim.x * gridDim.y; gridDim.y >= 2 && (total & 7) == 0) {   // XCD-major order, as in fused_conv_body
-        const int launch = blockIdx.y * gridDim.x + blockIdx.x;
-        const int w = (launch & 7) * (total >> 3) + (launch >> 3);
-        by = w / (int)gridDim.x;
-        bx = w - by * (int)gridDim.x;
-    }
+    int bx, by;
+    order.place(bx, by);
     const int k0 = by * stream_filters<FORM>();
     // requested first, compared by either role before it goes on from what does not depend on the blob (see fused_conv_roles_kernel)
     const BlobHeaderWords header = read_blob_header(blob);
     auto matches = [&] { return blob_matches(header, p.K, p.Cf, MODE, ENC::kMagic); };
     // this workgroup's tile blocks: bx, bx + gridDim.x, ...
-    const int my_blocks = (tile_blocks - bx + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int my_blocks = (tile_blocks - bx + order.across - 1) / order.across;
     const int units = my_blocks * p.CB;
     const int rnd = MODE == WG_SCALED ? 8 : 0;
 #ifdef WG_TIMESTAMPS
@@ -159,7 +154,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
                 among_us.sync(lane);   // every transform wave has read its share before any of them writes planes
             }
             WG_SPENT(1, mark);   // flush
-            const int tb = bx + jb * (int)gridDim.x;
+            const int tb = bx + jb * order.across;
             const bool last0 = u < units && cb == p.CB - 1;
             if (u < units) {
                 out.sink.base = slot + (u & 1) * kLdsBytes;
@@ -172,7 +167,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
                 if (++cb == p.CB) { cb = 0; ++jb; }
                 bias = next_bias;
                 if (more) {
-                    if (cb == 0) enter_tile_block(bx + jb * (int)gridDim.x);
+                    if (cb == 0) enter_tile_block(bx + jb * order.across);
                     loader.drop_absent_channels(p, cb, lane);
                 }
                 bias.apply(loader.patch);
@@ -344,10 +339,10 @@ hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC>), lds_bytes)) return e;
-    const int tile_blocks = ceil_div(c.p.T, kFusedTiles), filter_blocks = c.p.Kp / stream_filters<FORM>();   // Kp is a multiple of 64
-    const int gx = stream_workgroups(tile_blocks, filter_blocks);
-    fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC><<<dim3(gx, filter_blocks), 64 * (4 + stream_product_waves<FORM>()), lds_bytes, s>>>(
-        c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y, c.p, c.q8, tile_blocks, enc);
+    const int tile_blocks = ceil_div(c.p.T, kFusedTiles), filter_blocks = ceil_div(c.p.K, stream_filters<FORM>());
+    const dim3 grid(stream_workgroups(tile_blocks, filter_blocks), filter_blocks);
+    fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC><<<grid, 64 * (4 + stream_product_waves<FORM>()), lds_bytes, s>>>(
+        c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y, c.p, c.q8, tile_blocks, enc, grid_order(grid));
     return hipGetLastError();
 }
 

@@ -1,0 +1,51 @@
+"""Filter counts that fill a 64-filter block at most half, on grids of one and of several rounds of the compute units (the
+library's own choice of form), and grids whose size is no multiple of the eight XCDs.  Bit for bit against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1901_01965_amd as wg
+from paper_1901_01965_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+SHAPES = [  # N, C, K, H, W
+    (1, 16, 16, 260, 260),    # one channel block, 265 workgroups of 32 filters
+    (1, 16, 96, 190, 190),    # 144 tile blocks: 432 workgroups of 32 filters, 288 of 64
+    (1, 12, 161, 96, 96),     # a single round of 64 filters, 216 of 32 (one filter in the last block)
+    (1, 72, 32, 260, 259),    # two channel blocks
+    (1, 72, 96, 150, 150),    # 91 tile blocks
+    (1, 72, 330, 96, 96),     # 216 workgroups of 64 filters
+    (3, 72, 330, 9, 9),       # 22 of 32
+    (1, 264, 80, 20, 36),     # split channels
+]
+
+
+@pytest.mark.parametrize("mode", ["lossless", "scaled"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_equals_oracle(shape, mode):
+    N, C, K, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, act="relu", wgt="gauss", seed=8)
+    want = oracle.direct_conv2d(x, g) if mode == "lossless" else oracle.winograd_conv2d(x, g, oracle.SCALED, 127)[0]
+    packed = wg.winograd_filter_transform(_dev(wl.to_krsc(g)), wg.NHWC, wg.LOSSLESS if mode == "lossless" else wg.SCALED)
+    xd = _dev(wl.to_nhwc(x))
+    y = wg.winograd_conv2d_int8(xd, packed, wg.NHWC)
+    assert np.array_equal(wl.from_nhwc(y.cpu().numpy()), want)
+    q = wg.winograd_conv2d_int8_requant(xd, packed, 10, True, False, wg.NHWC)
+    assert np.array_equal(wl.from_nhwc(q.cpu().numpy()), oracle.requant_relu_pool(want, 10, True, False))
+
+
+@pytest.mark.parametrize("shape", [(1, 72, 16, 40, 33), (2, 40, 97, 30, 30), (1, 130, 330, 22, 18)])
+def test_activations_scaled_as_well(shape):
+    N, C, K, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, act="relu", wgt="gauss", seed=9)
+    want = oracle.winograd_conv2d(x, g, oracle.BOTH_SCALED, 127)[0]
+    packed = wg.winograd_filter_transform(_dev(wl.to_krsc(g)), wg.NHWC, wg.SCALED)
+    y = wg.winograd_conv2d_int8_act_scaled(_dev(wl.to_nhwc(x)), packed, wg.NHWC)
+    assert np.array_equal(wl.from_nhwc(y.cpu().numpy()), want)
