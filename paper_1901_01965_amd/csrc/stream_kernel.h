@@ -78,9 +78,9 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
     int bx, by;
     order.place(bx, by);
     const int k0 = by * stream_filters<FORM>();
-    // requested first, compared by either role before it goes on from what does not depend on the blob (see fused_conv_roles_kernel)
-    const BlobHeaderWords header = read_blob_header(blob);
-    auto matches = [&] { return blob_matches(header, p.K, p.Cf, MODE, ENC::kMagic); };
+    // looked at by either role before it goes on from what does not depend on the blob (see fused_conv_roles_kernel; held in
+    // scalar registers from the start, as there, it cost 56x56x64 N = 256 two of 95 us)
+    auto matches = [&] { return blob_matches(reinterpret_cast<const BlobHeader*>(blob), p.K, p.Cf, MODE, ENC::kMagic); };
     // this workgroup's tile blocks: bx, bx + gridDim.x, ...
     const int my_blocks = (tile_blocks - bx + order.across - 1) / order.across;
     const int units = my_blocks * p.CB;
