@@ -10,11 +10,13 @@ namespace wg {
 namespace {
 
 // ---- factors ---------------------------------------------------------------------------------------------
-// grid: ceil(T / 4), 64 CB threads: wave = 64-channel block, lane = (tile, four channels).  Bound by the latency of one patch
-// load and one transform.
+// grid: ceil(T / 4), 64 CB threads: wave = 64-channel block, lane = (tile, four channels).  Bound by latency: a patch load, a
+// transform, a reduction.  The factor table comes to LDS beside the patch (looked up in memory it was a second trip after the
+// reduction), and the reduction over a tile's sixteen lanes stays in the vector ALU.
 __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                            uint32_t* __restrict__ factors, int32_t* __restrict__ act_table, Problem p) {
     __shared__ int maxima[4 * kEntries];
+    __shared__ uint32_t table[kActMax + 1];
     const int tid = threadIdx.x, lane = tid & 63, cb = tid >> 6;
     const BlobHeaderWords header = read_blob_header(blob);
     const int tile = PatchLoader::tile_of(0, lane), t = blockIdx.x * 4 + tile, cq = PatchLoader::quad_of(lane);
@@ -24,6 +26,7 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
     loader.enter(p, n, ty, tx, lane);
     loader.drop_absent_channels(p, cb, lane);
     loader.request(activation_buffer(x, p), cb);
+    for (int i = tid; i <= kActMax; i += blockDim.x) table[i] = kActScale.v[i];
     for (int i = tid; i < 4 * kEntries; i += blockDim.x) maxima[i] = 0;
     __syncthreads();
     s16x2 mx[kEntries];
@@ -34,9 +37,13 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
 #pragma unroll
     for (int j = 0; j < kEntries / 2; ++j) {
         s16x2 m = {max(mx[2 * j].x, mx[2 * j].y), max(mx[2 * j + 1].x, mx[2 * j + 1].y)};
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1)
-            m = __builtin_elementwise_max(m, as_s16x2((uint32_t)__shfl_xor((int)as_u32(m), off)));
+        auto with_row_rotated = [&](auto by) {   // by 8, 4, 2, 1 lanes within the sixteen
+            m = __builtin_elementwise_max(m, as_s16x2((uint32_t)__builtin_amdgcn_update_dpp(0, (int)as_u32(m), 0x120 + by, 0xf, 0xf, false)));
+        };
+        with_row_rotated(std::integral_constant<int, 8>{});
+        with_row_rotated(std::integral_constant<int, 4>{});
+        with_row_rotated(std::integral_constant<int, 2>{});
+        with_row_rotated(std::integral_constant<int, 1>{});
         if (cq == j) {
             atomicMax(&maxima[tile * kEntries + 2 * j], (int)m.x);
             atomicMax(&maxima[tile * kEntries + 2 * j + 1], (int)m.y);
@@ -47,7 +54,7 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
     for (int i = tid; i < 4 * kEntries; i += blockDim.x) {
         const size_t at = (size_t)blockIdx.x * 4 * kEntries + i;   // [tile][entry]
         if (at >= (size_t)p.T * kEntries) break;
-        const uint32_t entry = kActScale.v[min(maxima[i], kActMax)];
+        const uint32_t entry = table[min(maxima[i], kActMax)];
         factors[at] = entry;
         if (act_table != nullptr) *reinterpret_cast<v4i*>(act_table + 4 * at) = act_table_row(entry);
     }
@@ -97,6 +104,9 @@ struct ActProducts {
     }
     // The filter's reverse scaling, then the tile's (register q of a lane belongs to tile 4 (lane / 16) + q), and the output
     // transform.
+    // NARROW: no channel sum exceeds 23 bits (see launch_act_scaled_roles), so the filter's scaling is a 24-bit multiply-add and a
+    // shift.  The tile's factors come as rounding << 16 | r << 8 | q: the funnel shift looks at the low five bits only.
+    template <bool NARROW>
     __device__ inline void finish(const LaneContext& cx, const uint32_t* rq_tab, int lane, v4i (&Y)[16]) const {
         v4i er[6], ei[6];
         static_for<NE>([&](auto S) {
@@ -107,11 +117,12 @@ struct ActProducts {
                 re -= acc[v + 2];
                 im = acc[v + 1];
             }
-            const ReverseScale filter_side = parked_scale<S>(cx);
+            const ReverseScale by_filter = parked_scale<S>(cx);
+            auto filter_side = [&](int m) { return NARROW ? (__mul24(m, by_filter.r) + by_filter.rnd) >> by_filter.q : by_filter(m); };
             const v4i rq = *reinterpret_cast<const v4i*>(rq_tab + sl.entry * 16 + 4 * (lane >> 4));
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const ReverseScale tile_side((int)(((uint32_t)rq[q] >> 16) & 255u), (int)((uint32_t)rq[q] >> 24));
+                const ReverseScale tile_side((rq[q] >> 8) & 255, rq[q], (int)((uint32_t)rq[q] >> 16));
                 re[q] = tile_side(filter_side(re[q]));
                 if constexpr (!is_real(sl.entry)) im[q] = tile_side(filter_side(im[q]));
             }
@@ -130,7 +141,7 @@ static_assert(2 * kActPlaneBuffer <= kLdsBytes && act_lds_bytes<8>() <= 160 * 10
 
 // grid (ceil(T/16), Kp/(8 PW)), 64 (4 + PW) threads: the roles of fused_conv_roles_kernel (roles_kernel.h): waves 0-3 transform one
 // channel block ahead, the others multiply; product wave pw owns filter block pw % (PW / 2) and half pw / (PW / 2) of the entries.
-template <int LAYOUT, int PW>
+template <int LAYOUT, int PW, bool NARROW>
 __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
                                                                          size_t table_off, size_t planes_off, int32_t* __restrict__ y,
                                                                          const uint32_t* __restrict__ factors, Problem p, GridOrder order) {
@@ -149,7 +160,8 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
             const int tile = i / kEntries, e = i - tile * kEntries;
             const uint32_t entry = tile0 + tile < p.T ? factors[(size_t)tile0 * kEntries + i] : 0x00010000u;
             np_tab[i] = act_factors(entry);
-            rq_tab[e * 16 + tile] = entry;
+            const uint32_t r = (entry >> 16) & 255u, q = entry >> 24;
+            rq_tab[e * 16 + tile] = ((1u << q) >> 1) << 16 | r << 8 | q;
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
@@ -224,7 +236,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) Y[i] = (v4i){0, 0, 0, 0};
-        products.finish(cx, rq_tab, lane, Y);
+        products.template finish<NARROW>(cx, rq_tab, lane, Y);
     };
     if (half == 0) blocks(std::integral_constant<int, 0>{}); else blocks(std::integral_constant<int, 1>{});
     StoreContext sc;
@@ -248,12 +260,12 @@ hipError_t launch_act_factors(const RolesCall& c, uint32_t* factors, int32_t* ac
 hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, hipStream_t s) {
     // 64 filters per workgroup unless 32 fill the compute units in one round, or in so few rounds that a half-empty 64-filter block
     // costs more (see run_roles in fused_conv.hip)
-    auto go = [&](auto L, auto W) -> hipError_t {
+    auto go = [&](auto L, auto W, auto NARROW) -> hipError_t {
         constexpr int PW = W;
         static LdsLimitOnce lds_limit;   // per instance
-        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW>), act_lds_bytes<PW>())) return e;
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW, NARROW>), act_lds_bytes<PW>())) return e;
         const dim3 grid(ceil_div(c.p.T, kFusedTiles), ceil_div(c.p.K, 8 * PW));
-        act_scaled_roles_kernel<L, PW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y,
+        act_scaled_roles_kernel<L, PW, NARROW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y,
                                                                                       factors, c.p, grid_order(grid));
         return hipGetLastError();
     };
@@ -261,9 +273,13 @@ hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, 
     const int tile_blocks = ceil_div(c.p.T, kFusedTiles), cus = compute_units();
     auto rounds = [&](int filters) { return ((long long)tile_blocks * ceil_div(c.p.K, filters) + cus - 1) / cus; };
     const bool wide = rounds(32) > 1 && 100 * rounds(32) >= 134 * rounds(64);
+    // a channel sum is at most 2 x 127 x 127 C (Re = Dr Wr - Di Wi), r at most 255
+    const bool narrow = 2ll * 127 * 127 * c.p.Cf < 1 << 23;
+    static_assert(((1ll << 23) - 1) * 255 + 64 < 1ll << 31, "a narrow sum times r, rounded, fits int32");
+    auto form = [&](auto L, auto W) { return narrow ? go(L, W, std::true_type{}) : go(L, W, std::false_type{}); };
     if (c.layout == WG_NHWC)
-        return wide ? go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NHWC>{}, integral_constant<int, 4>{});
-    return wide ? go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 8>{}) : go(integral_constant<int, WG_NCHW>{}, integral_constant<int, 4>{});
+        return wide ? form(integral_constant<int, WG_NHWC>{}, integral_constant<int, 8>{}) : form(integral_constant<int, WG_NHWC>{}, integral_constant<int, 4>{});
+    return wide ? form(integral_constant<int, WG_NCHW>{}, integral_constant<int, 8>{}) : form(integral_constant<int, WG_NCHW>{}, integral_constant<int, 4>{});
 }
 
 }  // namespace wg
