@@ -24,6 +24,12 @@ HIPCC_FLAGS = [
     "-Wall", "-Wno-unused-function",
 ]
 
+# A kernel's leading scalar arguments are in registers when a wave starts (WG_GEOMETRY_PARAMS).  Not in the one-tile-block
+# role-specialised kernels, which are slower with it (512 -> 512 at 7x7, N = 64: 19.8 -> 20.1 us, uint8 128 -> 128 at 28x28, N = 32:
+# 13.3 -> 13.6; signed int8 level).
+PRELOAD_FLAGS = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
+NOT_PRELOADED = ("roles_scaled.hip", "roles_lossless.hip")
+
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
@@ -70,7 +76,8 @@ def build(verbose=False, incremental=False, jobs=None):
         fresh = (incremental and os.path.exists(obj) and
                  os.path.getmtime(obj) > max(os.path.getmtime(src), newest_header))
         if not fresh:
-            todo.append([hipcc] + HIPCC_FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", src, "-o", obj])
+            preload = [] if os.path.basename(src) in NOT_PRELOADED else PRELOAD_FLAGS
+            todo.append([hipcc] + HIPCC_FLAGS + preload + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", src, "-o", obj])
     ext_obj = os.path.join(OBJ_DIR, "torch_binding.o")
     ext_compile, ext_link = _extension_commands(ext_obj)
     if not (incremental and os.path.exists(ext_obj) and os.path.getmtime(ext_obj) > max(os.path.getmtime(EXT_SOURCE), newest_header)):

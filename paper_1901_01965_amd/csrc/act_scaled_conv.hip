@@ -13,8 +13,9 @@ namespace {
 // grid: ceil(T / 4), 64 CB threads: wave = 64-channel block, lane = (tile, four channels).  Bound by latency: a patch load, a
 // transform, a reduction.  The factor table comes to LDS beside the patch (looked up in memory it was a second trip after the
 // reduction), and the reduction over a tile's sixteen lanes stays in the vector ALU.
-__global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
+__global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, const uint8_t* __restrict__ blob,
                                                            uint32_t* __restrict__ factors, int32_t* __restrict__ act_table, Problem p) {
+    WG_TAKE_GEOMETRY(p, 2);
     __shared__ int maxima[4 * kEntries];
     __shared__ uint32_t table[kActMax + 1];
     const int tid = threadIdx.x, lane = tid & 63, cb = tid >> 6;
@@ -142,13 +143,15 @@ static_assert(2 * kActPlaneBuffer <= kLdsBytes && act_lds_bytes<8>() <= 160 * 10
 // grid (ceil(T/16), Kp/(8 PW)), 64 (4 + PW) threads: the roles of fused_conv_roles_kernel (roles_kernel.h): waves 0-3 transform one
 // channel block ahead, the others multiply; product wave pw owns filter block pw % (PW / 2) and half pw / (PW / 2) of the entries.
 template <int LAYOUT, int PW, bool NARROW>
-__global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
+__global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS,
+                                                                         WG_ORDER_PARAMS, const uint8_t* __restrict__ blob,
                                                                          size_t table_off, size_t planes_off, int32_t* __restrict__ y,
-                                                                         const uint32_t* __restrict__ factors, Problem p, GridOrder order) {
+                                                                         const uint32_t* __restrict__ factors, Problem p) {
+    WG_TAKE_GEOMETRY(p, 2);
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int bx, by;
-    order.place(bx, by);
+    WG_TAKE_ORDER.place(bx, by);
     const int tile0 = bx * kFusedTiles, k0 = by * 8 * PW;
     const BlobHeaderWords header = read_blob_header(blob);   // compared by either role, see fused_conv_roles_kernel
     auto matches = [&] { return blob_matches(header, p.K, p.Cf, WG_SCALED); };
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
 }  // namespace
 
 hipError_t launch_act_factors(const RolesCall& c, uint32_t* factors, int32_t* act_table, hipStream_t s) {
-    act_factors_kernel<<<ceil_div(c.p.T, 4), 64 * c.p.CB, 0, s>>>(c.x, c.blob, factors, act_table, c.p);
+    act_factors_kernel<<<ceil_div(c.p.T, 4), 64 * c.p.CB, 0, s>>>(c.x, WG_GEOMETRY(c.p), c.blob, factors, act_table, c.p);
     return hipGetLastError();
 }
 
@@ -265,8 +268,9 @@ hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, 
         static LdsLimitOnce lds_limit;   // per instance
         if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW, NARROW>), act_lds_bytes<PW>())) return e;
         const dim3 grid(ceil_div(c.p.T, kFusedTiles), ceil_div(c.p.K, 8 * PW));
-        act_scaled_roles_kernel<L, PW, NARROW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y,
-                                                                                      factors, c.p, grid_order(grid));
+        const GridOrder order = grid_order(grid);
+        act_scaled_roles_kernel<L, PW, NARROW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(
+            c.x, WG_GEOMETRY(c.p), WG_ORDER(order), c.blob, c.bl.table_off, c.bl.planes_off, c.y, factors, c.p);
         return hipGetLastError();
     };
     using std::integral_constant;

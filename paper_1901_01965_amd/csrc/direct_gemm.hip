@@ -37,7 +37,8 @@ __host__ __device__ inline int halo_rows(int P, int W) { return (P + 2 * W + 2 +
 // grid: (ceil(pixels / P), ceil(K / F)), 64 WF WP threads.
 template <int LAYOUT, int WF, int WP, int PG>
 __global__ __launch_bounds__(64 * WF * WP) void direct_gemm_kernel(const int8_t* __restrict__ x, const int8_t* __restrict__ w,
-                                                                   int32_t* __restrict__ y, Problem p) {
+                                                                   int N, int C, int H, int W, int K, int32_t* __restrict__ y, Problem p) {
+    p.N = N; p.C = C; p.H = H; p.W = W; p.K = K;   // (in registers when a wave starts)
     constexpr int F = 64 * WF, P = 32 * PG * WP, T = 64 * WF * WP;
     constexpr int kTapBytes = 3 * F * kCBlock;
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
@@ -196,7 +197,7 @@ hipError_t launch(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&direct_gemm_kernel<LAYOUT, WF, WP, PG>), kLdsMost)) return e;
     const dim3 grid((unsigned)(((long long)p.N * p.H * p.W + f.P - 1) / f.P), ceil_div(p.K, f.F));
-    direct_gemm_kernel<LAYOUT, WF, WP, PG><<<grid, f.threads, lds_bytes(f, p), s>>>(x, w, y, p);
+    direct_gemm_kernel<LAYOUT, WF, WP, PG><<<grid, f.threads, lds_bytes(f, p), s>>>(x, w, p.N, p.C, p.H, p.W, p.K, y, p);
     return hipGetLastError();
 }
 template <int LAYOUT>

@@ -109,13 +109,14 @@ __device__ inline int unscale(int m, uint32_t rq) {
 // 16 w .. 16 w + 15 of the 16 tiles for all 16 entries.
 template <int LAYOUT, int MODE, bool Q8, bool NARROW, class ENC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f2_fast_kernel(
-    const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t table_off, size_t planes_off, int32_t* __restrict__ y,
-    Problem p, ENC enc, Int8Epilogue q8, GridOrder order) {
+    const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_ORDER_PARAMS, const uint8_t* __restrict__ blob, size_t table_off,
+    size_t planes_off, int32_t* __restrict__ y, Problem p, ENC enc, Int8Epilogue q8) {
+    WG_TAKE_GEOMETRY(p, 1);
     using Bytes = std::conditional_t<std::is_same_v<ENC, SignedInt8>, StoredInt8, BiasedBytes>;
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int bx, by;
-    order.place(bx, by);
+    WG_TAKE_ORDER.place(bx, by);
     const int tile0 = bx * kTiles, kbase = by * kFilters;
     const int a_tile = tid >> 4, cq = tid & 15;
     const __amdgpu_buffer_rsrc_t xbuf = Patch::buffer(x, p);
@@ -333,8 +334,9 @@ hipError_t launch_f2_fast(const int8_t* x, int is_unsigned, int zero_point, cons
     auto go = [&](auto L, auto M, auto Q, auto N, const auto& enc) -> hipError_t {
         using ENC = std::decay_t<decltype(enc)>;
         const dim3 grid(ceil_div(p.T, kTiles), p.Kp / kFilters);
-        f2_fast_kernel<L, M, Q, N, ENC><<<grid, 256, kLds, s>>>(x, static_cast<const uint8_t*>(blob), bl.table_off, bl.planes_off, y, p, enc, q8,
-                                                         grid_order(grid, 8));   // (with fewer filter blocks the launch order is as fast)
+        const GridOrder order = grid_order(grid, 8);   // (with fewer filter blocks the launch order is as fast)
+        f2_fast_kernel<L, M, Q, N, ENC><<<grid, 256, kLds, s>>>(x, WG_GEOMETRY(p), WG_ORDER(order), static_cast<const uint8_t*>(blob),
+                                                                bl.table_off, bl.planes_off, y, p, enc, q8);
         return hipGetLastError();
     };
     // a channel sum is at most C * 127 * (4 * 128, or 4 * 255 with a zero point)

@@ -37,6 +37,10 @@ struct GridOrder {
     int across;            // gridDim.x
     uint32_t each, rest;   // workgroups per XCD, rounded down, and what is left; each = 0: launch order
     FastDiv by_across;
+    __device__ inline GridOrder(uint32_t o_across, uint32_t o_each, uint32_t o_mul, uint32_t o_rest_shift)
+        : across((int)o_across), each(o_each), rest(o_rest_shift & 7), by_across{o_mul, o_rest_shift >> 3} {}
+    inline GridOrder(dim3 grid, unsigned from)   // from: filter blocks
+        : across((int)grid.x), each(grid.y < from ? 0 : grid.x * grid.y >> 3), rest(grid.x * grid.y & 7), by_across(make_fast_div(grid.x)) {}
     __device__ inline void place(int& bx, int& by) const {
         bx = blockIdx.x;
         by = blockIdx.y;
@@ -47,10 +51,11 @@ struct GridOrder {
         bx = (int)at - by * across;
     }
 };
-inline GridOrder grid_order(dim3 grid, unsigned from = 5) {   // from: filter blocks
-    const uint32_t total = grid.x * grid.y;
-    return GridOrder{(int)grid.x, grid.y < from ? 0 : total >> 3, total & 7, make_fast_div(grid.x)};
-}
+inline GridOrder grid_order(dim3 grid, unsigned from = 5) { return GridOrder(grid, from); }
+// as leading arguments (see WG_GEOMETRY_PARAMS, after which they fill what is loaded ahead)
+#define WG_ORDER_PARAMS uint32_t o_across, uint32_t o_each, uint32_t o_mul, uint32_t o_rest_shift
+#define WG_ORDER(o) (uint32_t)(o).across, (o).each, (o).by_across.mul, (o).rest | (o).by_across.shift << 3
+#define WG_TAKE_ORDER GridOrder(o_across, o_each, o_mul, o_rest_shift)
 
 // compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(<N-1>)
 template <class F, int... Is>

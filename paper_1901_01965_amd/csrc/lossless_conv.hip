@@ -476,10 +476,11 @@ struct RawPatch {
 // linear, so these add up to the whole; sums_finish_kernel adds, rescales and stores).
 constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2;
 template <int LAYOUT, int LOAD, int OUT>
-__global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
+__global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, const uint8_t* __restrict__ blob,
                                                             size_t pairs_off, int32_t* __restrict__ y, Problem p,
                                                             Int8Epilogue q8, int blocks) {
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
+    WG_TAKE_GEOMETRY(p, 2);
     constexpr bool Q8 = OUT == kOutInt8;
     const int cb_first = OUT == kOutSums ? (int)blockIdx.z * blocks : 0, cb_end = OUT == kOutSums ? min(cb_first + blocks, p.CB) : p.CB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -770,8 +771,9 @@ struct QuarterProducts {
 
 // grid (ceil(T/16), Kp/32, splits), 512 threads; sums: int32 [split][36][16 gridDim.x tiles][Kp].
 template <int LOAD>
-__global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t planes_off,
+__global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, const uint8_t* __restrict__ blob, size_t planes_off,
                                                           int32_t* __restrict__ sums, Problem p, int blocks) {
+    WG_TAKE_GEOMETRY(p, 2);
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tile0 = blockIdx.x * kTileBlock, k0 = blockIdx.y * kBlockFilters;
@@ -827,7 +829,7 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LAYOUT, LOAD, OUT>), kLdsBytes)) return e;
     // (of the padding to 64 filters, a block of 32 that do not exist has nothing to do: no sums of theirs are looked at)
     dim3 grid(ceil_div(p.T, kTileBlock), ceil_div(p.K, kBlockFilters), splits);
-    lossless_pair_kernel<LAYOUT, LOAD, OUT><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, blob, bl.pairs_off, y, p, q8, blocks);
+    lossless_pair_kernel<LAYOUT, LOAD, OUT><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, WG_GEOMETRY(p), blob, bl.pairs_off, y, p, q8, blocks);
     return hipGetLastError();
 }
 
@@ -895,7 +897,8 @@ hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, 
         static LdsLimitOnce lds_limit;   // per LOAD
         constexpr int lds_bytes = kPlanesBytes + 4 * kRawQuad;
         if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&scaled_sums_kernel<LOAD>), lds_bytes)) return e;
-        scaled_sums_kernel<LOAD><<<grid, 64 * kWaves, lds_bytes, s>>>(x, static_cast<const uint8_t*>(blob), bl.planes_off, sums, p, blocks);
+        scaled_sums_kernel<LOAD><<<grid, 64 * kWaves, lds_bytes, s>>>(x, WG_GEOMETRY(p), static_cast<const uint8_t*>(blob), bl.planes_off, sums, p,
+                                                                           blocks);
         return hipGetLastError();
     };
     using std::integral_constant;

@@ -91,9 +91,11 @@ __device__ inline int requantise_y16(int y16, int shift, int lo) {
 
 // grid: (ceil(T/tiles_per_wave), Kp/64), 64 threads.
 template <int MODE, bool Q8>
-__global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob,
+__global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, int tiles_per_wave,
+                                                         const uint8_t* __restrict__ blob,
                                                          size_t table_off, size_t narrow_off, int32_t* __restrict__ y,
-                                                         Problem p, Int8Epilogue q8, int tiles_per_wave) {
+                                                         Problem p, Int8Epilogue q8) {
+    WG_TAKE_GEOMETRY(p, 2);
     __shared__ uint4 values[kNarrowPieces * kNarrowTiles];   // [piece][tile]
     const int lane = threadIdx.x;
     const int tile0 = blockIdx.x * tiles_per_wave;
@@ -245,7 +247,7 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
     const long long work = (long long)p.T * (p.Kp / 64);
     const int tiles = (int)std::min<long long>(kNarrowTiles, std::max<long long>(2, (work + 2047) / 2048));
     dim3 grid(ceil_div(p.T, tiles), p.Kp / 64);
-    narrow_conv_kernel<MODE, Q8><<<grid, 64, 0, s>>>(x, blob, bl.table_off, bl.narrow_off, y, p, q8, tiles);
+    narrow_conv_kernel<MODE, Q8><<<grid, 64, 0, s>>>(x, WG_GEOMETRY(p), tiles, blob, bl.table_off, bl.narrow_off, y, p, q8);
     return hipGetLastError();
 }
 

@@ -67,8 +67,11 @@ template <int FORM> constexpr int stream_product_waves() { return FORM == kStrea
 
 template <int LAYOUT, int MODE, bool Q8, int FORM, class ENC>
 __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused_conv_stream_kernel(
-    const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t table_off, size_t planes_off, int32_t* __restrict__ y, Problem p,
-    Int8Epilogue q8, int tile_blocks, ENC enc, GridOrder order) {
+    const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_ORDER_PARAMS, const uint8_t* __restrict__ blob, size_t table_off,
+    size_t planes_off, int32_t* __restrict__ y, Problem p, Int8Epilogue q8, ENC enc) {
+    WG_TAKE_GEOMETRY(p, 2);
+    const GridOrder order = WG_TAKE_ORDER;
+    const int tile_blocks = (p.T + kFusedTiles - 1) / kFusedTiles;
     constexpr int PW = stream_product_waves<FORM>();
     constexpr bool OWN_BARRIER = FORM == kStreamEight;
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
@@ -341,8 +344,9 @@ hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC>), lds_bytes)) return e;
     const int tile_blocks = ceil_div(c.p.T, kFusedTiles), filter_blocks = ceil_div(c.p.K, stream_filters<FORM>());
     const dim3 grid(stream_workgroups(tile_blocks, filter_blocks), filter_blocks);
+    const GridOrder order = grid_order(grid);
     fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC><<<grid, 64 * (4 + stream_product_waves<FORM>()), lds_bytes, s>>>(
-        c.x, c.blob, c.bl.table_off, c.bl.planes_off, c.y, c.p, c.q8, tile_blocks, enc, grid_order(grid));
+        c.x, WG_GEOMETRY(c.p), WG_ORDER(order), c.blob, c.bl.table_off, c.bl.planes_off, c.y, c.p, c.q8, enc);
     return hipGetLastError();
 }
 

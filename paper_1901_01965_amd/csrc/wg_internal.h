@@ -64,8 +64,26 @@ __host__ __device__ inline void decode_tile(const Problem& p, int t, int& n, int
     ty = (int)row - n * p.TH;
 }
 
+__device__ inline void take_geometry(Problem& p, int N, int C, int H, int W, int log2_tile, FastDiv div_tw, FastDiv div_th) {
+    const int tile = 1 << log2_tile;
+    p.N = N; p.C = C; p.H = H; p.W = W;
+    p.TH = (H + tile - 1) >> log2_tile;
+    p.TW = (W + tile - 1) >> log2_tile;
+    p.T = N * p.TH * p.TW;
+    p.div_tw = div_tw;
+    p.div_th = div_th;
+}
+
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 inline size_t round_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
+
+// What a kernel's first loads depend on comes as its leading arguments: scalars at the front are in registers when a wave starts
+// (-amdgpu-kernarg-preload-count, fourteen dwords), while the rest of the arguments, a structure among them, takes a load that
+// misses every cache and stood before the first patch's request (56x56x64, N = 8, lossless 7.45 -> 7.15 us).
+#define WG_GEOMETRY_PARAMS int g_n, int g_c, int g_h, int g_w, uint32_t g_tw_mul, uint32_t g_tw_shift, uint32_t g_th_mul, uint32_t g_th_shift
+#define WG_GEOMETRY(p) (p).N, (p).C, (p).H, (p).W, (p).div_tw.mul, (p).div_tw.shift, (p).div_th.mul, (p).div_th.shift
+#define WG_TAKE_GEOMETRY(p, log2_tile) \
+    take_geometry(p, g_n, g_c, g_h, g_w, log2_tile, FastDiv{g_tw_mul, g_tw_shift}, FastDiv{g_th_mul, g_th_shift})
 
 inline Problem make_problem(int N, int C, int H, int W, int K) {
     Problem p;
