@@ -92,6 +92,21 @@ __device__ inline __amdgpu_buffer_rsrc_t activation_buffer(const int8_t* x, cons
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(x), 0, p.N * p.H * p.W * p.C, kRawBufferWord3);
 }
 
+// A 1 KB filter fragment, 16 bytes per lane: `base` is the same for the whole wave, `at` a constant, `lane16` = 16 x lane.  As a
+// buffer load it takes its address from scalar registers and one vector register; with 64-bit addresses every fourth fragment
+// cost two vector instructions and a pair of registers.
+__device__ inline v4i load_fragment(const int8_t* base, uint32_t lane16, int at) {
+    const __amdgpu_buffer_rsrc_t blob = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(base), 0, 0x7fffffff, kRawBufferWord3);
+    return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(blob, lane16, at, 0));
+}
+// The lane's number, formed anew where it is asked for: a register that is needed once per channel block is worth more than two
+// instructions there.
+__device__ inline int lane_again() {
+    int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
 // How the four transform waves of the role-specialised kernels bring the 6x6 patches of their 16 tiles, one channel block at
 // a time: wave w has tiles 4w .. 4w + 3, lane = (tile, four channels).  Every lane loads its four channels of every pixel,
 // sixteen neighbouring lanes 64 bytes in a row.  (Sixteen channels of every fourth pixel per lane, nine instructions instead of

@@ -233,13 +233,16 @@ struct ProductPhase {
     // F-th filter fragment of this wave's stream.  A workgroup that covers more than 32 filters
     // goes through its entries once per 32 (pass F / NB); the wave's 16-filter fragment of the
     // next pass lies two fragments (2 * planes KB) further on in the blob.
-    template <int F>
+    // BUFFER: see load_fragment.
+    template <int F, bool BUFFER = false>
     __device__ inline static v4i load_b(const LaneContext& cx) {
         constexpr int pass = F / NB, f = F % NB;
         constexpr int slot = b_slot_of<MODE>(HALF, f);
         constexpr int plane = b_plane<MODE>(half_slot(HALF, slot).entry, f - b_start<MODE>(HALF, slot));
         constexpr int planes = MODE == WG_LOSSLESS ? 138 : 46;
-        return *reinterpret_cast<const v4i*>(cx.b_glob + (pass * 2 * planes + plane) * kFilterFragBytes + cx.b_lane);
+        constexpr int at = (pass * 2 * planes + plane) * kFilterFragBytes;
+        if constexpr (BUFFER) return load_fragment(cx.b_glob, cx.b_lane, at);
+        else return *reinterpret_cast<const v4i*>(cx.b_glob + at + cx.b_lane);
     }
     template <int SLOT, int I>
     __device__ inline static v4i load_a(const LaneContext& cx) {
@@ -807,8 +810,10 @@ struct EitherHalf {
 // zero in each block, and one shift-and-add per register brings it in.  Re = Dr Wr - Di Wi keeps its two terms apart until
 // finish().  24 / 22 vector instructions per accumulator register and half and channel block, where joining the limbs per
 // block took 48 / 44 (56x56x256 N = 16 with int8 outputs 72.0 -> 64.9 us, together with the cheaper unpacking of StoredInt8).
-// RING filter fragments and ARING activation fragments are in flight.
-template <int HALF, int RING, int ARING>
+// RING filter fragments and ARING activation fragments are in flight.  BUFFER: the former come by buffer loads (with eight product
+// waves and signed int8: 56x56x256 N = 16 59.3 -> 57.3 us, 28x28x128 N = 32 13.35 -> 13.15; uint8 13.3 -> 13.55, the forms with
+// resident accumulators 18.8 -> 19.3 at 14x14x512 N = 16, lossless 75.7 -> 76.5 at 56x56x256).
+template <int HALF, int RING, int ARING, bool BUFFER>
 struct ChainedSums {
     using Phase = ProductPhase<kScaledTwoPlanes, HALF>;
     static constexpr int PM = kScaledTwoPlanes;
@@ -833,7 +838,7 @@ struct ChainedSums {
         return Phase::template load_a<slot, F - a_start(slot)>(cx);
     }
     __device__ inline void prefetch(const LaneContext& cx) {
-        static_for<RING>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
+        static_for<RING>([&](auto I) { ring[I] = Phase::template load_b<I, BUFFER>(cx); });
     }
     // The first block's prefetch, between the request for the reverse-scaling factors and their parking in `area`.
     __device__ inline void enter(LaneContext& cx, int8_t* area, int lane) {
@@ -871,7 +876,7 @@ struct ChainedSums {
                 if constexpr (a0 + I + ARING < NA) aring[(a0 + I) % ARING] = load_a<a0 + I + ARING>(cx);
             });
             static_for<num_b<PM>(entry)>([&](auto I) {
-                if constexpr (b0 + I + RING < NB) ring[(b0 + I) % RING] = Phase::template load_b<b0 + I + RING>(cx);
+                if constexpr (b0 + I + RING < NB) ring[(b0 + I) % RING] = Phase::template load_b<b0 + I + RING, BUFFER>(cx);
             });
 #pragma unroll
             for (int i = 0; i < (is_real(entry) ? 1 : 3); ++i) {

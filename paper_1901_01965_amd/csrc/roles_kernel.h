@@ -124,7 +124,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
     // One loop per half (the same barriers in both), so that each is allocated registers on its own.
     auto blocks = [&](auto H) {
         using Phase = std::conditional_t<MODE == WG_LOSSLESS, LosslessSums<H, PW == 8 ? 6 : 8>,
-                                         std::conditional_t<PW == 4, ResidentScaled<H>, ChainedSums<H, H == 0 ? 6 : 7, 4>>>;
+                                         std::conditional_t<PW == 4, ResidentScaled<H>, ChainedSums<H, H == 0 ? 6 : 7, 4, std::is_same_v<ENC, SignedInt8>>>>;
         Phase phase;
         v4i sums[Phase::kSums];
 #pragma unroll

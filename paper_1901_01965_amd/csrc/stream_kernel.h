@@ -52,9 +52,9 @@ struct RoleBarrier {
 //                   fused_conv_roles_kernel<PW = 8>, a third of its time at two channel blocks, run beside other tile blocks'
 //                   work.  The two halves would need twice the staging: the first writes, the second adds to it in LDS, a
 //                   longer chain per tile block, which one channel block does not pay for (56x56x64 N = 256 scaled: 77 us
-//                   with whole entries, 80 here).  Twelve waves leave 168 registers each, which is not quite enough: 4 - 6 are
-//                   spilled and reloaded in the unit loop with signed channels-last tensors, 12 - 25 with uint8 or channel-major
-//                   outputs, up to 45 with both.  It is the fastest form all the same where fused_conv.hip chooses it, except for
+//                   with whole entries, 80 here).  Twelve waves leave 168 registers each, which is not quite enough: 4 are spilled
+//                   and reloaded in the transform waves' loop with signed channels-last tensors, 7 - 22 with uint8 or channel-major
+//                   outputs.  It is the fastest form all the same where fused_conv.hip chooses it, except for
 //                   channel-major int32 outputs, whose 32 plane offsets also spill 66 - 232 scalar registers (in every form).
 // What bounds kStreamWhole (56x56x64, N = 256, clocks per tile block of 64 filters, lossless / scaled): the product wave's chain,
 // 13,500 / 12,400 = products with their joins, reverse scaling and output transform 10,700 / 9,800 + staging 880 + clearing the
@@ -216,15 +216,19 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
     const int8_t* const b_wave = filter_fragments(blob + planes_off, k - (lane & 15), p.Kp, NP);
     cx.b_lane = fragment_lane(lane);
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
+    // (twelve waves, scaled: spilled, these came back behind the filter fragments in flight, in every unit; lossless mode, 76.5 us at
+    // 56x56x256 N = 16 with lane_again, 75.8 without, spills others)
+    auto lane_here = [&] { if constexpr (FORM == kStreamEight && MODE == WG_SCALED) return lane_again(); else return lane; };
+    auto fragment_slot = [&] { const int l = lane_here(); return lds_slot(l >> 4, l & 15) * 16; };
     // stages a tile block's outputs once every product wave is done with the planes of unit u
     auto stage = [&](int u, const v4i (&Y)[16]) {
         int8_t* const at = lds + (u & 1) * kLdsBytes;
         if constexpr (OWN_BARRIER) among_us.sync(lane); else __syncthreads();
         WG_SPENT(3, mark);   // everyone is done with the planes
-        if (FORM != kStreamEight || half == 0) stage_outputs(at, lane, copy, kblock, Y);
+        if (FORM != kStreamEight || half == 0) stage_outputs(at, lane_here(), copy, kblock, Y);
         if constexpr (FORM == kStreamEight) {
             among_us.sync(lane);
-            if (half == 1) add_staged_outputs(at, lane, copy, kblock, Y);
+            if (half == 1) add_staged_outputs(at, lane_here(), copy, kblock, Y);
         } else {
             __syncthreads();
         }
@@ -254,7 +258,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             WG_SPENT(5, mark);   // clearing the outputs
             published();
             WG_SPENT(0, mark);   // barrier U
-            cx.a_lds = lds + (u & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
+            cx.a_lds = lds + (u & 1) * kLdsBytes + fragment_slot();
             all.run(cx, Y);
             WG_SPENT(1, mark);   // products
             const bool last = cb == p.CB - 1;
@@ -283,7 +287,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
                 WG_SPENT(5, mark);
                 published();
                 WG_SPENT(0, mark);   // barrier U
-                cx.a_lds = lds + (u & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
+                cx.a_lds = lds + (u & 1) * kLdsBytes + fragment_slot();
                 phase.run(cx, sums);
                 WG_SPENT(1, mark);   // products
                 const bool last = cb == p.CB - 1;
@@ -310,10 +314,10 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
         };
         if constexpr (MODE == WG_SCALED) {
             if (half == 0) {
-                ChainedSums<0, 6, PW == 8 ? 4 : 8> phase;
+                ChainedSums<0, 6, PW == 8 ? 4 : 8, PW == 8> phase;
                 stream(phase);
             } else {
-                ChainedSums<1, 6, PW == 8 ? 4 : 6> phase;
+                ChainedSums<1, 6, PW == 8 ? 4 : 6, PW == 8> phase;
                 stream(phase);
             }
         } else if constexpr (PW == 8) {
