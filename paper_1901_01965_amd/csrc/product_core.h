@@ -655,7 +655,7 @@ struct LeanProducts {
     v4i ring[RING];
 
     __device__ inline void prefetch(const LaneContext& cx) {
-        static_for<RING>([&](auto I) { ring[I] = Phase::template load_b<I>(cx); });
+        static_for<RING>([&](auto I) { ring[I] = Phase::template load_b<I, WHOLE>(cx); });
     }
 
     __device__ inline void run(const LaneContext& cx, Target to) {
@@ -682,7 +682,7 @@ struct LeanProducts {
                                                                     op.init ? zero : acc[op.acc], 0, 0, 0);
             });
             static_for<num_b<PM>(entry)>([&](auto I) {
-                if constexpr (b0 + I + RING < NB) ring[(b0 + I) % RING] = Phase::template load_b<b0 + I + RING>(cx);
+                if constexpr (b0 + I + RING < NB) ring[(b0 + I) % RING] = Phase::template load_b<b0 + I + RING, WHOLE>(cx);
             });
         };
         // the vector part of slot S: limbs joined (Re = Dr Wr - Di Wi, Im = Dr Wi + Di Wr); then into the channel sums, or
@@ -811,7 +811,7 @@ struct EitherHalf {
 // finish().  24 / 22 vector instructions per accumulator register and half and channel block, where joining the limbs per
 // block took 48 / 44 (56x56x256 N = 16 with int8 outputs 72.0 -> 64.9 us, together with the cheaper unpacking of StoredInt8).
 // RING filter fragments and ARING activation fragments are in flight.  BUFFER: the former come by buffer loads (with eight product
-// waves and signed int8: 56x56x256 N = 16 59.3 -> 57.3 us, 28x28x128 N = 32 13.35 -> 13.15; uint8 13.3 -> 13.55, the forms with
+// waves and signed int8: 56x56x256 N = 16 59.3 -> 57.3 us, 28x28x128 N = 32 13.35 -> 13.15, and every entry in one wave, 56x56x64 N = 256 94.7 -> 93.9; uint8 13.3 -> 13.55, the forms with
 // resident accumulators 18.8 -> 19.3 at 14x14x512 N = 16, lossless 75.7 -> 76.5 at 56x56x256).
 template <int HALF, int RING, int ARING, bool BUFFER>
 struct ChainedSums {
