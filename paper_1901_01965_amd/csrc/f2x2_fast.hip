@@ -5,11 +5,12 @@
 // multiplies, and a layer of 128 channels has two such rounds; with the limb products in accumulators of their own (32 or 48
 // of four registers) two workgroups fit a compute unit and 28x28, 128 -> 128, N = 32 (784 workgroups) took 22 us scaled and
 // 31 lossless for 3 us worth of bytes.  Here the limbs are joined block by block: the low products accumulate in the channel
-// sum itself, the others enter it by one shift-and-add per register, which leaves 16 sums per wave: 136 registers in scaled
-// mode, 166 in lossless, so that three workgroups share a compute unit and their waits overlap: 15.5 and 18.3 us.  (128
-// registers and four workgroups were 4-12 % slower.)  The 784 workgroups are 16 more than the chip holds, which cost the last
-// 3.5 of those microseconds: N = 31 takes 12.0 and 13.  The reverse-scaling factors are parked in LDS at the start, the
-// blob header is compared only before the store, and pixels outside the image arrive as zeros.
+// sum itself, the others enter it by one shift-and-add per register, which leaves 16 sums per wave.  Lossless mode: 161
+// registers, three workgroups per compute unit whose waits overlap, 16.5 us.  Scaled mode: the filter fragments come by buffer
+// loads (load_fragment), whose addresses take no vector registers, so that it fits 128 and four workgroups share a compute unit:
+// 15.7 -> 14.5 us, 56x56x256 N = 16 66.6 -> 63.2, 14x14x256 N = 64 23.0 -> 20.8 (with 64-bit addresses it spilled at 128 and four
+// workgroups were 4-12 % slower; the smallest layers, whose chip is not full either way, 7.05 -> 7.2).  The reverse-scaling factors
+// are parked in LDS at the start, the blob header is compared only before the store, and pixels outside the image arrive as zeros.
 #include "kernel_common.h"
 
 namespace wg {
@@ -108,7 +109,7 @@ __device__ inline int unscale(int m, uint32_t rq) {
 // grid: (ceil(T / 16), Kp / 64), 256 threads.  Transform: thread = (tile, four channels).  Products: wave w owns filters
 // 16 w .. 16 w + 15 of the 16 tiles for all 16 entries.
 template <int LAYOUT, int MODE, bool Q8, bool NARROW, class ENC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f2_fast_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == WG_SCALED ? 4 : 3))) void f2_fast_kernel(
     const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_ORDER_PARAMS, const uint8_t* __restrict__ blob, size_t table_off,
     size_t planes_off, int32_t* __restrict__ y, Problem p, ENC enc, Int8Epilogue q8) {
     WG_TAKE_GEOMETRY(p, 1);
@@ -159,14 +160,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     // Entries' filter fragments in flight (one less while an entry multiplies).  Where the fragments miss the L2 (fewer than eight
     // filter blocks, which every XCD then reads, and few workgroups to share them) a deep layer's time is their latency: lossless,
     // N = 1, 512 -> 256 at 28x28 32.4 us with two, 25.8 three, 23.3 four, 22.1 five, as many as three waves' registers hold
-    // (166 of 168); 28x28x128 N = 32 18.9 / 17.7 / 18.3 / 18.3.
+    // (161 of 168); 28x28x128 N = 32 18.9 / 17.7 / 18.3 / 18.3.
     constexpr int kRing = MODE == WG_LOSSLESS ? 5 : 4;
     for (int step = 0; step < p.CB; ++step) {
         const int8_t* const b_cb = b_wave + cb * b_block_stride;
         v4i bf[kRing][NBP];
         auto request_b = [&](auto E) {
 #pragma unroll
-            for (int i = 0; i < NBP; ++i) bf[E % kRing][i] = *reinterpret_cast<const v4i*>(b_cb + (NBP * E + i) * kFilterFragBytes + b_lane);
+            for (int i = 0; i < NBP; ++i) bf[E % kRing][i] = load_fragment(b_cb, b_lane, (NBP * E + i) * kFilterFragBytes);
         };
         if (step > 0) __syncthreads();   // the previous block's operand planes have been consumed
         patch.bias(u, enc);
