@@ -248,11 +248,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == WG_
     }
     const bool pooled = Q8 && q8.pool != 0;   // a 2x2 output tile is one pooling window
     const int NO = pooled ? 1 : 4, Ho = pooled ? p.H >> 1 : p.H, Wo = pooled ? p.W >> 1 : p.W;
-    if constexpr (Q8) {
+    if constexpr (Q8) {   // (requantisation is monotonic: it comes after the maximum)
+        if (pooled) {
+            out[0] = requantise(__builtin_elementwise_max(__builtin_elementwise_max(out[0], out[1]), __builtin_elementwise_max(out[2], out[3])), q8);
+        } else {
 #pragma unroll
-        for (int o = 0; o < 4; ++o) out[o] = requantise(out[o], q8);
-        if (pooled)
-            out[0] = __builtin_elementwise_max(__builtin_elementwise_max(out[0], out[1]), __builtin_elementwise_max(out[2], out[3]));
+            for (int o = 0; o < 4; ++o) out[o] = requantise(out[o], q8);
+        }
     }
 
     // ---- staged filter-fastest, then stored in whole lines ----------------------------------------------------------

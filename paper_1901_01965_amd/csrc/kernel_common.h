@@ -77,9 +77,8 @@ __device__ inline v4i requantise(v4i y, const Int8Epilogue& q) {
     return __builtin_elementwise_min(__builtin_elementwise_max(y, lo), hi);
 }
 __device__ inline uint32_t pack_bytes(v4i v) {
-    return (uint32_t)(v[0] & 0xff) | ((uint32_t)(v[1] & 0xff) << 8) | ((uint32_t)(v[2] & 0xff) << 16) | ((uint32_t)v[3] << 24);
+    return __builtin_amdgcn_perm((uint32_t)v[1], (uint32_t)v[0], 0x0c0c0400u) | __builtin_amdgcn_perm((uint32_t)v[3], (uint32_t)v[2], 0x04000c0cu);
 }
-
 // Patch loads of the role-specialised kernels go through a buffer descriptor over the activation
 // tensor: a load whose offset lies beyond the tensor returns zero, so a pixel outside the image
 // (pad 1, ragged tiles) is an offset that can never be in range instead of a select per pixel and

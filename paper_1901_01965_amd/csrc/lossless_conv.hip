@@ -558,11 +558,10 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
         return *reinterpret_cast<const v4i*>(stage + at) + *reinterpret_cast<const v4i*>(stage + kStageHalf + at);
     };
     auto staged = [&](int o, int tile, int k4) { return sixteen(o, tile, k4) >> 4; };
-    auto best_of_window = [&](int pi, int pj, int tile, int k4) {   // 2x2 maximum of requantised outputs
-        v4i best = requantise(staged(4 * (2 * pi) + 2 * pj, tile, k4), q8);
-        best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi) + 2 * pj + 1, tile, k4), q8));
-        best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj, tile, k4), q8));
-        return __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj + 1, tile, k4), q8));
+    auto best_of_window = [&](int pi, int pj, int tile, int k4) {   // the 2x2 maximum, then requantised (all of it is monotonic)
+        const v4i a = __builtin_elementwise_max(sixteen(4 * (2 * pi) + 2 * pj, tile, k4), sixteen(4 * (2 * pi) + 2 * pj + 1, tile, k4));
+        const v4i b = __builtin_elementwise_max(sixteen(4 * (2 * pi + 1) + 2 * pj, tile, k4), sixteen(4 * (2 * pi + 1) + 2 * pj + 1, tile, k4));
+        return requantise(__builtin_elementwise_max(a, b) >> 4, q8);
     };
     if constexpr (LAYOUT == WG_NCHW && OUT != kOutSums) {
         // a filter's outputs lie together: sixteen consecutive tiles of an image row are 64 consecutive pixels

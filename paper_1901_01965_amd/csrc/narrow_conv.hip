@@ -201,13 +201,8 @@ __global__ __launch_bounds__(64) void narrow_conv_kernel(const int8_t* __restric
                 for (int pi = 0; pi < 2; ++pi)
 #pragma unroll
                     for (int pj = 0; pj < 2; ++pj) {
-                        int best = -128;
-#pragma unroll
-                        for (int a = 0; a < 2; ++a)
-#pragma unroll
-                            for (int b = 0; b < 2; ++b)
-                                best = max(best, requantise_y16(out[2 * pj + b][2 * pi + a], shift, q8.lo));
-                        bytes[2 * pi + pj] = (int8_t)best;
+                        const int best = max(max(out[2 * pj][2 * pi], out[2 * pj + 1][2 * pi]), max(out[2 * pj][2 * pi + 1], out[2 * pj + 1][2 * pi + 1]));
+                        bytes[2 * pi + pj] = (int8_t)requantise_y16(best, shift, q8.lo);   // monotonic: once, after the maximum
                     }
             } else {
 #pragma unroll

@@ -482,18 +482,19 @@ template <int LAYOUT, bool Q8, bool ADD>
 __device__ __forceinline__ void store_staged(const StoreContext& sc, const Problem& p, const Int8Epilogue& q8, int kbase) {
     const int tid = sc.tid, lane = sc.lane;
     const int* const parki = reinterpret_cast<const int*>(sc.lds);
-    // finished outputs of filters 4*g .. 4*g+3 of the block
-    auto staged = [&](int o, int tile, int g) {
+    auto sixteen = [&](int o, int tile, int g) {   // 16 x the outputs of filters 4*g .. 4*g+3 of the block
         const int at = (o * 16 + tile) * kStageRow + 4 * g;
         v4i v = *reinterpret_cast<const v4i*>(parki + at);
         if constexpr (ADD) v += *reinterpret_cast<const v4i*>(parki + kStageHalf + at);
-        return (v + sc.rnd) >> 4;
+        return v;
     };
-    auto best_of_window = [&](int tile, int pi, int pj, int g) {   // 2x2 maximum of requantised outputs
-        v4i best = requantise(staged(4 * (2 * pi) + 2 * pj, tile, g), q8);
-        best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi) + 2 * pj + 1, tile, g), q8));
-        best = __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj, tile, g), q8));
-        return __builtin_elementwise_max(best, requantise(staged(4 * (2 * pi + 1) + 2 * pj + 1, tile, g), q8));
+    auto staged = [&](int o, int tile, int g) { return (sixteen(o, tile, g) + sc.rnd) >> 4; };
+    // the 2x2 maximum, requantised: rescale, requantisation and clamp are monotonic, so they come once, after the maximum
+    // (112x112x128 N = 16 65.8 -> 62.4 us, 224x224x64 73.8 -> 66.5)
+    auto best_of_window = [&](int tile, int pi, int pj, int g) {
+        const v4i a = __builtin_elementwise_max(sixteen(4 * (2 * pi) + 2 * pj, tile, g), sixteen(4 * (2 * pi) + 2 * pj + 1, tile, g));
+        const v4i b = __builtin_elementwise_max(sixteen(4 * (2 * pi + 1) + 2 * pj, tile, g), sixteen(4 * (2 * pi + 1) + 2 * pj + 1, tile, g));
+        return requantise((__builtin_elementwise_max(a, b) + sc.rnd) >> 4, q8);
     };
     if constexpr (LAYOUT == WG_NCHW) {
         // A filter's outputs lie together: sixteen consecutive tiles of an image row are 64 consecutive pixels.

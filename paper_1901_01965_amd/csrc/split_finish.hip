@@ -85,10 +85,8 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const int32_t* __rest
             for (int i = 0; i < 2; ++i) {
                 const int h = 2 * ty + i, w = 2 * tx + j;
                 if (h >= p.H >> 1 || w >= p.W >> 1) continue;
-                int best = -129;
-#pragma unroll
-                for (int a = 0; a < 4; ++a) best = max(best, requantise((out[2 * j + (a & 1)][2 * i + (a >> 1)] + rnd) >> 4, q8));
-                q8.out[at(h, w, p.H >> 1, p.W >> 1)] = (int8_t)best;
+                const int best = max(max(out[2 * j][2 * i], out[2 * j + 1][2 * i]), max(out[2 * j][2 * i + 1], out[2 * j + 1][2 * i + 1]));
+                q8.out[at(h, w, p.H >> 1, p.W >> 1)] = (int8_t)requantise((best + rnd) >> 4, q8);
             }
         return;
     }
@@ -136,10 +134,9 @@ __global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restr
     v4i v;
     if (pool) {
         const int pi = o >> 1, pj = o & 1;
-        v = requantise(total(8 * pi + 2 * pj), q8);
-        v = __builtin_elementwise_max(v, requantise(total(8 * pi + 2 * pj + 1), q8));
-        v = __builtin_elementwise_max(v, requantise(total(8 * pi + 4 + 2 * pj), q8));
-        v = __builtin_elementwise_max(v, requantise(total(8 * pi + 4 + 2 * pj + 1), q8));
+        v = __builtin_elementwise_max(__builtin_elementwise_max(total(8 * pi + 2 * pj), total(8 * pi + 2 * pj + 1)),
+                                      __builtin_elementwise_max(total(8 * pi + 4 + 2 * pj), total(8 * pi + 4 + 2 * pj + 1)));
+        v = requantise(v, q8);
         h = 2 * ty + pi; w = 2 * tx + pj; H >>= 1; W >>= 1;
     } else {
         v = total(o);
