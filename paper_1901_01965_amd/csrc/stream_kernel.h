@@ -75,9 +75,13 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
     constexpr int PW = stream_product_waves<FORM>();
     constexpr bool OWN_BARRIER = FORM == kStreamEight;
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
-    const int lane = threadIdx.x & 63, wave8 = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave8 = FORM == kStreamEight ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const bool transforms = wave8 < 4;
-    const int tid = threadIdx.x & 255, wave = wave8 & 3;   // within the role
+    const int wave = wave8 & 3;   // within the role
+    // Twelve waves have no registers to spare: what follows from the lane is formed where it is needed.  Spilled, it came back behind
+    // the loads in flight, in every unit: scaled, 128 -> 128 at 112x112 N = 16, formed 66.4 us, spilled 68.9; 40 mixed
+    // layers 1.2 % faster.  (With eight waves, nothing is spilled either way: 16 -> 16 lossless layers lost 11 % to the extra work.)
+    auto my_lane = [&] { if constexpr (FORM == kStreamEight) return lane_again(); else return lane; };
     int bx, by;
     order.place(bx, by);
     const int k0 = by * stream_filters<FORM>();
@@ -103,23 +107,26 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
 #endif
 
     if (transforms) {
-        const int a_tile = PatchLoader::tile_of(wave, lane), a_cq = PatchLoader::quad_of(lane);
         OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
-        int8_t* const slot = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
+        auto slot_of = [&](int l) {   // a lane's four bytes of an operand plane
+            const int cq = PatchLoader::quad_of(l);
+            return lds + lds_slot(cq >> 2, PatchLoader::tile_of(wave, l)) * 16 + (cq & 3) * 4;
+        };
+        int8_t* const slot = slot_of(lane);
         PatchBias<ENC> bias, next_bias;   // of the patch being transformed, of the one in flight
         PatchLoader loader;
         auto enter_tile_block = [&](int tb) {
-            const int t = tb * kFusedTiles + a_tile;
+            const int l = my_lane(), t = tb * kFusedTiles + PatchLoader::tile_of(wave, l);
             int n = 0, ty = 0, tx = 0;
             if (t < p.T) decode_tile(p, t, n, ty, tx);
-            loader.enter(p, n, ty, tx, lane);
+            loader.enter(p, n, ty, tx, l);
             next_bias.enter(p, ty, tx, enc);
         };
         const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
         // writes out what is staged in `buffer` for tile block tb
         auto flush = [&](int tb, int buffer) {
             StoreContext sc;
-            sc.lds = lds + buffer * kLdsBytes; sc.tid = tid; sc.lane = lane; sc.rnd = rnd; sc.y = y;
+            sc.lds = lds + buffer * kLdsBytes; sc.lane = my_lane(); sc.tid = FORM == kStreamEight ? wave * 64 + sc.lane : threadIdx.x & 255; sc.rnd = rnd; sc.y = y;
             // (opaque: what follows from these is formed here, not ahead of the loop: registers are scarce)
             if constexpr (FORM == kStreamEight || LAYOUT == WG_NCHW) asm volatile("" : "+v"(sc.tid), "+v"(sc.lane));
             locate_tile<LAYOUT>(sc, p, tb * kFusedTiles);
@@ -132,11 +139,11 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             }
         };
         RoleBarrier<4> among_us = {reinterpret_cast<uint32_t*>(lds + 2 * kLdsBytes), 0u};
-        if (tid < 2) among_us.counter[tid] = 0u;   // this role's counter and the other's: land before the first s_barrier, long before the first use
+        if (threadIdx.x < 2) among_us.counter[threadIdx.x] = 0u;   // this role's counter and the other's: land before the first s_barrier, long before the first use
         int cb = 0, jb = 0;   // unit u = (tile block number jb of this workgroup, channel block cb)
         if (units > 0) {
             enter_tile_block(bx);
-            loader.drop_absent_channels(p, 0, lane);
+            loader.drop_absent_channels(p, 0, my_lane());
             loader.request(xbuf, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -160,7 +167,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             const int tb = bx + jb * order.across;
             const bool last0 = u < units && cb == p.CB - 1;
             if (u < units) {
-                out.sink.base = slot + (u & 1) * kLdsBytes;
+                out.sink.base = (FORM == kStreamEight ? slot_of(my_lane()) : slot) + (u & 1) * kLdsBytes;
 #ifdef WG_TIMESTAMPS
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 WG_SPENT(2, mark);   // wait for the patch
@@ -171,7 +178,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
                 bias = next_bias;
                 if (more) {
                     if (cb == 0) enter_tile_block(bx + jb * order.across);
-                    loader.drop_absent_channels(p, cb, lane);
+                    loader.drop_absent_channels(p, cb, my_lane());
                 }
                 bias.apply(loader.patch);
                 WG_SPENT(5, mark);   // offsets
@@ -216,8 +223,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
     const int8_t* const b_wave = filter_fragments(blob + planes_off, k - (lane & 15), p.Kp, NP);
     cx.b_lane = fragment_lane(lane);
     const size_t b_block_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
-    // (twelve waves, scaled: spilled, these came back behind the filter fragments in flight, in every unit; lossless mode, 76.5 us at
-    // 56x56x256 N = 16 with lane_again, 75.8 without, spills others)
+    // (lossless mode: 56x56x256 N = 16 takes 76.5 us with it, 75.8 without, which spills others)
     auto lane_here = [&] { if constexpr (FORM == kStreamEight && MODE == WG_SCALED) return lane_again(); else return lane; };
     auto fragment_slot = [&] { const int l = lane_here(); return lds_slot(l >> 4, l & 15) * 16; };
     // stages a tile block's outputs once every product wave is done with the planes of unit u
