@@ -1,16 +1,20 @@
 // Direct convolution on the int8 matrix cores as an implicit matrix product over linear pixels: y[pixel][k] = sum over nine
 // taps and C channels.  Activations channels-last with C % 16 = 0 (as given, or as a padded copy), filters [K][9][C].
 //
-// What bounds it: with operands in LDS a wave reads (A + B) fragments of 1 KB for A x B matrix instructions of 32 clocks, and
-// LDS delivers 128 B per clock to a compute unit.  A wave tile of 64 filters x 128 pixels asks for 6 KB per eight
-// instructions, 96 B per clock for four SIMDs; the 32 x 64 tile per wave of the patch kernel (direct_conv.hip) asks for
-// 192 B per clock, which is what held that kernel at 1260 TOPS on 256 -> 256 channels at 56x56, N = 16 (47 us).
+// What bounds it: with operands in LDS a wave reads (A + B) fragments of 1 KB for A x B matrix instructions of 32 clocks.  A
+// wave tile of 64 filters x 128 pixels asks for 6 KB per eight of them, 96 B per clock for four SIMDs; the 32 x 64 tile per
+// wave of the patch kernel (direct_conv.hip) asks for 192 B per clock.  Vector instructions delay matrix instructions of their
+// SIMD, so the loop has few: read addresses are kept, not formed (see at_pixel), and transfers take one addition each
+// (93 vector instructions for 144 products; formed anew, 620).  256 -> 256 channels at 56x56, N = 16: 39.8 -> 37.4 us (1580 TOPS),
+// of which set-up and first transfers 3, stores of 51 MB at the end, all compute units at once, 11; 512 -> 512 at 28x28
+// 39.4 -> 35.5, 256 -> 256 at 56x56 N = 4 16.0 -> 12.7.  (A 256 x 224 tile of 16 x 16 x 64 products, 224 workgroups instead of
+// 196 there: 40.2 against 39.8.)
 //
 // Workgroup: P consecutive pixels of the batch (in memory order, so only the last workgroup has idle columns, whatever the
 // image size) x F filters.  LDS holds, per block of 64 channels, the pixel rows p0 - W - 1 .. p0 + P + W (a tap is a row
 // offset of (a - 1) W + (b - 1)) and the taps of one filter row; both double-buffered and filled by 16-byte transfers from
-// memory straight into LDS that run during the products.  A tap that falls outside the image reads a row of zeros: one
-// select per fragment address.  A stage is one filter row of one channel block: 48 matrix instructions per wave, one barrier.
+// memory straight into LDS that run during the products.  A tap that falls outside the image reads a row of zeros.  A stage is
+// one filter row of one channel block: 48 matrix instructions per wave, one barrier.
 #include <algorithm>
 
 #include "kernel_common.h"
@@ -20,8 +24,6 @@ namespace {
 
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kZeroRow = 64;   // bytes of zeros at the start of LDS
-
 // 16-byte pieces of a 64-byte LDS row are XOR-swizzled so that the fragment reads of 16 consecutive rows fall into
 // different banks; the swizzle is applied on the global side of the transfers.
 __device__ inline int piece_at(int row, int slot) { return slot ^ ((row >> 2) & 3); }
@@ -30,8 +32,13 @@ __device__ inline void to_lds_16(__amdgpu_buffer_rsrc_t buffer, int8_t* lds_dst,
     __builtin_amdgcn_raw_ptr_buffer_load_lds(buffer, (__attribute__((address_space(3))) int8_t*)lds_dst, 16, voffset, 0, 0, 0);
 }
 
-// Pixel rows a workgroup keeps, rounded up to whole 1 KB transfers.
+// Fragments are read at addresses within LDS, kept as integers: as offsets from its start each read added that start first.
+using LdsBytes = const __attribute__((address_space(3))) int8_t;
+__device__ inline v4i fragment_at(int address) { return *reinterpret_cast<const __attribute__((address_space(3))) v4i*>(reinterpret_cast<LdsBytes*>((uintptr_t)(uint32_t)address)); }
+
+// Pixel rows a workgroup keeps, rounded up to whole 1 KB transfers; a row of zeros follows them.
 __host__ __device__ inline int halo_rows(int P, int W) { return (P + 2 * W + 2 + 15) / 16 * 16; }
+__host__ __device__ inline int halo_bytes_of(int P, int W) { return (halo_rows(P, W) + 1) * kCBlock; }
 
 // WF x WP waves; a wave multiplies 64 filters x 32 PG pixels.  F = 64 WF, P = 32 PG WP.
 // grid: (ceil(pixels / P), ceil(K / F)), 64 WF WP threads.
@@ -39,55 +46,67 @@ template <int LAYOUT, int WF, int WP, int PG>
 __global__ __launch_bounds__(64 * WF * WP) void direct_gemm_kernel(const int8_t* __restrict__ x, const int8_t* __restrict__ w,
                                                                    int N, int C, int H, int W, int K, int32_t* __restrict__ y, Problem p) {
     p.N = N; p.C = C; p.H = H; p.W = W; p.K = K;   // (in registers when a wave starts)
-    constexpr int F = 64 * WF, P = 32 * PG * WP, T = 64 * WF * WP;
+    constexpr int F = 64 * WF, P = 32 * PG * WP, T = 64 * WF * WP, TAPS = (3 * F * 4 + T - 1) / T;
     constexpr int kTapBytes = 3 * F * kCBlock;
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wf = wave % WF, wp = wave / WF;
     const int pixels = p.N * p.H * p.W, p0 = blockIdx.x * P, k0 = blockIdx.y * F;
-    const int rows = halo_rows(P, p.W), halo_bytes = rows * kCBlock;
-    int8_t* const taps = lds + kZeroRow;                    // two buffers
-    int8_t* const halo = taps + 2 * kTapBytes;              // two buffers
+    const int rows = halo_rows(P, p.W), halo_bytes = halo_bytes_of(P, p.W);
+    int8_t* const taps = lds;                    // two buffers
+    int8_t* const halo = taps + 2 * kTapBytes;   // two buffers
     const __amdgpu_buffer_rsrc_t xbuf = activation_buffer(x, p);
     const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(w), 0, p.K * 9 * p.C, kRawBufferWord3);
-    if (tid < kZeroRow / 4) reinterpret_cast<int*>(lds)[tid] = 0;
+    if (tid < 2 * kCBlock / 4) reinterpret_cast<int*>(halo + (tid >> 4) * halo_bytes + rows * kCBlock)[tid & 15] = 0;
 
-    // pieces beyond C, pixels outside the batch and filters beyond K ask for an offset no buffer holds, and arrive as zeros
+    // A thread's transfers lie T / 4 rows apart, a multiple of 16: its piece of a row is the same in all.  Pixels outside the batch
+    // and filters beyond K lie outside the buffers and arrive as zeros.  So do taps beyond C; what the pixels hold there does not matter.
+    const int my_row = tid >> 2, my_c = 16 * piece_at(my_row, tid & 3);
+    const uint32_t first_pixel = (uint32_t)(p0 - p.W - 1 + my_row) * (uint32_t)p.C + (uint32_t)my_c;
+    uint32_t first_tap[TAPS];
+#pragma unroll
+    for (int i = 0; i < TAPS; ++i) {
+        const int row = i * (T / 4) + my_row, b = row / F, k = k0 + row % F;   // LDS row = 3 taps x F filters: [tap b][filter]
+        first_tap[i] = (uint32_t)(k * 9 + b) * (uint32_t)p.C + (uint32_t)my_c;
+    }
     auto request_halo = [&](int cb, int8_t* dst) {
-        const int total = rows * 4;
-        for (int base = wave * 64; base < total; base += T) {
-            const int at = base + lane, row = at >> 2, c = cb * kCBlock + 16 * piece_at(row, at & 3);
-            const int pixel = p0 - p.W - 1 + row;
-            const bool have = at < total && (unsigned)pixel < (unsigned)pixels && c < p.C;
-            to_lds_16(xbuf, dst + base * 16, have ? (uint32_t)pixel * (uint32_t)p.C + (uint32_t)c : kOutsideOffset);
+        uint32_t at = first_pixel + cb * kCBlock;
+        for (int base = wave * 64; base < rows * 4; base += T) {
+            to_lds_16(xbuf, dst + base * 16, at);
+            at += T / 4 * p.C;
         }
     };
     auto request_taps = [&](int cb, int a, int8_t* dst) {
-        // LDS row = 3 taps x F filters: [tap b][filter]
+        const bool have = cb * kCBlock + my_c < p.C;
+        const uint32_t from = 3 * a * p.C + cb * kCBlock;
 #pragma unroll
-        for (int i = 0; i < (3 * F * 4 + T - 1) / T; ++i) {
-            const int base = i * T + wave * 64, at = base + lane, row = at >> 2, b = row / F, k = k0 + row % F;
-            if (base >= 3 * F * 4) break;
-            const int c = cb * kCBlock + 16 * piece_at(row, at & 3);
-            const bool have = k < p.K && c < p.C;
-            to_lds_16(wbuf, dst + base * 16, have ? ((uint32_t)k * 9 + 3 * a + b) * (uint32_t)p.C + (uint32_t)c : kOutsideOffset);
+        for (int i = 0; i < TAPS; ++i) {
+            const int base = i * T + wave * 64;
+            if (base < 3 * F * 4) to_lds_16(wbuf, dst + base * 16, have ? first_tap[i] + from : kOutsideOffset);
         }
     };
 
-    // this lane's pixels (one per group): which of the nine taps lie inside the image
-    int valid[PG];
+    // Where this lane reads its pixels' rows (one pixel per group) for each tap, in the halo buffer of this channel block: rows outside
+    // the image are the row of zeros.  One addition and one exclusive or per tap, group and channel block keep them up to date
+    // (the channel halves are taken in the order 0 1, 1 0, ...).
+    int at_pixel[9][PG];
+    const int lds_start = (int)(uint32_t)reinterpret_cast<uintptr_t>((LdsBytes*)lds);
+    const int upper = lane >> 5;   // which 16 of a step's 32 channels
 #pragma unroll
     for (int g = 0; g < PG; ++g) {
-        const int pixel = p0 + (wp * PG + g) * 32 + (lane & 31);
+        const int in_block = (wp * PG + g) * 32 + (lane & 31), pixel = p0 + in_block;
         const int h = (pixel / p.W) % p.H, wcol = pixel % p.W;
-        int m = 0;
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int b = 0; b < 3; ++b)
-                m |= ((unsigned)(h + a - 1) < (unsigned)p.H && (unsigned)(wcol + b - 1) < (unsigned)p.W) << (3 * a + b);
-        valid[g] = m;
+            for (int b = 0; b < 3; ++b) {
+                const bool inside = (unsigned)(h + a - 1) < (unsigned)p.H && (unsigned)(wcol + b - 1) < (unsigned)p.W;
+                const int row = inside ? in_block + a * p.W + b : rows;
+                at_pixel[3 * a + b][g] = lds_start + 2 * kTapBytes + row * kCBlock + 16 * piece_at(row, upper);
+            }
     }
+    const int tap_row = wf * 64 + (lane & 31);   // the others lie a multiple of 32 rows away
+    const int at_tap = lds_start + tap_row * kCBlock + 16 * piece_at(tap_row, upper);
     v16i acc[2][PG];
 #pragma unroll
     for (int f = 0; f < 2; ++f)
@@ -98,45 +117,57 @@ __global__ __launch_bounds__(64 * WF * WP) void direct_gemm_kernel(const int8_t*
     request_taps(0, 0, taps);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    const int upper = lane >> 5;   // which 16 of a step's 32 channels
-    const int stages = 3 * p.CB;
-    int a = 0, cb = 0;
-    for (int s = 0; s < stages; ++s) {
-        const int next_a = a == 2 ? 0 : a + 1, next_cb = a == 2 ? cb + 1 : cb;
-        if (s + 1 < stages) request_taps(next_cb, next_a, taps + ((s + 1) & 1) * kTapBytes);
-        if (a == 0 && cb + 1 < p.CB) request_halo(cb + 1, halo + ((cb + 1) & 1) * halo_bytes);
-        const int8_t* const tap_rows = taps + (s & 1) * kTapBytes;
-        const int8_t* const pixel_rows = halo + (cb & 1) * halo_bytes;
-        // six steps of 32 channels (tap b, half ks); a step's fragments are read while the step before multiplies
-        v4i A[2][2], B[2][PG];
-        auto read = [&](auto S) {
-            constexpr int b = S / 2, ks = S % 2;
-            const int piece = 2 * ks + upper;
+    // Six steps of 32 channels (tap b, half) a stage.  A step's fragments are read while the step before multiplies, a stage's first
+    // ones too: the barrier that says that its rows are there comes before the last step of the stage before, when all
+    // fragments of that stage are in registers.
+    v4i A[2][2], B[2][PG];
+    auto read = [&](auto TAP, auto STEP, int cb, int stage) {   // STEP: 2 b + how many halves of this tap are read already
+        constexpr int tap = TAP, step = STEP;
+        const int tap_rows = (stage & 1) * kTapBytes + (at_tap ^ 32 * ((cb ^ step) & 1));
 #pragma unroll
-            for (int f = 0; f < 2; ++f) {
-                const int row = b * F + wf * 64 + f * 32 + (lane & 31);
-                A[S & 1][f] = *reinterpret_cast<const v4i*>(tap_rows + row * kCBlock + 16 * piece_at(row, piece));
-            }
+        for (int f = 0; f < 2; ++f) A[step & 1][f] = fragment_at(tap_rows + ((step / 2) * F + f * 32) * kCBlock);
 #pragma unroll
-            for (int g = 0; g < PG; ++g) {
-                const int row = (wp * PG + g) * 32 + (lane & 31) + a * p.W + b;
-                const int8_t* at = pixel_rows + row * kCBlock + 16 * piece_at(row, piece);
-                B[S & 1][g] = *reinterpret_cast<const v4i*>((valid[g] >> (3 * a + b)) & 1 ? at : lds);
-            }
-        };
-        read(std::integral_constant<int, 0>{});
-        static_for<6>([&](auto S) {
-            if constexpr (S + 1 < 6) read(std::integral_constant<int, S + 1>{});
-#pragma unroll
-            for (int g = 0; g < PG; ++g)
-#pragma unroll
-                for (int f = 0; f < 2; ++f) acc[f][g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[S & 1][f], B[S & 1][g], acc[f][g], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        });
+        for (int g = 0; g < PG; ++g) {
+            int& at = at_pixel[tap][g];
+            B[step & 1][g] = fragment_at(at);
+            if constexpr (step & 1) at += cb & 1 ? -halo_bytes : halo_bytes;
+            else at ^= 32;
+        }
+    };
+    auto rows_are_there = [] {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
-        a = next_a;
-        cb = next_cb;
+    };
+    request_halo(0, halo);
+    request_taps(0, 0, taps);
+    rows_are_there();
+    read(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, 0, 0);
+    for (int cb = 0; cb < p.CB; ++cb) {
+        const bool more = cb + 1 < p.CB;
+        static_for<3>([&](auto ROW) {
+            constexpr int a = ROW;
+            const int s = 3 * cb + a;
+            if (a < 2) request_taps(cb, a + 1, taps + ((s + 1) & 1) * kTapBytes);
+            else if (more) request_taps(cb + 1, 0, taps + ((s + 1) & 1) * kTapBytes);
+            if (a == 0 && more) request_halo(cb + 1, halo + ((cb + 1) & 1) * halo_bytes);
+            static_for<6>([&](auto S) {
+                constexpr int step = S;
+                if constexpr (step + 1 < 6) {
+                    read(std::integral_constant<int, 3 * a + (step + 1) / 2>{}, std::integral_constant<int, step + 1>{}, cb, s);
+                } else if constexpr (a < 2) {
+                    rows_are_there();
+                    read(std::integral_constant<int, 3 * a + 3>{}, std::integral_constant<int, 0>{}, cb, s + 1);
+                } else if (more) {
+                    rows_are_there();
+                    read(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, cb + 1, s + 1);
+                }
+#pragma unroll
+                for (int g = 0; g < PG; ++g)
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) acc[f][g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[step & 1][f], B[step & 1][g], acc[f][g], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
     }
 
     // register i of a 32x32 product: row (filter) 8 (i / 4) + 4 (lane / 32) + i % 4, column (pixel) lane % 32
@@ -168,10 +199,11 @@ struct Form {
 };
 constexpr Form kForms[] = {{128, 512, 512}, {64, 512, 512}, {64, 256, 512}, {64, 128, 256}};
 constexpr int kLdsMost = 160 * 1024;
-int lds_bytes(const Form& f, const Problem& p) { return kZeroRow + 2 * 3 * f.F * kCBlock + 2 * halo_rows(f.P, p.W) * kCBlock; }
+int lds_bytes(const Form& f, const Problem& p) { return 2 * 3 * f.F * kCBlock + 2 * halo_bytes_of(f.P, p.W); }
 
-// The form with the least estimated time: rounds of the compute units times what a workgroup takes, its matrix instructions
-// at the share of the peak that its wave tile reaches (128 x 512: 96 B of LDS reads per clock; the others 128 B and more).
+// The form with the least estimated time: workgroups of the fullest compute unit times what one takes, its matrix instructions
+// at the share of the peak that its wave tile reaches.  (Counting whole rounds of two where two fit a compute unit, as before, took
+// 64 x 128 for 196 workgroups of 64 x 256: 256 -> 256 channels at 56x56, N = 4, 14.4 us instead of 12.5.)
 int choose_form(const Problem& p) {
     const long long pixels = (long long)p.N * p.H * p.W;
     int best = -1;
@@ -180,9 +212,8 @@ int choose_form(const Problem& p) {
         const Form& f = kForms[i];
         if (lds_bytes(f, p) > kLdsMost) continue;
         const long long groups = (pixels + f.P - 1) / f.P * ceil_div(p.K, f.F);
-        const int per_cu = std::max(1, kLdsMost / lds_bytes(f, p));
         constexpr double clocks_per_product[4] = {1.0, 1.3, 1.6, 1.6};   // relative
-        const double cost = (double)((groups + compute_units() * per_cu - 1) / (compute_units() * per_cu)) * per_cu * f.F * f.P * clocks_per_product[i] + 4000.0;
+        const double cost = (double)((groups + compute_units() - 1) / compute_units()) * f.F * f.P * clocks_per_product[i];
         if (best < 0 || cost < best_cost) {
             best = i;
             best_cost = cost;

@@ -1,0 +1,21 @@
+"""The linear-pixel direct convolution over several channel blocks: its pixel buffers and the halves of a block alternate."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1901_01965_amd as wg
+from paper_1901_01965_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+# N, C, K, H, W: 1 to 6 channel blocks, last ones of 16 to 64 channels, in each of the four forms; the last pixel of the batch
+# beside every edge of a workgroup
+@pytest.mark.parametrize("C", [64, 112, 192, 208, 320, 336])
+@pytest.mark.parametrize("shape", [(1, 24, 9, 11), (5, 72, 51, 1), (7, 64, 60, 61), (9, 130, 61, 60), (17, 200, 33, 61)])
+def test_channel_blocks(C, shape):
+    N, K, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, act="uniform", wgt="uniform", seed=C)
+    y = wg.direct_conv2d_int8(torch.from_numpy(wl.to_nhwc(x)).cuda(), torch.from_numpy(wl.to_krsc(g)).cuda(), wg.NHWC)
+    assert np.array_equal(wl.from_nhwc(y.cpu().numpy()), oracle.direct_conv2d(x, g))
