@@ -5,8 +5,8 @@
 // wave tile of 64 filters x 128 pixels asks for 6 KB per eight of them, 96 B per clock for four SIMDs; the 32 x 64 tile per
 // wave of the patch kernel (direct_conv.hip) asks for 192 B per clock.  Vector instructions delay matrix instructions of their
 // SIMD, so the loop has few: read addresses are kept, not formed (see at_pixel), and transfers take one addition each
-// (93 vector instructions for 144 products; formed anew, 620).  256 -> 256 channels at 56x56, N = 16: 39.8 -> 37.4 us (1580 TOPS),
-// of which set-up and first transfers 3, stores of 51 MB at the end, all compute units at once, 11; 512 -> 512 at 28x28
+// (93 vector instructions for 144 products; formed anew, 620).  256 -> 256 channels at 56x56, N = 16: 39.8 -> 36.0 us (1640 TOPS),
+// of which set-up and first transfers 3, stores of 51 MB at the end, all compute units at once, 10; 512 -> 512 at 28x28
 // 39.4 -> 35.5, 256 -> 256 at 56x56 N = 4 16.0 -> 12.7.  (A 256 x 224 tile of 16 x 16 x 64 products, 224 workgroups instead of
 // 196 there: 40.2 against 39.8.)
 //
@@ -35,6 +35,8 @@ __device__ inline void to_lds_16(__amdgpu_buffer_rsrc_t buffer, int8_t* lds_dst,
 // Fragments are read at addresses within LDS, kept as integers: as offsets from its start each read added that start first.
 using LdsBytes = const __attribute__((address_space(3))) int8_t;
 __device__ inline v4i fragment_at(int address) { return *reinterpret_cast<const __attribute__((address_space(3))) v4i*>(reinterpret_cast<LdsBytes*>((uintptr_t)(uint32_t)address)); }
+
+constexpr int kStagedPixel = 64 * 4 + 16;   // bytes of a pixel's 64 sums in LDS, and what keeps the writes off each other's banks
 
 // Pixel rows a workgroup keeps, rounded up to whole 1 KB transfers; a row of zeros follows them.
 __host__ __device__ inline int halo_rows(int P, int W) { return (P + 2 * W + 2 + 15) / 16 * 16; }
@@ -170,6 +172,51 @@ __global__ __launch_bounds__(64 * WF * WP) void direct_gemm_kernel(const int8_t*
         });
     }
 
+    // Whole cache lines per store: 32 pixels x 64 filters at a time by way of LDS, 256 bytes of a pixel from 16 lanes, or from 64 where
+    // K is no multiple of 4.  Stored from the registers, 32 bytes a pixel, the 51 MB of 256 -> 256 channels at 56x56, N = 16 took
+    // 37.4 us in all instead of 36.0, 16 -> 320 at 19x19, N = 43 9.9 instead of 8.2; 151 -> 245 at 54x14,
+    // N = 106 112 instead of 73; 60 mixed channels-last layers 1.08 times as fast.  Waves with fewer filters, 33 where K is no multiple
+    // of 4: level, or slower by the trip (97 -> 23 at 18x18, N = 4 10.1 and 10.7).
+    const int kw = k0 + wf * 64;
+    const bool quads = (p.K & 3) == 0;
+    const int staged_from = quads ? 64 : 33;
+    if (LAYOUT == WG_NHWC && k0 + staged_from <= p.K) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // nobody reads the last stage's rows any more
+        if (kw + staged_from <= p.K) {
+            int8_t* const mine = lds + wave * (32 * kStagedPixel);
+            int8_t* const put = mine + (lane & 31) * kStagedPixel + 16 * upper;
+#pragma unroll
+            for (int g = 0; g < PG; ++g) {
+                const int first = p0 + (wp * PG + g) * 32;
+#pragma unroll
+                for (int f = 0; f < 2; ++f)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<v4i*>(put + 128 * f + 32 * q) = (v4i){acc[f][g][4 * q], acc[f][g][4 * q + 1], acc[f][g][4 * q + 2], acc[f][g][4 * q + 3]};
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if (quads) {
+                    const int8_t* const take = mine + (lane >> 4) * kStagedPixel + 16 * (lane & 15);
+                    const int pixel = first + (lane >> 4);
+                    int32_t* const out = y + (size_t)pixel * p.K + kw + 4 * (lane & 15);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const v4i v = *reinterpret_cast<const v4i*>(take + 4 * i * kStagedPixel);
+                        if (pixel + 4 * i < pixels) *reinterpret_cast<v4i*>(out + (size_t)(4 * i) * p.K) = v;
+                    }
+                } else if (kw + lane < p.K) {
+                    int32_t* const out = y + (size_t)first * p.K + kw + lane;
+#pragma unroll 8
+                    for (int i = 0; i < 32; ++i) {
+                        const int32_t v = *reinterpret_cast<const int32_t*>(mine + i * kStagedPixel + 4 * lane);
+                        if (first + i < pixels) out[(size_t)i * p.K] = v;
+                    }
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            }
+            return;
+        }
+    }
     // register i of a 32x32 product: row (filter) 8 (i / 4) + 4 (lane / 32) + i % 4, column (pixel) lane % 32
 #pragma unroll
     for (int g = 0; g < PG; ++g) {
@@ -183,7 +230,7 @@ __global__ __launch_bounds__(64 * WF * WP) void direct_gemm_kernel(const int8_t*
             for (int q = 0; q < 4; ++q) {
                 const int k = k0 + wf * 64 + f * 32 + 8 * q + 4 * upper;
                 const v4i v = {acc[f][g][4 * q], acc[f][g][4 * q + 1], acc[f][g][4 * q + 2], acc[f][g][4 * q + 3]};
-                if (LAYOUT == WG_NHWC && (p.K & 3) == 0) {
+                if (LAYOUT == WG_NHWC && quads) {
                     if (k < p.K) *reinterpret_cast<v4i*>(out + k) = v;
                 } else {
 #pragma unroll
@@ -199,7 +246,10 @@ struct Form {
 };
 constexpr Form kForms[] = {{128, 512, 512}, {64, 512, 512}, {64, 256, 512}, {64, 128, 256}};
 constexpr int kLdsMost = 160 * 1024;
-int lds_bytes(const Form& f, const Problem& p) { return 2 * 3 * f.F * kCBlock + 2 * halo_bytes_of(f.P, p.W); }
+// (the sums of 32 pixels and 64 filters per wave take the place of the operands)
+int lds_bytes(const Form& f, const Problem& p) {
+    return std::max(2 * 3 * f.F * kCBlock + 2 * halo_bytes_of(f.P, p.W), f.threads / 64 * 32 * kStagedPixel);
+}
 
 // The form with the least estimated time: workgroups of the fullest compute unit times what one takes, its matrix instructions
 // at the share of the peak that its wave tile reaches.  (Counting whole rounds of two where two fit a compute unit, as before, took

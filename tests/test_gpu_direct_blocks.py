@@ -19,3 +19,14 @@ def test_channel_blocks(C, shape):
     x, g = wl.make_custom(N, C, K, H, W, act="uniform", wgt="uniform", seed=C)
     y = wg.direct_conv2d_int8(torch.from_numpy(wl.to_nhwc(x)).cuda(), torch.from_numpy(wl.to_krsc(g)).cuda(), wg.NHWC)
     assert np.array_equal(wl.from_nhwc(y.cpu().numpy()), oracle.direct_conv2d(x, g))
+
+
+# sums that go to memory by way of LDS: K whole quads and not, one filter more and less than the lines (64, 33) in a workgroup's first and
+# last wave, the last pixel of the batch in the middle of a wave's 32
+@pytest.mark.parametrize("K", [32, 33, 60, 64, 65, 97, 124, 128, 161, 196, 257])
+@pytest.mark.parametrize("shape", [(1, 16, 3, 7), (2, 32, 37, 41), (17, 16, 59, 60)])
+def test_sums_by_way_of_lds(K, shape):
+    N, C, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, act="uniform", wgt="uniform", seed=K)
+    y = wg.direct_conv2d_int8(torch.from_numpy(wl.to_nhwc(x)).cuda(), torch.from_numpy(wl.to_krsc(g)).cuda(), wg.NHWC)
+    assert np.array_equal(wl.from_nhwc(y.cpu().numpy()), oracle.direct_conv2d(x, g))
