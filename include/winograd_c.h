@@ -362,7 +362,7 @@ int winograd_debug_force_path(int path);
 int winograd_debug_stream_workgroups(int n);
 /* Test hook for the single-kernel path in WG_LOSSLESS mode, which has two forms of the product phase: one whose
    matrix-core filter operand carries both int8 limbs of eight filters (a wave owns complete outputs; channels-last
-   inputs with C % 4 = 0), and one with 16 filters per operand and the rows of the Winograd-domain tile split over two
+   inputs with C % 4 = 0, channel-major ones whose patches can be read as they lie), and one with 16 filters per operand and the rows of the Winograd-domain tile split over two
    waves (any layout).  0: the library's choice, 1: the first form wherever the layout allows, 2: never the first
    form.  Process-wide, like winograd_debug_force_path. */
 int winograd_debug_lossless_variant(int variant);

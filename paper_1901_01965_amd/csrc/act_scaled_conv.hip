@@ -140,7 +140,7 @@ template <int PW> constexpr int act_rq_off() { return PW == 8 ? 2 * kLdsBytes : 
 template <int PW> constexpr int act_lds_bytes() { return act_rq_off<PW>() + kActRqBytes + PW * kParkedScaleBytes; }
 static_assert(2 * kActPlaneBuffer <= kLdsBytes && act_lds_bytes<8>() <= 160 * 1024, "LDS of one compute unit");
 
-// grid (ceil(T/16), Kp/(8 PW)), 64 (4 + PW) threads: the roles of fused_conv_roles_kernel (roles_kernel.h): waves 0-3 transform one
+// grid (ceil(T/16), ceil(K / (8 PW))), 64 (4 + PW) threads: the roles of fused_conv_roles_kernel (roles_kernel.h): waves 0-3 transform one
 // channel block ahead, the others multiply; product wave pw owns filter block pw % (PW / 2) and half pw / (PW / 2) of the entries.
 template <int LAYOUT, int PW, bool NARROW>
 __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS,

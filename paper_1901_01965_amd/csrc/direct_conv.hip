@@ -2,8 +2,8 @@
 // multiplications per 4x4 output tile and channel pair that Section 3.4 compares
 // against:  y[n,k,h,w] = sum_{c,a,b} x[n,c,h+a-1,w+b-1] g[k,c,a,b].
 // Serves as the on-device cross-check and the direct baseline.  Where scratch memory (or the layout) allows, the
-// matrix product over linear pixels in direct_gemm.hip runs; this file has what is left for calls without scratch memory,
-// for rows too long for that kernel's LDS and for deep layers of few pixels (see few_patches): channels-last tensors with
+// matrix product over linear pixels in direct_gemm.hip runs; this file has what is left for calls without scratch memory
+// and for rows too long for that kernel's LDS: channels-last tensors with
 // K % 4 == 0 and a 16-byte aligned output on the matrix cores by patches (operands are staged with 16-byte loads when
 // C % 16 == 0 and the pointers allow it, else byte by byte), everything else in the plain kernel; and the requantisation kernels.
 #include "wg_internal.h"
@@ -274,24 +274,15 @@ DirectPlan plan_direct(const Problem& p, int layout, bool operands_aligned) {
 
 }  // namespace
 
-// Deep layers of few pixels: a workgroup of the linear-pixel kernel takes 1.8 - 2.0 us per 64 channels (three stages, each
-// with a barrier and a wait for its taps), one of the patch kernel, which loads all nine taps of a block at once, 1.5 - 1.6, and
-// with fewer workgroups than the chip holds that is the layer's time (1x14x14, 512 -> 512: 16.4 us by patches, 19.6 by linear
-// pixels; 8x56x56, 256 -> 64: 12.3 / 12.9).  Beyond that the linear-pixel kernel's rate counts.  The lines, in patch workgroups
-// per compute unit, by patches / by linear pixels: four channel blocks or more, 1.5: 26.9 / 28.3 us and 16.5 / 17.7, 1.75: 16.9 / 16.6
-// and 26.9 / 28.0, 2: 28.5 / 26.5; two or three, 0.56: 7.8 / 8.1, 0.88: 8.7 / 8.5, 1: 8.7 / 8.3.  One block: level.
-bool few_patches(const Problem& p) {
-    const long long patches = (long long)p.N * ceil_div(p.H, kPatchRows) * ceil_div(p.W, kPatchCols) * ceil_div(p.K, kDirectFilters);
-    return p.CB >= 4 ? 8 * patches <= 13LL * compute_units() : p.CB >= 2 && 4 * patches <= 3LL * compute_units();
-}
-
 size_t direct_conv_scratch_wanted(const Problem& p, int layout) { return plan_direct(p, layout, true).bytes; }
 
 hipError_t launch_direct_conv(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, int layout,
                               const Scratch& scratch, hipStream_t s) {
     const bool vectors = p.C % 16 == 0 && aligned16(x) && aligned16(w), by_patches = layout == WG_NHWC && p.K % 4 == 0 && aligned16(y);
     const DirectPlan d = plan_direct(p, layout, aligned16(x) && aligned16(w));
-    if (d.applies && d.bytes <= scratch.bytes && !(by_patches && vectors && few_patches(p))) {
+    // (Patches are behind wherever both run, also where few workgroups make a layer's time that of one: 1x14x14, 512 -> 512 16.4 us by
+    // patches, 12.4 by linear pixels; 48x7x7, 512 -> 512 21.9 / 13.4; 36x14x14, 128 -> 128 7.4 / 6.1.)
+    if (d.applies && d.bytes <= scratch.bytes) {
         if (d.copy_x) {
             int8_t* const xs = static_cast<int8_t*>(scratch.p);
             int8_t* const ws = xs + d.x_bytes;

@@ -29,7 +29,7 @@
 namespace wg {
 namespace {
 
-// grid: (ceil(T/16), Kp/32), or Kp/64 for WIDE.  256 threads: in the transform phase one thread per (tile,
+// grid: (ceil(T/16), ceil(K/32)), or ceil(K/64) for WIDE.  256 threads: in the transform phase one thread per (tile,
 // four channels); in the product phase wave w owns filter block (w & 1) and half of the
 // rows of M (w >> 1: rows 0,1,2 or rows 5,3); all four waves stage their partial outputs
 // in LDS and the block stores the sums with full-line writes.
@@ -325,7 +325,7 @@ struct BothScaledSums {
     }
 };
 
-// grid (ceil(T/16), Kp/32), 256 threads with the roles of fused_conv_body; the blob is a WG_SCALED one of signed int8
+// grid (ceil(T/16), ceil(K/32)), 256 threads with the roles of fused_conv_body; the blob is a WG_SCALED one of signed int8
 // filters.  Pass 1 transforms every channel block of the workgroup's 16 tiles and keeps the running maxima; each
 // thread then looks up the factors of one or two (tile, entry) pairs; pass 2 transforms again (the patches now come
 // from the caches), scales, and multiplies.  act_table (may be null) receives int32 [T][26][4] = (n, p, r, q).

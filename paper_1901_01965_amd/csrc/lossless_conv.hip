@@ -470,7 +470,7 @@ struct RawPatch {
     }
 };
 
-// grid (ceil(T/16), Kp/32, splits), 512 threads.
+// grid (ceil(T/16), ceil(K/32), splits), 512 threads.
 // OUT kOutSums: the workgroup takes `blocks` channel blocks from blockIdx.z * blocks on and leaves the sum of its outputs,
 // before the rescale by 2^-4, at y as int32 [blockIdx.z][16 gridDim.x tiles][output 4i+j][Kp] (the output transform is
 // linear, so these add up to the whole; sums_finish_kernel adds, rescales and stores).
@@ -768,7 +768,7 @@ struct QuarterProducts {
     }
 };
 
-// grid (ceil(T/16), Kp/32, splits), 512 threads; sums: int32 [split][36][16 gridDim.x tiles][Kp].
+// grid (ceil(T/16), ceil(K/32), splits), 512 threads; sums: int32 [split][36][16 gridDim.x tiles][Kp].
 template <int LOAD>
 __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, const uint8_t* __restrict__ blob, size_t planes_off,
                                                           int32_t* __restrict__ sums, Problem p, int blocks) {
