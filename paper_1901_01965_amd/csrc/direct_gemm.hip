@@ -253,7 +253,8 @@ int lds_bytes(const Form& f, const Problem& p) {
 
 // The form with the least estimated time: workgroups of the fullest compute unit times what one takes, its matrix instructions
 // at the share of the peak that its wave tile reaches.  (Counting whole rounds of two where two fit a compute unit, as before, took
-// 64 x 128 for 196 workgroups of 64 x 256: 256 -> 256 channels at 56x56, N = 4, 14.4 us instead of 12.5.)
+// 64 x 128 for 196 workgroups of 64 x 256: 256 -> 256 channels at 56x56, N = 4, 14.4 us instead of 12.5.  The shares: 256 -> 256 at
+// 56x56, N = 16 37.3, 44.6, 43.5, 52.9 us by the four forms, 512 -> 512 at 28x28 48.9, 35.4, 36.2, 45.5.)
 int choose_form(const Problem& p) {
     const long long pixels = (long long)p.N * p.H * p.W;
     int best = -1;
@@ -262,7 +263,7 @@ int choose_form(const Problem& p) {
         const Form& f = kForms[i];
         if (lds_bytes(f, p) > kLdsMost) continue;
         const long long groups = (pixels + f.P - 1) / f.P * ceil_div(p.K, f.F);
-        constexpr double clocks_per_product[4] = {1.0, 1.3, 1.6, 1.6};   // relative
+        constexpr double clocks_per_product[4] = {1.0, 1.3, 1.4, 1.8};   // relative
         const double cost = (double)((groups + compute_units() - 1) / compute_units()) * f.F * f.P * clocks_per_product[i];
         if (best < 0 || cost < best_cost) {
             best = i;
