@@ -19,6 +19,9 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
     __shared__ int maxima[4 * kEntries];
     __shared__ uint32_t table[kActMax + 1];
     const int tid = threadIdx.x, lane = tid & 63, cb = tid >> 6;
+    // (one or two waves take longer to bring it than to look it up: 54 -> 48 channels at 51x51, N = 2 19.5 us and 16.4, 90 -> 200 at
+    // 40x40, N = 8 28.3 and 24.4; four, 256 -> 256 at 14x14, N = 64: 26.4 with it in LDS, 26.8 without)
+    const bool table_in_lds = p.CB > 2;
     const BlobHeaderWords header = read_blob_header(blob);
     const int tile = PatchLoader::tile_of(0, lane), t = blockIdx.x * 4 + tile, cq = PatchLoader::quad_of(lane);
     int n = 0, ty = 0, tx = 0;
@@ -27,7 +30,8 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
     loader.enter(p, n, ty, tx, lane);
     loader.drop_absent_channels(p, cb, lane);
     loader.request(activation_buffer(x, p), cb);
-    for (int i = tid; i <= kActMax; i += blockDim.x) table[i] = kActScale.v[i];
+    if (table_in_lds)
+        for (int i = tid; i <= kActMax; i += blockDim.x) table[i] = kActScale.v[i];
     for (int i = tid; i < 4 * kEntries; i += blockDim.x) maxima[i] = 0;
     __syncthreads();
     s16x2 mx[kEntries];
@@ -55,7 +59,8 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
     for (int i = tid; i < 4 * kEntries; i += blockDim.x) {
         const size_t at = (size_t)blockIdx.x * 4 * kEntries + i;   // [tile][entry]
         if (at >= (size_t)p.T * kEntries) break;
-        const uint32_t entry = table[min(maxima[i], kActMax)];
+        const int largest = min(maxima[i], kActMax);
+        const uint32_t entry = table_in_lds ? table[largest] : kActScale.v[largest];
         factors[at] = entry;
         if (act_table != nullptr) *reinterpret_cast<v4i*>(act_table + 4 * at) = act_table_row(entry);
     }
