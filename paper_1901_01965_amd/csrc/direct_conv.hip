@@ -281,7 +281,7 @@ hipError_t launch_direct_conv(const int8_t* x, const int8_t* w, int32_t* y, cons
     const bool vectors = p.C % 16 == 0 && aligned16(x) && aligned16(w), by_patches = layout == WG_NHWC && p.K % 4 == 0 && aligned16(y);
     const DirectPlan d = plan_direct(p, layout, aligned16(x) && aligned16(w));
     // (Patches are behind wherever both run, also where few workgroups make a layer's time that of one: 1x14x14, 512 -> 512 16.4 us by
-    // patches, 12.4 by linear pixels; 48x7x7, 512 -> 512 21.9 / 13.4; 36x14x14, 128 -> 128 7.4 / 6.1.)
+    // patches, 12.2 by linear pixels; 48x7x7, 512 -> 512 21.9 / 13.2; 36x14x14, 128 -> 128 7.4 / 5.7.)
     if (d.applies && d.bytes <= scratch.bytes) {
         if (d.copy_x) {
             int8_t* const xs = static_cast<int8_t*>(scratch.p);

@@ -5,10 +5,10 @@
 // wave tile of 64 filters x 128 pixels asks for 6 KB per eight of them, 96 B per clock for four SIMDs; the 32 x 64 tile per
 // wave of the patch kernel (direct_conv.hip) asks for 192 B per clock.  Vector instructions delay matrix instructions of their
 // SIMD, so the loop has few: read addresses are kept, not formed (see at_pixel), and transfers take one addition each
-// (93 vector instructions for 144 products; formed anew, 620).  256 -> 256 channels at 56x56, N = 16: 39.8 -> 36.0 us (1640 TOPS),
-// of which set-up and first transfers 3, stores of 51 MB at the end, all compute units at once, 10; 512 -> 512 at 28x28
-// 39.4 -> 35.5, 256 -> 256 at 56x56 N = 4 16.0 -> 12.7.  (A 256 x 224 tile of 16 x 16 x 64 products, 224 workgroups instead of
-// 196 there: 40.2 against 39.8.)
+// (93 vector instructions for 144 products; formed anew, 620, and 256 -> 256 channels at 56x56, N = 16 took 39.8 us instead of 37.4,
+// 512 -> 512 at 28x28 39.4 instead of 35.5).  The former takes 33.0 us (1790 TOPS) on activations of which half are zeros, 37.2 on
+// uniform ones, of which set-up and first transfers some 2, stores of 51 MB at the end, all compute units at once, 10; 256 -> 256 at
+// 56x56, N = 4 11.2.  (A 256 x 224 tile of 16 x 16 x 64 products, 224 workgroups instead of 196 there: level.)
 //
 // Workgroup: P consecutive pixels of the batch (in memory order, so only the last workgroup has idle columns, whatever the
 // image size) x F filters.  LDS holds, per block of 64 channels, the pixel rows p0 - W - 1 .. p0 + P + W (a tap is a row
@@ -115,10 +115,6 @@ __global__ __launch_bounds__(64 * WF * WP) void direct_gemm_kernel(const int8_t*
 #pragma unroll
         for (int g = 0; g < PG; ++g) acc[f][g] = (v16i){0};
 
-    request_halo(0, halo);
-    request_taps(0, 0, taps);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
     // Six steps of 32 channels (tap b, half) a stage.  A step's fragments are read while the step before multiplies, a stage's first
     // ones too: the barrier that says that its rows are there comes before the last step of the stage before, when all
     // fragments of that stage are in registers.
