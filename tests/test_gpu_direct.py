@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 # and next to a multiple of a workgroup's, several channel blocks with a partial last one, one-pixel images, rows too long
 # for its LDS
 SHAPES = [(1, 16, 64, 16, 32), (1, 64, 65, 1, 129), (3, 80, 130, 7, 7), (130, 16, 8, 1, 1), (4, 130, 64, 33, 31),
-          (2, 16, 257, 91, 113), (8, 64, 192, 56, 56), (33, 48, 640, 28, 28), (1, 20, 36, 3, 700), (1, 5, 3, 2, 600)]
+          (2, 16, 257, 91, 113), (8, 64, 192, 56, 56), (33, 48, 640, 28, 28), (1, 20, 36, 3, 700), (1, 5, 3, 2, 600),
+          # rows too long: the patch kernel with 16-byte loads (C % 16 = 0, K % 4 = 0), a partial last block, two filter blocks
+          (1, 32, 36, 3, 700), (2, 80, 68, 9, 650)]
 
 
 @pytest.mark.parametrize("layout", [wg.NCHW, wg.NHWC])
@@ -46,16 +48,16 @@ def test_requantisation_of_any_int32(shape, layout, pool):
         assert np.array_equal(wl.from_nhwc(got) if nhwc else got, v.astype(np.int8))
 
 
-# N, C, K, H, W around the lines between the patch kernel and the linear-pixel kernel (patch workgroups: 3/4 of 256 with two or
-# three channel blocks, 13/8 of 256 with more), and patches that are not full
+# N, C, K, H, W: deep layers of few pixels
 @pytest.mark.parametrize("shape", [(96, 128, 128, 8, 16), (97, 128, 128, 8, 16), (16, 176, 36, 19, 50), (104, 256, 256, 7, 16), (105, 256, 200, 8, 15),
                                    (1, 496, 68, 13, 21), (5, 256, 4, 1, 1)])
 def test_few_patches_of_deep_layers(shape):
-    """Channels-last tensors, which take either kernel by their sizes, against the same layer channel-major, which always runs
-    the linear-pixel kernel, and the first image against the oracle."""
+    """Both layouts run the linear-pixel kernel, channel-major through copies of both operands: the two against each other, and the
+    first and the last image against the oracle."""
     N, C, K, H, W = shape
     x, g = wl.make_custom(N, C, K, H, W, act="uniform", wgt="uniform", seed=4)
     got = wg.direct_conv2d_int8(torch.from_numpy(wl.to_nhwc(x)).cuda(), torch.from_numpy(wl.to_krsc(g)).cuda(), wg.NHWC)
     other = wg.direct_conv2d_int8(torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda(), wg.NCHW)
     assert torch.equal(got.permute(0, 3, 1, 2), other)
-    assert np.array_equal(other[:1].cpu().numpy(), oracle.direct_conv2d(x[:1], g))
+    for n in {0, N - 1}:
+        assert np.array_equal(other[n:n + 1].cpu().numpy(), oracle.direct_conv2d(x[n:n + 1], g))
