@@ -247,10 +247,12 @@ int lds_bytes(const Form& f, const Problem& p) {
     return std::max(2 * 3 * f.F * kCBlock + 2 * halo_bytes_of(f.P, p.W), f.threads / 64 * 32 * kStagedPixel);
 }
 
-// The form with the least estimated time: workgroups of the fullest compute unit times what one takes, its matrix instructions
-// at the share of the peak that its wave tile reaches.  (Counting whole rounds of two where two fit a compute unit, as before, took
-// 64 x 128 for 196 workgroups of 64 x 256: 256 -> 256 channels at 56x56, N = 4, 14.4 us instead of 12.5.  The shares: 256 -> 256 at
-// 56x56, N = 16 37.3, 44.6, 43.5, 52.9 us by the four forms, 512 -> 512 at 28x28 48.9, 35.4, 36.2, 45.5.)
+// The form with the least estimated time: workgroups of the fullest compute unit times what one takes.  Per output that is, for each
+// channel block, its products and the pixel rows that come beside its own, and once the set-up and the stores, which the other
+// workgroups' products hide where two or more fit a compute unit.  The weights are fitted to 1720 layers of 16 .. 512 channels and
+// rows of 7 .. 112 pixels, every form timed on each, and are 0.4 % from the best form on average.  (Products alone, at 1.0, 1.3, 1.4
+// and 1.8: 2.5 %, with one channel block 4 %: 16 -> 304 at 23x23, N = 28 9.3 us, by 64 x 128 7.4; 16 -> 16 at 70x70, N = 129 27.9, by
+// 64 x 256 22.1.)
 int choose_form(const Problem& p) {
     const long long pixels = (long long)p.N * p.H * p.W;
     int best = -1;
@@ -259,8 +261,9 @@ int choose_form(const Problem& p) {
         const Form& f = kForms[i];
         if (lds_bytes(f, p) > kLdsMost) continue;
         const long long groups = (pixels + f.P - 1) / f.P * ceil_div(p.K, f.F);
-        constexpr double clocks_per_product[4] = {1.0, 1.3, 1.4, 1.8};   // relative
-        const double cost = (double)((groups + compute_units() - 1) / compute_units()) * f.F * f.P * clocks_per_product[i];
+        constexpr double products[4] = {1.0, 1.55, 1.7, 1.7};   // relative, as are the others
+        const double beside = 1.95 * (halo_rows(f.P, p.W) - f.P) / f.P, once = 2 * lds_bytes(f, p) > kLdsMost ? 1.75 : 0.0;
+        const double cost = (double)((groups + compute_units() - 1) / compute_units()) * f.F * f.P * ((products[i] + beside) * p.CB + once);
         if (best < 0 || cost < best_cost) {
             best = i;
             best_cost = cost;

@@ -30,3 +30,14 @@ def test_sums_by_way_of_lds(K, shape):
     x, g = wl.make_custom(N, C, K, H, W, act="uniform", wgt="uniform", seed=K)
     y = wg.direct_conv2d_int8(torch.from_numpy(wl.to_nhwc(x)).cuda(), torch.from_numpy(wl.to_krsc(g)).cuda(), wg.NHWC)
     assert np.array_equal(wl.from_nhwc(y.cpu().numpy()), oracle.direct_conv2d(x, g))
+
+
+# the forms of 512 pixels per workgroup (64 and 128 filters), which take layers of three and more, or two, channel blocks on a full
+# chip: filters that end with, before and behind a workgroup's 64 or 128, in whole quads and not, rows short and long, ragged last blocks
+@pytest.mark.parametrize("shape", [(6, 144, 65, 72, 76), (17, 144, 129, 21, 61), (11, 144, 200, 22, 68), (16, 208, 191, 22, 62),
+                                   (15, 80, 193, 41, 80), (14, 144, 129, 39, 80), (7, 144, 257, 57, 80), (21, 144, 196, 22, 80)])
+def test_wide_forms(shape):
+    N, C, K, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, act="uniform", wgt="uniform", seed=K + W)
+    y = wg.direct_conv2d_int8(torch.from_numpy(wl.to_nhwc(x)).cuda(), torch.from_numpy(wl.to_krsc(g)).cuda(), wg.NHWC)
+    assert np.array_equal(wl.from_nhwc(y.cpu().numpy()), oracle.direct_conv2d(x, g))
