@@ -9,8 +9,9 @@
 // registers, three workgroups per compute unit whose waits overlap, 16.5 us.  Scaled mode: the filter fragments come by buffer
 // loads (load_fragment), whose addresses take no vector registers, so that it fits 128 and four workgroups share a compute unit:
 // 15.7 -> 14.5 us, 56x56x256 N = 16 66.6 -> 63.2, 14x14x256 N = 64 23.0 -> 20.8 (with 64-bit addresses it spilled at 128 and four
-// workgroups were 4-12 % slower; the smallest layers, whose chip is not full either way, 7.05 -> 7.2).  The reverse-scaling factors
-// are parked in LDS at the start, the blob header is compared only before the store, and pixels outside the image arrive as zeros.
+// workgroups were 4-12 % slower).  Layers with few channel blocks keep 64-bit addresses and three workgroups (launch_f2_fast).  The
+// reverse-scaling factors are parked in LDS at the start, the blob header is compared only before the store, and pixels outside the
+// image arrive as zeros.
 #include "kernel_common.h"
 
 namespace wg {
@@ -107,9 +108,10 @@ __device__ inline int unscale(int m, uint32_t rq) {
 }
 
 // grid: (ceil(T / 16), Kp / 64), 256 threads.  Transform: thread = (tile, four channels).  Products: wave w owns filters
-// 16 w .. 16 w + 15 of the 16 tiles for all 16 entries.
-template <int LAYOUT, int MODE, bool Q8, bool NARROW, class ENC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == WG_SCALED ? 4 : 3))) void f2_fast_kernel(
+// 16 w .. 16 w + 15 of the 16 tiles for all 16 entries.  BUFFERS: the filter fragments come by buffer loads, and in scaled mode four
+// workgroups share a compute unit.
+template <int LAYOUT, int MODE, bool Q8, bool NARROW, bool BUFFERS, class ENC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == WG_SCALED && BUFFERS ? 4 : 3))) void f2_fast_kernel(
     const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_ORDER_PARAMS, const uint8_t* __restrict__ blob, size_t table_off,
     size_t planes_off, int32_t* __restrict__ y, Problem p, ENC enc, Int8Epilogue q8) {
     WG_TAKE_GEOMETRY(p, 1);
@@ -167,7 +169,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == WG_
         v4i bf[kRing][NBP];
         auto request_b = [&](auto E) {
 #pragma unroll
-            for (int i = 0; i < NBP; ++i) bf[E % kRing][i] = load_fragment(b_cb, b_lane, (NBP * E + i) * kFilterFragBytes);
+            for (int i = 0; i < NBP; ++i) {
+                constexpr int first = NBP * E * kFilterFragBytes;
+                if constexpr (BUFFERS) bf[E % kRing][i] = load_fragment(b_cb, b_lane, first + i * kFilterFragBytes);
+                else                   bf[E % kRing][i] = *reinterpret_cast<const v4i*>(b_cb + first + i * kFilterFragBytes + b_lane);
+            }
         };
         if (step > 0) __syncthreads();   // the previous block's operand planes have been consumed
         patch.bias(u, enc);
@@ -334,13 +340,21 @@ bool f2_fast_holds(const Problem& p) {
 hipError_t launch_f2_fast(const int8_t* x, int is_unsigned, int zero_point, const void* blob, int32_t* y, const Problem& p, int layout,
                           int mode, const Int8Epilogue& q8, hipStream_t s) {
     const F2BlobLayout bl = f2_blob_layout(p.Kp, p.Cf, mode);
-    auto go = [&](auto L, auto M, auto Q, auto N, const auto& enc) -> hipError_t {
+    // 64-bit addresses and three workgroups per compute unit where buffer loads cost more than they give, us with / without:
+    // lossless, up to two channel blocks (56x56x64 N = 8 6.94 / 6.80, 28x28x128 N = 32 16.85 / 16.67; three blocks, 130 -> 176 at 58x30
+    // N = 36, 66.2 / 66.5, eight, 512 -> 512 at 7x7 N = 8, 18.0 / 18.6); scaled, one block and no fourth workgroup for any compute unit
+    // (56x56x64 N = 8 7.29 / 7.02, 64 -> 16 at 33x33 N = 22 6.72 / 6.55; with one, N = 16 11.0 / 11.7; two blocks level).
+    const dim3 grid(ceil_div(p.T, kTiles), p.Kp / kFilters);
+    const bool buffers = mode == WG_LOSSLESS ? p.CB > 2 : p.CB > 1 || (long long)grid.x * grid.y > 3LL * compute_units();
+    auto launch = [&](auto L, auto M, auto Q, auto N, auto B, const auto& enc) -> hipError_t {
         using ENC = std::decay_t<decltype(enc)>;
-        const dim3 grid(ceil_div(p.T, kTiles), p.Kp / kFilters);
         const GridOrder order = grid_order(grid, 8);   // (with fewer filter blocks the launch order is as fast)
-        f2_fast_kernel<L, M, Q, N, ENC><<<grid, 256, kLds, s>>>(x, WG_GEOMETRY(p), WG_ORDER(order), static_cast<const uint8_t*>(blob),
-                                                                bl.table_off, bl.planes_off, y, p, enc, q8);
+        f2_fast_kernel<L, M, Q, N, B, ENC><<<grid, 256, kLds, s>>>(x, WG_GEOMETRY(p), WG_ORDER(order), static_cast<const uint8_t*>(blob),
+                                                                   bl.table_off, bl.planes_off, y, p, enc, q8);
         return hipGetLastError();
+    };
+    auto go = [&](auto L, auto M, auto Q, auto N, const auto& enc) {
+        return buffers ? launch(L, M, Q, N, std::true_type{}, enc) : launch(L, M, Q, N, std::false_type{}, enc);
     };
     // a channel sum is at most C * 127 * (4 * 128, or 4 * 255 with a zero point)
     const long long most = (long long)p.Cf * 127 * 4 * (is_unsigned ? 255 : 128);

@@ -317,3 +317,26 @@ def test_rows_too_long_for_32_bit_offsets(layout, C):
             crop = wg.f2x2_conv2d_int8(x[:, :, first:last].contiguous(), packed, layout)
             inner = slice(0 if first == 0 else 2, 200 if last == W else 198)
             assert torch.equal(y[:, :, first:last][:, :, inner], crop[:, :, inner])
+
+
+# N, C, K, H, W, mode: the line between the two kinds of fragment loads (scaled, one channel block: three workgroups for each of 256
+# compute units, 768 and 774 or 776 here; lossless: two and three channel blocks), and reordered grids (from eight blocks of 64 filters)
+# that are no multiple of the eight XCDs
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("shape,mode", [((1, 8, 16, 192, 256), wg.SCALED), ((1, 8, 16, 192, 258), wg.SCALED), ((1, 4, 70, 128, 193), wg.SCALED),
+                                        ((2, 120, 70, 10, 14), wg.LOSSLESS), ((2, 132, 70, 10, 14), wg.LOSSLESS),
+                                        ((1, 16, 520, 10, 9), wg.LOSSLESS), ((1, 16, 520, 10, 9), wg.SCALED),
+                                        ((5, 72, 600, 13, 11), wg.SCALED), ((1, 136, 640, 7, 13), wg.LOSSLESS)])
+def test_kinds_of_fragment_loads_and_reordered_grids(shape, mode, layout):
+    N, C, K, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, act="uniform", wgt="uniform", seed=91)
+    want = oracle.direct_conv2d(x, g) if mode == wg.LOSSLESS else oracle.f2_conv2d(x, g, oracle.SCALED, 127)[0]
+    packed = wg.f2x2_filter_transform(_g(g, layout), layout, mode)
+    assert np.array_equal(_y(wg.f2x2_conv2d_int8(_x(x, layout), packed, layout), layout), want)
+    q = wg.f2x2_conv2d_int8_requant(_x(x, layout), packed, 10, False, False, layout).cpu().numpy()
+    assert np.array_equal(q if layout == wg.NCHW else wl.from_nhwc(q), oracle.requant_relu_pool(want, 10, False, False))
+    xq, gq, x9, g9 = _u8_case(N, C, K, H, W, 117, 131, seed=C)
+    xd, gd = _dev(xq if layout == wg.NCHW else wl.to_nhwc(xq)), _dev(gq if layout == wg.NCHW else wl.to_krsc(gq))
+    want = oracle.direct_conv2d_i16(x9, g9) if mode == wg.LOSSLESS else oracle.f2_conv2d_i16(x9, g9, oracle.SCALED, 127)[0]
+    y = wg.f2x2_conv2d_int8(xd, wg.f2x2_filter_transform(gd, layout, mode, zero_point=131), layout, zero_point=117)
+    assert np.array_equal(_y(y, layout), want)
