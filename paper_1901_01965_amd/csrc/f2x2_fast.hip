@@ -348,7 +348,7 @@ hipError_t launch_f2_fast(const int8_t* x, int is_unsigned, int zero_point, cons
     const bool buffers = mode == WG_LOSSLESS ? p.CB > 2 : p.CB > 1 || (long long)grid.x * grid.y > 3LL * compute_units();
     auto launch = [&](auto L, auto M, auto Q, auto N, auto B, const auto& enc) -> hipError_t {
         using ENC = std::decay_t<decltype(enc)>;
-        const GridOrder order = grid_order(grid, 8);   // (with fewer filter blocks the launch order is as fast)
+        const GridOrder order(grid, grid.y >= 8 ? kByFilters : kLaunchOrder);   // (with fewer filter blocks the launch order is as fast)
         f2_fast_kernel<L, M, Q, N, B, ENC><<<grid, 256, kLds, s>>>(x, WG_GEOMETRY(p), WG_ORDER(order), static_cast<const uint8_t*>(blob),
                                                                    bl.table_off, bl.planes_off, y, p, enc, q8);
         return hipGetLastError();

@@ -183,9 +183,6 @@ __device__ __forceinline__ void fused_conv_body(const int8_t* __restrict__ x, co
     }
 }
 
-// (with a single channel block the planes are small and the order made no difference)
-inline GridOrder order_of(dim3 grid, const Problem& p) { return grid_order(grid, p.CB >= 2 ? 5 : ~0u); }
-
 template <int LAYOUT, int LOAD, int MODE, bool SUMS, bool WIDE>
 __global__ __launch_bounds__(256) void fused_conv_kernel(const int8_t* __restrict__ x,
                                                          const uint8_t* __restrict__ blob, size_t table_off,
@@ -216,10 +213,11 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(kernel, lds_bytes)) return e;
     dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters * (WIDE ? 2 : 1)));
+    const GridOrder order(grid, workgroup_order(p, MODE));
     if constexpr (Q8)
-        fused_conv_int8_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE><<<grid, 256, lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, p, q8, order_of(grid, p));
+        fused_conv_int8_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE><<<grid, 256, lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, p, q8, order);
     else
-        fused_conv_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE><<<grid, 256, lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, order_of(grid, p));
+        fused_conv_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE><<<grid, 256, lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, order);
     return hipGetLastError();
 }
 
@@ -456,7 +454,8 @@ hipError_t launch_u8(const int8_t* x, ZeroPointU8 zero, const uint8_t* blob, con
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_u8_kernel<LAYOUT, LOAD, MODE, SUMS>), kLdsBytes)) return e;
     dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters));
-    fused_conv_u8_kernel<LAYOUT, LOAD, MODE, SUMS><<<grid, 256, kLdsBytes, s>>>(x, zero, blob, bl.table_off, bl.planes_off, y, p, order_of(grid, p));
+    fused_conv_u8_kernel<LAYOUT, LOAD, MODE, SUMS><<<grid, 256, kLdsBytes, s>>>(x, zero, blob, bl.table_off, bl.planes_off, y, p,
+                                                                              GridOrder(grid, workgroup_order(p, MODE)));
     return hipGetLastError();
 }
 

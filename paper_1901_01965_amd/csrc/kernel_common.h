@@ -25,37 +25,49 @@ struct LdsPlaneSink {
     }
 };
 
-// Workgroups are dealt to the eight XCDs (each with its own L2) in turn.  With five or more filter blocks, the order in which an
-// XCD runs consecutive tile blocks of as few filter blocks as possible, so that a filter block's operand planes enter one or two
-// L2s instead of all eight (several channel blocks: 272 -> 400 filters at 9x21, N = 32, scaled 20.5 -> 18.5 us, 336 -> 464 at
-// 20x10, N = 35, 33.5 -> 31.3; 166 -> 402 at 85x27, lossless, 19.3 -> 17.8).  With fewer, every XCD would read most of the activations
-// instead of an eighth, while all filters may lie in every L2: launch order (164 -> 67 filters at 27x27, N = 73, lossless 47.8 us in
-// the other, 42.6 in this one; 368 -> 64 at 31x31, N = 20, scaled 28.1, 25.2; 120 drawn layers of at most 256 filters 1.2 %).
-// (What it takes is worked out on the host: a division by gridDim.x, which is itself a load, stood before a workgroup's first
-// request and cost a 19 us kernel half a microsecond.)
+// Workgroups are dealt to the eight XCDs (each with its own L2) in turn.  kByTiles: an XCD runs all filter blocks of consecutive tile
+// blocks, which share their patches, the patches' overlaps and the cache lines of channels-last outputs that two filter blocks
+// write; kByFilters: consecutive tile blocks of as few filter blocks as possible, so that a filter block's operand planes enter one
+// or two L2s instead of all eight.  (What it takes is worked out on the host: a division by gridDim.x, which is itself a load, stood
+// before a workgroup's first request and cost a 19 us kernel half a microsecond.)
+enum WorkgroupOrder { kLaunchOrder, kByTiles, kByFilters };
 struct GridOrder {
     int across;            // gridDim.x
     uint32_t each, rest;   // workgroups per XCD, rounded down, and what is left; each = 0: launch order
-    FastDiv by_across;
-    __device__ inline GridOrder(uint32_t o_across, uint32_t o_each, uint32_t o_mul, uint32_t o_rest_shift)
-        : across((int)o_across), each(o_each), rest(o_rest_shift & 7), by_across{o_mul, o_rest_shift >> 3} {}
-    inline GridOrder(dim3 grid, unsigned from)   // from: filter blocks
-        : across((int)grid.x), each(grid.y < from ? 0 : grid.x * grid.y >> 3), rest(grid.x * grid.y & 7), by_across(make_fast_div(grid.x)) {}
+    uint32_t deep;         // gridDim.y, 0: by filters
+    FastDiv by_inner;      // by what lies together: filter blocks, or tile blocks
+    __device__ inline GridOrder(uint32_t o_across, uint32_t o_each, uint32_t o_mul, uint32_t o_small)
+        : across((int)o_across), each(o_each), rest(o_small & 7), deep(o_small >> 8), by_inner{o_mul, (o_small >> 3) & 31} {}
+    inline GridOrder(dim3 grid, WorkgroupOrder order)
+        : across((int)grid.x), each(order == kLaunchOrder || grid.y == 1 ? 0 : grid.x * grid.y >> 3), rest(grid.x * grid.y & 7),
+          deep(order == kByTiles ? grid.y : 0), by_inner(make_fast_div(order == kByTiles ? grid.y : grid.x)) {}
     __device__ inline void place(int& bx, int& by) const {
-        bx = blockIdx.x;
-        by = blockIdx.y;
-        if (each == 0) return;
-        const uint32_t launch = blockIdx.y * (uint32_t)across + blockIdx.x, xcd = launch & 7;
-        const uint32_t at = xcd * each + min(xcd, rest) + (launch >> 3);
-        by = (int)fast_div(at, by_across);
-        bx = (int)at - by * across;
+        int tile_block = blockIdx.x, filter_block = blockIdx.y;
+        if (each != 0) {
+            const uint32_t launch = blockIdx.y * (uint32_t)across + blockIdx.x, xcd = launch & 7;
+            const uint32_t at = xcd * each + min(xcd, rest) + (launch >> 3);
+            const uint32_t outer = fast_div(at, by_inner), inner = at - outer * (deep ? deep : (uint32_t)across);
+            tile_block = (int)(deep ? outer : inner);
+            filter_block = (int)(deep ? inner : outer);
+        }
+        bx = tile_block;
+        by = filter_block;
     }
 };
-inline GridOrder grid_order(dim3 grid, unsigned from = 5) { return GridOrder(grid, from); }
+// By tiles, except where the operand planes are more than an L2 holds beside the rest and outweigh the activations.  us, launch order /
+// by filters / by tiles: 32 -> 145 filters at 92x92, N = 39, both sides scaled, 225 / 247 / 192; 48 -> 128 at 56x84, N = 59, scaled,
+// channel-major, 88.4 / 72.6 / 70.2; 234 -> 65 at 57x9, N = 26, scaled, 20.8 / 20.9 / 18.0; 29 -> 432 at 49x12, N = 177, scaled, 72.6 / 86.0 /
+// 75.8; 176 -> 448 at 9x8, N = 28, lossless, int8 out, 14.8 / 13.0 / 14.6; 240 -> 443 at 9x9, N = 16, lossless, 18.6 / 16.7 / 18.3.  1300 drawn
+// layers of two and more filter blocks: 0.3 % behind the best order on average and 9 at worst (launch order alone 2.9 and 26, by
+// filters 3.0 and 28, by tiles 0.35 and 12, launch order or by filters from five filter blocks on 2.6 and 26).
+inline WorkgroupOrder workgroup_order(const Problem& p, int mode) {
+    const long long pixels = (long long)p.N * p.H * p.W, planes = (long long)p.K * num_filter_planes(mode);
+    return planes * p.CB * kCBlock > 3000000 && planes > 3 * pixels ? kByFilters : kByTiles;
+}
 // as leading arguments (see WG_GEOMETRY_PARAMS, after which they fill what is loaded ahead)
-#define WG_ORDER_PARAMS uint32_t o_across, uint32_t o_each, uint32_t o_mul, uint32_t o_rest_shift
-#define WG_ORDER(o) (uint32_t)(o).across, (o).each, (o).by_across.mul, (o).rest | (o).by_across.shift << 3
-#define WG_TAKE_ORDER GridOrder(o_across, o_each, o_mul, o_rest_shift)
+#define WG_ORDER_PARAMS uint32_t o_across, uint32_t o_each, uint32_t o_mul, uint32_t o_small
+#define WG_ORDER(o) (uint32_t)(o).across, (o).each, (o).by_inner.mul, (o).rest | (o).by_inner.shift << 3 | (o).deep << 8
+#define WG_TAKE_ORDER GridOrder(o_across, o_each, o_mul, o_small)
 
 // compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(<N-1>)
 template <class F, int... Is>

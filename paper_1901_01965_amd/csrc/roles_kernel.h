@@ -174,8 +174,9 @@ hipError_t launch_roles(const int8_t* x, const ENC& enc, const uint8_t* blob, co
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC>), lds_bytes)) return e;
     dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters * (PW / 4)));
+    const GridOrder order(grid, workgroup_order(p, MODE));
     fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC><<<grid, 64 * (4 + PW), lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, y, p, q8,
-                                                                                             enc, grid_order(grid));
+                                                                                             enc, order);
     return hipGetLastError();
 }
 
