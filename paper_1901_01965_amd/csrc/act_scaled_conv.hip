@@ -267,7 +267,9 @@ hipError_t launch_act_factors(const RolesCall& c, uint32_t* factors, int32_t* ac
 
 hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, hipStream_t s) {
     // 64 filters per workgroup unless 32 fill the compute units in one round, or in so few rounds that a half-empty 64-filter block
-    // costs more (see run_roles in fused_conv.hip)
+    // costs more: a round of 32 takes about four fifths of one of 64 (both kernels together, us, 64 / 32 filters: three rounds against
+    // four, 480 -> 80 at 59x79, N = 14, 108.8 / 126.3; six against eight, 79 -> 80 at 27x34, N = 169, 106.2 / 114.8; two each, 59 -> 32
+    // at 47x47, N = 57, 49.2 / 43.2; 350 drawn layers 0.01 % behind the better one on average, with the line at 1.34 0.08).
     auto go = [&](auto L, auto W, auto NARROW) -> hipError_t {
         constexpr int PW = W;
         static LdsLimitOnce lds_limit;   // per instance
@@ -281,7 +283,7 @@ hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, 
     using std::integral_constant;
     const int tile_blocks = ceil_div(c.p.T, kFusedTiles), cus = compute_units();
     auto rounds = [&](int filters) { return ((long long)tile_blocks * ceil_div(c.p.K, filters) + cus - 1) / cus; };
-    const bool wide = rounds(32) > 1 && 100 * rounds(32) >= 134 * rounds(64);
+    const bool wide = rounds(32) > 1 && 4 * rounds(32) >= 5 * rounds(64);
     // a channel sum is at most 2 x 127 x 127 C (Re = Dr Wr - Di Wi), r at most 255
     const bool narrow = 2ll * 127 * 127 * c.p.Cf < 1 << 23;
     static_assert(((1ll << 23) - 1) * 255 + 64 < 1ll << 31, "a narrow sum times r, rounded, fits int32");

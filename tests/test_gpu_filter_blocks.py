@@ -41,7 +41,11 @@ def test_equals_oracle(shape, mode):
     assert np.array_equal(wl.from_nhwc(q.cpu().numpy()), oracle.requant_relu_pool(want, 10, True, False))
 
 
-@pytest.mark.parametrize("shape", [(1, 72, 16, 40, 33), (2, 40, 97, 30, 30), (1, 130, 330, 22, 18)])
+@pytest.mark.parametrize("shape", [
+    (1, 72, 16, 40, 33), (2, 40, 97, 30, 30), (1, 130, 330, 22, 18),
+    (1, 20, 80, 256, 260),    # 260 tile blocks: four rounds of 32 filters, three of 64
+    (1, 12, 16, 280, 280),    # 307: two and two
+])
 def test_activations_scaled_as_well(shape):
     N, C, K, H, W = shape
     x, g = wl.make_custom(N, C, K, H, W, act="relu", wgt="gauss", seed=9)
