@@ -10,6 +10,9 @@ namespace wg {
 namespace {
 
 // ---- factors ---------------------------------------------------------------------------------------------
+// One or two waves take longer to bring the factor table than to look it up: 54 -> 48 channels at 51x51, N = 2 19.5 us and 16.4, 90 -> 200
+// at 40x40, N = 8 28.3 and 24.4; four, 256 -> 256 at 14x14, N = 64: 26.4 with it in LDS, 26.8 without.
+__host__ __device__ inline bool table_in_lds(const Problem& p) { return p.CB > 2; }
 // grid: ceil(T / 4), 64 CB threads: wave = 64-channel block, lane = (tile, four channels).  Bound by latency: a patch load, a
 // transform, a reduction.  The factor table comes to LDS beside the patch (looked up in memory it was a second trip after the
 // reduction), and the reduction over a tile's sixteen lanes stays in the vector ALU.
@@ -17,11 +20,8 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
                                                            uint32_t* __restrict__ factors, int32_t* __restrict__ act_table, Problem p) {
     WG_TAKE_GEOMETRY(p, 2);
     __shared__ int maxima[4 * kEntries];
-    __shared__ uint32_t table[kActMax + 1];
+    extern __shared__ uint32_t table[];   // kActMax + 1, or none
     const int tid = threadIdx.x, lane = tid & 63, cb = tid >> 6;
-    // (one or two waves take longer to bring it than to look it up: 54 -> 48 channels at 51x51, N = 2 19.5 us and 16.4, 90 -> 200 at
-    // 40x40, N = 8 28.3 and 24.4; four, 256 -> 256 at 14x14, N = 64: 26.4 with it in LDS, 26.8 without)
-    const bool table_in_lds = p.CB > 2;
     const BlobHeaderWords header = read_blob_header(blob);
     const int tile = PatchLoader::tile_of(0, lane), t = blockIdx.x * 4 + tile, cq = PatchLoader::quad_of(lane);
     int n = 0, ty = 0, tx = 0;
@@ -30,7 +30,7 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
     loader.enter(p, n, ty, tx, lane);
     loader.drop_absent_channels(p, cb, lane);
     loader.request(activation_buffer(x, p), cb);
-    if (table_in_lds)
+    if (table_in_lds(p))
         for (int i = tid; i <= kActMax; i += blockDim.x) table[i] = kActScale.v[i];
     for (int i = tid; i < 4 * kEntries; i += blockDim.x) maxima[i] = 0;
     __syncthreads();
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(1024) void act_factors_kernel(const int8_t* __restr
         const size_t at = (size_t)blockIdx.x * 4 * kEntries + i;   // [tile][entry]
         if (at >= (size_t)p.T * kEntries) break;
         const int largest = min(maxima[i], kActMax);
-        const uint32_t entry = table_in_lds ? table[largest] : kActScale.v[largest];
+        const uint32_t entry = table_in_lds(p) ? table[largest] : kActScale.v[largest];
         factors[at] = entry;
         if (act_table != nullptr) *reinterpret_cast<v4i*>(act_table + 4 * at) = act_table_row(entry);
     }
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
 }  // namespace
 
 hipError_t launch_act_factors(const RolesCall& c, uint32_t* factors, int32_t* act_table, hipStream_t s) {
-    act_factors_kernel<<<ceil_div(c.p.T, 4), 64 * c.p.CB, 0, s>>>(c.x, WG_GEOMETRY(c.p), c.blob, factors, act_table, c.p);
+    act_factors_kernel<<<ceil_div(c.p.T, 4), 64 * c.p.CB, table_in_lds(c.p) ? (kActMax + 1) * sizeof(uint32_t) : 0, s>>>(c.x, WG_GEOMETRY(c.p), c.blob, factors, act_table, c.p);
     return hipGetLastError();
 }
 
