@@ -485,10 +485,12 @@ struct Plan {
 // average, with filters in the L2 as well):
 //   lossless: 5.7 + 2.68 CB in one kernel, 4.8 + 3.27 b + W / 50 + CB K / 2700 split (N = 1, 512 -> 512 at 14x14: 26 - 36, 11.1 - 12.8)
 //   scaled:   5.9 + 1.65 CB in one kernel, 9.1 + 1.92 b + W / 28 split (18 - 24, 16.7 - 17.6; N = 4: 18.4, 21.4)
-// and 3.9 b - 2.2 more where the split kernels cannot read 16-byte pieces (N = 2, 324 -> 512 at 28x28, lossless: 21.6, 32.8).
-bool split_pays(int mode, int CB, int K, int b, int W, bool pieces) {
-    const double one = mode == WG_LOSSLESS ? 5.7 + 2.68 * CB : 5.9 + 1.65 * CB;
-    const double split = mode == WG_LOSSLESS ? 4.8 + 3.27 * b + W / 50.0 + CB * K / 2700.0 : 9.1 + 1.92 * b + W / 28.0;
+// and 3.9 b - 2.2 more where the split kernels cannot read 16-byte pieces (N = 2, 324 -> 512 at 28x28, lossless: 21.6, 32.8).  One
+// kernel takes 0.6 less with up to 32 filters (250 drawn layers; 272 -> 16 at 17x17, N = 10, scaled: 13.3, 14.1; 116 -> 16 at 64x7,
+// N = 15, lossless: 10.4, 11.2).
+bool split_pays(int mode, int CB, int K, int Kp, int b, int W, bool pieces) {
+    const double one = (mode == WG_LOSSLESS ? 5.7 + 2.68 * CB : 5.9 + 1.65 * CB) - (K <= kFusedFilters ? 0.6 : 0.0);
+    const double split = mode == WG_LOSSLESS ? 4.8 + 3.27 * b + W / 50.0 + CB * Kp / 2700.0 : 9.1 + 1.92 * b + W / 28.0;
     return one > split + (pieces ? 0.0 : 3.9 * b - 2.2);
 }
 
@@ -510,7 +512,7 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
     const bool may_split = p.CB >= 2 && 2 * workgroups <= compute_units() && !is_unsigned && !hooked;
     const int blocks = may_split ? ceil_div(p.CB, std::min(p.CB, compute_units() / workgroups)) : p.CB, splits = ceil_div(p.CB, blocks);
     auto split = [&](bool pieces) {
-        if (!may_split || !split_pays(mode, p.CB, p.Kp, blocks, splits * workgroups, pieces) || split_partial_bytes(p, mode, splits) > left) return false;
+        if (!may_split || !split_pays(mode, p.CB, p.K, p.Kp, blocks, splits * workgroups, pieces) || split_partial_bytes(p, mode, splits) > left) return false;
         plan.splits = splits;
         plan.blocks = blocks;
         return true;

@@ -24,6 +24,8 @@ SHAPES = [  # N, C, K, H, W
     (1, 72, 330, 96, 96),     # 216 workgroups of 64 filters
     (3, 72, 330, 9, 9),       # 22 of 32
     (1, 264, 80, 20, 36),     # split channels
+    (1, 224, 16, 24, 24), (1, 224, 16, 48, 48),   # at most 32 filters: split in either mode, and in lossless mode alone
+    (1, 116, 16, 80, 96),     # in one kernel in either mode, by 4-byte loads
 ]
 
 
