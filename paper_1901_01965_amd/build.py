@@ -25,8 +25,10 @@ HIPCC_FLAGS = [
 ]
 
 # A kernel's leading scalar arguments are in registers when a wave starts (WG_GEOMETRY_PARAMS).  Not in the one-tile-block
-# role-specialised kernels, which are slower with it (512 -> 512 at 7x7, N = 64: 19.8 -> 20.1 us, uint8 128 -> 128 at 28x28, N = 32:
-# 13.3 -> 13.6; signed int8 level).
+# role-specialised kernels: with the same arguments in the same order, deep layers of one round lose by it (512 -> 512 at 7x7, N = 32,
+# 18.7 -> 19.2 us, 384 -> 512 at 14x14, N = 16, 15.9 -> 16.3) more than shallow ones gain (128 -> 128 at 28x28, N = 32, 12.2 -> 12.1; uint8
+# 12.4 -> 12.5).  Why a prologue should cost eight channel blocks more than two is not known; it is not where their loops lie in
+# memory (aligned to 64 or 256 bytes: the same times).
 PRELOAD_FLAGS = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 NOT_PRELOADED = ("roles_scaled.hip", "roles_lossless.hip")
 
