@@ -594,6 +594,9 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
     // and with several blocks 32-filter rounds take 1 / 1.34 of those with eight product waves (C = 128, scaled: 32 filters 15.6
     // and 22.0 for two and three rounds, 64 filters 11.4, 20.4, 30.4 for one to three; lossless 18.0, 25.3 / 13.8, 23.5, 33.8).
     // (64 -> 32 filters, 28x28, N = 162, scaled: 34 -> 15.6 us, lossless N = 490 60 -> 30; 128 -> 32, N = 162, 30.2 -> 22.0.)
+    // Not where int8 outputs are stored byte by byte (not pooled, K no multiple of four): the four waves that store take up to 8 us a
+    // round of 32 filters and 13 one of 64, the limb-pair kernel's eight no longer than otherwise (62 -> 334 at 86x86, N = 2, 25.1 us against
+    // 35.8, 21 -> 138 at 43x43, N = 16, 24.3 / 32.4; 40 drawn layers 0.68 - 1.03 of what they took).
     if (!whole64 && w32 > cus && stream_variant == 0 && variant == 0 && !forced_stream && lossless_variant() != 1) {
         const int r32 = ceil_div(tile_blocks, std::max(1, (int)cus / filter_blocks)), r64 = (int)((wide_grid + cus - 1) / cus);
         if (p.CB > 1) {
@@ -605,7 +608,9 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
             const bool scaled = mode == WG_SCALED;
             const double halves = scaled ? 5.0 + 3.65 * r32 : 4.4 + 4.25 * r32, whole = scaled ? 4.8 + 5.5 * r64 : 4.3 + 6.15 * r64;
             const bool pairs = pair_layer && lossless_pair_conv_choice(c.x, p, c.layout) != 0;
-            const double other = scaled ? (r64 == 1 ? 9.0 : 1e9) : pairs ? 1.0 + 5.9 * (double)((w32 + cus - 1) / cus) : 1e9;
+            const bool by_bytes = c.q8.out != nullptr && !c.q8.pool && (p.K & 3) != 0;
+            const double pair_cost = by_bytes ? 0.0 : 1.0 + 5.9 * (double)((w32 + cus - 1) / cus);
+            const double other = scaled ? (r64 == 1 ? 9.0 : 1e9) : pairs ? pair_cost : 1e9;
             if (other < halves && other < whole) status = scaled ? launch_roles(c, mode, true, s) : launch_lossless_pair_conv(c.x, c.blob, c.y, p, c.layout, c.q8, s);
             else                                 status = launch_stream(c, mode, halves < whole ? kStreamHalves : kStreamWhole, s);
             return true;

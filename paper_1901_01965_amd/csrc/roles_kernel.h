@@ -30,7 +30,8 @@ namespace {
 
 template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
 __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS,
-                                                                         WG_ORDER_PARAMS, const uint8_t* __restrict__ blob, size_t table_off, size_t planes_off, int32_t* __restrict__ y,
+                                                                         WG_ORDER_PARAMS, const uint8_t* __restrict__ blob,
+                                                                         size_t table_off, size_t planes_off, int32_t* __restrict__ y,
                                                                          Problem p, Int8Epilogue q8, ENC enc) {
     WG_TAKE_GEOMETRY(p, 2);
     const GridOrder order = WG_TAKE_ORDER;

@@ -18,7 +18,7 @@ def _dev(a):
 SHAPES = [  # N, C, K, H, W
     (1, 16, 16, 260, 260),    # one channel block, 265 workgroups of 32 filters
     (1, 16, 96, 190, 190),    # 144 tile blocks: 432 workgroups of 32 filters, 288 of 64
-    (1, 12, 161, 96, 96),     # a single round of 64 filters, 216 of 32 (one filter in the last block)
+    (1, 12, 161, 96, 96),     # 216 workgroups of 32 filters (one filter in the last block): the rule for more than a round does not apply
     (1, 72, 32, 260, 259),    # two channel blocks
     (1, 72, 96, 150, 150),    # 91 tile blocks
     (1, 72, 330, 96, 96),     # 216 workgroups of 64 filters
@@ -41,6 +41,41 @@ def test_equals_oracle(shape, mode):
     assert np.array_equal(wl.from_nhwc(y.cpu().numpy()), want)
     q = wg.winograd_conv2d_int8_requant(xd, packed, 10, True, False, wg.NHWC)
     assert np.array_equal(wl.from_nhwc(q.cpu().numpy()), oracle.requant_relu_pool(want, 10, True, False))
+
+
+# One channel block, more than one round of 32 filters: what the rule takes for signed channels-last tensors, scaled / lossless
+ONE_BLOCK = [
+    (1, 16, 96, 160, 160),    # 100 tile blocks: eight product waves / whole entries
+    (1, 16, 80, 210, 210),    # 176: whole entries in either mode
+    (1, 16, 16, 364, 364),    # 518: halves in either mode
+    (1, 12, 90, 150, 150),    # 91, int8 outputs byte by byte: eight product waves / the limb-pair kernel
+    (1, 9, 23, 262, 259),     # 269, the same: halves / the limb-pair kernel
+]
+
+
+@pytest.mark.parametrize("layout", [wg.NHWC, wg.NCHW])
+@pytest.mark.parametrize("mode", ["lossless", "scaled"])
+@pytest.mark.parametrize("shape", ONE_BLOCK)
+def test_one_channel_block(shape, mode, layout):
+    N, C, K, H, W = shape
+    nhwc, lossless = layout == wg.NHWC, mode == "lossless"
+    blob_mode = wg.LOSSLESS if lossless else wg.SCALED
+    put = lambda a: _dev(wl.to_nhwc(a) if nhwc else a)
+    get = lambda t: wl.from_nhwc(t.cpu().numpy()) if nhwc else t.cpu().numpy()
+    filters = lambda g: _dev(wl.to_krsc(g) if nhwc else g)
+    x, g = wl.make_custom(N, C, K, H, W, act="relu", wgt="gauss", seed=10)
+    want = oracle.direct_conv2d(x, g) if lossless else oracle.winograd_conv2d(x, g, oracle.SCALED, 127)[0]
+    packed = wg.winograd_filter_transform(filters(g), layout, blob_mode)
+    assert np.array_equal(get(wg.winograd_conv2d_int8(put(x), packed, layout)), want)
+    for pool in (False, True) if H % 2 == 0 and W % 2 == 0 else (False,):
+        q = wg.winograd_conv2d_int8_requant(put(x), packed, 10, True, pool, layout)
+        assert np.array_equal(get(q), oracle.requant_relu_pool(want, 10, True, pool))
+    rng = np.random.default_rng(K)
+    xq, gq = rng.integers(0, 256, x.shape, dtype=np.uint8), rng.integers(0, 256, g.shape, dtype=np.uint8)
+    x9, g9 = xq.astype(np.int16) - 117, gq.astype(np.int16) - 131
+    want = oracle.direct_conv2d_i16(x9, g9) if lossless else oracle.winograd_conv2d_i16(x9, g9, oracle.SCALED, 127)[0]
+    packed = wg.winograd_filter_transform_u8(filters(gq), 131, layout, blob_mode)
+    assert np.array_equal(get(wg.winograd_conv2d_u8(put(xq), 117, packed, layout)), want)
 
 
 @pytest.mark.parametrize("shape", [
