@@ -14,7 +14,7 @@ namespace {
 
 constexpr int kItems = 64;   // filters of one tile per workgroup
 
-// grid: (padded tiles, Kp / 64), 256 threads: lane = filter.
+// grid: (T, Kp / 64), 256 threads: lane = filter.
 template <int LAYOUT, bool Q8>
 __global__ __launch_bounds__(256) void split_finish_kernel(const int32_t* __restrict__ partial, WG_GEOMETRY_PARAMS, int Kp, int splits,
                                                            const uint8_t* __restrict__ blob,
@@ -24,8 +24,7 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const int32_t* __rest
     __shared__ int sums[3][kAccPlanes][kItems];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int k = blockIdx.y * kItems + lane, t = blockIdx.x;
-    if (t >= p.T) return;
-    const size_t plane = (size_t)((p.T + 15) / 16 * 16) * p.Kp;   // gridDim.x is the padded tile count, but itself a load
+    const size_t plane = (size_t)((p.T + 15) / 16 * 16) * p.Kp;   // sums are there for whole blocks of 16 tiles
     const int32_t* const mine = partial + (size_t)t * p.Kp + k;
     const BlobHeaderWords header = read_blob_header(blob);
     // the first wave finishes: it asks for its filter's factors (r, q) along with its sums
@@ -104,7 +103,7 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const int32_t* __rest
 
 // The same for launch_lossless_pair_sums, whose workgroups leave 16 x outputs: adds the splits, rescales and stores.
 // Thread: four filters of one output (one 2x2 window) of a tile, all splits' reads in flight together.
-// grid: (padded tiles, ceil(items / 256)): items = 16 (4) x Kp / 4 per tile.
+// grid: (T, ceil(items / 256)): items = 16 (4) x Kp / 4 per tile.
 template <int LAYOUT, bool Q8>
 __global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restrict__ sums, WG_GEOMETRY_PARAMS, int Kp, int splits,
                                                           const uint8_t* __restrict__ blob, int32_t* __restrict__ y, Problem p, Int8Epilogue q8) {
@@ -112,10 +111,10 @@ __global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restr
     p.Kp = Kp;
     const int t = blockIdx.x, item = blockIdx.y * 256 + threadIdx.x, k4s = p.Kp >> 2;
     const int pool = Q8 ? q8.pool : 0;
-    if (t >= p.T || item >= (pool ? 4 : 16) * k4s) return;
+    if (item >= (pool ? 4 : 16) * k4s) return;
     const BlobHeaderWords header = read_blob_header(blob);
     const int o = item / k4s, kk = 4 * (item - o * k4s);
-    const size_t split = (size_t)((p.T + 15) / 16 * 16) * 4 * p.Kp;   // v4i per split (gridDim.x is the padded tile count, but itself a load)
+    const size_t split = (size_t)((p.T + 15) / 16 * 16) * 4 * p.Kp;   // v4i per split: whole blocks of 16 tiles
     auto total = [&](int out) {   // finished outputs of filters kk .. kk + 3 at output `out`
         const v4i* from = reinterpret_cast<const v4i*>(sums) + (((size_t)t * 16 + out) * p.Kp + kk) / 4;
         v4i v = {0, 0, 0, 0};
@@ -163,8 +162,7 @@ __global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restr
 
 hipError_t launch_sums_finish(const RolesCall& c, const int32_t* sums, int splits, hipStream_t s) {
     const int items = (c.q8.out != nullptr && c.q8.pool ? 4 : 16) * (c.p.Kp / 4);
-    // tiles beyond T have sums, but nothing to store; `gridDim.x` is the padded count because it strides the splits
-    const dim3 grid(16 * ceil_div(c.p.T, 16), ceil_div(items, 256));
+    const dim3 grid(c.p.T, ceil_div(items, 256));
     auto go = [&](auto kernel) {
         kernel<<<grid, 256, 0, s>>>(sums, WG_GEOMETRY(c.p), c.p.Kp, splits, c.blob, c.y, c.p, c.q8);
         return hipGetLastError();
@@ -174,7 +172,7 @@ hipError_t launch_sums_finish(const RolesCall& c, const int32_t* sums, int split
 }
 
 hipError_t launch_split_finish(const RolesCall& c, const int32_t* partial, int splits, hipStream_t s) {
-    const dim3 grid(16 * ceil_div(c.p.T, 16), c.p.Kp / kItems);
+    const dim3 grid(c.p.T, c.p.Kp / kItems);
     auto go = [&](auto kernel) {
         kernel<<<grid, 256, 0, s>>>(partial, WG_GEOMETRY(c.p), c.p.Kp, splits, c.blob, c.bl.table_off, c.y, c.p, c.q8);
         return hipGetLastError();
