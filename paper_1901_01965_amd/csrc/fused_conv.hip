@@ -620,15 +620,12 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
                                   (long long)tile_blocks * filter_blocks <= compute_units();
     const bool streams = forced_stream || wide_one_block || narrow_one_round ||
                          tile_blocks >= 6 * stream_workgroups(tile_blocks, filter_blocks);
-    // Lossless mode, channels-last, one channel block, too few tile blocks to stream over: the limb-pair form (eight waves
-    // per 16 tiles x 32 filters, lossless_conv.hip) against the four-wave forms of this file, by rounds of the compute
-    // units: measured on 56x56x64 layers, a round of the former takes 6.5 us, a round of the latter 7.4 us with 32 filters
-    // per workgroup (a grid of at most one round) and 11.7 us with 64 filters.
+    // Lossless mode, channels-last, one channel block, at most one round of 32-filter workgroups (layers with more are streamed): the
+    // limb-pair form (eight waves per 16 tiles x 32 filters, lossless_conv.hip), 6.9 us a round on 56x56x64 layers, against
+    // 7.4 for the four-wave form of this file.
     if (pair_layer && !streams) {
         const int form = lossless_pair_conv_choice(c.x, p, c.layout);   // 0: not applicable or switched off, 1: the library decides, 2: forced
-        const double pair_cost = 6.5 * (double)((w32 + cus - 1) / cus);
-        const double here_cost = w32 <= cus ? 7.4 : 11.7 * (double)((w32 / 2 + cus - 1) / cus);
-        if (form == 2 || (form == 1 && p.CB == 1 && pair_cost < here_cost)) {
+        if (form == 2 || (form == 1 && p.CB == 1 && w32 <= cus)) {
             status = launch_lossless_pair_conv(c.x, c.blob, c.y, p, c.layout, c.q8, s);
             return true;
         }
