@@ -487,9 +487,10 @@ struct Plan {
 //   scaled:   5.9 + 1.65 CB in one kernel, 9.1 + 1.92 b + W / 28 split (18 - 24, 16.7 - 17.6; N = 4: 18.4, 21.4)
 // and 3.9 b - 2.2 more where the split kernels cannot read 16-byte pieces (N = 2, 324 -> 512 at 28x28, lossless: 21.6, 32.8).  One
 // kernel takes 0.6 less with up to 32 filters (250 drawn layers; 272 -> 16 at 17x17, N = 10, scaled: 13.3, 14.1; 116 -> 16 at 64x7,
-// N = 15, lossless: 10.4, 11.2).
-bool split_pays(int mode, int CB, int K, int Kp, int b, int W, bool pieces) {
-    const double one = (mode == WG_LOSSLESS ? 5.7 + 2.68 * CB : 5.9 + 1.65 * CB) - (K <= kFusedFilters ? 0.6 : 0.0);
+// N = 15, lossless: 10.4, 11.2), unless it needs a copy that the split kernels do without (`planes`; 480 -> 32 at 81x81, N = 1, scaled:
+// 25.7, 21.2).
+bool split_pays(int mode, int CB, int K, int Kp, int b, int W, bool pieces, bool planes) {
+    const double one = (mode == WG_LOSSLESS ? 5.7 + 2.68 * CB : 5.9 + 1.65 * CB) - (K <= kFusedFilters && !planes ? 0.6 : 0.0);
     const double split = mode == WG_LOSSLESS ? 4.8 + 3.27 * b + W / 50.0 + CB * Kp / 2700.0 : 9.1 + 1.92 * b + W / 28.0;
     return one > split + (pieces ? 0.0 : 3.9 * b - 2.2);
 }
@@ -511,15 +512,15 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
     const int workgroups = ceil_div(p.T, kFusedTiles) * ceil_div(p.K, kFusedFilters);
     const bool may_split = p.CB >= 2 && 2 * workgroups <= compute_units() && !is_unsigned && !hooked;
     const int blocks = may_split ? ceil_div(p.CB, std::min(p.CB, compute_units() / workgroups)) : p.CB, splits = ceil_div(p.CB, blocks);
-    auto split = [&](bool pieces) {
-        if (!may_split || !split_pays(mode, p.CB, p.K, p.Kp, blocks, splits * workgroups, pieces) || split_partial_bytes(p, mode, splits) > left) return false;
+    auto split = [&](bool pieces, bool planes) {
+        if (!may_split || !split_pays(mode, p.CB, p.K, p.Kp, blocks, splits * workgroups, pieces, planes) || split_partial_bytes(p, mode, splits) > left) return false;
         plan.splits = splits;
         plan.blocks = blocks;
         return true;
     };
     if (layout == WG_NCHW && !is_unsigned && plane_patches_hold(p)) {
         // the split kernels read channel-major patches as well, at 1.1 us more per further block, while a copy is a launch
-        plan.planes = (blocks <= 2 && split(true)) || (mode == WG_LOSSLESS && (lossless_variant() == 1 || (!hooked && pair_reads_planes(p))));
+        plan.planes = (blocks <= 2 && split(true, true)) || (mode == WG_LOSSLESS && (lossless_variant() == 1 || (!hooked && pair_reads_planes(p))));
         if (plan.planes) return plan;
     }
     if (layout != WG_NHWC || p.C % 4 != 0) {
@@ -528,7 +529,7 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
         if (!plan.copies) return plan;
         left -= channels_last_bytes(p);
     }
-    split(plan.copies ? padded_channels(p.C) % 16 == 0 : p.C % 16 == 0);   // (a caller's view may still start off a boundary)
+    split(plan.copies ? padded_channels(p.C) % 16 == 0 : p.C % 16 == 0, false);   // (a caller's view may still start off a boundary)
     return plan;
 }
 

@@ -30,6 +30,16 @@ SHAPES = [  # N, C, K, H, W
 
 
 @pytest.mark.parametrize("mode", ["lossless", "scaled"])
+@pytest.mark.parametrize("shape", [(1, 224, 16, 48, 48), (4, 240, 20, 19, 19), (1, 116, 16, 80, 96)])
+def test_few_filters_from_channel_major(shape, mode):   # split without a copy, with either kernel's sums
+    N, C, K, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, act="relu", wgt="gauss", seed=8)
+    want = oracle.direct_conv2d(x, g) if mode == "lossless" else oracle.winograd_conv2d(x, g, oracle.SCALED, 127)[0]
+    packed = wg.winograd_filter_transform(_dev(g), wg.NCHW, wg.LOSSLESS if mode == "lossless" else wg.SCALED)
+    assert np.array_equal(wg.winograd_conv2d_int8(_dev(x), packed, wg.NCHW).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("mode", ["lossless", "scaled"])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_equals_oracle(shape, mode):
     N, C, K, H, W = shape
