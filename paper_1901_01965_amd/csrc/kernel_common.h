@@ -27,9 +27,9 @@ struct LdsPlaneSink {
 
 // Workgroups are dealt to the eight XCDs (each with its own L2) in turn.  kByTiles: an XCD runs all filter blocks of consecutive tile
 // blocks, which share their patches, the patches' overlaps and the cache lines of channels-last outputs that two filter blocks
-// write; kByFilters: consecutive tile blocks of as few filter blocks as possible, so that a filter block's operand planes enter one
-// or two L2s instead of all eight.  (What it takes is worked out on the host: a division by gridDim.x, which is itself a load, stood
-// before a workgroup's first request and cost a 19 us kernel half a microsecond.)
+// write.  kByFilters: consecutive tile blocks of as few filter blocks as possible, so that a filter block's operand planes enter
+// one or two L2s instead of all eight.  (What it takes is worked out on the host: a division by gridDim.x, which is itself a load,
+// stood before a workgroup's first request and cost a 19 us kernel half a microsecond.)
 enum WorkgroupOrder { kLaunchOrder, kByTiles, kByFilters };
 struct GridOrder {
     int across;            // gridDim.x
@@ -48,21 +48,25 @@ struct GridOrder {
             const uint32_t at = xcd * each + min(xcd, rest) + (launch >> 3);
             const uint32_t outer = fast_div(at, by_inner), inner = at - outer * (deep ? deep : (uint32_t)across);
             tile_block = (int)(deep ? outer : inner);
-            filter_block = (int)(deep ? inner : outer);
+            // An XCD deals its workgroups to four shader engines in turn: a multiple of four filter blocks is turned by one from tile
+            // block to tile block, or one engine would get every last, perhaps half-empty one (16 -> 201 at 105x105, N = 4, scaled,
+            // int8 out, 49.2 -> 44.7 us; 84 layers of four filter blocks 1 %).
+            const uint32_t turned = inner + ((deep & 3) == 0 ? outer & 3 : 0);
+            filter_block = (int)(deep ? (turned >= deep ? turned - deep : turned) : outer);
         }
         bx = tile_block;
         by = filter_block;
     }
 };
-// By tiles, except where the operand planes are more than an L2 holds beside the rest and outweigh the activations.  us, launch order /
-// by filters / by tiles: 32 -> 145 filters at 92x92, N = 39, both sides scaled, 225 / 247 / 192; 48 -> 128 at 56x84, N = 59, scaled,
-// channel-major, 88.4 / 72.6 / 70.2; 234 -> 65 at 57x9, N = 26, scaled, 20.8 / 20.9 / 18.0; 29 -> 432 at 49x12, N = 177, scaled, 72.6 / 86.0 /
-// 75.8; 176 -> 448 at 9x8, N = 28, lossless, int8 out, 14.8 / 13.0 / 14.6; 240 -> 443 at 9x9, N = 16, lossless, 18.6 / 16.7 / 18.3.  1300 drawn
-// layers of two and more filter blocks: 0.3 % behind the best order on average and 9 at worst (launch order alone 2.9 and 26, by
-// filters 3.0 and 28, by tiles 0.35 and 12, launch order or by filters from five filter blocks on 2.6 and 26).
+// By tiles, except where the operand planes are more than 3 MB (an L2 has 4) and than twice the activations.  us, launch order / by
+// filters / by tiles: 32 -> 145 filters at 92x92, N = 39, both sides scaled, 225 / 247 / 192; 48 -> 128 at 56x84, N = 59, scaled,
+// channel-major, 88.4 / 72.6 / 70.2; 234 -> 65 at 57x9, N = 26, scaled, 20.8 / 20.9 / 18.0; 29 -> 432 at 49x12, N = 177, scaled, 72.6 /
+// 86.0 / 75.8; 176 -> 448 at 9x8, N = 28, lossless, int8 out, 14.8 / 13.0 / 14.6; 240 -> 443 at 9x9, N = 16, lossless, 18.6 / 16.7 / 18.3.
+// 1300 drawn layers of two and more filter blocks: 0.3 % behind the best order on average and 9 at worst (launch order alone 2.9
+// and 26, by filters 3.0 and 28, by tiles 0.35 and 12, launch order or, from five filter blocks on, by filters 2.6 and 26).
 inline WorkgroupOrder workgroup_order(const Problem& p, int mode) {
     const long long pixels = (long long)p.N * p.H * p.W, planes = (long long)p.K * num_filter_planes(mode);
-    return planes * p.CB * kCBlock > 3000000 && planes > 3 * pixels ? kByFilters : kByTiles;
+    return planes * p.CB * kCBlock > 3000000 && planes > 2 * pixels ? kByFilters : kByTiles;
 }
 // as leading arguments (see WG_GEOMETRY_PARAMS, after which they fill what is loaded ahead)
 #define WG_ORDER_PARAMS uint32_t o_across, uint32_t o_each, uint32_t o_mul, uint32_t o_small

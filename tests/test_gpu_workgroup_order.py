@@ -47,8 +47,9 @@ def _set_form(form):
         wg.lossless_variant(2)
 
 
-# N, C, K, H, W: 3, 6, 2, 2 and 2 tile blocks; the planes of the last two outweigh the activations
-SHAPES = [(1, 72, 75, 30, 22), (2, 72, 161, 30, 22), (1, 60, 130, 22, 18), (1, 264, 330, 22, 18), (1, 136, 364, 21, 18)]
+# N, C, K, H, W: 3, 6, 2, 9, 2 and 2 tile blocks; four and eight filter blocks in the fourth; the planes of the last two outweigh the
+# activations
+SHAPES = [(1, 72, 75, 30, 22), (2, 72, 161, 30, 22), (1, 60, 130, 22, 18), (3, 40, 225, 30, 22), (1, 264, 330, 22, 18), (1, 136, 364, 21, 18)]
 
 
 @pytest.mark.parametrize("layout", [wg.NHWC, wg.NCHW])
