@@ -52,13 +52,14 @@ struct RoleBarrier {
 //                   fused_conv_roles_kernel<PW = 8>, a third of its time at two channel blocks, run beside other tile blocks'
 //                   work.  The two halves would need twice the staging: the first writes, the second adds to it in LDS, a
 //                   longer chain per tile block, which one channel block does not pay for (56x56x64 N = 256 scaled: 77 us
-//                   with whole entries, 80 here).  Twelve waves leave 168 registers each, which is not quite enough: 4 are spilled
-//                   and reloaded in the transform waves' loop with signed channels-last tensors, 7 - 22 with uint8 or channel-major
-//                   outputs.  It is the fastest form all the same where fused_conv.hip chooses it, except for
-//                   channel-major int32 outputs, whose 32 plane offsets also spill 66 - 232 scalar registers (in every form).
+//                   with whole entries, 80 here).  Twelve waves leave 168 registers each: enough with signed channels-last
+//                   tensors and with int8 outputs, one or two spilled with uint8, 6 - 12 with channel-major int32 outputs, whose
+//                   32 plane offsets also spill 82 - 237 scalar registers (in every form).  It is the fastest form where
+//                   fused_conv.hip chooses it, which it does not for those outputs.
 // What bounds kStreamWhole (56x56x64, N = 256, clocks per tile block of 64 filters, lossless / scaled): the product wave's chain,
-// 13,500 / 12,400 = products with their joins, reverse scaling and output transform 10,700 / 9,800 + staging 880 + clearing the
-// outputs 800 / 1,000 + barriers, waits and prefetch 1,060 / 650.  It issues some 1,200 instructions, an instruction per 5
+// 13,500 / 12,400 = products with their joins, reverse scaling and output transform 10,700 / 9,800 + staging 880 + from
+// there to the next unit's barrier 800 / 1,000 (lossless mode clears the outputs in it, 64 instructions; what the rest waits for, and
+// all of it in scaled mode, which clears nothing, is not known) + barriers, waits and prefetch 1,060 / 650.  It issues some 1,200 instructions, an instruction per 5
 // clocks alone; but the transform wave on its SIMD (transform 4,300, flush of the staged tile block 4,000, waiting 4,000)
 // is the older one and goes first, and their vector instructions together occupy the SIMD for 1,764 x 4.4 + 224 x 8 = 9,600
 // (scaled 1,831 x 4.4 + 112 x 8 = 9,000) of those clocks.
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
 #pragma unroll
                 for (int i = 0; i < 16; ++i) Y[i] = (v4i){0, 0, 0, 0};
             }
-            WG_SPENT(5, mark);   // clearing the outputs
+            WG_SPENT(5, mark);   // from the staging on: clearing the outputs (lossless)
             published();
             WG_SPENT(0, mark);   // barrier U
             cx.a_lds = lds + (u & 1) * kLdsBytes + fragment_slot();
