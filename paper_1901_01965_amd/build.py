@@ -21,16 +21,10 @@ HIPCC_FLAGS = [
     # keep matrix-core results in ordinary vector registers where they fit: the vector ALU reads
     # them right away (limb joins, output transform) and would otherwise pay one copy per register
     "-mllvm", "-amdgpu-mfma-vgpr-form=1",
+    # a kernel's leading scalar arguments are in registers when a wave starts (WG_GEOMETRY_PARAMS)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-function",
 ]
-
-# A kernel's leading scalar arguments are in registers when a wave starts (WG_GEOMETRY_PARAMS).  Not in the one-tile-block
-# role-specialised kernels: with the same arguments in the same order, deep layers of one round lose by it (512 -> 512 at 7x7, N = 32,
-# 18.7 -> 19.2 us, 384 -> 512 at 14x14, N = 16, 15.9 -> 16.3) more than shallow ones gain (128 -> 128 at 28x28, N = 32, 12.2 -> 12.1; uint8
-# 12.4 -> 12.5).  Why a prologue should cost eight channel blocks more than two is not known; it is not where their loops lie in
-# memory (aligned to 64 or 256 bytes: the same times).
-PRELOAD_FLAGS = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
-NOT_PRELOADED = ("roles_scaled.hip", "roles_lossless.hip")
 
 
 def sources():
@@ -78,8 +72,7 @@ def build(verbose=False, incremental=False, jobs=None):
         fresh = (incremental and os.path.exists(obj) and
                  os.path.getmtime(obj) > max(os.path.getmtime(src), newest_header))
         if not fresh:
-            preload = [] if os.path.basename(src) in NOT_PRELOADED else PRELOAD_FLAGS
-            todo.append([hipcc] + HIPCC_FLAGS + preload + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", src, "-o", obj])
+            todo.append([hipcc] + HIPCC_FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", src, "-o", obj])
     ext_obj = os.path.join(OBJ_DIR, "torch_binding.o")
     ext_compile, ext_link = _extension_commands(ext_obj)
     if not (incremental and os.path.exists(ext_obj) and os.path.getmtime(ext_obj) > max(os.path.getmtime(EXT_SOURCE), newest_header)):

@@ -275,7 +275,7 @@ hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, 
         static LdsLimitOnce lds_limit;   // per instance
         if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW, NARROW>), act_lds_bytes<PW>())) return e;
         const dim3 grid(ceil_div(c.p.T, kFusedTiles), ceil_div(c.p.K, 8 * PW));
-        const GridOrder order(grid, workgroup_order(c.p, WG_SCALED));
+        const GridOrder order(grid, workgroup_order(c.p, WG_SCALED, 8 * PW));
         act_scaled_roles_kernel<L, PW, NARROW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(
             c.x, WG_GEOMETRY(c.p), WG_ORDER(order), c.blob, c.bl.table_off, c.bl.planes_off, c.y, factors, c.p);
         return hipGetLastError();

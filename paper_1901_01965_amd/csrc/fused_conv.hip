@@ -213,7 +213,7 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(kernel, lds_bytes)) return e;
     dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters * (WIDE ? 2 : 1)));
-    const GridOrder order(grid, workgroup_order(p, MODE));
+    const GridOrder order(grid, workgroup_order(p, MODE, kFusedFilters * (WIDE ? 2 : 1)));
     if constexpr (Q8)
         fused_conv_int8_kernel<LAYOUT, LOAD, MODE, SUMS, WIDE><<<grid, 256, lds_bytes, s>>>(x, blob, bl.table_off, bl.planes_off, p, q8, order);
     else
@@ -455,7 +455,7 @@ hipError_t launch_u8(const int8_t* x, ZeroPointU8 zero, const uint8_t* blob, con
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_u8_kernel<LAYOUT, LOAD, MODE, SUMS>), kLdsBytes)) return e;
     dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters));
     fused_conv_u8_kernel<LAYOUT, LOAD, MODE, SUMS><<<grid, 256, kLdsBytes, s>>>(x, zero, blob, bl.table_off, bl.planes_off, y, p,
-                                                                              GridOrder(grid, workgroup_order(p, MODE)));
+                                                                              GridOrder(grid, workgroup_order(p, MODE, kFusedFilters)));
     return hipGetLastError();
 }
 

@@ -58,15 +58,18 @@ struct GridOrder {
         by = filter_block;
     }
 };
-// By tiles, except where the operand planes are more than 3 MB (an L2 has 4) and than twice the activations.  us, launch order / by
-// filters / by tiles: 32 -> 145 filters at 92x92, N = 39, both sides scaled, 225 / 247 / 192; 48 -> 128 at 56x84, N = 59, scaled,
-// channel-major, 88.4 / 72.6 / 70.2; 234 -> 65 at 57x9, N = 26, scaled, 20.8 / 20.9 / 18.0; 29 -> 432 at 49x12, N = 177, scaled, 72.6 /
-// 86.0 / 75.8; 176 -> 448 at 9x8, N = 28, lossless, int8 out, 14.8 / 13.0 / 14.6; 240 -> 443 at 9x9, N = 16, lossless, 18.6 / 16.7 / 18.3.
-// 1300 drawn layers of two and more filter blocks: 0.3 % behind the best order on average and 9 at worst (launch order alone 2.9
-// and 26, by filters 3.0 and 28, by tiles 0.35 and 12, launch order or, from five filter blocks on, by filters 2.6 and 26).
-inline WorkgroupOrder workgroup_order(const Problem& p, int mode) {
+// By tiles, except where the operand planes are more than 3 MB (an L2 has 4) and than twice the activations, or than these where
+// the filters come out even, eight or sixteen full blocks (`filters` in each): an XCD's share is the same everywhere then.  us,
+// launch order / by filters / by tiles: 32 -> 145 filters at 92x92, N = 39, both sides scaled, 225 / 247 / 192; 48 -> 128 at 56x84, N = 59,
+// scaled, channel-major, 88.4 / 72.6 / 70.2; 234 -> 65 at 57x9, N = 26, scaled, 20.8 / 20.9 / 18.0; 29 -> 432 at 49x12, N = 177, scaled,
+// 72.6 / 86.0 / 75.8; 176 -> 448 at 9x8, N = 28, lossless, int8 out, 14.8 / 13.0 / 14.6; 240 -> 443 at 9x9, N = 16, lossless, 18.6 / 16.7 /
+// 18.3.  1300 drawn layers of two and more filter blocks: 0.3 % behind the best order on average and 9 at worst (launch order
+// alone 2.9 and 26, by filters 3.0 and 28, by tiles 0.35 and 12, launch order or, from five filter blocks on, by filters 2.6 and 26).
+// 512 filters and planes of 1 .. 1.5, 1.5 .. 2, 2 .. 3 times the activations: by filters 0.965, 1.00 and 0.96 of the time by tiles.
+inline WorkgroupOrder workgroup_order(const Problem& p, int mode, int filters) {
     const long long pixels = (long long)p.N * p.H * p.W, planes = (long long)p.K * num_filter_planes(mode);
-    return planes * p.CB * kCBlock > 3000000 && planes > 2 * pixels ? kByFilters : kByTiles;
+    const bool even = p.K % (8 * filters) == 0;
+    return planes * p.CB * kCBlock > 3000000 && planes > (even ? 1 : 2) * pixels ? kByFilters : kByTiles;
 }
 // as leading arguments (see WG_GEOMETRY_PARAMS, after which they fill what is loaded ahead)
 #define WG_ORDER_PARAMS uint32_t o_across, uint32_t o_each, uint32_t o_mul, uint32_t o_small

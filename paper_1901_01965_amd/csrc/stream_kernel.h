@@ -355,7 +355,7 @@ hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC>), lds_bytes)) return e;
     const int tile_blocks = ceil_div(c.p.T, kFusedTiles), filter_blocks = ceil_div(c.p.K, stream_filters<FORM>());
     const dim3 grid(stream_workgroups(tile_blocks, filter_blocks), filter_blocks);
-    const GridOrder order(grid, workgroup_order(c.p, MODE));
+    const GridOrder order(grid, workgroup_order(c.p, MODE, stream_filters<FORM>()));
     fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC><<<grid, 64 * (4 + stream_product_waves<FORM>()), lds_bytes, s>>>(
         c.x, WG_GEOMETRY(c.p), WG_ORDER(order), c.blob, c.bl.table_off, c.bl.planes_off, c.y, c.p, c.q8, enc);
     return hipGetLastError();
