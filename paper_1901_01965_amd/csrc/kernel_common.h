@@ -117,6 +117,19 @@ __device__ inline v4i load_fragment(const int8_t* base, uint32_t lane16, int at)
     const __amdgpu_buffer_rsrc_t blob = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(base), 0, 0x7fffffff, kRawBufferWord3);
     return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(blob, lane16, at, 0));
 }
+// Most instructions of the product loops and of the transform have eight bytes: whether they begin at multiples of eight or four
+// behind them decides 2 - 3 % of a kernel's time, and any change further up shifts it.  So the place is fixed, for each kind of
+// kernel where it measured best.  The streaming kernel at a multiple of eight / four behind, us: products, 64 -> 64 at 56x56, N = 256,
+// lossless, 87.3 / 87.6, scaled 76.3 / 77.7 (left alone 89.4 and 77.3), with eight product waves 256 -> 256 at 56x56, N = 16, scaled, 57.7 /
+// 57.0 (57.3), lossless 76.5 / 76.3 (79.2); transform, 64 -> 64, lossless, 85.0 / 82.2 (83.4), with inputs in rotation 96.3 / 93.7,
+// scaled 72.4 / 74.6 (74.9).
+template <bool FOUR_BEHIND>
+__device__ inline void place_loop(std::integral_constant<bool, FOUR_BEHIND>) {
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (FOUR_BEHIND) asm volatile(".p2align 3\n\ts_nop 0");
+    else asm volatile(".p2align 3");
+    __builtin_amdgcn_sched_barrier(0);
+}
 // The lane's number, formed anew where it is asked for: a register that is needed once per channel block is worth more than two
 // instructions there.
 __device__ inline int lane_again() {

@@ -147,14 +147,9 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
             __builtin_amdgcn_s_barrier();   // barrier cb + 1
             WG_SPENT(0, mark);   // barrier
             cx.a_lds = lds + (cb & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
-            // Nearly every instruction from here on has eight bytes: whether they begin at multiples of eight, or four behind them,
-            // decides 2.5 % of a deep layer, and any change further up shifts it.  So the place is fixed, for each kind of kernel where
-            // it measured best, at a multiple of eight / four behind: 512 -> 512 at 7x7, N = 32, scaled, 18.8 / 19.2 us, int8 out, 14x14,
-            // N = 16, 19.0 / 18.7; 192 -> 32 at 28x28, N = 16, uint8, 10.5 / 10.8, 128 -> 128, N = 32, 12.5 / 12.3; lossless 14.4 / 14.2.
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (Q8 || MODE == WG_LOSSLESS || (PW == 8 && !std::is_same_v<ENC, SignedInt8>)) asm volatile(".p2align 3\n\ts_nop 0");
-            else asm volatile(".p2align 3");
-            __builtin_amdgcn_sched_barrier(0);
+            // (512 -> 512 at 7x7, N = 32, scaled, at a multiple of eight / four behind 18.8 / 19.2 us, int8 out, 14x14, N = 16, 19.0 / 18.7;
+            // 192 -> 32 at 28x28, N = 16, uint8, 10.5 / 10.8, 128 -> 128, N = 32, 12.5 / 12.3; lossless 14.4 / 14.2)
+            place_loop(std::integral_constant<bool, Q8 || MODE == WG_LOSSLESS || (PW == 8 && !std::is_same_v<ENC, SignedInt8>)>{});
             phase.run(cx, sums);
             WG_SPENT(2, mark);   // products
         }

@@ -181,6 +181,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
                     if (cb == 0) enter_tile_block(bx + jb * order.across);
                     loader.drop_absent_channels(p, cb, my_lane());
                 }
+                place_loop(std::integral_constant<bool, FORM != kStreamWhole || MODE != WG_SCALED>{});
                 bias.apply(loader.patch);
                 WG_SPENT(5, mark);   // offsets
                 if (more) transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc, NextColumns{loader, xbuf, cb});
@@ -266,6 +267,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             published();
             WG_SPENT(0, mark);   // barrier U
             cx.a_lds = lds + (u & 1) * kLdsBytes + fragment_slot();
+            place_loop(std::false_type{});
             all.run(cx, Y);
             WG_SPENT(1, mark);   // products
             const bool last = cb == p.CB - 1;
@@ -295,6 +297,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
                 published();
                 WG_SPENT(0, mark);   // barrier U
                 cx.a_lds = lds + (u & 1) * kLdsBytes + fragment_slot();
+                place_loop(std::integral_constant<bool, FORM == kStreamEight>{});
                 phase.run(cx, sums);
                 WG_SPENT(1, mark);   // products
                 const bool last = cb == p.CB - 1;
