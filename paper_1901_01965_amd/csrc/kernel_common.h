@@ -113,9 +113,11 @@ __device__ inline __amdgpu_buffer_rsrc_t activation_buffer(const int8_t* x, cons
 // A 1 KB filter fragment, 16 bytes per lane: `base` is the same for the whole wave, `at` a constant, `lane16` = 16 x lane.  As a
 // buffer load it takes its address from scalar registers and one vector register; with 64-bit addresses every fourth fragment
 // cost two vector instructions and a pair of registers.
+__device__ inline v4i buffer_fragment(__amdgpu_buffer_rsrc_t from, uint32_t lane16, int at) {
+    return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(from, lane16, at, 0));
+}
 __device__ inline v4i load_fragment(const int8_t* base, uint32_t lane16, int at) {
-    const __amdgpu_buffer_rsrc_t blob = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(base), 0, 0x7fffffff, kRawBufferWord3);
-    return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(blob, lane16, at, 0));
+    return buffer_fragment(__builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(base), 0, 0x7fffffff, kRawBufferWord3), lane16, at);
 }
 // Most instructions of the product loops and of the transform have eight bytes: whether they begin at multiples of eight or four
 // behind them decides 2 - 3 % of a kernel's time, and any change further up shifts it.  So the place is fixed, for each kind of

@@ -31,6 +31,7 @@
 #include <atomic>
 
 #include "kernel_common.h"
+#include "roles_conv.h"
 
 namespace wg {
 namespace {
@@ -119,32 +120,35 @@ __device__ inline v2i join_pair(v4i wd, v4i wl) {
 
 struct WaveContext {
     const int8_t* act;   // this lane's 16 bytes of activation plane 0 (LDS)
-    const int8_t* flt;   // this lane's 16 bytes of filter fragment 0 of the current channel block
+    const int8_t* flt;   // this lane's 16 bytes of filter fragment 0 of the current channel block (channels not split)
 };
-
 
 constexpr int kRing = 10;   // filter fragments in flight per wave
 
+// Eight waves share what the compute unit takes in, some 57 bytes per clock, so a wave's 16 to 20 filter fragments per channel
+// block are requested well ahead: the first kRing before the products, the others each time a ring slot has been used.
 template <int HALF>
 struct Products {
     static constexpr int NS = half_slots(HALF), NF = half_fragments(HALF);
-    // Eight waves share what the compute unit takes in, some 57 bytes per clock, so a wave's 16 to 20 filter
-    // fragments per channel block are requested well ahead: the first kRing before the transform, the others each
-    // time a ring slot has been used.
-    v4i ring[kRing];
 
     template <int F>
     __device__ inline static v4i fragment(const WaveContext& cx) {
         constexpr int offset = frag_value(HALF, F) * kFilterFragBytes;   // evaluated by the compiler
         return *reinterpret_cast<const v4i*>(cx.flt + offset);
     }
+    // the same of a channel block given as a buffer, `lane16` = 16 x lane
+    template <int F>
+    __device__ inline static v4i fragment(__amdgpu_buffer_rsrc_t block, uint32_t lane16) {
+        constexpr int offset = frag_value(HALF, F) * kFilterFragBytes;
+        return buffer_fragment(block, lane16, offset);
+    }
     template <int PLANE>
     __device__ inline static v4i activation(const WaveContext& cx) {
         return *reinterpret_cast<const v4i*>(cx.act + PLANE * kPlaneBytes);
     }
-    // the first kRing fragments, one per call (I = 0 .. kRing - 1), pinned where the caller puts them
+    // the first fragments, one per call (I = 0 .. kRing - 1), pinned where the caller puts them
     template <int I>
-    __device__ inline void prefetch_one(const WaveContext& cx) {
+    __device__ inline static void prefetch_one(const WaveContext& cx, v4i (&ring)[kRing]) {
         __builtin_amdgcn_sched_barrier(0);
         ring[I] = fragment<I>(cx);
         __builtin_amdgcn_sched_barrier(0);
@@ -152,7 +156,9 @@ struct Products {
 
     // One 64-channel block: entry s multiplies while entry s+1's activation fragments come from LDS,
     // the ring is refilled, and entry s-1 is joined and (at the end of a row of M) reduced into Y.
-    __device__ inline void run(const WaveContext& cx, v2i (&Y)[16]) {
+    // refill(F): fragment F has been used.
+    template <class Refill>
+    __device__ inline static void run(const WaveContext& cx, v4i (&ring)[kRing], v2i (&Y)[16], Refill&& refill) {
         v4i afr[2][4], acc[2][6];
         v2i er[6], ei[6];
         constexpr int e0 = half_slot(HALF, 0).entry;
@@ -186,7 +192,7 @@ struct Products {
                     a[5] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w1, d[3], zero, 0, 0, 0);
                 }
                 static_for<entry_fragments(e)>([&](auto I) {
-                    if constexpr (f0 + I + kRing < NF) ring[(f0 + I) % kRing] = fragment<f0 + I + kRing>(cx);
+                    refill(std::integral_constant<int, f0 + I>{});
                 });
             }
             if constexpr (s > 0) {
@@ -453,11 +459,12 @@ struct RawPatch {
                 u[i / 6][i % 6] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xbuf, have ? pixel[i] : kOutsideOffset, cb * kCBlock, 0);
         }
     }
-    // Waits for what was requested; afterwards (`again`: this is not the first block) everyone is done reading the
-    // previous block's planes as well.
+    // Waits for what was requested, but not for the YOUNGER loads that were issued after it; afterwards (`again`: this is not
+    // the first block) everyone is done reading the previous block's planes as well.
+    template <int YOUNGER = 0>
     __device__ inline void take(bool again, int lane, uint32_t (&u)[6][6]) const {
         if constexpr (LOAD == kLoadPlanes) planes.put();   // nobody reads the previous block's raw patches any more: its planes were published since
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(YOUNGER) : "memory");
         if (LOAD != kLoadDwords || again) {
             // the raw pieces of a wave's tiles were moved by other waves
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -470,22 +477,46 @@ struct RawPatch {
     }
 };
 
-// grid (ceil(T/16), ceil(K/32), splits), 512 threads.
-// OUT kOutSums: the workgroup takes `blocks` channel blocks from blockIdx.z * blocks on and leaves the sum of its outputs,
-// before the rescale by 2^-4, at y as int32 [blockIdx.z][16 gridDim.x tiles][output 4i+j][Kp] (the output transform is
+// grid (ceil(T/16), ceil(K/32)), 512 threads; lossless_pair_sums_kernel (OUT kOutSums): see SplitGrid.
+// OUT kOutSums: the workgroup takes `blocks` channel blocks, those of split bz, and leaves the sum of its outputs,
+// before the rescale by 2^-4, at y as int32 [split][tile block][32 filters][tile][output 4i+j][filter] (the output transform is
 // linear, so these add up to the whole; sums_finish_kernel adds, rescales and stores).
 constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2;
+
+// Where a workgroup works.  Not split: the grid's own numbers, all channel blocks.  Split channels: a grid of ceil(T/16) x ceil(K/32) x
+// splits.  Every tile block reads all filters, so in lossless mode the splits are dealt out first and the tile blocks last, which
+// brings the workgroups that read the same fragments to the same XCD wherever splits x filter blocks is a multiple of eight: 512 -> 512 at 28x28,
+// N = 1, 18.0 -> 15.0 us, 592 -> 240 at 33x33 18.4 -> 15.3.  With more than ten of them side by side that is the slower order (256 -> 256 at
+// 56x56 14.9 -> 15.5, 576 -> 48 at 63x65 14.1 -> 14.7), as it is in scaled mode, whose filters are half as large (640 -> 128 at 48x48 19.4 -> 20.9).
+struct SplitPlace {
+    int tile_blocks, tile_block, filter_block, split, first, end;   // channel blocks first .. end - 1
+};
+struct SplitGrid {
+    dim3 grid;
+    uint32_t across, packed;   // tile blocks; 2 x channel blocks per split + 1: splits are dealt out first
+    inline SplitGrid(int tile_blocks, int filter_blocks, int splits, int blocks, bool splits_first)
+        : grid(splits_first ? dim3(splits, filter_blocks, tile_blocks) : dim3(tile_blocks, filter_blocks, splits)),
+          across((uint32_t)tile_blocks), packed((uint32_t)blocks << 1 | splits_first) {}
+};
+// as leading arguments (see WG_GEOMETRY_PARAMS: the first patch's place depends on all of them)
+#define WG_SPLIT_PARAMS uint32_t s_across, uint32_t s_packed
+#define WG_SPLIT(g) (g).across, (g).packed
+__device__ inline SplitPlace place_split(WG_SPLIT_PARAMS) {
+    const bool splits_first = s_packed & 1;
+    const int blocks = s_packed >> 1, split = splits_first ? blockIdx.x : blockIdx.z, tile_block = splits_first ? blockIdx.z : blockIdx.x;
+    return SplitPlace{(int)s_across, tile_block, (int)blockIdx.y, split, split * blocks, (split + 1) * blocks};
+}
+
 template <int LAYOUT, int LOAD, int OUT>
-__global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, const uint8_t* __restrict__ blob,
-                                                            size_t pairs_off, int32_t* __restrict__ y, Problem p,
-                                                            Int8Epilogue q8, int blocks) {
+__device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t pairs_off,
+                                              int32_t* __restrict__ y, const Problem& p, const Int8Epilogue& q8, const SplitPlace at) {
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
-    WG_TAKE_GEOMETRY(p, 2);
-    constexpr bool Q8 = OUT == kOutInt8;
-    const int cb_first = OUT == kOutSums ? (int)blockIdx.z * blocks : 0, cb_end = OUT == kOutSums ? min(cb_first + blocks, p.CB) : p.CB;
+    constexpr bool Q8 = OUT == kOutInt8, SPLIT = OUT == kOutSums;
+    const int bx = at.tile_block, by = at.filter_block, bz = at.split;
+    const int cb_first = at.first, cb_end = SPLIT ? min(at.end, p.CB) : p.CB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tile0 = blockIdx.x * kTileBlock;
-    const int k0 = blockIdx.y * kBlockFilters;
+    const int tile0 = bx * kTileBlock;
+    const int k0 = by * kBlockFilters;
     WG_STAMP(0);
 
     // ---- the raw patch of the first channel block: the longest wait of the kernel, requested first ----
@@ -506,39 +537,86 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     out.sink.base = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
     WaveContext cx;
     cx.act = lds + lds_slot(lane >> 4, lane & 15) * 16;
-    const int8_t* const flt0 = reinterpret_cast<const int8_t*>(blob + pairs_off) +
-                               filter_pair_offset(0, 0, k0 + kPairFilters * quad, 0, 0, p.Kp) + lane * 16;
+    const int8_t* const wave_flt = reinterpret_cast<const int8_t*>(blob + pairs_off) + filter_pair_offset(0, 0, k0 + kPairFilters * (SPLIT ? __builtin_amdgcn_readfirstlane(quad) : quad), 0, 0, p.Kp);
     const size_t flt_block = (size_t)(p.Kp >> 3) * kPairValues * kFilterFragBytes;
-    cx.flt = flt0 + cb_first * flt_block;
+    cx.flt = wave_flt + lane * 16;
 
     v2i Y[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) Y[i] = (v2i){0, 0};
 
-    Products<0> products0;
-    Products<1> products1;
     WG_STAMP(1);
-    for (int cb = cb_first; cb < cb_end; ++cb) {
-        // This wave's share of the raw patch (or its 36 pixels) has arrived.  The filter fragments are only requested
-        // now, so that at the start of the kernel, when every workgroup of the grid asks at once, the patches do not
-        // share the memory system with them; the transform gives the fragments time enough to arrive.
-        raw.take(cb > cb_first, lane, u);
-        WG_STAMP(2);
-        // the first kRing filter fragments are requested at ten places spread over the transform
-        static_assert(kRing == 10, "transform_rows calls its tick ten times");
-        if (half == 0) transform_rows<0>(u, out, [&](auto I) { products0.template prefetch_one<I>(cx); });
-        else           transform_rows<1>(u, out, [&](auto I) { products1.template prefetch_one<I>(cx); });
-        if (cb == cb_first && !blob_matches(header, p.K, p.Cf, WG_LOSSLESS)) return;   // uniform: nobody reaches the next barrier
-        // the operand planes are complete once every wave's LDS writes have landed (and every wave has read its
-        // raw patch); global requests stay in flight across the barrier
+    // the first kRing filter fragments of a block are requested at ten places spread over a transform
+    static_assert(kRing == 10, "transform_rows calls its tick ten times");
+    // the operand planes are complete once every wave's LDS writes have landed (and every wave has read its
+    // raw patch); global requests stay in flight across the barrier
+    auto published = [&] {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         WG_STAMP(3);
         __builtin_amdgcn_s_barrier();
         WG_STAMP(4);
-        if (cb + 1 < cb_end) raw.request(x, p, cb + 1, wave, lane, u);   // travels while this block's products run
-        if (half == 0) products0.run(cx, Y); else products1.run(cx, Y);
-        cx.flt += flt_block;
-        WG_STAMP(5);
+    };
+    if constexpr (SPLIT) {
+        // Several blocks of few tiles are bound by what fetches the filters (147 KB per block and workgroup, from memory in a network, where
+        // a compute unit takes in 10 - 16 bytes per clock): the next block's fragments are requested as this one's are used, behind its
+        // patch, and travel beside its transform (452 -> 160 at 20x20, N = 4, 20.2 -> 14.3 us with the order of the grid).  The first
+        // block's, too, before its patch is waited for: 512 -> 512 at 14x14, N = 1, 8.6 -> 9.3 us, other workgroups' patches then queue behind them.
+        // A loop per half (the same barriers in both), so that the ring keeps its registers from block to block: one loop for both
+        // copied it at the end of a block, which waits for what is in flight.
+        const uint32_t lane16 = 16u * (uint32_t)lane;
+        auto block_fragments = [&](int cb) {   // those of a block that is not this workgroup's arrive as zeros, without a trip to memory
+            return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(wave_flt + cb * flt_block), 0, cb < cb_end ? 0x7fffffff : 0, kRawBufferWord3);
+        };
+        auto blocks_of = [&](auto H) -> bool {
+            using Half = Products<H>;
+            v4i ring[kRing];
+            for (int cb = cb_first; cb < cb_end; ++cb) {
+                const __amdgpu_buffer_rsrc_t now = block_fragments(cb), next = block_fragments(cb + 1);
+                if (cb == cb_first) {
+                    raw.template take<0>(false, lane, u);
+                    WG_STAMP(2);
+                    transform_rows<H>(u, out, [&](auto I) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        ring[I] = Half::template fragment<I>(now, lane16);
+                        __builtin_amdgcn_sched_barrier(0);
+                    });
+                    if (!blob_matches(header, p.K, p.Cf, WG_LOSSLESS)) return false;   // uniform: nobody reaches the next barrier
+                } else {
+                    raw.template take<kRing>(true, lane, u);
+                    WG_STAMP(2);
+                    transform_rows<H>(u, out, [](auto) {});
+                }
+                published();
+                if (cb + 1 < cb_end) raw.request(x, p, cb + 1, wave, lane, u);   // travels while this block's products run
+                Half::run(cx, ring, Y, [&](auto F) {
+                    if constexpr (F + kRing < Half::NF) ring[F % kRing] = Half::template fragment<F + kRing>(now, lane16);
+                    else ring[F % kRing] = Half::template fragment<F % kRing>(next, lane16);
+                });
+                WG_STAMP(5);
+            }
+            return true;
+        };
+        if (!(half == 0 ? blocks_of(std::integral_constant<int, 0>{}) : blocks_of(std::integral_constant<int, 1>{}))) return;
+    } else {
+        using First = Products<0>;
+        using Second = Products<1>;
+        v4i ring0[kRing], ring1[kRing];
+        for (int cb = 0; cb < cb_end; ++cb) {
+            // This wave's share of the raw patch (or its 36 pixels) has arrived.  The filter fragments are only requested
+            // now, so that at the start of the kernel, when every workgroup of the grid asks at once, the patches do not
+            // share the memory system with them; the transform gives the fragments time enough to arrive.
+            raw.template take<0>(cb > 0, lane, u);
+            WG_STAMP(2);
+            if (half == 0) transform_rows<0>(u, out, [&](auto I) { First::template prefetch_one<I>(cx, ring0); });
+            else           transform_rows<1>(u, out, [&](auto I) { Second::template prefetch_one<I>(cx, ring1); });
+            if (cb == 0 && !blob_matches(header, p.K, p.Cf, WG_LOSSLESS)) return;   // uniform: nobody reaches the next barrier
+            published();
+            if (cb + 1 < cb_end) raw.request(x, p, cb + 1, wave, lane, u);   // travels while this block's products run
+            if (half == 0) First::run(cx, ring0, Y, [&](auto F) { if constexpr (F + kRing < First::NF) ring0[F % kRing] = First::template fragment<F + kRing>(cx); });
+            else           Second::run(cx, ring1, Y, [&](auto F) { if constexpr (F + kRing < Second::NF) ring1[F % kRing] = Second::template fragment<F + kRing>(cx); });
+            cx.flt += flt_block;
+            WG_STAMP(5);
+        }
     }
 
     // ---- stage both halves' partial outputs, add them, store whole lines ------------------------------
@@ -551,7 +629,12 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
 #pragma unroll
         for (int o = 0; o < 16; ++o) *reinterpret_cast<v2i*>(dst + o * kStageOut) = Y[o];
     }
-    __syncthreads();
+    if constexpr (SPLIT) {   // loads that nobody takes are still in flight
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+    } else {
+        __syncthreads();
+    }
     WG_STAMP(6);
     auto sixteen = [&](int o, int tile, int k4) {   // 16 x the finished outputs of filters k0 + 4 k4 .. + 3 at output o of a tile
         const int at = o * kStageOut + tile * kStageRow + 4 * k4;
@@ -624,9 +707,9 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     const int row = 4 * ty, col = 4 * tx + j;
     const bool live = t < p.T && col < p.W && kk < p.K;
     if constexpr (OUT == kOutSums) {
-        v4i* const to = reinterpret_cast<v4i*>(y) + ((((size_t)blockIdx.z * gridDim.x * kTileBlock + t) * 16 + j) * p.Kp + kk) / 4;
+        v4i* const to = reinterpret_cast<v4i*>(y + split_sums_offset(16, bz, bx, by, at.tile_blocks, p.Kp)) + (16 * tile + j) * (kBlockFilters / 4) + k4;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) to[(size_t)r * p.Kp] = sixteen(4 * r + j, tile, k4);
+        for (int r = 0; r < 4; ++r) to[4 * r * (kBlockFilters / 4)] = sixteen(4 * r + j, tile, k4);
         return;
     }
     if constexpr (!Q8) {
@@ -678,6 +761,20 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
         }
     }
     WG_STAMP(7);
+}
+
+template <int LAYOUT, int LOAD, int OUT>
+__global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, const uint8_t* __restrict__ blob,
+                                                            size_t pairs_off, int32_t* __restrict__ y, Problem p, Int8Epilogue q8) {
+    WG_TAKE_GEOMETRY(p, 2);
+    lossless_pair<LAYOUT, LOAD, OUT>(x, blob, pairs_off, y, p, q8, SplitPlace{0, (int)blockIdx.x, (int)blockIdx.y, 0, 0, 0});
+}
+template <int LOAD>
+__global__ __launch_bounds__(512) void lossless_pair_sums_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_SPLIT_PARAMS,
+                                                                 const uint8_t* __restrict__ blob, size_t pairs_off, int32_t* __restrict__ sums, Problem p) {
+    WG_TAKE_GEOMETRY(p, 2);
+    lossless_pair<WG_NHWC, LOAD, kOutSums>(x, blob, pairs_off, sums, p, Int8Epilogue{nullptr, 0, 0, 0, 0},
+                                           place_split(s_across, s_packed));
 }
 
 // ---- scaled mode, split channels ---------------------------------------------------------------------
@@ -754,7 +851,7 @@ struct QuarterProducts {
         });
     }
     // lane = tile (lane & 15) x four filters: one 16-byte store per sum
-    __device__ inline void store(v4i* to, size_t plane) const {
+    __device__ inline void store(v4i* to, int plane) const {
         static_for<NS>([&](auto S) {
             constexpr int e = quarter_entry(Q, S), a = quarter_acc(Q, S);
             if constexpr (real_entry(e)) {
@@ -768,15 +865,16 @@ struct QuarterProducts {
     }
 };
 
-// grid (ceil(T/16), ceil(K/32), splits), 512 threads; sums: int32 [split][36][16 gridDim.x tiles][Kp].
+// grid: see SplitGrid, 512 threads; sums: int32 [split][tile block][32 filters][36][tile][filter].
 template <int LOAD>
-__global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, const uint8_t* __restrict__ blob, size_t planes_off,
-                                                          int32_t* __restrict__ sums, Problem p, int blocks) {
+__global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_SPLIT_PARAMS, const uint8_t* __restrict__ blob, size_t planes_off,
+                                                          int32_t* __restrict__ sums, Problem p) {
     WG_TAKE_GEOMETRY(p, 2);
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tile0 = blockIdx.x * kTileBlock, k0 = blockIdx.y * kBlockFilters;
-    const int cb_first = (int)blockIdx.z * blocks, cb_end = min(cb_first + blocks, p.CB);
+    const SplitPlace at = place_split(s_across, s_packed);
+    const int tile0 = at.tile_block * kTileBlock, k0 = at.filter_block * kBlockFilters;
+    const int cb_first = at.first, cb_end = min(at.end, p.CB);
     const int quad = wave & 3, half = wave >> 2;   // of the transform
     const int a_tile = 4 * quad + (lane >> 4), a_cq = lane & 15;
     RawPatch<LOAD> raw;
@@ -799,9 +897,9 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
         QuarterProducts<Q> products;
         products.clear();
         for (int cb = cb_first; cb < cb_end; ++cb) {
-            raw.take(cb > cb_first, lane, u);
+            raw.template take<0>(cb > cb_first, lane, u);
             auto tick = [&](auto I) { products.template prefetch_one<I>(flt); };
-            if (half == 0) transform_rows<0>(u, out, tick); else transform_rows<1>(u, out, tick);
+            transform_rows<(Q < 2 ? 0 : 1)>(u, out, tick);
             if (cb == cb_first && !blob_matches(header, p.K, p.Cf, WG_SCALED)) return;   // uniform: nobody reaches the next barrier
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
@@ -809,9 +907,9 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
             products.run(act);
             flt += flt_block;
         }
-        const size_t tiles = (size_t)gridDim.x * kTileBlock, plane = tiles * p.Kp / 4;   // in units of four sums
-        products.store(reinterpret_cast<v4i*>(sums) + (size_t)blockIdx.z * kAccPlanes * plane +
-                           ((size_t)(tile0 + (lane & 15)) * p.Kp + kgroup + 4 * (lane >> 4)) / 4, plane);
+        constexpr int plane = kTileBlock * kBlockFilters / 4;   // in units of four sums
+        products.store(reinterpret_cast<v4i*>(sums + split_sums_offset(kAccPlanes, at.split, at.tile_block, at.filter_block, at.tile_blocks, p.Kp)) +
+                           (lane & 15) * (kBlockFilters / 4) + 4 * (wave & 1) + (lane >> 4), plane);
     };
     switch (wave >> 1) {
         case 0: blocks_of(std::integral_constant<int, 0>{}); break;
@@ -821,15 +919,18 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
     }
 }
 
+// (of the padding to 64 filters, a block of 32 that do not exist has nothing to do: no sums of theirs are looked at)
 template <int LAYOUT, int LOAD, int OUT>
-hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p,
-                  const Int8Epilogue& q8, hipStream_t s, int blocks = 0, int splits = 1) {
+hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p, const Int8Epilogue& q8, hipStream_t s) {
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LAYOUT, LOAD, OUT>), kLdsBytes)) return e;
-    // (of the padding to 64 filters, a block of 32 that do not exist has nothing to do: no sums of theirs are looked at)
-    dim3 grid(ceil_div(p.T, kTileBlock), ceil_div(p.K, kBlockFilters), splits);
-    lossless_pair_kernel<LAYOUT, LOAD, OUT><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, WG_GEOMETRY(p), blob, bl.pairs_off, y, p, q8, blocks);
+    dim3 grid(ceil_div(p.T, kTileBlock), ceil_div(p.K, kBlockFilters));
+    lossless_pair_kernel<LAYOUT, LOAD, OUT><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, WG_GEOMETRY(p), blob, bl.pairs_off, y, p, q8);
     return hipGetLastError();
+}
+inline SplitGrid split_grid(const Problem& p, int blocks, int splits, int mode) {
+    const int tile_blocks = ceil_div(p.T, kTileBlock);
+    return SplitGrid(tile_blocks, ceil_div(p.K, kBlockFilters), splits, blocks, mode == WG_LOSSLESS && tile_blocks <= 10);
 }
 
 // How the patches of a tensor are read (see kLoadDwords ..).
@@ -879,8 +980,14 @@ hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t*
 hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits,
                                      hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
-    const uint8_t* b = static_cast<const uint8_t*>(blob);
-    auto go = [&](auto LOAD) { return launch<WG_NHWC, LOAD, kOutSums>(x, b, bl, sums, p, no_int8_epilogue(), s, blocks, splits); };
+    const SplitGrid grid = split_grid(p, blocks, splits, WG_LOSSLESS);
+    auto go = [&](auto LOAD) -> hipError_t {
+        static LdsLimitOnce lds_limit;   // per LOAD
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_sums_kernel<LOAD>), kLdsBytes)) return e;
+        lossless_pair_sums_kernel<LOAD><<<grid.grid, 64 * kWaves, kLdsBytes, s>>>(x, WG_GEOMETRY(p), WG_SPLIT(grid), static_cast<const uint8_t*>(blob),
+                                                                                     bl.pairs_off, sums, p);
+        return hipGetLastError();
+    };
     using std::integral_constant;
     switch (load_of(x, p, layout)) {
         case kLoadPlanes: return go(integral_constant<int, kLoadPlanes>{});
@@ -891,13 +998,13 @@ hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t*
 
 hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits, hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
-    const dim3 grid(ceil_div(p.T, kTileBlock), ceil_div(p.K, kBlockFilters), splits);
+    const SplitGrid grid = split_grid(p, blocks, splits, WG_SCALED);
     auto go = [&](auto LOAD) -> hipError_t {
         static LdsLimitOnce lds_limit;   // per LOAD
         constexpr int lds_bytes = kPlanesBytes + 4 * kRawQuad;
         if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&scaled_sums_kernel<LOAD>), lds_bytes)) return e;
-        scaled_sums_kernel<LOAD><<<grid, 64 * kWaves, lds_bytes, s>>>(x, WG_GEOMETRY(p), static_cast<const uint8_t*>(blob), bl.planes_off, sums, p,
-                                                                           blocks);
+        scaled_sums_kernel<LOAD><<<grid.grid, 64 * kWaves, lds_bytes, s>>>(x, WG_GEOMETRY(p), WG_SPLIT(grid), static_cast<const uint8_t*>(blob),
+                                                                              bl.planes_off, sums, p);
         return hipGetLastError();
     };
     using std::integral_constant;

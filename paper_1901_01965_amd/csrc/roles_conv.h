@@ -26,6 +26,11 @@ inline hipError_t launch_roles(const RolesCall& c, int mode, bool wide, hipStrea
 // launch_lossless_pair_sums left.
 hipError_t launch_split_finish(const RolesCall& c, const int32_t* partial, int splits, hipStream_t s);
 hipError_t launch_sums_finish(const RolesCall& c, const int32_t* sums, int splits, hipStream_t s);
+// A workgroup's sums lie together (what one XCD writes would otherwise fall into a few of its L2's channels: rows of Kp filters,
+// 592 -> 240 at 33x33, N = 1, scaled: 16.5 us): `values` numbers of 16 tiles x 32 filters from here on.
+__host__ __device__ inline size_t split_sums_offset(int values, int split, int tile_block, int filter_block, int tile_blocks, int Kp) {
+    return (((size_t)split * tile_blocks + tile_block) * (Kp >> 5) + filter_block) * (size_t)(values * 16 * 32);
+}
 inline size_t split_partial_bytes(const Problem& p, int mode, int splits) {
     return (size_t)splits * (mode == WG_LOSSLESS ? 16 : kAccPlanes) * 16 * ceil_div(p.T, 16) * p.Kp * sizeof(int32_t);
 }

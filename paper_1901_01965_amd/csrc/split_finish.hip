@@ -25,8 +25,9 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const int32_t* __rest
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int k = blockIdx.y * kItems + lane, t = blockIdx.x;
     if (t >= p.T) return;
-    const size_t plane = (size_t)((p.T + 15) / 16 * 16) * p.Kp;   // sums are there for whole blocks of 16 tiles
-    const int32_t* const mine = partial + (size_t)t * p.Kp + k;
+    const int tile_blocks = (p.T + 15) / 16;
+    const size_t split = split_sums_offset(kAccPlanes, 1, 0, 0, tile_blocks, p.Kp);
+    const int32_t* const mine = partial + split_sums_offset(kAccPlanes, 0, t >> 4, k >> 5, tile_blocks, p.Kp) + (t & 15) * 32 + (k & 31);
     const BlobHeaderWords header = read_blob_header(blob);
     // the first wave finishes: it asks for its filter's factors (r, q) along with its sums
     int2 rq[kEntries];
@@ -44,7 +45,7 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const int32_t* __rest
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int e = 0; e < kAccPlanes; ++e) v[i][e] = mine[((size_t)(second ? s + 4 * i : s) * kAccPlanes + e) * plane];
+            for (int e = 0; e < kAccPlanes; ++e) v[i][e] = mine[(second ? s + 4 * i : s) * split + e * (16 * 32)];
 #pragma unroll
         for (int e = 0; e < kAccPlanes; ++e) m[e] += v[0][e] + (second ? v[1][e] : 0);
     }
@@ -115,9 +116,11 @@ __global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restr
     if (t >= p.T || item >= (pool ? 4 : 16) * k4s) return;
     const BlobHeaderWords header = read_blob_header(blob);
     const int o = item / k4s, kk = 4 * (item - o * k4s);
-    const size_t split = (size_t)((p.T + 15) / 16 * 16) * 4 * p.Kp;   // v4i per split: whole blocks of 16 tiles
+    const int tile_blocks = (p.T + 15) / 16;
+    const size_t split = split_sums_offset(16, 1, 0, 0, tile_blocks, p.Kp) / 4;   // v4i per split
+    const int32_t* const mine = sums + split_sums_offset(16, 0, t >> 4, kk >> 5, tile_blocks, p.Kp) + (t & 15) * (16 * 32) + (kk & 31);
     auto total = [&](int out) {   // finished outputs of filters kk .. kk + 3 at output `out`
-        const v4i* from = reinterpret_cast<const v4i*>(sums) + (((size_t)t * 16 + out) * p.Kp + kk) / 4;
+        const v4i* from = reinterpret_cast<const v4i*>(mine + out * 32);
         v4i v = {0, 0, 0, 0};
         for (int s = 0; s < splits; s += 4) {
             v4i part[4];

@@ -297,8 +297,8 @@ bool plane_patches_hold(const Problem& p);   // channel-major activations of p c
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout);
 void set_lossless_variant(int v);
 int lossless_variant();
-// The same form with the channel blocks dealt to `splits` workgroups each: leaves 16 x outputs as int32
-// [splits][16 ceil(T/16)][16][Kp], which launch_sums_finish adds and stores.
+// The same form with the channel blocks dealt to `splits` workgroups each: leaves 16 x outputs as int32, 16 per tile and filter
+// (split_sums_offset), which launch_sums_finish adds and stores.
 hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits,
                                      hipStream_t s);
 // Test hook (both modes): 0 the library's choice, 1 the role-specialised kernel with eight product waves (64 filters
@@ -306,7 +306,7 @@ hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t*
 void set_scaled_variant(int v);
 // The same for the streaming kernel's form with eight product waves (0, 1: wherever the layer streams, 2: never).
 void set_stream_variant(int v);
-// Scaled mode, likewise: leaves the Winograd-domain channel sums as int32 [splits][36][16 ceil(T/16)][Kp] for launch_split_finish.
+// Scaled mode, likewise: leaves the Winograd-domain channel sums as int32, 36 per tile and filter, for launch_split_finish.
 hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits, hipStream_t s);
 // Single-kernel path with the activations scaled per tile as well (WG_SCALED blob of signed int8 filters).
 // act_table: null, or int32 [T][26][4] that receives every tile's (n, p, r, q).

@@ -147,3 +147,15 @@ def test_calls_run_without_the_memory_they_would_like_and_outputs_without_memory
         torch.cuda.set_per_process_memory_fraction(1.0)
     for out, want in zip(outs, wanted):
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("mode", [wg.LOSSLESS, wg.SCALED])
+@pytest.mark.parametrize("shape", [(1, 320, 192, 40, 64), (1, 320, 160, 44, 64), (1, 260, 250, 52, 56), (1, 600, 20, 49, 66)])
+def test_split_channels_in_either_order_of_the_grid(shape, mode):
+    """Ten, eleven and more tile blocks (up to ten, lossless mode deals out the splits first, above that the tile blocks), two
+    channel blocks per workgroup with one in the last split, odd numbers of 32-filter blocks, C no multiple of 16 (4-byte loads)."""
+    x, g, xd, gd = _inputs(shape, wg.NHWC)
+    want = oracle.direct_conv2d(x, g) if mode == wg.LOSSLESS else oracle.winograd_conv2d(x, g, oracle.SCALED, 127)[0]
+    packed = wg.winograd_filter_transform(gd, wg.NHWC, mode)
+    for _ in range(2):
+        assert np.array_equal(_nchw(wg.winograd_conv2d_int8(xd, packed, wg.NHWC), wg.NHWC), want)
