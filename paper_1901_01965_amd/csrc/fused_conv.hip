@@ -480,18 +480,29 @@ struct Plan {
 // Deep layers with few tiles leave most of the chip idle while a workgroup walks through its channel blocks one after the
 // other.  Dealing the blocks to several workgroups takes a second kernel that adds the splits and finishes.  CB channel blocks in
 // one workgroup against b in each of W, whose partial sums are written and read (36 per tile and filter in scaled mode, 16
-// otherwise).  Fitted to 330 layers of 128 .. 896 channels and K = 32 .. 512 filters that fill at most half the chip, with filters
-// that are not in the L2, as in a network (us; nine in ten are off by 8 % at most, the choice is 0.2 % from the better one on
-// average, with filters in the L2 as well):
-//   lossless: 5.7 + 2.68 CB in one kernel, 4.8 + 3.27 b + W / 50 + CB K / 2700 split (N = 1, 512 -> 512 at 14x14: 26 - 36, 11.1 - 12.8)
+// otherwise).  Fitted to layers of 128 .. 896 channels and K = 16 .. 512 filters that fill at most half the chip, with filters
+// that are not in the L2, as in a network (us; 330 layers in scaled mode, 220 in lossless mode, off by 3 - 8 % on average):
+//   lossless: 3.9 + 3.3 b + W / 48 split; one kernel, which is the limb-pair form with 16 filters per workgroup there (lossless_conv.hip),
+//             2.1 + 2.6 CB + W16 / 120 for W16 workgroups with 16-byte pieces, 1.6 + 3.3 CB with 4-byte loads, both + CB min(K, 256) / 1500 for the
+//             filters that come from memory (128 -> 64 at 28x28, N = 16: split 10.95, 9.0; 256 -> 32 at 20x20, N = 16: 9.6, 12.6; near
+//             the line, 256 -> 256 at 56x56, N = 1, the split that it chooses takes 15.5, one kernel 14.6);
+//             on channel-major tensors 4.0 + 4.4 b + W / 53 + 6.4 per million outputs split and 2.5 + 3.9 CB + W16 / 120 (112 -> 448 at 58x29,
+//             N = 1: 18.5, 12.7), with a copy, where there are more than two blocks, 8.7 + 2.68 CB;
+//             4.8 + 3.27 b + W / 50 + CB K / 2700 and 5.7 + 2.68 CB, both with a copy
 //   scaled:   5.9 + 1.65 CB in one kernel, 9.1 + 1.92 b + W / 28 split (18 - 24, 16.7 - 17.6; N = 4: 18.4, 21.4)
-// and 3.9 b - 2.2 more where the split kernels cannot read 16-byte pieces (N = 2, 324 -> 512 at 28x28, lossless: 21.6, 32.8).  One
-// kernel takes 0.6 less with up to 32 filters (250 drawn layers; 272 -> 16 at 17x17, N = 10, scaled: 13.3, 14.1; 116 -> 16 at 64x7,
-// N = 15, lossless: 10.4, 11.2), unless it needs a copy that the split kernels do without (`planes`; 480 -> 32 at 81x81, N = 1, scaled:
-// 25.7, 21.2).
-bool split_pays(int mode, int CB, int K, int Kp, int b, int W, bool pieces, bool planes) {
-    const double one = (mode == WG_LOSSLESS ? 5.7 + 2.68 * CB : 5.9 + 1.65 * CB) - (K <= kFusedFilters && !planes ? 0.6 : 0.0);
-    const double split = mode == WG_LOSSLESS ? 4.8 + 3.27 * b + W / 50.0 + CB * Kp / 2700.0 : 9.1 + 1.92 * b + W / 28.0;
+// and 3.9 b - 2.2 more where the split kernels cannot read 16-byte pieces (N = 2, 324 -> 512 at 28x28, lossless: 21.6, 32.8).  The
+// kernels that transform on waves of their own take 0.6 less with up to 32 filters (250 drawn layers; 272 -> 16 at 17x17, N = 10, scaled: 13.3, 14.1;
+// 116 -> 16 at 64x7, N = 15, lossless: 10.4, 11.2), unless it needs a copy that the split kernels do without (`planes`; 480 -> 32 at
+// 81x81, N = 1, scaled: 25.7, 21.2).
+// pairs: one kernel would be the limb-pair form.
+bool split_pays(int mode, const Problem& p, int b, int W, bool pieces, bool planes, bool pairs) {
+    const double w16 = (double)ceil_div(p.T, kFusedTiles) * ceil_div(p.K, 16), outputs = (double)p.N * p.H * p.W * p.K / 1e6;
+    double one = (mode == WG_LOSSLESS ? (planes ? 8.7 : 5.7) + 2.68 * p.CB : 5.9 + 1.65 * p.CB) - (p.K <= kFusedFilters && !planes ? 0.6 : 0.0);
+    if (pairs) one = (planes ? 2.5 + 3.9 * p.CB : pieces ? 2.1 + 2.6 * p.CB : 1.6 + 3.3 * p.CB) + w16 / 120.0 + (planes ? 0.0 : p.CB * std::min(p.Kp, 256) / 1500.0);
+    const double split = mode != WG_LOSSLESS ? 9.1 + 1.92 * b + W / 28.0
+                       : planes              ? 4.0 + 4.4 * b + W / 53.0 + 6.4 * outputs
+                       : pairs               ? 3.9 + 3.3 * b + W / 48.0
+                                             : 4.8 + 3.27 * b + W / 50.0 + p.CB * p.Kp / 2700.0;
     return one > split + (pieces ? 0.0 : 3.9 * b - 2.2);
 }
 
@@ -512,15 +523,15 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
     const int workgroups = ceil_div(p.T, kFusedTiles) * ceil_div(p.K, kFusedFilters);
     const bool may_split = p.CB >= 2 && 2 * workgroups <= compute_units() && !is_unsigned && !hooked;
     const int blocks = may_split ? ceil_div(p.CB, std::min(p.CB, compute_units() / workgroups)) : p.CB, splits = ceil_div(p.CB, blocks);
-    auto split = [&](bool pieces, bool planes) {
-        if (!may_split || !split_pays(mode, p.CB, p.K, p.Kp, blocks, splits * workgroups, pieces, planes) || split_partial_bytes(p, mode, splits) > left) return false;
+    auto split = [&](bool pieces, bool planes, bool pairs) {
+        if (!may_split || !split_pays(mode, p, blocks, splits * workgroups, pieces, planes, pairs) || split_partial_bytes(p, mode, splits) > left) return false;
         plan.splits = splits;
         plan.blocks = blocks;
         return true;
     };
     if (layout == WG_NCHW && !is_unsigned && plane_patches_hold(p)) {
         // the split kernels read channel-major patches as well, at 1.1 us more per further block, while a copy is a launch
-        plan.planes = (blocks <= 2 && split(true, true)) || (mode == WG_LOSSLESS && (lossless_variant() == 1 || (!hooked && pair_reads_planes(p))));
+        plan.planes = (blocks <= 2 && split(true, true, mode == WG_LOSSLESS && pair_reads_planes(p))) || (mode == WG_LOSSLESS && (lossless_variant() == 1 || (!hooked && pair_reads_planes(p))));
         if (plan.planes) return plan;
     }
     if (layout != WG_NHWC || p.C % 4 != 0) {
@@ -529,7 +540,8 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
         if (!plan.copies) return plan;
         left -= channels_last_bytes(p);
     }
-    split(plan.copies ? padded_channels(p.C) % 16 == 0 : p.C % 16 == 0, false);   // (a caller's view may still start off a boundary)
+    const bool pieces = plan.copies ? padded_channels(p.C) % 16 == 0 : p.C % 16 == 0;
+    split(pieces, false, mode == WG_LOSSLESS && layout == WG_NHWC && lossless_pair_takes(p, pieces));   // (a caller's view may still start off a boundary)
     return plan;
 }
 
@@ -623,10 +635,11 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
                          tile_blocks >= 6 * stream_workgroups(tile_blocks, filter_blocks);
     // Lossless mode, channels-last, one channel block, at most one round of 32-filter workgroups (layers with more are streamed): the
     // limb-pair form (eight waves per 16 tiles x 32 filters, lossless_conv.hip), 6.9 us a round on 56x56x64 layers, against
-    // 7.4 for the four-wave form of this file.
+    // 7.4 for the four-wave form of this file.  Several channel blocks: see lossless_pair_takes.
     if (pair_layer && !streams) {
         const int form = lossless_pair_conv_choice(c.x, p, c.layout);   // 0: not applicable or switched off, 1: the library decides, 2: forced
-        if (form == 2 || (form == 1 && p.CB == 1 && w32 <= cus)) {
+        const bool others_asked_for = variant != 0 || stream_variant != 0;
+        if (form == 2 || (form == 1 && (p.CB == 1 ? w32 <= cus : !others_asked_for && lossless_pair_takes(p, p.C % 16 == 0 && reinterpret_cast<uintptr_t>(c.x) % 16 == 0)))) {
             status = launch_lossless_pair_conv(c.x, c.blob, c.y, p, c.layout, c.q8, s);
             return true;
         }

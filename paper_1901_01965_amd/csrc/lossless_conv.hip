@@ -28,6 +28,8 @@
 //   partial-line stores from the lanes' own two filters measured twice as slow.
 // Several channel blocks: the output transform is linear, so every block's rows of M are reduced
 // into the same 16 outputs.
+// Small grids (in_quarters): 16 filters per workgroup, a wave = filter group of 8 x a quarter of the entries, 28 matrix-core
+// instructions on average instead of 56.
 #include <atomic>
 
 #include "kernel_common.h"
@@ -59,28 +61,42 @@ constexpr int kRawQuad = 36 * kRawPixel + 16;           // 9 KB: nine 1 KB trans
 // output staging (after the products): stage[half][output o][tile][32 filters], tile rows 36 dwords apart and
 // outputs 16*36 + 32 dwords apart, so that the 16-byte reads of a 16-lane group (two outputs x eight filter
 // quads) fall into different banks
-constexpr int kStageRow = 36, kStageOut = 16 * kStageRow + 32, kStageHalf = 16 * kStageOut;   // dwords
+// PARTS = 4 (16 filters per workgroup, four quarters of the entries): rows 20 dwords apart, outputs 336: a 16-lane group reads four
+// outputs x four filter quads, and the writers' rows begin at every fourth bank.
+template <int PARTS>
+struct Stage {
+    static constexpr int kFilters = 8 * kPairFilters / PARTS;   // per workgroup
+    static constexpr int kRow = PARTS == 2 ? 36 : 20, kOut = 16 * kRow + (PARTS == 2 ? 32 : 16), kPart = 16 * kOut;   // dwords
+    static constexpr int kBytes = PARTS * kPart * 4;
+};
 // LDS: [operand planes 72 KB][raw patches 36 KB, later the first part of the staged outputs][rest of the staged outputs]:
 // the outputs are staged outside the operand planes, so a wave can stage its outputs while others still multiply
-constexpr int kStageBytes = 2 * kStageHalf * 4;
-static_assert(kStageBytes >= 4 * kRawQuad, "the staged outputs start in the raw patches' area");
-constexpr int kLdsBytes = kPlanesBytes + kStageBytes;
-static_assert(kLdsBytes <= 160 * 1024, "LDS of one compute unit");
+template <int PARTS>
+constexpr int pair_lds_bytes() {
+    static_assert(Stage<PARTS>::kBytes >= 4 * kRawQuad, "the staged outputs start in the raw patches' area");
+    static_assert(kPlanesBytes + Stage<PARTS>::kBytes <= 160 * 1024, "LDS of one compute unit");
+    return kPlanesBytes + Stage<PARTS>::kBytes;
+}
 constexpr int kLoadDwords = 1, kLoadDirect = 2;         // 4-byte loads into registers / 16-byte pieces straight into LDS
 constexpr int kLoadPlanes = 3;                          // channel-major activations: rows of a patch, turned on the way into LDS
 
 // ---- which entries a wave multiplies, in order -------------------------------------------------
+// A wave owns half or a quarter of the entries ("share").
 // Half 0: rows 0, 1, 2 of M (five entries each: four real, then the complex M[row][3]) and M[3][0];
 // half 1: M[3][1], M[3][2], M[3][5], M[3][3], M[3][4] and row 5.  56 matrix-core instructions each.
+// Quarters (shares 2 .. 5): rows 0 and 1; row 2 and row 5; M[3][0], M[3][1], M[3][2]; M[3][5], M[3][3], M[3][4].  32, 32, 24 and 24 instructions.
 // Entry numbering as in the blob: real entries 0..15 (4 RI + CI over rows/columns 0,1,2,5), complex
 // 16..19 = M[RI][3], 20..23 = M[3][CI], 24 = M[3][3], 25 = M[3][4].
 struct Slot {
     int entry, row, pos;   // row 0..3: real rows 0,1,2,5; row 4: the complex row 3; pos: place in finish_row's arrays
     bool ends;             // last entry of its row in this half
 };
-constexpr int half_slots(int half) { return half == 0 ? 16 : 10; }
+constexpr int kFirstQuarter = 2;
+constexpr int half_slots(int half) { return half == 0 ? 16 : half < 4 ? 10 : 3; }
 constexpr Slot half_slot(int half, int s) {
-    if (half == 0) {
+    if (half == 3) return s < 5 ? Slot{s < 4 ? 8 + s : 18, 2, s, s == 4} : Slot{s < 9 ? 7 + s : 19, 3, s - 5, s == 9};
+    if (half >= 4) return Slot{20 + 3 * (half - 4) + s, 4, 3 * (half - 4) + s, s == 2};
+    if (half == 0 || half == 2) {
         if (s < 15) return Slot{s % 5 < 4 ? 4 * (s / 5) + s % 5 : 16 + s / 5, s / 5, s % 5, s % 5 == 4};
         return Slot{20, 4, 0, true};
     }
@@ -99,6 +115,7 @@ constexpr int frag_start(int half, int s) {   // index of slot s's first fragmen
 }
 constexpr int half_fragments(int half) { return frag_start(half, half_slots(half)); }
 static_assert(half_fragments(0) + half_fragments(1) == kPairValues, "one fragment per Winograd-domain value");
+static_assert(half_fragments(2) + half_fragments(3) + half_fragments(4) + half_fragments(5) == kPairValues, "the same in quarters");
 constexpr int frag_value(int half, int f) {   // blob value index of fragment f of the stream
     int s = 0;
     while (frag_start(half, s + 1) <= f) ++s;
@@ -129,7 +146,7 @@ constexpr int kRing = 10;   // filter fragments in flight per wave
 // block are requested well ahead: the first kRing before the products, the others each time a ring slot has been used.
 template <int HALF>
 struct Products {
-    static constexpr int NS = half_slots(HALF), NF = half_fragments(HALF);
+    static constexpr int NS = half_slots(HALF), NF = half_fragments(HALF);   // HALF: a share
 
     template <int F>
     __device__ inline static v4i fragment(const WaveContext& cx) {
@@ -218,6 +235,10 @@ struct Products {
                     if constexpr (HALF == 1 && sl.row == 4 && sl.pos == 1) {   // M[3][0] belongs to the other half
                         er[0] = (v2i){0, 0};
                         ei[0] = (v2i){0, 0};
+                    }
+                    if constexpr (HALF >= 4 && s == 1) {   // and half of the row to the other quarter
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) er[HALF == 4 ? 3 + e : e] = ei[HALF == 4 ? 3 + e : e] = (v2i){0, 0};
                     }
                     if constexpr (sl.ends) finish_row<sl.row, false>(er, ei, Y);
                 }
@@ -477,7 +498,8 @@ struct RawPatch {
     }
 };
 
-// grid (ceil(T/16), ceil(K/32)), 512 threads; lossless_pair_sums_kernel (OUT kOutSums): see SplitGrid.
+// grid (ceil(T/16), ceil(K/32)), 512 threads; PARTS = 4: ceil(K/16), for grids that leave half of the compute units idle: products
+// and store take half as long there, see in_quarters.  lossless_pair_sums_kernel (OUT kOutSums): see SplitGrid.
 // OUT kOutSums: the workgroup takes `blocks` channel blocks, those of split bz, and leaves the sum of its outputs,
 // before the rescale by 2^-4, at y as int32 [split][tile block][32 filters][tile][output 4i+j][filter] (the output transform is
 // linear, so these add up to the whole; sums_finish_kernel adds, rescales and stores).
@@ -507,21 +529,32 @@ __device__ inline SplitPlace place_split(WG_SPLIT_PARAMS) {
     return SplitPlace{(int)s_across, tile_block, (int)blockIdx.y, split, split * blocks, (split + 1) * blocks};
 }
 
-template <int LAYOUT, int LOAD, int OUT>
+template <int LAYOUT, int LOAD, int OUT, int PARTS>
 __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t pairs_off,
                                               int32_t* __restrict__ y, const Problem& p, const Int8Epilogue& q8, const SplitPlace at) {
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
-    constexpr bool Q8 = OUT == kOutInt8, SPLIT = OUT == kOutSums;
+    constexpr bool Q8 = OUT == kOutInt8, SPLIT = OUT == kOutSums, STREAMS = SPLIT || PARTS == 4;   // the next block's filters travel early
     const int bx = at.tile_block, by = at.filter_block, bz = at.split;
     const int cb_first = at.first, cb_end = SPLIT ? min(at.end, p.CB) : p.CB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tile0 = bx * kTileBlock;
-    const int k0 = by * kBlockFilters;
+    const int k0 = by * Stage<PARTS>::kFilters;
     WG_STAMP(0);
 
     // ---- the raw patch of the first channel block: the longest wait of the kernel, requested first ----
     // Transform thread: tile 4 (wave % 4) + lane / 16, channels 4 (lane % 16) .. + 3, rows by wave / 4.
-    const int quad = wave & 3, half = wave >> 2;   // the same split serves the product phase: filters 8 quad .. + 7, half of the entries
+    const int quad = wave & 3, half = wave >> 2;
+    // Product phase: filters 8 group .. + 7, share `part` of the entries (halves: the same split again).
+    const int group = PARTS == 2 ? quad : wave & 1, part = PARTS == 2 ? half : wave >> 1;
+    constexpr int kFirstShare = PARTS == 2 ? 0 : kFirstQuarter;
+    auto by_share = [&](auto&& f) {   // f(share of the entries, rows this wave transforms)
+        using std::integral_constant;
+        if constexpr (PARTS == 2) return half == 0 ? f(integral_constant<int, 0>{}, integral_constant<int, 0>{}) : f(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+        else return part < 2 ? (part == 0 ? f(integral_constant<int, kFirstShare>{}, integral_constant<int, 0>{})
+                                          : f(integral_constant<int, kFirstShare + 1>{}, integral_constant<int, 0>{}))
+                             : (part == 2 ? f(integral_constant<int, kFirstShare + 2>{}, integral_constant<int, 1>{})
+                                          : f(integral_constant<int, kFirstShare + 3>{}, integral_constant<int, 1>{}));
+    };
     const int a_tile = 4 * quad + (lane >> 4), a_cq = lane & 15;
     RawPatch<LOAD> raw;
     raw.init(p, lds, tile0, quad, half, lane);
@@ -537,7 +570,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
     out.sink.base = lds + lds_slot(a_cq >> 2, a_tile) * 16 + (a_cq & 3) * 4;
     WaveContext cx;
     cx.act = lds + lds_slot(lane >> 4, lane & 15) * 16;
-    const int8_t* const wave_flt = reinterpret_cast<const int8_t*>(blob + pairs_off) + filter_pair_offset(0, 0, k0 + kPairFilters * (SPLIT ? __builtin_amdgcn_readfirstlane(quad) : quad), 0, 0, p.Kp);
+    const int8_t* const wave_flt = reinterpret_cast<const int8_t*>(blob + pairs_off) + filter_pair_offset(0, 0, k0 + kPairFilters * (STREAMS ? __builtin_amdgcn_readfirstlane(group) : group), 0, 0, p.Kp);
     const size_t flt_block = (size_t)(p.Kp >> 3) * kPairValues * kFilterFragBytes;
     cx.flt = wave_flt + lane * 16;
 
@@ -556,7 +589,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         __builtin_amdgcn_s_barrier();
         WG_STAMP(4);
     };
-    if constexpr (SPLIT) {
+    if constexpr (STREAMS) {
         // Several blocks of few tiles are bound by what fetches the filters (147 KB per block and workgroup, from memory in a network, where
         // a compute unit takes in 10 - 16 bytes per clock): the next block's fragments are requested as this one's are used, behind its
         // patch, and travel beside its transform (452 -> 160 at 20x20, N = 4, 20.2 -> 14.3 us with the order of the grid).  The first
@@ -567,8 +600,8 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         auto block_fragments = [&](int cb) {   // those of a block that is not this workgroup's arrive as zeros, without a trip to memory
             return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(wave_flt + cb * flt_block), 0, cb < cb_end ? 0x7fffffff : 0, kRawBufferWord3);
         };
-        auto blocks_of = [&](auto H) -> bool {
-            using Half = Products<H>;
+        auto blocks_of = [&](auto SHARE, auto H) -> bool {
+            using Half = Products<SHARE>;
             v4i ring[kRing];
             for (int cb = cb_first; cb < cb_end; ++cb) {
                 const __amdgpu_buffer_rsrc_t now = block_fragments(cb), next = block_fragments(cb + 1);
@@ -577,12 +610,12 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
                     WG_STAMP(2);
                     transform_rows<H>(u, out, [&](auto I) {
                         __builtin_amdgcn_sched_barrier(0);
-                        ring[I] = Half::template fragment<I>(now, lane16);
+                        if constexpr (I < Half::NF) ring[I] = Half::template fragment<I>(now, lane16);
                         __builtin_amdgcn_sched_barrier(0);
                     });
                     if (!blob_matches(header, p.K, p.Cf, WG_LOSSLESS)) return false;   // uniform: nobody reaches the next barrier
                 } else {
-                    raw.template take<kRing>(true, lane, u);
+                    raw.template take<(kRing < Half::NF ? kRing : Half::NF)>(true, lane, u);
                     WG_STAMP(2);
                     transform_rows<H>(u, out, [](auto) {});
                 }
@@ -596,7 +629,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
             }
             return true;
         };
-        if (!(half == 0 ? blocks_of(std::integral_constant<int, 0>{}) : blocks_of(std::integral_constant<int, 1>{}))) return;
+        if (!by_share(blocks_of)) return;
     } else {
         using First = Products<0>;
         using Second = Products<1>;
@@ -619,17 +652,18 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         }
     }
 
-    // ---- stage both halves' partial outputs, add them, store whole lines ------------------------------
+    // ---- stage the shares' partial outputs, add them, store whole lines ------------------------------
     // the staging area lies behind the operand planes (it begins where the raw patches were, which nobody reads
     // after the last transform), so a wave stages its outputs as soon as it has them
     int* const stage = reinterpret_cast<int*>(lds + kPlanesBytes);
+    using St = Stage<PARTS>;
     {
-        // lane = tile (lane & 15) x filters 8 quad + 2 (lane / 16), + 1
-        int* dst = stage + half * kStageHalf + (lane & 15) * kStageRow + 8 * quad + 2 * (lane >> 4);
+        // lane = tile (lane & 15) x filters 8 group + 2 (lane / 16), + 1
+        int* dst = stage + part * St::kPart + (lane & 15) * St::kRow + 8 * group + 2 * (lane >> 4);
 #pragma unroll
-        for (int o = 0; o < 16; ++o) *reinterpret_cast<v2i*>(dst + o * kStageOut) = Y[o];
+        for (int o = 0; o < 16; ++o) *reinterpret_cast<v2i*>(dst + o * St::kOut) = Y[o];
     }
-    if constexpr (SPLIT) {   // loads that nobody takes are still in flight
+    if constexpr (STREAMS) {   // loads that nobody takes are still in flight
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
     } else {
@@ -637,8 +671,11 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
     }
     WG_STAMP(6);
     auto sixteen = [&](int o, int tile, int k4) {   // 16 x the finished outputs of filters k0 + 4 k4 .. + 3 at output o of a tile
-        const int at = o * kStageOut + tile * kStageRow + 4 * k4;
-        return *reinterpret_cast<const v4i*>(stage + at) + *reinterpret_cast<const v4i*>(stage + kStageHalf + at);
+        const int at = o * St::kOut + tile * St::kRow + 4 * k4;
+        v4i sum = *reinterpret_cast<const v4i*>(stage + at);
+#pragma unroll
+        for (int i = 1; i < PARTS; ++i) sum += *reinterpret_cast<const v4i*>(stage + i * St::kPart + at);
+        return sum;
     };
     auto staged = [&](int o, int tile, int k4) { return sixteen(o, tile, k4) >> 4; };
     auto best_of_window = [&](int pi, int pj, int tile, int k4) {   // the 2x2 maximum, then requantised (all of it is monotonic)
@@ -646,6 +683,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         const v4i b = __builtin_elementwise_max(sixteen(4 * (2 * pi + 1) + 2 * pj, tile, k4), sixteen(4 * (2 * pi + 1) + 2 * pj + 1, tile, k4));
         return requantise(__builtin_elementwise_max(a, b) >> 4, q8);
     };
+    constexpr int kQuads = St::kFilters / 4;   // of four filters
     if constexpr (LAYOUT == WG_NCHW && OUT != kOutSums) {
         // a filter's outputs lie together: sixteen consecutive tiles of an image row are 64 consecutive pixels
         const int tile = (tid >> 2) & 15, t = tile0 + tile;
@@ -655,12 +693,12 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         const size_t plane = (size_t)H * W;
         auto first = [&](auto* base, int k4, int h, int w) { return base + ((size_t)n * p.K + k0 + 4 * k4) * plane + (size_t)h * W + w; };
         if constexpr (!Q8) {
-            // thread: row i, column j of a tile, four groups of four filters
+            // thread: row i, column j of a tile, half of the workgroup's groups of four filters
             const int j = tid & 3, i = (tid >> 6) & 3, h = 4 * ty + i, w = 4 * tx + j;
             if (t >= p.T || h >= H || w >= W) return;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int k4 = 4 * (tid >> 8) + g;
+            for (int g = 0; g < kQuads / 2; ++g) {
+                const int k4 = kQuads / 2 * (tid >> 8) + g;
                 const v4i v = staged(4 * i + j, tile, k4);
                 int32_t* const at = first(y, k4, h, w);
 #pragma unroll
@@ -670,7 +708,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         } else if (q8.pool) {
             // thread: one pooled pixel of a tile, four filters
             const int pj = tid & 1, pi = (tid >> 1) & 1, k4 = tid >> 6, h = 2 * ty + pi, w = 2 * tx + pj;
-            if (t >= p.T || h >= H || w >= W) return;
+            if (t >= p.T || h >= H || w >= W || k4 >= kQuads) return;
             const v4i best = best_of_window(pi, pj, tile, k4);
             int8_t* const at = first(q8.out, k4, h, w);
 #pragma unroll
@@ -679,7 +717,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         } else {
             // thread: row i of a tile (four pixels: one dword where rows stay aligned), four filters
             const int i = tid & 3, k4 = tid >> 6, h = 4 * ty + i, w = 4 * tx;
-            if (t >= p.T || h >= H) return;
+            if (t >= p.T || h >= H || k4 >= kQuads) return;
             const bool word_store = ((W & 3) | (int)(reinterpret_cast<uintptr_t>(q8.out) & 3)) == 0;
             v4i px[4];
 #pragma unroll
@@ -699,29 +737,31 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         }
         return;
     }
-    // thread: filters k0 + 4 k4 .. + 3 of output column j of tile `tile`; round r: output row r
-    const int k4 = tid & 7, j = (tid >> 3) & 3, tile = tid >> 5;
+    // thread: filters k0 + 4 k4 .. + 3 of output column j of tile `tile`; round r: output row r, of four (two with 16 filters, row0 ..)
+    constexpr int kRows = 2 * kQuads / 4;
+    const int k4 = tid & (kQuads - 1), j = (tid / kQuads) & 3, tile = (tid / (4 * kQuads)) & 15, row0 = kRows == 4 ? 0 : 2 * (tid >> 8);
     const int t = tile0 + tile, kk = k0 + 4 * k4;
     int n = 0, ty = 0, tx = 0;
     if (t < p.T) decode_tile(p, t, n, ty, tx);
     const int row = 4 * ty, col = 4 * tx + j;
     const bool live = t < p.T && col < p.W && kk < p.K;
     if constexpr (OUT == kOutSums) {
-        v4i* const to = reinterpret_cast<v4i*>(y + split_sums_offset(16, bz, bx, by, at.tile_blocks, p.Kp)) + (16 * tile + j) * (kBlockFilters / 4) + k4;
+        v4i* const to = reinterpret_cast<v4i*>(y + split_sums_offset(16, bz, bx, k0 / kBlockFilters, at.tile_blocks, p.Kp)) +
+                        (16 * tile + j) * (kBlockFilters / 4) + k0 % kBlockFilters / 4 + k4;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) to[4 * r * (kBlockFilters / 4)] = sixteen(4 * r + j, tile, k4);
+        for (int r = row0; r < row0 + kRows; ++r) to[4 * r * (kBlockFilters / 4)] = sixteen(4 * r + j, tile, k4);
         return;
     }
     if constexpr (!Q8) {
         int32_t* const first = y + ((size_t)(n * p.H + row) * p.W + col) * p.K + kk;
         const bool vector_store = (p.K & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
-        v4i v[4];
+        v4i v[kRows];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = staged(4 * r + j, tile, k4);
+        for (int r = 0; r < kRows; ++r) v[r] = staged(4 * (row0 + r) + j, tile, k4);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (!live || row + r >= p.H) continue;
-            int32_t* at = first + (size_t)r * p.W * p.K;
+        for (int r = 0; r < kRows; ++r) {
+            if (!live || row + row0 + r >= p.H) continue;
+            int32_t* at = first + (size_t)(row0 + r) * p.W * p.K;
             if (vector_store) {
                 *reinterpret_cast<v4i*>(at) = v[r];
             } else {
@@ -743,17 +783,17 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
             }
         };
         if (!q8.pool) {
-            v4i v[4];
+            v4i v[kRows];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = requantise(staged(4 * r + j, tile, k4), q8);
+            for (int r = 0; r < kRows; ++r) v[r] = requantise(staged(4 * (row0 + r) + j, tile, k4), q8);
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (live && row + r < p.H) put(q8.out + ((size_t)(n * p.H + row + r) * p.W + col) * p.K + kk, v[r]);
+            for (int r = 0; r < kRows; ++r)
+                if (live && row + row0 + r < p.H) put(q8.out + ((size_t)(n * p.H + row + row0 + r) * p.W + col) * p.K + kk, v[r]);
         } else if (j < 2) {
-            // thread: pooled column j (0, 1) of its tile, both pooled rows
+            // thread: pooled column j (0, 1) of its tile, both pooled rows (one)
             const int Ho = p.H >> 1, Wo = p.W >> 1, ocol = 2 * tx + j;
 #pragma unroll
-            for (int pi = 0; pi < 2; ++pi) {
+            for (int pi = row0 / 2; pi < row0 / 2 + kRows / 2; ++pi) {
                 const v4i best = best_of_window(pi, j, tile, k4);
                 if (t < p.T && kk < p.K && ocol < Wo && 2 * ty + pi < Ho)
                     put(q8.out + ((size_t)(n * Ho + 2 * ty + pi) * Wo + ocol) * p.K + kk, best);
@@ -763,17 +803,17 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
     WG_STAMP(7);
 }
 
-template <int LAYOUT, int LOAD, int OUT>
+template <int LAYOUT, int LOAD, int OUT, int PARTS>
 __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, const uint8_t* __restrict__ blob,
                                                             size_t pairs_off, int32_t* __restrict__ y, Problem p, Int8Epilogue q8) {
     WG_TAKE_GEOMETRY(p, 2);
-    lossless_pair<LAYOUT, LOAD, OUT>(x, blob, pairs_off, y, p, q8, SplitPlace{0, (int)blockIdx.x, (int)blockIdx.y, 0, 0, 0});
+    lossless_pair<LAYOUT, LOAD, OUT, PARTS>(x, blob, pairs_off, y, p, q8, SplitPlace{0, (int)blockIdx.x, (int)blockIdx.y, 0, 0, 0});
 }
-template <int LOAD>
+template <int LOAD, int PARTS>
 __global__ __launch_bounds__(512) void lossless_pair_sums_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_SPLIT_PARAMS,
                                                                  const uint8_t* __restrict__ blob, size_t pairs_off, int32_t* __restrict__ sums, Problem p) {
     WG_TAKE_GEOMETRY(p, 2);
-    lossless_pair<WG_NHWC, LOAD, kOutSums>(x, blob, pairs_off, sums, p, Int8Epilogue{nullptr, 0, 0, 0, 0},
+    lossless_pair<WG_NHWC, LOAD, kOutSums, PARTS>(x, blob, pairs_off, sums, p, Int8Epilogue{nullptr, 0, 0, 0, 0},
                                            place_split(s_across, s_packed));
 }
 
@@ -920,17 +960,23 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
 }
 
 // (of the padding to 64 filters, a block of 32 that do not exist has nothing to do: no sums of theirs are looked at)
-template <int LAYOUT, int LOAD, int OUT>
+template <int LAYOUT, int LOAD, int OUT, int PARTS>
 hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p, const Int8Epilogue& q8, hipStream_t s) {
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LAYOUT, LOAD, OUT>), kLdsBytes)) return e;
-    dim3 grid(ceil_div(p.T, kTileBlock), ceil_div(p.K, kBlockFilters));
-    lossless_pair_kernel<LAYOUT, LOAD, OUT><<<grid, 64 * kWaves, kLdsBytes, s>>>(x, WG_GEOMETRY(p), blob, bl.pairs_off, y, p, q8);
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LAYOUT, LOAD, OUT, PARTS>), pair_lds_bytes<PARTS>())) return e;
+    dim3 grid(ceil_div(p.T, kTileBlock), ceil_div(p.K, Stage<PARTS>::kFilters));
+    lossless_pair_kernel<LAYOUT, LOAD, OUT, PARTS><<<grid, 64 * kWaves, pair_lds_bytes<PARTS>(), s>>>(x, WG_GEOMETRY(p), blob, bl.pairs_off, y, p, q8);
     return hipGetLastError();
 }
-inline SplitGrid split_grid(const Problem& p, int blocks, int splits, int mode) {
+// Quarters of the entries and 16 filters per workgroup where their grid is still one round of the compute units: products and
+// store take half as long, while the patches are loaded and transformed twice as often, on compute units that had nothing to do
+// (us, halves / quarters: 16 -> 16 at 16x16, channel-major, 7.5 / 6.5; 100 -> 75 at 37x53, N = 4, channel-major, 12.3 / 10.75).
+bool in_quarters(const Problem& p, int splits) {
+    return (long long)ceil_div(p.T, kTileBlock) * ceil_div(p.K, Stage<4>::kFilters) * splits <= compute_units();
+}
+inline SplitGrid split_grid(const Problem& p, int blocks, int splits, int mode, int filters = kBlockFilters) {
     const int tile_blocks = ceil_div(p.T, kTileBlock);
-    return SplitGrid(tile_blocks, ceil_div(p.K, kBlockFilters), splits, blocks, mode == WG_LOSSLESS && tile_blocks <= 10);
+    return SplitGrid(tile_blocks, ceil_div(p.K, filters), splits, blocks, mode == WG_LOSSLESS && tile_blocks <= 10);
 }
 
 // How the patches of a tensor are read (see kLoadDwords ..).
@@ -954,6 +1000,8 @@ int lossless_variant() { return g_lossless_variant.load(std::memory_order_relaxe
 
 bool plane_patches_hold(const Problem& p) { return (long long)p.N * p.C * p.H * p.W >= 8; }   // whole 8-byte loads exist
 
+bool lossless_pair_takes(const Problem& p, bool pieces) { return in_quarters(p, 1) && (pieces || p.CB <= 6); }
+
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout) {
     const int v = lossless_variant();
     const bool applies = layout == WG_NHWC ? p.C % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 4 == 0 : plane_patches_hold(p);
@@ -965,8 +1013,11 @@ hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t*
                                      const Int8Epilogue& q8, hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
+    auto form = [&](auto LAYOUT, auto LOAD, auto PARTS) {
+        return q8.out != nullptr ? launch<LAYOUT, LOAD, kOutInt8, PARTS>(x, b, bl, y, p, q8, s) : launch<LAYOUT, LOAD, kOutInt32, PARTS>(x, b, bl, y, p, q8, s);
+    };
     auto go = [&](auto LAYOUT, auto LOAD) {
-        return q8.out != nullptr ? launch<LAYOUT, LOAD, kOutInt8>(x, b, bl, y, p, q8, s) : launch<LAYOUT, LOAD, kOutInt32>(x, b, bl, y, p, q8, s);
+        return in_quarters(p, 1) ? form(LAYOUT, LOAD, std::integral_constant<int, 4>{}) : form(LAYOUT, LOAD, std::integral_constant<int, 2>{});
     };
     using std::integral_constant;
     constexpr integral_constant<int, WG_NHWC> nhwc{};
@@ -980,13 +1031,16 @@ hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t*
 hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits,
                                      hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
-    const SplitGrid grid = split_grid(p, blocks, splits, WG_LOSSLESS);
-    auto go = [&](auto LOAD) -> hipError_t {
-        static LdsLimitOnce lds_limit;   // per LOAD
-        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_sums_kernel<LOAD>), kLdsBytes)) return e;
-        lossless_pair_sums_kernel<LOAD><<<grid.grid, 64 * kWaves, kLdsBytes, s>>>(x, WG_GEOMETRY(p), WG_SPLIT(grid), static_cast<const uint8_t*>(blob),
-                                                                                     bl.pairs_off, sums, p);
+    auto form = [&](auto LOAD, auto PARTS) -> hipError_t {
+        static LdsLimitOnce lds_limit;   // per instance
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_sums_kernel<LOAD, PARTS>), pair_lds_bytes<PARTS>())) return e;
+        const SplitGrid grid = split_grid(p, blocks, splits, WG_LOSSLESS, Stage<PARTS>::kFilters);
+        lossless_pair_sums_kernel<LOAD, PARTS><<<grid.grid, 64 * kWaves, pair_lds_bytes<PARTS>(), s>>>(
+            x, WG_GEOMETRY(p), WG_SPLIT(grid), static_cast<const uint8_t*>(blob), bl.pairs_off, sums, p);
         return hipGetLastError();
+    };
+    auto go = [&](auto LOAD) {
+        return in_quarters(p, splits) ? form(LOAD, std::integral_constant<int, 4>{}) : form(LOAD, std::integral_constant<int, 2>{});
     };
     using std::integral_constant;
     switch (load_of(x, p, layout)) {

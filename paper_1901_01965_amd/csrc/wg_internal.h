@@ -295,6 +295,10 @@ hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t*
 bool plane_patches_hold(const Problem& p);   // channel-major activations of p can be read that way
 // 0: this form does not apply (layout) or is switched off, 1: applies, the dispatcher decides, 2: forced by the test hook
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout);
+// Channels-last activations of several channel blocks, not split: whether this form, with 16 filters per workgroup, is ahead of
+// the role-specialised one.  It is wherever its grid is one round of the compute units (2.1 + 2.6 us per block against 5.7 + 2.7, with
+// 4-byte instead of 16-byte loads, !pieces, 1.6 + 3.3).
+bool lossless_pair_takes(const Problem& p, bool pieces);
 void set_lossless_variant(int v);
 int lossless_variant();
 // The same form with the channel blocks dealt to `splits` workgroups each: leaves 16 x outputs as int32, 16 per tile and filter

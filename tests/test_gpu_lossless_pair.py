@@ -125,3 +125,26 @@ def test_quoted_layer_both_forms_agree_with_the_oracle():
     y_auto = wg.winograd_conv2d_int8(xd, packed, wg.NHWC)
     assert torch.equal(y_pair, y_other) and torch.equal(y_pair, y_auto)
     assert np.array_equal(wl.from_nhwc(y_pair.cpu().numpy()), oracle.direct_conv2d(x, g))
+
+
+@pytest.mark.parametrize("layout", [wg.NHWC, wg.NCHW])
+@pytest.mark.parametrize("shape", [  # N, C, K, H, W; 16 tiles x 16 filters per workgroup up to a grid of one round (256 compute units), else 32
+    (1, 24, 256, 64, 64),     # 16 x 16 workgroups of 16 filters: the last grid in quarters
+    (1, 24, 257, 64, 64),     # the first one in halves
+    (1, 136, 25, 31, 18),     # three channel blocks, the second 16-filter block has 9
+    (2, 64, 5, 10, 14),       # filters of a workgroup's second wave group do not exist; pooled tiles cut
+    (3, 100, 140, 44, 52),    # two blocks, 4-byte loads, 27 x 9 workgroups
+])
+def test_quarters_and_halves_of_the_entries(shape, layout):
+    """int32 and int8 outputs, pooled and not, of the forms that share the entries among two and among four waves."""
+    N, C, K, H, W = shape
+    x, g = wl.make_custom(N, C, K, H, W, seed=97)
+    want = oracle.direct_conv2d(x, g)
+    channels_last = layout == wg.NHWC
+    xd, gd = (_dev(wl.to_nhwc(x)), _dev(wl.to_krsc(g))) if channels_last else (_dev(x), _dev(g))
+    host = lambda y: wl.from_nhwc(y.cpu().numpy()) if channels_last else y.cpu().numpy()
+    packed = wg.winograd_filter_transform(gd, layout, wg.LOSSLESS)
+    assert np.array_equal(host(wg.winograd_conv2d_int8(xd, packed, layout)), want)
+    for pool in (False, True) if H % 2 == 0 and W % 2 == 0 else (False,):
+        got = wg.winograd_conv2d_int8_requant(xd, packed, 11, True, pool, layout)
+        assert np.array_equal(host(got), oracle.requant_relu_pool(want, 11, True, pool)), pool
