@@ -38,11 +38,18 @@ constexpr ActScaleTable make_act_scale_table() {
     }
     return t;
 }
+constexpr uint32_t largest_act_shift() {
+    const ActScaleTable t = make_act_scale_table();
+    uint32_t p = 0;
+    for (int mx = 0; mx <= kActMax; ++mx) p = ((t.v[mx] >> 8) & 255u) > p ? (t.v[mx] >> 8) & 255u : p;
+    return p;
+}
+static_assert(largest_act_shift() <= 8, "act_factors");
 __device__ const ActScaleTable kActScale = make_act_scale_table();
 
 constexpr int kActPlanes = 36;                       // 16 real entries, then (Re, Im) of each complex entry
 static_assert(kActPlanes * kPlaneBytes <= kLdsBytes, "the single-limb planes lie where the two-limb planes do");
-constexpr int kActNpBytes = 16 * kEntries * 16;         // v4i [tile][26]: (n, n), (half, half), (p, p) in 16-bit pairs
+constexpr int kActNpBytes = 16 * kEntries * 4;          // uint32 [tile][26]: act_factors
 constexpr int kActRqBytes = kEntries * 16 * 4;         // uint32 [26][tile]: the table entry (r, q in its upper bytes)
 
 __device__ inline s16x2 abs_max(Quad v) {
@@ -60,11 +67,10 @@ struct MaxKeeper {
 // ... and in the second: every value times its tile's factor, rounded half up, as one int8 operand plane
 struct ScaledPlanes {
     LdsPlaneSink sink;
-    const v4i* np;   // this tile's 26 factors
+    const uint32_t* np;   // this tile's 26 factors
     __device__ inline uint32_t scaled(int entry, Quad v) const {
-        const v4i t = np[entry];
-        const s16x2 mul = as_s16x2((uint32_t)t[0]), half = as_s16x2((uint32_t)t[1]), sh = as_s16x2((uint32_t)t[2]);
-        return pack_low_bytes(Quad{(v.a * mul + half) >> sh, (v.b * mul + half) >> sh});
+        const s16x2 mul = as_s16x2(np[entry]), half = {128, 128};
+        return pack_high_bytes(Quad{v.a * mul + half, v.b * mul + half});
     }
     __device__ inline void real_entry(int p, Quad v) const { sink.put(p, scaled(p, v)); }
     __device__ inline void complex_entry(int j, Quad re, Quad im) const {
@@ -73,10 +79,12 @@ struct ScaledPlanes {
     }
 };
 
-// What a table entry means to the transform threads: (n, n), (half, half), (p, p) in 16-bit pairs.
-__device__ inline v4i act_factors(uint32_t entry) {
-    const uint32_t n = max(entry & 255u, 1u), sh = (entry >> 8) & 255u, hf = (1u << sh) >> 1;
-    return (v4i){(int)(n * 0x00010001u), (int)(hf * 0x00010001u), (int)(sh * 0x00010001u), 0};
+// What a table entry means to the transform threads: n 2^(8-p) twice, in 16 bits each.  p <= 8, so (v n + 2^(p-1)) >> p is
+// (v n 2^(8-p) + 128) >> 8, the upper byte of 16 bits (|v n| <= 127 2^p; unscaled, n = 1 and p = 0, |v| <= 127): one multiply-add per
+// two channels and the permutation that packs the bytes anyway, one dword of LDS per entry.  With n, 2^(p-1) and p in three it
+// took a shift more and a 16-byte read: 256 -> 256 at 14x14, N = 64, both kernels, 26.5 us.
+__device__ inline uint32_t act_factors(uint32_t entry) {
+    return (max(entry & 255u, 1u) << (8u - ((entry >> 8) & 255u))) * 0x00010001u;
 }
 // ... and (n, p, r, q) as the exported table has it.
 __device__ inline v4i act_table_row(uint32_t entry) {

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
     const int tile0 = bx * kFusedTiles, k0 = by * 8 * PW;
     const BlobHeaderWords header = read_blob_header(blob);   // compared by either role, see fused_conv_roles_kernel
     auto matches = [&] { return blob_matches(header, p.K, p.Cf, WG_SCALED); };
-    v4i* const np_tab = reinterpret_cast<v4i*>(lds + kActFactorsOff);
+    uint32_t* const np_tab = reinterpret_cast<uint32_t*>(lds + kActFactorsOff);
     uint32_t* const rq_tab = reinterpret_cast<uint32_t*>(lds + act_rq_off<PW>());
     // the tiles' factors; tiles beyond the last one keep n = 1
     auto expand_factors = [&] {

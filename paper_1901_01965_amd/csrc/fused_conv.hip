@@ -344,7 +344,7 @@ __global__ __launch_bounds__(256) void fused_conv_act_scaled_kernel(const int8_t
     const int a_tile = tid >> 4, a_cq = tid & 15;
     const int a_t = tile0 + a_tile;
     const int a_tx = __shfl(my_tx, a_tile), a_ty = __shfl(my_ty, a_tile), a_n = __shfl(my_n, a_tile);
-    v4i* np_tab = reinterpret_cast<v4i*>(lds + kActNpOff);
+    uint32_t* np_tab = reinterpret_cast<uint32_t*>(lds + kActNpOff);
     uint32_t* rq_tab = reinterpret_cast<uint32_t*>(lds + kActRqOff);
     constexpr bool VEC4 = LOAD == kLoadDwords;
     uint32_t patch[6][6];
