@@ -130,12 +130,14 @@ __device__ inline void bias_patch(const Problem& p, int ty, int tx, int c0, uint
 // The 1-D rule of B^T on a real 6-vector (Section 3.4, the expansion of d' = B^T d):
 //   t0 = v0 - v4, t1 = v1+v2+v3+v4, t2 = -v1+v2-v3+v4, t3 = (v4-v2) + i (v3-v1), t5 = v5 - v1
 // (t4 is the conjugate of t3 and never formed).
+template <class V>
 struct Line {
-    Quad t0, t1, t2, t3r, t3i, t5;
+    V t0, t1, t2, t3r, t3i, t5;
 };
-__device__ inline Line bt_rule(Quad v0, Quad v1, Quad v2, Quad v3, Quad v4, Quad v5) {
-    Line o;
-    const Quad s13 = v1 + v3, s24 = v2 + v4;
+template <class V>
+__device__ inline Line<V> bt_rule(V v0, V v1, V v2, V v3, V v4, V v5) {
+    Line<V> o;
+    const V s13 = v1 + v3, s24 = v2 + v4;
     o.t0 = v0 - v4;
     o.t1 = s24 + s13;
     o.t2 = s24 - s13;
@@ -205,6 +207,8 @@ struct OperandSplitter {
 //                 where the XOR and two permutations took three (1.5 times: a third of the transform's unpacking);
 //   ChannelPairs: u = x + bias like BiasedBytes, but lanes a = (c0, c1), b = (c2, c3) for a receiver that multiplies pairs of
 //                 neighbouring channels.
+//   HalfPairs:    two channels as half-precision numbers (x itself: an integer of at most 2048, as everything the transform
+//                 forms from int8 is, is exact there), for a receiver that multiplies them as such.
 struct BiasedBytes {
     __device__ inline static Quad lanes(uint32_t u) { return unpack_u8x4(u); }
     template <class ENC> __device__ inline static Quad bias11(const ENC enc) { return Quad{as_s16x2(enc.bias11()), as_s16x2(enc.bias11())}; }
@@ -218,6 +222,17 @@ struct ChannelPairs : BiasedBytes {
         return Quad{as_s16x2(__builtin_amdgcn_perm(0u, u, 0x0c010c00u)), as_s16x2(__builtin_amdgcn_perm(0u, u, 0x0c030c02u))};
     }
 };
+typedef _Float16 h16x2 __attribute__((ext_vector_type(2)));
+struct HalfPairs {
+    __device__ inline static h16x2 lanes(uint32_t x) { return __builtin_bit_cast(h16x2, x); }
+    // bytes u = x + 128 of two channels, selected by `pair` (kFirstPair or kSecondPair), -> x: 1024 + u has u as its low mantissa bits
+    static constexpr uint32_t kFirstPair = 0x04010400u, kSecondPair = 0x04030402u;
+    __device__ inline static uint32_t from_biased(uint32_t u, uint32_t pair) {
+        const h16x2 bias = {(_Float16)1152.0f, (_Float16)1152.0f};
+        return __builtin_bit_cast(uint32_t, lanes(__builtin_amdgcn_perm(0x64646464u, u, pair)) - bias);
+    }
+    template <class ENC> __device__ inline static h16x2 bias11(const ENC) { return (h16x2){0, 0}; }
+};
 
 // Transforms one loaded patch (four channels, pixel (a, b) at 6 b + a) and hands every free entry to `out`
 // (real_entry(p, v), complex_entry(j, re, im)): an OperandSplitter emits the operand planes.
@@ -229,18 +244,19 @@ struct NothingToDo {
 template <class Bytes = BiasedBytes, class Out, class ENC = SignedInt8, class Done = NothingToDo>
 __device__ inline void transform_patch(const uint32_t (&u)[36], const Out& out, const ENC enc = ENC{}, const Done& done_with = Done{}) {
     // column pass: d'[.][b] = B^T applied down each of the six tile columns
-    Line col[6];
+    using V = decltype(Bytes::lanes(0u));
+    Line<V> col[6];
 #pragma unroll
     for (int b = 0; b < 6; ++b) {
         col[b] = bt_rule(Bytes::lanes(u[6 * b]), Bytes::lanes(u[6 * b + 1]), Bytes::lanes(u[6 * b + 2]), Bytes::lanes(u[6 * b + 3]),
                          Bytes::lanes(u[6 * b + 4]), Bytes::lanes(u[6 * b + 5]));
         done_with(b);
     }
-    const Quad bias11 = Bytes::bias11(enc);   // what the bias leaves at entry (1,1): 16 * 128 for signed int8
+    const V bias11 = Bytes::bias11(enc);   // what the bias leaves at entry (1,1): 16 * 128 for signed int8
     // row pass on the real rows 0,1,2,5 of d': entries (r, {0,1,2,5}) real, (r,3) complex
 #define WG_REAL_ROW(ri, field)                                                                      \
     {                                                                                               \
-        Line r = bt_rule(col[0].field, col[1].field, col[2].field, col[3].field, col[4].field,      \
+        Line<V> r = bt_rule(col[0].field, col[1].field, col[2].field, col[3].field, col[4].field,      \
                          col[5].field);                                                             \
         if (ri == 1) r.t1 = r.t1 - bias11;                                                          \
         out.real_entry(4 * ri + 0, r.t0);                                                           \
@@ -256,8 +272,8 @@ __device__ inline void transform_patch(const uint32_t (&u)[36], const Out& out, 
 #undef WG_REAL_ROW
     // row 3 of d' is complex, a + i b: the rule acts on a and b separately; the two
     // entries (3,3) and (3,4) mix them: (x4-x2) +- i (x3-x1).
-    const Line ra = bt_rule(col[0].t3r, col[1].t3r, col[2].t3r, col[3].t3r, col[4].t3r, col[5].t3r);
-    const Line rb = bt_rule(col[0].t3i, col[1].t3i, col[2].t3i, col[3].t3i, col[4].t3i, col[5].t3i);
+    const Line<V> ra = bt_rule(col[0].t3r, col[1].t3r, col[2].t3r, col[3].t3r, col[4].t3r, col[5].t3r);
+    const Line<V> rb = bt_rule(col[0].t3i, col[1].t3i, col[2].t3i, col[3].t3i, col[4].t3i, col[5].t3i);
     out.complex_entry(4, ra.t0, rb.t0);
     out.complex_entry(5, ra.t1, rb.t1);
     out.complex_entry(6, ra.t2, rb.t2);

@@ -268,7 +268,7 @@ __device__ inline void transform_rows(const uint32_t (&u)[6][6], const Out& out,
     });
     const Quad bias11 = StoredInt8::bias11(SignedInt8{});
     auto row_rule = [](const Quad (&c)[6]) { return bt_rule(c[0], c[1], c[2], c[3], c[4], c[5]); };
-    auto emit_real_row = [&](int ri, const Line& l) {
+    auto emit_real_row = [&](int ri, const Line<Quad>& l) {
         out.real_entry(4 * ri + 0, l.t0);
         out.real_entry(4 * ri + 1, l.t1);
         out.real_entry(4 * ri + 2, l.t2);
@@ -287,7 +287,7 @@ __device__ inline void transform_rows(const uint32_t (&u)[6][6], const Out& out,
         tick(std::integral_constant<int, 6>{});
         emit_real_row(0, row_rule(r0));
         tick(std::integral_constant<int, 7>{});
-        Line l1 = row_rule(r1);
+        Line<Quad> l1 = row_rule(r1);
         l1.t1 = l1.t1 - bias11;
         emit_real_row(1, l1);
         tick(std::integral_constant<int, 8>{});
@@ -305,7 +305,7 @@ __device__ inline void transform_rows(const uint32_t (&u)[6][6], const Out& out,
         emit_real_row(3, row_rule(r5));
         tick(std::integral_constant<int, 7>{});
         // the rule acts on the real and the imaginary part of row 3 separately; entries (3,3) and (3,4) mix them
-        const Line ra = row_rule(ra_), rb = row_rule(rb_);
+        const Line<Quad> ra = row_rule(ra_), rb = row_rule(rb_);
         out.complex_entry(4, ra.t0, rb.t0);
         out.complex_entry(5, ra.t1, rb.t1);
         out.complex_entry(6, ra.t2, rb.t2);
