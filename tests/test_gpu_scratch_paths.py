@@ -57,6 +57,21 @@ def test_int32_and_int8_outputs(shape, layout, mode):
 
 
 @pytest.mark.parametrize("mode", [wg.LOSSLESS, wg.SCALED])
+@pytest.mark.parametrize("C", [256, 576, 640])
+@pytest.mark.parametrize("K, H, W", [(32, 6, 10), (33, 10, 6), (100, 2, 14), (68, 4, 4)])
+def test_splits_are_finished_whatever_their_number(C, K, H, W, mode):
+    """Four splits, nine and ten (more than a thread reads at once); tiles cut by the image's edge and windows of them;
+    filters just into and just short of a block of 32, channels-last outputs stored by fours and one by one."""
+    x, g, xd, gd = _inputs((1, C, K, H, W), wg.NHWC)
+    want = oracle.direct_conv2d(x, g) if mode == wg.LOSSLESS else oracle.winograd_conv2d(x, g, oracle.SCALED, 127)[0]
+    packed = wg.winograd_filter_transform(gd, wg.NHWC, mode)
+    assert np.array_equal(_nchw(wg.winograd_conv2d_int8(xd, packed, wg.NHWC), wg.NHWC), want)
+    for relu, pool in ((True, True), (False, False)):
+        got = wg.winograd_conv2d_int8_requant(xd, packed, 10, relu, pool, wg.NHWC)
+        assert np.array_equal(_nchw(got, wg.NHWC), oracle.requant_relu_pool(want, 10, relu, pool))
+
+
+@pytest.mark.parametrize("mode", [wg.LOSSLESS, wg.SCALED])
 @pytest.mark.parametrize("layout", [wg.NCHW, wg.NHWC])
 @pytest.mark.parametrize("shape", [(2, 64, 64, 9, 10), (2, 6, 70, 5, 5), (1, 200, 33, 14, 7), (40, 32, 128, 14, 14), (9, 128, 72, 28, 28)])
 def test_uint8_inputs(shape, layout, mode):
