@@ -482,14 +482,17 @@ struct Plan {
 // one workgroup against b in each of W, whose partial sums are written and read (36 per tile and filter in scaled mode, 16
 // otherwise).  Fitted to layers of 128 .. 896 channels and K = 16 .. 512 filters that fill at most half the chip, with filters
 // that are not in the L2, as in a network (us; 330 layers in scaled mode, 220 in lossless mode, off by 3 - 8 % on average):
-//   lossless: 3.9 + 3.3 b + W / 48 split; one kernel, which is the limb-pair form with 16 filters per workgroup there (lossless_conv.hip),
+//   lossless: 4.3 + 3.3 b + W / 50 split; one kernel, which is the limb-pair form with 16 filters per workgroup there (lossless_conv.hip),
 //             2.1 + 2.6 CB + W16 / 120 for W16 workgroups with 16-byte pieces, 1.6 + 3.3 CB with 4-byte loads, both + CB min(K, 256) / 1500 for the
 //             filters that come from memory (128 -> 64 at 28x28, N = 16: split 10.95, 9.0; 256 -> 32 at 20x20, N = 16: 9.6, 12.6; near
 //             the line, 256 -> 256 at 56x56, N = 1, the split that it chooses takes 15.5, one kernel 14.6);
 //             on channel-major tensors 4.0 + 4.4 b + W / 53 + 6.4 per million outputs split and 2.5 + 3.9 CB + W16 / 120 (112 -> 448 at 58x29,
-//             N = 1: 18.5, 12.7), with a copy, where there are more than two blocks, 8.7 + 2.68 CB;
+//             N = 1: 18.5, 12.7); with a copy, where there are more than two blocks, 9.3 + 2.75 CB and 5.1 + 3.7 b + W / 68 + 7.1 per million
+//             outputs split (256 -> 128 at 72x72, N = 1: 20.3, 19.2);
 //             4.8 + 3.27 b + W / 50 + CB K / 2700 and 5.7 + 2.68 CB, both with a copy
-//   scaled:   5.9 + 1.65 CB in one kernel, 9.1 + 1.92 b + W / 28 split (18 - 24, 16.7 - 17.6; N = 4: 18.4, 21.4)
+//   scaled:   5.9 + 1.65 CB in one kernel, 7.4 + 3.0 b + W / 29 split (512 -> 512 at 17x12, N = 1: 18.8, 15.0; 256 -> 64 at 38x26, N = 2: 11.4, 12.4);
+//             on channel-major tensors 8.0 + 1.75 CB, with a copy, and 8.6 + 2.9 b + W / 24 (256 -> 16 at 42x17, N = 2: 14.8, 12.0; 192 -> 512 at 23x23,
+//             N = 1: 13.7, 16.8; 118 layers after the finishing kernel reads 16 bytes at a time, off by 5 and 4 %; 0.3 in favour of one kernel)
 // and 3.9 b - 2.2 more where the split kernels cannot read 16-byte pieces (N = 2, 324 -> 512 at 28x28, lossless: 21.6, 32.8).  The
 // kernels that transform on waves of their own take 0.6 less with up to 32 filters (250 drawn layers; 272 -> 16 at 17x17, N = 10, scaled: 13.3, 14.1;
 // 116 -> 16 at 64x7, N = 15, lossless: 10.4, 11.2), unless it needs a copy that the split kernels do without (`planes`; 480 -> 32 at
@@ -497,11 +500,14 @@ struct Plan {
 // pairs: one kernel would be the limb-pair form.
 bool split_pays(int mode, const Problem& p, int b, int W, bool pieces, bool planes, bool pairs) {
     const double w16 = (double)ceil_div(p.T, kFusedTiles) * ceil_div(p.K, 16), outputs = (double)p.N * p.H * p.W * p.K / 1e6;
-    double one = (mode == WG_LOSSLESS ? (planes ? 8.7 : 5.7) + 2.68 * p.CB : 5.9 + 1.65 * p.CB) - (p.K <= kFusedFilters && !planes ? 0.6 : 0.0);
+    double one = mode == WG_LOSSLESS ? (planes ? 9.3 + 2.75 * p.CB : 5.7 + 2.68 * p.CB)
+                                     : (planes ? 8.0 + 1.75 * p.CB : 5.9 + 1.65 * p.CB);
+    if (p.K <= kFusedFilters && !planes) one -= 0.6;
     if (pairs) one = (planes ? 2.5 + 3.9 * p.CB : pieces ? 2.1 + 2.6 * p.CB : 1.6 + 3.3 * p.CB) + w16 / 120.0 + (planes ? 0.0 : p.CB * std::min(p.Kp, 256) / 1500.0);
-    const double split = mode != WG_LOSSLESS ? 9.1 + 1.92 * b + W / 28.0
+    const double split = mode != WG_LOSSLESS ? (planes ? 8.6 + 2.9 * b + W / 24.0 : 7.4 + 3.0 * b + W / 29.0)
+                       : planes && !pairs    ? 5.1 + 3.7 * b + W / 68.0 + 7.1 * outputs
                        : planes              ? 4.0 + 4.4 * b + W / 53.0 + 6.4 * outputs
-                       : pairs               ? 3.9 + 3.3 * b + W / 48.0
+                       : pairs               ? 4.3 + 3.3 * b + W / 50.0
                                              : 4.8 + 3.27 * b + W / 50.0 + p.CB * p.Kp / 2700.0;
     return one > split + (pieces ? 0.0 : 3.9 * b - 2.2);
 }

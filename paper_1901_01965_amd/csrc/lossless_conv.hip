@@ -1000,7 +1000,7 @@ int lossless_variant() { return g_lossless_variant.load(std::memory_order_relaxe
 
 bool plane_patches_hold(const Problem& p) { return (long long)p.N * p.C * p.H * p.W >= 8; }   // whole 8-byte loads exist
 
-bool lossless_pair_takes(const Problem& p, bool pieces) { return in_quarters(p, 1) && (pieces || p.CB <= 6); }
+bool lossless_pair_takes(const Problem& p, bool pieces) { return in_quarters(p, 1) && (pieces || (p.CB <= 6 && p.CB * p.Kp <= 2048)); }
 
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout) {
     const int v = lossless_variant();

@@ -12,63 +12,93 @@
 namespace wg {
 namespace {
 
-constexpr int kItems = 64;   // filters of one tile per workgroup
+constexpr int kItems = 64;   // filters of one tile per workgroup (lossless mode)
 
-// grid: (padded tiles, Kp / 64), 256 threads: lane = filter.
+// Sum of the splits of N vectors that lie `step` vectors apart (and a split `split` vectors from the next), up to eight splits in flight.
+template <int N>
+__device__ inline void add_splits(const v4i* from, size_t split, int step, int splits, v4i (&sum)[N]) {
+    auto add = [&](auto FLIGHT) {
+        constexpr int n = decltype(FLIGHT)::value;
+        for (int s = 0; s < splits; s += n) {
+            v4i part[N][n];
+#pragma unroll
+            for (int j = 0; j < n; ++j)
+#pragma unroll
+                for (int i = 0; i < N; ++i) part[i][j] = from[(size_t)min(s + j, splits - 1) * split + i * step];
+#pragma unroll
+            for (int j = 0; j < n; ++j)
+#pragma unroll
+                for (int i = 0; i < N; ++i) sum[i] += s + j < splits ? part[i][j] : (v4i){0, 0, 0, 0};
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < N; ++i) sum[i] = (v4i){0, 0, 0, 0};
+    if (splits <= 2)      add(std::integral_constant<int, 2>{});
+    else if (splits <= 4) add(std::integral_constant<int, 4>{});
+    else                  add(std::integral_constant<int, 8>{});
+}
+
+// Scaled mode.  grid: (padded tiles, ceil(K / 32)), 128 threads: 32 filters of one tile.  First 96 threads take four filters of three
+// sums each, in 16-byte reads, while the other 32 bring the filters' factors (r, q) to LDS in whole lines; then a thread has one row of
+// outputs (one pooled output) of one filter.
+// (The kernel alone, 512 -> 512 at 14x14, N = 1, eight splits, pooled or not: 9.1 - 12.4 us with a lane per filter, four-byte reads, factors read 8
+// bytes of every 16 by lanes 416 apart, and one wave in four finishing; 5.0 now.  Both kernels, 512 -> 16 at 7x14: 12.5 -> 10.4.)
+constexpr int kSumsFilters = 32, kSumsReaders = 96;
+constexpr int kFactorRow = kEntries + 1;   // of a filter in LDS: an odd number of 8-byte pairs
 template <int LAYOUT, bool Q8>
-__global__ __launch_bounds__(256) void split_finish_kernel(const int32_t* __restrict__ partial, WG_GEOMETRY_PARAMS, int Kp, int splits,
+__global__ __launch_bounds__(128) void split_finish_kernel(const int32_t* __restrict__ partial, WG_GEOMETRY_PARAMS, int Kp, int splits,
                                                            const uint8_t* __restrict__ blob,
                                                            size_t table_off, int32_t* __restrict__ y, Problem p, Int8Epilogue q8) {
     WG_TAKE_GEOMETRY(p, 2);
     p.Kp = Kp;
-    __shared__ int sums[3][kAccPlanes][kItems];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int k = blockIdx.y * kItems + lane, t = blockIdx.x;
-    if (t >= p.T) return;
+    __shared__ __attribute__((aligned(16))) int sums[kAccPlanes][kSumsFilters];
+    __shared__ int2 factors[kSumsFilters * kFactorRow];
+    const int tid = threadIdx.x, t = blockIdx.x, k0 = blockIdx.y * kSumsFilters;
+    if (t >= p.T) return;   // (uniform)
     const int tile_blocks = (p.T + 15) / 16;
-    const size_t split = split_sums_offset(kAccPlanes, 1, 0, 0, tile_blocks, p.Kp);
-    const int32_t* const mine = partial + split_sums_offset(kAccPlanes, 0, t >> 4, k >> 5, tile_blocks, p.Kp) + (t & 15) * 32 + (k & 31);
     const BlobHeaderWords header = read_blob_header(blob);
-    // the first wave finishes: it asks for its filter's factors (r, q) along with its sums
-    int2 rq[kEntries];
-    if (wave == 0) {
-        const ScaleEntry* tk = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k * kEntries;
+    constexpr int kOwn = kAccPlanes / (kSumsReaders / 8);   // sums per reading thread
+    static_assert(kOwn * (kSumsReaders / 8) == kAccPlanes, "every sum has a reader");
+    const int l = tid & 7, e0 = (tid >> 3) * kOwn;
+    v4i m[kOwn];
+    if (tid < kSumsReaders) {
+        const size_t split = split_sums_offset(kAccPlanes, 1, 0, 0, tile_blocks, p.Kp) / 4;
+        const v4i* const from = reinterpret_cast<const v4i*>(partial + split_sums_offset(kAccPlanes, 0, t >> 4, k0 >> 5, tile_blocks, p.Kp) +
+                                                             (t & 15) * 32 + e0 * (16 * 32)) + l;
+        add_splits<kOwn>(from, split, 16 * 32 / 4, splits, m);
+    } else {
+        const ScaleEntry* const table = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k0 * kEntries;
+        const int i0 = tid - kSumsReaders;
 #pragma unroll
-        for (int e = 0; e < kEntries; ++e) rq[e] = *reinterpret_cast<const int2*>(&tk[e].r);
-    }
-    int m[kAccPlanes];
-#pragma unroll
-    for (int e = 0; e < kAccPlanes; ++e) m[e] = 0;
-    for (int s = wave; s < splits; s += 8) {   // two splits at a time
-        int v[2][kAccPlanes];
-        const bool second = s + 4 < splits;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int e = 0; e < kAccPlanes; ++e) v[i][e] = mine[(second ? s + 4 * i : s) * split + e * (16 * 32)];
-#pragma unroll
-        for (int e = 0; e < kAccPlanes; ++e) m[e] += v[0][e] + (second ? v[1][e] : 0);
-    }
-    if (wave > 0) {
-#pragma unroll
-        for (int e = 0; e < kAccPlanes; ++e) sums[wave - 1][e][lane] = m[e];
+        for (int i = 0; i < kEntries; ++i) {
+            const int at = 32 * i + i0, k = at / kEntries;   // kEntries x 32 entries
+            const v4i entry = *reinterpret_cast<const v4i*>(table + at);
+            factors[k * kFactorRow + at - k * kEntries] = make_int2(entry[2], entry[3]);
+        }
     }
     __syncthreads();
-    if (wave > 0) return;
-    const int others = min(splits, 4) - 1;
-    for (int w = 0; w < others; ++w)
+    if (tid < kSumsReaders) {
 #pragma unroll
-        for (int e = 0; e < kAccPlanes; ++e) m[e] += sums[w][e][lane];
+        for (int i = 0; i < kOwn; ++i) {
+            const int e = e0 + i, entry = e < kRealEntries ? e : kRealEntries + (e - kRealEntries) / 2;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int2 rq = factors[(4 * l + c) * kFactorRow + entry];
+                m[i][c] = ReverseScale(rq.x, rq.y)(m[i][c]);   // Section 4.2
+            }
+            *reinterpret_cast<v4i*>(&sums[e][4 * l]) = m[i];
+        }
+    }
+    __syncthreads();
+    const int kk = tid & (kSumsFilters - 1), row = tid / kSumsFilters, k = k0 + kk;
     if (k >= p.K || !blob_matches(header, p.K, p.Cf, WG_SCALED)) return;
-
     int re[16], cr[10], ci[10];
-    auto unscale = [&](int e, int v) { return ReverseScale(rq[e].x, rq[e].y)(v); };   // Section 4.2
 #pragma unroll
-    for (int e = 0; e < 16; ++e) re[e] = unscale(e, m[e]);
+    for (int e = 0; e < 16; ++e) re[e] = sums[e][kk];
 #pragma unroll
     for (int j = 0; j < 10; ++j) {
-        cr[j] = unscale(16 + j, m[16 + 2 * j]);
-        ci[j] = unscale(16 + j, m[17 + 2 * j]);
+        cr[j] = sums[16 + 2 * j][kk];
+        ci[j] = sums[17 + 2 * j][kk];
     }
     int out[4][4];   // out[j][i]: output row i, column j
     output_tile(re, cr, ci, out);
@@ -79,28 +109,22 @@ __global__ __launch_bounds__(256) void split_finish_kernel(const int32_t* __rest
     auto at = [&](int h, int w, int H, int W) {
         return LAYOUT == WG_NHWC ? (((size_t)n * H + h) * W + w) * p.K + k : (((size_t)n * p.K + k) * H + h) * W + w;
     };
-    if (Q8 && q8.pool) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int h = 2 * ty + i, w = 2 * tx + j;
-                if (h >= p.H >> 1 || w >= p.W >> 1) continue;
-                const int best = max(max(out[2 * j][2 * i], out[2 * j + 1][2 * i]), max(out[2 * j][2 * i + 1], out[2 * j + 1][2 * i + 1]));
-                q8.out[at(h, w, p.H >> 1, p.W >> 1)] = (int8_t)requantise((best + rnd) >> 4, q8);
-            }
+    auto mine = [&](int a, int b, int c, int d) { return row < 2 ? (row == 0 ? a : b) : (row == 2 ? c : d); };
+    if (Q8 && q8.pool) {   // window (row / 2, row % 2)
+        auto best = [&](int i, int j) { return max(max(out[2 * j][2 * i], out[2 * j + 1][2 * i]), max(out[2 * j][2 * i + 1], out[2 * j + 1][2 * i + 1])); };
+        const int h = 2 * ty + (row >> 1), w = 2 * tx + (row & 1), v = mine(best(0, 0), best(0, 1), best(1, 0), best(1, 1));
+        if (h < p.H >> 1 && w < p.W >> 1) q8.out[at(h, w, p.H >> 1, p.W >> 1)] = (int8_t)requantise((v + rnd) >> 4, q8);
         return;
     }
+    const int h = 4 * ty + row;
+    if (h >= p.H) return;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int h = 4 * ty + i, w = 4 * tx + j;
-            if (h >= p.H || w >= p.W) continue;
-            const int v = (out[j][i] + rnd) >> 4;
-            if constexpr (Q8) q8.out[at(h, w, p.H, p.W)] = (int8_t)requantise(v, q8);
-            else              y[at(h, w, p.H, p.W)] = v;
-        }
+    for (int j = 0; j < 4; ++j) {
+        const int w = 4 * tx + j, v = (mine(out[j][0], out[j][1], out[j][2], out[j][3]) + rnd) >> 4;
+        if (w >= p.W) continue;
+        if constexpr (Q8) q8.out[at(h, w, p.H, p.W)] = (int8_t)requantise(v, q8);
+        else              y[at(h, w, p.H, p.W)] = v;
+    }
 }
 
 // The same for launch_lossless_pair_sums, whose workgroups leave 16 x outputs: adds the splits, rescales and stores.
@@ -123,21 +147,9 @@ __global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restr
     const size_t split = split_sums_offset(16, 1, 0, 0, tile_blocks, p.Kp) / 4;   // v4i per split
     const v4i* const from = reinterpret_cast<const v4i*>(sums + split_sums_offset(16, 0, t >> 4, kk >> 5, tile_blocks, p.Kp) +
                                                          (t & 15) * (16 * 32) + o * 32 + (kk & 31));
-    v4i v = {0, 0, 0, 0};
-    auto add = [&](auto FLIGHT) {
-        constexpr int n = decltype(FLIGHT)::value;
-        for (int s = 0; s < splits; s += n) {
-            v4i part[n];
-#pragma unroll
-            for (int j = 0; j < n; ++j) part[j] = from[(size_t)min(s + j, splits - 1) * split];
-#pragma unroll
-            for (int j = 0; j < n; ++j) v += s + j < splits ? part[j] : (v4i){0, 0, 0, 0};
-        }
-    };
-    if (splits <= 2)      add(std::integral_constant<int, 2>{});
-    else if (splits <= 4) add(std::integral_constant<int, 4>{});
-    else                  add(std::integral_constant<int, 8>{});
-    v = v >> 4;
+    v4i total[1];
+    add_splits<1>(from, split, 0, splits, total);
+    v4i v = total[0] >> 4;
     int n, ty, tx;
     decode_tile(p, t, n, ty, tx);
     int h = 4 * ty + (o >> 2), w = 4 * tx + (o & 3), H = p.H, W = p.W;
@@ -185,9 +197,9 @@ hipError_t launch_sums_finish(const RolesCall& c, const int32_t* sums, int split
 }
 
 hipError_t launch_split_finish(const RolesCall& c, const int32_t* partial, int splits, hipStream_t s) {
-    const dim3 grid(padded_tiles(c.p), c.p.Kp / kItems);
+    const dim3 grid(padded_tiles(c.p), ceil_div(c.p.K, kSumsFilters));
     auto go = [&](auto kernel) {
-        kernel<<<grid, 256, 0, s>>>(partial, WG_GEOMETRY(c.p), c.p.Kp, splits, c.blob, c.bl.table_off, c.y, c.p, c.q8);
+        kernel<<<grid, 128, 0, s>>>(partial, WG_GEOMETRY(c.p), c.p.Kp, splits, c.blob, c.bl.table_off, c.y, c.p, c.q8);
         return hipGetLastError();
     };
     if (c.layout == WG_NHWC) return c.q8.out ? go(&split_finish_kernel<WG_NHWC, true>) : go(&split_finish_kernel<WG_NHWC, false>);

@@ -297,7 +297,7 @@ bool plane_patches_hold(const Problem& p);   // channel-major activations of p c
 int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout);
 // Channels-last activations of several channel blocks, not split: whether this form, with 16 filters per workgroup, is ahead of
 // the role-specialised one.  It is wherever its grid is one round of the compute units (2.1 + 2.6 us per block against 5.7 + 2.7, with
-// 4-byte instead of 16-byte loads, !pieces, 1.6 + 3.3).
+// 4-byte instead of 16-byte loads, !pieces, 1.6 + 3.3), unless those loads meet many filters (348 -> 512 at 11x26, N = 4: 21.8, here 23.7).
 bool lossless_pair_takes(const Problem& p, bool pieces);
 void set_lossless_variant(int v);
 int lossless_variant();
