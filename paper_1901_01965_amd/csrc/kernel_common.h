@@ -144,7 +144,8 @@ __device__ inline int lane_again() {
 // a time: wave w has tiles 4w .. 4w + 3, lane = (tile, four channels).  Every lane loads its four channels of every pixel,
 // sixteen neighbouring lanes 64 bytes in a row.  (Sixteen channels of every fourth pixel per lane, nine instructions instead of
 // 36, and an exchange of dwords between lanes by lane swaps or through LDS were 1-2 % and 5-15 % slower: the exchange lengthens
-// the transform waves' chain, and these loads are not what fills the memory path.)
+// the transform waves' chain.  Eight channels of every second pixel and one swap of lane rows per two pixels, as many instructions as
+// here: 4 - 17 % slower.  With half of these loads left out the kernels take 3 - 9 % less: that is all a cheaper form could give.)
 // Pixels are numbered down the columns, i = 6 b + a.
 struct PatchLoader {
     uint32_t patch[36];   // the patch, or what is in flight of it
