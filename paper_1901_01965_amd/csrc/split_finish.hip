@@ -12,7 +12,9 @@
 namespace wg {
 namespace {
 
-constexpr int kItems = 64;   // filters of one tile per workgroup (lossless mode)
+// Filters of one tile per workgroup: as many as lie together in memory (lossless mode, 64 / 32, both kernels: 512 -> 75 at 14x14, N = 4,
+// channel-major, 10.5 / 10.2 us, 512 -> 512 at 14x14, N = 1, 11.07 / 10.98).
+constexpr int kItems = 32;
 
 // Sum of the splits of N vectors that lie `step` vectors apart (and a split `split` vectors from the next), up to eight splits in flight.
 template <int N>
@@ -43,7 +45,7 @@ __device__ inline void add_splits(const v4i* from, size_t split, int step, int s
 // outputs (one pooled output) of one filter.
 // (The kernel alone, 512 -> 512 at 14x14, N = 1, eight splits, pooled or not: 9.1 - 12.4 us with a lane per filter, four-byte reads, factors read 8
 // bytes of every 16 by lanes 416 apart, and one wave in four finishing; 5.0 now.  Both kernels, 512 -> 16 at 7x14: 12.5 -> 10.4.)
-constexpr int kSumsFilters = 32, kSumsReaders = 96;
+constexpr int kReaders = 96;
 constexpr int kFactorRow = kEntries + 1;   // of a filter in LDS: an odd number of 8-byte pairs
 template <int LAYOUT, bool Q8>
 __global__ __launch_bounds__(128) void split_finish_kernel(const int32_t* __restrict__ partial, WG_GEOMETRY_PARAMS, int Kp, int splits,
@@ -51,24 +53,24 @@ __global__ __launch_bounds__(128) void split_finish_kernel(const int32_t* __rest
                                                            size_t table_off, int32_t* __restrict__ y, Problem p, Int8Epilogue q8) {
     WG_TAKE_GEOMETRY(p, 2);
     p.Kp = Kp;
-    __shared__ __attribute__((aligned(16))) int sums[kAccPlanes][kSumsFilters];
-    __shared__ int2 factors[kSumsFilters * kFactorRow];
-    const int tid = threadIdx.x, t = blockIdx.x, k0 = blockIdx.y * kSumsFilters;
+    __shared__ __attribute__((aligned(16))) int sums[kAccPlanes][kItems];
+    __shared__ int2 factors[kItems * kFactorRow];
+    const int tid = threadIdx.x, t = blockIdx.x, k0 = blockIdx.y * kItems;
     if (t >= p.T) return;   // (uniform)
     const int tile_blocks = (p.T + 15) / 16;
     const BlobHeaderWords header = read_blob_header(blob);
-    constexpr int kOwn = kAccPlanes / (kSumsReaders / 8);   // sums per reading thread
-    static_assert(kOwn * (kSumsReaders / 8) == kAccPlanes, "every sum has a reader");
+    constexpr int kOwn = kAccPlanes / (kReaders / 8);   // sums per reading thread
+    static_assert(kOwn * (kReaders / 8) == kAccPlanes, "every sum has a reader");
     const int l = tid & 7, e0 = (tid >> 3) * kOwn;
     v4i m[kOwn];
-    if (tid < kSumsReaders) {
+    if (tid < kReaders) {
         const size_t split = split_sums_offset(kAccPlanes, 1, 0, 0, tile_blocks, p.Kp) / 4;
         const v4i* const from = reinterpret_cast<const v4i*>(partial + split_sums_offset(kAccPlanes, 0, t >> 4, k0 >> 5, tile_blocks, p.Kp) +
                                                              (t & 15) * 32 + e0 * (16 * 32)) + l;
         add_splits<kOwn>(from, split, 16 * 32 / 4, splits, m);
     } else {
         const ScaleEntry* const table = reinterpret_cast<const ScaleEntry*>(blob + table_off) + (size_t)k0 * kEntries;
-        const int i0 = tid - kSumsReaders;
+        const int i0 = tid - kReaders;
 #pragma unroll
         for (int i = 0; i < kEntries; ++i) {
             const int at = 32 * i + i0, k = at / kEntries;   // kEntries x 32 entries
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(128) void split_finish_kernel(const int32_t* __rest
         }
     }
     __syncthreads();
-    if (tid < kSumsReaders) {
+    if (tid < kReaders) {
 #pragma unroll
         for (int i = 0; i < kOwn; ++i) {
             const int e = e0 + i, entry = e < kRealEntries ? e : kRealEntries + (e - kRealEntries) / 2;
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(128) void split_finish_kernel(const int32_t* __rest
         }
     }
     __syncthreads();
-    const int kk = tid & (kSumsFilters - 1), row = tid / kSumsFilters, k = k0 + kk;
+    const int kk = tid & (kItems - 1), row = tid / kItems, k = k0 + kk;
     if (k >= p.K || !blob_matches(header, p.K, p.Cf, WG_SCALED)) return;
     int re[16], cr[10], ci[10];
 #pragma unroll
@@ -129,16 +131,16 @@ __global__ __launch_bounds__(128) void split_finish_kernel(const int32_t* __rest
 
 // The same for launch_lossless_pair_sums, whose workgroups leave 16 x outputs: adds the splits, rescales and stores.
 // Thread: four filters of one output of a tile, up to eight splits' reads in flight together; with pooling the four outputs of a
-// window lie in the four quarters of a wave, which take their maximum across it.
+// window lie in lanes eight apart, which take their maximum across them.
 // (The kernel alone, 512 -> 512 at 14x14, N = 1, eight splits, pooled: 5.2 us with a thread per window that read its four outputs, and four
 // splits of each, one after another; 3.1 now.  One image through the VGG-16-shaped network, eight such layers, 170.1 -> 163.9.)
-// grid: (padded tiles, Kp / 64), 256 threads: 16 x four filters, 16 outputs.
+// grid: (padded tiles, ceil(K / 32)), 128 threads: 8 x four filters, 16 outputs.
 template <int LAYOUT, bool Q8>
-__global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restrict__ sums, WG_GEOMETRY_PARAMS, int Kp, int splits,
+__global__ __launch_bounds__(128) void sums_finish_kernel(const int32_t* __restrict__ sums, WG_GEOMETRY_PARAMS, int Kp, int splits,
                                                           const uint8_t* __restrict__ blob, int32_t* __restrict__ y, Problem p, Int8Epilogue q8) {
     WG_TAKE_GEOMETRY(p, 2);
     p.Kp = Kp;
-    const int t = blockIdx.x, kk = kItems * blockIdx.y + 4 * (threadIdx.x & 15), i = threadIdx.x >> 4;
+    const int t = blockIdx.x, kk = kItems * blockIdx.y + 4 * (threadIdx.x & 7), i = threadIdx.x >> 3;
     const bool pool = Q8 && q8.pool;
     if (t >= p.T) return;   // (uniform)
     const BlobHeaderWords header = read_blob_header(blob);
@@ -156,11 +158,11 @@ __global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restr
     if (pool) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
+            v[c] = max(v[c], __shfl_xor(v[c], 8));
             v[c] = max(v[c], __shfl_xor(v[c], 16));
-            v[c] = max(v[c], __shfl_xor(v[c], 32));
         }
         h >>= 1; w >>= 1; H >>= 1; W >>= 1;
-        if (threadIdx.x & 48) return;   // the first quarter stores
+        if (threadIdx.x & 24) return;   // one of the four stores
     }
     if constexpr (Q8) v = requantise(v, q8);
     if (!blob_matches(header, p.K, p.Cf, WG_LOSSLESS) || h >= H || w >= W) return;
@@ -187,9 +189,9 @@ __global__ __launch_bounds__(256) void sums_finish_kernel(const int32_t* __restr
 static int padded_tiles(const Problem& p) { return 16 * ceil_div(p.T, 16); }
 
 hipError_t launch_sums_finish(const RolesCall& c, const int32_t* sums, int splits, hipStream_t s) {
-    const dim3 grid(padded_tiles(c.p), c.p.Kp / kItems);
+    const dim3 grid(padded_tiles(c.p), ceil_div(c.p.K, kItems));
     auto go = [&](auto kernel) {
-        kernel<<<grid, 256, 0, s>>>(sums, WG_GEOMETRY(c.p), c.p.Kp, splits, c.blob, c.y, c.p, c.q8);
+        kernel<<<grid, 128, 0, s>>>(sums, WG_GEOMETRY(c.p), c.p.Kp, splits, c.blob, c.y, c.p, c.q8);
         return hipGetLastError();
     };
     if (c.layout == WG_NHWC) return c.q8.out ? go(&sums_finish_kernel<WG_NHWC, true>) : go(&sums_finish_kernel<WG_NHWC, false>);
@@ -197,7 +199,7 @@ hipError_t launch_sums_finish(const RolesCall& c, const int32_t* sums, int split
 }
 
 hipError_t launch_split_finish(const RolesCall& c, const int32_t* partial, int splits, hipStream_t s) {
-    const dim3 grid(padded_tiles(c.p), ceil_div(c.p.K, kSumsFilters));
+    const dim3 grid(padded_tiles(c.p), ceil_div(c.p.K, kItems));
     auto go = [&](auto kernel) {
         kernel<<<grid, 128, 0, s>>>(partial, WG_GEOMETRY(c.p), c.p.Kp, splits, c.blob, c.bl.table_off, c.y, c.p, c.q8);
         return hipGetLastError();
