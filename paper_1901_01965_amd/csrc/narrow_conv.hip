@@ -496,17 +496,28 @@ __global__ __launch_bounds__(256, 2) void narrow_conv_kernel(const int8_t* __res
     }
 }
 
+}  // namespace
+
+// Few tiles: 16 of them take a wave longer from the patch to the last store than the vector ALU's few.  64 groups of 16 tiles x 64
+// filters are two waves of narrow_wave_kernel per compute unit, 128 four, one per SIMD: the next group costs it 6 - 8 %.  (us,
+// narrow_wave_kernel and narrow_conv_kernel: scaled, int8 out, 49 groups 7.1, 7.9; 64 groups 7.3, 7.7, pooled 6.9, 7.1; 66 groups 8.0, 7.7, pooled
+// 7.6, 7.0; 98 groups 8.6, 7.7; 196 groups, 224x224x3 -> 64 at N = 1, 10.7, 7.9.  Lossless, int8 out, 98 groups 6.5, 6.9; 128 groups 6.75, 6.95;
+// 196 groups 7.8, 7.1.)  int32 outputs are four times the stores, which a lone workgroup does not hide (scaled, 66 groups 8.0, 8.1, 128 groups
+// 9.4, 8.6; lossless, 224x224 -> 64, N = 2 12.2, 12.9; N = 8 24.7, 25.7; N = 16 41.9, 40.0; N = 32 107, 85).
+bool narrow_on_matrix_cores(int tiles, int Kp, int mode, bool int8_out) {
+    const long long groups = (long long)ceil_div(tiles, 16) * (Kp / 64);
+    return groups > (mode == WG_SCALED ? (int8_out ? 64 : 70) : int8_out ? 128 : 1999);
+}
+
+namespace {
+
 template <int MODE, bool Q8>
 hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p,
                   const Int8Epilogue& q8, hipStream_t s) {
     const int tile_groups = ceil_div(p.T, 16), blocks = p.Kp / 64;
-    // Few tiles: 16 of them take a wave longer from the patch to the last store than the vector ALU's few.  (us, narrow_wave_kernel and
-    // narrow_conv_kernel: 224x224x3 -> 64 N = 1, 196 groups, int8 out, lossless 7.8, 7.1, scaled 10.7, 7.9; 112x112 N = 2, 98 groups, 6.5, 6.9 and
-    // 8.6, 7.7; N = 1 5.8, 7.0 and 7.1, 7.9.)  int32 outputs are four times the stores, which a lone workgroup does not hide
-    // (lossless, 224x224 N = 2 12.2, 12.9; N = 8 24.7, 25.7; N = 16 41.9, 40.0; N = 32 107, 85).
     // Nor outputs that cannot be stored four filters at a time (K = 75, 224x224 N = 4, lossless, pooled 21.4, 24.8; K = 130, 100x120 N = 4, C = 4 10.7, 15.5).
     const uint32_t uneven = Q8 ? (uint32_t)p.K | (uint32_t)reinterpret_cast<uintptr_t>(q8.out) : 4u * (uint32_t)p.K | (uint32_t)reinterpret_cast<uintptr_t>(y);
-    if ((uneven & (Q8 ? 3 : 15)) != 0 || (long long)tile_groups * blocks < (MODE == WG_SCALED ? 64 : Q8 ? 128 : 2000)) {
+    if ((uneven & (Q8 ? 3 : 15)) != 0 || !narrow_on_matrix_cores(p.T, p.Kp, MODE, Q8)) {
         // Tiles per wave: the kernel is bound by vector instructions, so the waves should fill every
         // SIMD evenly: two waves on each of the 1,024 SIMDs (two cover each other's LDS and memory
         // waits; a third would only add transform phases with mostly idle lanes).

@@ -268,3 +268,15 @@ def test_which_layers_deal_their_channel_blocks_to_several_workgroups(lib, N, C,
     for mode, sums in ((wg.LOSSLESS, 16), (wg.SCALED, 36)):
         per_split = sums * tiles * ((K + 63) // 64 * 64) * 4
         assert wanted(N, C, HW, HW, K, wg.NHWC, mode, 0) == (0 if splits[mode] == 1 else splits[mode] * per_split), mode
+
+
+@pytest.mark.parametrize("mode,int8_out,most", [(wg.SCALED, True, 64), (wg.SCALED, False, 70), (wg.LOSSLESS, True, 128), (wg.LOSSLESS, False, 1999)])
+def test_first_layers_of_few_tiles_stay_on_the_vector_alu(lib, mode, int8_out, most):
+    """Groups of 16 tiles x 64 filters up to which the one-wave kernel takes a first layer: where it measured faster (scaled, 64 groups
+    7.3 us against 7.7)."""
+    takes = lib._ZN2wg22narrow_on_matrix_coresEiiib
+    takes.restype, takes.argtypes = ctypes.c_bool, [ctypes.c_int] * 3 + [ctypes.c_bool]
+    for filter_blocks in (1, 2, 3):
+        groups = most // filter_blocks
+        assert not takes(16 * groups, 64 * filter_blocks, mode, int8_out)
+        assert takes(16 * groups + 1, 64 * filter_blocks, mode, int8_out)
