@@ -376,6 +376,9 @@ int winograd_debug_scaled_variant(int variant);
    mode, or one channel block).  0: the library's choice, 1: the 64-filter form wherever a layer streams and the form
    applies, 2: never, 3: always the form with eight product waves and 64 filters. */
 int winograd_debug_stream_variant(int variant);
+/* The same switch for first layers (channels-last, C <= 4).  0: the library's choice, 1: products on the matrix cores wherever the
+   outputs can be stored four filters at a time, 2: never. */
+int winograd_debug_narrow_variant(int variant);
 int winograd_num_filter_planes(int mode);
 
 /* Host-only: the (n, ty, tx) the kernels derive from tile index t = (n*TH + ty)*TW + tx for

@@ -52,6 +52,7 @@ def load_library():
         "winograd_debug_lossless_variant": (i, [i]),
         "winograd_debug_scaled_variant": (i, [i]),
         "winograd_debug_stream_variant": (i, [i]),
+        "winograd_debug_narrow_variant": (i, [i]),
         "winograd_conv2d_path": (i, [i, i, i, i, i, i]),
         "winograd_debug_tile_decode": (i, [i, i, i, i, i, i, vp]),
         "winograd_packed_filter_bytes": (sz, [i, i, i]),
@@ -111,7 +112,7 @@ def _done(result, where):
 
 EXPORTED_SYMBOLS = (
     "winograd_status_string", "winograd_num_activation_planes", "winograd_num_filter_planes",
-    "winograd_debug_force_path", "winograd_debug_stream_workgroups", "winograd_debug_lossless_variant", "winograd_debug_scaled_variant", "winograd_debug_stream_variant", "winograd_conv2d_path", "winograd_debug_tile_decode",
+    "winograd_debug_force_path", "winograd_debug_stream_workgroups", "winograd_debug_lossless_variant", "winograd_debug_scaled_variant", "winograd_debug_stream_variant", "winograd_debug_narrow_variant", "winograd_conv2d_path", "winograd_debug_tile_decode",
     "winograd_packed_filter_bytes", "winograd_workspace_bytes", "winograd_filter_transform",
     "winograd_packed_filter_check", "winograd_conv2d_int8", "winograd_conv2d_int8_requant",
     "winograd_static_workspace_limit", "winograd_conv2d_int8_static_workspace",
@@ -209,6 +210,12 @@ def scaled_variant(v):
     """Test hook (both modes): 0 = library's choice, 1 = the role-specialised kernel with eight product waves (64 filters
     per workgroup) wherever the layout allows, 2 = never that form."""
     _check(load_library().winograd_debug_scaled_variant(int(v)), "winograd_debug_scaled_variant")
+
+
+def narrow_variant(v):
+    """Test hook: 0 = library's choice for first layers (channels-last, C <= 4), 1 = products on the matrix cores wherever the
+    outputs can be stored four filters at a time, 2 = never."""
+    _check(load_library().winograd_debug_narrow_variant(int(v)), "winograd_debug_narrow_variant")
 
 
 def conv2d_path(N, C, H, W, K, mode):

@@ -25,6 +25,7 @@
 #include "wg_internal.h"
 
 #include <algorithm>
+#include <atomic>
 
 namespace wg {
 namespace {
@@ -496,7 +497,11 @@ __global__ __launch_bounds__(256, 2) void narrow_conv_kernel(const int8_t* __res
     }
 }
 
+std::atomic<int> g_narrow_variant{0};
+
 }  // namespace
+
+void set_narrow_variant(int v) { g_narrow_variant.store(v, std::memory_order_relaxed); }
 
 // Few tiles: 16 of them take a wave longer from the patch to the last store than the vector ALU's few.  64 groups of 16 tiles x 64
 // filters are two waves of narrow_wave_kernel per compute unit, 128 four, one per SIMD: the next group costs it 6 - 8 %.  (us,
@@ -505,6 +510,7 @@ __global__ __launch_bounds__(256, 2) void narrow_conv_kernel(const int8_t* __res
 // 196 groups 7.8, 7.1.)  int32 outputs are four times the stores, which a lone workgroup does not hide (scaled, 66 groups 8.0, 8.1, 128 groups
 // 9.4, 8.6; lossless, 224x224 -> 64, N = 2 12.2, 12.9; N = 8 24.7, 25.7; N = 16 41.9, 40.0; N = 32 107, 85).
 bool narrow_on_matrix_cores(int tiles, int Kp, int mode, bool int8_out) {
+    if (const int forced = g_narrow_variant.load(std::memory_order_relaxed)) return forced == 1;
     const long long groups = (long long)ceil_div(tiles, 16) * (Kp / 64);
     return groups > (mode == WG_SCALED ? (int8_out ? 64 : 70) : int8_out ? 128 : 1999);
 }

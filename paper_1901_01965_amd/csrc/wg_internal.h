@@ -323,6 +323,7 @@ hipError_t launch_fused_conv_u8(const uint8_t* x, int zero_point, const void* bl
 // Single-kernel path for channels-last inputs with C <= kNarrowChannels.
 // narrow_on_matrix_cores: whether such a layer of `tiles` tiles, whose outputs can be stored four filters at a time, has its products there.
 bool narrow_on_matrix_cores(int tiles, int Kp, int mode, bool int8_out);
+void set_narrow_variant(int v);   // test hook: 0 as measured, 1 always, 2 never
 hipError_t launch_narrow_conv(const int8_t* x, const void* blob, int32_t* y, const Problem& p, int mode,
                               const Int8Epilogue& q8, hipStream_t s);
 // Direct convolution; with scratch memory for channels-last copies of both operands any layout and channel count runs as a

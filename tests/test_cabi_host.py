@@ -280,3 +280,10 @@ def test_first_layers_of_few_tiles_stay_on_the_vector_alu(lib, mode, int8_out, m
         groups = most // filter_blocks
         assert not takes(16 * groups, 64 * filter_blocks, mode, int8_out)
         assert takes(16 * groups + 1, 64 * filter_blocks, mode, int8_out)
+    try:
+        for variant in (1, 2):
+            binding.narrow_variant(variant)
+            assert [takes(t, 64, mode, int8_out) for t in (1, 10 ** 6)] == [variant == 1] * 2
+    finally:
+        binding.narrow_variant(0)
+    assert lib.winograd_debug_narrow_variant(3) == EINVAL and lib.winograd_debug_narrow_variant(-1) == EINVAL
