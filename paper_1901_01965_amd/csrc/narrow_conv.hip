@@ -40,6 +40,30 @@ constexpr int kStagedGroupBytes = 16 * kStagedTileBytes;
 typedef _Float16 h16x4 __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+// What makes it exact.  The 1-D rules' sums of |coefficients|, rows 0, 1, 2 and 5, and the real and imaginary part of row 3; two of them
+// make an entry of 128 times their product.
+constexpr int kActReach[4] = {2, 4, 4, 2}, kActRe = 2, kActIm = 2;          // B^T
+constexpr int kFilterReach[4] = {4, 3, 3, 4}, kFilterRe = 2, kFilterIm = 1;   // 4 G
+constexpr int largest_value() {
+    int most = 0;
+    for (int r = 0; r < 4; ++r)
+        for (int c = 0; c < 4; ++c) most = std::max({most, kActReach[r] * kActReach[c], kFilterReach[r] * kFilterReach[c]});
+    return 128 * std::max({most, kActRe * kActRe + kActIm * kActIm, kFilterRe * kFilterRe + kFilterIm * kFilterIm});   // (the other parts are smaller)
+}
+constexpr int largest_sum() {   // lossless; scaled filters are smaller
+    int most = 0;
+    for (int r = 0; r < 4; ++r) {
+        const int row = kActReach[r] * kFilterReach[r];
+        for (int c = 0; c < 4; ++c) most = std::max(most, row * kActReach[c] * kFilterReach[c]);
+        most = std::max(most, row * (kActRe * kFilterRe + kActIm * kFilterIm));
+    }
+    const int act = kActRe * kActRe + kActIm * kActIm;   // either part of an entry of two complex rows
+    most = std::max(most, act * (kFilterRe * kFilterRe + kFilterIm * kFilterIm) + act * 2 * kFilterRe * kFilterIm);
+    return kNarrowChannels * 128 * 128 * most;
+}
+static_assert(largest_value() <= 2048, "transformed activations and filters are integers that a half holds");
+static_assert(largest_sum() <= 1 << 24, "a float holds every channel sum, and every partial sum of it");
+
 // ---- narrow_wave_kernel's pieces
 // Receives the free entries from the input transform: value index = real entry p, or
 // 16 + 2j (Re) and 17 + 2j (Im) of complex entry j, the order of the blob's narrow table.
