@@ -482,10 +482,11 @@ struct Plan {
 // one workgroup against b in each of W, whose partial sums are written and read (36 per tile and filter in scaled mode, 16
 // otherwise).  Fitted to layers of 128 .. 896 channels and K = 16 .. 512 filters that fill at most half the chip, with filters
 // that are not in the L2, as in a network (us; 330 layers in scaled mode, 220 in lossless mode, off by 3 - 8 % on average):
-//   lossless: 4.0 + 3.3 b + W / 50 split; one kernel, which is the limb-pair form with 16 filters per workgroup there (lossless_conv.hip),
+//   lossless: 4.3 + 3.3 b + W / 50 split; one kernel, which is the limb-pair form with 16 filters per workgroup there (lossless_conv.hip),
 //             2.1 + 2.6 CB + W16 / 120 for W16 workgroups with 16-byte pieces, 1.6 + 3.3 CB with 4-byte loads, both + CB min(K, 256) / 1500 for the
-//             filters that come from memory (128 -> 64 at 28x28, N = 16: split 10.95, 9.0; 256 -> 32 at 20x20, N = 16: 9.6, 12.6; near
-//             the line, 256 -> 256 at 56x56, N = 1, the split that it chooses takes 1.0 more than one kernel);
+//             filters that come from memory, unless filter blocks are dealt out first (split / one kernel: 256 -> 256 at 56x56, N = 1, 14.9, 13.8;
+//             256 -> 512 at 28x28, N = 1, 12.1, 12.8; 128 -> 64 at 14x14, N = 1, 9.1, 7.7; 256 -> 256 at 14x14, N = 1, 9.1, 12.4; of 226 layers the choice
+//             is 0.2 % from the better one on average, 12 % at most; with 4.0 it was 1.0 % and 26 %);
 //             on channel-major tensors 4.0 + 4.4 b + W / 53 + 6.4 per million outputs split and 2.5 + 3.9 CB + W16 / 120 (112 -> 448 at 58x29,
 //             N = 1: 18.5, 12.7); with a copy, where there are more than two blocks, 9.3 + 2.75 CB and 5.1 + 3.7 b + W / 68 + 7.1 per million
 //             outputs split (256 -> 128 at 72x72, N = 1: 20.3, 19.2);
@@ -503,11 +504,12 @@ bool split_pays(int mode, const Problem& p, int b, int W, bool pieces, bool plan
     double one = mode == WG_LOSSLESS ? (planes ? 9.3 + 2.75 * p.CB : 5.7 + 2.68 * p.CB)
                                      : (planes ? 8.0 + 1.75 * p.CB : 5.9 + 1.65 * p.CB);
     if (p.K <= kFusedFilters && !planes) one -= 0.6;
-    if (pairs) one = (planes ? 2.5 + 3.9 * p.CB : pieces ? 2.1 + 2.6 * p.CB : 1.6 + 3.3 * p.CB) + w16 / 120.0 + (planes ? 0.0 : p.CB * std::min(p.Kp, 256) / 1500.0);
+    if (pairs) one = (planes ? 2.5 + 3.9 * p.CB : pieces ? 2.1 + 2.6 * p.CB : 1.6 + 3.3 * p.CB) + w16 / 120.0 +
+                     (planes || lossless_pair_filters_first(p) ? 0.0 : p.CB * std::min(p.Kp, 256) / 1500.0);
     const double split = mode != WG_LOSSLESS ? (planes ? 8.6 + 2.9 * b + W / 24.0 : 7.4 + 3.0 * b + W / 29.0)
                        : planes && !pairs    ? 5.1 + 3.7 * b + W / 68.0 + 7.1 * outputs
                        : planes              ? 4.0 + 4.4 * b + W / 53.0 + 6.4 * outputs
-                       : pairs               ? 4.0 + 3.3 * b + W / 50.0
+                       : pairs               ? 4.3 + 3.3 * b + W / 50.0
                                              : 4.8 + 3.27 * b + W / 50.0 + p.CB * p.Kp / 2700.0;
     return one > split + (pieces ? 0.0 : 3.9 * b - 2.2);
 }

@@ -812,7 +812,7 @@ template <int LAYOUT, int LOAD, int OUT, int PARTS>
 __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, const uint8_t* __restrict__ blob,
                                                             size_t pairs_off, int32_t* __restrict__ y, Problem p, Int8Epilogue q8) {
     WG_TAKE_GEOMETRY(p, 2);
-    // grid (tile blocks, filter blocks), or (1, filter blocks, tile blocks): see filters_first
+    // grid (tile blocks, filter blocks), or (1, filter blocks, tile blocks): see lossless_pair_filters_first
     lossless_pair<LAYOUT, LOAD, OUT, PARTS>(x, blob, pairs_off, y, p, q8, SplitPlace{0, (int)(blockIdx.x + blockIdx.z), (int)blockIdx.y, 0, 0, 0});
 }
 template <int LOAD, int PARTS>
@@ -965,27 +965,20 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
     }
 }
 
-// Workgroups go to the XCDs in turn.  With the tile blocks dealt out first and a multiple of eight of them, every XCD reads all filters of
-// its few tiles' blocks; dealt out first, a multiple of eight filter blocks leaves each XCD an eighth of the filters.  (Quarters, several channel
-// blocks, us, tile blocks / filter blocks first: 256 -> 512 at 9x55, N = 3, 16.2 / 12.7, 320 -> 512 at 10x17, N = 8, 18.7 / 15.3, 256 -> 256 at
-// 53x12, N = 6, 13.9 / 13.1; 224 layers of 16 filter blocks and more 0.77 - 0.99, level with one channel block, with eight filter blocks 0.92 - 1.1,
-// with other numbers of them up to 1.05.)
-inline bool filters_first(const Problem& p, int filter_blocks) { return p.CB > 1 && filter_blocks >= 16 && filter_blocks % 8 == 0; }
-
 // (of the padding to 64 filters, a block of 32 that do not exist has nothing to do: no sums of theirs are looked at)
 template <int LAYOUT, int LOAD, int OUT, int PARTS>
 hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p, const Int8Epilogue& q8, hipStream_t s) {
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_kernel<LAYOUT, LOAD, OUT, PARTS>), pair_lds_bytes<PARTS>())) return e;
     dim3 grid(ceil_div(p.T, kTileBlock), ceil_div(p.K, Stage<PARTS>::kFilters));
-    if (PARTS == 4 && filters_first(p, grid.y)) grid = dim3(1, grid.y, grid.x);
+    if (PARTS == 4 && lossless_pair_filters_first(p)) grid = dim3(1, grid.y, grid.x);
     lossless_pair_kernel<LAYOUT, LOAD, OUT, PARTS><<<grid, 64 * kWaves, pair_lds_bytes<PARTS>(), s>>>(x, WG_GEOMETRY(p), blob, bl.pairs_off, y, p, q8);
     return hipGetLastError();
 }
 // Quarters of the entries and 16 filters per workgroup where their grid is still one round of the compute units: products and
 // store take half as long, while the patches are loaded and transformed twice as often, on compute units that had nothing to do
 // (us, halves / quarters: 16 -> 16 at 16x16, channel-major, 7.5 / 6.5; 100 -> 75 at 37x53, N = 4, channel-major, 12.3 / 10.75).  Against the
-// role-specialised kernel, 510 layers of up to one round: 0.65 - 1.02 (see filters_first for what it would be with many filters).
+// role-specialised kernel, 510 layers of up to one round: 0.65 - 1.02 (see lossless_pair_filters_first for what it would be with many filters).
 bool in_quarters(const Problem& p, int splits) {
     return (long long)ceil_div(p.T, kTileBlock) * ceil_div(p.K, Stage<4>::kFilters) * splits <= compute_units();
 }
@@ -1014,6 +1007,16 @@ void set_lossless_variant(int v) { g_lossless_variant.store(v, std::memory_order
 int lossless_variant() { return g_lossless_variant.load(std::memory_order_relaxed); }
 
 bool plane_patches_hold(const Problem& p) { return (long long)p.N * p.C * p.H * p.W >= 8; }   // whole 8-byte loads exist
+
+// Workgroups go to the XCDs in turn.  With the tile blocks dealt out first and a multiple of eight of them, every XCD reads all filters of
+// its few tiles' blocks; dealt out first, a multiple of eight filter blocks leaves each XCD an eighth of the filters.  (Quarters, several channel
+// blocks, us, tile blocks / filter blocks first: 256 -> 512 at 9x55, N = 3, 16.2 / 12.7, 320 -> 512 at 10x17, N = 8, 18.7 / 15.3, 256 -> 256 at
+// 53x12, N = 6, 13.9 / 13.1; 224 layers of 16 filter blocks and more 0.77 - 0.99, level with one channel block, with eight filter blocks 0.92 - 1.1,
+// with other numbers of them up to 1.05.)
+bool lossless_pair_filters_first(const Problem& p) {
+    const int filter_blocks = ceil_div(p.K, Stage<4>::kFilters);
+    return p.CB > 1 && filter_blocks >= 16 && filter_blocks % 8 == 0;
+}
 
 bool lossless_pair_takes(const Problem& p, bool pieces) { return in_quarters(p, 1) && (pieces || (p.CB <= 6 && p.CB * p.Kp <= 2048)); }
 

@@ -299,6 +299,7 @@ int lossless_pair_conv_choice(const int8_t* x, const Problem& p, int layout);
 // the role-specialised one.  It is wherever its grid is one round of the compute units (2.1 + 2.6 us per block against 5.7 + 2.7, with
 // 4-byte instead of 16-byte loads, !pieces, 1.6 + 3.3), unless those loads meet many filters (348 -> 512 at 11x26, N = 4: 21.8, here 23.7).
 bool lossless_pair_takes(const Problem& p, bool pieces);
+bool lossless_pair_filters_first(const Problem& p);   // its order of dealing out workgroups: every XCD then reads an eighth of the filters
 void set_lossless_variant(int v);
 int lossless_variant();
 // The same form with the channel blocks dealt to `splits` workgroups each: leaves 16 x outputs as int32, 16 per tile and filter

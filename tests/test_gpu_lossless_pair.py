@@ -134,7 +134,7 @@ def test_quoted_layer_both_forms_agree_with_the_oracle():
     (1, 136, 25, 31, 18),     # three channel blocks, the second 16-filter block has 9
     (2, 64, 5, 10, 14),       # filters of a workgroup's second wave group do not exist; pooled tiles cut
     (3, 100, 140, 44, 52),    # two blocks, 4-byte loads, 27 x 9 workgroups
-    # filter blocks dealt out first, see filters_first: several channel blocks, 16 filter blocks and more, a multiple of eight
+    # filter blocks dealt out first, see lossless_pair_filters_first: several channel blocks, 16 filter blocks and more, a multiple of eight
     (3, 136, 512, 16, 40),    # 32 x 8 workgroups: a whole round
     (1, 100, 250, 37, 41),    # the last of 16 filter blocks has 10, 7 tile blocks, the last with 14 tiles, 4-byte loads
     (2, 80, 384, 18, 26),     # 24 x 5
