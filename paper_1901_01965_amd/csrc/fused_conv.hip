@@ -491,7 +491,8 @@ struct Plan {
 //             N = 1: 18.5, 12.7); with a copy, where there are more than two blocks, 9.3 + 2.75 CB and 5.1 + 3.7 b + W / 68 + 7.1 per million
 //             outputs split (256 -> 128 at 72x72, N = 1: 20.3, 19.2);
 //             4.8 + 3.27 b + W / 50 + CB K / 2700 and 5.7 + 2.68 CB, both with a copy
-//   scaled:   5.9 + 1.65 CB in one kernel, 7.4 + 3.0 b + W / 29 split (512 -> 512 at 17x12, N = 1: 18.8, 15.0; 256 -> 64 at 38x26, N = 2: 11.4, 12.4);
+//   scaled:   5.9 + 1.65 CB in one kernel, 7.4 + 3.0 b + W / 29 split, 0.5 more up to three blocks, where the fit is 1.2 too high for one kernel
+//             (512 -> 512 at 17x12, N = 1: 18.8, 15.0; 256 -> 64 at 38x26, N = 2: 11.4, 12.4; 176 -> 64 at 8x8, N = 1: 9.1, 9.9);
 //             on channel-major tensors 8.0 + 1.75 CB, with a copy, and 8.6 + 2.9 b + W / 24 (256 -> 16 at 42x17, N = 2: 14.8, 12.0; 192 -> 512 at 23x23,
 //             N = 1: 13.7, 16.8; 118 layers after the finishing kernel reads 16 bytes at a time, off by 5 and 4 %; 0.3 in favour of one kernel)
 // and 3.9 b - 2.2 more where the split kernels cannot read 16-byte pieces (N = 2, 324 -> 512 at 28x28, lossless: 21.6, 32.8).  The
@@ -506,7 +507,7 @@ bool split_pays(int mode, const Problem& p, int b, int W, bool pieces, bool plan
     if (p.K <= kFusedFilters && !planes) one -= 0.6;
     if (pairs) one = (planes ? 2.5 + 3.9 * p.CB : pieces ? 2.1 + 2.6 * p.CB : 1.6 + 3.3 * p.CB) + w16 / 120.0 +
                      (planes || lossless_pair_filters_first(p) ? 0.0 : p.CB * std::min(p.Kp, 256) / 1500.0);
-    const double split = mode != WG_LOSSLESS ? (planes ? 8.6 + 2.9 * b + W / 24.0 : 7.4 + 3.0 * b + W / 29.0)
+    const double split = mode != WG_LOSSLESS ? (planes ? 8.6 + 2.9 * b + W / 24.0 : (p.CB <= 3 ? 7.9 : 7.4) + 3.0 * b + W / 29.0)
                        : planes && !pairs    ? 5.1 + 3.7 * b + W / 68.0 + 7.1 * outputs
                        : planes              ? 4.0 + 4.4 * b + W / 53.0 + 6.4 * outputs
                        : pairs               ? 4.3 + 3.3 * b + W / 50.0

@@ -258,7 +258,8 @@ def test_a_forced_form_runs_in_one_kernel(lib, hook, value, modes):
 @pytest.mark.parametrize("N,C,K,HW,splits", [
     # channel blocks dealt to this many workgroups (lossless, scaled); 1: one kernel
     (1, 512, 512, 14, (8, 8)), (1, 512, 512, 28, (4, 1)), (4, 512, 512, 14, (4, 1)), (1, 256, 256, 56, (1, 1)), (2, 256, 512, 28, (1, 1)),
-    (1, 256, 512, 28, (4, 1)), (4, 820, 250, 14, (7, 7)), (2, 324, 512, 28, (1, 1)), (1, 128, 64, 14, (1, 1)), (8, 512, 512, 28, (1, 1))])
+    (1, 256, 512, 28, (4, 1)), (4, 820, 250, 14, (7, 7)), (2, 324, 512, 28, (1, 1)), (1, 128, 64, 14, (1, 1)), (8, 512, 512, 28, (1, 1)),
+    (1, 176, 64, 8, (3, 1))])
 def test_which_layers_deal_their_channel_blocks_to_several_workgroups(lib, N, C, K, HW, splits):
     """The scratch memory that the extension asks for holds the splits' partial sums: 16 outputs (lossless) or 36 channel sums
     (scaled) per tile and filter, tiles padded to 16 and filters to 64."""
