@@ -539,8 +539,12 @@ Plan plan_conv(const Problem& p, int layout, int mode, bool is_unsigned, size_t 
         return true;
     };
     if (layout == WG_NCHW && !is_unsigned && plane_patches_hold(p)) {
-        // the split kernels read channel-major patches as well, at 1.1 us more per further block, while a copy is a launch
-        plan.planes = (blocks <= 2 && split(true, true, mode == WG_LOSSLESS && pair_reads_planes(p))) || (mode == WG_LOSSLESS && (lossless_variant() == 1 || (!hooked && pair_reads_planes(p))));
+        // The split kernels read channel-major patches as well, at 1.1 us more per further block, while a copy is a launch: with up to two blocks
+        // per workgroup what would be split after a copy is split without (us, split after a copy / without: 224 -> 32 at 82x98, N = 3, lossless,
+        // 25.2 / 20.1; 208 -> 48 at 16x16, N = 59, 23.7 / 20.3; 196 -> 92 at 63x63, N = 2, 19.9 / 19.2).
+        const bool pairs = mode == WG_LOSSLESS && pair_reads_planes(p);
+        plan.planes = (blocks <= 2 && (split(true, true, pairs) || (!pairs && split(true, false, false)))) ||
+                      (mode == WG_LOSSLESS && (lossless_variant() == 1 || (!hooked && pairs)));
         if (plan.planes) return plan;
     }
     if (layout != WG_NHWC || p.C % 4 != 0) {
