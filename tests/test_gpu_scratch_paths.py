@@ -164,13 +164,29 @@ def test_calls_run_without_the_memory_they_would_like_and_outputs_without_memory
         assert torch.equal(out, want)
 
 
-@pytest.mark.parametrize("mode", [wg.LOSSLESS, wg.SCALED])
-@pytest.mark.parametrize("shape", [(1, 320, 192, 40, 64), (1, 320, 160, 44, 64), (1, 260, 250, 52, 56), (1, 600, 20, 49, 66)])
-def test_split_channels_in_either_order_of_the_grid(shape, mode):
-    """Ten, eleven and more tile blocks (up to ten, lossless mode deals out the splits first, above that the tile blocks), two
-    channel blocks per workgroup with one in the last split, odd numbers of 32-filter blocks, C no multiple of 16 (4-byte loads)."""
-    x, g, xd, gd = _inputs(shape, wg.NHWC)
+@pytest.mark.parametrize("mode, layout, shape, splits", [
+    # two to three channel blocks per workgroup, fewer in the last split.  Lossless mode, up to ten tile blocks: splits are dealt out first
+    (wg.LOSSLESS, wg.NHWC, (1, 320, 192, 40, 64), 3), (wg.LOSSLESS, wg.NHWC, (1, 516, 250, 38, 40), 3),   # the second: C no multiple of 16
+    (wg.LOSSLESS, wg.NHWC, (1, 320, 160, 44, 64), 3),                                                     # eleven tile blocks: those first
+    # the same with 16 filters per workgroup, its waves sharing the entries in quarters
+    (wg.LOSSLESS, wg.NHWC, (1, 580, 75, 40, 64), 5), (wg.LOSSLESS, wg.NHWC, (1, 324, 100, 52, 56), 3),
+    (wg.LOSSLESS, wg.NHWC, (2, 512, 9, 56, 112), 4), (wg.LOSSLESS, wg.NHWC, (1, 320, 48, 80, 84), 3),
+    (wg.LOSSLESS, wg.NCHW, (1, 512, 16, 84, 112), 4),
+    (wg.SCALED, wg.NHWC, (1, 640, 60, 60, 64), 5),
+    # one block per workgroup, C no multiple of 16
+    (wg.LOSSLESS, wg.NHWC, (1, 600, 20, 49, 66), 10), (wg.SCALED, wg.NHWC, (1, 600, 20, 49, 66), 10), (wg.SCALED, wg.NHWC, (1, 580, 130, 32, 40), 10)])
+def test_split_channels_in_either_order_of_the_grid(mode, layout, shape, splits):
+    N, C, K, H, W = shape
+    wanted = wg.load_library()._ZN2wg20conv2d_scratch_bytesEiiiiiiii
+    wanted.restype, wanted.argtypes = ctypes.c_size_t, [ctypes.c_int] * 8
+    tiles = (N * ((H + 3) // 4) * ((W + 3) // 4) + 15) // 16 * 16
+    sums = (16 if mode == wg.LOSSLESS else 36) * tiles * ((K + 63) // 64 * 64) * 4
+    assert wanted(N, C, H, W, K, layout, mode, 0) == splits * sums   # as many splits as this shape is here for, and no copy
+    x, g, xd, gd = _inputs(shape, layout)
     want = oracle.direct_conv2d(x, g) if mode == wg.LOSSLESS else oracle.winograd_conv2d(x, g, oracle.SCALED, 127)[0]
-    packed = wg.winograd_filter_transform(gd, wg.NHWC, mode)
+    packed = wg.winograd_filter_transform(gd, layout, mode)
     for _ in range(2):
-        assert np.array_equal(_nchw(wg.winograd_conv2d_int8(xd, packed, wg.NHWC), wg.NHWC), want)
+        assert np.array_equal(_nchw(wg.winograd_conv2d_int8(xd, packed, layout), layout), want)
+    for pool in (False, True) if (H | W) % 2 == 0 else (False,):
+        got = wg.winograd_conv2d_int8_requant(xd, packed, 10, True, pool, layout)
+        assert np.array_equal(_nchw(got, layout), oracle.requant_relu_pool(want, 10, True, pool)), pool
