@@ -481,7 +481,7 @@ struct Plan {
 // other.  Dealing the blocks to several workgroups takes a second kernel that adds the splits and finishes.  CB channel blocks in
 // one workgroup against b in each of W, whose partial sums are written and read (36 per tile and filter in scaled mode, 16
 // otherwise).  Fitted to layers of 128 .. 896 channels and K = 16 .. 512 filters that fill at most half the chip, with filters
-// that are not in the L2, as in a network (us; 330 layers in scaled mode, 220 in lossless mode, off by 3 - 8 % on average):
+// that are not in the L2, as in a network (us; 248 layers in scaled mode, 226 in lossless mode, off by 4 - 8 % on average):
 //   lossless: 4.3 + 3.3 b + W / 50 split; one kernel, which is the limb-pair form with 16 filters per workgroup there (lossless_conv.hip),
 //             2.1 + 2.6 CB + W16 / 120 for W16 workgroups with 16-byte pieces, 1.6 + 3.3 CB with 4-byte loads, both + CB min(K, 256) / 1500 for the
 //             filters that come from memory, unless filter blocks are dealt out first (split / one kernel: 256 -> 256 at 56x56, N = 1, 14.9, 13.8;
@@ -518,7 +518,8 @@ bool split_pays(int mode, const Problem& p, int b, int W, bool pieces, bool plan
 // Channel-major activations in lossless mode, not split: the limb-pair kernel with patches turned on their way into LDS, while
 // its grid is one round of the compute units, against a copy and the forms of run_roles (fifty drawn layers, us: one
 // channel block 7.9 - 8.9 against 10.1 - 12.4; two 12.3 - 13.5 / 12.8 - 15.4; three 16.9 - 18.7 / 15.4 - 23.5, seven 35 / 30 - 41; two
-// rounds, one block 15.4 - 16.7 / 14.4 - 18.5).
+// rounds, one block 15.4 - 16.7 / 14.4 - 18.5).  Those are times of the halves; with quarters, where the grid allows them, three blocks that are
+// not split would take 0.66 - 1.05 of what runs them (twelve layers, 0.89 on average), four and five 0.97 - 1.16 (eight).
 bool pair_reads_planes(const Problem& p) {
     return p.CB <= 2 && (long long)ceil_div(p.T, kFusedTiles) * ceil_div(p.K, kFusedFilters) <= compute_units();
 }

@@ -29,7 +29,7 @@
 // Several channel blocks: the output transform is linear, so every block's rows of M are reduced
 // into the same 16 outputs.
 // Small grids (in_quarters): 16 filters per workgroup, a wave = filter group of 8 x a quarter of the entries, 28 matrix-core
-// instructions on average instead of 56.
+// instructions on average instead of 56.  Such layers of several channel blocks run here, too (lossless_pair_takes).
 #include <atomic>
 
 #include "kernel_common.h"
@@ -506,10 +506,11 @@ struct RawPatch {
 constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2;
 
 // Where a workgroup works.  Not split: the grid's own numbers, all channel blocks.  Split channels: a grid of ceil(T/16) x ceil(K/32) x
-// splits.  Every tile block reads all filters, so in lossless mode the splits are dealt out first and the tile blocks last, which
-// brings the workgroups that read the same fragments to the same XCD wherever splits x filter blocks is a multiple of eight: 512 -> 512 at 28x28,
-// N = 1, 18.0 -> 15.0 us, 592 -> 240 at 33x33 18.4 -> 15.3.  With more than ten of them side by side that is the slower order (256 -> 256 at
-// 56x56 14.9 -> 15.5, 576 -> 48 at 63x65 14.1 -> 14.7), as it is in scaled mode, whose filters are half as large (640 -> 128 at 48x48 19.4 -> 20.9).
+// splits.  Every tile block reads all filters, so in lossless mode the splits are dealt out first and the tile blocks last, which brings more of the
+// workgroups that read the same fragments to one XCD, whatever their numbers: 512 -> 512 at 28x28, N = 1, 18.0 -> 15.0 us, 592 -> 240 at
+// 33x33 18.4 -> 15.3; of the time of the other order, up to ten tile blocks, 0.96 with 32 filters per workgroup (76 layers, 0.80 - 1.04), 0.99 with 16
+// (192).  With more of them side by side it is level or behind (152 layers, 1.01 and 1.00; 0.93 - 1.14), as in scaled mode, whose filters
+// are half as large (640 -> 128 at 48x48 19.4 -> 20.9).
 struct SplitPlace {
     int tile_blocks, tile_block, filter_block, split, first, end;   // channel blocks first .. end - 1
 };

@@ -3,8 +3,8 @@
 // lossless mode: 16 x outputs.  Only layers with few tiles come here (without the split they would fill less than half the
 // chip), so the kernels are bound by the latency of their reads, not by their amount: all of a thread's reads of a split are
 // in flight together.
-// One image, lossless, int8 out, both kernels together: 512 -> 512 at 14x14 28 -> 12 us (16 workgroups of eight channel
-// blocks before, 128 of one now), at 28x28 27 -> 19 us.
+// One image, int8 out, filters out of the L2s, one kernel against both of these together: 512 -> 512 at 14x14 lossless 21.9 / 11.5 us (16
+// workgroups of eight channel blocks, 128 of one), scaled 18.6 / 15.0; at 28x28 lossless 22.5 / 15.6.
 #include "kernel_common.h"
 #include "output_transform_core.h"
 #include "roles_conv.h"

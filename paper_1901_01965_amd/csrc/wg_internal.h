@@ -150,9 +150,9 @@ struct ReverseScale {
     }
 };
 
-// Layers with at most kNarrowChannels input channels (a network's first layer) are served by a
-// kernel that multiplies on the vector ALU; for them the blob also carries the Winograd-domain
-// filters (after the scaling, in scaled mode) as 16-bit values, four channel slots per value:
+// Layers with at most kNarrowChannels input channels (a network's first layer) have kernels of their own, which multiply whole
+// Winograd-domain numbers, on the matrix cores in half precision or, few tiles, on the vector ALU (narrow_conv.hip); for them the blob also
+// carries the Winograd-domain filters (after the scaling, in scaled mode) as 16-bit values, four channel slots per value:
 // the 36 real numbers of the 26 free entries in the order 16 real entries, then (Re, Im) of
 // each complex entry.
 constexpr int kNarrowChannels = 4;
