@@ -982,8 +982,8 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
 }
 // Quarters of the entries and 16 filters per workgroup where their grid is still one round of the compute units: products and
 // store take half as long, while the patches are loaded and transformed twice as often, on compute units that had nothing to do
-// (us, halves / quarters: 16 -> 16 at 16x16, channel-major, 7.5 / 6.5; 100 -> 75 at 37x53, N = 4, channel-major, 12.3 / 10.75).  Against the
-// role-specialised kernel, 510 layers of up to one round: 0.65 - 1.02 (see lossless_pair_filters_first for what it would be with many filters).
+// (us, halves / quarters: 16 -> 16 at 16x16, channel-major, 7.5 / 6.5; 100 -> 75 at 37x53, N = 4, channel-major, 12.3 / 10.75).  Several
+// channel blocks, against the role-specialised kernel or a split that ran them before, 510 layers: 0.65 - 1.03 of the time, 0.87 on average.
 bool in_quarters(const Problem& p, int splits) {
     return (long long)ceil_div(p.T, kTileBlock) * ceil_div(p.K, Stage<4>::kFilters) * splits <= compute_units();
 }
