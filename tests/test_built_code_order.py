@@ -54,6 +54,8 @@ def test_a_listing_with_a_fragment_ahead_is_found():
 def test_patches_are_requested_ahead_of_the_fragments_that_the_wait_counts(tmp_path):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no disassembler")
+    if not os.path.exists(build.LIB_PATH):
+        build.build()
     library = shutil.copy(build.LIB_PATH, tmp_path)
     subprocess.run([OBJDUMP, "--offloading", library], cwd=tmp_path, check=True, stdout=subprocess.DEVNULL)
     checked = 0
