@@ -374,7 +374,8 @@ int winograd_debug_scaled_variant(int variant);
 /* The same switch for the streaming form of that kernel (a workgroup walks over many tile blocks; chosen for large
    layers), which also exists with 64 filters per workgroup (each product wave owns every entry of 16 filters; lossless
    mode, or one channel block).  0: the library's choice, 1: the 64-filter form wherever a layer streams and the form
-   applies, 2: never, 3: always the form with eight product waves and 64 filters. */
+   applies, 2: never, 3: always the form with eight product waves and 64 filters, 4: as 1, in lossless mode and with one channel
+   block with eight product waves of 8 filters each. */
 int winograd_debug_stream_variant(int variant);
 /* The same switch for first layers (channels-last, C <= 4).  0: the library's choice, 1: products on the matrix cores wherever the
    outputs can be stored four filters at a time, 2: never. */

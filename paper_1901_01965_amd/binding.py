@@ -202,7 +202,7 @@ def lossless_variant(v):
 def stream_variant(v):
     """Test hook: 0 = library's choice of the streaming kernel's form, 1 = 64 filters per workgroup wherever a layer
     streams and the form applies (lossless mode, or one channel block), 2 = never, 3 = always the form with eight product waves
-    and 64 filters."""
+    and 64 filters, 4 = as 1, in lossless mode and with one channel block with eight product waves of 8 filters each."""
     _check(load_library().winograd_debug_stream_variant(int(v)), "winograd_debug_stream_variant")
 
 

@@ -240,7 +240,7 @@ int winograd_debug_scaled_variant(int variant) {
 }
 
 int winograd_debug_stream_variant(int variant) {
-    if (variant < 0 || variant > 3) return WG_EINVAL;
+    if (variant < 0 || variant > 4) return WG_EINVAL;
     set_stream_variant(variant);
     return WG_OK;
 }

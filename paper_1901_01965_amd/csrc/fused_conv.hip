@@ -582,6 +582,20 @@ size_t fused_conv_scratch_wanted(const Problem& p, int layout, int mode, bool is
 
 namespace {
 
+// The streaming kernel's 64-filter form without halves of the entries: in lossless mode and with one channel block four product waves with
+// 16 filters each or eight with 8 (kStreamPairs).  The latter's chain per tile block is half as long, but they read the activation
+// planes twice as often; they are ahead where a workgroup has few tile blocks and the store takes long.  us, four waves / eight, 64 -> 64
+// at 56x56, one tile block per workgroup (N = 16): int8 out 10.4 / 9.4, pooled 9.9 / 8.9, channel-major int32 18.3 / 15.9, int32 11.1 / 10.8,
+// uint8 11.2 / 11.0; two (N = 32) 16.6 / 16.0, 15.6 / 15.0, 27.5 / 26.6, 18.1 / 18.6, 17.6 / 17.8; three (N = 48) 22.6 / 21.8, 20.9 / 20.4, 35.7 / 35.5,
+// 23.5 / 24.3, 23.7 / 24.7; four (N = 64, int8 out) 26.0 / 26.6.
+StreamForm whole_form(const RolesCall& c, int mode) {
+    const int variant = g_stream_variant.load(std::memory_order_relaxed);
+    if (mode != WG_LOSSLESS || c.p.CB != 1 || variant == 1) return kStreamWhole;
+    const int tile_blocks = ceil_div(c.p.T, kFusedTiles), each = ceil_div(tile_blocks, stream_workgroups(tile_blocks, ceil_div(c.p.K, 2 * kFusedFilters)));
+    const bool planes32 = c.layout == WG_NCHW && c.q8.out == nullptr;
+    return variant == 4 || each <= (c.q8.out != nullptr ? 3 : planes32 ? 2 : 1) ? kStreamPairs : kStreamWhole;
+}
+
 // Runs c through one of the role-specialised forms, which read channels-last activations with C % 4 = 0.  False: another
 // kernel is the better one (it is left to the caller).
 bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial, hipStream_t s, hipError_t& status) {
@@ -639,7 +653,7 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
             const double pair_cost = by_bytes ? 0.0 : 1.0 + 5.9 * (double)((w32 + cus - 1) / cus);
             const double other = scaled ? (r64 == 1 ? 9.0 : 1e9) : pairs ? pair_cost : 1e9;
             if (other < halves && other < whole) status = scaled ? launch_roles(c, mode, true, s) : launch_lossless_pair_conv(c.x, c.blob, c.y, p, c.layout, c.q8, s);
-            else                                 status = launch_stream(c, mode, halves < whole ? kStreamHalves : kStreamWhole, s);
+            else                                 status = launch_stream(c, mode, halves < whole ? kStreamHalves : whole_form(c, mode), s);
             return true;
         }
     }
@@ -691,8 +705,8 @@ bool run_roles(const RolesCall& c, int mode, const Plan& plan, int32_t* partial,
         // the 64-filter form: lossless mode, or one channel block (see the kernel), unless the padding to 64 filters
         // would add a 32-filter block of nothing
         const bool wide = !narrow_one_round && (mode == WG_LOSSLESS || p.CB == 1) &&
-                          (stream_variant == 1 || (stream_variant == 0 && whole64));
-        status = launch_stream(c, mode, wide ? kStreamWhole : kStreamHalves, s);
+                          (stream_variant == 1 || stream_variant == 4 || (stream_variant == 0 && whole64));
+        status = launch_stream(c, mode, wide ? whole_form(c, mode) : kStreamHalves, s);
         return true;
     }
     // Transform and products on separate waves: with several channel blocks and no more 32-filter workgroups than compute

@@ -35,8 +35,8 @@ inline size_t split_partial_bytes(const Problem& p, int mode, int splits) {
     return (size_t)splits * (mode == WG_LOSSLESS ? 16 : kAccPlanes) * 16 * ceil_div(p.T, 16) * p.Kp * sizeof(int32_t);
 }
 // A workgroup walks over many tile blocks of one filter block (see stream_kernel.h for the forms): 32 filters or, kStreamWhole
-// (lossless mode, or one channel block) and kStreamEight, 64.
-enum StreamForm { kStreamHalves, kStreamWhole, kStreamEight };
+// (lossless mode, or one channel block), kStreamEight and kStreamPairs (lossless mode and one channel block), 64.
+enum StreamForm { kStreamHalves, kStreamWhole, kStreamEight, kStreamPairs };
 hipError_t launch_stream_lossless(const RolesCall& c, StreamForm form, hipStream_t s);
 hipError_t launch_stream_scaled(const RolesCall& c, StreamForm form, hipStream_t s);
 inline hipError_t launch_stream(const RolesCall& c, int mode, StreamForm form, hipStream_t s) {

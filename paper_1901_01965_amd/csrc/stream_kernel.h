@@ -1,6 +1,7 @@
 // fused_conv_stream_kernel: the role-specialised convolution as a stream over tile blocks.  See fused_conv.hip for the
 // method and the dispatch.
 #pragma once
+#include "pair_products.h"
 #include "product_core.h"
 #include "roles_conv.h"
 
@@ -36,7 +37,8 @@ struct RoleBarrier {
 // u - 2; after the last channel block of a tile block, D_u (every product wave has finished reading the planes) and S_u (the
 // outputs are staged).  kStreamEight: the product waves meet at a barrier of their own instead of D_u and again between the two
 // stagings, and U_{u+2} (there is a U_{U+1}) stands for S_u, so that the transform waves wait for neither; with four product
-// waves, whose chain is the longer one, that barrier's polling cost more than it gave (2-3 %).
+// waves, whose chain is the longer one, that barrier's polling cost more than it gave (2-3 %).  kStreamPairs: likewise, and the product
+// waves store what they staged themselves, before U_{u+2}.
 // The staged outputs of unit u - 2 and the planes of unit u share a buffer, and the four transform waves both read the former
 // (each thread reads rows that other waves' plane writes cover) and write the latter: between the two they meet at a barrier
 // of their own.
@@ -56,6 +58,13 @@ struct RoleBarrier {
 //                   tensors and with int8 outputs, one or two spilled with uint8, 6 - 12 with channel-major int32 outputs, whose
 //                   32 plane offsets also spill 82 - 237 scalar registers (in every form).  It is the fastest form where
 //                   fused_conv.hip chooses it, which it does not for those outputs.
+//   kStreamPairs:   64 filters, lossless mode, one channel block; eight product waves, each every entry of 8 filters by way of the
+//                   limb-pair operand (pair_products.h), whose outputs take half the registers: enough with twelve waves.  Half the chain per
+//                   tile block of kStreamWhole, no halves to add, and all eight waves store: ahead where a workgroup has few tile
+//                   blocks, so that this chain is not hidden behind others (see fused_conv.hip).  In a long stream twice as many waves read the
+//                   activation planes (576 KB a tile block), and with the transform left out the products alone take 5.1 of 7.4 us a tile block:
+//                   56x56x64 N = 256 102 us, int8 out 84, with kStreamWhole 94.5 and 80; with the stores left to the transform
+//                   waves 98 and 81, and nothing gained in short ones.
 // What bounds kStreamWhole (56x56x64, N = 256, clocks per tile block of 64 filters, lossless / scaled): the product wave's chain,
 // 13,500 / 12,400 = products with their joins, reverse scaling and output transform 10,700 / 9,800 + staging 880 + from
 // there to the next unit's barrier 800 / 1,000 (lossless mode clears the outputs in it, 64 instructions; what the rest waits for, and
@@ -64,7 +73,8 @@ struct RoleBarrier {
 // is the older one and goes first, and their vector instructions together occupy the SIMD for 1,764 x 4.4 + 224 x 8 = 9,600
 // (scaled 1,831 x 4.4 + 112 x 8 = 9,000) of those clocks.
 template <int FORM> constexpr int stream_filters() { return FORM == kStreamHalves ? 32 : 64; }
-template <int FORM> constexpr int stream_product_waves() { return FORM == kStreamEight ? 8 : 4; }
+template <int FORM> constexpr bool twelve_waves() { return FORM == kStreamEight || FORM == kStreamPairs; }
+template <int FORM> constexpr int stream_product_waves() { return twelve_waves<FORM>() ? 8 : 4; }
 
 template <int LAYOUT, int MODE, bool Q8, int FORM, class ENC>
 __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused_conv_stream_kernel(
@@ -74,15 +84,15 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
     const GridOrder order = WG_TAKE_ORDER;
     const int tile_blocks = (p.T + kFusedTiles - 1) / kFusedTiles;
     constexpr int PW = stream_product_waves<FORM>();
-    constexpr bool OWN_BARRIER = FORM == kStreamEight;
+    constexpr bool OWN_BARRIER = twelve_waves<FORM>();
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
-    const int lane = threadIdx.x & 63, wave8 = FORM == kStreamEight ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave8 = twelve_waves<FORM>() ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const bool transforms = wave8 < 4;
     const int wave = wave8 & 3;   // within the role
     // Twelve waves have no registers to spare: what follows from the lane is formed where it is needed.  Spilled, it came back behind
     // the loads in flight, in every unit: scaled, 128 -> 128 at 112x112 N = 16, formed 66.4 us, spilled 68.9; 40 mixed
     // layers 1.2 % faster.  (With eight waves, nothing is spilled either way: 16 -> 16 lossless layers lost 11 % to the extra work.)
-    auto my_lane = [&] { if constexpr (FORM == kStreamEight) return lane_again(); else return lane; };
+    auto my_lane = [&] { if constexpr (twelve_waves<FORM>()) return lane_again(); else return lane; };
     int bx, by;
     order.place(bx, by);
     const int k0 = by * stream_filters<FORM>();
@@ -108,7 +118,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
 #endif
 
     if (transforms) {
-        OperandSplitter<MODE == WG_SCALED ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
+        OperandSplitter<MODE == WG_SCALED || FORM == kStreamPairs ? kSplitByteLimbs : kSplitTwoLimb, LdsPlaneSink> out;
         auto slot_of = [&](int l) {   // a lane's four bytes of an operand plane
             const int cq = PatchLoader::quad_of(l);
             return lds + lds_slot(cq >> 2, PatchLoader::tile_of(wave, l)) * 16 + (cq & 3) * 4;
@@ -127,9 +137,9 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
         // writes out what is staged in `buffer` for tile block tb
         auto flush = [&](int tb, int buffer) {
             StoreContext sc;
-            sc.lds = lds + buffer * kLdsBytes; sc.lane = my_lane(); sc.tid = FORM == kStreamEight ? wave * 64 + sc.lane : threadIdx.x & 255; sc.rnd = rnd; sc.y = y;
+            sc.lds = lds + buffer * kLdsBytes; sc.lane = my_lane(); sc.tid = twelve_waves<FORM>() ? wave * 64 + sc.lane : threadIdx.x & 255; sc.rnd = rnd; sc.y = y;
             // (opaque: what follows from these is formed here, not ahead of the loop: registers are scarce)
-            if constexpr (FORM == kStreamEight || LAYOUT == WG_NCHW) asm volatile("" : "+v"(sc.tid), "+v"(sc.lane));
+            if constexpr (twelve_waves<FORM>() || LAYOUT == WG_NCHW) asm volatile("" : "+v"(sc.tid), "+v"(sc.lane));
             locate_tile<LAYOUT>(sc, p, tb * kFusedTiles);
             if constexpr (FORM != kStreamHalves) {   // one finished copy per 32 filters
                 store_staged<LAYOUT, Q8, false>(sc, p, q8, k0);
@@ -160,7 +170,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
                 __builtin_amdgcn_s_barrier();
             }
             WG_SPENT(0, mark);   // barrier U
-            if (last2) {   // staged in the buffer of unit u - 2, which unit u is about to overwrite
+            if (FORM != kStreamPairs && last2) {   // staged in the buffer of unit u - 2, which unit u is about to overwrite
                 flush(tb2, u & 1);
                 among_us.sync(lane);   // every transform wave has read its share before any of them writes planes
             }
@@ -168,7 +178,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             const int tb = bx + jb * order.across;
             const bool last0 = u < units && cb == p.CB - 1;
             if (u < units) {
-                out.sink.base = (FORM == kStreamEight ? slot_of(my_lane()) : slot) + (u & 1) * kLdsBytes;
+                out.sink.base = (twelve_waves<FORM>() ? slot_of(my_lane()) : slot) + (u & 1) * kLdsBytes;
 #ifdef WG_TIMESTAMPS
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 WG_SPENT(2, mark);   // wait for the patch
@@ -184,8 +194,14 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
                 place_loop(std::integral_constant<bool, FORM != kStreamWhole || MODE != WG_SCALED>{});
                 bias.apply(loader.patch);
                 WG_SPENT(5, mark);   // offsets
-                if (more) transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc, NextColumns{loader, xbuf, cb});
-                else      transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc);
+                if constexpr (FORM == kStreamPairs) {   // one copy of the transform (two spill): what comes after the last unit is asked for in a buffer of nothing
+                    const __amdgpu_buffer_rsrc_t next = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(x), 0, more ? p.N * p.H * p.W * p.C : 0, kRawBufferWord3);
+                    transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc, NextColumns{loader, next, cb});
+                } else if (more) {
+                    transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc, NextColumns{loader, xbuf, cb});
+                } else {
+                    transform_patch<typename PatchBias<ENC>::Bytes>(loader.patch, out, enc);
+                }
             }
             WG_SPENT(3, mark);   // transform
             if (!OWN_BARRIER && last1) {   // D_{u-1}, S_{u-1}
@@ -196,7 +212,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             last2 = last1; tb2 = tb1;
             last1 = last0; tb1 = tb;
         }
-        if (units > 0) {   // the last unit ends a tile block, staged in its buffer
+        if (FORM != kStreamPairs && units > 0) {   // the last unit ends a tile block, staged in its buffer
             if (OWN_BARRIER) {   // U_{U+1}
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
@@ -246,7 +262,37 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
     };
-    if constexpr (FORM == kStreamWhole) {
+    if constexpr (FORM == kStreamPairs) {
+        // one channel block: a unit is a tile block; `planes_off` is that of the limb-pair planes
+        constexpr int RING = 6;
+        using All = pairs::WholeProducts<RING>;
+        const __amdgpu_buffer_rsrc_t filters = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<int8_t*>(reinterpret_cast<const int8_t*>(blob + planes_off) + filter_pair_offset(0, 0, k0 + kPairFilters * pw, 0, 0, p.Kp)), 0,
+            kPairValues * kFilterFragBytes, kRawBufferWord3);
+        v4i ring[RING];
+        const uint32_t lane16 = fragment_lane(lane);
+        static_for<RING>([&](auto F) { ring[F] = All::template fragment<F>(filters, lane16); });
+        for (int u = 0; u < units; ++u) {
+            published();
+            place_loop(std::false_type{});
+            pairs::v2i Y[16];
+            // (the next unit's first fragments travel while this one is staged)
+            All::run(lds + (u & 1) * kLdsBytes + fragment_slot(), ring, Y, [&](auto F) { ring[F % RING] = All::template fragment<(F + RING < All::NF ? F + RING : F % RING)>(filters, lane16); });
+            among_us.sync(lane);   // every product wave is done with the planes
+            // lane = tile (lane & 15) x filters 8 pw + 2 (lane / 16), + 1
+            const int l = lane_here();
+            int* const to = reinterpret_cast<int*>(lds + (u & 1) * kLdsBytes) + (pw >> 2) * kStageHalf + (l & 15) * kStageRow + kPairFilters * (pw & 3) + 2 * (l >> 4);
+#pragma unroll
+            for (int o = 0; o < 16; ++o) *reinterpret_cast<pairs::v2i*>(to + o * 16 * kStageRow) = Y[o];
+            among_us.sync(lane);   // staged
+            StoreContext sc;
+            sc.lds = lds + (u & 1) * kLdsBytes + (pw >> 2) * kStageHalf * 4;
+            sc.lane = lane_again(); sc.tid = (pw & 3) * 64 + sc.lane; sc.rnd = rnd; sc.y = y;
+            asm volatile("" : "+v"(sc.tid));
+            locate_tile<LAYOUT>(sc, p, (bx + u * order.across) * kFusedTiles);
+            store_staged<LAYOUT, Q8, false>(sc, p, q8, k0 + (pw >> 2) * kFusedFilters);
+        }
+    } else if constexpr (FORM == kStreamWhole) {
         // filter ring: lossless mode has twice the fragments per entry and the registers for twelve in flight
         LeanProducts<MODE, kAllRows, MODE == WG_SCALED ? 8 : 12> all;
         v4i Y[16];
@@ -343,7 +389,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             stream(phase);
         }
     }
-    if (OWN_BARRIER && units > 0) published();   // U_{U+1}
+    if (FORM == kStreamEight && units > 0) published();   // U_{U+1}
 #ifdef WG_TIMESTAMPS
     report();
 #endif
@@ -352,7 +398,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
 template <int LAYOUT, int MODE, bool Q8, int FORM, class ENC>
 hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
     // two plane buffers, the roles' barrier counters, the parked reverse-scaling factors
-    constexpr int lds_bytes = 2 * kLdsBytes + 64 + (FORM == kStreamWhole ? 4 * ParkedScales<kAllRows>::kBytes : stream_product_waves<FORM>() * kParkedScaleBytes);
+    constexpr int lds_bytes = 2 * kLdsBytes + 64 + (FORM == kStreamPairs ? 0 : FORM == kStreamWhole ? 4 * ParkedScales<kAllRows>::kBytes : stream_product_waves<FORM>() * kParkedScaleBytes);
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
     static LdsLimitOnce lds_limit;   // per template instance
     if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC>), lds_bytes)) return e;
@@ -360,7 +406,7 @@ hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
     const dim3 grid(stream_workgroups(tile_blocks, filter_blocks), filter_blocks);
     const GridOrder order(grid, workgroup_order(c.p, MODE, stream_filters<FORM>()));
     fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC><<<grid, 64 * (4 + stream_product_waves<FORM>()), lds_bytes, s>>>(
-        c.x, WG_GEOMETRY(c.p), WG_ORDER(order), c.blob, c.bl.table_off, c.bl.planes_off, c.y, c.p, c.q8, enc);
+        c.x, WG_GEOMETRY(c.p), WG_ORDER(order), c.blob, c.bl.table_off, FORM == kStreamPairs ? c.bl.pairs_off : c.bl.planes_off, c.y, c.p, c.q8, enc);
     return hipGetLastError();
 }
 
@@ -368,6 +414,8 @@ hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
 template <int MODE>
 hipError_t launch_stream_mode(const RolesCall& c, StreamForm which, hipStream_t s) {
     auto form = [&](auto L, auto Q8, const auto& enc) {
+        if constexpr (MODE == WG_LOSSLESS)
+            if (which == kStreamPairs) return launch_stream<L, MODE, Q8, kStreamPairs>(c, enc, s);
         if (which == kStreamEight) return launch_stream<L, MODE, Q8, kStreamEight>(c, enc, s);
         if (which == kStreamWhole) return launch_stream<L, MODE, Q8, kStreamWhole>(c, enc, s);
         return launch_stream<L, MODE, Q8, kStreamHalves>(c, enc, s);
