@@ -147,7 +147,7 @@ static_assert(2 * kActPlaneBuffer <= kLdsBytes && act_lds_bytes<8>() <= 160 * 10
 
 // grid (ceil(T/16), ceil(K / (8 PW))), 64 (4 + PW) threads: the roles of fused_conv_roles_kernel (roles_kernel.h): waves 0-3 transform one
 // channel block ahead, the others multiply; product wave pw owns filter block pw % (PW / 2) and half pw / (PW / 2) of the entries.
-template <int LAYOUT, int PW, bool NARROW>
+template <int LAYOUT, int OUT, int PW, bool NARROW>
 __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS,
                                                                          WG_ORDER_PARAMS, const uint8_t* __restrict__ blob,
                                                                          size_t table_off, size_t planes_off, int32_t* __restrict__ y,
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void act_scaled_roles_kernel(const i
     __syncthreads();   // the operand planes are dead
     stage_outputs(sc.lds, lane, half, kblock, Y);
     __syncthreads();
-    store_staged<LAYOUT, false, true>(sc, p, Int8Epilogue{}, k0 + group * kFusedFilters);
+    store_staged<LAYOUT, OUT, true>(sc, p, Int8Epilogue{}, k0 + group * kFusedFilters);
 }
 
 }  // namespace
@@ -270,17 +270,21 @@ hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, 
     // costs more: a round of 32 takes about four fifths of one of 64 (both kernels together, us, 64 / 32 filters: three rounds against
     // four, 480 -> 80 at 59x79, N = 14, 108.8 / 126.3; six against eight, 79 -> 80 at 27x34, N = 169, 106.2 / 114.8; two each, 59 -> 32
     // at 47x47, N = 57, 49.2 / 43.2; 350 drawn layers 0.01 % behind the better one on average, with the line at 1.34 0.08).
-    auto go = [&](auto L, auto W, auto NARROW) -> hipError_t {
+    auto launch = [&](auto L, auto OUT, auto W, auto NARROW) -> hipError_t {
         constexpr int PW = W;
         static LdsLimitOnce lds_limit;   // per instance
-        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, PW, NARROW>), act_lds_bytes<PW>())) return e;
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&act_scaled_roles_kernel<L, OUT, PW, NARROW>), act_lds_bytes<PW>())) return e;
         const dim3 grid(ceil_div(c.p.T, kFusedTiles), ceil_div(c.p.K, 8 * PW));
         const GridOrder order(grid, workgroup_order(c.p, WG_SCALED, 8 * PW));
-        act_scaled_roles_kernel<L, PW, NARROW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(
+        act_scaled_roles_kernel<L, OUT, PW, NARROW><<<grid, 64 * (4 + PW), act_lds_bytes<PW>(), s>>>(
             c.x, WG_GEOMETRY(c.p), WG_ORDER(order), c.blob, c.bl.table_off, c.bl.planes_off, c.y, factors, c.p);
         return hipGetLastError();
     };
     using std::integral_constant;
+    const bool through = int32_out(c.p, c.layout) == kOutThrough;
+    auto go = [&](auto L, auto W, auto NARROW) {
+        return through ? launch(L, integral_constant<int, kOutThrough>{}, W, NARROW) : launch(L, integral_constant<int, kOutInt32>{}, W, NARROW);
+    };
     const int tile_blocks = ceil_div(c.p.T, kFusedTiles), cus = compute_units();
     auto rounds = [&](int filters) { return ((long long)tile_blocks * ceil_div(c.p.K, filters) + cus - 1) / cus; };
     const bool wide = rounds(32) > 1 && 4 * rounds(32) >= 5 * rounds(64);

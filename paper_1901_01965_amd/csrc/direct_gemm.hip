@@ -42,9 +42,9 @@ constexpr int kStagedPixel = 64 * 4 + 16;   // bytes of a pixel's 64 sums in LDS
 __host__ __device__ inline int halo_rows(int P, int W) { return (P + 2 * W + 2 + 15) / 16 * 16; }
 __host__ __device__ inline int halo_bytes_of(int P, int W) { return (halo_rows(P, W) + 1) * kCBlock; }
 
-// WF x WP waves; a wave multiplies 64 filters x 32 PG pixels.  F = 64 WF, P = 32 PG WP.
+// WF x WP waves; a wave multiplies 64 filters x 32 PG pixels.  F = 64 WF, P = 32 PG WP.  THROUGH: whole pixels are written through the L2 (write_out).
 // grid: (ceil(pixels / P), ceil(K / F)), 64 WF WP threads.
-template <int LAYOUT, int WF, int WP, int PG>
+template <int LAYOUT, int WF, int WP, int PG, bool THROUGH>
 __global__ __launch_bounds__(64 * WF * WP) void direct_gemm_kernel(const int8_t* __restrict__ x, const int8_t* __restrict__ w,
                                                                    int N, int C, int H, int W, int K, int32_t* __restrict__ y, Problem p) {
     p.N = N; p.C = C; p.H = H; p.W = W; p.K = K;   // (in registers when a wave starts)
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(64 * WF * WP) void direct_gemm_kernel(const int8_t*
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         const v4i v = *reinterpret_cast<const v4i*>(take + 4 * i * kStagedPixel);
-                        if (pixel + 4 * i < pixels) *reinterpret_cast<v4i*>(out + (size_t)(4 * i) * p.K) = v;
+                        if (pixel + 4 * i < pixels) write_as<THROUGH>(reinterpret_cast<v4i*>(out + (size_t)(4 * i) * p.K), v);
                     }
                 } else if (kw + lane < p.K) {
                     int32_t* const out = y + (size_t)first * p.K + kw + lane;
@@ -272,22 +272,22 @@ int choose_form(const Problem& p) {
     return best;
 }
 
-template <int LAYOUT, int WF, int WP, int PG>
+template <int LAYOUT, int WF, int WP, int PG, bool THROUGH>
 hipError_t launch(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, hipStream_t s) {
     constexpr Form f = {64 * WF, 32 * PG * WP, 64 * WF * WP};
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&direct_gemm_kernel<LAYOUT, WF, WP, PG>), kLdsMost)) return e;
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&direct_gemm_kernel<LAYOUT, WF, WP, PG, THROUGH>), kLdsMost)) return e;
     const dim3 grid((unsigned)(((long long)p.N * p.H * p.W + f.P - 1) / f.P), ceil_div(p.K, f.F));
-    direct_gemm_kernel<LAYOUT, WF, WP, PG><<<grid, f.threads, lds_bytes(f, p), s>>>(x, w, p.N, p.C, p.H, p.W, p.K, y, p);
+    direct_gemm_kernel<LAYOUT, WF, WP, PG, THROUGH><<<grid, f.threads, lds_bytes(f, p), s>>>(x, w, p.N, p.C, p.H, p.W, p.K, y, p);
     return hipGetLastError();
 }
-template <int LAYOUT>
+template <int LAYOUT, bool THROUGH>
 hipError_t launch_form(int form, const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, hipStream_t s) {
     switch (form) {
-        case 0: return launch<LAYOUT, 2, 4, 4>(x, w, y, p, s);
-        case 1: return launch<LAYOUT, 1, 8, 2>(x, w, y, p, s);
-        case 2: return launch<LAYOUT, 1, 8, 1>(x, w, y, p, s);
-        default: return launch<LAYOUT, 1, 4, 1>(x, w, y, p, s);
+        case 0: return launch<LAYOUT, 2, 4, 4, THROUGH>(x, w, y, p, s);
+        case 1: return launch<LAYOUT, 1, 8, 2, THROUGH>(x, w, y, p, s);
+        case 2: return launch<LAYOUT, 1, 8, 1, THROUGH>(x, w, y, p, s);
+        default: return launch<LAYOUT, 1, 4, 1, THROUGH>(x, w, y, p, s);
     }
 }
 
@@ -297,7 +297,8 @@ bool direct_gemm_applies(const Problem& p) { return choose_form(p) >= 0; }
 
 hipError_t launch_direct_gemm(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, int layout, hipStream_t s) {
     const int form = choose_form(p);
-    return layout == WG_NHWC ? launch_form<WG_NHWC>(form, x, w, y, p, s) : launch_form<WG_NCHW>(form, x, w, y, p, s);
+    if (layout != WG_NHWC) return launch_form<WG_NCHW, false>(form, x, w, y, p, s);
+    return p.through & kThroughRows ? launch_form<WG_NHWC, true>(form, x, w, y, p, s) : launch_form<WG_NHWC, false>(form, x, w, y, p, s);
 }
 
 }  // namespace wg

@@ -110,7 +110,7 @@ __device__ inline int unscale(int m, uint32_t rq) {
 // grid: (ceil(T / 16), Kp / 64), 256 threads.  Transform: thread = (tile, four channels).  Products: wave w owns filters
 // 16 w .. 16 w + 15 of the 16 tiles for all 16 entries.  BUFFERS: the filter fragments come by buffer loads, and in scaled mode four
 // workgroups share a compute unit.
-template <int LAYOUT, int MODE, bool Q8, bool NARROW, bool BUFFERS, class ENC>
+template <int LAYOUT, int MODE, bool Q8, bool NARROW, bool BUFFERS, bool THROUGH, class ENC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == WG_SCALED && BUFFERS ? 4 : 3))) void f2_fast_kernel(
     const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_ORDER_PARAMS, const uint8_t* __restrict__ blob, size_t table_off,
     size_t planes_off, int32_t* __restrict__ y, Problem p, ENC enc, Int8Epilogue q8) {
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == WG_
             const size_t at = (((size_t)n * Ho + h) * Wo + w) * p.K + kk;
             if (quads) {
                 if constexpr (Q8) *reinterpret_cast<uint32_t*>(q8.out + at) = pack_bytes(v);
-                else              *reinterpret_cast<v4i*>(y + at) = v;
+                else              write_as<THROUGH>(reinterpret_cast<v4i*>(y + at), v);
             } else {
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
@@ -349,9 +349,14 @@ hipError_t launch_f2_fast(const int8_t* x, int is_unsigned, int zero_point, cons
     auto launch = [&](auto L, auto M, auto Q, auto N, auto B, const auto& enc) -> hipError_t {
         using ENC = std::decay_t<decltype(enc)>;
         const GridOrder order(grid, grid.y >= 8 ? kByFilters : kLaunchOrder);   // (with fewer filter blocks the launch order is as fast)
-        f2_fast_kernel<L, M, Q, N, B, ENC><<<grid, 256, kLds, s>>>(x, WG_GEOMETRY(p), WG_ORDER(order), static_cast<const uint8_t*>(blob),
-                                                                   bl.table_off, bl.planes_off, y, p, enc, q8);
-        return hipGetLastError();
+        auto run = [&](auto THROUGH) {
+            f2_fast_kernel<L, M, Q, N, B, THROUGH, ENC><<<grid, 256, kLds, s>>>(x, WG_GEOMETRY(p), WG_ORDER(order), static_cast<const uint8_t*>(blob),
+                                                                                bl.table_off, bl.planes_off, y, p, enc, q8);
+            return hipGetLastError();
+        };
+        if constexpr (!Q && L == WG_NHWC)
+            if (p.through & kThroughRows) return run(std::true_type{});   // (see write_out; a branch in the kernel cost small layers 2 - 5 %)
+        return run(std::false_type{});
     };
     auto go = [&](auto L, auto M, auto Q, auto N, const auto& enc) {
         return buffers ? launch(L, M, Q, N, std::true_type{}, enc) : launch(L, M, Q, N, std::false_type{}, enc);

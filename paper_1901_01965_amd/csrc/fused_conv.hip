@@ -179,7 +179,7 @@ __device__ __forceinline__ void fused_conv_body(const int8_t* __restrict__ x, co
         __syncthreads();   // the operand planes (or the previous pass's staged outputs) are dead
         stage_outputs(lds, lane, half, kblock, Yall[pass]);
         __syncthreads();
-        store_staged<LAYOUT, Q8, true>(sc, p, q8, k0 + pass * kFusedFilters);
+        store_staged<LAYOUT, Q8 ? kOutInt8 : kOutInt32, true>(sc, p, q8, k0 + pass * kFusedFilters);
     }
 }
 
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(256) void fused_conv_act_scaled_kernel(const int8_t
     __syncthreads();   // the operand planes are dead (the tables lie behind them)
     stage_outputs(lds, lane, half, kblock, Y);
     __syncthreads();
-    store_staged<LAYOUT, false, true>(sc, p, Int8Epilogue{}, k0);
+    store_staged<LAYOUT, kOutInt32, true>(sc, p, Int8Epilogue{}, k0);
 }
 
 template <int LAYOUT, int LOAD>

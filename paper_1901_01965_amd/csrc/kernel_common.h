@@ -98,6 +98,24 @@ __device__ inline v4i requantise(v4i y, const Int8Epilogue& q) {
 __device__ inline uint32_t pack_bytes(v4i v) {
     return __builtin_amdgcn_perm((uint32_t)v[1], (uint32_t)v[0], 0x0c0c0400u) | __builtin_amdgcn_perm((uint32_t)v[3], (uint32_t)v[2], 0x04000c0cu);
 }
+// An output, or a sum for the next kernel, written through the L2 (device scope).  Left in the L2s, what a kernel wrote is written back when it
+// ends, and a kernel of one round or two, whose compute units all store at the end, waits for that; written through, it is under way as
+// soon as it is stored.  us, plain / through: 128 -> 128 at 28x28, N = 32, scaled 12.7 / 11.8 (with the requantisation that reads it 19.3 / 19.0),
+// 64 -> 64 at 56x56, N = 32 16.7 / 14.8, direct 256 -> 256 at 56x56, N = 16 33.8 / 31.5 (42.5 / 41.4), F(2x2) at 28x28 15.4 / 13.8; partial sums of
+// 512 -> 512 at 14x14, N = 1, scaled, both kernels 15.2 / 13.3.  (Non-temporal stores: as fast by themselves, but what reads the outputs
+// next is slower by as much or more, direct 256 -> 256 43.9.)  Which outputs: writes_through (wg_internal.h).  int8 outputs, a fourth of the
+// bytes in parts of lines, gain in the limb-pair kernel (64 -> 64 at 56x56, N = 8 7.3 / 6.9) and first layers (N = 16 at 224x224 38.6 / 35.9), and are
+// level or behind elsewhere (0.98 - 1.03); so are the requantisation's (1.00 - 1.03) and channels-last copies (1.02 - 1.10).
+template <class T>
+__device__ inline void write_out(T* at, T v) {
+    static_assert(sizeof(T) == 16 || sizeof(T) == 4, "dwords");
+    if constexpr (sizeof(T) == 16) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(at), "v"(v) : "memory");
+    else                           asm volatile("global_store_dword %0, %1, off sc1" ::"v"(at), "v"(v) : "memory");
+}
+template <bool THROUGH, class T>
+__device__ inline void write_as(T* at, T v) {
+    if constexpr (THROUGH) write_out(at, v); else *at = v;
+}
 // Patch loads of the role-specialised kernels go through a buffer descriptor over the activation
 // tensor: a load whose offset lies beyond the tensor returns zero, so a pixel outside the image
 // (pad 1, ragged tiles) is an offset that can never be in range instead of a select per pixel and

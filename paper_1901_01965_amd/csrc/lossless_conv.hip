@@ -336,7 +336,7 @@ struct RawPatch {
 // OUT kOutSums: the workgroup takes `blocks` channel blocks, those of split bz, and leaves the sum of its outputs,
 // before the rescale by 2^-4, at y as int32 [split][tile block][32 filters][tile][output 4i+j][filter] (the output transform is
 // linear, so these add up to the whole; sums_finish_kernel adds, rescales and stores).
-constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2;
+constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2, kOutSumsThrough = 3;
 
 // Where a workgroup works.  Not split: the grid's own numbers, all channel blocks.  Split channels: a grid of ceil(T/16) x ceil(K/32) x
 // splits.  Every tile block reads all filters, so in lossless mode the splits are dealt out first and the tile blocks last, which brings more of the
@@ -369,7 +369,7 @@ template <int LAYOUT, int LOAD, int OUT, int PARTS>
 __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t pairs_off,
                                               int32_t* __restrict__ y, const Problem p, const Int8Epilogue q8, const SplitPlace at) {
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
-    constexpr bool Q8 = OUT == kOutInt8, SPLIT = OUT == kOutSums, STREAMS = SPLIT || PARTS == 4;   // the next block's filters travel early
+    constexpr bool Q8 = OUT == kOutInt8, SPLIT = (OUT >= kOutSums), STREAMS = SPLIT || PARTS == 4;   // the next block's filters travel early
     const int bx = at.tile_block, by = at.filter_block, bz = at.split;
     const int cb_first = at.first, cb_end = SPLIT ? min(at.end, p.CB) : p.CB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -525,7 +525,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         return requantise(__builtin_elementwise_max(a, b) >> 4, q8);
     };
     constexpr int kQuads = St::kFilters / 4;   // of four filters
-    if constexpr (LAYOUT == WG_NCHW && OUT != kOutSums) {
+    if constexpr (LAYOUT == WG_NCHW && (OUT < kOutSums)) {
         // a filter's outputs lie together: sixteen consecutive tiles of an image row are 64 consecutive pixels
         const int tile = (tid >> 2) & 15, t = tile0 + tile;
         int n = 0, ty = 0, tx = 0;
@@ -542,9 +542,11 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
                 const int k4 = kQuads / 2 * (tid >> 8) + g;
                 const v4i v = staged(4 * i + j, tile, k4);
                 int32_t* const at = first(y, k4, h, w);
+                // (always through: at W = 14 level to 1 % behind, 100 -> 75 at 37x53 0.96, 64 -> 64 at 128x128 0.91 of the time; with a choice 16 -> 16
+                // at 16x16 took 1 % longer)
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    if (k0 + 4 * k4 + c < p.K) at[c * plane] = v[c];
+                    if (k0 + 4 * k4 + c < p.K) write_out(at + c * plane, (int32_t)v[c]);
             }
         } else if (q8.pool) {
             // thread: one pooled pixel of a tile, four filters
@@ -586,11 +588,11 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
     if (t < p.T) decode_tile(p, t, n, ty, tx);
     const int row = 4 * ty, col = 4 * tx + j;
     const bool live = t < p.T && col < p.W && kk < p.K;
-    if constexpr (OUT == kOutSums) {
+    if constexpr ((OUT >= kOutSums)) {
         v4i* const to = reinterpret_cast<v4i*>(y + split_sums_offset(16, bz, bx, k0 / kBlockFilters, at.tile_blocks, p.Kp)) +
                         (16 * tile + j) * (kBlockFilters / 4) + k0 % kBlockFilters / 4 + k4;
 #pragma unroll
-        for (int r = row0; r < row0 + kRows; ++r) to[4 * r * (kBlockFilters / 4)] = sixteen(4 * r + j, tile, k4);
+        for (int r = row0; r < row0 + kRows; ++r) write_as<OUT == kOutSumsThrough>(to + 4 * r * (kBlockFilters / 4), sixteen(4 * r + j, tile, k4));
         return;
     }
     if constexpr (!Q8) {
@@ -599,6 +601,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         v4i v[kRows];
 #pragma unroll
         for (int r = 0; r < kRows; ++r) v[r] = staged(4 * (row0 + r) + j, tile, k4);
+        // (not through the L2: level at best, 64 -> 64 at 28x28, N = 1, 5.57 us, through 5.71)
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
             if (!live || row + row0 + r >= p.H) continue;
@@ -614,9 +617,9 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
     } else {
         // requantisation and clamp, then (a 4x4 tile holds whole 2x2 windows) the pooling maximum
         const bool word_store = (p.K & 3) == 0 && (reinterpret_cast<uintptr_t>(q8.out) & 3) == 0;
-        auto put = [&](int8_t* at, v4i q) {
+        auto put_bytes = [&](int8_t* at, v4i q) {
             if (word_store) {
-                *reinterpret_cast<uint32_t*>(at) = pack_bytes(q);
+                write_out(reinterpret_cast<uint32_t*>(at), pack_bytes(q));
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -629,7 +632,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
             for (int r = 0; r < kRows; ++r) v[r] = requantise(staged(4 * (row0 + r) + j, tile, k4), q8);
 #pragma unroll
             for (int r = 0; r < kRows; ++r)
-                if (live && row + row0 + r < p.H) put(q8.out + ((size_t)(n * p.H + row + row0 + r) * p.W + col) * p.K + kk, v[r]);
+                if (live && row + row0 + r < p.H) put_bytes(q8.out + ((size_t)(n * p.H + row + row0 + r) * p.W + col) * p.K + kk, v[r]);
         } else if (j < 2) {
             // thread: pooled column j (0, 1) of its tile, both pooled rows (one)
             const int Ho = p.H >> 1, Wo = p.W >> 1, ocol = 2 * tx + j;
@@ -637,7 +640,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
             for (int pi = row0 / 2; pi < row0 / 2 + kRows / 2; ++pi) {
                 const v4i best = best_of_window(pi, j, tile, k4);
                 if (t < p.T && kk < p.K && ocol < Wo && 2 * ty + pi < Ho)
-                    put(q8.out + ((size_t)(n * Ho + 2 * ty + pi) * Wo + ocol) * p.K + kk, best);
+                    put_bytes(q8.out + ((size_t)(n * Ho + 2 * ty + pi) * Wo + ocol) * p.K + kk, best);
             }
         }
     }
@@ -653,11 +656,11 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     const int tile_block = PARTS == 4 ? (int)(blockIdx.x + blockIdx.z) : (int)blockIdx.x;
     lossless_pair<LAYOUT, LOAD, OUT, PARTS>(x, blob, pairs_off, y, p, q8, SplitPlace{0, tile_block, (int)blockIdx.y, 0, 0, 0});
 }
-template <int LOAD, int PARTS>
+template <int LOAD, int OUT, int PARTS>
 __global__ __launch_bounds__(512) void lossless_pair_sums_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_SPLIT_PARAMS,
                                                                  const uint8_t* __restrict__ blob, size_t pairs_off, int32_t* __restrict__ sums, Problem p) {
     WG_TAKE_GEOMETRY(p, 2);
-    lossless_pair<WG_NHWC, LOAD, kOutSums, PARTS>(x, blob, pairs_off, sums, p, Int8Epilogue{nullptr, 0, 0, 0, 0},
+    lossless_pair<WG_NHWC, LOAD, OUT, PARTS>(x, blob, pairs_off, sums, p, Int8Epilogue{nullptr, 0, 0, 0, 0},
                                            place_split(s_across, s_packed));
 }
 
@@ -735,15 +738,16 @@ struct QuarterProducts {
         });
     }
     // lane = tile (lane & 15) x four filters: one 16-byte store per sum
+    template <bool THROUGH>
     __device__ inline void store(v4i* to, int plane) const {
         static_for<NS>([&](auto S) {
             constexpr int e = quarter_entry(Q, S), a = quarter_acc(Q, S);
             if constexpr (real_entry(e)) {
-                to[e * plane] = (acc[a] << kByteLimbShift) + acc[a + 1];
+                write_as<THROUGH>(to + e * plane, (acc[a] << kByteLimbShift) + acc[a + 1]);
             } else {
                 constexpr int at = kRealEntries + 2 * (e - kRealEntries);
-                to[at * plane] = ((acc[a] - acc[a + 4]) << kByteLimbShift) + (acc[a + 1] - acc[a + 5]);
-                to[(at + 1) * plane] = (acc[a + 2] << kByteLimbShift) + acc[a + 3];
+                write_as<THROUGH>(to + at * plane, ((acc[a] - acc[a + 4]) << kByteLimbShift) + (acc[a + 1] - acc[a + 5]));
+                write_as<THROUGH>(to + (at + 1) * plane, (acc[a + 2] << kByteLimbShift) + acc[a + 3]);
             }
         });
     }
@@ -792,8 +796,9 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
             flt += flt_block;
         }
         constexpr int plane = kTileBlock * kBlockFilters / 4;   // in units of four sums
-        products.store(reinterpret_cast<v4i*>(sums + split_sums_offset(kAccPlanes, at.split, at.tile_block, at.filter_block, at.tile_blocks, p.Kp)) +
-                           (lane & 15) * (kBlockFilters / 4) + 4 * (wave & 1) + (lane >> 4), plane);
+        v4i* const to = reinterpret_cast<v4i*>(sums + split_sums_offset(kAccPlanes, at.split, at.tile_block, at.filter_block, at.tile_blocks, p.Kp)) +
+                           (lane & 15) * (kBlockFilters / 4) + 4 * (wave & 1) + (lane >> 4);
+        if (p.through & kThroughSums) products.template store<true>(to, plane); else products.template store<false>(to, plane);
     };
     switch (wave >> 1) {
         case 0: blocks_of(std::integral_constant<int, 0>{}); break;
@@ -884,16 +889,25 @@ hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t*
     }
 }
 
+// The splits' sums, which the next kernel reads from every XCD, are written through the L2 (write_out) where they are not few: 512 -> 512 at 14x14,
+// N = 1 (4 and 9 MB), both kernels, scaled 15.2 us, through 13.3, lossless 10.4, 10.2; 128 -> 64 at 14x14, N = 2 (0.3 MB) 9.1, 9.4.
+static bool sums_through(const Problem& p, int mode, int splits) { return split_partial_bytes(p, mode, splits) >= sizeof(int32_t) * kThroughFewest; }
+
 hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits,
                                      hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
-    auto form = [&](auto LOAD, auto PARTS) -> hipError_t {
+    auto launch = [&](auto LOAD, auto OUT, auto PARTS) -> hipError_t {
         static LdsLimitOnce lds_limit;   // per instance
-        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_sums_kernel<LOAD, PARTS>), pair_lds_bytes<PARTS>())) return e;
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_sums_kernel<LOAD, OUT, PARTS>), pair_lds_bytes<PARTS>())) return e;
         const SplitGrid grid = split_grid(p, blocks, splits, WG_LOSSLESS, Stage<PARTS>::kFilters);
-        lossless_pair_sums_kernel<LOAD, PARTS><<<grid.grid, 64 * kWaves, pair_lds_bytes<PARTS>(), s>>>(
+        lossless_pair_sums_kernel<LOAD, OUT, PARTS><<<grid.grid, 64 * kWaves, pair_lds_bytes<PARTS>(), s>>>(
             x, WG_GEOMETRY(p), WG_SPLIT(grid), static_cast<const uint8_t*>(blob), bl.pairs_off, sums, p);
         return hipGetLastError();
+    };
+    // (a kernel each: with a branch 256 -> 128 at 14x14, N = 2, took 8.4 us instead of 7.9)
+    auto form = [&](auto LOAD, auto PARTS) {
+        return sums_through(p, WG_LOSSLESS, splits) ? launch(LOAD, std::integral_constant<int, kOutSumsThrough>{}, PARTS)
+                                                    : launch(LOAD, std::integral_constant<int, kOutSums>{}, PARTS);
     };
     auto go = [&](auto LOAD) {
         return in_quarters(p, splits) ? form(LOAD, std::integral_constant<int, 4>{}) : form(LOAD, std::integral_constant<int, 2>{});
@@ -909,12 +923,14 @@ hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t*
 hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits, hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
     const SplitGrid grid = split_grid(p, blocks, splits, WG_SCALED);
+    Problem through = p;
+    through.through = sums_through(p, WG_SCALED, splits) ? kThroughSums : 0;
     auto go = [&](auto LOAD) -> hipError_t {
         static LdsLimitOnce lds_limit;   // per LOAD
         constexpr int lds_bytes = kPlanesBytes + 4 * kRawQuad;
         if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&scaled_sums_kernel<LOAD>), lds_bytes)) return e;
         scaled_sums_kernel<LOAD><<<grid.grid, 64 * kWaves, lds_bytes, s>>>(x, WG_GEOMETRY(p), WG_SPLIT(grid), static_cast<const uint8_t*>(blob),
-                                                                              bl.planes_off, sums, p);
+                                                                              bl.planes_off, sums, through);
         return hipGetLastError();
     };
     using std::integral_constant;

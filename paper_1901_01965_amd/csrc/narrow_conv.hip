@@ -449,9 +449,11 @@ __global__ __launch_bounds__(256, 2) void narrow_conv_kernel(const int8_t* __res
                 for (int m = 0; m < 4; ++m) {
                     const int tile = 4 * m + wave;
                     const TilePlace to = places[16 * g + tile];
-                    if ((int)I < to.rows && j < to.cols && k0 + f0 < p.K)
-                        *reinterpret_cast<uint4*>(y + ((size_t)to.pixel + (int)I * Wo + j) * p.K + k0 + f0) =
-                            *reinterpret_cast<const uint4*>(stage + tile * kStagedTileBytes + 256 * j + 4 * f0);
+                    if ((int)I < to.rows && j < to.cols && k0 + f0 < p.K) {
+                        v4i* const at = reinterpret_cast<v4i*>(y + ((size_t)to.pixel + (int)I * Wo + j) * p.K + k0 + f0);
+                        const v4i v = *reinterpret_cast<const v4i*>(stage + tile * kStagedTileBytes + 256 * j + 4 * f0);
+                        write_out(at, v);
+                    }
                 }
             });
         } else {
@@ -490,7 +492,7 @@ __global__ __launch_bounds__(256, 2) void narrow_conv_kernel(const int8_t* __res
                 if (i < to.rows && j < to.cols && left > 0) {
                     int8_t* const at = q8.out + ((size_t)to.pixel + i * Wo + j) * p.K + k0 + 16 * piece;
                     if (whole_pieces) {
-                        *reinterpret_cast<uint4*>(at) = v;
+                        write_out(reinterpret_cast<v4i*>(at), __builtin_bit_cast(v4i, v));
                     } else {
                         uint32_t* const dwords = reinterpret_cast<uint32_t*>(at);
                         dwords[0] = v.x;

@@ -475,11 +475,17 @@ __device__ __forceinline__ void locate_tile(StoreContext& sc, const Problem& p, 
     sc.my_origin = t >= p.T ? -1 : LAYOUT == WG_NHWC ? ((n * p.H + 4 * ty) * p.W + 4 * tx) * p.K : (n * p.K * p.H + 4 * ty) * p.W + 4 * tx;
 }
 
+// What a kernel writes: int32, requantised int8, or int32 written through the L2 (write_out); which of the first and the last is chosen
+// on the host, so that a kernel has one of them (with both, and a branch, small layers took 1 % longer).
+constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutThrough = 2;
+inline int int32_out(const Problem& p, int layout) { return p.through & (layout == WG_NHWC ? kThroughRows : kThroughPlanes) ? kOutThrough : kOutInt32; }
+
 // Stores the 16 tiles x 32 filters (from kbase) that were staged (a barrier lies between): int32 to y, or requantised
 // (and pooled) to int8 at q8.out.  ADD: two halves were staged and are added; otherwise one finished copy (half 0).
 // Any K and either layout; 16-byte (int8: 4- or 16-byte) stores where K and the alignment allow.
-template <int LAYOUT, bool Q8, bool ADD>
+template <int LAYOUT, int OUT, bool ADD>
 __device__ __forceinline__ void store_staged(const StoreContext& sc, const Problem& p, const Int8Epilogue& q8, int kbase) {
+    constexpr bool Q8 = OUT == kOutInt8, THROUGH = OUT == kOutThrough;
     const int tid = sc.tid, lane = sc.lane;
     const int* const parki = reinterpret_cast<const int*>(sc.lds);
     auto sixteen = [&](int o, int tile, int g) {   // 16 x the outputs of filters 4*g .. 4*g+3 of the block
@@ -510,7 +516,7 @@ __device__ __forceinline__ void store_staged(const StoreContext& sc, const Probl
                 const v4i v = staged(4 * i + j, tile, g);
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    if (ok && kbase + 4 * g + c < p.K) first[(size_t)(kbase + 4 * g + c) * plane] = v[c];
+                    if (ok && kbase + 4 * g + c < p.K) write_as<THROUGH>(first + (size_t)(kbase + 4 * g + c) * plane, (int32_t)v[c]);
             }
         } else if (q8.pool) {
             // thread: one pooled pixel of a tile; the four waves take two groups of four filters each
@@ -626,7 +632,7 @@ __device__ __forceinline__ void store_staged(const StoreContext& sc, const Probl
         if (first[e] == nullptr || i >= rows[e]) continue;
         int32_t* at = first[e] + i * row_pitch;
         if (quads) {
-            *reinterpret_cast<v4i*>(at) = v[ps];
+            write_as<THROUGH>(reinterpret_cast<v4i*>(at), v[ps]);
         } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
@@ -634,7 +640,6 @@ __device__ __forceinline__ void store_staged(const StoreContext& sc, const Probl
         }
     }
 }
-
 // Product phase of the role-specialised kernels: the same arithmetic as ProductPhase / ScaledSums in the registers a product
 // wave has there, with a filter ring of RING fragments.
 //   Half of the entries (lossless mode only): channel sums of the joined values; one set of fragments and accumulators, no

@@ -28,7 +28,7 @@ namespace {
 // fragments and patches through the memory path, 2,500 + up to 2,300; LDS, 288 fragment reads and 288 writes, some 4,000; and the
 // transform wave's own chain, an instruction per 5 clocks, 2,650.  (Four product waves and 32 filters: 1.76 us, 3,700 clocks.)
 
-template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
+template <int LAYOUT, int MODE, int OUT, int PW, class ENC>
 __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS,
                                                                          WG_ORDER_PARAMS, const uint8_t* __restrict__ blob,
                                                                          size_t table_off, size_t planes_off, int32_t* __restrict__ y,
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
             cx.a_lds = lds + (cb & 1) * kLdsBytes + lds_slot(lane >> 4, lane & 15) * 16;
             // (512 -> 512 at 7x7, N = 32, scaled, at a multiple of eight / four behind 18.8 / 19.2 us, int8 out, 14x14, N = 16, 19.0 / 18.7;
             // 192 -> 32 at 28x28, N = 16, uint8, 10.5 / 10.8, 128 -> 128, N = 32, 12.5 / 12.3; lossless 14.4 / 14.2)
-            place_loop(std::integral_constant<bool, Q8 || MODE == WG_LOSSLESS || (PW == 8 && !std::is_same_v<ENC, SignedInt8>)>{});
+            place_loop(std::integral_constant<bool, OUT == kOutInt8 || MODE == WG_LOSSLESS || (PW == 8 && !std::is_same_v<ENC, SignedInt8>)>{});
             phase.run(cx, sums);
             WG_SPENT(2, mark);   // products
         }
@@ -168,23 +168,23 @@ __global__ __launch_bounds__(64 * (4 + PW)) void fused_conv_roles_kernel(const i
     __syncthreads();   // the operand planes are dead
     stage_outputs(sc.lds, lane, half, kblock, Y);
     __syncthreads();
-    store_staged<LAYOUT, Q8, true>(sc, p, q8, k0 + group * kFusedFilters);
+    store_staged<LAYOUT, OUT, true>(sc, p, q8, k0 + group * kFusedFilters);
 #ifdef WG_TIMESTAMPS
     if (g_roles_stamps != nullptr && lane == 0)
         g_roles_stamps[((size_t)(blockIdx.y * gridDim.x + blockIdx.x) * 12 + wave8) * 8 + 5] = WG_CLOCK() - entered;
 #endif
 }
 
-template <int LAYOUT, int MODE, bool Q8, int PW, class ENC>
+template <int LAYOUT, int MODE, int OUT, int PW, class ENC>
 hipError_t launch_roles(const int8_t* x, const ENC& enc, const uint8_t* blob, const BlobLayout& bl, int32_t* y, const Problem& p,
                         const Int8Epilogue& q8, hipStream_t s) {
     constexpr int lds_bytes = 2 * kLdsBytes + PW * kParkedScaleBytes;   // two plane buffers, the parked reverse-scaling factors
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC>), lds_bytes)) return e;
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_roles_kernel<LAYOUT, MODE, OUT, PW, ENC>), lds_bytes)) return e;
     dim3 grid(ceil_div(p.T, kFusedTiles), ceil_div(p.K, kFusedFilters * (PW / 4)));
     const GridOrder order(grid, workgroup_order(p, MODE, kFusedFilters * (PW / 4)));
-    fused_conv_roles_kernel<LAYOUT, MODE, Q8, PW, ENC><<<grid, 64 * (4 + PW), lds_bytes, s>>>(
+    fused_conv_roles_kernel<LAYOUT, MODE, OUT, PW, ENC><<<grid, 64 * (4 + PW), lds_bytes, s>>>(
         x, WG_GEOMETRY(p), WG_ORDER(order), blob, bl.table_off, bl.planes_off, y, p, q8, enc);
     return hipGetLastError();
 }
@@ -192,10 +192,13 @@ hipError_t launch_roles(const int8_t* x, const ENC& enc, const uint8_t* blob, co
 // One mode's launches (each mode is compiled in a file of its own).
 template <int MODE>
 hipError_t launch_roles_mode(const RolesCall& c, bool wide, hipStream_t s) {
-    auto go = [&](auto L, auto Q8, auto PW, const auto& enc) {
-        return launch_roles<L, MODE, Q8, PW>(c.x, enc, c.blob, c.bl, c.y, c.p, c.q8, s);
-    };
     using std::integral_constant;
+    const bool through = int32_out(c.p, c.layout) == kOutThrough;
+    auto go = [&](auto L, auto Q8, auto PW, const auto& enc) {
+        auto launch = [&](auto OUT) { return launch_roles<L, MODE, OUT, PW>(c.x, enc, c.blob, c.bl, c.y, c.p, c.q8, s); };
+        if constexpr (Q8) return launch(integral_constant<int, kOutInt8>{});
+        else return through ? launch(integral_constant<int, kOutThrough>{}) : launch(integral_constant<int, kOutInt32>{});
+    };
     auto form = [&](auto L, auto Q8, const auto& enc) {
         return wide ? go(L, Q8, integral_constant<int, 8>{}, enc) : go(L, Q8, integral_constant<int, 4>{}, enc);
     };

@@ -76,7 +76,7 @@ template <int FORM> constexpr int stream_filters() { return FORM == kStreamHalve
 template <int FORM> constexpr bool twelve_waves() { return FORM == kStreamEight || FORM == kStreamPairs; }
 template <int FORM> constexpr int stream_product_waves() { return twelve_waves<FORM>() ? 8 : 4; }
 
-template <int LAYOUT, int MODE, bool Q8, int FORM, class ENC>
+template <int LAYOUT, int MODE, int OUT, int FORM, class ENC>
 __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused_conv_stream_kernel(
     const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_ORDER_PARAMS, const uint8_t* __restrict__ blob, size_t table_off,
     size_t planes_off, int32_t* __restrict__ y, Problem p, Int8Epilogue q8, ENC enc) {
@@ -142,11 +142,11 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             if constexpr (twelve_waves<FORM>() || LAYOUT == WG_NCHW) asm volatile("" : "+v"(sc.tid), "+v"(sc.lane));
             locate_tile<LAYOUT>(sc, p, tb * kFusedTiles);
             if constexpr (FORM != kStreamHalves) {   // one finished copy per 32 filters
-                store_staged<LAYOUT, Q8, false>(sc, p, q8, k0);
+                store_staged<LAYOUT, OUT, false>(sc, p, q8, k0);
                 sc.lds += kStageHalf * 4;
-                store_staged<LAYOUT, Q8, false>(sc, p, q8, k0 + kFusedFilters);
+                store_staged<LAYOUT, OUT, false>(sc, p, q8, k0 + kFusedFilters);
             } else {
-                store_staged<LAYOUT, Q8, true>(sc, p, q8, k0);
+                store_staged<LAYOUT, OUT, true>(sc, p, q8, k0);
             }
         };
         RoleBarrier<4> among_us = {reinterpret_cast<uint32_t*>(lds + 2 * kLdsBytes), 0u};
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
             sc.lane = lane_again(); sc.tid = (pw & 3) * 64 + sc.lane; sc.rnd = rnd; sc.y = y;
             asm volatile("" : "+v"(sc.tid));
             locate_tile<LAYOUT>(sc, p, (bx + u * order.across) * kFusedTiles);
-            store_staged<LAYOUT, Q8, false>(sc, p, q8, k0 + (pw >> 2) * kFusedFilters);
+            store_staged<LAYOUT, OUT, false>(sc, p, q8, k0 + (pw >> 2) * kFusedFilters);
         }
     } else if constexpr (FORM == kStreamWhole) {
         // filter ring: lossless mode has twice the fragments per entry and the registers for twelve in flight
@@ -395,17 +395,17 @@ __global__ __launch_bounds__(64 * (4 + stream_product_waves<FORM>())) void fused
 #endif
 }
 
-template <int LAYOUT, int MODE, bool Q8, int FORM, class ENC>
+template <int LAYOUT, int MODE, int OUT, int FORM, class ENC>
 hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
     // two plane buffers, the roles' barrier counters, the parked reverse-scaling factors
     constexpr int lds_bytes = 2 * kLdsBytes + 64 + (FORM == kStreamPairs ? 0 : FORM == kStreamWhole ? 4 * ParkedScales<kAllRows>::kBytes : stream_product_waves<FORM>() * kParkedScaleBytes);
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
     static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC>), lds_bytes)) return e;
+    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&fused_conv_stream_kernel<LAYOUT, MODE, OUT, FORM, ENC>), lds_bytes)) return e;
     const int tile_blocks = ceil_div(c.p.T, kFusedTiles), filter_blocks = ceil_div(c.p.K, stream_filters<FORM>());
     const dim3 grid(stream_workgroups(tile_blocks, filter_blocks), filter_blocks);
     const GridOrder order(grid, workgroup_order(c.p, MODE, stream_filters<FORM>()));
-    fused_conv_stream_kernel<LAYOUT, MODE, Q8, FORM, ENC><<<grid, 64 * (4 + stream_product_waves<FORM>()), lds_bytes, s>>>(
+    fused_conv_stream_kernel<LAYOUT, MODE, OUT, FORM, ENC><<<grid, 64 * (4 + stream_product_waves<FORM>()), lds_bytes, s>>>(
         c.x, WG_GEOMETRY(c.p), WG_ORDER(order), c.blob, c.bl.table_off, FORM == kStreamPairs ? c.bl.pairs_off : c.bl.planes_off, c.y, c.p, c.q8, enc);
     return hipGetLastError();
 }
@@ -414,11 +414,24 @@ hipError_t launch_stream(const RolesCall& c, const ENC& enc, hipStream_t s) {
 template <int MODE>
 hipError_t launch_stream_mode(const RolesCall& c, StreamForm which, hipStream_t s) {
     auto form = [&](auto L, auto Q8, const auto& enc) {
+        auto go = [&](auto FORM) {
+            if constexpr (Q8) {
+                return launch_stream<L, MODE, kOutInt8, FORM>(c, enc, s);
+            } else {
+                // in a longer stream the stores are spread over it already (64 -> 64 at 56x56, four tile blocks per workgroup, N = 64, scaled 27.0 us,
+                // through 24.8; seven and thirteen level, channel-major thirteen 119 and 149)
+                const int tile_blocks = ceil_div(c.p.T, kFusedTiles);
+                const bool few = FORM == kStreamEight || tile_blocks <= 4 * stream_workgroups(tile_blocks, ceil_div(c.p.K, stream_filters<FORM>()));
+                return few && int32_out(c.p, c.layout) == kOutThrough ? launch_stream<L, MODE, kOutThrough, FORM>(c, enc, s)
+                                                                      : launch_stream<L, MODE, kOutInt32, FORM>(c, enc, s);
+            }
+        };
+        using std::integral_constant;
         if constexpr (MODE == WG_LOSSLESS)
-            if (which == kStreamPairs) return launch_stream<L, MODE, Q8, kStreamPairs>(c, enc, s);
-        if (which == kStreamEight) return launch_stream<L, MODE, Q8, kStreamEight>(c, enc, s);
-        if (which == kStreamWhole) return launch_stream<L, MODE, Q8, kStreamWhole>(c, enc, s);
-        return launch_stream<L, MODE, Q8, kStreamHalves>(c, enc, s);
+            if (which == kStreamPairs) return go(integral_constant<int, kStreamPairs>{});
+        if (which == kStreamEight) return go(integral_constant<int, kStreamEight>{});
+        if (which == kStreamWhole) return go(integral_constant<int, kStreamWhole>{});
+        return go(integral_constant<int, kStreamHalves>{});
     };
     constexpr std::integral_constant<int, WG_NHWC> nhwc{};
     constexpr std::integral_constant<int, WG_NCHW> nchw{};
