@@ -336,7 +336,7 @@ struct RawPatch {
 // OUT kOutSums: the workgroup takes `blocks` channel blocks, those of split bz, and leaves the sum of its outputs,
 // before the rescale by 2^-4, at y as int32 [split][tile block][32 filters][tile][output 4i+j][filter] (the output transform is
 // linear, so these add up to the whole; sums_finish_kernel adds, rescales and stores).
-constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2, kOutSumsThrough = 3;
+constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2;
 
 // Where a workgroup works.  Not split: the grid's own numbers, all channel blocks.  Split channels: a grid of ceil(T/16) x ceil(K/32) x
 // splits.  Every tile block reads all filters, so in lossless mode the splits are dealt out first and the tile blocks last, which brings more of the
@@ -346,21 +346,22 @@ constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2, kOutSumsThrough = 3;
 // are half as large (640 -> 128 at 48x48 19.4 -> 20.9).
 struct SplitPlace {
     int tile_blocks, tile_block, filter_block, split, first, end;   // channel blocks first .. end - 1
+    bool through;                                                   // the sums are written through the L2
 };
 struct SplitGrid {
     dim3 grid;
-    uint32_t across, packed;   // tile blocks; 2 x channel blocks per split + 1: splits are dealt out first
-    inline SplitGrid(int tile_blocks, int filter_blocks, int splits, int blocks, bool splits_first)
+    uint32_t across, packed;   // tile blocks; 4 x channel blocks per split, + 1: splits are dealt out first, + 2: SplitPlace::through
+    inline SplitGrid(int tile_blocks, int filter_blocks, int splits, int blocks, bool splits_first, bool through)
         : grid(splits_first ? dim3(splits, filter_blocks, tile_blocks) : dim3(tile_blocks, filter_blocks, splits)),
-          across((uint32_t)tile_blocks), packed((uint32_t)blocks << 1 | splits_first) {}
+          across((uint32_t)tile_blocks), packed((uint32_t)blocks << 2 | (uint32_t)through << 1 | splits_first) {}
 };
 // as leading arguments (see WG_GEOMETRY_PARAMS: the first patch's place depends on all of them)
 #define WG_SPLIT_PARAMS uint32_t s_across, uint32_t s_packed
 #define WG_SPLIT(g) (g).across, (g).packed
 __device__ inline SplitPlace place_split(WG_SPLIT_PARAMS) {
     const bool splits_first = s_packed & 1;
-    const int blocks = s_packed >> 1, split = splits_first ? blockIdx.x : blockIdx.z, tile_block = splits_first ? blockIdx.z : blockIdx.x;
-    return SplitPlace{(int)s_across, tile_block, (int)blockIdx.y, split, split * blocks, (split + 1) * blocks};
+    const int blocks = s_packed >> 2, split = splits_first ? blockIdx.x : blockIdx.z, tile_block = splits_first ? blockIdx.z : blockIdx.x;
+    return SplitPlace{(int)s_across, tile_block, (int)blockIdx.y, split, split * blocks, (split + 1) * blocks, (s_packed & 2) != 0};
 }
 
 // (p and q8 by value: by reference the compiler formed every store's conditions anew, 45 comparisons instead of 19 behind the last
@@ -369,7 +370,7 @@ template <int LAYOUT, int LOAD, int OUT, int PARTS>
 __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, const uint8_t* __restrict__ blob, size_t pairs_off,
                                               int32_t* __restrict__ y, const Problem p, const Int8Epilogue q8, const SplitPlace at) {
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
-    constexpr bool Q8 = OUT == kOutInt8, SPLIT = (OUT >= kOutSums), STREAMS = SPLIT || PARTS == 4;   // the next block's filters travel early
+    constexpr bool Q8 = OUT == kOutInt8, SPLIT = OUT == kOutSums, STREAMS = SPLIT || PARTS == 4;   // the next block's filters travel early
     const int bx = at.tile_block, by = at.filter_block, bz = at.split;
     const int cb_first = at.first, cb_end = SPLIT ? min(at.end, p.CB) : p.CB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -525,7 +526,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         return requantise(__builtin_elementwise_max(a, b) >> 4, q8);
     };
     constexpr int kQuads = St::kFilters / 4;   // of four filters
-    if constexpr (LAYOUT == WG_NCHW && (OUT < kOutSums)) {
+    if constexpr (LAYOUT == WG_NCHW && OUT != kOutSums) {
         // a filter's outputs lie together: sixteen consecutive tiles of an image row are 64 consecutive pixels
         const int tile = (tid >> 2) & 15, t = tile0 + tile;
         int n = 0, ty = 0, tx = 0;
@@ -588,11 +589,19 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
     if (t < p.T) decode_tile(p, t, n, ty, tx);
     const int row = 4 * ty, col = 4 * tx + j;
     const bool live = t < p.T && col < p.W && kk < p.K;
-    if constexpr ((OUT >= kOutSums)) {
+    if constexpr (OUT == kOutSums) {
         v4i* const to = reinterpret_cast<v4i*>(y + split_sums_offset(16, bz, bx, k0 / kBlockFilters, at.tile_blocks, p.Kp)) +
                         (16 * tile + j) * (kBlockFilters / 4) + k0 % kBlockFilters / 4 + k4;
+        v4i v[kRows];
 #pragma unroll
-        for (int r = row0; r < row0 + kRows; ++r) write_as<OUT == kOutSumsThrough>(to + 4 * r * (kBlockFilters / 4), sixteen(4 * r + j, tile, k4));
+        for (int r = 0; r < kRows; ++r) v[r] = sixteen(4 * (row0 + r) + j, tile, k4);
+        if (at.through) {
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) write_out(to + 4 * (row0 + r) * (kBlockFilters / 4), v[r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) to[4 * (row0 + r) * (kBlockFilters / 4)] = v[r];
+        }
         return;
     }
     if constexpr (!Q8) {
@@ -654,13 +663,13 @@ __global__ __launch_bounds__(512) void lossless_pair_kernel(const int8_t* __rest
     // grid (tile blocks, filter blocks), quarters also (1, filter blocks, tile blocks): see lossless_pair_filters_first.  (A third number that is
     // not needed costs the halves 0.5 %, 64 -> 64 at 56x56, N = 8, 7.02 us instead of 6.99.)
     const int tile_block = PARTS == 4 ? (int)(blockIdx.x + blockIdx.z) : (int)blockIdx.x;
-    lossless_pair<LAYOUT, LOAD, OUT, PARTS>(x, blob, pairs_off, y, p, q8, SplitPlace{0, tile_block, (int)blockIdx.y, 0, 0, 0});
+    lossless_pair<LAYOUT, LOAD, OUT, PARTS>(x, blob, pairs_off, y, p, q8, SplitPlace{0, tile_block, (int)blockIdx.y, 0, 0, 0, false});
 }
-template <int LOAD, int OUT, int PARTS>
+template <int LOAD, int PARTS>
 __global__ __launch_bounds__(512) void lossless_pair_sums_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, WG_SPLIT_PARAMS,
                                                                  const uint8_t* __restrict__ blob, size_t pairs_off, int32_t* __restrict__ sums, Problem p) {
     WG_TAKE_GEOMETRY(p, 2);
-    lossless_pair<WG_NHWC, LOAD, OUT, PARTS>(x, blob, pairs_off, sums, p, Int8Epilogue{nullptr, 0, 0, 0, 0},
+    lossless_pair<WG_NHWC, LOAD, kOutSums, PARTS>(x, blob, pairs_off, sums, p, Int8Epilogue{nullptr, 0, 0, 0, 0},
                                            place_split(s_across, s_packed));
 }
 
@@ -798,7 +807,7 @@ __global__ __launch_bounds__(512) void scaled_sums_kernel(const int8_t* __restri
         constexpr int plane = kTileBlock * kBlockFilters / 4;   // in units of four sums
         v4i* const to = reinterpret_cast<v4i*>(sums + split_sums_offset(kAccPlanes, at.split, at.tile_block, at.filter_block, at.tile_blocks, p.Kp)) +
                            (lane & 15) * (kBlockFilters / 4) + 4 * (wave & 1) + (lane >> 4);
-        if (p.through & kThroughSums) products.template store<true>(to, plane); else products.template store<false>(to, plane);
+        if (at.through) products.template store<true>(to, plane); else products.template store<false>(to, plane);
     };
     switch (wave >> 1) {
         case 0: blocks_of(std::integral_constant<int, 0>{}); break;
@@ -825,9 +834,12 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
 bool in_quarters(const Problem& p, int splits) {
     return (long long)ceil_div(p.T, kTileBlock) * ceil_div(p.K, Stage<4>::kFilters) * splits <= compute_units();
 }
+// The splits' sums, which the next kernel reads from every XCD, are written through the L2 (write_out) where they are not few: 512 -> 512 at 14x14,
+// N = 1 (4 and 9 MB), both kernels, scaled 15.2 us, through 13.3, lossless 10.4, 10.2; 128 -> 64 at 14x14, N = 2 (0.3 MB) 9.1, 9.4.
+inline bool sums_through(const Problem& p, int mode, int splits) { return split_partial_bytes(p, mode, splits) >= sizeof(int32_t) * kThroughFewest; }
 inline SplitGrid split_grid(const Problem& p, int blocks, int splits, int mode, int filters = kBlockFilters) {
     const int tile_blocks = ceil_div(p.T, kTileBlock);
-    return SplitGrid(tile_blocks, ceil_div(p.K, filters), splits, blocks, mode == WG_LOSSLESS && tile_blocks <= 10);
+    return SplitGrid(tile_blocks, ceil_div(p.K, filters), splits, blocks, mode == WG_LOSSLESS && tile_blocks <= 10, sums_through(p, mode, splits));
 }
 
 // How the patches of a tensor are read (see kLoadDwords ..).
@@ -889,25 +901,16 @@ hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t*
     }
 }
 
-// The splits' sums, which the next kernel reads from every XCD, are written through the L2 (write_out) where they are not few: 512 -> 512 at 14x14,
-// N = 1 (4 and 9 MB), both kernels, scaled 15.2 us, through 13.3, lossless 10.4, 10.2; 128 -> 64 at 14x14, N = 2 (0.3 MB) 9.1, 9.4.
-static bool sums_through(const Problem& p, int mode, int splits) { return split_partial_bytes(p, mode, splits) >= sizeof(int32_t) * kThroughFewest; }
-
 hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits,
                                      hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
-    auto launch = [&](auto LOAD, auto OUT, auto PARTS) -> hipError_t {
+    auto form = [&](auto LOAD, auto PARTS) -> hipError_t {
         static LdsLimitOnce lds_limit;   // per instance
-        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_sums_kernel<LOAD, OUT, PARTS>), pair_lds_bytes<PARTS>())) return e;
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&lossless_pair_sums_kernel<LOAD, PARTS>), pair_lds_bytes<PARTS>())) return e;
         const SplitGrid grid = split_grid(p, blocks, splits, WG_LOSSLESS, Stage<PARTS>::kFilters);
-        lossless_pair_sums_kernel<LOAD, OUT, PARTS><<<grid.grid, 64 * kWaves, pair_lds_bytes<PARTS>(), s>>>(
+        lossless_pair_sums_kernel<LOAD, PARTS><<<grid.grid, 64 * kWaves, pair_lds_bytes<PARTS>(), s>>>(
             x, WG_GEOMETRY(p), WG_SPLIT(grid), static_cast<const uint8_t*>(blob), bl.pairs_off, sums, p);
         return hipGetLastError();
-    };
-    // (a kernel each: with a branch 256 -> 128 at 14x14, N = 2, took 8.4 us instead of 7.9)
-    auto form = [&](auto LOAD, auto PARTS) {
-        return sums_through(p, WG_LOSSLESS, splits) ? launch(LOAD, std::integral_constant<int, kOutSumsThrough>{}, PARTS)
-                                                    : launch(LOAD, std::integral_constant<int, kOutSums>{}, PARTS);
     };
     auto go = [&](auto LOAD) {
         return in_quarters(p, splits) ? form(LOAD, std::integral_constant<int, 4>{}) : form(LOAD, std::integral_constant<int, 2>{});
@@ -923,14 +926,12 @@ hipError_t launch_lossless_pair_sums(const int8_t* x, const void* blob, int32_t*
 hipError_t launch_scaled_sums(const int8_t* x, const void* blob, int32_t* sums, const Problem& p, int layout, int blocks, int splits, hipStream_t s) {
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_SCALED);
     const SplitGrid grid = split_grid(p, blocks, splits, WG_SCALED);
-    Problem through = p;
-    through.through = sums_through(p, WG_SCALED, splits) ? kThroughSums : 0;
     auto go = [&](auto LOAD) -> hipError_t {
         static LdsLimitOnce lds_limit;   // per LOAD
         constexpr int lds_bytes = kPlanesBytes + 4 * kRawQuad;
         if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&scaled_sums_kernel<LOAD>), lds_bytes)) return e;
         scaled_sums_kernel<LOAD><<<grid.grid, 64 * kWaves, lds_bytes, s>>>(x, WG_GEOMETRY(p), WG_SPLIT(grid), static_cast<const uint8_t*>(blob),
-                                                                              bl.planes_off, sums, through);
+                                                                              bl.planes_off, sums, p);
         return hipGetLastError();
     };
     using std::integral_constant;

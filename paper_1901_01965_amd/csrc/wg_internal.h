@@ -50,7 +50,7 @@ struct Problem {
     int Cf;          // channels the filters were packed for; C, the pixel stride of channels-last activations, is larger only
                      // where the activations are a padded channels-last copy
     int TH, TW, T;   // tiles per column / row, total tiles
-    int through;     // which outputs are written through the L2: kThroughRows | kThroughPlanes | kThroughSums (write_out, kernel_common.h)
+    int through;     // which outputs are written through the L2: kThroughRows | kThroughPlanes (write_out, kernel_common.h)
     int CB;          // ceil(C / 64)
     int Kp;          // K padded to kFilterPad
     FastDiv div_tw, div_th;   // by TW and by TH
@@ -94,7 +94,7 @@ inline size_t round_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
 // K = 100, 18 MB 0.87, 38 MB 0.95 of the time, 50 MB 2.1).  Channel-major rows of W outputs are parts of lines: from 16 outputs on (7x7 1.05,
 // 14x14 1.03 of the time, 28x28 0.98), and above 16 MB from 48 on (128 -> 128, N = 128 at 28x28, 51 MB, 1.04 - 1.06; 64 -> 64, N = 64 at
 // 56x56 0.91).
-constexpr int kThroughRows = 1, kThroughPlanes = 2, kThroughSums = 4, kThroughFewest = 512 << 10;   // outputs
+constexpr int kThroughRows = 1, kThroughPlanes = 2, kThroughFewest = 512 << 10;   // outputs
 inline int writes_through(int N, int H, int W, int K) {
     const long long outputs = (long long)N * H * W * K;
     if (outputs < kThroughFewest || outputs > (K % 32 == 0 ? 16 << 20 : 6 << 20)) return 0;
