@@ -106,11 +106,17 @@ __device__ inline uint32_t pack_bytes(v4i v) {
 // next is slower by as much or more, direct 256 -> 256 43.9.)  Which outputs: writes_through (wg_internal.h).  int8 outputs, a fourth of the
 // bytes in parts of lines, gain in the limb-pair kernel (64 -> 64 at 56x56, N = 8 7.3 / 6.9) and first layers (N = 16 at 224x224 38.6 / 35.9), and are
 // level or behind elsewhere (0.98 - 1.03); so are the requantisation's (1.00 - 1.03) and channels-last copies (1.02 - 1.10).
+// The compiler's own stores, not assembly: it keeps what overwrites a 16-byte store's data two wait states behind it (gfx950), which it does not
+// do for a store that it cannot see.
 template <class T>
 __device__ inline void write_out(T* at, T v) {
     static_assert(sizeof(T) == 16 || sizeof(T) == 4, "dwords");
-    if constexpr (sizeof(T) == 16) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(at), "v"(v) : "memory");
-    else                           asm volatile("global_store_dword %0, %1, off sc1" ::"v"(at), "v"(v) : "memory");
+    if constexpr (sizeof(T) == 16) {
+        typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_global_store_b128((v4u __attribute__((address_space(1)))*)at, __builtin_bit_cast(v4u, v), "agent");
+    } else {
+        __hip_atomic_store((T __attribute__((address_space(1)))*)at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 template <bool THROUGH, class T>
 __device__ inline void write_as(T* at, T v) {
