@@ -54,6 +54,7 @@ def load_library():
         "winograd_debug_stream_variant": (i, [i]),
         "winograd_debug_narrow_variant": (i, [i]),
         "winograd_conv2d_path": (i, [i, i, i, i, i, i]),
+        "winograd_debug_writes_through": (i, [i, i, i, i, i, i, sz]),
         "winograd_debug_tile_decode": (i, [i, i, i, i, i, i, vp]),
         "winograd_packed_filter_bytes": (sz, [i, i, i]),
         "winograd_workspace_bytes": (sz, [i, i, i, i, i, i]),
@@ -112,7 +113,7 @@ def _done(result, where):
 
 EXPORTED_SYMBOLS = (
     "winograd_status_string", "winograd_num_activation_planes", "winograd_num_filter_planes",
-    "winograd_debug_force_path", "winograd_debug_stream_workgroups", "winograd_debug_lossless_variant", "winograd_debug_scaled_variant", "winograd_debug_stream_variant", "winograd_debug_narrow_variant", "winograd_conv2d_path", "winograd_debug_tile_decode",
+    "winograd_debug_force_path", "winograd_debug_stream_workgroups", "winograd_debug_lossless_variant", "winograd_debug_scaled_variant", "winograd_debug_stream_variant", "winograd_debug_narrow_variant", "winograd_conv2d_path", "winograd_debug_tile_decode", "winograd_debug_writes_through",
     "winograd_packed_filter_bytes", "winograd_workspace_bytes", "winograd_filter_transform",
     "winograd_packed_filter_check", "winograd_conv2d_int8", "winograd_conv2d_int8_requant",
     "winograd_static_workspace_limit", "winograd_conv2d_int8_static_workspace",

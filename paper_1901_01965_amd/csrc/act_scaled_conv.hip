@@ -5,6 +5,7 @@
 // products, and the products run beside the next channel block's transform.
 #include "act_scale.h"
 #include "roles_conv.h"
+#include "write_through.h"
 
 namespace wg {
 namespace {
@@ -281,7 +282,7 @@ hipError_t launch_act_scaled_roles(const RolesCall& c, const uint32_t* factors, 
         return hipGetLastError();
     };
     using std::integral_constant;
-    const bool through = int32_out(c.p, c.layout) == kOutThrough;
+    const bool through = f4_through(c.p, c.y, c.layout);
     auto go = [&](auto L, auto W, auto NARROW) {
         return through ? launch(L, integral_constant<int, kOutThrough>{}, W, NARROW) : launch(L, integral_constant<int, kOutInt32>{}, W, NARROW);
     };

@@ -4,6 +4,7 @@
 
 #include "api_checks.h"
 #include "host_api.h"
+#include "write_through.h"
 
 using namespace wg;
 
@@ -210,6 +211,19 @@ int winograd_conv2d_path(int N, int C, int H, int W, int K, int mode) {
     if (!valid_mode(mode)) return WG_EINVAL;
     if (int st = check_shape(N, C, H, W, K)) return st;
     return use_fused() ? 2 : 1;
+}
+
+int winograd_debug_writes_through(int kernel, int N, int C, int H, int W, int K, size_t address) {
+    if (kernel < 0 || kernel > 3) return WG_EINVAL;
+    if (int st = check_shape(N, C, H, W, K)) return st;
+    int32_t* const y = reinterpret_cast<int32_t*>(address);
+    const Problem p = kernel == 2 ? make_problem_f2(N, C, H, W, K) : make_problem(N, C, H, W, K);
+    switch (kernel) {
+        case 0: return f4_through(p, y, WG_NHWC);
+        case 1: return f4_through(p, y, WG_NCHW);
+        case 2: return f2_through(p, y);
+        default: return direct_through(p, y, WG_NHWC);
+    }
 }
 
 int winograd_debug_tile_decode(int N, int C, int H, int W, int K, int t, int* out3_host) {

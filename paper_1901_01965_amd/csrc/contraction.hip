@@ -46,15 +46,15 @@ struct BlockLoader {
                                 int lane) {
         constexpr int NP = MODE == WG_LOSSLESS ? 138 : 46;
         V = V_; U = U_;
-        a_plane_stride = (size_t)p.CB * p.padded_tiles() * kCBlock;
-        a_cb_stride = (size_t)p.padded_tiles() * kCBlock;
+        a_plane_stride = (size_t)p.CB * p.Tp * kCBlock;
+        a_cb_stride = (size_t)p.Tp * kCBlock;
         b_cb_stride = (size_t)(p.Kp >> 4) * NP * kFilterFragBytes;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int row = wave * 32 + i * 16 + (lane >> 2);
             const int chunk = (lane & 3) ^ swizzle(row);
             // rows beyond the padded extent are clamped: their products are never stored
-            const int t = min(t0 + row, p.padded_tiles() - 1), k = min(k0 + wave * 32 + i * 16 + (lane & 15), p.Kp - 1);
+            const int t = min(t0 + row, p.Tp - 1), k = min(k0 + wave * 32 + i * 16 + (lane & 15), p.Kp - 1);
             a_off[i] = t * kCBlock + chunk * 16;
             b_off[i] = (int)filter_plane_offset(0, 0, k, (lane >> 4) * 16, p.Kp, NP);   // a whole fragment, kept in its own order
             lds_off[i] = (wave * 32 + i * 16) * kCBlock;
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(512) void contraction_kernel(const int8_t* __restri
         multiply_stage(fb);
     }
 
-    int32_t* Mu = M + (size_t)unit * p.padded_tiles() * p.Kp;
+    int32_t* Mu = M + (size_t)unit * p.Tp * p.Kp;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int k = k0 + wn * 64 + j * 32 + (lane & 31);
@@ -285,7 +285,7 @@ __global__ void unpack_accumulators_kernel(const int32_t* M, int32_t* dense, Pro
     int k = (int)(i % p.K);
     int t = (int)((i / p.K) % p.T);
     int pl = (int)(i / ((size_t)p.K * p.T));
-    dense[i] = accumulator_plane(M, (size_t)p.padded_tiles() * p.Kp, (size_t)t * p.Kp + k, mode, pl);
+    dense[i] = accumulator_plane(M, (size_t)p.Tp * p.Kp, (size_t)t * p.Kp + k, mode, pl);
 }
 
 template <int MODE>

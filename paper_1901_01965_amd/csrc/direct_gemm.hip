@@ -18,6 +18,7 @@
 #include <algorithm>
 
 #include "kernel_common.h"
+#include "write_through.h"
 
 namespace wg {
 namespace {
@@ -293,12 +294,13 @@ hipError_t launch_form(int form, const int8_t* x, const int8_t* w, int32_t* y, c
 
 }  // namespace
 
+bool direct_through(const Problem& p, const int32_t* y, int layout) { return layout == WG_NHWC && writes_through(p, y) & kThroughRows; }
 bool direct_gemm_applies(const Problem& p) { return choose_form(p) >= 0; }
 
 hipError_t launch_direct_gemm(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, int layout, hipStream_t s) {
     const int form = choose_form(p);
     if (layout != WG_NHWC) return launch_form<WG_NCHW, false>(form, x, w, y, p, s);
-    return p.through & kThroughRows ? launch_form<WG_NHWC, true>(form, x, w, y, p, s) : launch_form<WG_NHWC, false>(form, x, w, y, p, s);
+    return direct_through(p, y, layout) ? launch_form<WG_NHWC, true>(form, x, w, y, p, s) : launch_form<WG_NHWC, false>(form, x, w, y, p, s);
 }
 
 }  // namespace wg

@@ -13,6 +13,7 @@
 // reverse-scaling factors are parked in LDS at the start, the blob header is compared only before the store, and pixels outside the
 // image arrive as zeros.
 #include "kernel_common.h"
+#include "write_through.h"
 
 namespace wg {
 namespace {
@@ -355,7 +356,7 @@ hipError_t launch_f2_fast(const int8_t* x, int is_unsigned, int zero_point, cons
             return hipGetLastError();
         };
         if constexpr (!Q && L == WG_NHWC)
-            if (p.through & kThroughRows) return run(std::true_type{});   // (see write_out; a branch in the kernel cost small layers 2 - 5 %)
+            if (f2_through(p, y)) return run(std::true_type{});   // (see write_out; a branch in the kernel cost small layers 2 - 5 %)
         return run(std::false_type{});
     };
     auto go = [&](auto L, auto M, auto Q, auto N, const auto& enc) {

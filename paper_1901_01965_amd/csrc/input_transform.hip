@@ -30,8 +30,8 @@ __global__ __launch_bounds__(256) void input_transform_kernel(const int8_t* __re
     decode_tile(p, t, n, ty, tx);
     constexpr int SPLIT = MODE == WG_LOSSLESS ? kSplitKaratsuba : kSplitTwoLimb;
     OperandSplitter<SPLIT, GlobalPlaneSink> out;
-    out.sink.base = V + (((size_t)cb * p.padded_tiles() + t) * kCBlock + 4 * cq);
-    out.sink.plane_stride = (size_t)p.CB * p.padded_tiles() * kCBlock;
+    out.sink.base = V + (((size_t)cb * p.Tp + t) * kCBlock + 4 * cq);
+    out.sink.plane_stride = (size_t)p.CB * p.Tp * kCBlock;
     transform_tile<LAYOUT, VEC4, SPLIT>(x, p, n, ty, tx, cb * kCBlock + 4 * cq, out);
 }
 
@@ -42,7 +42,7 @@ __global__ void unpack_activation_planes_kernel(const int8_t* V, int8_t* dense, 
     int c = (int)(i % p.C);
     int t = (int)((i / p.C) % p.T);
     int pl = (int)(i / ((size_t)p.C * p.T));
-    dense[i] = V[(((size_t)pl * p.CB + (c >> 6)) * p.padded_tiles() + t) * kCBlock + (c & 63)];
+    dense[i] = V[(((size_t)pl * p.CB + (c >> 6)) * p.Tp + t) * kCBlock + (c & 63)];
 }
 
 }  // namespace

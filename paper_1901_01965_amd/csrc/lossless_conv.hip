@@ -35,6 +35,7 @@
 #include "kernel_common.h"
 #include "pair_products.h"
 #include "roles_conv.h"
+#include "write_through.h"
 
 namespace wg {
 namespace {

@@ -18,7 +18,7 @@ __global__ __launch_bounds__(256) void output_transform_kernel(const int32_t* __
     const int k = blockIdx.y * 64 + (threadIdx.x & 63);
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (k >= p.K || t >= p.T) return;
-    const size_t plane = (size_t)p.padded_tiles() * p.Kp;
+    const size_t plane = (size_t)p.Tp * p.Kp;
     const int32_t* m = M + (size_t)t * p.Kp + k;
 
     int re[16], cr[10], ci[10];

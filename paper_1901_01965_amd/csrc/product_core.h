@@ -478,7 +478,6 @@ __device__ __forceinline__ void locate_tile(StoreContext& sc, const Problem& p, 
 // What a kernel writes: int32, requantised int8, or int32 written through the L2 (write_out); which of the first and the last is chosen
 // on the host, so that a kernel has one of them (with both, and a branch, small layers took 1 % longer).
 constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutThrough = 2;
-inline int int32_out(const Problem& p, int layout) { return p.through & (layout == WG_NHWC ? kThroughRows : kThroughPlanes) ? kOutThrough : kOutInt32; }
 
 // Stores the 16 tiles x 32 filters (from kbase) that were staged (a barrier lies between): int32 to y, or requantised
 // (and pooled) to int8 at q8.out.  ADD: two halves were staged and are added; otherwise one finished copy (half 0).

@@ -3,6 +3,7 @@
 #pragma once
 #include "product_core.h"
 #include "roles_conv.h"
+#include "write_through.h"
 
 namespace wg {
 namespace {
@@ -193,7 +194,7 @@ hipError_t launch_roles(const int8_t* x, const ENC& enc, const uint8_t* blob, co
 template <int MODE>
 hipError_t launch_roles_mode(const RolesCall& c, bool wide, hipStream_t s) {
     using std::integral_constant;
-    const bool through = int32_out(c.p, c.layout) == kOutThrough;
+    const bool through = f4_through(c.p, c.y, c.layout);
     auto go = [&](auto L, auto Q8, auto PW, const auto& enc) {
         auto launch = [&](auto OUT) { return launch_roles<L, MODE, OUT, PW>(c.x, enc, c.blob, c.bl, c.y, c.p, c.q8, s); };
         if constexpr (Q8) return launch(integral_constant<int, kOutInt8>{});

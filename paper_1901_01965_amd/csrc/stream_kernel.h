@@ -4,6 +4,7 @@
 #include "pair_products.h"
 #include "product_core.h"
 #include "roles_conv.h"
+#include "write_through.h"
 
 namespace wg {
 namespace {
@@ -422,7 +423,7 @@ hipError_t launch_stream_mode(const RolesCall& c, StreamForm which, hipStream_t 
                 // through 24.8; seven and thirteen level, channel-major thirteen 119 and 149)
                 const int tile_blocks = ceil_div(c.p.T, kFusedTiles);
                 const bool few = FORM == kStreamEight || tile_blocks <= 4 * stream_workgroups(tile_blocks, ceil_div(c.p.K, stream_filters<FORM>()));
-                return few && int32_out(c.p, c.layout) == kOutThrough ? launch_stream<L, MODE, kOutThrough, FORM>(c, enc, s)
+                return few && f4_through(c.p, c.y, c.layout) ? launch_stream<L, MODE, kOutThrough, FORM>(c, enc, s)
                                                                       : launch_stream<L, MODE, kOutInt32, FORM>(c, enc, s);
             }
         };

@@ -50,11 +50,10 @@ struct Problem {
     int Cf;          // channels the filters were packed for; C, the pixel stride of channels-last activations, is larger only
                      // where the activations are a padded channels-last copy
     int TH, TW, T;   // tiles per column / row, total tiles
-    int through;     // which outputs are written through the L2: kThroughRows | kThroughPlanes (write_out, kernel_common.h)
+    int Tp;          // T padded to kTilePad
     int CB;          // ceil(C / 64)
     int Kp;          // K padded to kFilterPad
     FastDiv div_tw, div_th;   // by TW and by TH
-    __host__ __device__ inline int padded_tiles() const { return (T + kTilePad - 1) / kTilePad * kTilePad; }
 };
 // (four bytes more shifted what a kernel loads late to another line: 64 -> 64 at 28x28, N = 1, scaled, 7.4 us instead of 7.25)
 static_assert(sizeof(Problem) == 64, "one line of a kernel's arguments");
@@ -88,26 +87,14 @@ inline size_t round_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
 #define WG_TAKE_GEOMETRY(p, log2_tile) \
     take_geometry(p, g_n, g_c, g_h, g_w, log2_tile, FastDiv{g_tw_mul, g_tw_shift}, FastDiv{g_th_mul, g_th_shift})
 
-// Where writing through pays (write_out).  Few outputs are written back in no time (64 -> 64 at 56x56, N = 1, 0.8 MB, scaled 7.43 us,
-// through 7.54, direct 4.13 and 4.18); of more than 64 MB most are written back while the kernel runs (102 and 205 MB 0.98 - 1.04 of the time);
-// lines that are written in parts (channels-last, K % 32 != 0) cost the memory a read each where they are many (direct convolution,
-// K = 100, 18 MB 0.87, 38 MB 0.95 of the time, 50 MB 2.1).  Channel-major rows of W outputs are parts of lines: from 16 outputs on (7x7 1.05,
-// 14x14 1.03 of the time, 28x28 0.98), and above 16 MB from 48 on (128 -> 128, N = 128 at 28x28, 51 MB, 1.04 - 1.06; 64 -> 64, N = 64 at
-// 56x56 0.91).
-constexpr int kThroughRows = 1, kThroughPlanes = 2, kThroughFewest = 512 << 10;   // outputs
-inline int writes_through(int N, int H, int W, int K) {
-    const long long outputs = (long long)N * H * W * K;
-    if (outputs < kThroughFewest || outputs > (K % 32 == 0 ? 16 << 20 : 6 << 20)) return 0;
-    return kThroughRows | (W >= 16 && (W >= 48 || outputs <= 4 << 20) ? kThroughPlanes : 0);
-}
 inline Problem make_problem(int N, int C, int H, int W, int K) {
     Problem p;
     p.N = N; p.C = p.Cf = C; p.H = H; p.W = W; p.K = K;
     p.TH = ceil_div(H, 4); p.TW = ceil_div(W, 4);
     p.T = N * p.TH * p.TW;
+    p.Tp = ceil_div(p.T, kTilePad) * kTilePad;
     p.CB = ceil_div(C, kCBlock);
     p.Kp = ceil_div(K, kFilterPad) * kFilterPad;
-    p.through = writes_through(N, H, W, K);
     p.div_tw = make_fast_div((uint32_t)p.TW);
     p.div_th = make_fast_div((uint32_t)p.TH);
     return p;
@@ -229,6 +216,7 @@ inline Problem make_problem_f2(int N, int C, int H, int W, int K) {
     Problem p = make_problem(N, C, H, W, K);
     p.TH = ceil_div(H, 2); p.TW = ceil_div(W, 2);
     p.T = N * p.TH * p.TW;
+    p.Tp = ceil_div(p.T, kTilePad) * kTilePad;
     p.div_tw = make_fast_div((uint32_t)p.TW);
     p.div_th = make_fast_div((uint32_t)p.TH);
     return p;
@@ -261,8 +249,8 @@ struct WorkspaceLayout {
 inline WorkspaceLayout workspace_layout(const Problem& p, int mode) {
     WorkspaceLayout w;
     w.v_off = 0;
-    w.m_off = round_up((size_t)num_activation_planes(mode) * p.CB * p.padded_tiles() * kCBlock, 256);
-    w.total = w.m_off + (size_t)(mode == WG_LOSSLESS ? kMaxWorkspacePlanes : kAccPlanes) * p.padded_tiles() * p.Kp * sizeof(int32_t);
+    w.m_off = round_up((size_t)num_activation_planes(mode) * p.CB * p.Tp * kCBlock, 256);
+    w.total = w.m_off + (size_t)(mode == WG_LOSSLESS ? kMaxWorkspacePlanes : kAccPlanes) * p.Tp * p.Kp * sizeof(int32_t);
     return w;
 }
 

@@ -1,0 +1,40 @@
+"""Which int32 outputs are written through the L2 (write_through.h): the rule's choice, asked on the host, on either side of each of its lines."""
+import os
+
+import pytest
+
+import paper_1901_01965_amd as wg
+from paper_1901_01965_amd import binding
+
+ROWS, PLANES, F2, DIRECT = range(4)
+BASE = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def through():
+    if not os.path.exists(binding.LIB_PATH):
+        from paper_1901_01965_amd import build
+        build.build()
+    lib = wg.load_library()
+
+    def ask(kernel, N, K, H, W, offset=0, C=64):
+        r = lib.winograd_debug_writes_through(kernel, N, C, H, W, K, BASE + offset)
+        assert r in (0, 1)
+        return bool(r)
+
+    return ask
+
+
+@pytest.mark.parametrize("kernel", [ROWS, PLANES, F2, DIRECT])
+def test_few_and_many_outputs_are_left_to_the_l2(through, kernel):
+    assert not through(kernel, 1, 64, 64, 127) and through(kernel, 1, 64, 64, 128)            # 512 Ki outputs
+    assert through(kernel, 1, 64, 512, 512) and not through(kernel, 1, 64, 512, 528)          # 16 Mi outputs
+
+
+@pytest.mark.parametrize("kernel", [ROWS, PLANES, F2, DIRECT])
+@pytest.mark.parametrize("offset", [4, 16, 48])
+def test_outputs_off_a_64_byte_boundary_are_written_in_parts(through, kernel, offset):
+    """64 outputs per pixel, rows of 64: whole lines on the boundary, none off it."""
+    assert through(kernel, 4, 64, 256, 256) and through(kernel, 4, 64, 256, 256, 64)          # 16 Mi outputs
+    assert not through(kernel, 4, 64, 256, 256, offset)
+    assert through(kernel, 4, 64, 64, 64, offset)                                             # 1 Mi
