@@ -294,7 +294,7 @@ hipError_t launch_form(int form, const int8_t* x, const int8_t* w, int32_t* y, c
 
 }  // namespace
 
-bool direct_through(const Problem& p, const int32_t* y, int layout) { return layout == WG_NHWC && writes_through(p, y) & kThroughRows; }
+bool direct_through(const Problem& p, const int32_t* y, int layout) { return layout == WG_NHWC && rows_through(p, y, 64); }
 bool direct_gemm_applies(const Problem& p) { return choose_form(p) >= 0; }
 
 hipError_t launch_direct_gemm(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, int layout, hipStream_t s) {

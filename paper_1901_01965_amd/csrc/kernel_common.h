@@ -103,7 +103,7 @@ __device__ inline uint32_t pack_bytes(v4i v) {
 // soon as it is stored.  us, plain / through: 128 -> 128 at 28x28, N = 32, scaled 12.7 / 11.8 (with the requantisation that reads it 19.3 / 19.0),
 // 64 -> 64 at 56x56, N = 32 16.7 / 14.8, direct 256 -> 256 at 56x56, N = 16 33.8 / 31.5 (42.5 / 41.4), F(2x2) at 28x28 15.4 / 13.8; partial sums of
 // 512 -> 512 at 14x14, N = 1, scaled, both kernels 15.2 / 13.3.  (Non-temporal stores: as fast by themselves, but what reads the outputs
-// next is slower by as much or more, direct 256 -> 256 43.9.)  Which outputs: writes_through (wg_internal.h).  int8 outputs, a fourth of the
+// next is slower by as much or more, direct 256 -> 256 43.9.)  Which outputs: write_through.h.  int8 outputs, a fourth of the
 // bytes in parts of lines, gain in the limb-pair kernel (64 -> 64 at 56x56, N = 8 7.3 / 6.9) and first layers (N = 16 at 224x224 38.6 / 35.9), and are
 // level or behind elsewhere (0.98 - 1.03); so are the requantisation's (1.00 - 1.03) and channels-last copies (1.02 - 1.10).
 // The compiler's own stores, not assembly: it keeps what overwrites a 16-byte store's data two wait states behind it (gfx950), which it does not
