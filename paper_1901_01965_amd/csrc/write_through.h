@@ -9,9 +9,10 @@ namespace wg {
 // lines that are written in parts (channels-last, K % 32 != 0) cost the memory a read each where they are many.  Where a kernel stores 32 filters of a
 // pixel at once, that begins at 20 MB (of the time, scaled, lossless, both scaled, K = 36 .. 200: 17 MB 0.93 - 1.03, 20 MB 0.97 - 1.08, 24 MB
 // 1.06 - 1.21), unless 64-byte units are whole (K % 16 = 0: 24 MB 0.88 - 0.99, 60 MB 0.91 - 1.03); F(2x2) and direct kernels store 64, 20 MB 0.87 - 1.02,
-// 24 MB 0.93 - 1.13 (K % 16 = 0 0.90 - 1.03, F(2x2) with K = 16 1.05).  Channel-major rows of W outputs are parts of lines: from 16 outputs on (7x7 1.05,
-// 14x14 1.03 of the time, 28x28 0.98), and above 16 MB from 48 on (128 -> 128, N = 128 at 28x28, 51 MB, 1.04 - 1.06; 64 -> 64, N = 64 at
-// 56x56 0.91).
+// 24 MB 0.93 - 1.13 (K % 16 = 0 0.90 - 1.03, F(2x2) with K = 16 1.05).
+// Channel-major rows of W outputs are whole units where W % 16 = 0, whatever K is (16 -> 256 at most, to 60 MB 0.87 - 1.01), else parts: from 20 outputs on,
+// where they are few (8 MB, W = 20 .. 56 0.91 - 1.03; W = 15 .. 19 up to 1.05; 7x7 1.05), from 28 on up to 16 MB (0.91 - 1.03; W = 20 and 24 up to 1.08), not
+// above (W = 28 .. 75, 28 MB 1.02 - 1.21, 60 MB 1.04 - 1.49: 64 -> 64 at 56x56, N = 62, lossless 37.9 us plain, 45.2 through).
 // Memory takes 64 bytes at a time: outputs that start 16 bytes after a multiple of 64, as a view may, are all written in parts (of the
 // time, plain / through: scaled, lossless, both scaled, F(2x2) and direct, 64 -> 64 at 56x56, N = 64 1.21, 1.15, 1.30, 1.25, 1.29, 128 -> 128, N = 40
 // 1.25, 1.20, 1.35, 1.10, 1.50; channel-major 64 -> 64 at 32x64, N = 61 1.12, 1.16; 64 bytes after one 0.87 - 1.03).
@@ -23,10 +24,12 @@ inline bool rows_through(const Problem& p, const void* y, int filters) {
     const long long most = on_unit(y) && p.K % 32 == 0 ? 16 << 20 : on_unit(y) && p.K % 16 == 0 && 2 * p.K >= filters ? 6 << 20 : filters == 64 ? 5 << 20 : 4 << 20;
     return outputs_of(p) >= kThroughFewest && outputs_of(p) <= most;
 }
-inline bool planes_through(const Problem& p, const void* y) {
-    if (outputs_of(p) < kThroughFewest || outputs_of(p) > (p.K % 32 == 0 && on_unit(y) ? 16 << 20 : 6 << 20)) return false;
-    return p.W >= 16 && ((p.W >= 48 && on_unit(y)) || outputs_of(p) <= 4 << 20);
+// The most channel-major outputs that are written through.
+inline long long planes_most(const Problem& p, const void* y) {
+    if (on_unit(y) && p.W % 16 == 0) return 16 << 20;
+    return on_unit(y) && p.W >= 28 ? 4 << 20 : p.W >= 20 ? 2 << 20 : 0;
 }
+inline bool planes_through(const Problem& p, const void* y) { return outputs_of(p) >= kThroughFewest && outputs_of(p) <= planes_most(p, y); }
 inline bool f4_through(const Problem& p, const void* y, int layout) { return layout == WG_NHWC ? rows_through(p, y, 32) : planes_through(p, y); }
 inline bool f2_through(const Problem& p, const void* y) { return rows_through(p, y, 64); }   // channels-last
 bool direct_through(const Problem& p, const int32_t* y, int layout);   // direct_gemm.hip

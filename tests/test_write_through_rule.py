@@ -46,3 +46,13 @@ def test_channels_last_lines_in_parts_are_few(through, kernel, most):
     for K, offset, limit in ((96, 0, 16), (48, 0, 6), (80, 0, 6), (16, 0, 6 if kernel == ROWS else most), (100, 0, most), (36, 0, most), (64, 16, most)):
         pixels = (limit << 20) // K
         assert through(kernel, 1, K, 1, pixels, offset) and not through(kernel, 1, K, 1, pixels + 1, offset), (K, offset)
+
+
+def test_channel_major_rows_in_parts_are_few_and_not_narrow(through):
+    """Mi outputs: rows of whole 64-byte units; of parts from 28, from 20 outputs on, and narrower; off a 64-byte boundary."""
+    for W, offset, limit in ((16, 0, 16), (48, 0, 16), (224, 0, 16), (56, 0, 4), (53, 0, 4), (28, 0, 4), (27, 0, 2), (20, 0, 2), (19, 0, 0), (15, 0, 0),
+                             (7, 0, 0), (64, 16, 2), (56, 4, 2), (16, 4, 0)):
+        for K in (64, 75):
+            rows = (limit << 20) // (K * W)
+            assert limit == 0 or through(PLANES, 1, K, rows, W, offset), (W, offset, K)
+            assert not through(PLANES, 1, K, max(rows + 1, (1 << 20) // (K * W)), W, offset), (W, offset, K)
