@@ -28,7 +28,7 @@ def through():
 @pytest.mark.parametrize("kernel", [ROWS, PLANES, F2, DIRECT])
 def test_few_and_many_outputs_are_left_to_the_l2(through, kernel):
     assert not through(kernel, 1, 64, 64, 127) and through(kernel, 1, 64, 64, 128)            # 512 Ki outputs
-    assert through(kernel, 1, 64, 512, 512) and not through(kernel, 1, 64, 512, 528)          # 16 Mi outputs
+    assert through(kernel, 64, 64, 64, 64) and not through(kernel, 65, 64, 64, 64)            # 16 Mi outputs
 
 
 @pytest.mark.parametrize("kernel", [ROWS, PLANES, F2, DIRECT])
@@ -43,9 +43,9 @@ def test_outputs_off_a_64_byte_boundary_are_written_in_parts(through, kernel, of
 @pytest.mark.parametrize("kernel,most", [(ROWS, 4), (F2, 5), (DIRECT, 5)])
 def test_channels_last_lines_in_parts_are_few(through, kernel, most):
     """Mi outputs: K a multiple of 32, of 16, of neither; and of 32, but off a 64-byte boundary."""
-    for K, offset, limit in ((96, 0, 16), (48, 0, 6), (80, 0, 6), (16, 0, 6 if kernel == ROWS else most), (100, 0, most), (36, 0, most), (64, 16, most)):
+    for K, offset, limit in ((96, 0, 16), (48, 0, 6), (16, 0, 6 if kernel == ROWS else most), (36, 0, most), (60, 0, most), (64, 16, most)):
         pixels = (limit << 20) // K
-        assert through(kernel, 1, K, 1, pixels, offset) and not through(kernel, 1, K, 1, pixels + 1, offset), (K, offset)
+        assert through(kernel, 1, K, pixels, 1, offset) and not through(kernel, 1, K, pixels + 1, 1, offset), (K, offset)
 
 
 def test_channel_major_rows_in_parts_are_few_and_not_narrow(through):
@@ -56,3 +56,18 @@ def test_channel_major_rows_in_parts_are_few_and_not_narrow(through):
             rows = (limit << 20) // (K * W)
             assert limit == 0 or through(PLANES, 1, K, rows, W, offset), (W, offset, K)
             assert not through(PLANES, 1, K, max(rows + 1, (1 << 20) // (K * W)), W, offset), (W, offset, K)
+
+
+@pytest.mark.parametrize("C,K,N,H,W", [(64, 84, 16, 32, 32), (64, 100, 32, 32, 32), (128, 72, 4, 64, 64), (64, 84, 13, 56, 56), (64, 80, 15, 56, 56),
+                                       (64, 132, 16, 32, 32)])
+def test_direct_filter_blocks_of_one_xcd_do_not_share_lines(through, C, K, N, H, W):
+    """Pixel blocks a multiple of eight, so that the filter blocks of one go to one XCD: lines that two of them write stay in its L2."""
+    assert not through(DIRECT, N, K, H, W, 0, C)
+    assert through(DIRECT, N, K // 32 * 32, H, W, 0, C)                    # whole lines
+    assert through(F2, N, K, H, W, 0, C)
+
+
+def test_direct_lines_of_different_xcds_or_of_one_workgroup(through):
+    assert through(DIRECT, 12, 84, 56, 56) and through(DIRECT, 14, 84, 56, 56)      # 147 and 172 pixel blocks
+    assert through(DIRECT, 32, 48, 32, 32) and through(DIRECT, 32, 36, 32, 32)      # one filter block
+    assert not through(DIRECT, 16, 96, 32, 32, 64)                                  # a base in the middle of a line
