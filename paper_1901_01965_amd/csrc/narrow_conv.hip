@@ -23,6 +23,7 @@
 #include "kernel_common.h"
 #include "output_transform_core.h"
 #include "wg_internal.h"
+#include "write_through.h"
 
 #include <algorithm>
 #include <atomic>
@@ -297,8 +298,8 @@ struct Factor {   // r, and q in the bits that a 24-bit multiply ignores; what i
 };
 constexpr int kFactorBytes = 64 * kEntries * (int)sizeof(Factor);   // [filter][entry]: 52 dwords apart, sixteen filters in different banks
 
-// grid: (ceil(T / (16 groups)), Kp / 64), 256 threads.
-template <int MODE, bool Q8>
+// grid: (ceil(T / (16 groups)), Kp / 64), 256 threads.  THROUGH: 16-byte stores go through the L2 (write_out; which: first_layer_through).
+template <int MODE, bool Q8, bool THROUGH>
 __global__ __launch_bounds__(256, 2) void narrow_conv_kernel(const int8_t* __restrict__ x, WG_GEOMETRY_PARAMS, int groups,
                                                              const uint8_t* __restrict__ blob,
                                                              size_t table_off, size_t narrow_off, int32_t* __restrict__ y,
@@ -452,7 +453,7 @@ __global__ __launch_bounds__(256, 2) void narrow_conv_kernel(const int8_t* __res
                     if ((int)I < to.rows && j < to.cols && k0 + f0 < p.K) {
                         v4i* const at = reinterpret_cast<v4i*>(y + ((size_t)to.pixel + (int)I * Wo + j) * p.K + k0 + f0);
                         const v4i v = *reinterpret_cast<const v4i*>(stage + tile * kStagedTileBytes + 256 * j + 4 * f0);
-                        write_out(at, v);
+                        write_as<THROUGH>(at, v);
                     }
                 }
             });
@@ -492,7 +493,7 @@ __global__ __launch_bounds__(256, 2) void narrow_conv_kernel(const int8_t* __res
                 if (i < to.rows && j < to.cols && left > 0) {
                     int8_t* const at = q8.out + ((size_t)to.pixel + i * Wo + j) * p.K + k0 + 16 * piece;
                     if (whole_pieces) {
-                        write_out(reinterpret_cast<v4i*>(at), __builtin_bit_cast(v4i, v));
+                        write_as<THROUGH>(reinterpret_cast<v4i*>(at), __builtin_bit_cast(v4i, v));
                     } else {
                         uint32_t* const dwords = reinterpret_cast<uint32_t*>(at);
                         dwords[0] = v.x;
@@ -574,11 +575,15 @@ hipError_t launch(const int8_t* x, const uint8_t* blob, const BlobLayout& bl, in
     auto lds_bytes = [](int g) {
         return g * 16 * (kTileValuesBytes + (int)sizeof(TilePlace)) + 2 * kStagedGroupBytes + (MODE == WG_SCALED ? kFactorBytes : 0);
     };
-    static LdsLimitOnce lds_limit;   // per template instance
-    if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&narrow_conv_kernel<MODE, Q8>), lds_bytes(kNarrowGroups))) return e;
-    dim3 grid(ceil_div(tile_groups, groups), blocks);
-    narrow_conv_kernel<MODE, Q8><<<grid, 256, lds_bytes(groups), s>>>(x, WG_GEOMETRY(p), groups, blob, bl.table_off, bl.narrow_off, y, p, q8);
-    return hipGetLastError();
+    auto run = [&](auto THROUGH) -> hipError_t {
+        static LdsLimitOnce lds_limit;   // per template instance
+        if (hipError_t e = lds_limit.set(reinterpret_cast<const void*>(&narrow_conv_kernel<MODE, Q8, THROUGH>), lds_bytes(kNarrowGroups))) return e;
+        dim3 grid(ceil_div(tile_groups, groups), blocks);
+        narrow_conv_kernel<MODE, Q8, THROUGH><<<grid, 256, lds_bytes(groups), s>>>(x, WG_GEOMETRY(p), groups, blob, bl.table_off, bl.narrow_off, y, p, q8);
+        return hipGetLastError();
+    };
+    const bool through = Q8 ? first_layer_through(p, q8.out, 1, q8.pool) : first_layer_through(p, y, 4, false);
+    return through ? run(std::true_type{}) : run(std::false_type{});
 }
 
 }  // namespace

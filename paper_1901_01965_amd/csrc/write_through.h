@@ -32,6 +32,15 @@ inline long long planes_most(const Problem& p, const void* y) {
 inline bool planes_through(const Problem& p, const void* y) { return outputs_of(p) >= kThroughFewest && outputs_of(p) <= planes_most(p, y); }
 inline bool f4_through(const Problem& p, const void* y, int layout) { return layout == WG_NHWC ? rows_through(p, y, 32) : planes_through(p, y); }
 inline bool f2_through(const Problem& p, const void* y) { return rows_through(p, y, 64); }   // channels-last
+// First layers on the matrix cores, channels-last, `bytes` 4 (int32) or 1 (int8): 64 filters of the pixels of a tile's row are stored together, so that
+// up to 64 filters are whole units also where one pixel's are not.  Whole, any number of them pays (224x224, N = 1 .. 16, K = 32 .. 256, 6 - 200 MB
+// 0.83 - 1.01 of the time, int8 0.87 - 1.02); int32 parts up to 20 MB (K = 68 .. 200 0.84 - 0.95, 25 MB 0.95 - 1.11; above, up to 1.4: K = 52 at 223x225, N = 16,
+// 49.3 us plain, 69.4 through, 168 at 112x112, N = 24, lossless 71.1 / 89.2), int8 parts up to 32 MB (0.83 - 0.98; 38 - 100 MB 1.01 - 1.09).
+inline bool first_layer_through(const Problem& p, const void* out, int bytes, bool pool) {
+    const long long row = (pool ? 2 : 4) * (long long)p.K * bytes, outputs = pool ? outputs_of(p) / 4 : outputs_of(p);
+    const bool whole = p.K * bytes % 64 == 0 || (p.K <= 64 && p.W % 4 == 0 && row % 64 == 0);
+    return (whole && on_unit(out)) || outputs <= (bytes == 4 ? 5 << 20 : 32 << 20);
+}
 bool direct_through(const Problem& p, const int32_t* y, int layout);   // direct_gemm.hip
 
 }  // namespace wg

@@ -58,3 +58,16 @@ def test_split_channels_equal_the_oracle(shape, mode):
         for image in (x, x[..., ::-1]):
             want = oracle.direct_conv2d(np.ascontiguousarray(image), g) if mode == wg.LOSSLESS else oracle.winograd_conv2d(np.ascontiguousarray(image), g, oracle.SCALED, 127)[0]
             assert np.array_equal(_nchw(wg.winograd_conv2d_int8(_in(image, wg.NHWC, wl.to_nhwc), packed, wg.NHWC), wg.NHWC), want)
+
+
+@pytest.mark.parametrize("N,K,pool", [(24, 96, False), (23, 96, False), (96, 48, True)])   # 33.7, 32.3 and, pooled, 34.0 million: parts of lines beyond 32 Mi, below, beyond
+def test_first_layers_with_many_int8_outputs_equal_the_oracle(N, K, pool):
+    rng = np.random.default_rng(79)
+    H, W = (120, 122) if not pool else (180, 164)
+    x, g = rng.integers(-128, 128, (N, 3, H, W)).astype(np.int8), rng.integers(-128, 128, (K, 3, 3, 3)).astype(np.int8)
+    some = [0, N // 2, N - 1]
+    for mode in (wg.LOSSLESS, wg.SCALED):
+        packed = wg.winograd_filter_transform(_in(g, wg.NHWC, wl.to_krsc), wg.NHWC, mode)
+        got = _nchw(wg.winograd_conv2d_int8_requant(_in(x, wg.NHWC, wl.to_nhwc), packed, 9, True, pool, wg.NHWC)[some], wg.NHWC)
+        want = oracle.direct_conv2d(x[some], g) if mode == wg.LOSSLESS else oracle.winograd_conv2d(x[some], g, oracle.SCALED, 127)[0]
+        assert np.array_equal(got, oracle.requant_relu_pool(want, 9, True, pool))

@@ -6,7 +6,7 @@ import pytest
 import paper_1901_01965_amd as wg
 from paper_1901_01965_amd import binding
 
-ROWS, PLANES, F2, DIRECT = range(4)
+ROWS, PLANES, F2, DIRECT, FIRST, FIRST_INT8, FIRST_POOLED = range(7)
 BASE = 1 << 20
 
 
@@ -17,7 +17,7 @@ def through():
         build.build()
     lib = wg.load_library()
 
-    def ask(kernel, N, K, H, W, offset=0, C=64):
+    def ask(kernel, N, K, H, W, offset=0, C=64):   # (C matters to direct convolution alone)
         r = lib.winograd_debug_writes_through(kernel, N, C, H, W, K, BASE + offset)
         assert r in (0, 1)
         return bool(r)
@@ -71,3 +71,19 @@ def test_direct_lines_of_different_xcds_or_of_one_workgroup(through):
     assert through(DIRECT, 12, 84, 56, 56) and through(DIRECT, 14, 84, 56, 56)      # 147 and 172 pixel blocks
     assert through(DIRECT, 32, 48, 32, 32) and through(DIRECT, 32, 36, 32, 32)      # one filter block
     assert not through(DIRECT, 16, 96, 32, 32, 64)                                  # a base in the middle of a line
+
+
+@pytest.mark.parametrize("kernel,K,W,offset", [
+    (FIRST, 100, 224, 0), (FIRST, 132, 224, 0), (FIRST, 36, 225, 0), (FIRST, 52, 226, 0), (FIRST, 64, 224, 16), (FIRST, 48, 224, 16),
+    (FIRST_INT8, 96, 224, 0), (FIRST_INT8, 48, 225, 0), (FIRST_INT8, 64, 224, 16), (FIRST_POOLED, 16, 224, 0), (FIRST_POOLED, 48, 224, 0), (FIRST_POOLED, 32, 226, 0)])
+def test_first_layers_in_parts_are_few(through, kernel, K, W, offset):
+    limit, per_row = (5 if kernel == FIRST else 32) << 20, K * W // (4 if kernel == FIRST_POOLED else 1)
+    H = limit // per_row // 2 * 2
+    assert through(kernel, 1, K, H, W, offset, 3) and not through(kernel, 1, K, H + 2, W, offset, 3)
+
+
+@pytest.mark.parametrize("kernel,K,W", [
+    (FIRST, 64, 223), (FIRST, 36, 224), (FIRST, 52, 56), (FIRST, 96, 225), (FIRST, 256, 224), (FIRST_INT8, 16, 224), (FIRST_INT8, 48, 224),
+    (FIRST_INT8, 128, 225), (FIRST_POOLED, 32, 224), (FIRST_POOLED, 64, 226)])
+def test_first_layers_of_whole_units_are_written_through(through, kernel, K, W):
+    assert through(kernel, 1, K, 224, W, 0, 3) and through(kernel, 64, K, 224, W, 0, 3)
