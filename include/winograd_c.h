@@ -385,7 +385,7 @@ int winograd_num_filter_planes(int mode);
 /* Host-only: 1 where a convolution writes its outputs at this address through the L2, 0 where not, or a status code.
    kernel: 0 the F(4x4) kernels that transform on waves of their own, channels-last outputs (the streaming one only in short streams),
    1 the same with channel-major outputs, 2 F(2x2) and 3 direct convolution, channels-last, 4 first layers on the matrix cores, 5 the same with int8
-   outputs (K % 16 = 0), 6 pooled. */
+   outputs (K % 16 = 0), 6 pooled, 7 the limb-pair kernel, channel-major. */
 int winograd_debug_writes_through(int kernel, int N, int C, int H, int W, int K, size_t address);
 
 /* Host-only: the (n, ty, tx) the kernels derive from tile index t = (n*TH + ty)*TW + tx for

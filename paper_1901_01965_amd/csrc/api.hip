@@ -214,7 +214,7 @@ int winograd_conv2d_path(int N, int C, int H, int W, int K, int mode) {
 }
 
 int winograd_debug_writes_through(int kernel, int N, int C, int H, int W, int K, size_t address) {
-    if (kernel < 0 || kernel > 6) return WG_EINVAL;
+    if (kernel < 0 || kernel > 7) return WG_EINVAL;
     if (int st = check_shape(N, C, H, W, K)) return st;
     int32_t* const y = reinterpret_cast<int32_t*>(address);
     const Problem p = kernel == 2 ? make_problem_f2(N, C, H, W, K) : make_problem(N, C, H, W, K);
@@ -224,7 +224,9 @@ int winograd_debug_writes_through(int kernel, int N, int C, int H, int W, int K,
         case 2: return f2_through(p, y);
         case 3: return direct_through(p, y, WG_NHWC);
         case 4: return first_layer_through(p, y, 4, false);
-        default: return first_layer_through(p, y, 1, kernel == 6);
+        case 5: return first_layer_through(p, y, 1, false);
+        case 6: return first_layer_through(p, y, 1, true);
+        default: return pair_planes_through(p, y);
     }
 }
 

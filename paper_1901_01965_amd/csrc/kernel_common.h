@@ -122,6 +122,10 @@ template <bool THROUGH, class T>
 __device__ inline void write_as(T* at, T v) {
     if constexpr (THROUGH) write_out(at, v); else *at = v;
 }
+// What a kernel writes: int32, requantised int8, int32 written through the L2, or, limb-pair kernel, its channels' part of the sums (kOutSums).  Which
+// of the first and the third is chosen on the host, so that a kernel has one of them (with both, and a branch, small layers took 1 % longer).
+constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutThrough = 2, kOutSums = 3;
+
 // Patch loads of the role-specialised kernels go through a buffer descriptor over the activation
 // tensor: a load whose offset lies beyond the tensor returns zero, so a pixel outside the image
 // (pad 1, ragged tiles) is an offset that can never be in range instead of a select per pixel and

@@ -337,7 +337,6 @@ struct RawPatch {
 // OUT kOutSums: the workgroup takes `blocks` channel blocks, those of split bz, and leaves the sum of its outputs,
 // before the rescale by 2^-4, at y as int32 [split][tile block][32 filters][tile][output 4i+j][filter] (the output transform is
 // linear, so these add up to the whole; sums_finish_kernel adds, rescales and stores).
-constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutSums = 2;
 
 // Where a workgroup works.  Not split: the grid's own numbers, all channel blocks.  Split channels: a grid of ceil(T/16) x ceil(K/32) x
 // splits.  Every tile block reads all filters, so in lossless mode the splits are dealt out first and the tile blocks last, which brings more of the
@@ -544,11 +543,9 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
                 const int k4 = kQuads / 2 * (tid >> 8) + g;
                 const v4i v = staged(4 * i + j, tile, k4);
                 int32_t* const at = first(y, k4, h, w);
-                // (always through: at W = 14 level to 1 % behind, 100 -> 75 at 37x53 0.96, 64 -> 64 at 128x128 0.91 of the time; with a choice 16 -> 16
-                // at 16x16 took 1 % longer)
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    if (k0 + 4 * k4 + c < p.K) write_out(at + c * plane, (int32_t)v[c]);
+                    if (k0 + 4 * k4 + c < p.K) write_as<OUT == kOutThrough>(at + c * plane, (int32_t)v[c]);
             }
         } else if (q8.pool) {
             // thread: one pooled pixel of a tile, four filters
@@ -888,7 +885,10 @@ hipError_t launch_lossless_pair_conv(const int8_t* x, const void* blob, int32_t*
     const BlobLayout bl = blob_layout(p.Kp, p.Cf, WG_LOSSLESS);
     const uint8_t* b = static_cast<const uint8_t*>(blob);
     auto form = [&](auto LAYOUT, auto LOAD, auto PARTS) {
-        return q8.out != nullptr ? launch<LAYOUT, LOAD, kOutInt8, PARTS>(x, b, bl, y, p, q8, s) : launch<LAYOUT, LOAD, kOutInt32, PARTS>(x, b, bl, y, p, q8, s);
+        if (q8.out != nullptr) return launch<LAYOUT, LOAD, kOutInt8, PARTS>(x, b, bl, y, p, q8, s);
+        if constexpr (LAYOUT == WG_NCHW)
+            if (pair_planes_through(p, y)) return launch<LAYOUT, LOAD, kOutThrough, PARTS>(x, b, bl, y, p, q8, s);
+        return launch<LAYOUT, LOAD, kOutInt32, PARTS>(x, b, bl, y, p, q8, s);
     };
     auto go = [&](auto LAYOUT, auto LOAD) {
         return in_quarters(p, 1) ? form(LAYOUT, LOAD, std::integral_constant<int, 4>{}) : form(LAYOUT, LOAD, std::integral_constant<int, 2>{});

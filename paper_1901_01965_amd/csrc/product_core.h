@@ -475,10 +475,6 @@ __device__ __forceinline__ void locate_tile(StoreContext& sc, const Problem& p, 
     sc.my_origin = t >= p.T ? -1 : LAYOUT == WG_NHWC ? ((n * p.H + 4 * ty) * p.W + 4 * tx) * p.K : (n * p.K * p.H + 4 * ty) * p.W + 4 * tx;
 }
 
-// What a kernel writes: int32, requantised int8, or int32 written through the L2 (write_out); which of the first and the last is chosen
-// on the host, so that a kernel has one of them (with both, and a branch, small layers took 1 % longer).
-constexpr int kOutInt32 = 0, kOutInt8 = 1, kOutThrough = 2;
-
 // Stores the 16 tiles x 32 filters (from kbase) that were staged (a barrier lies between): int32 to y, or requantised
 // (and pooled) to int8 at q8.out.  ADD: two halves were staged and are added; otherwise one finished copy (half 0).
 // Any K and either layout; 16-byte (int8: 4- or 16-byte) stores where K and the alignment allow.

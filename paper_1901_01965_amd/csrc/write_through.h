@@ -32,6 +32,9 @@ inline long long planes_most(const Problem& p, const void* y) {
 inline bool planes_through(const Problem& p, const void* y) { return outputs_of(p) >= kThroughFewest && outputs_of(p) <= planes_most(p, y); }
 inline bool f4_through(const Problem& p, const void* y, int layout) { return layout == WG_NHWC ? rows_through(p, y, 32) : planes_through(p, y); }
 inline bool f2_through(const Problem& p, const void* y) { return rows_through(p, y, 64); }   // channels-last
+// Limb-pair kernel, channel-major outputs, which are not many: few pay as well (plain / through, us, 64 -> 64 at 28x28, N = 4, 7.54 / 7.42, 56x56, N = 8 9.8 / 9.1, 16 -> 16
+// at 16x16 level), but no narrow rows (8x7x7 7.32 / 7.72, 60x14x7 7.60 / 7.96, 14x14 1.01, W = 17 and 18 1.00 - 1.02 of the time).
+inline bool pair_planes_through(const Problem& p, const void* y) { return outputs_of(p) <= planes_most(p, y); }
 // First layers on the matrix cores, channels-last, `bytes` 4 (int32) or 1 (int8): 64 filters of the pixels of a tile's row are stored together, so that
 // up to 64 filters are whole units also where one pixel's are not.  Whole, any number of them pays (224x224, N = 1 .. 16, K = 32 .. 256, 6 - 200 MB
 // 0.83 - 1.01 of the time, int8 0.87 - 1.02); int32 parts up to 20 MB (K = 68 .. 200 0.84 - 0.95, 25 MB 0.95 - 1.11; above, up to 1.4: K = 52 at 223x225, N = 16,

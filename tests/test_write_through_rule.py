@@ -6,7 +6,7 @@ import pytest
 import paper_1901_01965_amd as wg
 from paper_1901_01965_amd import binding
 
-ROWS, PLANES, F2, DIRECT, FIRST, FIRST_INT8, FIRST_POOLED = range(7)
+ROWS, PLANES, F2, DIRECT, FIRST, FIRST_INT8, FIRST_POOLED, PAIR_PLANES = range(8)
 BASE = 1 << 20
 
 
@@ -87,3 +87,11 @@ def test_first_layers_in_parts_are_few(through, kernel, K, W, offset):
     (FIRST_INT8, 128, 225), (FIRST_POOLED, 32, 224), (FIRST_POOLED, 64, 226)])
 def test_first_layers_of_whole_units_are_written_through(through, kernel, K, W):
     assert through(kernel, 1, K, 224, W, 0, 3) and through(kernel, 64, K, 224, W, 0, 3)
+
+
+def test_narrow_channel_major_rows_of_the_limb_pair_kernel_are_left_to_the_l2(through):
+    for W in (7, 13, 14, 15, 17, 19):
+        assert not through(PAIR_PLANES, 4, 64, 14, W)
+    for W in (16, 20, 28, 53, 56):
+        assert through(PAIR_PLANES, 1, 16, 14, W) and through(PAIR_PLANES, 4, 64, 14, W)
+    assert not through(PAIR_PLANES, 4, 64, 14, 16, 16) and through(PAIR_PLANES, 4, 64, 14, 28, 16)
