@@ -1,4 +1,4 @@
-// Which int32 outputs are written through the L2 (write_out, kernel_common.h): rules on their number, their lines and where they lie.  Host only.
+// Which outputs are written through the L2 (write_out, kernel_common.h): rules on their number, their lines and where they lie.  Host only.
 #pragma once
 #include "wg_internal.h"
 
@@ -13,15 +13,18 @@ namespace wg {
 // Channel-major rows of W outputs are whole units where W % 16 = 0, whatever K is (16 -> 256 at most, to 60 MB 0.87 - 1.01), else parts: from 20 outputs on,
 // where they are few (8 MB, W = 20 .. 56 0.91 - 1.03; W = 15 .. 19 up to 1.05; 7x7 1.05), from 28 on up to 16 MB (0.91 - 1.03; W = 20 and 24 up to 1.08), not
 // above (W = 28 .. 75, 28 MB 1.02 - 1.21, 60 MB 1.04 - 1.49: 64 -> 64 at 56x56, N = 62, lossless 37.9 us plain, 45.2 through).
-// Memory takes 64 bytes at a time: outputs that start 16 bytes after a multiple of 64, as a view may, are all written in parts (of the
-// time, plain / through: scaled, lossless, both scaled, F(2x2) and direct, 64 -> 64 at 56x56, N = 64 1.21, 1.15, 1.30, 1.25, 1.29, 128 -> 128, N = 40
-// 1.25, 1.20, 1.35, 1.10, 1.50; channel-major 64 -> 64 at 32x64, N = 61 1.12, 1.16; 64 bytes after one 0.87 - 1.03).
+// Memory takes 64 bytes at a time: outputs that start 16 bytes after a multiple of 64, as a view may, are all written in parts (through, of the
+// time: scaled, lossless, both scaled, F(2x2) and direct, 64 -> 64 at 56x56, N = 64 1.21, 1.15, 1.30, 1.25, 1.29, 128 -> 128, N = 40
+// 1.25, 1.20, 1.35, 1.10, 1.50; channel-major 64 -> 64 at 32x64, N = 61 1.12, 1.16; 64 bytes after one 0.87 - 1.03).  With 32 filters of
+// a pixel at once that does not pay in any number (2 - 8 MB 0.97 - 1.01, 16 MB 0.97 - 1.06), with 64 up to 20 MB (0.88 - 1.00).
 constexpr int kThroughFewest = 512 << 10;   // outputs
 inline long long outputs_of(const Problem& p) { return (long long)p.N * p.H * p.W * p.K; }
 inline bool on_unit(const void* y) { return reinterpret_cast<uintptr_t>(y) % 64 == 0; }
 // Channels-last outputs, `filters` of a pixel stored at once.
 inline bool rows_through(const Problem& p, const void* y, int filters) {
-    const long long most = on_unit(y) && p.K % 32 == 0 ? 16 << 20 : on_unit(y) && p.K % 16 == 0 && 2 * p.K >= filters ? 6 << 20 : filters == 64 ? 5 << 20 : 4 << 20;
+    const bool wide = filters == 64;
+    const long long parts = wide ? 5 << 20 : on_unit(y) ? 4 << 20 : 0;
+    const long long most = !on_unit(y) ? parts : p.K % 32 == 0 ? 16 << 20 : p.K % 16 == 0 && 2 * p.K >= filters ? 6 << 20 : parts;
     return outputs_of(p) >= kThroughFewest && outputs_of(p) <= most;
 }
 // The most channel-major outputs that are written through.
