@@ -1,5 +1,5 @@
-"""Outputs and partial sums that are written through the L2, on either side of the rule (writes_through in wg_internal.h: 512 Ki outputs
-and more, up to 16 Mi, or 6 Mi where K is no multiple of 32; channel-major rows of 16 and more): bit for bit against the oracle."""
+"""Outputs and partial sums that are written through the L2, on either side of the rules (write_through.h): bit for bit against the oracle.
+(tests/test_write_through_rule.py asks the rules themselves.)"""
 import numpy as np
 import pytest
 import torch
@@ -20,32 +20,76 @@ def _nchw(t, layout):
     return wl.from_nhwc(a) if layout == wg.NHWC else a
 
 
+def _calls(gd, layout):
+    """Every call with int32 outputs, and the oracle's answer to it."""
+    lossless, scaled = wg.winograd_filter_transform(gd, layout, wg.LOSSLESS), wg.winograd_filter_transform(gd, layout, wg.SCALED)
+    f2 = wg.f2x2_filter_transform(gd, layout, wg.LOSSLESS)
+    return [(lambda x, out=None: wg.winograd_conv2d_int8(x, lossless, layout, out=out), oracle.direct_conv2d),
+            (lambda x, out=None: wg.direct_conv2d_int8(x, gd, layout, out=out), oracle.direct_conv2d),
+            (lambda x, out=None: wg.f2x2_conv2d_int8(x, f2, layout, out=out), oracle.direct_conv2d),
+            (lambda x, out=None: wg.winograd_conv2d_int8(x, scaled, layout, out=out), lambda x, g: oracle.winograd_conv2d(x, g, oracle.SCALED, 127)[0]),
+            (lambda x, out=None: wg.winograd_conv2d_int8_act_scaled(x, scaled, layout, out=out), lambda x, g: oracle.winograd_conv2d(x, g, oracle.BOTH_SCALED, 127)[0])]
+
+
+def _operands(shape):
+    N, C, K, H, W = shape
+    rng = np.random.default_rng(77)
+    return rng.integers(-128, 128, (N, C, H, W)).astype(np.int8), rng.integers(-128, 128, (K, C, 3, 3)).astype(np.int8)
+
+
 @pytest.mark.parametrize("layout", [wg.NHWC, wg.NCHW])
 @pytest.mark.parametrize("shape", [
     (6, 16, 64, 37, 37),     # 525,696 outputs: just through; partial tiles
     (6, 16, 64, 36, 37),     # 511,488: just not
-    (7, 80, 75, 32, 32),     # lines written in parts, two channel blocks, K odd
-    (9, 48, 68, 49, 21),     # K a multiple of four only
+    (7, 80, 75, 32, 32),     # K odd: channels-last outputs stored one by one; two channel blocks
+    (9, 48, 68, 49, 21),     # channels-last lines in parts, rows of 21
     (42, 16, 64, 14, 14),    # channel-major rows that are too short
     (128, 64, 64, 9, 9),     # more than a round of tile blocks
 ])
 def test_convolutions_equal_the_oracle(shape, layout):
-    N, C, K, H, W = shape
-    rng = np.random.default_rng(77)
-    x, g = rng.integers(-128, 128, (N, C, H, W)).astype(np.int8), rng.integers(-128, 128, (K, C, 3, 3)).astype(np.int8)
+    x, g = _operands(shape)
+    xd, ends, answers = _in(x, layout, wl.to_nhwc), [0, len(x) - 1], {}
+    for call, answer in _calls(_in(g, layout, wl.to_krsc), layout):
+        whole = answer is oracle.direct_conv2d
+        if answer not in answers:
+            answers[answer] = answer(x if whole else x[ends], g)
+        got = call(xd) if whole else call(xd)[ends]
+        assert np.array_equal(_nchw(got, layout), answers[answer])
+
+
+@pytest.mark.parametrize("layout", [wg.NHWC, wg.NCHW])
+@pytest.mark.parametrize("shape", [
+    (13, 16, 100, 56, 56), (14, 16, 100, 56, 56),   # parts of lines, 4.08 and 4.39 million outputs (4 Mi); direct: 160 and 172 pixel blocks
+    (17, 16, 100, 56, 56),                          # 5.33 (5 Mi)
+    (20, 16, 64, 56, 56), (21, 16, 64, 56, 56),     # channel-major rows in parts, 4.01 and 4.21 (4 Mi)
+    (41, 16, 48, 56, 56), (42, 16, 48, 56, 56),     # whole 64-byte units, 6.17 and 6.32 (6 Mi)
+    (20, 16, 64, 112, 112), (21, 16, 64, 112, 112), # whole lines, 16.1 and 16.9 (16 Mi)
+    (32, 64, 84, 32, 32),                           # direct: two filter blocks of one XCD write a line
+])
+def test_many_outputs_equal_the_oracle(shape, layout):
+    x, g = _operands(shape)
+    some = [0, len(x) // 2, len(x) - 1]
+    xd, answers = _in(x, layout, wl.to_nhwc), {}
+    for call, answer in _calls(_in(g, layout, wl.to_krsc), layout):
+        if answer not in answers:
+            answers[answer] = answer(x[some], g)
+        assert np.array_equal(_nchw(call(xd)[some], layout), answers[answer])
+
+
+@pytest.mark.parametrize("layout", [wg.NHWC, wg.NCHW])
+@pytest.mark.parametrize("offset", [4, 16, 64])
+@pytest.mark.parametrize("shape", [(6, 16, 64, 37, 37), (4, 48, 96, 64, 32), (14, 64, 68, 28, 28)])
+def test_outputs_off_a_boundary_are_the_same(shape, offset, layout):
+    x, g = _operands(shape)
     xd, gd = _in(x, layout, wl.to_nhwc), _in(g, layout, wl.to_krsc)
-    want = oracle.direct_conv2d(x, g)
-    ends = [0, N - 1]
-    packed = wg.winograd_filter_transform(gd, layout, wg.LOSSLESS)
-    assert np.array_equal(_nchw(wg.winograd_conv2d_int8(xd, packed, layout), layout), want)
-    assert np.array_equal(_nchw(wg.direct_conv2d_int8(xd, gd, layout), layout), want)
-    assert np.array_equal(_nchw(wg.f2x2_conv2d_int8(xd, wg.f2x2_filter_transform(gd, layout, wg.LOSSLESS), layout), layout), want)
-    scaled = wg.winograd_filter_transform(gd, layout, wg.SCALED)
-    got = _nchw(wg.winograd_conv2d_int8(xd, scaled, layout), layout)
-    assert np.array_equal(got[ends], oracle.winograd_conv2d(x[ends], g, oracle.SCALED, 127)[0])
-    both = _nchw(wg.winograd_conv2d_int8_act_scaled(xd, scaled, layout), layout)
-    alone = [_nchw(wg.winograd_conv2d_int8_act_scaled(_in(x[n:n + 1], layout, wl.to_nhwc), scaled, layout), layout)[0] for n in ends]   # few outputs
-    assert np.array_equal(both[ends], np.stack(alone))
+    for call, _ in _calls(gd, layout):
+        want = call(xd)
+        assert want.data_ptr() % 128 == 0
+        room = torch.full((want.numel() + 64,), 97531, dtype=torch.int32, device="cuda")
+        out = room[offset // 4:offset // 4 + want.numel()].view(want.shape)
+        call(xd, out=out)
+        assert torch.equal(out, want)
+        assert bool((room[:offset // 4] == 97531).all()) and bool((room[offset // 4 + want.numel():] == 97531).all())
 
 
 @pytest.mark.parametrize("mode", [wg.LOSSLESS, wg.SCALED])
