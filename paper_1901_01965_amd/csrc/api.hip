@@ -222,7 +222,7 @@ int winograd_debug_writes_through(int kernel, int N, int C, int H, int W, int K,
         case 0: return f4_through(p, y, WG_NHWC);
         case 1: return f4_through(p, y, WG_NCHW);
         case 2: return f2_through(p, y);
-        case 3: return direct_through(p, y, WG_NHWC);
+        case 3: return direct_through(p, y);
         case 4: return first_layer_through(p, y, 4, false);
         case 5: return first_layer_through(p, y, 1, false);
         case 6: return first_layer_through(p, y, 1, true);

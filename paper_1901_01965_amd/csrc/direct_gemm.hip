@@ -297,18 +297,20 @@ hipError_t launch_form(int form, const int8_t* x, const int8_t* w, int32_t* y, c
 // Two filter blocks that write a line together (K % 32 != 0, or outputs off a line) must not do so from the same XCD at the same time: workgroups go
 // to the eight XCDs in turn, so they do where the pixel blocks are a multiple of eight (us, plain / through: 64 -> 84 at 32x32, N = 16, 5.2 / 8.5,
 // N = 32 7.0 / 13.1; at 56x56, N = 13, 160 pixel blocks, 8.3 / 12.5, N = 12 and 14, 147 and 172, 8.6 / 7.8 and 9.1 / 8.4; 64 -> 80, N = 15 8.4 / 9.7).
-bool direct_through(const Problem& p, const int32_t* y, int layout) {
-    const int form = choose_form(p);
-    if (layout != WG_NHWC || form < 0 || !rows_through(p, y, 64)) return false;
+static bool through(const Problem& p, const int32_t* y, const Form& f) {
     const bool whole_lines = p.K % 32 == 0 && reinterpret_cast<uintptr_t>(y) % 128 == 0;
-    return whole_lines || p.K <= kForms[form].F || ((long long)p.N * p.H * p.W + kForms[form].P - 1) / kForms[form].P % 8 != 0;
+    return rows_through(p, y, 64) && (whole_lines || p.K <= f.F || ((long long)p.N * p.H * p.W + f.P - 1) / f.P % 8 != 0);
+}
+bool direct_through(const Problem& p, const int32_t* y) {
+    const int form = choose_form(p);
+    return form >= 0 && through(p, y, kForms[form]);
 }
 bool direct_gemm_applies(const Problem& p) { return choose_form(p) >= 0; }
 
 hipError_t launch_direct_gemm(const int8_t* x, const int8_t* w, int32_t* y, const Problem& p, int layout, hipStream_t s) {
     const int form = choose_form(p);
     if (layout != WG_NHWC) return launch_form<WG_NCHW, false>(form, x, w, y, p, s);
-    return direct_through(p, y, layout) ? launch_form<WG_NHWC, true>(form, x, w, y, p, s) : launch_form<WG_NHWC, false>(form, x, w, y, p, s);
+    return through(p, y, kForms[form]) ? launch_form<WG_NHWC, true>(form, x, w, y, p, s) : launch_form<WG_NHWC, false>(form, x, w, y, p, s);
 }
 
 }  // namespace wg

@@ -99,13 +99,13 @@ __device__ inline uint32_t pack_bytes(v4i v) {
     return __builtin_amdgcn_perm((uint32_t)v[1], (uint32_t)v[0], 0x0c0c0400u) | __builtin_amdgcn_perm((uint32_t)v[3], (uint32_t)v[2], 0x04000c0cu);
 }
 // An output, or a sum for the next kernel, written through the L2 (device scope).  Left in the L2s, what a kernel wrote is written back when it
-// ends, and a kernel of one round or two, whose compute units all store at the end, waits for that; written through, it is under way as
-// soon as it is stored.  us, plain / through: 128 -> 128 at 28x28, N = 32, scaled 12.7 / 11.8 (with the requantisation that reads it 19.3 / 19.0),
-// 64 -> 64 at 56x56, N = 32 16.7 / 14.8, direct 256 -> 256 at 56x56, N = 16 33.8 / 31.5 (42.5 / 41.4), F(2x2) at 28x28 15.4 / 13.8; partial sums of
-// 512 -> 512 at 14x14, N = 1, scaled, both kernels 15.2 / 13.3.  (Non-temporal stores: as fast by themselves, but what reads the outputs
-// next is slower by as much or more, direct 256 -> 256 43.9.)  Which outputs: write_through.h.  int8 outputs, a fourth of the
-// bytes in parts of lines, gain in the limb-pair kernel (64 -> 64 at 56x56, N = 8 7.3 / 6.9) and first layers (N = 16 at 224x224 38.6 / 35.9), and are
-// level or behind elsewhere (0.98 - 1.03); so are the requantisation's (1.00 - 1.03) and channels-last copies (1.02 - 1.10).
+// ends (128 -> 128 at 28x28, N = 32: all of its 100,352 lines, written through none), and its end waits for that; written through, it is under way as
+// soon as it is stored.  us, plain / through, outputs in rotation: that layer, scaled, 13.3 / 12.2 (with the requantisation that reads it 16.8 / 16.0),
+// F(2x2) 15.5 / 14.6; 64 -> 64 at 56x56, N = 32, scaled 17.2 / 15.3, N = 8, direct 5.4 / 4.9; both scaled 256 -> 256 at 14x14, N = 64 26.4 / 23.9; partial
+// sums of 512 -> 512 at 14x14, N = 1, scaled, both kernels 15.2 / 13.5.  (Non-temporal stores: as fast by themselves, but what reads the outputs
+// next is slower by as much or more.)  Which outputs: write_through.h.  int8 outputs, a fourth of the bytes in parts of lines, gain in the limb-pair
+// kernel (64 -> 64 at 56x56, N = 8 7.9 / 7.6) and first layers (3 -> 64 at 224x224, N = 16 39.7 / 37.4), and are level or behind elsewhere (0.98 - 1.03); so
+// are the requantisation's (1.00 - 1.03) and channels-last copies (1.02 - 1.10).
 // The compiler's own stores, not assembly: it keeps what overwrites a 16-byte store's data two wait states behind it (gfx950), which it does not
 // do for a store that it cannot see.
 template <class T>

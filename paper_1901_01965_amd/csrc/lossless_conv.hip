@@ -625,7 +625,7 @@ __device__ __forceinline__ void lossless_pair(const int8_t* __restrict__ x, cons
         // requantisation and clamp, then (a 4x4 tile holds whole 2x2 windows) the pooling maximum
         const bool word_store = (p.K & 3) == 0 && (reinterpret_cast<uintptr_t>(q8.out) & 3) == 0;
         auto put_bytes = [&](int8_t* at, v4i q) {
-            if (word_store) {
+            if (word_store) {   // (always through: whole words of no more than two rounds of workgroups, 4 MB)
                 write_out(reinterpret_cast<uint32_t*>(at), pack_bytes(q));
             } else {
 #pragma unroll
@@ -833,7 +833,7 @@ bool in_quarters(const Problem& p, int splits) {
     return (long long)ceil_div(p.T, kTileBlock) * ceil_div(p.K, Stage<4>::kFilters) * splits <= compute_units();
 }
 // The splits' sums, which the next kernel reads from every XCD, are written through the L2 (write_out) where they are not few: 512 -> 512 at 14x14,
-// N = 1 (4 and 9 MB), both kernels, scaled 15.2 us, through 13.3, lossless 10.4, 10.2; 128 -> 64 at 14x14, N = 2 (0.3 MB) 9.1, 9.4.
+// N = 1 (4 and 9 MB), both kernels, scaled 15.2 us, through 13.5, lossless level; 128 -> 64 at 14x14, N = 2 (0.3 MB) 9.1, 9.4.
 inline bool sums_through(const Problem& p, int mode, int splits) { return split_partial_bytes(p, mode, splits) >= sizeof(int32_t) * kThroughFewest; }
 inline SplitGrid split_grid(const Problem& p, int blocks, int splits, int mode, int filters = kBlockFilters) {
     const int tile_blocks = ceil_div(p.T, kTileBlock);

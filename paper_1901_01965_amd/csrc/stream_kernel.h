@@ -63,7 +63,7 @@ struct RoleBarrier {
 //                   limb-pair operand (pair_products.h), whose outputs take half the registers: enough with twelve waves.  Half the chain per
 //                   tile block of kStreamWhole, no halves to add, and all eight waves store: ahead where a workgroup has few tile
 //                   blocks, so that this chain is not hidden behind others (see fused_conv.hip).  In a long stream twice as many waves read the
-//                   activation planes (576 KB a tile block), and with the transform left out the products alone take 5.1 of 7.4 us a tile block:
+//                   activation planes (576 KB a tile block), and with the transform left out the products alone take 5.1 of a tile block's 7.3 us (kStreamWhole):
 //                   56x56x64 N = 256 102 us, int8 out 84, with kStreamWhole 94.5 and 80; with the stores left to the transform
 //                   waves 98 and 81, and nothing gained in short ones.
 // What bounds kStreamWhole (56x56x64, N = 256, clocks per tile block of 64 filters, lossless / scaled): the product wave's chain,
@@ -419,8 +419,8 @@ hipError_t launch_stream_mode(const RolesCall& c, StreamForm which, hipStream_t 
             if constexpr (Q8) {
                 return launch_stream<L, MODE, kOutInt8, FORM>(c, enc, s);
             } else {
-                // in a longer stream the stores are spread over it already (64 -> 64 at 56x56, four tile blocks per workgroup, N = 64, scaled 27.0 us,
-                // through 24.8; seven and thirteen level, channel-major thirteen 119 and 149)
+                // in a longer stream the stores are spread over it already (64 -> 64 at 56x56, four tile blocks per workgroup, N = 64, scaled 29.2 us,
+                // through 27.0; seven and thirteen level)
                 const int tile_blocks = ceil_div(c.p.T, kFusedTiles);
                 const bool few = FORM == kStreamEight || tile_blocks <= 4 * stream_workgroups(tile_blocks, ceil_div(c.p.K, stream_filters<FORM>()));
                 return few && f4_through(c.p, c.y, c.layout) ? launch_stream<L, MODE, kOutThrough, FORM>(c, enc, s)

@@ -12,7 +12,7 @@ namespace wg {
 // 24 MB 0.93 - 1.13 (K % 16 = 0 0.90 - 1.03, F(2x2) with K = 16 1.05).
 // Channel-major rows of W outputs are whole units where W % 16 = 0, whatever K is (16 -> 256 at most, to 60 MB 0.87 - 1.01), else parts: from 20 outputs on,
 // where they are few (8 MB, W = 20 .. 56 0.91 - 1.03; W = 15 .. 19 up to 1.05; 7x7 1.05), from 28 on up to 16 MB (0.91 - 1.03; W = 20 and 24 up to 1.08), not
-// above (W = 28 .. 75, 28 MB 1.02 - 1.21, 60 MB 1.04 - 1.49: 64 -> 64 at 56x56, N = 62, lossless 37.9 us plain, 45.2 through).
+// above (W = 28 .. 75, 28 MB 1.02 - 1.21, 60 MB 1.04 - 1.49: 64 -> 64 at 56x56, N = 62, lossless 45.3 us plain, 54.0 through).
 // Memory takes 64 bytes at a time: outputs that start 16 bytes after a multiple of 64, as a view may, are all written in parts (through, of the
 // time: scaled, lossless, both scaled, F(2x2) and direct, 64 -> 64 at 56x56, N = 64 1.21, 1.15, 1.30, 1.25, 1.29, 128 -> 128, N = 40
 // 1.25, 1.20, 1.35, 1.10, 1.50; channel-major 64 -> 64 at 32x64, N = 61 1.12, 1.16; 64 bytes after one 0.87 - 1.03).  With 32 filters of
@@ -47,6 +47,6 @@ inline bool first_layer_through(const Problem& p, const void* out, int bytes, bo
     const bool whole = p.K * bytes % 64 == 0 || (p.K <= 64 && p.W % 4 == 0 && row % 64 == 0);
     return (whole && on_unit(out)) || outputs <= (bytes == 4 ? 5 << 20 : 32 << 20);
 }
-bool direct_through(const Problem& p, const int32_t* y, int layout);   // direct_gemm.hip
+bool direct_through(const Problem& p, const int32_t* y);   // channels-last (direct_gemm.hip)
 
 }  // namespace wg
